@@ -144,7 +144,8 @@ int lora_cache_fill_slot(lora_cache_t *c, int32_t slot, int64_t adapter_id, int3
  * One wait for earlier applies, one event, and -- with LORA_CACHE_DIRECT_FILL and pinned, 16-byte
  * aligned host arrays -- one kernel per 32 parts instead of one per part: the host side of loading an
  * adapter then costs about as much as one part did.  Otherwise the parts go through the staging
- * buffers one after the other as lora_cache_fill_slot sends them.  Errors as lora_cache_fill_slot;
+ * buffers, a buffer full of parts at a time: one kernel per buffer, and one copy for all arrays that follow each other
+ * in one pinned allocation (an adapter kept back to back travels at the rate of the link).  Errors as lora_cache_fill_slot;
  * on an error no part of the call is enqueued. */
 typedef struct {
     int32_t layer, proj;

@@ -10,10 +10,10 @@ namespace lora {
 
 constexpr int REPACK_HOST_BLOCKS = 32;
 
-// One launch per part; the grid walks over the part's work units: units [0, h_in/64) transpose
-// A, the rest pack B.  A fill runs beside the applies and slows them down for as long as its
-// kernel is running, so from device memory (a staging buffer) the launch is one block per unit
-// and over in a few microseconds; from host memory a few dozen blocks already keep more bytes in
+// One launch for the parts that lie ready (up to 32, or one staging buffer full of them); the grid walks over their
+// work units: of a part, units [0, h_in/64) transpose A, the rest pack B.  A fill runs beside the applies and slows
+// them down for as long as its kernel is running, so from device memory (a staging buffer) the launch is one block
+// per unit and over in about 10 microseconds; from host memory a few dozen blocks already keep more bytes in
 // flight than the link needs and more would only hold wavefront slots.  The source may be
 // device memory (a staging buffer) or pinned host memory read over PCIe, so it is read exactly
 // once, in 16-byte pieces of contiguous runs, with every load of a thread issued before the
@@ -105,16 +105,6 @@ __device__ __forceinline__ void repack_unit(const E *__restrict__ A, const E *__
     }
 }
 
-template <typename E>
-__global__ __launch_bounds__(256) void repack_kernel(const E *__restrict__ A, const E *__restrict__ B, E *__restrict__ At,
-                                                     E *__restrict__ Bp, int h_in, int h_out, int r, int rs, int n_a_blocks)
-{
-    __shared__ E tile[64 * REPACK_TROW];
-    const int n_units = n_a_blocks + (rs / 8) * ((h_out + 256 * 8 - 1) / (256 * 8));
-    for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x)  // uniform over the block
-        repack_unit<E>(A, B, At, Bp, h_in, h_out, r, rs, n_a_blocks, unit, tile);
-}
-
 // Several parts of one adapter (same rank) in one launch: the blocks walk over the units of all parts.
 template <typename E>
 __global__ __launch_bounds__(256) void repack_parts_kernel(RepackTable t)
@@ -132,26 +122,6 @@ __global__ __launch_bounds__(256) void repack_parts_kernel(RepackTable t)
     }
 }
 
-template <typename E>
-static hipError_t repack_t(const void *sa, const void *sb, void *slab, int h_in, int h_out, int r, bool from_host, hipStream_t st)
-{
-    const int rs = rank_storage(r);
-    E *At = static_cast<E *>(slab);
-    E *Bp = At + (size_t)rs * h_in;
-    const int n_a = h_in / 64, n_b = (rs / 8) * ((h_out + 2047) / 2048);
-    hipLaunchKernelGGL((repack_kernel<E>), dim3(from_host ? std::min(n_a + n_b, REPACK_HOST_BLOCKS) : n_a + n_b), dim3(256), 0, st, static_cast<const E *>(sa),
-                       static_cast<const E *>(sb), At, Bp, h_in, h_out, r, rs, n_a);
-    return hipGetLastError();
-}
-
-// Sources must be 16-byte aligned (device staging buffers and pinned allocations are).
-hipError_t launch_repack(int dtype, const void *src_A, const void *src_B, void *slab, int32_t h_in, int32_t h_out,
-                         int32_t rank, bool from_host, hipStream_t st)
-{
-    if (dtype == LORA_BF16) return repack_t<__bf16>(src_A, src_B, slab, h_in, h_out, rank, from_host, st);
-    return repack_t<float>(src_A, src_B, slab, h_in, h_out, rank, from_host, st);
-}
-
 // Parts of one adapter of rank `rank`: sources A, B and destination slab per part, all 16-byte aligned;
 // unit_end is filled in here.  from_host as above.
 hipError_t launch_repack_parts(int dtype, RepackTable &t, int32_t rank, bool from_host, hipStream_t st)
@@ -164,7 +134,7 @@ hipError_t launch_repack_parts(int dtype, RepackTable &t, int32_t rank, bool fro
         total += t.p[i].h_in / 64 + (t.rs / 8) * ((t.p[i].h_out + 2047) / 2048);
         t.p[i].unit_end = total;
     }
-    const dim3 grid(from_host ? std::min(total, 2 * REPACK_HOST_BLOCKS) : total);
+    const dim3 grid(from_host ? std::min(total, (t.n > 1 ? 2 : 1) * REPACK_HOST_BLOCKS) : total);
     if (dtype == LORA_BF16) hipLaunchKernelGGL((repack_parts_kernel<__bf16>), grid, dim3(256), 0, st, t);
     else hipLaunchKernelGGL((repack_parts_kernel<float>), grid, dim3(256), 0, st, t);
     return hipGetLastError();

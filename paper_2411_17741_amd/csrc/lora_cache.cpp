@@ -25,6 +25,9 @@ thread_local int g_last_hip = 0;
 
 constexpr int N_INTERNAL_PLANS = 4;
 constexpr int N_STAGES = 2;
+// One staging buffer of a fill.  The link moves 16 MB in 0.3 ms; the repack launch behind them (about 15 us with its
+// waits on both sides) is then a twentieth of that.
+constexpr size_t STAGE_BYTES = (size_t)16 << 20;
 constexpr int N_APPLY_EVENTS = 64;
 constexpr size_t ALIGN = 256;
 // Tile shrink: at most this many runs per launch (two resident blocks per compute unit of a 256-unit part), and
@@ -270,11 +273,12 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
         }
     c.proj_off.assign(n_proj, 0);
     c.row_bytes.assign(n_proj, 0);
-    size_t off = 0, max_part = 0;
+    size_t off = 0, max_part = 0, row_sum = 0;
     for (int p = 0; p < n_proj; ++p) {
         const size_t width = (size_t)c.proj[p].h_in + (size_t)c.proj[p].h_out;
         c.proj_off[p] = off;
         c.row_bytes[p] = width * c.esize;  // a multiple of 256 bytes: h_in, h_out are multiples of 64
+        row_sum += c.row_bytes[p];
         off += (size_t)c.total_rows * c.row_bytes[p];
         max_part = std::max(max_part, (size_t)c.class_rank[n_cls - 1] * width * c.esize);
     }
@@ -290,7 +294,8 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
                  align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
                  align_up(sizeof(lora_item_t) * (max_tiles + (size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
                  SHRINK_VARIANTS * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
-    c.stage_cap = align_up(max_part) + ALIGN;
+    // fill staging: a buffer takes parts of an adapter until STAGE_BYTES (or the largest adapter) are in it
+    c.stage_cap = align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
 
     size_t cur = align_up(c.layer_stride * (size_t)c.n_layers);
     c.off_fault = cur;  // (once the fault word; now the flags of the fused linear kernel's split tiles)
@@ -976,24 +981,136 @@ static const void *device_view_of_pinned(const void *host)
     return at.type == hipMemoryTypeHost ? at.devicePointer : nullptr;
 }
 
+// End of the pinned host allocation that `host` lies in, or null for any other kind of pointer.
+static const char *pinned_end(const void *host)
+{
+    const void *dev = device_view_of_pinned(host);
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (!dev) return nullptr;
+    if (hipMemGetAddressRange(&base, &size, const_cast<void *>(dev)) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return static_cast<const char *>(host) + (static_cast<const char *>(base) + size - static_cast<const char *>(dev));
+}
+
 int lora_cache_fill_slot(lora_cache_t *c, int32_t slot, int64_t adapter_id, int32_t rank, float alpha, int32_t layer,
                          int32_t proj, const void *host_A, const void *host_B, void *fill_stream)
 {
-    if (!c || slot < 0 || slot >= c->n_slots || layer < 0 || layer >= c->n_layers || proj < 0 ||
-        proj >= (int32_t)c->proj.size() || rank < 1)
-        return LORA_E_INVAL;
+    const lora_fill_part_t part{layer, proj, host_A, host_B};
+    return lora_cache_fill_slot_parts(c, slot, adapter_id, rank, alpha, &part, 1, fill_stream);
+}
+
+// Copies parts [0, n) of an adapter into the slot's slabs by way of the staging buffers: as many parts as fit go into
+// a buffer back to back (a part's arrays are multiples of 128 bytes), and one kernel repacks them all.  Arrays that
+// follow each other in one pinned allocation travel as one copy: a copy has a fixed cost of several us on the engine,
+// and an adapter of rank 16 is 256 copies of 128 KB (five adapters of ranks 8 to 128 on 128 parts each, 520 MB: 31.7 ms
+// with two copies, a kernel and two events per part; copies of whole buffers: 10.2 ms, the link's rate is 9.1 ms).
+static int fill_staged(lora_cache *c, int32_t slot, int32_t rank, const lora_fill_part_t *parts, int32_t n, hipStream_t st)
+{
+    auto bytes_of = [&](const lora_fill_part_t &q, size_t &a, size_t &b) {
+        a = (size_t)rank * c->proj[q.proj].h_in * c->esize;
+        b = (size_t)rank * c->proj[q.proj].h_out * c->esize;
+    };
+    std::vector<int32_t> in_buffer(c->proj.size() * (size_t)c->n_layers, -1);  // per part: the buffer that holds it
+    for (int32_t i = 0, buffer = 0; i < n; ++buffer) {
+        Stage &sg = c->stage[c->stage_next++ % N_STAGES];
+        if (sg.pending) HIP_TRY(hipStreamWaitEvent(st, sg.ev, 0));
+        lora::RepackTable t;
+        t.n = 0;
+        size_t used = 0;
+        // the run of host bytes that is not enqueued yet, where it goes, and the end of the allocation it lies in
+        const char *run = nullptr, *run_end = nullptr, *alloc_end = nullptr;
+        char *to = nullptr;
+        auto flush = [&]() -> hipError_t {
+            if (!run) return hipSuccess;
+            const hipError_t e = hipMemcpyAsync(to, run, (size_t)(run_end - run), hipMemcpyHostToDevice, st);
+            run = nullptr;
+            return e;
+        };
+        auto add = [&](const void *host, size_t bytes) -> hipError_t {
+            const char *h = static_cast<const char *>(host);
+            if (run && h == run_end && h + bytes <= alloc_end) {
+                run_end = h + bytes;
+            } else {
+                const hipError_t e = flush();
+                if (e != hipSuccess) return e;
+                run = h;
+                run_end = h + bytes;
+                to = sg.dev + used;
+                alloc_end = pinned_end(h);
+            }
+            used += bytes;
+            return hipSuccess;
+        };
+        for (; i < n && t.n < lora::REPACK_MAX_PARTS; ++i) {
+            size_t bytes_a, bytes_b;
+            bytes_of(parts[i], bytes_a, bytes_b);
+            if (used + bytes_a + bytes_b > c->stage_cap) break;  // (a buffer holds the largest part)
+            int32_t &seen = in_buffer[(size_t)parts[i].layer * c->proj.size() + parts[i].proj];
+            if (seen == buffer) break;  // the part once more: the later one counts, and a launch's blocks run in no order
+            seen = buffer;
+            lora::RepackPart &q = t.p[t.n++];
+            q.A = sg.dev + used;
+            q.B = sg.dev + used + bytes_a;
+            q.slab = slab_ptr(*c, parts[i].layer, parts[i].proj, slot);
+            q.h_in = c->proj[parts[i].proj].h_in;
+            q.h_out = c->proj[parts[i].proj].h_out;
+            HIP_TRY(add(parts[i].host_A, bytes_a));
+            HIP_TRY(add(parts[i].host_B, bytes_b));
+        }
+        HIP_TRY(flush());
+        HIP_TRY(lora::launch_repack_parts(c->dtype, t, rank, false, st));
+        HIP_TRY(hipEventRecord(sg.ev, st));
+        sg.pending = true;
+    }
+    return LORA_OK;
+}
+
+// The same without staging: pinned host memory is mapped into the device's address space, the repack kernel reads it over
+// PCIe itself (fastest for a fill that has the device to itself; kernels that wait on PCIe reads slow concurrent applies
+// down far more than copy engines do).  dev_view: the parts' A and B as the device sees them.
+static int fill_direct(lora_cache *c, int32_t slot, int32_t rank, const lora_fill_part_t *parts, int32_t n,
+                       const std::vector<const void *> &dev_view, hipStream_t st)
+{
+    for (int32_t i0 = 0; i0 < n; i0 += lora::REPACK_MAX_PARTS) {
+        lora::RepackTable t;
+        t.n = std::min<int32_t>(lora::REPACK_MAX_PARTS, n - i0);
+        for (int32_t i = 0; i < t.n; ++i) {
+            const lora_fill_part_t &q = parts[i0 + i];
+            t.p[i].A = dev_view[2 * (size_t)(i0 + i)];
+            t.p[i].B = dev_view[2 * (size_t)(i0 + i) + 1];
+            t.p[i].slab = slab_ptr(*c, q.layer, q.proj, slot);
+            t.p[i].h_in = c->proj[q.proj].h_in;
+            t.p[i].h_out = c->proj[q.proj].h_out;
+        }
+        HIP_TRY(lora::launch_repack_parts(c->dtype, t, rank, true, st));
+    }
+    return LORA_OK;
+}
+
+int lora_cache_fill_slot_parts(lora_cache_t *c, int32_t slot, int64_t adapter_id, int32_t rank, float alpha,
+                               const lora_fill_part_t *parts, int32_t n_parts, void *fill_stream)
+{
+    if (!c || slot < 0 || slot >= c->n_slots || rank < 1 || n_parts < 0 || (n_parts > 0 && !parts)) return LORA_E_INVAL;
     Slot &s = c->slots[slot];
     if (rank > c->class_rank[s.cls]) return LORA_E_INVAL;
-    if (!c->host_only && (!host_A || !host_B)) return LORA_E_INVAL;
-    const size_t part = (size_t)layer * c->proj.size() + proj;
-
+    for (int32_t i = 0; i < n_parts; ++i) {
+        const lora_fill_part_t &q = parts[i];
+        if (q.layer < 0 || q.layer >= c->n_layers || q.proj < 0 || q.proj >= (int32_t)c->proj.size()) return LORA_E_INVAL;
+        if (!c->host_only && (!q.host_A || !q.host_B)) return LORA_E_INVAL;
+    }
     const bool was_bound = s.bound;
     if (s.bound) {
         if (s.adapter_id != adapter_id || s.rank != rank || s.alpha != alpha) return LORA_E_STATE;
-        if (s.part[part] && s.refcount > 0) return LORA_E_STATE;  // would overwrite data in use
-    } else {
-        auto other = c->id2slot.find(adapter_id);
-        if (other != c->id2slot.end()) return LORA_E_STATE;  // the adapter is already cached elsewhere
+        for (int32_t i = 0; i < n_parts; ++i)  // would overwrite data in use
+            if (s.part[(size_t)parts[i].layer * c->proj.size() + parts[i].proj] && s.refcount > 0) return LORA_E_STATE;
+    } else if (c->id2slot.find(adapter_id) != c->id2slot.end()) {
+        return LORA_E_STATE;  // the adapter is already cached elsewhere
+    }
+    if (n_parts == 0) return LORA_OK;
+    if (!s.bound) {
         s.bound = true;
         s.adapter_id = adapter_id;
         s.rank = rank;
@@ -1002,9 +1119,6 @@ int lora_cache_fill_slot(lora_cache_t *c, int32_t slot, int64_t adapter_id, int3
         ++s.generation;
         c->id2slot[adapter_id] = slot;
     }
-
-    const int32_t h_in = c->proj[proj].h_in, h_out = c->proj[proj].h_out;
-    const size_t bytes_a = (size_t)rank * h_in * c->esize, bytes_b = (size_t)rank * h_out * c->esize;
     if (!c->host_only) {
         hipStream_t st = static_cast<hipStream_t>(fill_stream);
         // a HIP failure below must not leave a bound, empty entry behind
@@ -1017,123 +1131,30 @@ int lora_cache_fill_slot(lora_cache_t *c, int32_t slot, int64_t adapter_id, int3
                 if (armed) unbind(*c, *s);
             }
         } rollback{c, &s, !was_bound};
-        // applies enqueued earlier may still read this slab; an earlier fill of the slot (of the entry it
-        // held before, or of the same part) may still be writing it on another stream
+        // pinned host arrays as the device sees them (all parts, or the call takes the staged way)
+        bool direct = c->direct_fill;
+        std::vector<const void *> dev_view;
+        if (direct) {
+            dev_view.resize(2 * (size_t)n_parts);
+            for (int32_t i = 0; i < n_parts && direct; ++i) {
+                dev_view[2 * i] = device_view_of_pinned(parts[i].host_A);
+                dev_view[2 * i + 1] = device_view_of_pinned(parts[i].host_B);
+                if (!dev_view[2 * i] || !dev_view[2 * i + 1] ||
+                    ((reinterpret_cast<uintptr_t>(dev_view[2 * i]) | reinterpret_cast<uintptr_t>(dev_view[2 * i + 1])) & 15))
+                    direct = false;
+            }
+        }
+        // applies enqueued earlier may still read this slot; an earlier fill of it (of the entry it held before, or of
+        // the same part) may still be writing it on another stream
         if (int rc = wait_for_applies(*c, s, st)) return rc;
         if (s.fill_pending) HIP_TRY(hipStreamWaitEvent(st, s.fill_ev, 0));
-        char *slab = slab_ptr(*c, layer, proj, slot);
-        const void *dev_A = c->direct_fill ? device_view_of_pinned(host_A) : nullptr;
-        const void *dev_B = c->direct_fill ? device_view_of_pinned(host_B) : nullptr;
-        if (dev_A && dev_B && ((reinterpret_cast<uintptr_t>(dev_A) | reinterpret_cast<uintptr_t>(dev_B)) & 15) == 0) {
-            // pinned host memory is mapped into the device's address space: the repack kernel reads
-            // it over PCIe itself (fastest for a fill that has the device to itself; kernels that
-            // wait on PCIe reads slow concurrent applies down far more than copy engines do)
-            HIP_TRY(lora::launch_repack(c->dtype, dev_A, dev_B, slab, h_in, h_out, rank, true, st));
-        } else {
-            // copy engine -> staging buffer -> repack, all on the caller's stream.  (Copies on a
-            // stream of the cache's own, to overlap them with the repack of the part before, made
-            // every call block on the host for ~300 us with this runtime.)
-            Stage &sg = c->stage[c->stage_next++ % N_STAGES];
-            if (sg.pending) HIP_TRY(hipStreamWaitEvent(st, sg.ev, 0));
-            char *stage_b = sg.dev + align_up(bytes_a);
-            HIP_TRY(hipMemcpyAsync(sg.dev, host_A, bytes_a, hipMemcpyHostToDevice, st));
-            HIP_TRY(hipMemcpyAsync(stage_b, host_B, bytes_b, hipMemcpyHostToDevice, st));
-            HIP_TRY(lora::launch_repack(c->dtype, sg.dev, stage_b, slab, h_in, h_out, rank, false, st));
-            HIP_TRY(hipEventRecord(sg.ev, st));
-            sg.pending = true;
-        }
+        if (const int rc = direct ? fill_direct(c, slot, rank, parts, n_parts, dev_view, st) : fill_staged(c, slot, rank, parts, n_parts, st))
+            return rc;
         if (!s.fill_ev) HIP_TRY(hipEventCreateWithFlags(&s.fill_ev, hipEventDisableTiming));
         HIP_TRY(hipEventRecord(s.fill_ev, st));
         s.fill_pending = true;
         rollback.armed = false;
     }
-    if (!s.part[part]) {
-        s.part[part] = 1;
-        ++s.parts_filled;
-    }
-    ++c->stats.fills;
-    c->stats.bytes_filled += (int64_t)(bytes_a + bytes_b);
-    return LORA_OK;
-}
-
-int lora_cache_fill_slot_parts(lora_cache_t *c, int32_t slot, int64_t adapter_id, int32_t rank, float alpha,
-                               const lora_fill_part_t *parts, int32_t n_parts, void *fill_stream)
-{
-    if (!c || slot < 0 || slot >= c->n_slots || rank < 1 || n_parts < 0 || (n_parts > 0 && !parts)) return LORA_E_INVAL;
-    Slot &s = c->slots[slot];
-    if (rank > c->class_rank[s.cls]) return LORA_E_INVAL;
-    bool direct = c->direct_fill && !c->host_only;
-    for (int32_t i = 0; i < n_parts; ++i) {
-        const lora_fill_part_t &q = parts[i];
-        if (q.layer < 0 || q.layer >= c->n_layers || q.proj < 0 || q.proj >= (int32_t)c->proj.size()) return LORA_E_INVAL;
-        if (!c->host_only && (!q.host_A || !q.host_B)) return LORA_E_INVAL;
-        if (s.bound && s.part[(size_t)q.layer * c->proj.size() + q.proj] && s.refcount > 0) return LORA_E_STATE;
-    }
-    if (s.bound) {
-        if (s.adapter_id != adapter_id || s.rank != rank || s.alpha != alpha) return LORA_E_STATE;
-    } else if (c->id2slot.find(adapter_id) != c->id2slot.end()) {
-        return LORA_E_STATE;
-    }
-    if (n_parts == 0) return LORA_OK;
-    // pinned host arrays as the device sees them (all parts, or the call takes the staged way)
-    std::vector<const void *> dev_view;
-    if (direct) {
-        dev_view.resize(2 * (size_t)n_parts);
-        for (int32_t i = 0; i < n_parts && direct; ++i) {
-            dev_view[2 * i] = device_view_of_pinned(parts[i].host_A);
-            dev_view[2 * i + 1] = device_view_of_pinned(parts[i].host_B);
-            if (!dev_view[2 * i] || !dev_view[2 * i + 1] ||
-                ((reinterpret_cast<uintptr_t>(dev_view[2 * i]) | reinterpret_cast<uintptr_t>(dev_view[2 * i + 1])) & 15))
-                direct = false;
-        }
-    }
-    if (!direct) {
-        for (int32_t i = 0; i < n_parts; ++i) {
-            const int rc = lora_cache_fill_slot(c, slot, adapter_id, rank, alpha, parts[i].layer, parts[i].proj, parts[i].host_A,
-                                                parts[i].host_B, fill_stream);
-            if (rc != LORA_OK) return rc;
-        }
-        return LORA_OK;
-    }
-    const bool was_bound = s.bound;
-    if (!s.bound) {
-        s.bound = true;
-        s.adapter_id = adapter_id;
-        s.rank = rank;
-        s.alpha = alpha;
-        s.use_count = 0;
-        ++s.generation;
-        c->id2slot[adapter_id] = slot;
-    }
-    hipStream_t st = static_cast<hipStream_t>(fill_stream);
-    struct Rollback {
-        lora_cache *c;
-        Slot *s;
-        bool armed;
-        ~Rollback()
-        {
-            if (armed) unbind(*c, *s);
-        }
-    } rollback{c, &s, !was_bound};
-    if (int rc = wait_for_applies(*c, s, st)) return rc;
-    if (s.fill_pending) HIP_TRY(hipStreamWaitEvent(st, s.fill_ev, 0));
-    for (int32_t i0 = 0; i0 < n_parts; i0 += lora::REPACK_MAX_PARTS) {
-        lora::RepackTable t;
-        t.n = std::min<int32_t>(lora::REPACK_MAX_PARTS, n_parts - i0);
-        for (int32_t i = 0; i < t.n; ++i) {
-            const lora_fill_part_t &q = parts[i0 + i];
-            t.p[i].A = dev_view[2 * (size_t)(i0 + i)];
-            t.p[i].B = dev_view[2 * (size_t)(i0 + i) + 1];
-            t.p[i].slab = slab_ptr(*c, q.layer, q.proj, slot);
-            t.p[i].h_in = c->proj[q.proj].h_in;
-            t.p[i].h_out = c->proj[q.proj].h_out;
-        }
-        HIP_TRY(lora::launch_repack_parts(c->dtype, t, rank, true, st));
-    }
-    if (!s.fill_ev) HIP_TRY(hipEventCreateWithFlags(&s.fill_ev, hipEventDisableTiming));
-    HIP_TRY(hipEventRecord(s.fill_ev, st));
-    s.fill_pending = true;
-    rollback.armed = false;
     for (int32_t i = 0; i < n_parts; ++i) {
         const lora_fill_part_t &q = parts[i];
         const size_t part = (size_t)q.layer * c->proj.size() + q.proj;

@@ -260,11 +260,8 @@ size_t linear_split_bytes(int n_rt, int h_in, int h_out, int n_cu);
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
                                size_t split_scratch_bytes, uint32_t *split_flags, int n_split_flags, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm);
-// A [h_in][r] / B [r][h_out] (16-byte aligned; device memory, or pinned host memory as the device
-// sees it: from_host) -> slab layout
-hipError_t launch_repack(int dtype, const void *src_A, const void *src_B, void *slab, int32_t h_in, int32_t h_out,
-                         int32_t rank, bool from_host, hipStream_t st);
-// the same for up to REPACK_MAX_PARTS parts of one adapter in one launch (unit_end, r, rs are set by the launcher)
+// A [h_in][r] / B [r][h_out] (16-byte aligned; device memory, or pinned host memory as the device sees it: from_host)
+// -> slab layout, for up to REPACK_MAX_PARTS parts of one adapter in one launch (unit_end, r, rs are set by the launcher)
 constexpr int REPACK_MAX_PARTS = 32;
 struct RepackPart {
     const void *A, *B;
