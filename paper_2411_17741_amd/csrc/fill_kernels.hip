@@ -140,4 +140,22 @@ hipError_t launch_repack_parts(int dtype, RepackTable &t, int32_t rank, bool fro
     return hipGetLastError();
 }
 
+// Upload of a plan's work lists.  The lists lie in pinned host memory and the kernel reads them over the link itself:
+// the copy engine takes 15 us from its request to the kernel behind it for the 10 to 100 KB of a plan, this kernel
+// adds 2.5 us (32 KB) to 7 us (256 KB) ahead of the first apply.
+__global__ __launch_bounds__(256) void upload_kernel(uint4 *__restrict__ dst, const uint4 *__restrict__ src, uint32_t n)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+}
+
+hipError_t launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st, hipEvent_t done)
+{
+    const uint32_t n = (uint32_t)((bytes + 15) / 16);
+    if (n == 0) return hipSuccess;
+    launch_k(nullptr, done, 0, upload_kernel, dim3((n + 255) / 256), dim3(256), 0, st, static_cast<uint4 *>(dst),
+             static_cast<const uint4 *>(src), n);
+    return hipGetLastError();
+}
+
 }  // namespace lora

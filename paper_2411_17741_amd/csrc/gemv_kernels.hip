@@ -439,25 +439,25 @@ hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, const int32_t *t
     return hipGetLastError();
 }
 
-hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm)
+hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     const int n_proj = (int)(m.n_proj_phase & 0xffu);
     if (m.n_gs == 0 || a.n_ge <= 0 || n_proj <= 0) return hipSuccess;
     const int n_shrink = n_proj * (int)m.n_gs, n_expand = (m.unit_end[GEMV_MAX_PROJS - 1] + 3) / 4;
-    auto go = [&](uint32_t phase, int blocks, int kind) {
+    auto go = [&](uint32_t phase, int blocks, int kind, hipEvent_t ev) {
         const uint32_t pp = (uint32_t)n_proj | (phase << 8);
         if (dtype == LORA_BF16)
-            launch_k(tm, kind, gemv_kernel<__bf16>, dim3(blocks), dim3(256), st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
+            launch_k(tm, ev, kind, gemv_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
                      m.unit_end[2], m.unit_end[3], m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a);
         else
-            launch_k(tm, kind, gemv_kernel<float>, dim3(blocks), dim3(256), st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
+            launch_k(tm, ev, kind, gemv_kernel<float>, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
                      m.unit_end[2], m.unit_end[3], m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a);
     };
     if (a.epoch) {
-        go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED);
+        go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
     } else {
-        go(1u, n_shrink, LORA_K_GEMV_SHRINK);
-        go(2u, n_expand, LORA_K_GEMV_EXPAND);
+        go(1u, n_shrink, LORA_K_GEMV_SHRINK, nullptr);
+        go(2u, n_expand, LORA_K_GEMV_EXPAND, done);
     }
     return hipGetLastError();
 }

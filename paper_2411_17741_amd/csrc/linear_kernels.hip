@@ -435,7 +435,7 @@ size_t linear_split_bytes(int n_rt, int h_in, int h_out, int n_cu)
 
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
                                size_t split_scratch_bytes, uint32_t *split_flags, int n_split_flags, int32_t *fault, int n_cu,
-                               hipStream_t st, const KernelTimer *tm)
+                               hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (n_rt <= 0) return hipSuccess;
     static bool attr_set = false;
@@ -452,14 +452,8 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem
         parts = 1, n_tail = 0;  // no room for the partial sums: whole tiles only
     const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_flags, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;
-    hipEvent_t s = nullptr, e = nullptr;
-    if (tm) tm->pair(tm->ctx, LORA_K_LINEAR, &s, &e);
-    if (s && e)
-        hipExtLaunchKernelGGL(linear_tiles_kernel, dim3(blocks), dim3(512), 2 * L_STAGE, st, s, e, 0, a,
-                              static_cast<const __bf16 *>(Wt), row_tiles, n_rt, n_mt, sp);
-    else
-        hipLaunchKernelGGL(linear_tiles_kernel, dim3(blocks), dim3(512), 2 * L_STAGE, st, a, static_cast<const __bf16 *>(Wt),
-                           row_tiles, n_rt, n_mt, sp);
+    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), 2 * L_STAGE, st, a, static_cast<const __bf16 *>(Wt),
+             row_tiles, n_rt, n_mt, sp);
     return hipGetLastError();
 }
 

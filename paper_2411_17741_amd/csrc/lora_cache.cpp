@@ -132,8 +132,10 @@ struct lora_plan {
     bool internal = false;
     char *dev = nullptr;
     char *pinned = nullptr;
-    hipEvent_t ev_upload = nullptr, ev_last_use = nullptr;
-    bool upload_pending = false, use_pending = false;
+    const char *pinned_dev = nullptr;  // the same as the device sees it
+    hipEvent_t ev_upload = nullptr;
+    bool upload_pending = false;
+    int32_t last_use = -1;  // fence of the latest call that used the plan
     int32_t T = 0;
     int32_t n_tok_list = 0, n_tiles = 0, n_gs = 0, n_ge = 0;
     int32_t n_tile_tok = 0;  // tokens of all tiles = leading entries of tok_list
@@ -196,9 +198,18 @@ struct lora_cache {
     int n_cu = 256;  // its compute units
     bool fencing = true;
     int64_t apply_seq = 0;
-    hipEvent_t apply_ev[N_APPLY_EVENTS] = {};
-    int64_t apply_ev_seq[N_APPLY_EVENTS] = {};
-    std::unordered_map<hipStream_t, hipEvent_t> stream_fence;  // per stream that ran applies: an event of its own, recorded with every fence
+    // Fences: every call that enqueues applies has one event that stands for its end.  It is held by its place in a
+    // ring of the latest calls, by the stream it is the latest of and by the plan it is the latest use of; an event
+    // that nobody holds is free (one event per call instead of one per holder: a record costs the device 4 us).
+    struct Fence {
+        hipEvent_t ev;
+        int32_t holders;
+    };
+    std::vector<Fence> fences;
+    size_t next_fence = 0;  // where the search for a free one starts
+    int32_t ring[N_APPLY_EVENTS];  // index into fences, -1: none
+    int64_t ring_seq[N_APPLY_EVENTS] = {};
+    std::unordered_map<hipStream_t, int32_t> stream_fence;
     // raised by a kernel that gave up a bounded wait: one word of pinned host memory that the kernels
     // write through its device address, so the host sees it without a synchronisation
     int32_t *fault_host = nullptr, *fault_dev = nullptr;
@@ -542,6 +553,32 @@ void build_shrink_runs(const lora::DevItem *tiles, int n_tiles, int quanta, int 
     }
 }
 
+// `place` now holds fence `f` (-1: none) instead of the one it held
+void hold_fence(lora_cache &c, int32_t &place, int32_t f)
+{
+    if (f >= 0) ++c.fences[f].holders;
+    if (place >= 0) --c.fences[place].holders;
+    place = f;
+}
+// a fence nobody holds; -1 if the runtime gives no more events
+int32_t free_fence(lora_cache &c)
+{
+    for (size_t i = 0; i < c.fences.size(); ++i)
+        if (c.fences[(c.next_fence + i) % c.fences.size()].holders == 0) {
+            const int32_t f = (int32_t)((c.next_fence + i) % c.fences.size());
+            c.next_fence = (size_t)f + 1;
+            return f;
+        }
+    hipEvent_t ev = nullptr;
+    const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+        g_last_hip = (int)e;
+        return -1;
+    }
+    c.fences.push_back({ev, 0});
+    return (int32_t)c.fences.size() - 1;
+}
+
 // Validates a batch against the slot table and writes its work lists into plan `p`
 // (pinned copy + upload on `st`).
 int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
@@ -758,12 +795,11 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.bytes = bytes;
     p.build_seq = ++c.plan_builds;
     if (!c.host_only && bytes) {
-        if (p.use_pending) {
-            HIP_TRY(hipStreamWaitEvent(st, p.ev_last_use, 0));
-            p.use_pending = false;
+        if (p.last_use >= 0) {
+            HIP_TRY(hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0));
+            hold_fence(c, p.last_use, -1);
         }
-        HIP_TRY(hipMemcpyAsync(p.dev, p.pinned, bytes, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipEventRecord(p.ev_upload, st));
+        HIP_TRY(lora::launch_upload(p.dev, p.pinned_dev, bytes, st, p.ev_upload));
         p.upload_pending = true;
     }
     return LORA_OK;
@@ -776,10 +812,10 @@ int wait_for_applies(lora_cache &c, const Slot &s, hipStream_t st)
 {
     if (!c.fencing || s.last_used <= 0) return LORA_OK;
     const int e = (int)(s.last_used % N_APPLY_EVENTS);
-    if (c.apply_ev_seq[e] == s.last_used) {
-        HIP_TRY(hipStreamWaitEvent(st, c.apply_ev[e], 0));
+    if (c.ring_seq[e] == s.last_used) {
+        HIP_TRY(hipStreamWaitEvent(st, c.fences[c.ring[e]].ev, 0));
     } else {
-        for (const auto &kv : c.stream_fence) HIP_TRY(hipStreamWaitEvent(st, kv.second, 0));
+        for (const auto &kv : c.stream_fence) HIP_TRY(hipStreamWaitEvent(st, c.fences[kv.second].ev, 0));
     }
     return LORA_OK;
 }
@@ -914,15 +950,21 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
     for (size_t i = 0; i < c->plans.size() && rc == LORA_OK; ++i) {
         lora_plan &p = c->plans[i];
         p.dev = c->pool + c->off_plans + c->plan_cap * i;
-        fail(hipHostMalloc(reinterpret_cast<void **>(&p.pinned), c->plan_cap, hipHostMallocDefault));
+        fail(hipHostMalloc(reinterpret_cast<void **>(&p.pinned), c->plan_cap, hipHostMallocMapped));
+        if (rc == LORA_OK) fail(hipHostGetDevicePointer(reinterpret_cast<void **>(const_cast<char **>(&p.pinned_dev)), p.pinned, 0));
         fail(hipEventCreateWithFlags(&p.ev_upload, hipEventDisableTiming));
-        fail(hipEventCreateWithFlags(&p.ev_last_use, hipEventDisableTiming));
     }
     for (int i = 0; i < N_STAGES && rc == LORA_OK; ++i) {
         c->stage[i].dev = c->pool + c->off_stage + c->stage_cap * i;
         fail(hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming));
     }
-    for (int i = 0; i < N_APPLY_EVENTS && rc == LORA_OK; ++i) fail(hipEventCreateWithFlags(&c->apply_ev[i], hipEventDisableTiming));
+    std::fill(c->ring, c->ring + N_APPLY_EVENTS, -1);
+    // what the ring, the plans and a few streams hold; more streams, more events
+    for (size_t i = 0; i < N_APPLY_EVENTS + c->plans.size() + 8 && rc == LORA_OK; ++i) {
+        hipEvent_t ev = nullptr;
+        fail(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        if (ev) c->fences.push_back({ev, 0});
+    }
     if (rc == LORA_OK && !(c->flags & LORA_CACHE_NO_OVERLAP)) {
         fail(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
         fail(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
@@ -945,14 +987,10 @@ int lora_cache_destroy(lora_cache_t *c)
         for (auto &p : c->plans) {
             if (p.pinned) (void)hipHostFree(p.pinned);
             if (p.ev_upload) (void)hipEventDestroy(p.ev_upload);
-            if (p.ev_last_use) (void)hipEventDestroy(p.ev_last_use);
         }
         for (auto &s : c->stage)
             if (s.ev) (void)hipEventDestroy(s.ev);
-        for (auto &e : c->apply_ev)
-            if (e) (void)hipEventDestroy(e);
-        for (auto &kv : c->stream_fence)
-            if (kv.second) (void)hipEventDestroy(kv.second);
+        for (auto &f : c->fences) (void)hipEventDestroy(f.ev);
         if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
         if (c->ev_join) (void)hipEventDestroy(c->ev_join);
         if (c->side_stream) (void)hipStreamDestroy(c->side_stream);
@@ -1621,7 +1659,7 @@ static int shrink_setup(const lora_cache_t *c, const lora_plan_t *p, int n, char
 // hand-over when the part is small (the launch in between then costs more than the hand-over), else a
 // shrink and an expand launch.  y32[i], when set, receives projection i's update as fp32 instead of y.
 static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::ApplyArgs *a, float *const *y32, int n, bool allow_one_launch,
-                        hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm)
+                        hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
     lora::GemvArgs ga{};
@@ -1680,12 +1718,13 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::ApplyArgs *
         }
         ga.epoch = ++*sc.epoch;
     }
-    HIP_TRY(lora::launch_gemv(c->dtype, gm, ga, st, tm));
+    HIP_TRY(lora::launch_gemv(c->dtype, gm, ga, st, tm, done));
     return LORA_OK;
 }
 
+// `fence` (null: none) is to stand for the group's end on `st`.
 static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t *descs, int n, float scale, hipStream_t st,
-                         const Scratch &sc)
+                         const Scratch &sc, hipEvent_t fence)
 {
     // the work lists may have been uploaded on another stream
     if (p->upload_pending) {
@@ -1752,20 +1791,25 @@ static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     struct Join {
         lora_cache_t *c;
         hipStream_t st;
-        bool armed;
+        bool armed, rides;  // rides: the join event is the GEMV launch's own (not while capturing, where it must be an edge of the graph)
         hipError_t now()
         {
             if (!armed) return hipSuccess;
             armed = false;
-            const hipError_t e = hipEventRecord(c->ev_join, c->side_stream);
+            const hipError_t e = rides ? hipSuccess : hipEventRecord(c->ev_join, c->side_stream);
             return e == hipSuccess ? hipStreamWaitEvent(st, c->ev_join, 0) : e;
         }
         ~Join() { (void)now(); }
-    } join{c, st, fork};
-    if (const int rc_g = enqueue_gemv(c, p, a, nullptr, n, true, gemv_st, sc, tm)) return rc_g;
+    } join{c, st, fork, false};
+    // the fence rides on the group's last kernel, where that is the last thing on `st`
+    const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
+    const bool join_rides = fork && !is_capturing(st);
+    if (const int rc_g = enqueue_gemv(c, p, a, nullptr, n, true, gemv_st, sc, tm, join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr)))
+        return rc_g;
+    join.rides = join_rides;
     // the updates of base_out
     for (int i = 0; i < n; ++i) {
-        HIP_TRY(lora::launch_mfma_expand(a[i], tiles, p->n_tiles, st, tm));
+        HIP_TRY(lora::launch_mfma_expand(a[i], tiles, p->n_tiles, st, tm, ride && i == n - 1 ? fence : nullptr));
         const int64_t seq = ++c->apply_seq;
         ++c->stats.applies;
         for (int32_t sl : p->slots) {
@@ -1774,28 +1818,36 @@ static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         }
     }
     HIP_TRY(join.now());
+    if (fence && !ride) HIP_TRY(hipEventRecord(fence, st));
     return LORA_OK;
 }
 
-static int enqueue_apply(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t proj, const void *x, void *base_out,
-                         float scale, hipStream_t st)
+// The event that is to stand for the end of a call that enqueues applies on `st`: fills that come later and uploads
+// into the same plan wait for it.  None (-1) without fencing and under capture.
+static int take_fence(lora_cache_t *c, hipStream_t st, int32_t &f)
 {
-    const lora_apply_desc_t d{layer, proj, x, base_out};
-    return enqueue_group(c, p, &d, 1, scale, st, pool_scratch(c));
+    f = -1;
+    if (!c->fencing || is_capturing(st)) return LORA_OK;
+    f = free_fence(*c);
+    return f < 0 ? LORA_E_HIP : LORA_OK;
+}
+static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32_t f)
+{
+    if (f < 0) return;
+    const int64_t seq = c->apply_seq;
+    hold_fence(*c, c->ring[seq % N_APPLY_EVENTS], f);
+    c->ring_seq[seq % N_APPLY_EVENTS] = seq;
+    hold_fence(*c, c->stream_fence.try_emplace(st, -1).first->second, f);
+    hold_fence(*c, p->last_use, f);
 }
 
-// One event pair per call (not per apply): fills that come later wait for it.
-static int fence_applies(lora_cache_t *c, lora_plan_t *p, hipStream_t st)
+// one projection as a call with a fence of its own
+static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t &d, float scale, hipStream_t st, const Scratch &sc)
 {
-    if (!c->fencing || is_capturing(st)) return LORA_OK;
-    const int64_t seq = c->apply_seq;
-    HIP_TRY(hipEventRecord(c->apply_ev[seq % N_APPLY_EVENTS], st));
-    c->apply_ev_seq[seq % N_APPLY_EVENTS] = seq;
-    hipEvent_t &own = c->stream_fence[st];
-    if (!own) HIP_TRY(hipEventCreateWithFlags(&own, hipEventDisableTiming));
-    HIP_TRY(hipEventRecord(own, st));
-    HIP_TRY(hipEventRecord(p->ev_last_use, st));
-    p->use_pending = true;
+    int32_t f;
+    if (const int rc = take_fence(c, st, f)) return rc;
+    if (const int rc = enqueue_group(c, p, &d, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
+    publish_fence(c, p, st, f);
     return LORA_OK;
 }
 
@@ -1806,9 +1858,7 @@ int lora_apply_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t proj
     hipStream_t st = static_cast<hipStream_t>(stream);
     int rc = validate_apply(c, p, layer, proj, x, base_out);
     if (rc != LORA_OK) return rc;
-    rc = enqueue_apply(c, p, layer, proj, x, base_out, scale, st);
-    if (rc != LORA_OK) return rc;
-    return fence_applies(c, p, st);
+    return apply_fenced(c, p, {layer, proj, x, base_out}, scale, st, pool_scratch(c));
 }
 
 int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t proj, const void *x, void *base_out,
@@ -1823,13 +1873,11 @@ int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32
     if (!ss.ptr) return LORA_E_STATE;
     const Scratch sc{ss.ptr, STATIC_V_BYTES, 1, ss.ptr + STATIC_V_BYTES, STATIC_VPART_ROWS, true,
                      ss.ptr + STATIC_V_BYTES + STATIC_VPART_BYTES, STATIC_VTAG_BYTES, &ss.epoch, &ss.cap_id, &ss.cap_plan, &ss.cap_sets};
-    const lora_apply_desc_t d{layer, proj, x, base_out};
     const bool timing = c->timing;
     c->timing = false;  // timed launches take events from a pool that may have to grow
-    rc = enqueue_group(c, p, &d, 1, scale, st, sc);
+    rc = apply_fenced(c, p, {layer, proj, x, base_out}, scale, st, sc);
     c->timing = timing;
-    if (rc != LORA_OK) return rc;
-    return fence_applies(c, p, st);
+    return rc;
 }
 
 int lora_linear_workspace_bytes(const lora_cache_t *c, const lora_plan_t *p, int32_t proj, size_t *bytes)
@@ -1874,6 +1922,8 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     a.h_out = c->proj[proj].h_out;
     a.v_stride = c->v_stride;
     a.scale = scale;
+    int32_t f;
+    if (const int rc_f = take_fence(c, st, f)) return rc_f;
     // shrink of the tiles and of the GEMV groups (x is read, v written)
     if (p->n_tiles > 0) {
         lora::ShrinkProjs ps;
@@ -1891,7 +1941,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         a.y32 = static_cast<float *>(workspace);
         if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + p->n_tile_tok, p->n_tok_list - p->n_tile_tok, a.h_out, st));
         float *const y32 = a.y32;
-        if (const int rc_g = enqueue_gemv(c, p, &a, &y32, 1, false, st, pool_scratch(c), tm)) return rc_g;
+        if (const int rc_g = enqueue_gemv(c, p, &a, &y32, 1, false, st, pool_scratch(c), tm, nullptr)) return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
     lora::ApplyArgs lin = a;
@@ -1899,14 +1949,16 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
     HIP_TRY(lora::launch_linear_tiles(lin, Wt, reinterpret_cast<const lora::DevItem *>(p->dev + p->off_lin_tiles), p->n_lin_tiles,
                                       c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<uint32_t *>(c->pool + c->off_fault),
-                                      N_LINEAR_FLAGS, c->fault_dev, c->n_cu, st, tm));
+                                      N_LINEAR_FLAGS, c->fault_dev, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));
+    if (tm && f >= 0) HIP_TRY(hipEventRecord(c->fences[f].ev, st));
     const int64_t seq = ++c->apply_seq;
     ++c->stats.applies;
     for (int32_t sl : p->slots) {
         c->slots[sl].last_used = seq;
         ++c->slots[sl].use_count;
     }
-    return fence_applies(c, p, st);
+    publish_fence(c, p, st, f);
+    return LORA_OK;
 }
 
 int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t *descs, int32_t n, float scale,
@@ -1918,6 +1970,8 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         const int rc = validate_apply(c, p, descs[i].layer, descs[i].proj, descs[i].x, descs[i].base_out);
         if (rc != LORA_OK) return rc;
     }
+    int32_t f;
+    if (const int rc_f = take_fence(c, st, f)) return rc_f;
     // runs of applies that read the same x (q, k, v; gate, up) and do not write to it go as a group
     const size_t e = c->esize;
     for (int32_t i = 0; i < n;) {
@@ -1933,11 +1987,12 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
                    c->proj[descs[i + g].proj].h_in == c->proj[descs[i].proj].h_in && !writes_x(descs[i + g]))
                 ++g;
         }
-        const int rc = enqueue_group(c, p, descs + i, g, scale, st, pool_scratch(c));
+        const int rc = enqueue_group(c, p, descs + i, g, scale, st, pool_scratch(c), f >= 0 && i + g == n ? c->fences[f].ev : nullptr);
         if (rc != LORA_OK) return rc;
         i += g;
     }
-    return n > 0 ? fence_applies(c, p, st) : LORA_OK;
+    if (n > 0) publish_fence(c, p, st, f);
+    return LORA_OK;
 }
 
 int lora_apply(lora_cache_t *c, int32_t layer, int32_t proj, const void *x, void *base_out, int32_t T,

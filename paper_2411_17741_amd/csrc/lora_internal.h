@@ -187,19 +187,23 @@ struct KernelTimer {
     void (*pair)(void *ctx, int kind, hipEvent_t *start, hipEvent_t *stop);
 };
 
+// `done`, when set, is an event that stands for the end of this kernel: it rides on the kernel's own completion signal
+// instead of being recorded behind it (a record is a packet of its own that the queue processes after the kernel:
+// 4.0 us per call on the device, 1.6 us this way; measured with an empty kernel).  A timed launch carries the timer's
+// events instead: with a timer the caller records.
 template <typename K, typename... A>
-inline void launch_k(const KernelTimer *tm, int kind, K kernel, dim3 grid, dim3 block, hipStream_t st, A... args)
+inline void launch_k(const KernelTimer *tm, hipEvent_t done, int kind, K kernel, dim3 grid, dim3 block, unsigned lds, hipStream_t st, A... args)
 {
-    hipEvent_t s = nullptr, e = nullptr;
+    hipEvent_t s = nullptr, e = done;
     if (tm) tm->pair(tm->ctx, kind, &s, &e);
-    if (s && e) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, s, e, 0, args...);
-    else hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
+    if (e) hipExtLaunchKernelGGL(kernel, grid, block, lds, st, s, e, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, st, args...);
 }
 
-// launches (all asynchronous on `st`); dtype is LORA_F32 or LORA_BF16; tm may be null
+// launches (all asynchronous on `st`); dtype is LORA_F32 or LORA_BF16; tm and done may be null (done: see launch_k)
 // GEMV shrink and expand of the group's projections: phase 0 as one launch (a.epoch != 0: the expand
 // wavefronts wait for the hand-over words to carry that number), phases 1 and 2 as two
-hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm);
+hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // bytes of one projection's hand-over words for max_tokens tokens
 size_t gemv_handover_bytes(int dtype, int64_t max_tokens);
 // zeroes the hand-over words of tokens toks[0 .. n) (device list) in `vw`
@@ -249,7 +253,8 @@ struct ShrinkProjs {
 // proj_base, row_bytes and v of `a` are ignored (taken from ps)
 hipError_t launch_mfma_shrink(const ApplyArgs &a, const ShrinkProjs &ps, const DevItem *tiles, int n_tiles, hipStream_t st,
                               const KernelTimer *tm);
-hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm);
+hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm,
+                              hipEvent_t done);
 // y = x . Wt^T + adapter update for row tiles (tiles of the plan, then plain runs of the other tokens:
 // rank 0); a.tok_list must be the list the row tiles index; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]
@@ -259,7 +264,9 @@ hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipS
 size_t linear_split_bytes(int n_rt, int h_in, int h_out, int n_cu);
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
                                size_t split_scratch_bytes, uint32_t *split_flags, int n_split_flags, int32_t *fault, int n_cu,
-                               hipStream_t st, const KernelTimer *tm);
+                               hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+// a plan's work lists (bytes rounded up to 16) from pinned host memory as the device sees it to their place in the pool
+hipError_t launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st, hipEvent_t done);
 // A [h_in][r] / B [r][h_out] (16-byte aligned; device memory, or pinned host memory as the device sees it: from_host)
 // -> slab layout, for up to REPACK_MAX_PARTS parts of one adapter in one launch (unit_end, r, rs are set by the launcher)
 constexpr int REPACK_MAX_PARTS = 32;

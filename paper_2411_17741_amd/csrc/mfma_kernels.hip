@@ -574,14 +574,14 @@ hipError_t launch_mfma_shrink(const ApplyArgs &a, const ShrinkProjs &ps, const D
     if (n_tiles <= 0 || ps.n <= 0 || ps.n_runs <= 0) return hipSuccess;
     if (ps.n_runs % 8 != 0 || ps.quanta < 1) return hipErrorInvalidValue;
     const int runs_per_xcd = ps.n_runs / 8;
-    launch_k(tm, LORA_K_MFMA_SHRINK, mfma_shrink_kernel, dim3(ps.n_runs * ps.n), dim3(256), st, ps.cuts, tiles, runs_per_xcd, ps.n,
+    launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel, dim3(ps.n_runs * ps.n), dim3(256), 0, st, ps.cuts, tiles, runs_per_xcd, ps.n,
              ps.quanta, n_tiles, a, ps);
     if (ps.any_pieces)
-        launch_k(tm, LORA_K_MFMA_REDUCE, mfma_reduce_kernel, dim3(n_tiles * 8, ps.n), dim3(256), st, a, ps, tiles);
+        launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel, dim3(n_tiles * 8, ps.n), dim3(256), 0, st, a, ps, tiles);
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm)
+hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (n_tiles <= 0) return hipSuccess;
     // the widest column run per block that still gives 512 blocks (two per CU), else the narrowest
@@ -593,7 +593,7 @@ hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_ti
         last_width = 1;
         while (last_width < (n_runs & 7)) last_width <<= 1;
     }
-    launch_k(tm, LORA_K_MFMA_EXPAND, mfma_expand_kernel, dim3(n_tiles * ((n_runs & ~7) + last_width)), dim3(256), st, a, tiles, n_tiles,
+    launch_k(tm, done, LORA_K_MFMA_EXPAND, mfma_expand_kernel, dim3(n_tiles * ((n_runs & ~7) + last_width)), dim3(256), 0, st, a, tiles, n_tiles,
              cols / 128, n_runs, last_width);
     return hipGetLastError();
 }
