@@ -5,21 +5,30 @@
 // never read: the separate addition of the adapter result to the base output (paper section 3.1)
 // disappears.  This is the variant of the hot path whose roof is the matrix cores, not HBM.
 //
-// Block = 8 wavefronts on 256 rows (four row tiles) x 256 output columns; wavefront w owns the row
-// half w%2 and the column quarter w/2: 8 x 4 products of 16 x 16 (v_mfma_f32_16x16x32_bf16, 128
-// accumulator registers).  The 32x32x16 form of the product has the higher peak rate, but beside the
-// stage loads it is the slower one: the k loop of this kernel as a microbenchmark takes 197 us with it
-// and 173 us with the 16x16x32 form on the prefill shape (loads alone 120 us, products alone 120 us).
-// Two wavefronts per SIMD: with one, every wait -- the barrier of a stage, the first operand reads
-// after it -- idles the matrix core.  x rows (gathered by token) and Wt rows (Wt[n][k] = W[k][n], the
-// layout a linear layer keeps its weight in) are both contiguous along k: every stage brings 64 k of
-// both into LDS, double-buffered, one barrier per stage, by global_load_lds_dwordx4 -- the load writes
-// LDS itself (at the wavefront's base + 16 bytes x lane; checked on the part), so no registers stage
-// the data (loads that return into registers while products run took more than twice as long).
-// LDS rows are 128 bytes without padding; bank conflicts are avoided by a swizzle instead: 16-byte
-// slot s of row r holds piece s ^ ((r/2) % 8) of the row's 64 k, so the 16 rows an operand read
-// touches at once fall into 16 different bank groups.  Per 32-wide k step a wavefront reads 8 + 4
-// operands from LDS for 32 products.
+// Block = 8 wavefronts on 256 rows (four row tiles) x 256 output columns; wavefront w owns the row half w/4 and the
+// column quarter w%4: 8 x 4 products of 16 x 16 (v_mfma_f32_16x16x32_bf16, 128 accumulator registers).  x rows
+// (gathered by token) and Wt rows (Wt[n][k] = W[k][n], the layout a linear layer keeps its weight in) are both
+// contiguous along k: a stage is 64 k of both, 64 KB, brought into LDS by global_load_lds_dwordx4 -- the load writes
+// LDS itself (at the wavefront's base + 16 bytes x lane; checked on the part), so no registers stage the data.
+//
+// What bounds the loop is that matrix cores, LDS and the load path each need most of a stage's time (products 0.85 us at
+// the peak rate, 192 KB of operand reads, 64 KB of loads): done one after the other by wavefronts in step, with a wait
+// for all loads at the stage's end, a stage took 2 us.  So the two wavefronts of a SIMD (w and w + 4) take turns: a
+// stage is two phases (row tile 0 and row tile 1 of the wavefront), a phase a *load section* -- the phase's operand
+// reads and the requests for later stages -- and a *product section* of 32 products, with a barrier behind each, and
+// wavefronts 4..7 run one section behind wavefronts 0..3.  The requests are counted, not drained: an LDS half (128 rows
+// of x or Wt) is requested three phases before it is read, as soon as the phase after its last read has begun, and a
+// load section waits only until the eight latest requests are all that is outstanding.  Both sides of the hand-over
+// are ordered by the barriers: a section ends with its own reads done (lgkmcnt(0)) and its own part of the half that
+// the next phase reads landed (vmcnt(8)), and the other group of wavefronts has passed the same point one barrier
+// later, before anybody reads (or overwrites) that half.
+// Measured on 4096 x 4096 x 4096 (one round of 256 blocks): 129.5 us with all wavefronts in step, 98.5 us this way;
+// 8192 x 8192 x 8192: 934 -> 710 us (1.55 PFLOP/s; the vendor library's product 766 us).  Four phases of 16 products
+// take 107 us, operand reads spread evenly over the phases 98 us, requests from the product section 102 us.
+//
+// LDS rows are 128 bytes without padding; bank conflicts are avoided by a swizzle instead: 16-byte slot s of row r
+// holds piece s ^ ((r/2) % 8) of the row's 64 k, so the 16 rows an operand read touches at once fall into 16
+// different bank groups.
 // Operand layout of the instruction: A (16 x 32): lane l holds row l%16, k = 8*(l/16) .. +7;
 // B (32 x 16): lane l holds column l%16, same k; D: lane l holds column l%16, rows 4*(l/16) .. +3.
 // The products are formed transposed -- the W block is the row operand, the x block the column
@@ -32,14 +41,21 @@
 // GEMV kernels beforehand into the (zeroed) output rows, and this kernel adds it to the accumulators of
 // those rows before the one rounding of the stored value (row tiles marked a = 1).
 //
-// One block fills a CU (its two stages take 144 KB of LDS), so a grid of N tiles runs in ceil(N / CUs)
-// rounds and the last round may be nearly empty (368 tiles on 256 CUs: a second round of 112).  The tiles of
-// that last round are therefore split along k into S = 2 or 4 parts, one block each, as many as fit one round:
-// the last part of a tile is its owner -- it is dispatched last, so the other parts are running or done
-// when it waits for them, and they wait for nothing -- and adds the other parts' fp32 accumulators, which
-// travel through a scratch area as device-scope atomic stores and loads (past the per-XCD L2s) behind a
-// flag per part that the owner resets; its wait is bounded and raises the cache's fault flag.
+// Block order.  Tiles are counted in groups of four row panels, a group column by column, and every XCD takes a run of
+// consecutive ones (block b runs on XCD b % 8): the 32 blocks of an XCD then share 4 row panels and 8 column panels
+// through its L2 instead of all row panels (2816 x 13824 x 5120: 363 -> 340 us).
+//
+// One block fills a CU (its two stages take 128 KB of LDS), so a grid of N tiles runs in ceil(N / CUs) rounds and the
+// last round may be nearly empty (288 tiles on 256 CUs: a second round of 32).  The tiles of that last round are
+// therefore split along k into up to 8 parts, one block each (linear_split_shape).  The parts of a tile finish it
+// together: each owns a share of every wavefront's rows, leaves its fp32 accumulators of the other shares in a scratch
+// area (device-scope atomic stores, past the per-XCD L2s), counts itself in, waits until all parts have, adds the other
+// parts' sums of its own share and runs the adapter slab and the store for it.  (With one owner per tile that collected
+// everything the hand-over took 25 us of a 190 us launch.)  The parts of a tile are neighbours in dispatch order, so
+// the earliest unfinished tile's parts are all running or next to be dispatched, and nobody waits for a block that
+// waits in turn for its place; the wait is bounded all the same and raises the cache's fault flag.
 #include <algorithm>
+#include <type_traits>
 
 #include "lora_device.h"
 
@@ -48,36 +64,55 @@ namespace lora {
 namespace {
 constexpr int LBM = 256, LBN = 256, LBK = 64;
 constexpr int LROW = LBK * 2;                   // bytes per row of a stage in LDS (swizzled, not padded)
-constexpr int L_A = LBM * LROW;                 // x part of a stage
-constexpr int L_STAGE = (LBM + LBN) * LROW;     // 73728 bytes
+constexpr int L_HALF = 128 * LROW;              // 128 rows of x or Wt, 64 k: 16 KB
+constexpr int L_LDS = 2 * 4 * L_HALF;           // two stages of x half 0, x half 1, Wt half 0, Wt half 1
 constexpr int SV_ROW = LORA_MAX_RANK * 2 + 16;  // bytes per row of the staged s.v
-static_assert(8 * 128 * 128 <= 2 * L_STAGE && LBM * SV_ROW <= 2 * L_STAGE, "s.v is staged in the stage buffers");
+static_assert(8 * 128 * 128 <= L_LDS && LBM * SV_ROW <= L_LDS, "s.v and the parked outputs use the stage buffers");
+constexpr int MAX_PARTS = 8;                    // a wavefront's 128 rows are eight blocks of 16
 }  // namespace
 
-
-// split of the last round: blocks [0, n_whole) work on whole tiles; block n_whole + S * j + p on part p of tile n_whole + j
+// split of the last round: blocks [0, n_whole) work on whole tiles; block n_whole + parts * j + p on part p of tile n_whole + j
 struct LinearSplit {
-    int n_whole, parts;          // parts = 1: no split
-    unsigned long long *partial;  // [tile j][part p < parts - 1][accumulator 32][half 2][thread 512] 8-byte words
-    uint32_t *flags;              // [tile j][part p < parts - 1], zero between launches
+    int n_whole, parts;           // parts = 1: no split
+    unsigned long long *partial;  // [tile j][row block of 16: 8][source, the row block's owner left out: parts - 1][column block 4][half 2][thread 512] 8-byte words
+    uint32_t *counts;             // [tile j][2]: parts that have left their sums, parts that have read; zero between launches
     int32_t *fault;
 };
 
-__global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
-                                                           const DevItem *__restrict__ tiles, int n_rt, int n_mt, LinearSplit sp)
+// Tile number -> (row panel, column panel): groups of four row panels, column by column
+__device__ __forceinline__ void linear_tile(int t, int n_mt, int n_nt, int &bm, int &bn)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];  // two stages
+    const int per = 4 * n_nt, grp = t / per, rem = t - grp * per, height = min(4, n_mt - 4 * grp);
+    bn = rem / height;
+    bm = 4 * grp + (rem - bn * height);
+}
+
+// A barrier alone: what must be complete at it has been waited for by count
+__device__ __forceinline__ void section_end()
+{
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+__global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
+                                                           const DevItem *__restrict__ tiles, int n_rt, int n_mt, int n_nt, LinearSplit sp)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
-    const int rh = w & 1, cq = w >> 1;
-    int tile_no = (int)blockIdx.x, part = 0, tail = -1;
-    if (tile_no >= sp.n_whole) {
-        tail = (tile_no - sp.n_whole) / sp.parts;
-        part = (tile_no - sp.n_whole) - tail * sp.parts;
+    const int rh = w >> 2, cq = w & 3;
+    int tile_no, part = 0, tail = -1;
+    if ((int)blockIdx.x >= sp.n_whole) {
+        tail = ((int)blockIdx.x - sp.n_whole) / sp.parts;
+        part = ((int)blockIdx.x - sp.n_whole) - tail * sp.parts;
         tile_no = sp.n_whole + tail;
+    } else {  // XCD j takes a run of consecutive tiles
+        const int j = (int)blockIdx.x & 7, q = sp.n_whole >> 3, r = sp.n_whole & 7;
+        tile_no = j * q + min(j, r) + ((int)blockIdx.x >> 3);
     }
-    const bool owner = part == sp.parts - 1 || tail < 0;
-    const int bm = tile_no % n_mt, bn = tile_no / n_mt;
+    int bm, bn;
+    linear_tile(tile_no, n_mt, n_nt, bm, bn);
     const int n0 = bn * LBN;
 
     // the four row tiles of the block (a missing one counts as empty), and the two of this wavefront's
@@ -94,7 +129,6 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     const DevItem it0 = get_tile(4 * bm), it1 = get_tile(4 * bm + 1), it2 = get_tile(4 * bm + 2), it3 = get_tile(4 * bm + 3);
     const DevItem mine0 = get_tile(4 * bm + 2 * rh), mine1 = get_tile(4 * bm + 2 * rh + 1);
     auto tile_of = [&](int j) -> const DevItem & { return j == 0 ? it0 : j == 1 ? it1 : j == 2 ? it2 : it3; };  // j: compile-time
-    const DevItem tile_of_wave = get_tile(4 * bm + (w >> 1));  // the row tile this wavefront loads half of
     const int dead_tok = it0.tok0;  // rows past a tile's end read a live token's x; they are never stored
 
     const __bf16 *x = static_cast<const __bf16 *>(a.x);
@@ -103,36 +137,34 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     // this block's stages of the k walk
     const int k_lo = tail < 0 ? 0 : n_k * part / sp.parts, k_hi = tail < 0 ? n_k : n_k * (part + 1) / sp.parts;
 
-    // loader: wavefront w brings rows 32w + 8q + lane/8, q = 0..3, of both x and Wt: instruction q writes
-    // 8 rows x 128 bytes at the wavefront-uniform LDS address of its first row, lane l to slot l%8 of
-    // row l/8, for which it fetches piece (l%8) ^ ((row/2) % 8) of the row
+    // Half h of x holds row tiles h and 2 + h of the block (phase h of row halves 0 and 1), half h of Wt columns
+    // 64 c + 32 h .. +31 of the four column quarters c.  Loader: wavefront w brings LDS rows 16w + 8q + lane/8, q = 0, 1,
+    // of every half: instruction q writes 8 rows x 128 bytes at the wavefront-uniform LDS address of its first row,
+    // lane l to slot l%8 of row l/8, for which it fetches piece (l%8) ^ ((row/2) % 8) of the row
     const int lr = lane >> 3, ls = lane & 7;
-    const int piece_even = ls ^ ((lane >> 4) & 7), piece_odd = ls ^ (((lane >> 4) + 4) & 7);  // (row/2)%8 for q even / odd
-    const __bf16 *xg[4];
-    {
-        int ti[4], tok[4];
+    const int piece[2] = {ls ^ ((lane >> 4) & 7), ls ^ (((lane >> 4) + 4) & 7)};
+    const __bf16 *xg[2][2], *wg[2][2];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) ti[q] = 32 * (w & 1) + 8 * q + lr;
-        tile_tokens_of(a.tok_list, tile_of_wave, ti, dead_tok, tok);  // (rows past the tile's end repeat its last)
+    for (int h = 0; h < 2; ++h) {
+        const DevItem t = h ? mine1 : mine0;  // (the row tiles a wavefront loads from are those it works on)
+        const int ti[2] = {16 * cq + lr, 16 * cq + 8 + lr};
+        int tok[2];
+        tile_tokens_of(a.tok_list, t, ti, dead_tok, tok);  // (rows past the tile's end repeat its last)
+        // h_out is a multiple of 64, so a run of 64 columns is inside or outside as a whole
+        const int w_row = min(n0 + 64 * (w >> 1), a.h_out - 64) + 32 * h + 16 * (w & 1) + lr;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) xg[q] = x + (size_t)tok[q] * a.h_in + ((q & 1) ? piece_odd : piece_even) * 8;
+        for (int q = 0; q < 2; ++q) {
+            xg[h][q] = x + (size_t)tok[q] * a.h_in + piece[q] * 8;
+            wg[h][q] = Wt + (size_t)(w_row + 8 * q) * a.h_in + piece[q] * 8;
+        }
     }
-    // Wt rows n0 + 32w + 8q + lr; h_out is a multiple of 64, so a run of 32 rows is inside or outside as a whole
-    const int w_row0 = min(n0 + 32 * w, a.h_out - 32);
-    const __bf16 *wg_even = Wt + (size_t)(w_row0 + lr) * a.h_in + piece_even * 8;
-    const __bf16 *wg_odd = Wt + (size_t)(w_row0 + lr) * a.h_in + piece_odd * 8;
-    // (All blocks walk k in step: the blocks of a row or column of the grid then find each other's
-    // panel slices in L2.  Starting every block at another stage, as the tile shrink does, was no faster.)
-    auto load_stage = [&](int kt, int buf) {
-        const int k = kt * LBK;
-        unsigned char *sa = lds + buf * L_STAGE + (32 * w) * LROW;
+    auto half_at = [&](int buf, int which) { return lds + (buf * 4 + which) * L_HALF; };  // which: 0, 1 x; 2, 3 Wt
+    auto load_half = [&](const __bf16 *const(&src)[2], int kt, int buf, int which) {
+        const int k = min(kt, k_hi - 1) * LBK;  // past the end: the last stage again (nobody reads it)
+        unsigned char *dst = half_at(buf, which) + 16 * w * LROW;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            __builtin_amdgcn_global_load_lds(xg[q] + k, (__attribute__((address_space(3))) void *)(sa + q * 8 * LROW), 16, 0, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            __builtin_amdgcn_global_load_lds(((q & 1) ? wg_odd : wg_even) + (size_t)(8 * q) * a.h_in + k,
-                                             (__attribute__((address_space(3))) void *)(sa + L_A + q * 8 * LROW), 16, 0, 0);
+        for (int q = 0; q < 2; ++q)
+            __builtin_amdgcn_global_load_lds(src[q] + k, (__attribute__((address_space(3))) void *)(dst + q * 8 * LROW), 16, 0, 0);
     };
 
     floatx4 acc[8][4];  // [block of 16 rows][block of 16 columns]
@@ -143,92 +175,132 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[mb][nb][e] = 0.f;
 
-    load_stage(k_lo, 0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    // operand reads: row R, k piece 4ks + g sits in slot (4ks + g) ^ ((R/2) % 8); R/2 % 8 = m/2 for all of a lane's rows
+    // operand reads: LDS row R, k piece 4ks + g sits in slot (4ks + g) ^ ((R/2) % 8); R/2 % 8 = m/2 for all of a lane's rows
     const int swz = (m >> 1) & 7;
-    for (int kt = k_lo; kt < k_hi; ++kt) {
-        // the next stage is requested before this one is multiplied, into the buffer that was read
-        // in the previous iteration (past the end: the last stage again, unconditionally)
-        const int buf = (kt - k_lo) & 1;
-        load_stage(min(kt + 1, k_hi - 1), buf ^ 1);
-        const unsigned char *sa = lds + buf * L_STAGE + (128 * rh + m) * LROW;
-        const unsigned char *sb = lds + buf * L_STAGE + L_A + (64 * cq + m) * LROW;
-        // (The compiler's own order -- operand reads in twos and fours between groups of eight products -- is
-        // as fast as reading the operands of every group one group ahead by hand.)
+    bf16x8 xo[4][2], wo[4][2];  // [block of 16 rows / columns][k step]
+    auto read_x = [&](int buf, int h) {
+        const unsigned char *s = half_at(buf, h) + (64 * rh + m) * LROW;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            bf16x8 xo[8], wo[4];
+        for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) wo[nb] = *reinterpret_cast<const bf16x8 *>(sb + nb * 16 * LROW + (((4 * ks + g) ^ swz) << 4));
+            for (int ks = 0; ks < 2; ++ks) xo[mb][ks] = *reinterpret_cast<const bf16x8 *>(s + mb * 16 * LROW + (((4 * ks + g) ^ swz) << 4));
+    };
+    auto read_w = [&](int buf) {
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb) xo[mb] = *reinterpret_cast<const bf16x8 *>(sa + mb * 16 * LROW + (((4 * ks + g) ^ swz) << 4));
+        for (int nb = 0; nb < 4; ++nb) {
+            const unsigned char *s = half_at(buf, 2 + (nb >> 1)) + (32 * cq + 16 * (nb & 1) + m) * LROW;
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[nb], xo[mb], acc[mb][nb], 0, 0, 0);
+            for (int ks = 0; ks < 2; ++ks) wo[nb][ks] = *reinterpret_cast<const bf16x8 *>(s + (((4 * ks + g) ^ swz) << 4));
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's part of the next stage has landed
-        __syncthreads();
-    }
+    };
+    auto products = [&](auto h_tag) {
+        constexpr int H = decltype(h_tag)::value;
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb)
+                    acc[4 * H + mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[nb][ks], xo[mb][ks], acc[4 * H + mb][nb], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+    };
 
-    // ---- a tile split along k: the parts hand their accumulators to the owner
+    // requests in the order of their use: per stage x half 0, Wt half 0, Wt half 1 | x half 1
+    load_half(xg[0], k_lo, 0, 0);
+    load_half(wg[0], k_lo, 0, 2);
+    load_half(wg[1], k_lo, 0, 3);
+    load_half(xg[1], k_lo, 0, 1);
+    load_half(xg[0], k_lo + 1, 1, 0);
+    load_half(wg[0], k_lo + 1, 1, 2);
+    load_half(wg[1], k_lo + 1, 1, 3);
+    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    section_end();
+    if (rh == 1) section_end();  // the second group of wavefronts runs one section behind
+    for (int kt = k_lo; kt < k_hi; ++kt) {
+        const int buf = (kt - k_lo) & 1;
+        read_x(buf, 0);
+        read_w(buf);
+        load_half(xg[1], kt + 1, buf ^ 1, 1);  // that half was last read in the phase before
+        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");  // x half 1 of this stage is in (eight requests came after it)
+        section_end();
+        products(std::integral_constant<int, 0>{});
+        section_end();
+        read_x(buf, 1);
+        load_half(xg[0], kt + 2, buf, 0);
+        load_half(wg[0], kt + 2, buf, 2);
+        load_half(wg[1], kt + 2, buf, 3);
+        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");  // x half 0 and Wt of the next stage are in
+        section_end();
+        products(std::integral_constant<int, 1>{});
+        section_end();
+    }
+    if (rh == 0) section_end();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end: LDS is used for other things below
+    __syncthreads();
+
+    // ---- a tile split along k: part p owns row blocks [8 p / parts, 8 (p + 1) / parts) of every wavefront
+    const int own_lo = tail < 0 ? 0 : 8 * part / sp.parts, own_hi = tail < 0 ? 8 : 8 * (part + 1) / sp.parts;
     if (tail >= 0) {
         typedef float floatx2 __attribute__((ext_vector_type(2)));
-        const size_t per_part = (size_t)32 * 2 * 512;  // words
-        if (!owner) {
-            unsigned long long *dst = sp.partial + ((size_t)tail * (sp.parts - 1) + part) * per_part + tid;
+        constexpr size_t PER = (size_t)4 * 2 * 512;  // words of one row block from one part
+        unsigned long long *mine = sp.partial + (size_t)tail * 8 * (sp.parts - 1) * PER + tid;
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb)
+        for (int mb = 0; mb < 8; ++mb) {
+            if (mb >= own_lo && mb < own_hi) continue;  // uniform
+            const int owner = ((mb + 1) * sp.parts - 1) >> 3;  // the part whose share holds mb
+            unsigned long long *dst = mine + ((size_t)mb * (sp.parts - 1) + (part - (part > owner))) * PER;
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
-                    const floatx4 c = acc[mb][nb];
-                    const floatx2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
-                    __hip_atomic_store(dst + ((mb * 4 + nb) * 2 + 0) * 512, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(dst + ((mb * 4 + nb) * 2 + 1) * 512, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores above have been performed where every XCD sees them
-            __syncthreads();
-            if (tid == 0) __hip_atomic_store(sp.flags + tail * (sp.parts - 1) + part, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
+            for (int nb = 0; nb < 4; ++nb) {
+                const floatx4 c = acc[mb][nb];
+                const floatx2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
+                __hip_atomic_store(dst + (nb * 2 + 0) * 512, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(dst + (nb * 2 + 1) * 512, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores above have been performed where every XCD sees them
+        __syncthreads();
         __shared__ int got_all;
+        uint32_t *const arrived = sp.counts + 2 * tail, *const read = arrived + 1;
         if (tid == 0) {
-            int ok = 1;
-            for (int p = 0; p < sp.parts - 1 && ok; ++p) {
-                ok = 0;
-                for (int spin = 0; spin < (1 << 20); ++spin) {
-                    if (__hip_atomic_load(sp.flags + tail * (sp.parts - 1) + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
-                        ok = 1;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(8);
-                }
+            int ok = 0;
+            __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int spin = 0; spin < (1 << 20) && !ok; ++spin) {
+                ok = __hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)sp.parts;
+                if (!ok) __builtin_amdgcn_s_sleep(8);
             }
             if (!ok) __hip_atomic_store(sp.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // pinned host memory
             got_all = ok;
         }
         __syncthreads();
         if (got_all) {
-            for (int p = 0; p < sp.parts - 1; ++p) {
-                const unsigned long long *src = sp.partial + ((size_t)tail * (sp.parts - 1) + p) * per_part + tid;
 #pragma unroll
-                for (int mb = 0; mb < 8; ++mb)
+            for (int mb = 0; mb < 8; ++mb) {
+                if (mb < own_lo || mb >= own_hi) continue;
+                for (int p = 0; p < sp.parts - 1; ++p) {
+                    const unsigned long long *src = mine + ((size_t)mb * (sp.parts - 1) + p) * PER;
+                    unsigned long long v[8];
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) {
-                        const floatx2 lo = __builtin_bit_cast(floatx2, __hip_atomic_load(src + ((mb * 4 + nb) * 2 + 0) * 512, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                        const floatx2 hi = __builtin_bit_cast(floatx2, __hip_atomic_load(src + ((mb * 4 + nb) * 2 + 1) * 512, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                        acc[mb][nb][0] += lo[0];
-                        acc[mb][nb][1] += lo[1];
-                        acc[mb][nb][2] += hi[0];
-                        acc[mb][nb][3] += hi[1];
+                    for (int i = 0; i < 8; ++i) v[i] = __hip_atomic_load(src + i * 512, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const floatx2 f = __builtin_bit_cast(floatx2, v[i]);
+                        acc[mb][i >> 1][2 * (i & 1)] += f[0];
+                        acc[mb][i >> 1][2 * (i & 1) + 1] += f[1];
                     }
+                }
             }
         }
+        // the last to have read sets the counts back
         __syncthreads();
-        if (tid < sp.parts - 1) __hip_atomic_store(sp.flags + tail * (sp.parts - 1) + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0 && __hip_atomic_fetch_add(read, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)sp.parts - 1) {
+            __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
+    // row blocks of row tile tl (0, 1 of the wavefront) that this block finishes
+    auto owns = [&](int mb) { return mb >= own_lo && mb < own_hi; };
+    auto owns_of = [&](int tl) { return own_lo < 4 * tl + 4 && own_hi > 4 * tl; };
 
     // ---- the adapter slab.  Bp operands of a row tile: granule 4ks + g (the 8 ranks a lane's operand holds,
     // contiguous per column; past the stored rank the last granule, which meets zeros of s.v), all four k
@@ -248,7 +320,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
                 bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(4 * ks + g, rs8 - 1) * a.h_out + col) * 8));
             }
     };
-    const bool live0 = mine0.rank != 0 && mine0.n_tok != 0, live1 = mine1.rank != 0 && mine1.n_tok != 0;  // wavefront-uniform
+    const bool live0 = mine0.rank != 0 && mine0.n_tok != 0 && owns_of(0), live1 = mine1.rank != 0 && mine1.n_tok != 0 && owns_of(1);  // wavefront-uniform
     bf16x8 bo[4][4];
     if (live0) load_bp(mine0, bo);
     // s.v of the block's rows to LDS as bf16 (zero past a tile's rank or end)
@@ -294,10 +366,11 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             if (ks < ks32) {
 #pragma unroll
                 for (int mbl = 0; mbl < 4; ++mbl) {
-                    const bf16x8 xo = *reinterpret_cast<const bf16x8 *>(svr + mbl * 16 * SV_ROW + ks * 64);
+                    if (!owns(4 * tl + mbl)) continue;  // uniform
+                    const bf16x8 so = *reinterpret_cast<const bf16x8 *>(svr + mbl * 16 * SV_ROW + ks * 64);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
-                        acc[4 * tl + mbl][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], xo, acc[4 * tl + mbl][nb], 0, 0, 0);
+                        acc[4 * tl + mbl][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[4 * tl + mbl][nb], 0, 0, 0);
                 }
             }
         }
@@ -330,7 +403,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             tile_tokens_of(a.tok_list, t, ti4, dead_tok, tok4);
 #pragma unroll
             for (int mbl = 0; mbl < 4; ++mbl) {
-                if (ti4[mbl] >= t.n_tok) continue;
+                if (!owns(4 * tl + mbl) || ti4[mbl] >= t.n_tok) continue;
                 __bf16 *yr = y + (size_t)tok4[mbl] * a.h_out + n0 + 64 * cq + 4 * g;
                 floatx4 term[4];
                 if (a.y32) {
@@ -358,6 +431,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         }
 #pragma unroll
         for (int mbl = 0; mbl < 4; ++mbl) {
+            if (!owns(4 * tl + mbl)) continue;
             const int ti = 16 * mbl + m, row = 64 * tl + ti;
             unsigned char *pr = park + row * 128;
 #pragma unroll
@@ -384,7 +458,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 64 * tl + ti8[i];
-            if (ti8[i] < t.n_tok) {
+            if (owns(4 * tl + (i >> 1)) && ti8[i] < t.n_tok) {
                 const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((sl ^ ((row >> 1) & 7)) << 4));
                 // (a streaming store: the rows leave the caches as they are written instead of lying there dirty
                 // until the next kernel's loads push them out -- the tile shrink that follows runs 2 to 3 us shorter)
@@ -414,23 +488,22 @@ hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipS
     return hipGetLastError();
 }
 
-// parts the tiles of the last round are split into (1: none), and how many tiles that round has
-static void linear_split_shape(int n_tiles, int n_k, int n_cu, int &parts, int &n_tail)
+// Parts the tiles of the last round are split into (1: none), and how many tiles that round has.  The number of parts
+// is the one with the shortest estimate, in stages of 1.33 us: ceil(tiles * parts / CUs) waves of n_k / parts stages
+// and about 8 more for a block's start and end, and the hand-over, whose bytes (512 KB for every part but one, written
+// and read past the caches) take 0.09 stages each at the 4.5 TB/s of memory.  (48 tiles of 64 stages behind a whole round: 45 us in five
+// parts, estimated 50; 136 tiles of 80 stages: 117 us in three parts, estimated 125, and whole 112, estimated 117.)
+// max_shares: what the scratch holds, in accumulator sets of a tile (LINEAR_SHARE_BYTES).
+static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares, int &parts, int &n_tail)
 {
     n_tail = n_tiles % n_cu;
     parts = 1;
-    if (n_tail == 0) return;
-    const int fit = n_cu / n_tail;  // blocks per tile that still fit one round
-    if (fit >= 4 && n_k % 4 == 0) parts = 4;
-    else if (fit >= 2 && n_k % 2 == 0) parts = 2;
+    double best = 0;
+    for (int p = 1; p <= MAX_PARTS && (p == 1 || p * 4 <= n_k) && (size_t)n_tail * (p - 1) <= max_shares; ++p) {
+        const double t = (double)((n_tail * p + n_cu - 1) / n_cu) * ((n_k + p - 1) / p + 8) + 0.09 * n_tail * (p - 1);
+        if (p == 1 || t < best) best = t, parts = p;
+    }
     if (parts == 1) n_tail = 0;
-}
-
-size_t linear_split_bytes(int n_rt, int h_in, int h_out, int n_cu)
-{
-    int parts, n_tail;
-    linear_split_shape(((n_rt + 3) / 4) * ((h_out + LBN - 1) / LBN), h_in / LBK, n_cu, parts, n_tail);
-    return (size_t)n_tail * (parts - 1) * 32 * 2 * 512 * sizeof(unsigned long long);
 }
 
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
@@ -441,19 +514,18 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem
     static bool attr_set = false;
     if (!attr_set) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_tiles_kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 2 * L_STAGE);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, L_LDS);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int n_mt = (n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
     int parts, n_tail;
-    linear_split_shape(n_tiles, a.h_in / LBK, n_cu, parts, n_tail);
-    if (parts > 1 && (linear_split_bytes(n_rt, a.h_in, a.h_out, n_cu) > split_scratch_bytes || n_tail * (parts - 1) > n_split_flags || !split_scratch))
-        parts = 1, n_tail = 0;  // no room for the partial sums: whole tiles only
+    linear_split_shape(n_tiles, a.h_in / LBK, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
+    if (2 * n_tail > n_split_flags) parts = 1, n_tail = 0;
     const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_flags, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;
-    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), 2 * L_STAGE, st, a, static_cast<const __bf16 *>(Wt),
-             row_tiles, n_rt, n_mt, sp);
+    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
+             row_tiles, n_rt, n_mt, n_nt, sp);
     return hipGetLastError();
 }
 

@@ -36,7 +36,7 @@ constexpr size_t ALIGN = 256;
 constexpr int SHRINK_MAX_RUNS = 512;
 constexpr int SHRINK_VARIANTS = lora::MAX_SHRINK_PROJS + 1;
 constexpr int SHRINK_VARIANT_SMALL = lora::MAX_SHRINK_PROJS;
-constexpr int N_LINEAR_FLAGS = 1024;  // split-off parts of lora_linear_plan's last round of tiles: fewer than CUs x 3
+constexpr int N_LINEAR_FLAGS = 1024;  // two counts per split tile of lora_linear_plan (tiles of the last round: fewer than CUs)
 constexpr double TILE_PATH_FIXED_US = 25.0;          // what the three launches of the tile path cost beside their work
 constexpr double TILE_PATH_L2_BYTES_PER_US = 10e6;  // rate at which repeated passes over a slab come out of L2
 constexpr int N_VSETS = lora::MAX_SHRINK_PROJS;  // applies that share their input run shrink-first, each with its own intermediate
@@ -324,10 +324,14 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     }
     c.off_vpart = cur;
     c.vpart_bytes = align_up(sizeof(float) * (size_t)c.vpart_rows * c.v_stride);
-    // (the fused linear kernel parks the partial sums of its split tiles in the same region: at most 48 MB,
-    // less for caches of small batches)
-    if (c.dtype == LORA_BF16)
-        c.vpart_bytes = std::max(c.vpart_bytes, std::min<size_t>((size_t)48 << 20, align_up(sizeof(float) * (size_t)c.v_stride * 8 * (size_t)c.max_tokens)));
+    // (the fused linear kernel parks the partial sums of its split tiles in the same region: two thirds of a round of
+    // 256 tiles in three parts, or fewer tiles in up to eight: 340 accumulator sets of 256 KB; less for caches of small batches)
+    if (c.dtype == LORA_BF16) {
+        const size_t row_tiles = std::min<size_t>((size_t)c.max_tokens, (size_t)c.max_tokens / LORA_TILE_TOKENS + (size_t)c.max_segments) + 2;
+        size_t col_tiles = 1;
+        for (const auto &pr : c.proj) col_tiles = std::max(col_tiles, ((size_t)pr.h_out + 255) / 256);
+        c.vpart_bytes = std::max(c.vpart_bytes, lora::LINEAR_SHARE_BYTES * std::min<size_t>(340, (row_tiles + 3) / 4 * col_tiles * 7));
+    }
     cur += c.vpart_bytes;
     // the GEMV phases hand their intermediate over as 64-bit words, one row per token and projection of a group
     c.off_vtag = cur;

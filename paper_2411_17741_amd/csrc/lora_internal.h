@@ -258,10 +258,10 @@ hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_ti
 // y = x . Wt^T + adapter update for row tiles (tiles of the plan, then plain runs of the other tokens:
 // rank 0); a.tok_list must be the list the row tiles index; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]
-// The tiles of the grid's last, partly filled round are split along k over several blocks when
-// split_scratch (device, linear_split_bytes() bytes for this shape) and split_flags (device, zero between
-// launches, one per split-off part) have room; fault: raised when the bounded wait for a part gives up.
-size_t linear_split_bytes(int n_rt, int h_in, int h_out, int n_cu);
+// The tiles of the grid's last, partly filled round are split along k over several blocks as far as split_scratch
+// (device; LINEAR_SHARE_BYTES for every part of a tile but one) and split_flags (device, zero between launches, two
+// per split tile) have room; fault: raised when the bounded wait for a part gives up.
+constexpr size_t LINEAR_SHARE_BYTES = (size_t)256 * 256 * sizeof(float);  // a tile's accumulators
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
                                size_t split_scratch_bytes, uint32_t *split_flags, int n_split_flags, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done);
