@@ -343,9 +343,10 @@ int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32
 
 /* The same for a list of (layer, projection, x, base_out): the result is that of n calls of
  * lora_apply_plan in order on `stream` (one iteration's worth of applies with a single trip
- * through the binding).  Up to 4 consecutive entries that read the same x (q, k, v; gate, up) and
- * do not write into it are run shrink-first -- one pass over x for all of them, then their updates
- * of base_out.  Nothing is enqueued if any entry fails validation. */
+ * through the binding).  Consecutive entries that do not depend on each other (no base_out overlaps
+ * another entry's base_out or any entry's x) run as batches of up to 64: one launch per phase for all of them, and one
+ * pass over x for those that read the same x (q, k, v; gate, up; up to 4 neighbours).  Nothing is
+ * enqueued if any entry fails validation. */
 typedef struct {
     int32_t layer, proj;
     const void *x;  /* device [T][h_in] */

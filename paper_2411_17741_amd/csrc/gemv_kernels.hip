@@ -49,6 +49,20 @@ __device__ __forceinline__ uint4 load_slab16(const char *p)
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
+// What the bodies need of one projection and of the launch, whichever of the two kernels below runs them
+struct GemvUse {
+    const char *proj_base;
+    int64_t row_bytes;
+    const char *x;
+    char *y;
+    float *y32;
+    unsigned long long *vw;
+    int32_t *fault;
+    int h_in, h_out;
+    uint32_t epoch;
+    float scale;
+};
+
 // A work item as a wavefront holds it: every field the same in all lanes and said to be so, so that the
 // fields and the addresses built from them stay in scalar registers; the tokens as four named members
 // (an array indexed by a lane's token number would be kept in scratch memory).
@@ -88,7 +102,7 @@ __device__ __forceinline__ void put_word(unsigned long long *p, uint32_t epoch, 
 // One word per token of the batch and lane (word `lane` of the token's row; `need` says which lanes'
 // words exist).  One launch: polls until every needed word of the wavefront carries this launch's
 // number; bounded -- a wavefront that gives up raises the fault flag and does no work.
-__device__ __forceinline__ bool fetch_words(const GemvArgs &a, const unsigned long long *const (&p)[TB], bool need, int nt,
+__device__ __forceinline__ bool fetch_words(const GemvUse &a, const unsigned long long *const (&p)[TB], bool need, int nt,
                                             uint32_t (&out)[TB])
 {
     if (a.epoch == 0) {
@@ -132,7 +146,7 @@ __device__ __forceinline__ bool fetch_words(const GemvArgs &a, const unsigned lo
 // through LDS.  NT = 1, 2 or 4 (a batch of 3 runs as one of 4 with its first token repeated).
 // ---------------------------------------------------------------------------------------
 template <typename E, int NT>
-__device__ __forceinline__ void gemv_shrink_item(const GemvArgs &a, const GemvProj &pj, const ItemU it, int nt, float (*red)[16])
+__device__ __forceinline__ void gemv_shrink_item(const GemvUse &a, const ItemU it, int nt, float (*red)[16])
 {
     constexpr int U = sizeof(E) == 2 ? 2 : 1;  // runs per wavefront and pass (fp32 chunks take twice the registers)
     constexpr int NV = 4 * NT;                 // values folded; value 4t + r is row r of token t
@@ -143,11 +157,11 @@ __device__ __forceinline__ void gemv_shrink_item(const GemvArgs &a, const GemvPr
     int j0, n_rows;
     gemv_shrink_rows(as_item(it), j0, n_rows);
     const char *arow[4], *xrow[NT];
-    const char *slab = pj.proj_base + (int64_t)it.row * pj.row_bytes;
+    const char *slab = a.proj_base + (int64_t)it.row * a.row_bytes;
 #pragma unroll
     for (int r = 0; r < 4; ++r) arow[r] = slab + (size_t)(j0 + r) * row_b;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) xrow[t] = static_cast<const char *>(a.x) + (size_t)(t < nt ? it.tok(t) : it.tok0) * row_b;
+    for (int t = 0; t < NT; ++t) xrow[t] = a.x + (size_t)(t < nt ? it.tok(t) : it.tok0) * row_b;
 
     float acc[4][NT];
 #pragma unroll
@@ -202,9 +216,9 @@ __device__ __forceinline__ void gemv_shrink_item(const GemvArgs &a, const GemvPr
         pr[0] = (__bf16)(s * val);
         pr[1] = (__bf16)(s * nxt);
         if (lane < NV && t < nt && (r & 1) == 0)
-            put_word(pj.vw + (size_t)tok * 64 + ((j0 + r) >> 1), a.epoch, __builtin_bit_cast(uint32_t, pr));
+            put_word(a.vw + (size_t)tok * 64 + ((j0 + r) >> 1), a.epoch, __builtin_bit_cast(uint32_t, pr));
     } else {
-        if (lane < NV && t < nt) put_word(pj.vw + (size_t)tok * 128 + j0 + r, a.epoch, __float_as_uint(val));
+        if (lane < NV && t < nt) put_word(a.vw + (size_t)tok * 128 + j0 + r, a.epoch, __float_as_uint(val));
     }
 }
 
@@ -229,7 +243,7 @@ typedef float gv_floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 gv_bf16x4 __attribute__((ext_vector_type(4)));
 
 template <int G, int KS>
-__device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvProj &pj, const ItemU it, int nt, int c0, int c1,
+__device__ __forceinline__ void gemv_expand_mfma(const GemvUse &a, const ItemU it, int nt, int c0, int c1,
                                                  uint32_t *vb /* this wavefront's LDS: [TB][64] words */)
 {
     constexpr int NQ = 16 / KS;   // column spans (one accumulator each) of a whole unit
@@ -237,15 +251,15 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvPr
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int rs = rank_storage(it.rank), rs8 = rs >> 3;
     const int n_q = (c1 - c0) / SPAN;  // spans of this unit (widths are multiples of 64)
-    const char *Bp = pj.proj_base + (int64_t)it.row * pj.row_bytes + (size_t)rs * a.h_in * 2 + (size_t)c0 * 16;
+    const char *Bp = a.proj_base + (int64_t)it.row * a.row_bytes + (size_t)rs * a.h_in * 2 + (size_t)c0 * 16;
 
     // lane part of the Bp addresses: (granule * h_out + column within the span) * 16 bytes
     uint32_t boff[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
         if constexpr (G == 4) boff[ks] = (uint32_t)lane * 16u;                                                 // group g, granule 0
-        else if constexpr (G == 2) boff[ks] = ((uint32_t)(g & 1) * pj.h_out + 16u * (g >> 1) + m) * 16u;       // group g / 2, granule g % 2
-        else boff[ks] = ((uint32_t)min(4 * ks + g, rs8 - 1) * pj.h_out + m) * 16u;  // granules past the stored rank repeat the last (they meet zeros)
+        else if constexpr (G == 2) boff[ks] = ((uint32_t)(g & 1) * a.h_out + 16u * (g >> 1) + m) * 16u;       // group g / 2, granule g % 2
+        else boff[ks] = ((uint32_t)min(4 * ks + g, rs8 - 1) * a.h_out + m) * 16u;  // granules past the stored rank repeat the last (they meet zeros)
     }
     // all loads up front, unconditional: spans past the unit repeat its first
     uint4 br[NQ][KS];
@@ -259,8 +273,8 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvPr
     const int t = m & 3, gq = m >> 2;
     const bool live = gq < G && t < nt;
     const int tok_l = live ? it.tok(t) : it.tok0;
-    const uint32_t yoff = (uint32_t)tok_l * pj.h_out + (live ? 16 * gq : 0) + 4 * g;  // elements from column c0 of row 0
-    const char *ybase = static_cast<const char *>(pj.y) + (size_t)c0 * 2;
+    const uint32_t yoff = (uint32_t)tok_l * a.h_out + (live ? 16 * gq : 0) + 4 * g;  // elements from column c0 of row 0
+    const char *ybase = a.y + (size_t)c0 * 2;
     uint2 yv[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) yv[q] = *reinterpret_cast<const uint2 *>(ybase + (q < n_q ? q * SPAN * 2 : 0) + yoff * 2u);
@@ -268,7 +282,7 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvPr
     // the intermediate: word `lane` of every token's row holds ranks 2 lane, 2 lane + 1
     const unsigned long long *vp[TB];
 #pragma unroll
-    for (int tt = 0; tt < TB; ++tt) vp[tt] = pj.vw + (size_t)(tt < nt ? it.tok(tt) : it.tok0) * 64 + lane;
+    for (int tt = 0; tt < TB; ++tt) vp[tt] = a.vw + (size_t)(tt < nt ? it.tok(tt) : it.tok0) * 64 + lane;
     uint32_t vword[TB];
     if (!fetch_words(a, vp, 2 * lane < rs, nt, vword)) return;
 #pragma unroll
@@ -295,11 +309,11 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvPr
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gv_bf16x8, br[q][ks]), vop[ks], acc, 0, 0, 0);
         return acc;
     };
-    if (pj.y32) {  // uniform
+    if (a.y32) {  // uniform
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const gv_floatx4 acc = product(q);
-            if (live && q < n_q) *reinterpret_cast<gv_floatx4 *>(pj.y32 + (size_t)c0 + q * SPAN + yoff) = acc;
+            if (live && q < n_q) *reinterpret_cast<gv_floatx4 *>(a.y32 + (size_t)c0 + q * SPAN + yoff) = acc;
         }
         return;
     }
@@ -318,19 +332,19 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvArgs &a, const GemvPr
 
 // expand, fp32 (the small full-precision configuration): granule loop on the vector ALUs, s.v of the
 // item's tokens staged in this wavefront's LDS rows.
-__device__ __forceinline__ void gemv_expand_f32(const GemvArgs &a, const GemvProj &pj, const ItemU it, int nt, int c0, int c1,
+__device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it, int nt, int c0, int c1,
                                                 float *vs /* [TB][128] */)
 {
     const int lane = threadIdx.x & 63;
     const int rs = rank_storage(it.rank), rs8 = rs >> 3;
     const float s = a.scale * it.alpha;
-    const float *Bp = reinterpret_cast<const float *>(pj.proj_base + (int64_t)it.row * pj.row_bytes) + (size_t)rs * a.h_in;
-    float *y = static_cast<float *>(pj.y);
+    const float *Bp = reinterpret_cast<const float *>(a.proj_base + (int64_t)it.row * a.row_bytes) + (size_t)rs * a.h_in;
+    float *y = reinterpret_cast<float *>(a.y);
     for (int half = 0; half < 2; ++half) {
         const int j = half * 64 + lane;
         const unsigned long long *vp[TB];
 #pragma unroll
-        for (int tt = 0; tt < TB; ++tt) vp[tt] = pj.vw + (size_t)(tt < nt ? it.tok(tt) : it.tok0) * 128 + j;
+        for (int tt = 0; tt < TB; ++tt) vp[tt] = a.vw + (size_t)(tt < nt ? it.tok(tt) : it.tok0) * 128 + j;
         uint32_t vword[TB] = {0u, 0u, 0u, 0u};
         if (half * 64 < rs) {  // uniform
             if (!fetch_words(a, vp, j < rs, nt, vword)) return;
@@ -346,7 +360,7 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvArgs &a, const GemvPro
         for (int tt = 0; tt < TB; ++tt) acc[tt] = 0.f;
         for (int j8 = 0; j8 < rs8; ++j8) {
             float bf[8];
-            unpack_chunk(load_chunk(Bp + ((size_t)j8 * pj.h_out + n) * 8), bf);
+            unpack_chunk(load_chunk(Bp + ((size_t)j8 * a.h_out + n) * 8), bf);
 #pragma unroll
             for (int tt = 0; tt < TB; ++tt)
 #pragma unroll
@@ -355,16 +369,45 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvArgs &a, const GemvPro
 #pragma unroll
         for (int tt = 0; tt < TB; ++tt) {
             if (tt < nt) {
-                const size_t idx = (size_t)it.tok(tt) * pj.h_out + n;
-                if (pj.y32) pj.y32[idx] = acc[tt];
+                const size_t idx = (size_t)it.tok(tt) * a.h_out + n;
+                if (a.y32) a.y32[idx] = acc[tt];
                 else y[idx] += acc[tt];
             }
         }
     }
 }
 
+template <typename E>
+__device__ __forceinline__ void gemv_shrink_work(const GemvUse &a, const ItemU it, float (*red)[16])
+{
+    const int nt = it.n_tok();
+    if (nt == 1) gemv_shrink_item<E, 1>(a, it, nt, red);  // uniform over the block
+    else if (nt == 2) gemv_shrink_item<E, 2>(a, it, nt, red);
+    else gemv_shrink_item<E, 4>(a, it, nt, red);
+}
+
+template <typename E>
+__device__ __forceinline__ void gemv_expand_work(const GemvUse &a, const ItemU it, uint32_t sc, uint32_t *stage /* this wavefront's */)
+{
+    int c0, c1;
+    gemv_expand_cols(as_item(it), (int)sc, a.h_out, c0, c1);
+    if (c0 >= c1) return;
+    const int nt = it.n_tok();
+    if constexpr (sizeof(E) == 2) {
+        const int rs8 = rank_storage(it.rank) >> 3;  // uniform over the wavefront
+        if (rs8 == 1) gemv_expand_mfma<4, 1>(a, it, nt, c0, c1, stage);
+        else if (rs8 == 2) gemv_expand_mfma<2, 1>(a, it, nt, c0, c1, stage);
+        else if (rs8 <= 4) gemv_expand_mfma<1, 1>(a, it, nt, c0, c1, stage);
+        else if (rs8 <= 8) gemv_expand_mfma<1, 2>(a, it, nt, c0, c1, stage);
+        else if (rs8 <= 12) gemv_expand_mfma<1, 3>(a, it, nt, c0, c1, stage);
+        else gemv_expand_mfma<1, 4>(a, it, nt, c0, c1, stage);
+    } else {
+        gemv_expand_f32(a, it, nt, c0, c1, reinterpret_cast<float *>(stage));
+    }
+}
+
 // ---------------------------------------------------------------------------------------
-// the kernel: blocks of 4 wavefronts.  Blocks [0, n_proj * n_gs) are the shrink blocks, one (item,
+// the kernels: blocks of 4 wavefronts.  Blocks [0, n_proj * n_gs) are the shrink blocks, one (item,
 // projection) each; the rest hold 4 expand wavefronts each, one unit = (projection, item, super-chunk)
 // per wavefront.  Shrink blocks come first in the grid and wait for nothing, so waiting expand
 // wavefronts cannot starve them; waits are bounded all the same.
@@ -380,15 +423,14 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
     __shared__ __attribute__((aligned(16))) uint32_t stage[4][sizeof(E) == 2 ? TB * 64 : TB * 128];
     const uint32_t n_proj = n_proj_phase & 0xffu, phase = n_proj_phase >> 8;
     const uint32_t n_shrink = phase == 2 ? 0u : n_proj * n_gs;
+    auto use = [&](uint32_t proj) {
+        const GemvProj &q = a.p[proj];
+        return GemvUse{q.proj_base, q.row_bytes, static_cast<const char *>(a.x), static_cast<char *>(q.y), q.y32, q.vw, a.fault, a.h_in, q.h_out, a.epoch, a.scale};
+    };
     if (blockIdx.x < n_shrink) {
         uint32_t item, proj;
         gemv_shrink_block(blockIdx.x, n_gs, n_proj, item, proj);
-        const ItemU it = load_item(gs + item);
-        const GemvProj pj = a.p[proj];
-        const int nt = it.n_tok();
-        if (nt == 1) gemv_shrink_item<E, 1>(a, pj, it, nt, red);  // uniform over the block
-        else if (nt == 2) gemv_shrink_item<E, 2>(a, pj, it, nt, red);
-        else gemv_shrink_item<E, 4>(a, pj, it, nt, red);
+        gemv_shrink_work<E>(use(proj), load_item(gs + item), red);
     } else {
         if (phase == 1) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -397,32 +439,46 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
         if (unit >= (uint32_t)ue3) return;  // (entries past the group repeat its last)
         uint32_t proj, item, sc;
         gemv_expand_unit(unit, m, proj, item, sc);
-        const ItemU it = load_item(ge + item);
-        const GemvProj pj = a.p[proj];
-        int c0, c1;
-        gemv_expand_cols(as_item(it), (int)sc, pj.h_out, c0, c1);
-        if (c0 >= c1) return;
-        const int nt = it.n_tok();
-        if constexpr (sizeof(E) == 2) {
-            const int rs8 = rank_storage(it.rank) >> 3;  // uniform over the wavefront
-            if (rs8 == 1) gemv_expand_mfma<4, 1>(a, pj, it, nt, c0, c1, stage[w]);
-            else if (rs8 == 2) gemv_expand_mfma<2, 1>(a, pj, it, nt, c0, c1, stage[w]);
-            else if (rs8 <= 4) gemv_expand_mfma<1, 1>(a, pj, it, nt, c0, c1, stage[w]);
-            else if (rs8 <= 8) gemv_expand_mfma<1, 2>(a, pj, it, nt, c0, c1, stage[w]);
-            else if (rs8 <= 12) gemv_expand_mfma<1, 3>(a, pj, it, nt, c0, c1, stage[w]);
-            else gemv_expand_mfma<1, 4>(a, pj, it, nt, c0, c1, stage[w]);
-        } else {
-            gemv_expand_f32(a, pj, it, nt, c0, c1, reinterpret_cast<float *>(stage[w]));
-        }
+        gemv_expand_work<E>(use(proj), load_item(ge + item), sc, stage[w]);
     }
 }
 
-// zeroes the hand-over words of the listed tokens: one block per token
+// The same for a batch of groups (GemvBatch): every projection brings its own x.  What a launch of one group costs beside
+// its bytes -- the gap to the kernel before it, the ramp, the hand-over at its end, 5 to 6 us -- is paid once per batch.
 template <typename E>
-__global__ __launch_bounds__(64) void gemv_clear_kernel(unsigned long long *vw, const int32_t *__restrict__ toks)
+__global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
+{
+    __shared__ float red[4][16];
+    __shared__ __attribute__((aligned(16))) uint32_t stage[4][sizeof(E) == 2 ? TB * 64 : TB * 128];
+    const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
+    auto use = [&](uint32_t proj) {
+        const BatchProj &q = b.p[proj];
+        return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * (int64_t)sizeof(E), static_cast<const char *>(q.x), static_cast<char *>(q.y), nullptr,
+                       b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
+    };
+    if (blockIdx.x < n_shrink) {
+        uint32_t item, proj;
+        gemv_batch_shrink(blockIdx.x, b.m, proj, item);
+        if (item >= b.m.n_gs) return;
+        gemv_shrink_work<E>(use(proj), load_item(b.gs + item), red);
+    } else {
+        if (b.m.phase == 1) return;
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
+        if (unit >= b.m.n_units) return;
+        uint32_t super, item;
+        gemv_batch_unit(unit, b.m, super, item);
+        const uint32_t s = (b.supers[super >> 1] >> (16 * (super & 1))) & 0xffffu;
+        gemv_expand_work<E>(use(s & 0xffu), load_item(b.ge + item), s >> 8, stage[w]);
+    }
+}
+
+// zeroes the hand-over words of the listed tokens: one block per token and set
+template <typename E>
+__global__ __launch_bounds__(64) void gemv_clear_kernel(unsigned long long *vw, uint64_t vw_set, const int32_t *__restrict__ toks)
 {
     constexpr int WPT = words_per_token<E>();
-    unsigned long long *row = vw + (size_t)toks[blockIdx.x] * WPT;
+    unsigned long long *row = vw + blockIdx.y * vw_set + (size_t)toks[blockIdx.x] * WPT;
     for (int i = threadIdx.x; i < WPT; i += 64) row[i] = 0ull;
 }
 
@@ -431,11 +487,11 @@ size_t gemv_handover_bytes(int dtype, int64_t max_tokens)
     return sizeof(unsigned long long) * (size_t)max_tokens * (dtype == LORA_BF16 ? words_per_token<__bf16>() : words_per_token<float>());
 }
 
-hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, const int32_t *toks, int n, hipStream_t st)
+hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, uint64_t vw_set, int sets, const int32_t *toks, int n, hipStream_t st)
 {
-    if (n <= 0) return hipSuccess;
-    if (dtype == LORA_BF16) hipLaunchKernelGGL(gemv_clear_kernel<__bf16>, dim3(n), dim3(64), 0, st, vw, toks);
-    else hipLaunchKernelGGL(gemv_clear_kernel<float>, dim3(n), dim3(64), 0, st, vw, toks);
+    if (n <= 0 || sets <= 0) return hipSuccess;
+    if (dtype == LORA_BF16) hipLaunchKernelGGL(gemv_clear_kernel<__bf16>, dim3(n, sets), dim3(64), 0, st, vw, vw_set, toks);
+    else hipLaunchKernelGGL(gemv_clear_kernel<float>, dim3(n, sets), dim3(64), 0, st, vw, vw_set, toks);
     return hipGetLastError();
 }
 
@@ -454,6 +510,25 @@ hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream
                      m.unit_end[2], m.unit_end[3], m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a);
     };
     if (a.epoch) {
+        go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
+    } else {
+        go(1u, n_shrink, LORA_K_GEMV_SHRINK, nullptr);
+        go(2u, n_expand, LORA_K_GEMV_EXPAND, done);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+{
+    if (b.m.n_gs == 0 || b.m.n_ge == 0 || b.m.n_proj == 0) return hipSuccess;
+    const unsigned n_shrink = b.m.n_proj * b.m.shrink_blocks, n_expand = (b.m.n_units + 3) / 4;
+    auto go = [&](uint32_t phase, unsigned blocks, int kind, hipEvent_t ev) {
+        GemvBatch q = b;
+        q.m.phase = phase;
+        if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, q);
+        else launch_k(tm, ev, kind, gemv_batch_kernel<float>, dim3(blocks), dim3(256), 0, st, q);
+    };
+    if (b.epoch) {
         go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
     } else {
         go(1u, n_shrink, LORA_K_GEMV_SHRINK, nullptr);

@@ -30,16 +30,21 @@ constexpr int N_STAGES = 2;
 constexpr size_t STAGE_BYTES = (size_t)16 << 20;
 constexpr int N_APPLY_EVENTS = 64;
 constexpr size_t ALIGN = 256;
-// Tile shrink: at most this many runs per launch (two resident blocks per compute unit of a 256-unit part), and
-// the variants of the run tables a plan carries: one per number of projections served by one launch, and one with
-// few runs for the small fixed scratch.
+// Tile shrink: at most this many runs per projection (two resident blocks per compute unit of a 256-unit part), and
+// the variants of the run tables a plan carries: one per number of projections served by one launch up to a group's,
+// one with few runs for the small fixed scratch, and two with few runs for batches of many projections.
 constexpr int SHRINK_MAX_RUNS = 512;
-constexpr int SHRINK_VARIANTS = lora::MAX_SHRINK_PROJS + 1;
-constexpr int SHRINK_VARIANT_SMALL = lora::MAX_SHRINK_PROJS;
+constexpr int SHRINK_VARIANT_SMALL = lora::GROUP_MAX_PROJS;
+constexpr int SHRINK_VARIANT_BATCH = SHRINK_VARIANT_SMALL + 1;
+constexpr int SHRINK_BATCH_RUNS[] = {64, 32};
+constexpr int SHRINK_VARIANTS = SHRINK_VARIANT_BATCH + 2;
+constexpr int SHRINK_BATCH_BLOCKS = 1024;  // a batch's launch has at most this many blocks, where a table is small enough
 constexpr int N_LINEAR_FLAGS = 1024;  // two counts per split tile of lora_linear_plan (tiles of the last round: fewer than CUs)
 constexpr double TILE_PATH_FIXED_US = 25.0;          // what the three launches of the tile path cost beside their work
 constexpr double TILE_PATH_L2_BYTES_PER_US = 10e6;  // rate at which repeated passes over a slab come out of L2
-constexpr int N_VSETS = lora::MAX_SHRINK_PROJS;  // applies that share their input run shrink-first, each with its own intermediate
+// Applies that run together in one batch each have their own copy of the intermediate (a set): as many sets as fit into
+// BATCH_SCRATCH_BYTES (0.2 % of the card's memory), a group's at least.  64 one-token requests: 4 MB for 64 sets.
+constexpr size_t BATCH_SCRATCH_BYTES = (size_t)512 << 20;
 
 size_t align_up(size_t v, size_t a = ALIGN) { return (v + a - 1) / a * a; }
 
@@ -172,6 +177,7 @@ struct lora_cache {
     std::vector<size_t> row_bytes;  // [n_proj] (h_in + h_out) * element size
     int64_t total_rows = 0;
     size_t off_fault = 0, off_vpart = 0, off_vtag = 0, v_set_bytes = 0, vtag_set_bytes = 0;
+    int n_sets = lora::GROUP_MAX_PROJS;  // copies of the intermediate buffers: projections of a batch
     uint32_t tag_epoch = 0;  // one-launch GEMV launches so far; the number the words of the latest one carry
     unsigned long long cap_id = 0;
     uint64_t cap_plan = 0;  // build number of the plan
@@ -313,13 +319,16 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     cur += align_up(sizeof(uint32_t) * N_LINEAR_FLAGS);
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
-    cur += c.v_set_bytes * N_VSETS;
-    // partial sums of the tile shrink: two slots per run and projection of a group; a launch has at most
-    // SHRINK_MAX_RUNS blocks whatever the group's size, and a batch of few tiles has few runs (a piece is at least
-    // two of the parts a tile's k range is cut into)
+    c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
+    c.n_sets = (int)std::min<size_t>(std::min<size_t>(lora::BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
+                                     std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / (c.v_set_bytes + c.vtag_set_bytes)));
+    cur += c.v_set_bytes * c.n_sets;
+    // partial sums of the tile shrink: two slots per run and projection; a launch has at most SHRINK_MAX_RUNS blocks
+    // for a group whatever its size, twice that for a batch, and a batch of few tiles has few runs (a piece is at
+    // least two of the parts a tile's k range is cut into)
     {
         const int64_t tiles = std::max<int64_t>(1, ((int64_t)c.max_tokens + LORA_TILE_TOKENS - 1) / LORA_TILE_TOKENS);
-        const int64_t runs = std::min<int64_t>(SHRINK_MAX_RUNS, 16 * N_VSETS * tiles);
+        const int64_t runs = std::min<int64_t>(2 * SHRINK_MAX_RUNS, 16 * c.n_sets * tiles);
         c.vpart_rows = c.dtype == LORA_BF16 ? 2 * lora::SHRINK_SLOT_ROWS * runs : 0;
     }
     c.off_vpart = cur;
@@ -335,8 +344,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     cur += c.vpart_bytes;
     // the GEMV phases hand their intermediate over as 64-bit words, one row per token and projection of a group
     c.off_vtag = cur;
-    c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
-    cur += c.vtag_set_bytes * N_VSETS;
+    cur += c.vtag_set_bytes * c.n_sets;
     c.off_plans = cur;
     cur += c.plan_cap * (size_t)(c.n_user_plans + N_INTERNAL_PLANS);
     c.off_stage = cur;
@@ -708,8 +716,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
         for (int v = 0; v < SHRINK_VARIANTS && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
             if (v == SHRINK_VARIANT_SMALL && T > LORA_STATIC_MAX_TOKENS) continue;  // lora_apply_plan_static refuses such a batch
-            const int n = v == SHRINK_VARIANT_SMALL ? 1 : v + 1;
-            int64_t max_runs = slots / 8 / n * 8;
+            const int n = v >= SHRINK_VARIANT_SMALL ? 1 : v + 1;
+            int64_t max_runs = v >= SHRINK_VARIANT_BATCH ? SHRINK_BATCH_RUNS[v - SHRINK_VARIANT_BATCH] : slots / 8 / n * 8;
             max_runs = std::min(max_runs, (v == SHRINK_VARIANT_SMALL ? STATIC_VPART_ROWS : c.vpart_rows) / (2 * lora::SHRINK_SLOT_ROWS) / n / 8 * 8);
             build_shrink_runs(dev_tiles, w.n_tiles, p.shrink_quanta, (int)std::max<int64_t>(8, max_runs), shrink_runs[v]);
         }
@@ -939,7 +947,7 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
     if (hipHostMalloc(reinterpret_cast<void **>(&c->fault_host), 64, hipHostMallocMapped) != hipSuccess ||
         hipHostGetDevicePointer(reinterpret_cast<void **>(&c->fault_dev), c->fault_host, 0) != hipSuccess ||
         (*c->fault_host = 0, false) ||
-        hipMemset(c->pool + c->off_vtag, 0, c->vtag_set_bytes * N_VSETS) != hipSuccess ||
+        hipMemset(c->pool + c->off_vtag, 0, c->vtag_set_bytes * c->n_sets) != hipSuccess ||
         hipMemset(c->pool + c->off_fault, 0, sizeof(uint32_t) * N_LINEAR_FLAGS) != hipSuccess) {
         g_last_hip = (int)hipGetLastError();
         delete c;
@@ -1629,40 +1637,92 @@ static int validate_apply(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_
 // shrink items up to which the one-launch GEMV form is chosen: measured faster than two launches up to
 // 7726 items (2048 one-token requests over 300 adapters: 83 against 86 us); not measured beyond
 constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
+constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 20;  // the same for a batch
+static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
 
-// Applies descs[0 .. n), n <= N_VSETS: one projection, or several that read the same x and do not
-// write to it.  Those run shrink-first, each with its own copy of the intermediate buffers: one
-// tile-shrink launch for all of them (x is then fetched from memory once), their GEMV launches,
-// then their expands.
 static Scratch pool_scratch(lora_cache_t *c)
 {
-    return Scratch{c->pool + c->off_v, c->v_set_bytes, N_VSETS, c->pool + c->off_vpart, c->vpart_rows, false,
+    return Scratch{c->pool + c->off_v, c->v_set_bytes, c->n_sets, c->pool + c->off_vpart, c->vpart_rows, false,
                    c->pool + c->off_vtag, c->vtag_set_bytes, &c->tag_epoch, &c->cap_id, &c->cap_plan, &c->cap_sets};
 }
 
-// The run table of a tile-shrink launch for n projections, and where their partial sums go in `vpart`.
-static int shrink_setup(const lora_cache_t *c, const lora_plan_t *p, int n, char *vpart, int64_t vpart_rows, bool small, lora::ShrinkProjs &ps)
+// The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
+// rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
+// SHRINK_BATCH_BLOCKS blocks.
+static int shrink_variant(const lora_plan_t *p, int n, int64_t vpart_rows, bool small)
 {
-    const int v = small ? SHRINK_VARIANT_SMALL : n - 1;
-    if (n < 1 || n > lora::MAX_SHRINK_PROJS || (small && n != 1)) return LORA_E_INVAL;
-    ps.n = n;
-    ps.n_runs = p->shrink_runs[v];
-    if (p->n_tiles > 0 && ps.n_runs == 0) return LORA_E_STATE;  // the plan carries no such table
-    ps.quanta = p->shrink_quanta;
-    ps.any_pieces = p->shrink_pieces[v] ? 1 : 0;
-    ps.cuts = reinterpret_cast<const lora::ShrinkCut *>(p->dev + p->off_cuts[v]);
-    ps.sums = reinterpret_cast<const lora::ShrinkSum *>(p->dev + p->off_sums[v]);
-    const int64_t rows_per_proj = 2 * (int64_t)lora::SHRINK_SLOT_ROWS * ps.n_runs;
-    if (rows_per_proj * n > vpart_rows) return LORA_E_NOMEM;
-    for (int i = 0; i < lora::MAX_SHRINK_PROJS; ++i)
-        ps.part[i] = i < n ? reinterpret_cast<float *>(vpart) + (size_t)i * rows_per_proj * c->v_stride : nullptr;
+    if (small) return SHRINK_VARIANT_SMALL;
+    if (n <= lora::GROUP_MAX_PROJS) return n - 1;
+    const int order[] = {0, 1, 2, 3, SHRINK_VARIANT_BATCH, SHRINK_VARIANT_BATCH + 1};  // falling number of runs
+    for (int v : order)
+        if (p->shrink_runs[v] * n <= SHRINK_BATCH_BLOCKS && 2 * (int64_t)lora::SHRINK_SLOT_ROWS * p->shrink_runs[v] * n <= vpart_rows) return v;
+    return SHRINK_VARIANT_BATCH + 1;
+}
+// The tile kernels' arguments but for the projections; n: how many there are.
+static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, const Scratch &sc, float scale, lora::TileBatch &tb)
+{
+    if (n < 1 || n > lora::BATCH_MAX_PROJS || n > sc.n_sets) return LORA_E_INVAL;
+    const int v = shrink_variant(p, n, sc.vpart_rows, sc.small);
+    tb.n = n;
+    tb.n_runs = p->shrink_runs[v];
+    if (p->n_tiles > 0 && tb.n_runs == 0) return LORA_E_STATE;  // the plan carries no such table
+    tb.quanta = p->shrink_quanta;
+    tb.n_tiles = p->n_tiles;
+    tb.v_stride = c->v_stride;
+    tb.any_pieces = p->shrink_pieces[v] ? 1 : 0;
+    tb.scale = scale;
+    tb.tiles = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_tiles);
+    tb.cuts = reinterpret_cast<const lora::ShrinkCut *>(p->dev + p->off_cuts[v]);
+    tb.sums = reinterpret_cast<const lora::ShrinkSum *>(p->dev + p->off_sums[v]);
+    tb.tok_list = reinterpret_cast<const int32_t *>(p->dev);
+    tb.v = reinterpret_cast<float *>(sc.v);
+    tb.part = reinterpret_cast<float *>(sc.vpart);
+    const int64_t rows_per_proj = 2 * (int64_t)lora::SHRINK_SLOT_ROWS * tb.n_runs;
+    if (rows_per_proj * n > sc.vpart_rows) return LORA_E_NOMEM;
+    tb.v_set = sc.v_set_bytes / sizeof(float);
+    tb.part_set = (uint64_t)rows_per_proj * c->v_stride;
     return LORA_OK;
+}
+static lora::BatchProj batch_proj(const lora_cache_t *c, const lora_apply_desc_t &d)
+{
+    return lora::BatchProj{c->pool + (size_t)d.layer * c->layer_stride + c->proj_off[d.proj], d.x, d.base_out, c->proj[d.proj].h_in, c->proj[d.proj].h_out};
+}
+
+// One-launch GEMV form under stream capture, for n projections with plan p.  A graph freezes the launch number, so a
+// replay could take the words its own launch wrote in the replay before for fresh ones.  Not when another launch of the
+// same graph has written the same words in between (its number differs): that holds for every launch after the first of a
+// capture that works on the same plan with at least as many projections.  Otherwise the words are cleared first, by a
+// small kernel that becomes part of the graph.
+static int clear_words_for_capture(lora_cache_t *c, lora_plan_t *p, int n, hipStream_t st, const Scratch &sc)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    unsigned long long cap = 0;
+    if (hipStreamGetCaptureInfo(st, &cs, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cs = hipStreamCaptureStatusNone;
+    }
+    if (cs == hipStreamCaptureStatusNone) return LORA_OK;
+    const bool covered = cap == *sc.cap_id && p->build_seq == *sc.cap_plan && n <= *sc.cap_sets;
+    if (!covered) {
+        const int32_t *toks = reinterpret_cast<const int32_t *>(p->dev) + p->n_tile_tok;
+        HIP_TRY(lora::launch_gemv_clear(c->dtype, reinterpret_cast<unsigned long long *>(sc.vtag), sc.vtag_set_bytes / sizeof(unsigned long long), n, toks,
+                                        p->n_tok_list - p->n_tile_tok, st));
+    }
+    *sc.cap_id = cap;
+    *sc.cap_plan = p->build_seq;
+    *sc.cap_sets = n;
+    return LORA_OK;
+}
+// the one-launch form, for a launch of `items` shrink items? (after 2^32 - 1 launches the numbers would repeat)
+static bool one_gemv_launch(const lora_cache_t *c, const Scratch &sc, int64_t items, int64_t max_items)
+{
+    return *sc.epoch < UINT32_MAX - 1 && (c->fused_gemv == 2 || (c->fused_gemv == 1 && items <= max_items));
 }
 
 // The GEMV part of a group of n projections that read the same x: one launch with the in-kernel
 // hand-over when the part is small (the launch in between then costs more than the hand-over), else a
 // shrink and an expand launch.  y32[i], when set, receives projection i's update as fp32 instead of y.
-static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::ApplyArgs *a, float *const *y32, int n, bool allow_one_launch,
+static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *a, float *const *y32, int n, float scale, bool allow_one_launch,
                         hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -1676,18 +1736,18 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::ApplyArgs *
     ga.fault = c->fault_dev;
     ga.h_in = a[0].h_in;
     ga.n_ge = p->n_ge;
-    ga.scale = a[0].scale;
+    ga.scale = scale;
     int64_t units = 0;
     for (int i = 0; i < lora::GEMV_MAX_PROJS; ++i) {
         const int k = std::min(i, n - 1);  // entries past the group repeat its last
         lora::GemvProj &q = ga.p[i];
         q.proj_base = a[k].proj_base;
-        q.row_bytes = a[k].row_bytes;
+        q.row_bytes = (int64_t)(a[k].h_in + a[k].h_out) * c->esize;
         q.y = a[k].y;
         q.y32 = y32 ? y32[k] : nullptr;
         q.vw = reinterpret_cast<unsigned long long *>(sc.vtag + (size_t)k * sc.vtag_set_bytes);
         q.h_out = a[k].h_out;
-        const int32_t n_super = (a[k].h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS;
+        const int32_t n_super = supers_of(a[k].h_out);
         if (n_super > 255) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
         gm.n_super_packed |= (uint32_t)n_super << (8 * i);
         gm.super_magic[i] = lora::gemv_magic((uint32_t)n_super);
@@ -1695,39 +1755,74 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::ApplyArgs *
         gm.unit_end[i] = (int32_t)std::min<int64_t>(units, INT32_MAX);
     }
     if (units >= (1 << 24) || (int64_t)p->n_gs * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
-    // (after 2^32 - 1 one-launch applies the numbers would repeat: two launches from then on)
-    const bool one = allow_one_launch && *sc.epoch < UINT32_MAX - 1 &&
-                     (c->fused_gemv == 2 || (c->fused_gemv == 1 && (int64_t)p->n_gs * n <= FUSED_GEMV_MAX_ITEMS));
-    if (one) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        unsigned long long cap = 0;
-        if (hipStreamGetCaptureInfo(st, &cs, &cap) != hipSuccess) {
-            (void)hipGetLastError();
-            cs = hipStreamCaptureStatusNone;
-        }
-        if (cs != hipStreamCaptureStatusNone) {
-            // A graph freezes the launch number, so a replay could take the words its own launch wrote in the
-            // replay before for fresh ones.  Not when another launch of the same graph has written the same
-            // words in between (its number differs): that holds for every launch after the first of a capture
-            // that works on the same plan with at least as many projections.  Otherwise the words are cleared
-            // first, by a small kernel that becomes part of the graph.
-            const bool covered = cap == *sc.cap_id && p->build_seq == *sc.cap_plan && n <= *sc.cap_sets;
-            if (!covered) {
-                const int32_t *toks = reinterpret_cast<const int32_t *>(p->dev) + p->n_tile_tok;
-                for (int i = 0; i < n; ++i) HIP_TRY(lora::launch_gemv_clear(c->dtype, ga.p[i].vw, toks, p->n_tok_list - p->n_tile_tok, st));
-            }
-            *sc.cap_id = cap;
-            *sc.cap_plan = p->build_seq;
-            *sc.cap_sets = n;
-        }
+    if (allow_one_launch && one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_ITEMS)) {
+        if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         ga.epoch = ++*sc.epoch;
     }
     HIP_TRY(lora::launch_gemv(c->dtype, gm, ga, st, tm, done));
     return LORA_OK;
 }
 
-// `fence` (null: none) is to stand for the group's end on `st`.
-static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t *descs, int n, float scale, hipStream_t st,
+// The same for a batch of several groups.
+static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, int n, float scale, hipStream_t st, const Scratch &sc,
+                              const lora::KernelTimer *tm, hipEvent_t done)
+{
+    if (p->n_gs <= 0) return LORA_OK;
+    lora::GemvBatch b{};
+    b.gs = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_gs);
+    b.ge = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_ge);
+    b.vw = reinterpret_cast<unsigned long long *>(sc.vtag);
+    b.vw_set = sc.vtag_set_bytes / sizeof(unsigned long long);
+    b.fault = c->fault_dev;
+    b.scale = scale;
+    b.m.n_gs = (uint32_t)p->n_gs;
+    b.m.n_ge = (uint32_t)p->n_ge;
+    b.m.n_proj = (uint32_t)n;
+    b.m.by_xcd = b.m.n_gs >= lora::GEMV_BATCH_XCD_ITEMS;
+    b.m.shrink_blocks = b.m.by_xcd ? (b.m.n_gs + 7) & ~7u : b.m.n_gs;
+    b.m.div_shrink = lora::div24_of(b.m.shrink_blocks);
+    b.m.div_ge = lora::div24_of(b.m.n_ge);
+    int32_t n_super = 0;
+    for (int i = 0; i < n; ++i) {
+        b.p[i] = projs[i];
+        if (supers_of(projs[i].h_out) > 255) return LORA_E_INVAL;  // as a group's launch
+        for (int32_t k = 0; k < supers_of(projs[i].h_out); ++k, ++n_super) {
+            if (n_super >= lora::GEMV_BATCH_MAX_SUPERS) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
+            b.supers[n_super >> 1] |= ((uint32_t)i | (uint32_t)k << 8) << (16 * (n_super & 1));
+        }
+    }
+    const int64_t units = (int64_t)b.m.n_ge * n_super;
+    if (units >= (1 << 24) || (int64_t)b.m.shrink_blocks * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
+    b.m.n_units = (uint32_t)units;
+    if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_BATCH_ITEMS)) {
+        if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
+        b.epoch = ++*sc.epoch;
+    }
+    HIP_TRY(lora::launch_gemv_batch(c->dtype, b, st, tm, done));
+    return LORA_OK;
+}
+
+// How many projections, and super-chunks of projections, a batch with plan p may have: the scratch's sets, the partial sums of the
+// smallest run table of the tile shrink, and the ranges of the GEMV launch's unit arithmetic.
+static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
+{
+    int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
+    if (p->n_tiles > 0)
+        projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
+    if (p->n_gs > 0) {
+        projs = std::min<int64_t>(projs, ((1 << 24) - 1) / (p->n_gs + 7));
+        supers = std::min<int64_t>(supers, ((1 << 24) - 1) / std::max(1, p->n_ge));
+    }
+    max_projs = (int32_t)std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (a group has tables and checks of its own)
+    max_supers = (int32_t)supers;
+}
+
+// Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of
+// them.  Entries that read the same x (a group, at most GROUP_MAX_PROJS) are neighbours; group_n[i] is the size of the group that
+// starts at entry i.  The tile shrink runs first, for all entries (x of a group is then fetched from memory once), each
+// with its own copy of the intermediate buffers.
+// `fence` (null: none) is to stand for the batch's end on `st`.
+static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t *descs, const uint8_t *group_n, int n, float scale, hipStream_t st,
                          const Scratch &sc, hipEvent_t fence)
 {
     // the work lists may have been uploaded on another stream
@@ -1750,33 +1845,21 @@ static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     }
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
-    const lora::DevItem *tiles = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_tiles);
-
-    lora::ApplyArgs a[N_VSETS];
-    lora::ShrinkProjs ps;
-    if (const int rc_s = shrink_setup(c, p, n, sc.vpart, sc.vpart_rows, sc.small, ps)) return rc_s;
-    for (int i = 0; i < n; ++i) {
-        const int32_t proj = descs[i].proj;
-        a[i].proj_base = c->pool + (size_t)descs[i].layer * c->layer_stride + c->proj_off[proj];
-        a[i].row_bytes = (int64_t)c->row_bytes[proj];
-        a[i].tok_list = reinterpret_cast<const int32_t *>(p->dev);
-        a[i].x = descs[i].x;
-        a[i].y = descs[i].base_out;
-        a[i].v = reinterpret_cast<float *>(sc.v + (size_t)i * sc.v_set_bytes);
-        a[i].h_in = c->proj[proj].h_in;
-        a[i].h_out = c->proj[proj].h_out;
-        a[i].v_stride = c->v_stride;
-        a[i].scale = scale;
-        ps.proj_base[i] = a[i].proj_base;
-        ps.row_bytes[i] = a[i].row_bytes;
-        ps.v[i] = a[i].v;
+    lora::TileBatch tb;
+    if (const int rc_s = tile_setup(c, p, n, sc, scale, tb)) return rc_s;
+    // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
+    int n_groups = 0;
+    uint8_t first[lora::BATCH_MAX_PROJS];
+    for (int i = 0; i < n; i += group_n[i]) first[n_groups++] = (uint8_t)i;
+    std::stable_sort(first, first + n_groups, [&](uint8_t g, uint8_t h) { return c->proj[descs[g].proj].h_in > c->proj[descs[h].proj].h_in; });
+    for (int g = 0, i = 0; g < n_groups; ++g) {
+        const int size = group_n[first[g]], at = i;
+        for (int k = 0; k < size; ++k, ++i) {
+            tb.p[i] = batch_proj(c, descs[first[g] + k]);
+            tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
+        }
     }
-    for (int i = n; i < N_VSETS; ++i) {
-        ps.proj_base[i] = nullptr;
-        ps.row_bytes[i] = 0;
-        ps.v[i] = nullptr;
-    }
-    // The GEMV launch and the tile kernels of a group work on different tokens (rows of base_out) with different
+    // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
     // scratch: when a batch has both, the GEMV launch goes to the cache's side stream, forked off here and
     // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
     // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
@@ -1789,7 +1872,7 @@ static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     }
     // everything that reads x
     if (p->n_tiles > 0) {
-        HIP_TRY(lora::launch_mfma_shrink(a[0], ps, tiles, p->n_tiles, st, tm));
+        HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
     // joined behind the tile expands, whatever happens in between: a captured fork must not stay open
     struct Join {
@@ -1808,12 +1891,14 @@ static int enqueue_group(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     // the fence rides on the group's last kernel, where that is the last thing on `st`
     const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
-    if (const int rc_g = enqueue_gemv(c, p, a, nullptr, n, true, gemv_st, sc, tm, join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr)))
+    const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr);
+    if (const int rc_g = n_groups == 1 ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, true, gemv_st, sc, tm, gemv_done)
+                                       : enqueue_gemv_batch(c, p, tb.p, n, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
     // the updates of base_out
+    HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
     for (int i = 0; i < n; ++i) {
-        HIP_TRY(lora::launch_mfma_expand(a[i], tiles, p->n_tiles, st, tm, ride && i == n - 1 ? fence : nullptr));
         const int64_t seq = ++c->apply_seq;
         ++c->stats.applies;
         for (int32_t sl : p->slots) {
@@ -1850,7 +1935,8 @@ static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t
 {
     int32_t f;
     if (const int rc = take_fence(c, st, f)) return rc;
-    if (const int rc = enqueue_group(c, p, &d, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
+    const uint8_t one = 1;
+    if (const int rc = enqueue_batch(c, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
     publish_fence(c, p, st, f);
     return LORA_OK;
 }
@@ -1914,9 +2000,9 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     }
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
-    const lora::DevItem *tiles = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_tiles);
+    const lora::BatchProj bp = batch_proj(c, {layer, proj, x, y});
     lora::ApplyArgs a;
-    a.proj_base = c->pool + (size_t)layer * c->layer_stride + c->proj_off[proj];
+    a.proj_base = bp.proj_base;
     a.row_bytes = (int64_t)c->row_bytes[proj];
     a.tok_list = reinterpret_cast<const int32_t *>(p->dev);
     a.x = x;
@@ -1930,14 +2016,11 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     if (const int rc_f = take_fence(c, st, f)) return rc_f;
     // shrink of the tiles and of the GEMV groups (x is read, v written)
     if (p->n_tiles > 0) {
-        lora::ShrinkProjs ps;
-        if (const int rc_s = shrink_setup(c, p, 1, c->pool + c->off_vpart, c->vpart_rows, false, ps)) return rc_s;
-        for (int i = 0; i < lora::MAX_SHRINK_PROJS; ++i) {
-            ps.proj_base[i] = i ? nullptr : a.proj_base;
-            ps.row_bytes[i] = i ? 0 : a.row_bytes;
-            ps.v[i] = i ? nullptr : a.v;
-        }
-        HIP_TRY(lora::launch_mfma_shrink(a, ps, tiles, p->n_tiles, st, tm));
+        lora::TileBatch tb;
+        if (const int rc_s = tile_setup(c, p, 1, pool_scratch(c), scale, tb)) return rc_s;
+        tb.p[0] = bp;
+        tb.group[0] = 1u << 8;
+        HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
     // the adapter term of the GEMV tokens: as fp32 into the caller's workspace (row = token), or, without
     // one, into their zeroed output rows (rounded to the output type on the way)
@@ -1945,7 +2028,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         a.y32 = static_cast<float *>(workspace);
         if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + p->n_tile_tok, p->n_tok_list - p->n_tile_tok, a.h_out, st));
         float *const y32 = a.y32;
-        if (const int rc_g = enqueue_gemv(c, p, &a, &y32, 1, false, st, pool_scratch(c), tm, nullptr)) return rc_g;
+        if (const int rc_g = enqueue_gemv(c, p, &bp, &y32, 1, scale, false, st, pool_scratch(c), tm, nullptr)) return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
     lora::ApplyArgs lin = a;
@@ -1976,24 +2059,50 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
     }
     int32_t f;
     if (const int rc_f = take_fence(c, st, f)) return rc_f;
-    // runs of applies that read the same x (q, k, v; gate, up) and do not write to it go as a group
+    // Entries that do not depend on each other go as one batch: no output of the batch may overlap an input of it (an
+    // earlier entry's: it may not have been read yet; a later one's: it would be read too early) or another output (both
+    // would be updated from what was there before).  Within a batch neighbours that read the same x (q, k, v; gate, up)
+    // form groups.  An entry that overwrites its own input is a batch by itself.
+    struct Range {
+        const char *lo, *hi;
+        bool meets(const Range &o) const { return lo < o.hi && o.lo < hi; }
+    };
     const size_t e = c->esize;
+    Range in[lora::BATCH_MAX_PROJS], out[lora::BATCH_MAX_PROJS];  // inputs of the batch's groups, outputs of its entries
+    uint8_t group_n[lora::BATCH_MAX_PROJS];
+    const Scratch scratch = pool_scratch(c);
+    int32_t max_projs, max_supers;
+    batch_limits(p, scratch, max_projs, max_supers);
     for (int32_t i = 0; i < n;) {
-        int32_t g = 1;
-        const char *x0 = static_cast<const char *>(descs[i].x);
-        const size_t x_bytes = (size_t)p->T * c->proj[descs[i].proj].h_in * e;
-        auto writes_x = [&](const lora_apply_desc_t &d) {
-            const char *y0 = static_cast<const char *>(d.base_out);
-            return y0 < x0 + x_bytes && x0 < y0 + (size_t)p->T * c->proj[d.proj].h_out * e;
-        };
-        if (!writes_x(descs[i])) {
-            while (g < N_VSETS && i + g < n && descs[i + g].x == descs[i].x &&
-                   c->proj[descs[i + g].proj].h_in == c->proj[descs[i].proj].h_in && !writes_x(descs[i + g]))
-                ++g;
+        int32_t m = 0, n_in = 0, last = 0, supers = 0;  // last: entry the latest group starts at
+        for (; i + m < n && m < max_projs; ++m) {
+            const lora_apply_desc_t &d = descs[i + m];
+            const lora_proj_t &pr = c->proj[d.proj];
+            const char *x0 = static_cast<const char *>(d.x), *y0 = static_cast<const char *>(d.base_out);
+            const Range x{x0, x0 + (size_t)p->T * pr.h_in * e}, y{y0, y0 + (size_t)p->T * pr.h_out * e};
+            const bool same_x = m > 0 && d.x == descs[i + m - 1].x && pr.h_in == c->proj[descs[i + m - 1].proj].h_in;
+            bool ok = !y.meets(x);
+            for (int32_t k = 0; k < n_in && ok; ++k) ok = !in[k].meets(y);
+            for (int32_t k = 0; k < m && ok; ++k) ok = !out[k].meets(y) && (same_x || !out[k].meets(x));
+            supers += supers_of(pr.h_out);
+            const bool joins_only_group = same_x && last == 0 && m < lora::GROUP_MAX_PROJS;
+            if (m > 0 && (!ok || (supers > max_supers && !joins_only_group))) break;
+            out[m] = y;
+            if (same_x && group_n[last] < lora::GROUP_MAX_PROJS) {
+                ++group_n[last];
+            } else {
+                last = m;
+                group_n[m] = 1;
+                in[n_in++] = x;
+            }
+            if (!ok) {
+                ++m;
+                break;
+            }
         }
-        const int rc = enqueue_group(c, p, descs + i, g, scale, st, pool_scratch(c), f >= 0 && i + g == n ? c->fences[f].ev : nullptr);
+        const int rc = enqueue_batch(c, p, descs + i, group_n, m, scale, st, scratch, f >= 0 && i + m == n ? c->fences[f].ev : nullptr);
         if (rc != LORA_OK) return rc;
-        i += g;
+        i += m;
     }
     if (n > 0) publish_fence(c, p, st, f);
     return LORA_OK;

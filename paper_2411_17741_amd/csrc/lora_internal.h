@@ -98,9 +98,19 @@ inline __host__ __device__ void gemv_expand_cols(const GemvItem &it, int32_t sc,
     if (c1 > h_out) c1 = h_out;
 }
 
+// A batch: the projections one launch serves.  They do not depend on each other (no output overlaps another entry's
+// output or any entry's input), so that every phase is one launch for all of them.
+constexpr int BATCH_MAX_PROJS = 64;
+struct BatchProj {
+    const char *proj_base;    // device: first slab of this (layer, projection)
+    const void *x;            // device [T][h_in]
+    void *y;                  // device [T][h_out], in/out
+    int32_t h_in, h_out;
+};
+
 // One GEMV launch serves up to GEMV_MAX_PROJS projections that read the same activations (q, k, v;
 // gate, up): block and unit numbers map to (projection, item) by the two routines below, which the
-// kernels and lora_plan_dump share.
+// kernels and lora_plan_dump share.  (A batch of several such groups: GemvBatch further down.)
 constexpr int GEMV_MAX_PROJS = 4;
 struct GemvProj {
     const char *proj_base;    // device: first slab of this (layer, projection)
@@ -163,6 +173,58 @@ inline __host__ __device__ void gemv_expand_unit(uint32_t u, const GemvMap &m, u
     sc = r - item * n_super;
 }
 
+// floor(v / n) for v < 2^24 and 1 <= n < 2^24 as (v * mul) >> shift.  With shift = 24 + ceil(log2 n) and
+// mul = ceil(2^shift / n) = (2^shift + e) / n, e < n, the product is v / n + v * e / (n * 2^shift), and v * e < 2^shift: less than 1 / n too much
+struct Div24 {
+    uint32_t mul, shift;
+};
+inline Div24 div24_of(uint32_t n)
+{
+    uint32_t l = 0;
+    while ((1u << l) < n) ++l;
+    return Div24{(uint32_t)((((uint64_t)1 << (24 + l)) + n - 1) / n), 24 + l};
+}
+inline __host__ __device__ uint32_t div24(uint32_t v, Div24 d) { return (uint32_t)(((uint64_t)v * d.mul) >> d.shift); }
+
+// The GEMV launch of a batch (several groups of projections, each with its own x).  Blocks
+// [0, n_proj * shrink_blocks) are the shrink blocks, projection by projection; expand units go super-chunk by
+// super-chunk of all projections, items innermost.
+constexpr int GEMV_BATCH_MAX_SUPERS = 512;
+struct GemvBatchMap {
+    uint32_t n_gs, n_ge, n_proj, n_units;  // n_units = n_ge * super-chunks of all projections
+    uint32_t shrink_blocks;                // per projection: n_gs, or (by_xcd) n_gs rounded up to a multiple of 8
+    uint32_t by_xcd, phase;                // phase as in GemvMap::n_proj_phase
+    Div24 div_shrink, div_ge;              // by shrink_blocks, by n_ge
+};
+// From this many shrink items up XCD j (blocks j, j + 8, ...) takes a run of a projection's items: the items of a token
+// batch read the same x rows.  Fewer items are dealt out one by one, or some XCDs would have none.
+constexpr uint32_t GEMV_BATCH_XCD_ITEMS = 64;
+// shrink block b -> (projection, item); item >= n_gs: nothing to do
+inline __host__ __device__ void gemv_batch_shrink(uint32_t b, const GemvBatchMap &m, uint32_t &proj, uint32_t &item)
+{
+    proj = div24(b, m.div_shrink);
+    const uint32_t r = b - proj * m.shrink_blocks;
+    item = m.by_xcd ? (r & 7) * (m.shrink_blocks >> 3) + (r >> 3) : r;
+}
+// expand unit u -> (number of the super-chunk, item)
+inline __host__ __device__ void gemv_batch_unit(uint32_t u, const GemvBatchMap &m, uint32_t &super, uint32_t &item)
+{
+    super = div24(u, m.div_ge);
+    item = u - super * m.n_ge;
+}
+struct GemvBatch {
+    const GemvItem *gs, *ge;  // device: shrink and expand items
+    unsigned long long *vw;   // hand-over words of projection 0; those of projection p lie vw_set words behind those of p - 1
+    uint64_t vw_set;
+    int32_t *fault;
+    uint32_t epoch;           // as in GemvArgs
+    float scale;
+    GemvBatchMap m;
+    uint32_t supers[GEMV_BATCH_MAX_SUPERS / 2];  // per super-chunk its projection | its number there << 8, two to a word
+    BatchProj p[BATCH_MAX_PROJS];
+};
+static_assert(sizeof(GemvBatch) <= 3900, "kernel arguments are at most 4 KB");
+
 // Arguments common to the apply kernels of one (layer, projection).
 struct ApplyArgs {
     const char *proj_base;    // device: first slab of this (layer, projection)
@@ -204,10 +266,11 @@ inline void launch_k(const KernelTimer *tm, hipEvent_t done, int kind, K kernel,
 // GEMV shrink and expand of the group's projections: phase 0 as one launch (a.epoch != 0: the expand
 // wavefronts wait for the hand-over words to carry that number), phases 1 and 2 as two
 hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // bytes of one projection's hand-over words for max_tokens tokens
 size_t gemv_handover_bytes(int dtype, int64_t max_tokens);
-// zeroes the hand-over words of tokens toks[0 .. n) (device list) in `vw`
-hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, const int32_t *toks, int n, hipStream_t st);
+// zeroes the hand-over words of tokens toks[0 .. n) (device list) in `sets` sets from `vw` on, vw_set words apart
+hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, uint64_t vw_set, int sets, const int32_t *toks, int n, hipStream_t st);
 // Tile shrink.  Its work is the sequence of all tiles' k ranges, every tile's range divided into `quanta`
 // equal parts (a part is a whole number of the kernel's k stages for every projection of the cache).  A plan
 // cuts that sequence into n_runs runs of about equal cost (a tile's cost per part: its x rows plus its At
@@ -236,25 +299,32 @@ inline __host__ __device__ int32_t shrink_part_stage(int32_t part, int32_t quant
     return (int32_t)(((int64_t)part * n_st + quanta / 2) / quanta);
 }
 constexpr int SHRINK_STAGE_K = 128;
-// The projections one tile-shrink launch serves (they read the same x): slab base and row pitch,
-// destination of the intermediate, scratch for the partial sums (2 * n_runs slots of SHRINK_SLOT_ROWS rows).
-constexpr int MAX_SHRINK_PROJS = 4;
-struct ShrinkProjs {
-    int n;
-    int n_runs, quanta;       // n_runs: a multiple of 8 (run r is worked on by XCD r / (n_runs / 8))
-    int any_pieces;           // some tile is worked on in pieces: the reduce launch is needed
+// The projections one launch of the tile kernels serves, and the run table the shrink works through for each of them:
+// projections that read the same x are neighbours (a group); projection i's intermediate lies v_set floats behind that of
+// i - 1, its partial sums part_set floats (2 * n_runs slots of SHRINK_SLOT_ROWS rows).
+constexpr int GROUP_MAX_PROJS = 4;
+struct TileBatchHead {
+    int32_t n;
+    int32_t n_runs, quanta;   // n_runs: a multiple of 8 (run r is worked on by XCD r / (n_runs / 8))
+    int32_t n_tiles, v_stride;
+    int32_t any_pieces;       // some tile is worked on in pieces: the reduce launch is needed
+    float scale;
+    const DevItem *tiles;     // device, n_tiles
     const ShrinkCut *cuts;    // device, n_runs + 1
     const ShrinkSum *sums;    // device, n_tiles
-    const char *proj_base[MAX_SHRINK_PROJS];
-    int64_t row_bytes[MAX_SHRINK_PROJS];
-    float *v[MAX_SHRINK_PROJS];     // as ApplyArgs::v
-    float *part[MAX_SHRINK_PROJS];  // fp32 partial sums of the tiles worked on in pieces
+    const int32_t *tok_list;  // device
+    float *v;                 // as ApplyArgs::v
+    float *part;              // fp32 partial sums of the tiles worked on in pieces
+    uint64_t v_set, part_set;
 };
-// proj_base, row_bytes and v of `a` are ignored (taken from ps)
-hipError_t launch_mfma_shrink(const ApplyArgs &a, const ShrinkProjs &ps, const DevItem *tiles, int n_tiles, hipStream_t st,
-                              const KernelTimer *tm);
-hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm,
-                              hipEvent_t done);
+template <int N> struct TileBatchArgs : TileBatchHead {  // as the kernels take it: N is a group's size or a batch's
+    uint32_t group[N];  // of projection i: first projection of its group | projections of the group << 8
+    BatchProj p[N];
+};
+using TileBatch = TileBatchArgs<BATCH_MAX_PROJS>;
+static_assert(sizeof(TileBatch) <= 3500, "kernel arguments are at most 4 KB");
+hipError_t launch_mfma_shrink(const TileBatch &tb, hipStream_t st, const KernelTimer *tm);
+hipError_t launch_mfma_expand(const TileBatch &tb, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // y = x . Wt^T + adapter update for row tiles (tiles of the plan, then plain runs of the other tokens:
 // rank 0); a.tok_list must be the list the row tiles index; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]

@@ -45,7 +45,7 @@ constexpr int VS_ROW = LORA_MAX_RANK * 2 + 16;  // bytes per token row of the st
 //    configuration showed half of the blocks done at 15 us and the last at 26 us.)
 // Blocks are numbered so that consecutive runs (same tiles, same segment, same At) fall on one XCD (blocks
 // b, b + 8, ... run on XCD b % 8).
-// One launch can serve several projections that read the same x (q, k, v; gate, up).
+// One launch serves the projections of a batch; those that read the same x (q, k, v; gate, up) share its fetch.
 // ---------------------------------------------------------------------------------------
 namespace {
 constexpr int SK = SHRINK_STAGE_K;      // k elements per stage
@@ -277,23 +277,48 @@ __device__ __forceinline__ void mfma_shrink_body(const ApplyArgs &a, const DevIt
     }
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_shrink_kernel(const ShrinkCut *__restrict__ cuts, const DevItem *__restrict__ tiles,
-                                                          int runs_per_xcd, int n_proj, int quanta, int n_tiles, ApplyArgs a,
-                                                          ShrinkProjs ps)
+// the arguments of one projection of the batch
+template <int N>
+__device__ __forceinline__ ApplyArgs tile_args(const TileBatchArgs<N> &tb, int pj)
 {
+    const BatchProj &p = tb.p[pj];
+    ApplyArgs a;
+    a.proj_base = p.proj_base;
+    a.row_bytes = (int64_t)(p.h_in + p.h_out) * 2;
+    a.tok_list = tb.tok_list;
+    a.x = p.x;
+    a.y = p.y;
+    a.v = tb.v + (size_t)pj * tb.v_set;
+    a.h_in = p.h_in;
+    a.h_out = p.h_out;
+    a.v_stride = tb.v_stride;
+    a.scale = tb.scale;
+    return a;
+}
+
+template <int N>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_shrink_kernel(const ShrinkCut *__restrict__ cuts, const DevItem *__restrict__ tiles, int runs_per_xcd, int n_proj, int quanta,
+                                                                                                        int n_tiles, TileBatchArgs<N> tb)
+{
+    // (the scalars in front are fields of tb: leading arguments arrive in registers with the wavefront)
     __shared__ __attribute__((aligned(16))) unsigned char xs[NSTAGE][LORA_TILE_TOKENS * XROW];
     static_assert(sizeof(xs) >= 4 * 4 * 3 * 4 * 64 * 4, "the sum over the wavefronts' k parts reuses the x ring");
 
-    // XCD j = blockIdx % 8 works on the runs [j * runs_per_xcd, (j + 1) * runs_per_xcd); its i-th block on
-    // (run, projection) number i, projection innermost: the blocks that read the same part of x for the
-    // projections of a group are neighbours in the dispatch order of one XCD and walk k in the same order, so
-    // that x is fetched from memory once and found in L2 by the others
+    // XCD j = blockIdx % 8 works on the runs [j * runs_per_xcd, (j + 1) * runs_per_xcd) of every group, group by group;
+    // its i-th block of a group on (run, projection) number i, projection innermost: the blocks that read the same part
+    // of x for the projections of a group are neighbours in the dispatch order of one XCD and walk k in the same order,
+    // so that x is fetched from memory once and found in L2 by the others
     const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
-    const int run = xcd * runs_per_xcd + local / n_proj, pj = local % n_proj;
+    int g0 = 0, gn = n_proj;  // the block's group: first projection and size
+    if constexpr (N > GROUP_MAX_PROJS) {
+        const uint32_t grp = tb.group[local / runs_per_xcd];  // (indexed by a projection of the group)
+        g0 = (int)(grp & 0xffu);
+        gn = (int)(grp >> 8);
+    }
+    const int in_group = local - g0 * runs_per_xcd;
+    const int run = xcd * runs_per_xcd + in_group / gn, pj = g0 + in_group % gn;
     const ShrinkCut from = cuts[run], to = cuts[run + 1];
-    a.proj_base = ps.proj_base[pj];
-    a.row_bytes = ps.row_bytes[pj];
-    a.v = ps.v[pj];
+    const ApplyArgs a = tile_args(tb, pj);
     const int last_tile = min(to.part > 0 ? to.tile : to.tile - 1, n_tiles - 1);
     for (int tile = from.tile; tile <= last_tile; ++tile) {
         const int lo = tile == from.tile ? from.part : 0, hi = tile == to.tile ? to.part : quanta;
@@ -305,7 +330,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int phase = (int)(((unsigned)(run + tile) * 5u) % (unsigned)n_st);
         float *my_part = (lo == 0 && hi == quanta)
                              ? nullptr
-                             : ps.part[pj] + (size_t)shrink_slot(run, from.tile, tile) * SHRINK_SLOT_ROWS * a.v_stride;
+                             : tb.part + (size_t)pj * tb.part_set + (size_t)shrink_slot(run, from.tile, tile) * SHRINK_SLOT_ROWS * a.v_stride;
         const int NB = (it.rank + 15) >> 4;
         if (NB > 4) mfma_shrink_body<true, 2>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 4) mfma_shrink_body<true, 1>(a, it, k_begin, k_end, phase, my_part, xs);
@@ -318,17 +343,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // V[token][0..rank) = sum over the tile's pieces of their partial sums, for the tiles worked on in pieces.
 // (Atomic adds into V instead cost about 30 us per launch: device-scope fp32 atomics execute at the memory side.)
-__global__ __launch_bounds__(256) void mfma_reduce_kernel(ApplyArgs a, ShrinkProjs ps, const DevItem *__restrict__ tiles)
+template <int N>
+__global__ __launch_bounds__(256) void mfma_reduce_kernel(TileBatchArgs<N> tb)
 {
-    // 8 blocks per tile (and projection of the group: blockIdx.y), 8 tokens each; a thread sums one
+    // 8 blocks per tile (and projection of the batch: blockIdx.y), 8 tokens each; a thread sums one
     // float4 column of one token
     const int tile = blockIdx.x >> 3;
-    const ShrinkSum sm = ps.sums[tile];
-    const DevItem it = tiles[tile];  // (requested together with sm: one trip to memory, not two)
+    const ShrinkSum sm = tb.sums[tile];
+    const DevItem it = tb.tiles[tile];  // (requested together with sm: one trip to memory, not two)
     const int ti = (blockIdx.x & 7) * 8 + (threadIdx.x >> 5), j4 = threadIdx.x & 31;
     if ((sm.n_pieces < 2) | (ti >= it.n_tok) | (j4 * 4 >= rank_storage(it.rank))) return;  // entries past the rank are never used
+    const ApplyArgs a = tile_args(tb, (int)blockIdx.y);
     const size_t slot_f4 = (size_t)SHRINK_SLOT_ROWS * (a.v_stride >> 2);
-    const float4 *src = reinterpret_cast<const float4 *>(ps.part[blockIdx.y]) + (size_t)ti * (a.v_stride >> 2) + j4;
+    const float4 *src = reinterpret_cast<const float4 *>(tb.part + (size_t)blockIdx.y * tb.part_set) + (size_t)ti * (a.v_stride >> 2) + j4;
     // four pieces at a time: their loads are issued together (one after the other, a tile in seven pieces took
     // seven trips to memory: 6.5 us per launch on the stress configuration), and only the loads that are needed (loads of a
     // padded batch cost the mixed configuration, two to three pieces per tile, 1 to 2 us)
@@ -357,7 +384,7 @@ __global__ __launch_bounds__(256) void mfma_reduce_kernel(ApplyArgs a, ShrinkPro
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     bf16x4_t o;
     o[0] = (__bf16)(s_v * sum.x), o[1] = (__bf16)(s_v * sum.y), o[2] = (__bf16)(s_v * sum.z), o[3] = (__bf16)(s_v * sum.w);
-    reinterpret_cast<bf16x4_t *>(reinterpret_cast<__bf16 *>(ps.v[blockIdx.y]) + (size_t)tile_token(a, it, ti) * (2 * a.v_stride))[j4] = o;
+    reinterpret_cast<bf16x4_t *>(reinterpret_cast<__bf16 *>(a.v) + (size_t)tile_token(a, it, ti) * (2 * a.v_stride))[j4] = o;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -534,67 +561,120 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
     }
 }
 
-// Blocks -> (tile, column run).  Block b runs on XCD b % 8; the blocks are numbered so that a column run -- the same
-// columns of every tile -- always falls on the same XCD (or the same two or four), and a prompt's Bp is fetched
-// from memory by one XCD per column run instead of by all eight (with the tiles as the fast index the prefill
-// expand fetched 147 MB for 101 MB).  The column runs go in groups of eight: within a group block
-// (tile * 8 + run % 8) works on that tile and run; what is left over after the whole groups forms a last group of
+// Blocks -> (projection, tile, column run).  A projection's blocks start at a multiple of 8.  Block b runs on XCD b % 8; the
+// blocks are numbered so that a column run -- the same columns of every tile -- always falls on the same XCD (or the same
+// two or four), and a prompt's Bp is fetched from memory by one XCD per column run instead of by all eight (with the tiles
+// as the fast index the prefill expand fetched 147 MB for 101 MB).  The column runs go in groups of eight: within a group
+// block (tile * 8 + run % 8) works on that tile and run; what is left over after the whole groups forms a last group of
 // 1, 2, 4 or 8 runs (the next power of two: at most a twelfth of a launch's blocks are padding, which return at once --
 // padding every launch to a multiple of 8 runs cost the two 11-run launches of the mixed configuration 29 us each).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void mfma_expand_kernel(ApplyArgs a, const DevItem *__restrict__ tiles, int n_tiles,
-                                                                                                        int n_pass, int n_runs, int last_width)
+template <int N> struct ExpandShape {
+    int32_t n_pass;      // passes of 128 columns per block
+    int32_t blk_end[N];  // blocks of projections 0 .. p (entries past the batch repeat the last)
+};
+// blocks of n_tiles x n_runs as numbered above, without the rounding to a multiple of 8
+inline __host__ __device__ int expand_last_width(int n_runs)
+{
+    const int rest = n_runs & 7;
+    return rest == 0 ? 0 : (rest == 1 ? 1 : (rest == 2 ? 2 : (rest <= 4 ? 4 : 8)));
+}
+template <int N>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void mfma_expand_kernel(TileBatchArgs<N> tb, ExpandShape<N> sh)
 {
     __shared__ __attribute__((aligned(16))) unsigned char vs[LORA_TILE_TOKENS * VS_ROW];
     __shared__ __attribute__((aligned(16))) unsigned char cs[4][32 * CS_ROW];
+    int pj = 0;  // the first projection whose blocks end behind this one
+    if (tb.n > 1) {
+#pragma unroll
+        for (int step = N / 2; step > 0; step >>= 1)
+            if ((int)blockIdx.x >= sh.blk_end[pj + step - 1]) pj += step;
+    }
+    const int b = (int)blockIdx.x - (pj ? sh.blk_end[pj - 1] : 0);
+    const ApplyArgs a = tile_args(tb, pj);
+    const int n_tiles = tb.n_tiles, n_runs = (a.h_out + sh.n_pass * 128 - 1) / (sh.n_pass * 128);
     const int whole = (n_runs >> 3) * n_tiles * 8;  // blocks of the groups of eight
     int tile, col_run;
-    if ((int)blockIdx.x < whole) {
-        const int grp = (int)blockIdx.x / (n_tiles * 8), r = (int)blockIdx.x - grp * n_tiles * 8;
+    if (b < whole) {
+        const int grp = b / (n_tiles * 8), r = b - grp * n_tiles * 8;
         tile = r >> 3;
         col_run = 8 * grp + (r & 7);
     } else {
-        const int r = (int)blockIdx.x - whole;
+        const int r = b - whole, last_width = expand_last_width(n_runs);
+        if (last_width == 0) return;  // padding
         tile = r / last_width;
         col_run = (n_runs & ~7) + (r - tile * last_width);
-        if (col_run >= n_runs) return;  // padding
+        if (col_run >= n_runs || tile >= n_tiles) return;  // padding
     }
-    const DevItem it = tiles[tile];
+    const DevItem it = tb.tiles[tile];
     switch ((it.rank + 31) >> 5) {
-    case 1: mfma_expand_body<1>(a, it, col_run, n_pass, vs, cs); break;
-    case 2: mfma_expand_body<2>(a, it, col_run, n_pass, vs, cs); break;
-    case 3: mfma_expand_body<3>(a, it, col_run, n_pass, vs, cs); break;
-    default: mfma_expand_body<4>(a, it, col_run, n_pass, vs, cs); break;
+    case 1: mfma_expand_body<1>(a, it, col_run, sh.n_pass, vs, cs); break;
+    case 2: mfma_expand_body<2>(a, it, col_run, sh.n_pass, vs, cs); break;
+    case 3: mfma_expand_body<3>(a, it, col_run, sh.n_pass, vs, cs); break;
+    default: mfma_expand_body<4>(a, it, col_run, sh.n_pass, vs, cs); break;
     }
+}
+
+// The arguments of a batch are 2.4 KB; a group's calls, one after the other as a model's forward pass makes them, take them
+// along as 0.25 KB instead (a short prompt called projection by projection: 288 us with the large ones, 282 us).
+template <typename F> static void with_batch_size(const TileBatch &tb, F go)
+{
+    if (tb.n > GROUP_MAX_PROJS) {
+        go(tb);
+        return;
+    }
+    TileBatchArgs<GROUP_MAX_PROJS> g;
+    static_cast<TileBatchHead &>(g) = tb;
+    for (int i = 0; i < GROUP_MAX_PROJS; ++i) {
+        g.group[i] = 0;  // (one group)
+        g.p[i] = tb.p[std::min(i, tb.n - 1)];
+    }
+    go(g);
 }
 
 // k ranges are multiples of the 128-element stage.
-hipError_t launch_mfma_shrink(const ApplyArgs &a, const ShrinkProjs &ps, const DevItem *tiles, int n_tiles, hipStream_t st,
-                              const KernelTimer *tm)
+hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const KernelTimer *tm)
 {
-    if (n_tiles <= 0 || ps.n <= 0 || ps.n_runs <= 0) return hipSuccess;
-    if (ps.n_runs % 8 != 0 || ps.quanta < 1) return hipErrorInvalidValue;
-    const int runs_per_xcd = ps.n_runs / 8;
-    launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel, dim3(ps.n_runs * ps.n), dim3(256), 0, st, ps.cuts, tiles, runs_per_xcd, ps.n,
-             ps.quanta, n_tiles, a, ps);
-    if (ps.any_pieces)
-        launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel, dim3(n_tiles * 8, ps.n), dim3(256), 0, st, a, ps, tiles);
+    if (batch.n_tiles <= 0 || batch.n <= 0 || batch.n_runs <= 0) return hipSuccess;
+    if (batch.n > BATCH_MAX_PROJS || batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
+    with_batch_size(batch, [&](const auto &tb) {
+        constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
+        launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), 0, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
+                 tb.quanta, tb.n_tiles, tb);
+        if (tb.any_pieces) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel<N>, dim3(tb.n_tiles * 8, tb.n), dim3(256), 0, st, tb);
+    });
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_expand(const ApplyArgs &a, const DevItem *tiles, int n_tiles, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+hipError_t launch_mfma_expand(const TileBatch &batch, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
-    if (n_tiles <= 0) return hipSuccess;
+    if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
+    if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
     // the widest column run per block that still gives 512 blocks (two per CU), else the narrowest
+    auto runs_of = [&](int i, int cols) { return (batch.p[i].h_out + cols - 1) / cols; };
     int cols = 1024;
-    while (cols > 256 && (int64_t)n_tiles * ((a.h_out + cols - 1) / cols) < 512) cols >>= 1;
-    const int n_runs = (a.h_out + cols - 1) / cols;
-    int last_width = 0;  // of the last, partial group of column runs: the next power of two
-    if (n_runs & 7) {
-        last_width = 1;
-        while (last_width < (n_runs & 7)) last_width <<= 1;
+    for (; cols > 256; cols >>= 1) {
+        int64_t blocks = 0;
+        for (int i = 0; i < batch.n; ++i) blocks += (int64_t)batch.n_tiles * runs_of(i, cols);
+        if (blocks >= 512) break;
     }
-    launch_k(tm, done, LORA_K_MFMA_EXPAND, mfma_expand_kernel, dim3(n_tiles * ((n_runs & ~7) + last_width)), dim3(256), 0, st, a, tiles, n_tiles,
-             cols / 128, n_runs, last_width);
+    int64_t total = 0;
+    auto blocks_of = [&](int i) {
+        const int n_runs = runs_of(i, cols);
+        return ((int64_t)batch.n_tiles * ((n_runs & ~7) + expand_last_width(n_runs)) + 7) / 8 * 8;
+    };
+    for (int i = 0; i < batch.n; ++i) total += blocks_of(i);
+    if (total > INT32_MAX) return hipErrorInvalidValue;
+    with_batch_size(batch, [&](const auto &tb) {
+        constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
+        ExpandShape<N> sh;
+        sh.n_pass = cols / 128;
+        int32_t end = 0;
+        for (int i = 0; i < N; ++i) {
+            if (i < tb.n) end += (int32_t)blocks_of(i);
+            sh.blk_end[i] = end;
+        }
+        launch_k(tm, done, LORA_K_MFMA_EXPAND, mfma_expand_kernel<N>, dim3((unsigned)end), dim3(256), 0, st, tb, sh);
+    });
     return hipGetLastError();
 }
 

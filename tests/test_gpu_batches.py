@@ -1,0 +1,148 @@
+"""lora_apply_plan_multi as batches (one launch per phase for all entries that do not depend on each other) against one
+lora_apply_plan per entry, where batches can go wrong: more entries than a batch holds, groups of every size, rows and columns
+of different lengths, few and many GEMV items, few and many tiles, entries that depend on earlier ones, capture."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+PROJS = [(512, 512), (512, 512), (512, 192), (512, 1088), (512, 512), (512, 64), (192, 512), (1088, 512), (2112, 2240)]  # 0..5 read one x
+BATCHES = {
+    "one token": ([1], [16]),
+    "decode": ([1] * 90, [8, 16, 12, 32, 64, 96, 128, 33]),            # more than 64 shrink items
+    "few prompts": ([77, 9], [16, 128]),
+    "tiles of a few tokens": ([9, 10, 11, 12, 13, 14, 15, 8] * 3, [8, 40, 128]),
+    "mixed": ([300, 1, 65, 1, 1, 17, 128, 1, 3, 1, 200], [16, 64, 128, 8]),
+}
+
+
+def _setup(lens, ranks, layers, dtype="bf16", flags=0, m0=8):
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    T = sum(lens)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda").manual_seed(len(lens) + layers)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda", dtype=dt).mul_(sigma)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    slot = np.asarray([i % len(ranks) if i % 7 != 6 else -1 for i in range(len(lens))], np.int32)
+    pool = LoraPool(PROJS, layers, [128], [len(ranks)], B.LORA_BF16 if dtype == "bf16" else B.LORA_F32, max_tokens=T,
+                    max_segments=len(lens), mfma_min_tokens=m0 if dtype == "bf16" else 0, flags=flags)
+    for s, r in enumerate(ranks):
+        for layer in range(layers):
+            for p, (h_in, h_out) in enumerate(PROJS):
+                pool.fill(s, s + 1, r, 0.5 + s, layer, p, normal(h_in, r, sigma=0.05).cpu(), normal(r, h_out, sigma=0.05).cpu())
+    torch.cuda.synchronize()
+    plan = pool.plan(T, off, slot, np.where(slot >= 0, np.asarray(ranks)[slot], 0).astype(np.int32))
+    return B, pool, plan, T, normal
+
+
+def _same(got, want, dtype, what):
+    """The sums may be split in other places: the intermediate then rounds elsewhere once in a while (2^-9 of an entry, well
+    under 2^-8 of the RMS in the sum) and the output by up to two halves of its last place."""
+    got, want = got.double(), want.double()
+    rms = want.pow(2).mean().sqrt()
+    rel, floor = (2.0**-7, 2.0**-7) if dtype == "bf16" else (2.0**-21, 2.0**-20)
+    err = (got - want).abs()
+    assert bool((err <= rel * want.abs() + floor * rms).all()), f"{what}: {float((err / rms).max())}"
+
+
+@pytest.mark.parametrize("dtype,flags", [("bf16", "auto"), ("bf16", "split"), ("f32", "auto")])
+@pytest.mark.parametrize("batch", list(BATCHES))
+def test_batches_against_single_applies(batch, dtype, flags):
+    from paper_2411_17741_amd import binding as B0
+
+    layers = 9  # 81 entries: more than a batch holds
+    fl = B0.LORA_CACHE_SPLIT_GEMV if flags == "split" else 0
+    B, pool, plan, T, normal = _setup(*BATCHES[batch], layers, dtype, fl)
+    try:
+        xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
+        x_of = lambda p: xs[0 if p < 6 else p - 5]
+        sh = torch.cuda.current_stream().cuda_stream
+        base = [[normal(T, h_out) for _i, h_out in PROJS] for _ in range(layers)]
+        want = [[y.clone() for y in ys] for ys in base]
+        for layer in range(layers):
+            for p in range(len(PROJS)):
+                pool.apply_plan(plan, layer, p, x_of(p), want[layer][p], 2.0)
+        for _ in range(2):  # again with the scratch as the first call left it
+            got = [[y.clone() for y in ys] for ys in base]
+            descs = B.make_descs([(l, p, x_of(p).data_ptr(), got[l][p].data_ptr()) for l in range(layers) for p in range(len(PROJS))])
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, sh))
+            pool.check_fault()
+            for l in range(layers):
+                for p in range(len(PROJS)):
+                    assert not torch.equal(got[l][p], base[l][p])
+                    _same(got[l][p], want[l][p], dtype, f"layer {l} projection {p}")
+    finally:
+        pool.close()
+
+
+@pytest.mark.parametrize("batch", ["decode", "mixed"])
+def test_entries_that_depend_on_earlier_ones(batch):
+    """Each list in order: an output that is a later entry's input; a later output over an earlier input; one output twice;
+    an output that overlaps another's last row; an entry in place."""
+    B, pool, plan, T, normal = _setup(*BATCHES[batch], 2)
+    try:
+        sh = torch.cuda.current_stream().cuda_stream
+
+        def fresh(seed):
+            g = torch.Generator(device="cuda").manual_seed(seed)
+            return [torch.randn(2 * T, 512, generator=g, device="cuda").bfloat16() for _ in range(4)]
+
+        at = lambda t, row=0: t.data_ptr() + row * t.shape[1] * 2
+        lists = [
+            lambda t: [(0, 0, at(t[0]), at(t[1])), (1, 0, at(t[1]), at(t[2])), (1, 1, at(t[2]), at(t[3]))],
+            lambda t: [(0, 0, at(t[0]), at(t[1])), (1, 0, at(t[2]), at(t[0])), (1, 1, at(t[0]), at(t[3]))],
+            lambda t: [(0, 0, at(t[0]), at(t[1])), (0, 1, at(t[0]), at(t[1])), (1, 4, at(t[2]), at(t[1]))],
+            lambda t: [(0, 0, at(t[0]), at(t[1])), (1, 0, at(t[0]), at(t[1], T - 1)), (1, 1, at(t[1], T - 1), at(t[2]))],
+            lambda t: [(0, 1, at(t[3]), at(t[2])), (0, 0, at(t[0]), at(t[0])), (1, 0, at(t[0]), at(t[1]))],
+        ]
+        # (a token-by-token batch of one in-place entry reads its row while it writes it: a one-launch decode batch is left out)
+        for n, make in enumerate(lists):
+            if batch == "decode" and n == 4:
+                continue
+            want, got = fresh(n), fresh(n)
+            for layer, p, x, y in make(want):
+                B.check(B.lora_apply_plan(pool.handle, plan, layer, p, x, y, 2.0, sh))
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, B.make_descs(make(got)), 2.0, sh))
+            pool.check_fault()
+            for k, (a, b) in enumerate(zip(got, want)):
+                _same(a, b, "bf16", f"list {n}, tensor {k}")
+    finally:
+        pool.close()
+
+
+@pytest.mark.parametrize("batch", ["decode", "mixed"])
+def test_a_captured_batch_replays(batch):
+    B, pool, plan, T, normal = _setup(*BATCHES[batch], 3)
+    try:
+        xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
+        x_of = lambda p: xs[0 if p < 6 else p - 5]
+        base = [[normal(T, h_out) for _i, h_out in PROJS] for _ in range(3)]
+        y = [[t.clone() for t in ys] for ys in base]
+        descs = B.make_descs([(l, p, x_of(p).data_ptr(), y[l][p].data_ptr()) for l in range(3) for p in range(len(PROJS))])
+        call = lambda: B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
+        call()
+        torch.cuda.synchronize()
+        B.check(B.lora_cache_set_fencing(pool.handle, 0))
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, capture_error_mode="thread_local"):
+            call()
+        B.check(B.lora_cache_set_fencing(pool.handle, 1))
+        restore = lambda: [t.copy_(b) for ys, bs in zip(y, base) for t, b in zip(ys, bs)]
+        for f in (1.0, -0.5, 2.0):
+            for x in xs:
+                x.mul_(f)  # eager work between the replays
+            restore()
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            got = [t.clone() for ys in y for t in ys]
+            restore()
+            call()
+            pool.check_fault()
+            for k, (a, b) in enumerate(zip(got, [t for ys in y for t in ys])):
+                assert torch.equal(a, b), f"entry {k}"
+    finally:
+        pool.close()
