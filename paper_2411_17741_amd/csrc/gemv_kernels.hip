@@ -473,6 +473,286 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Wide items (bf16): launches that fill the chip are bound by what the compute units take in, so an item keeps what it has
+// fetched for more rows and more tokens.
+//
+// shrink: a block of 4 wavefronts on 8 or 16 rank rows and up to 8 tokens.  The wavefronts split k as above; a wavefront keeps
+// its 2 chunks of x of every token -- 4 tokens in registers, the others in LDS of its own -- and goes over the rows in quads of
+// 4, the next quad's 8 KB requested before this one's products.
+// ---------------------------------------------------------------------------------------
+struct ItemW {
+    int row, rank, a, n_tok;
+    float alpha;
+};
+__device__ __forceinline__ ItemW load_wide(const GemvWideItem *p)
+{
+    const int4 lo = *reinterpret_cast<const int4 *>(p);
+    const int n = p->n_tok;
+    ItemW u;
+    u.row = __builtin_amdgcn_readfirstlane(lo.x);
+    u.rank = __builtin_amdgcn_readfirstlane(lo.y);
+    u.a = __builtin_amdgcn_readfirstlane(lo.z);
+    u.alpha = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(lo.w));
+    u.n_tok = __builtin_amdgcn_readfirstlane(n);
+    return u;
+}
+constexpr int WIDE_X_LDS = 4 * 2 * 64 * 16;                            // bytes per wavefront: 2 chunks of 4 tokens' x
+constexpr int WIDE_SUMS = GEMV_WIDE_ROWS * GEMV_WIDE_SHRINK_TOKENS;    // sums of an item
+constexpr int WIDE_V_ROW = 64 + 4;                                     // words per token of the staged s.v (padded: the 16 tokens' rows are read side by side)
+constexpr int WIDE_LDS = 4 * (WIDE_X_LDS + WIDE_SUMS * 4);
+static_assert(WIDE_LDS >= 4 * GEMV_WIDE_TOKENS * WIDE_V_ROW * 4, "a block's expand wavefronts stage s.v in the same memory");
+
+template <int NT, int NQ>  // tokens (1, 2, 4 or 8: what the item has, rounded up), quads of rows (2 or 4)
+__device__ __forceinline__ void gemv_wide_shrink(const GemvUse &a, const ItemW it, const GemvWideItem *item, unsigned char *lds)
+{
+    constexpr int NR = NT < 4 ? NT : 4;  // tokens whose x stays in registers
+    constexpr int NV = 4 * NR;           // sums of a quad and token half
+    constexpr int HALVES = NT / NR;
+    const int lane = threadIdx.x & 63, kp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint4 *const xl = reinterpret_cast<uint4 *>(lds + kp * WIDE_X_LDS) + lane;  // [token - 4][chunk][lane]
+    float *const sums = reinterpret_cast<float *>(lds + 4 * WIDE_X_LDS);        // [wavefront][quad][half][value]
+    const int n_chunks = a.h_in >> 3;
+    const size_t row_b = (size_t)a.h_in * 2;
+    const char *slab = a.proj_base + (int64_t)it.row * a.row_bytes + (size_t)it.a * row_b;
+    const char *xrow[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) xrow[t] = a.x + (size_t)__builtin_amdgcn_readfirstlane(item->tok[t]) * row_b;
+    // the sums this thread hands over in the end: rows 2 * pair, 2 * pair + 1 of token ft
+    constexpr int PAIRS = 2 * NQ;
+    const int ft = threadIdx.x / PAIRS, pair = threadIdx.x % PAIRS;
+    const int ftok = item->tok[ft < NT ? ft : 0];
+
+    for (int c0 = 0; c0 < n_chunks; c0 += 4 * 64 * 2) {
+        uint32_t off[2];
+        bool ok[2];
+        Chunk<__bf16> xv[NR][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = c0 + (u * 4 + kp) * 64 + lane;
+            ok[u] = c < n_chunks;  // clamped lanes do not count: their x is zeroed
+            off[u] = (uint32_t)min(c, n_chunks - 1) * 16u;
+        }
+        Chunk<__bf16> av[2][4][2];
+        auto load_quad = [&](int q, Chunk<__bf16>(&d)[4][2]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) d[r][u].v = load_slab16(slab + (size_t)(4 * q + r) * row_b + off[u]);
+        };
+        if constexpr (HALVES == 2) {
+            uint4 far[4][2];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) far[t][u] = *reinterpret_cast<const uint4 *>(xrow[NR + t] + off[u]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) xl[(2 * t + u) * 64] = ok[u] ? far[t][u] : make_uint4(0u, 0u, 0u, 0u);  // (each lane reads back what it wrote)
+        }
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) xv[t][u] = *reinterpret_cast<const Chunk<__bf16> *>(xrow[t] + off[u]);
+        load_quad(0, av[0]);
+        __builtin_amdgcn_sched_barrier(0);  // keep the scheduler from trading loads in flight for registers
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (!ok[u]) xv[t][u] = zero_chunk<__bf16>();
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (q + 1 < NQ) load_quad(q + 1, av[(q + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) {
+                float acc[NV];
+#pragma unroll
+                for (int i = 0; i < NV; ++i) acc[i] = 0.f;
+#pragma unroll
+                for (int t = 0; t < NR; ++t)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        Chunk<__bf16> x = xv[t][u];
+                        if constexpr (HALVES == 2) {
+                            if (h == 1) x.v = xl[(2 * t + u) * 64];
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) acc[4 * t + r] = dot_chunk_acc(acc[4 * t + r], av[q & 1][r][u], x);
+                    }
+                wave_fold(acc);  // value i now on the lanes i * (64 / NV) ..
+                if (lane % (64 / NV) == 0) {
+                    float *s = sums + kp * WIDE_SUMS + (q * HALVES + h) * NV + lane / (64 / NV);
+                    *s = c0 ? *s + acc[0] : acc[0];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= PAIRS * NT) return;
+    // value 4 (t % NR) + r of quad q and half t / NR is row 4q + r of token t
+    const float *s = sums + ((pair >> 1) * HALVES + ft / NR) * NV + 4 * (ft % NR) + 2 * (pair & 1);
+    float v0 = 0.f, v1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        v0 += s[w * WIDE_SUMS];
+        v1 += s[w * WIDE_SUMS + 1];
+    }
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    const float f = a.scale * it.alpha;
+    bf16x2_t pr;
+    pr[0] = (__bf16)(f * v0);
+    pr[1] = (__bf16)(f * v1);
+    if (ft < it.n_tok) put_word(a.vw + (size_t)ftok * 64 + (it.a >> 1) + pair, a.epoch, __builtin_bit_cast(uint32_t, pr));
+}
+
+// expand: as gemv_expand_mfma, with the 16 columns of a product for 16 tokens (G = 1), or G groups of 16 / G tokens one after the
+// other for the small ranks, the Bp operands staying in registers.
+template <int G, int KS>
+__device__ __forceinline__ void gemv_wide_expand(const GemvUse &a, const ItemW it, const GemvWideItem *item, int c0, int c1,
+                                                 uint32_t *vb /* this wavefront's LDS: [16][WIDE_V_ROW] words */)
+{
+    constexpr int NQ = KS == 1 ? 8 : 16 / KS, SPAN = 16 * G, TG = 16 / G;  // NQ: spans of a whole unit; TG: tokens of a pass
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int rs = rank_storage(it.rank), rs8 = rs >> 3;
+    const int n_q = (c1 - c0) / SPAN;
+    const char *Bp = a.proj_base + (int64_t)it.row * a.row_bytes + (size_t)rs * a.h_in * 2 + (size_t)c0 * 16;
+    const int my_tok = item->tok[m];  // lane m (and m + 16, ...): token m of the item
+
+    uint32_t boff[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+        if constexpr (G == 4) boff[ks] = (uint32_t)lane * 16u;
+        else if constexpr (G == 2) boff[ks] = ((uint32_t)(g & 1) * a.h_out + 16u * (g >> 1) + m) * 16u;
+        else boff[ks] = ((uint32_t)min(4 * ks + g, rs8 - 1) * a.h_out + m) * 16u;
+    }
+    uint4 br[NQ][KS];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const char *bq = Bp + (q < n_q ? q * SPAN * 16 : 0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) br[q][ks] = load_slab16(bq + boff[ks]);
+    }
+    const int t = m % TG, gq = m / TG;
+    char *const ybase = a.y + (size_t)c0 * 2;
+    // base_out of pass s: lane (m, g) updates columns 16 * group + 4g .. +3 of the span for token s * TG + t
+    auto where = [&](int s) {
+        const int tok = G == 1 ? my_tok : __shfl(my_tok, s * TG + t);
+        return (uint32_t)tok * a.h_out + 16 * gq + 4 * g;  // elements from column c0 of row 0
+    };
+    uint2 yv[NQ];
+    auto load_y = [&](uint32_t yoff) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) yv[q] = *reinterpret_cast<const uint2 *>(ybase + (q < n_q ? q * SPAN * 2 : 0) + yoff * 2u);
+    };
+    uint32_t yoff = where(0);
+    load_y(yoff);
+    for (int t0 = 0; t0 < it.n_tok; t0 += TB) {
+        const int nt = min(TB, it.n_tok - t0);
+        const unsigned long long *vp[TB];
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt) vp[tt] = a.vw + (size_t)__builtin_amdgcn_readlane(my_tok, t0 + tt) * 64 + lane;
+        uint32_t vword[TB];
+        if (!fetch_words(a, vp, 2 * lane < rs, nt, vword)) return;
+#pragma unroll
+        for (int tt = 0; tt < TB; ++tt) vb[(t0 + tt) * WIDE_V_ROW + lane] = (tt < nt && 2 * lane < rs) ? vword[tt] : 0u;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int s = 0;;) {
+        const bool live = s * TG + t < it.n_tok;
+        gv_bf16x8 vop[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            int gran;
+            bool mine = live;
+            if constexpr (G == 4) gran = 0, mine = mine && g == gq;
+            else if constexpr (G == 2) gran = g & 1, mine = mine && (g >> 1) == gq;
+            else gran = 4 * ks + g;
+            const uint4 w = *reinterpret_cast<const uint4 *>(vb + (s * TG + t) * WIDE_V_ROW + 4 * gran);
+            vop[ks] = __builtin_bit_cast(gv_bf16x8, mine ? w : make_uint4(0u, 0u, 0u, 0u));
+        }
+        auto product = [&](int q) {
+            gv_floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(gv_bf16x8, br[q][ks]), vop[ks], acc, 0, 0, 0);
+            return acc;
+        };
+        if (a.y32) {  // uniform
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const gv_floatx4 acc = product(q);
+                if (live && q < n_q) *reinterpret_cast<gv_floatx4 *>(a.y32 + (size_t)c0 + q * SPAN + yoff) = acc;
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const gv_floatx4 acc = product(q);
+                const unsigned lo = yv[q].x, hi = yv[q].y;
+                gv_bf16x4 o;
+                o[0] = (__bf16)(__uint_as_float(lo << 16) + acc[0]);
+                o[1] = (__bf16)(__uint_as_float(lo & 0xffff0000u) + acc[1]);
+                o[2] = (__bf16)(__uint_as_float(hi << 16) + acc[2]);
+                o[3] = (__bf16)(__uint_as_float(hi & 0xffff0000u) + acc[3]);
+                if (live && q < n_q) *reinterpret_cast<gv_bf16x4 *>(ybase + q * SPAN * 2 + yoff * 2u) = o;
+            }
+        }
+        s += 1;
+        if (G == 1 || s * TG >= it.n_tok) break;
+        yoff = where(s);
+        load_y(yoff);
+    }
+}
+
+__global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char lds[WIDE_LDS];
+    const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
+    auto use = [&](uint32_t proj) {
+        const BatchProj &q = b.p[proj];
+        return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * 2, static_cast<const char *>(q.x), static_cast<char *>(q.y), b.y32,
+                       b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
+    };
+    if (blockIdx.x < n_shrink) {
+        uint32_t item, proj;
+        gemv_batch_shrink(blockIdx.x, b.m, proj, item);
+        if (item >= b.m.n_gs) return;
+        const GemvWideItem *p = b.wgs + item;
+        const ItemW it = load_wide(p);
+        const GemvUse a = use(proj);
+        const bool q4 = gemv_wide_rows(it.rank, it.a) == GEMV_WIDE_ROWS;  // uniform over the block, as n_tok
+        if (it.n_tok == 1) q4 ? gemv_wide_shrink<1, 4>(a, it, p, lds) : gemv_wide_shrink<1, 2>(a, it, p, lds);
+        else if (it.n_tok == 2) q4 ? gemv_wide_shrink<2, 4>(a, it, p, lds) : gemv_wide_shrink<2, 2>(a, it, p, lds);
+        else if (it.n_tok <= 4) q4 ? gemv_wide_shrink<4, 4>(a, it, p, lds) : gemv_wide_shrink<4, 2>(a, it, p, lds);
+        else q4 ? gemv_wide_shrink<8, 4>(a, it, p, lds) : gemv_wide_shrink<8, 2>(a, it, p, lds);
+    } else {
+        if (b.m.phase == 1) return;
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
+        if (unit >= b.m.n_units) return;
+        uint32_t super, item;
+        gemv_batch_unit(unit, b.m, super, item);
+        const uint32_t s = (b.supers[super >> 1] >> (16 * (super & 1))) & 0xffffu;
+        const GemvWideItem *p = b.wge + item;
+        const ItemW it = load_wide(p);
+        const GemvUse a = use(s & 0xffu);
+        int c0, c1;
+        gemv_wide_cols(it.rank, it.a, (int)(s >> 8), a.h_out, c0, c1);
+        if (c0 >= c1) return;
+        uint32_t *vb = reinterpret_cast<uint32_t *>(lds) + w * GEMV_WIDE_TOKENS * WIDE_V_ROW;
+        const int rs8 = rank_storage(it.rank) >> 3;  // uniform over the wavefront
+        if (rs8 == 1) gemv_wide_expand<4, 1>(a, it, p, c0, c1, vb);
+        else if (rs8 == 2) gemv_wide_expand<2, 1>(a, it, p, c0, c1, vb);
+        else if (rs8 <= 4) gemv_wide_expand<1, 1>(a, it, p, c0, c1, vb);
+        else if (rs8 <= 8) gemv_wide_expand<1, 2>(a, it, p, c0, c1, vb);
+        else if (rs8 <= 12) gemv_wide_expand<1, 3>(a, it, p, c0, c1, vb);
+        else gemv_wide_expand<1, 4>(a, it, p, c0, c1, vb);
+    }
+}
+
 // zeroes the hand-over words of the listed tokens: one block per token and set
 template <typename E>
 __global__ __launch_bounds__(64) void gemv_clear_kernel(unsigned long long *vw, uint64_t vw_set, const int32_t *__restrict__ toks)
@@ -518,14 +798,16 @@ hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (b.m.n_gs == 0 || b.m.n_ge == 0 || b.m.n_proj == 0) return hipSuccess;
+    if ((wide && dtype != LORA_BF16) || (b.y32 && !(wide && b.m.n_proj == 1))) return hipErrorInvalidValue;
     const unsigned n_shrink = b.m.n_proj * b.m.shrink_blocks, n_expand = (b.m.n_units + 3) / 4;
     auto go = [&](uint32_t phase, unsigned blocks, int kind, hipEvent_t ev) {
         GemvBatch q = b;
         q.m.phase = phase;
-        if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, q);
+        if (wide) launch_k(tm, ev, kind, gemv_wide_kernel, dim3(blocks), dim3(256), 0, st, q);
+        else if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, q);
         else launch_k(tm, ev, kind, gemv_batch_kernel<float>, dim3(blocks), dim3(256), 0, st, q);
     };
     if (b.epoch) {

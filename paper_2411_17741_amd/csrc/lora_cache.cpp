@@ -152,6 +152,8 @@ struct lora_plan {
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     uint64_t build_seq = 0;     // changes whenever the plan's lists are rebuilt
     size_t off_tiles = 0, off_gs = 0, off_ge = 0, bytes = 0;
+    int32_t n_wgs = 0, n_wge = 0;  // the GEMV work as wide items (bf16 caches)
+    size_t off_wgs = 0, off_wge = 0;
     // for lora_linear_plan: every token of the batch in row tiles -- the tiles above, then runs of up
     // to 64 of the other tokens (rank 0) -- over a token list of its own
     size_t off_lin_tok = 0, off_lin_tiles = 0;
@@ -306,8 +308,11 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     // GEMV items: per token batch up to 32 shrink + 16 expand items; batches <= groups + tokens/4
     const size_t max_batches = (size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_BATCH + 1;
     const size_t max_items = max_tiles + max_batches * (LORA_MAX_RANK / 4 + 16);
+    const size_t max_wide = c.dtype != LORA_BF16 ? 0
+                                                 : ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_SHRINK_TOKENS + 1) * (LORA_MAX_RANK / lora::GEMV_WIDE_ROWS) +
+                                                       ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_TOKENS + 1) * 16;
     c.plan_cap = align_up(sizeof(int32_t) * (size_t)c.max_tokens) + align_up(sizeof(lora_item_t) * max_items) +
-                 align_up(sizeof(int32_t) * max_batches) + 4 * ALIGN +
+                 align_up(sizeof(int32_t) * max_batches) + 6 * ALIGN + align_up(sizeof(lora::GemvWideItem) * max_wide) +
                  align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
                  align_up(sizeof(lora_item_t) * (max_tiles + (size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
                  SHRINK_VARIANTS * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
@@ -678,6 +683,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // Groups in order of rising rank, whatever the caller's slot numbering (measured on the decode configuration:
     // 10.0 us per layer, 10.5 us with the order reversed).
     std::vector<lora::GemvItem> gs, ge;
+    std::vector<lora::GemvWideItem> wgs, wge;  // the same work as wide items
     std::vector<int> group_order((size_t)w.n_groups);
     for (int i = 0; i < w.n_groups; ++i) group_order[i] = i;
     std::stable_sort(group_order.begin(), group_order.end(),
@@ -705,6 +711,28 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
                 }
             }
     }
+    for (int gi = 0; gi < w.n_groups && c.dtype == LORA_BF16; ++gi) {
+        const lora_item_t &gr = w.groups[group_order[gi]];
+        lora::GemvWideItem d{};
+        d.row = c.slot_row[gr.slot];
+        d.rank = gr.rank;
+        d.alpha = c.slots[gr.slot].alpha;
+        for (int pass = 0; pass < 2; ++pass) {
+            const int32_t most = pass == 0 ? lora::GEMV_WIDE_SHRINK_TOKENS : lora::GEMV_WIDE_TOKENS;
+            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += most) {
+                d.n_tok = std::min(most, gr.n_tok - b0);
+                for (int t = 0; t < lora::GEMV_WIDE_TOKENS; ++t) d.tok[t] = w.tok_list[gr.tok_off + b0 + (t < d.n_tok ? t : 0)];
+                if (pass == 0) {
+                    for (d.a = 0; d.a < lora::rank_storage(gr.rank); d.a += lora::GEMV_WIDE_ROWS) wgs.push_back(d);
+                } else {
+                    for (int32_t col = 0; col < lora::GEMV_SUPER_COLS; col += lora::gemv_wide_width(gr.rank)) {
+                        d.a = lora::gemv_pack_expand(col);
+                        wge.push_back(d);
+                    }
+                }
+            }
+        }
+    }
     stamp(w.tiles, w.n_tiles);
     // the tile shrink's run tables
     ShrinkRuns shrink_runs[SHRINK_VARIANTS];
@@ -728,6 +756,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.n_tiles = w.n_tiles;
     p.n_gs = (int32_t)gs.size();
     p.n_ge = (int32_t)ge.size();
+    p.n_wgs = (int32_t)wgs.size();
+    p.n_wge = (int32_t)wge.size();
     p.off_tiles = align_up(sizeof(int32_t) * (size_t)w.n_tok_list);
     p.off_gs = p.off_tiles + align_up(sizeof(lora_item_t) * (size_t)w.n_tiles);
     p.off_ge = p.off_gs + align_up(sizeof(lora::GemvItem) * gs.size());
@@ -762,7 +792,9 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         plain_runs(w.n_tok_list, (int32_t)lin_tok.size(), 0);
     }
     p.n_lin_tiles = (int32_t)lin_tiles.size();
-    p.off_lin_tok = p.off_ge + align_up(sizeof(lora::GemvItem) * ge.size());
+    p.off_wgs = p.off_ge + align_up(sizeof(lora::GemvItem) * ge.size());
+    p.off_wge = p.off_wgs + align_up(sizeof(lora::GemvWideItem) * wgs.size());
+    p.off_lin_tok = p.off_wge + align_up(sizeof(lora::GemvWideItem) * wge.size());
     p.off_lin_tiles = p.off_lin_tok + align_up(sizeof(int32_t) * lin_tok.size());
     size_t bytes = p.off_lin_tiles + align_up(sizeof(lora::DevItem) * lin_tiles.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
@@ -798,6 +830,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     lora_worklists_free(&w);
     if (!gs.empty()) std::memcpy(p.pinned + p.off_gs, gs.data(), sizeof(lora::GemvItem) * gs.size());
     if (!ge.empty()) std::memcpy(p.pinned + p.off_ge, ge.data(), sizeof(lora::GemvItem) * ge.size());
+    if (!wgs.empty()) std::memcpy(p.pinned + p.off_wgs, wgs.data(), sizeof(lora::GemvWideItem) * wgs.size());
+    if (!wge.empty()) std::memcpy(p.pinned + p.off_wge, wge.data(), sizeof(lora::GemvWideItem) * wge.size());
     if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
     if (!lin_tiles.empty()) std::memcpy(p.pinned + p.off_lin_tiles, lin_tiles.data(), sizeof(lora::DevItem) * lin_tiles.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
@@ -1637,6 +1671,12 @@ static int validate_apply(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_
 // shrink items up to which the one-launch GEMV form is chosen: measured faster than two launches up to
 // 7726 items (2048 one-token requests over 300 adapters: 83 against 86 us); not measured beyond
 constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
+// Wide items (up to 16 rank rows and 8 or 16 tokens) from so many wide shrink items of a launch up, for several groups and for one:
+// with fewer, the items of 4 rows and 4 tokens share the work out better.  One request on every projection of a 7B model,
+// 64 items a launch: 59 us wide, 46 us not; 8 layers' q for 16 requests, about 300: 24.4 against 26.8 us; 64 requests on 32 layers'
+// q 167 against 194 us, 512 on q, k, v, o of 8 layers 791 against 1084 us.  One projection by itself: 200 requests, about
+// 350 items, 21.8 against 20.3 us; 512 requests, about 700, 34.8 against 37.5 us.
+constexpr int GEMV_WIDE_MIN_ITEMS = 256, GEMV_WIDE_MIN_ITEMS_ONE_GROUP = 512;
 constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 20;  // the same for a batch
 static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
 
@@ -1763,8 +1803,17 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *
     return LORA_OK;
 }
 
+// wide items for a GEMV launch of n projections in n_groups groups?
+static bool gemv_wide(const lora_cache_t *c, const lora_plan_t *p, const lora::BatchProj *projs, int n, int n_groups)
+{
+    if (c->dtype != LORA_BF16 || (int64_t)p->n_wgs * n < (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) return false;
+    int64_t supers = 0;  // (a group may be beyond the batch kernels' unit arithmetic, a batch is cut to it)
+    for (int i = 0; i < n; ++i) supers += supers_of(projs[i].h_out);
+    return supers <= lora::GEMV_BATCH_MAX_SUPERS && supers * p->n_wge < (1 << 24);
+}
+
 // The same for a batch of several groups.
-static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, int n, float scale, hipStream_t st, const Scratch &sc,
+static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
                               const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -1775,8 +1824,11 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
     b.vw_set = sc.vtag_set_bytes / sizeof(unsigned long long);
     b.fault = c->fault_dev;
     b.scale = scale;
-    b.m.n_gs = (uint32_t)p->n_gs;
-    b.m.n_ge = (uint32_t)p->n_ge;
+    const bool wide = gemv_wide(c, p, projs, n, n_groups);
+    b.wgs = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wgs);
+    b.wge = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wge);
+    b.m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
+    b.m.n_ge = (uint32_t)(wide ? p->n_wge : p->n_ge);
     b.m.n_proj = (uint32_t)n;
     b.m.by_xcd = b.m.n_gs >= lora::GEMV_BATCH_XCD_ITEMS;
     b.m.shrink_blocks = b.m.by_xcd ? (b.m.n_gs + 7) & ~7u : b.m.n_gs;
@@ -1798,7 +1850,7 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         b.epoch = ++*sc.epoch;
     }
-    HIP_TRY(lora::launch_gemv_batch(c->dtype, b, st, tm, done));
+    HIP_TRY(lora::launch_gemv_batch(c->dtype, b, wide, st, tm, done));
     return LORA_OK;
 }
 
@@ -1807,13 +1859,15 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
 static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
 {
     int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
-    if (p->n_tiles > 0)
+    if (p->n_tiles > 0) {
         projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
-    if (p->n_gs > 0) {
-        projs = std::min<int64_t>(projs, ((1 << 24) - 1) / (p->n_gs + 7));
-        supers = std::min<int64_t>(supers, ((1 << 24) - 1) / std::max(1, p->n_ge));
+        projs = std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (up to a group's size there are tables of their own)
     }
-    max_projs = (int32_t)std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (a group has tables and checks of its own)
+    if (p->n_gs > 0) {
+        projs = std::max<int64_t>(1, std::min<int64_t>(projs, ((1 << 24) - 1) / (p->n_gs + 7)));
+        supers = std::min<int64_t>(supers, ((1 << 24) - 1) / std::max({1, p->n_ge, p->n_wge}));
+    }
+    max_projs = (int32_t)projs;
     max_supers = (int32_t)supers;
 }
 
@@ -1892,8 +1946,8 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups == 1 ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, true, gemv_st, sc, tm, gemv_done)
-                                       : enqueue_gemv_batch(c, p, tb.p, n, scale, gemv_st, sc, tm, gemv_done))
+    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, tb.p, n, 1) ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, true, gemv_st, sc, tm, gemv_done)
+                                       : enqueue_gemv_batch(c, p, tb.p, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
     // the updates of base_out

@@ -89,13 +89,17 @@ inline __host__ __device__ void gemv_shrink_rows(const GemvItem &it, int32_t &j0
     j0 = it.a;
     n = GEMV_SHRINK_ROWS;
 }
-// output columns [c0, c1) of expand item `it` in super-chunk `sc` of a projection h_out wide (empty if c0 >= c1)
-inline __host__ __device__ void gemv_expand_cols(const GemvItem &it, int32_t sc, int32_t h_out, int32_t &c0, int32_t &c1)
+// `width` output columns [c0, c1) from a * 64 on in super-chunk `sc` of a projection h_out wide (empty if c0 >= c1)
+inline __host__ __device__ void gemv_cols(int32_t width, int32_t a, int32_t sc, int32_t h_out, int32_t &c0, int32_t &c1)
 {
-    c0 = sc * GEMV_SUPER_COLS + it.a * 64;
-    const int32_t end = c0 + gemv_expand_width(it.rank), super_end = (sc + 1) * GEMV_SUPER_COLS;
+    c0 = sc * GEMV_SUPER_COLS + a * 64;
+    const int32_t end = c0 + width, super_end = (sc + 1) * GEMV_SUPER_COLS;
     c1 = end < super_end ? end : super_end;
     if (c1 > h_out) c1 = h_out;
+}
+inline __host__ __device__ void gemv_expand_cols(const GemvItem &it, int32_t sc, int32_t h_out, int32_t &c0, int32_t &c1)
+{
+    gemv_cols(gemv_expand_width(it.rank), it.a, sc, h_out, c0, c1);
 }
 
 // A batch: the projections one launch serves.  They do not depend on each other (no output overlaps another entry's
@@ -212,8 +216,31 @@ inline __host__ __device__ void gemv_batch_unit(uint32_t u, const GemvBatchMap &
     super = div24(u, m.div_ge);
     item = u - super * m.n_ge;
 }
+// Wide work items, for launches that fill the chip with them (bf16): a shrink item is up to GEMV_WIDE_ROWS stored rank rows
+// (8 or 16) and GEMV_WIDE_SHRINK_TOKENS tokens, an expand item the columns of a GemvItem and GEMV_WIDE_TOKENS tokens.  What bounds such
+// a launch is what the compute units take in (6 to 8 TB/s over all of them): per slab row the items of 4 rows and 4 tokens
+// take in the activations of their tokens once per 4 rows, and a slab once per 4 tokens.
+constexpr int GEMV_WIDE_ROWS = 16, GEMV_WIDE_SHRINK_TOKENS = 8, GEMV_WIDE_TOKENS = 16;
+struct GemvWideItem {
+    int32_t row, rank, a;  // as in GemvItem
+    float alpha;
+    int32_t n_tok, pad[3];
+    int32_t tok[GEMV_WIDE_TOKENS];  // entries from n_tok on repeat the first
+};
+static_assert(sizeof(GemvWideItem) == 96, "items are read in 16-byte pieces");
+// stored rank rows of a wide shrink item
+inline __host__ __device__ int32_t gemv_wide_rows(int32_t rank, int32_t j0) { return rank_storage(rank) - j0 >= GEMV_WIDE_ROWS ? GEMV_WIDE_ROWS : 8; }
+// columns of a wide expand item: those of a GemvItem, half of them up to rank 32 (8 KB of Bp: with 16 KB and the base_out rows
+// of 16 products a lane would need more than the 128 registers that four wavefronts per SIMD leave it)
+inline __host__ __device__ int32_t gemv_wide_width(int32_t rank) { return rank <= 32 ? gemv_expand_width(rank) / 2 : gemv_expand_width(rank); }
+inline __host__ __device__ void gemv_wide_cols(int32_t rank, int32_t a, int32_t sc, int32_t h_out, int32_t &c0, int32_t &c1)
+{
+    gemv_cols(gemv_wide_width(rank), a, sc, h_out, c0, c1);
+}
 struct GemvBatch {
     const GemvItem *gs, *ge;  // device: shrink and expand items
+    const GemvWideItem *wgs, *wge;  // the same as wide items: what gemv_wide_kernel reads, with m for their numbers
+    float *y32;               // as GemvProj::y32 (a batch of one, wide)
     unsigned long long *vw;   // hand-over words of projection 0; those of projection p lie vw_set words behind those of p - 1
     uint64_t vw_set;
     int32_t *fault;
@@ -266,7 +293,7 @@ inline void launch_k(const KernelTimer *tm, hipEvent_t done, int kind, K kernel,
 // GEMV shrink and expand of the group's projections: phase 0 as one launch (a.epoch != 0: the expand
 // wavefronts wait for the hand-over words to carry that number), phases 1 and 2 as two
 hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
-hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // bytes of one projection's hand-over words for max_tokens tokens
 size_t gemv_handover_bytes(int dtype, int64_t max_tokens);
 // zeroes the hand-over words of tokens toks[0 .. n) (device list) in `sets` sets from `vw` on, vw_set words apart

@@ -8,25 +8,34 @@ import torch
 pytestmark = pytest.mark.gpu
 
 PROJS = [(512, 512), (512, 512), (512, 192), (512, 1088), (512, 512), (512, 64), (192, 512), (1088, 512), (2112, 2240)]  # 0..5 read one x
+# lengths, ranks, tokens from which tiles are formed, tokens per slot (None: dealt out in turn, every seventh without an adapter)
 BATCHES = {
-    "one token": ([1], [16]),
-    "decode": ([1] * 90, [8, 16, 12, 32, 64, 96, 128, 33]),            # more than 64 shrink items
-    "few prompts": ([77, 9], [16, 128]),
-    "tiles of a few tokens": ([9, 10, 11, 12, 13, 14, 15, 8] * 3, [8, 40, 128]),
-    "mixed": ([300, 1, 65, 1, 1, 17, 128, 1, 3, 1, 200], [16, 64, 128, 8]),
+    "one token": ([1], [16], 8, None),
+    "decode": ([1] * 90, [8, 16, 12, 32, 64, 96, 128, 33], 8, None),
+    "decode, no tiles": ([1] * 90, [8, 16, 12, 32, 64, 96, 128, 33], 1000, None),  # more than 64 shrink items
+    # every number of tokens of an item and its remainders, with ranks of every body: 8 and 16 rows, 1 to 4 k steps
+    "popular": (None, [8, 16, 24, 32, 5, 12, 100, 128, 64, 33, 40, 72], 1000, [1, 2, 3, 4, 5, 8, 9, 12, 16, 17, 7, 35]),
+    "popular, other ranks": (None, [128, 100, 64, 33, 8, 3, 16, 11, 24, 8, 16, 8], 1000, [1, 2, 3, 4, 5, 8, 9, 12, 16, 17, 7, 35]),
+    "few prompts": ([77, 9], [16, 128], 8, None),
+    "tiles of a few tokens": ([9, 10, 11, 12, 13, 14, 15, 8] * 3, [8, 40, 128], 8, None),
+    "mixed": ([300, 1, 65, 1, 1, 17, 128, 1, 3, 1, 200], [16, 64, 128, 8], 8, None),
 }
 
 
-def _setup(lens, ranks, layers, dtype="bf16", flags=0, m0=8):
+def _setup(lens, ranks, m0, counts, layers, dtype="bf16", flags=0):
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
+    if counts:
+        slot = np.random.default_rng(1).permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)
+        lens = [1] * len(slot)
+    else:
+        slot = np.asarray([i % len(ranks) if i % 7 != 6 else -1 for i in range(len(lens))], np.int32)
     T = sum(lens)
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(len(lens) + layers)
     normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda", dtype=dt).mul_(sigma)
     off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
-    slot = np.asarray([i % len(ranks) if i % 7 != 6 else -1 for i in range(len(lens))], np.int32)
     pool = LoraPool(PROJS, layers, [128], [len(ranks)], B.LORA_BF16 if dtype == "bf16" else B.LORA_F32, max_tokens=T,
                     max_segments=len(lens), mfma_min_tokens=m0 if dtype == "bf16" else 0, flags=flags)
     for s, r in enumerate(ranks):
