@@ -389,8 +389,8 @@ __global__ __launch_bounds__(256) void mfma_reduce_kernel(TileBatchArgs<N> tb)
 
 // ---------------------------------------------------------------------------------------
 // expand.  Block = 4 wavefronts, tile of up to 64 tokens x (128 * n_pass) columns in passes of
-// 128 columns (the launcher picks n_pass: long column runs per block amortise the staging of V
-// when there are many tiles, short ones keep the chip full when there are few); wavefront w owns token half w&1 and column half w>>1 of a pass (32 tokens x 64
+// 128 columns (the launcher picks n_pass: longer column runs amortise the staging of V, shorter ones
+// sweep base_out faster and keep the chip full when there are few tiles); wavefront w owns token half w&1 and column half w>>1 of a pass (32 tokens x 64
 // columns).  The scaled V tile is staged once in LDS as bf16.  The product is formed
 // transposed (rows = output columns, columns = tokens): MFMA row r of column block b is column
 // 16b + r, so the 16 lanes of a Bp operand load read 256 contiguous bytes.
@@ -399,8 +399,10 @@ __global__ __launch_bounds__(256) void mfma_reduce_kernel(TileBatchArgs<N> tb)
 // which stalls L1 on the second): the wavefront parks its fp32 products in LDS and goes over
 // base_out with 8 lanes per token row, whole 128-byte lines per instruction, for the load (issued
 // one pass ahead), the add and the store.
-// Register use is held to three blocks per CU (the V operands are re-read from LDS in every pass
-// rather than kept): with two, short launches of a few hundred blocks leave CUs idle at the end.
+// Register use of a group's launch is held to three blocks per CU (the V operands are re-read from LDS in every pass
+// rather than kept): with two, short launches of a few hundred blocks leave CUs idle at the end (one prompt of 700 tokens,
+// call by call: 391 us instead of 371).  A batch's launch is long and takes two blocks per CU: fewer rows of base_out are in flight at
+// once, and memory serves them faster (13B mixed batch 922 -> 862 us).
 // ---------------------------------------------------------------------------------------
 namespace {
 constexpr int CS_ROW = 64 * 4 + 16;  // bytes per token row of a wavefront's parked products (padded)
@@ -561,25 +563,18 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
     }
 }
 
-// Blocks -> (projection, tile, column run).  A projection's blocks start at a multiple of 8.  Block b runs on XCD b % 8; the
-// blocks are numbered so that a column run -- the same columns of every tile -- always falls on the same XCD (or the same
-// two or four), and a prompt's Bp is fetched from memory by one XCD per column run instead of by all eight (with the tiles
-// as the fast index the prefill expand fetched 147 MB for 101 MB).  The column runs go in groups of eight: within a group
-// block (tile * 8 + run % 8) works on that tile and run; what is left over after the whole groups forms a last group of
-// 1, 2, 4 or 8 runs (the next power of two: at most a twelfth of a launch's blocks are padding, which return at once --
-// padding every launch to a multiple of 8 runs cost the two 11-run launches of the mixed configuration 29 us each).
+// Blocks -> (projection, tile, column run).  What the launch is bound by is base_out, read and written, and the rate of that
+// depends on the order: with the column runs as the fast index the blocks in flight cover whole rows of a few tiles
+// (a read-modify-write of this shape alone: 5.6 TB/s in runs of 1024 columns, 6.2 in runs of 256), with the tiles as the fast
+// index a column window of many (4.2 TB/s).  A tile's runs are numbered up to the next multiple of 8, so that a run -- the
+// same columns of every tile -- always falls on the same XCD (block b runs on XCD b % 8) and a prompt's Bp is fetched from memory by one
+// XCD per column run instead of by all eight; the blocks past the last run return at once.
 template <int N> struct ExpandShape {
-    int32_t n_pass;      // passes of 128 columns per block
     int32_t blk_end[N];  // blocks of projections 0 .. p (entries past the batch repeat the last)
+    int32_t runs[N];     // per projection: passes of 128 columns per run | blocks per tile (a multiple of 8) << 8
 };
-// blocks of n_tiles x n_runs as numbered above, without the rounding to a multiple of 8
-inline __host__ __device__ int expand_last_width(int n_runs)
-{
-    const int rest = n_runs & 7;
-    return rest == 0 ? 0 : (rest == 1 ? 1 : (rest == 2 ? 2 : (rest <= 4 ? 4 : 8)));
-}
 template <int N>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void mfma_expand_kernel(TileBatchArgs<N> tb, ExpandShape<N> sh)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N > GROUP_MAX_PROJS ? 2 : 3, N > GROUP_MAX_PROJS ? 2 : 3))) void mfma_expand_kernel(TileBatchArgs<N> tb, ExpandShape<N> sh)
 {
     __shared__ __attribute__((aligned(16))) unsigned char vs[LORA_TILE_TOKENS * VS_ROW];
     __shared__ __attribute__((aligned(16))) unsigned char cs[4][32 * CS_ROW];
@@ -591,26 +586,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
     const int b = (int)blockIdx.x - (pj ? sh.blk_end[pj - 1] : 0);
     const ApplyArgs a = tile_args(tb, pj);
-    const int n_tiles = tb.n_tiles, n_runs = (a.h_out + sh.n_pass * 128 - 1) / (sh.n_pass * 128);
-    const int whole = (n_runs >> 3) * n_tiles * 8;  // blocks of the groups of eight
-    int tile, col_run;
-    if (b < whole) {
-        const int grp = b / (n_tiles * 8), r = b - grp * n_tiles * 8;
-        tile = r >> 3;
-        col_run = 8 * grp + (r & 7);
-    } else {
-        const int r = b - whole, last_width = expand_last_width(n_runs);
-        if (last_width == 0) return;  // padding
-        tile = r / last_width;
-        col_run = (n_runs & ~7) + (r - tile * last_width);
-        if (col_run >= n_runs || tile >= n_tiles) return;  // padding
-    }
+    const int n_pass = sh.runs[pj] & 0xff, width = sh.runs[pj] >> 8;
+    const int tile = b / width, col_run = b - tile * width;
+    if (col_run * n_pass * 128 >= a.h_out) return;  // padding
     const DevItem it = tb.tiles[tile];
     switch ((it.rank + 31) >> 5) {
-    case 1: mfma_expand_body<1>(a, it, col_run, sh.n_pass, vs, cs); break;
-    case 2: mfma_expand_body<2>(a, it, col_run, sh.n_pass, vs, cs); break;
-    case 3: mfma_expand_body<3>(a, it, col_run, sh.n_pass, vs, cs); break;
-    default: mfma_expand_body<4>(a, it, col_run, sh.n_pass, vs, cs); break;
+    case 1: mfma_expand_body<1>(a, it, col_run, n_pass, vs, cs); break;
+    case 2: mfma_expand_body<2>(a, it, col_run, n_pass, vs, cs); break;
+    case 3: mfma_expand_body<3>(a, it, col_run, n_pass, vs, cs); break;
+    default: mfma_expand_body<4>(a, it, col_run, n_pass, vs, cs); break;
     }
 }
 
@@ -645,33 +629,38 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
     return hipGetLastError();
 }
 
+// Longest column run, in passes: in a batch eight runs to a tile whenever that is possible -- one per XCD -- (7B mixed batch 2056 us
+// with 8 passes, 2005 with 16; 13B 862 and 832), in a group's launch, which a few tiles have to spread over the chip, shorter.
+constexpr int EXPAND_PASSES_BATCH = 16, EXPAND_PASSES_GROUP = 8;
 hipError_t launch_mfma_expand(const TileBatch &batch, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
     if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
-    // the widest column run per block that still gives 512 blocks (two per CU), else the narrowest
-    auto runs_of = [&](int i, int cols) { return (batch.p[i].h_out + cols - 1) / cols; };
-    int cols = 1024;
-    for (; cols > 256; cols >>= 1) {
-        int64_t blocks = 0;
-        for (int i = 0; i < batch.n; ++i) blocks += (int64_t)batch.n_tiles * runs_of(i, cols);
-        if (blocks >= 512) break;
-    }
+    // blocks per tile: the multiple of 8 that keeps a run within the limit; shorter runs (at least two passes) where that leaves the launch below 512 blocks (two per CU)
+    int32_t shape[BATCH_MAX_PROJS];
     int64_t total = 0;
-    auto blocks_of = [&](int i) {
-        const int n_runs = runs_of(i, cols);
-        return ((int64_t)batch.n_tiles * ((n_runs & ~7) + expand_last_width(n_runs)) + 7) / 8 * 8;
-    };
-    for (int i = 0; i < batch.n; ++i) total += blocks_of(i);
+    for (int passes = batch.n > GROUP_MAX_PROJS ? EXPAND_PASSES_BATCH : EXPAND_PASSES_GROUP;; passes >>= 1) {
+        int64_t live = 0;
+        total = 0;
+        for (int i = 0; i < batch.n; ++i) {
+            const int all = (batch.p[i].h_out + 127) / 128, width = (all + 8 * passes - 1) / (8 * passes) * 8;  // blocks per tile
+            const int n_pass = std::max(std::min(2, all), (all + width - 1) / width);
+            const int used = (all + n_pass - 1) / n_pass, padded = (used + 7) / 8 * 8;
+            shape[i] = n_pass | padded << 8;
+            live += (int64_t)batch.n_tiles * used;
+            total += (int64_t)batch.n_tiles * padded;
+        }
+        if (live >= 512 || passes <= 2) break;
+    }
     if (total > INT32_MAX) return hipErrorInvalidValue;
     with_batch_size(batch, [&](const auto &tb) {
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
         ExpandShape<N> sh;
-        sh.n_pass = cols / 128;
         int32_t end = 0;
         for (int i = 0; i < N; ++i) {
-            if (i < tb.n) end += (int32_t)blocks_of(i);
+            if (i < tb.n) end += tb.n_tiles * (shape[i] >> 8);
             sh.blk_end[i] = end;
+            sh.runs[i] = i < tb.n ? shape[i] : 0;
         }
         launch_k(tm, done, LORA_K_MFMA_EXPAND, mfma_expand_kernel<N>, dim3((unsigned)end), dim3(256), 0, st, tb, sh);
     });
