@@ -1762,7 +1762,7 @@ static bool one_gemv_launch(const lora_cache_t *c, const Scratch &sc, int64_t it
 // The GEMV part of a group of n projections that read the same x: one launch with the in-kernel
 // hand-over when the part is small (the launch in between then costs more than the hand-over), else a
 // shrink and an expand launch.  y32[i], when set, receives projection i's update as fp32 instead of y.
-static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *a, float *const *y32, int n, float scale, bool allow_one_launch,
+static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *a, float *const *y32, int n, float scale,
                         hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -1795,7 +1795,7 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *
         gm.unit_end[i] = (int32_t)std::min<int64_t>(units, INT32_MAX);
     }
     if (units >= (1 << 24) || (int64_t)p->n_gs * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
-    if (allow_one_launch && one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_ITEMS)) {
+    if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_ITEMS)) {
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         ga.epoch = ++*sc.epoch;
     }
@@ -1813,7 +1813,7 @@ static bool gemv_wide(const lora_cache_t *c, const lora_plan_t *p, const lora::B
 }
 
 // The same for a batch of several groups.
-static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
+static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, float *y32, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
                               const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -1822,6 +1822,7 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
     b.ge = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_ge);
     b.vw = reinterpret_cast<unsigned long long *>(sc.vtag);
     b.vw_set = sc.vtag_set_bytes / sizeof(unsigned long long);
+    b.y32 = y32;
     b.fault = c->fault_dev;
     b.scale = scale;
     const bool wide = gemv_wide(c, p, projs, n, n_groups);
@@ -1946,8 +1947,8 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, tb.p, n, 1) ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, true, gemv_st, sc, tm, gemv_done)
-                                       : enqueue_gemv_batch(c, p, tb.p, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
+    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, tb.p, n, 1) ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
+                                       : enqueue_gemv_batch(c, p, tb.p, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
     // the updates of base_out
@@ -2068,7 +2069,11 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     a.scale = scale;
     int32_t f;
     if (const int rc_f = take_fence(c, st, f)) return rc_f;
-    // shrink of the tiles and of the GEMV groups (x is read, v written)
+    // shrink of the tiles (x is read, v written), then the adapter term of the GEMV tokens: as fp32 into the caller's workspace
+    // (row = token), or, without one, into their zeroed output rows (rounded to the output type on the way).  One after the
+    // other: the GEMV launch on the side stream, between a fork off the last base product and a join into the next, waits 10 us at
+    // both for 20 us of shrink and reduce beside it (a 13B layer 2034 us, 2015 us this way).
+    const int32_t n_gemv_tok = p->n_tok_list - p->n_tile_tok;
     if (p->n_tiles > 0) {
         lora::TileBatch tb;
         if (const int rc_s = tile_setup(c, p, 1, pool_scratch(c), scale, tb)) return rc_s;
@@ -2076,13 +2081,13 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         tb.group[0] = 1u << 8;
         HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
-    // the adapter term of the GEMV tokens: as fp32 into the caller's workspace (row = token), or, without
-    // one, into their zeroed output rows (rounded to the output type on the way)
-    if (p->n_tok_list > p->n_tile_tok) {
+    if (n_gemv_tok > 0) {
         a.y32 = static_cast<float *>(workspace);
-        if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + p->n_tile_tok, p->n_tok_list - p->n_tile_tok, a.h_out, st));
+        if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + p->n_tile_tok, n_gemv_tok, a.h_out, st));
         float *const y32 = a.y32;
-        if (const int rc_g = enqueue_gemv(c, p, &bp, &y32, 1, scale, false, st, pool_scratch(c), tm, nullptr)) return rc_g;
+        if (const int rc_g = gemv_wide(c, p, &bp, 1, 1) ? enqueue_gemv_batch(c, p, &bp, y32, 1, 1, scale, st, pool_scratch(c), tm, nullptr)
+                                                        : enqueue_gemv(c, p, &bp, &y32, 1, scale, st, pool_scratch(c), tm, nullptr))
+            return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
     lora::ApplyArgs lin = a;

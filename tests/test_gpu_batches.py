@@ -155,3 +155,38 @@ def test_a_captured_batch_replays(batch):
                 assert torch.equal(a, b), f"entry {k}"
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("workspace", [True, False])
+@pytest.mark.parametrize("n_prompt", [0, 130])
+def test_linear_with_many_requests(n_prompt, workspace):
+    """The adapter term of requests in numbers that take wide items, as fp32 into the workspace or into the zeroed rows,
+    beside the tile shrink of a prompt or without one."""
+    ranks = [8, 16, 24, 32, 5, 12, 100, 128, 64, 33, 40, 72] * 8
+    counts = [1 + (5 * i) % 19 for i in range(len(ranks))]
+    B, pool, plan, T, normal = _setup(None, ranks, 100 if n_prompt else 1000, counts, 1)
+    pool.plan_destroy(plan)
+    try:
+        slot = np.random.default_rng(1).permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)
+        lens = np.ones(len(slot), np.int32)
+        if n_prompt:
+            lens[7] = n_prompt  # one of the requests as a prompt, the last ones left out
+            lens = lens[: len(slot) - n_prompt + 1]
+            slot = slot[: len(lens)]
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        plan = pool.plan(int(off[-1]), off, slot, np.asarray(ranks, np.int32)[slot])
+        T, p = int(off[-1]), 3
+        h_in, h_out = PROJS[p]
+        x, wt, zeros = normal(T, h_in), normal(h_out, h_in, sigma=0.05), torch.zeros(T, h_out, dtype=torch.bfloat16, device="cuda")
+        sh = torch.cuda.current_stream().cuda_stream
+        space = torch.empty(T * h_out, dtype=torch.float32, device="cuda")
+        pool.apply_plan(plan, 0, p, x, zeros, 2.0)  # the adapter terms alone, each rounded once
+        want = x.double() @ wt.double().t() + zeros.double()
+        for _ in range(2):
+            y = torch.full((T, h_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.check(B.lora_linear_plan(pool.handle, plan, 0, p, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0, sh,
+                                       space.data_ptr() if workspace else 0, space.numel() * 4 if workspace else 0))
+            pool.check_fault()
+            _same(y, want, "bf16", f"prompt {n_prompt}, workspace {workspace}")
+    finally:
+        pool.close()
