@@ -570,6 +570,18 @@ void build_shrink_runs(const lora::DevItem *tiles, int n_tiles, int quanta, int 
     }
 }
 
+// Wide items (up to 16 rank rows and 8 or 16 tokens) from so many wide shrink items of a launch up, for several groups and for one:
+// with fewer, the items of 4 rows and 4 tokens share the work out better.  One request on every projection of a 7B model,
+// 64 items a launch: 59 us wide, 46 us not; 8 layers' q for 16 requests, about 300: 24.4 against 26.8 us; 64 requests on 32 layers'
+// q 167 against 194 us, 512 on q, k, v, o of 8 layers 791 against 1084 us.  One projection by itself: 200 requests, about
+// 350 items, 21.8 against 20.3 us; 512 requests, about 700, 34.8 against 37.5 us.
+constexpr int GEMV_WIDE_MIN_ITEMS = 256, GEMV_WIDE_MIN_ITEMS_ONE_GROUP = 512;
+int64_t wide_shrink_items(int32_t n_tok, int32_t rank)
+{
+    return (int64_t)((n_tok + lora::GEMV_WIDE_SHRINK_TOKENS - 1) / lora::GEMV_WIDE_SHRINK_TOKENS) *
+           ((lora::rank_storage(rank) + lora::GEMV_WIDE_ROWS - 1) / lora::GEMV_WIDE_ROWS);
+}
+
 // `place` now holds fence `f` (-1: none) instead of the one it held
 void hold_fence(lora_cache &c, int32_t &place, int32_t f)
 {
@@ -711,7 +723,11 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
                 }
             }
     }
-    for (int gi = 0; gi < w.n_groups && c.dtype == LORA_BF16; ++gi) {
+    // (lora_apply's own plans serve one projection: no wide items where that would not take them)
+    int64_t n_wide = 0;
+    for (int gi = 0; gi < w.n_groups; ++gi) n_wide += wide_shrink_items(w.groups[gi].n_tok, w.groups[gi].rank);
+    const bool make_wide = c.dtype == LORA_BF16 && (!p.internal || n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP);
+    for (int gi = 0; gi < w.n_groups && make_wide; ++gi) {
         const lora_item_t &gr = w.groups[group_order[gi]];
         lora::GemvWideItem d{};
         d.row = c.slot_row[gr.slot];
@@ -743,6 +759,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         const int64_t slots = std::min<int64_t>(SHRINK_MAX_RUNS, 2 * (int64_t)c.n_cu);
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
         for (int v = 0; v < SHRINK_VARIANTS && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
+            if (v > 0 && p.internal) break;  // (lora_apply's own plans serve one projection)
             if (v == SHRINK_VARIANT_SMALL && T > LORA_STATIC_MAX_TOKENS) continue;  // lora_apply_plan_static refuses such a batch
             const int n = v >= SHRINK_VARIANT_SMALL ? 1 : v + 1;
             int64_t max_runs = v >= SHRINK_VARIANT_BATCH ? SHRINK_BATCH_RUNS[v - SHRINK_VARIANT_BATCH] : slots / 8 / n * 8;
@@ -1671,13 +1688,9 @@ static int validate_apply(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_
 // shrink items up to which the one-launch GEMV form is chosen: measured faster than two launches up to
 // 7726 items (2048 one-token requests over 300 adapters: 83 against 86 us); not measured beyond
 constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
-// Wide items (up to 16 rank rows and 8 or 16 tokens) from so many wide shrink items of a launch up, for several groups and for one:
-// with fewer, the items of 4 rows and 4 tokens share the work out better.  One request on every projection of a 7B model,
-// 64 items a launch: 59 us wide, 46 us not; 8 layers' q for 16 requests, about 300: 24.4 against 26.8 us; 64 requests on 32 layers'
-// q 167 against 194 us, 512 on q, k, v, o of 8 layers 791 against 1084 us.  One projection by itself: 200 requests, about
-// 350 items, 21.8 against 20.3 us; 512 requests, about 700, 34.8 against 37.5 us.
-constexpr int GEMV_WIDE_MIN_ITEMS = 256, GEMV_WIDE_MIN_ITEMS_ONE_GROUP = 512;
-constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 20;  // the same for a batch
+// The same for a batch, whose shrink blocks are long done when its expand blocks are dispatched: one launch up to the range of the
+// unit arithmetic (64 requests on 32 projections, 15808 items: 167 against 180 us; 512 requests, 91328 items: 792 against 803 us).
+constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
 static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
 
 static Scratch pool_scratch(lora_cache_t *c)
