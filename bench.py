@@ -35,15 +35,15 @@ WORKLOAD_TEXT = {
     "decode_qkv": "decode_qkv (extra): the decode configuration's batch on the projections q, k, v (4096->4096 bf16 each, same activations), applied as one group",
     "decode_paper": "decode_paper (extra): one-token requests, one 4096->4096 bf16 projection, the paper's adapter population: --adapters N_a, N_a/5 of each rank 8..128, rank uniform, power law within the rank",
 }
-# HBM bytes per launch (average over a layer's launches of that kernel) from rocprofv3 counter runs of this same
+# HBM bytes per launch (one launch serves a batch of layers) from rocprofv3 counter runs of this same
 # script (FETCH_SIZE and WRITE_SIZE, each in a run of its own, scaled by what the same counters read for a plain
 # 256 MiB copy).  A counter run cannot happen inside this process, so the figures measured for the same workloads
 # are carried here; the line names their source, and they are left out when the flags change what is launched.
 TRAFFIC_SOURCE = "profiles/kernel_traffic_all_workloads.txt"
-MEASURED_TRAFFIC = {("decode", "gemv_fused"): 24.74e6, ("decode_qkv", "gemv_fused"): 71.81e6, ("prefill", "mfma_shrink"): 66.64e6,
-                    ("prefill", "mfma_expand"): 121.58e6, ("mixed", "mfma_expand"): 558.77e6, ("mixed", "mfma_shrink"): 404.12e6,
-                    ("mixed", "gemv_fused"): 177.94e6, ("stress", "gemv_fused"): 356.77e6, ("stress", "mfma_expand"): 103.75e6,
-                    ("stress", "mfma_shrink"): 73.25e6}
+MEASURED_TRAFFIC = {("decode", "gemv_fused"): 378.9e6, ("decode_qkv", "gemv_fused"): 1115.9e6, ("prefill", "mfma_expand"): 971.1e6,
+                    ("prefill", "mfma_shrink"): 589.7e6, ("mixed", "gemv_fused"): 1402.4e6, ("mixed", "mfma_expand"): 7961.2e6,
+                    ("mixed", "mfma_shrink"): 4168.5e6, ("stress", "gemv_fused"): 2743.6e6, ("stress", "mfma_expand"): 1324.2e6,
+                    ("stress", "mfma_shrink"): 714.7e6}
 DEFAULT_LAYERS = {"decode": 32, "prefill": 8, "mixed": 2, "stress": 4, "decode_heavy": 8, "decode_paper": 32, "decode_qkv": 16}
 DEFAULT_STEPS = {"decode": 100, "prefill": 60, "mixed": 20, "stress": 20, "decode_heavy": 40, "decode_paper": 100, "decode_qkv": 100}
 
