@@ -66,6 +66,8 @@ enum {
     LORA_CACHE_NO_OVERLAP = 16,   /* every kernel of an apply on the caller's stream: by default the GEMV launch of a batch that
                                      also has tiles runs on a stream of the cache's own, forked off the caller's stream and
                                      joined to it again inside the call, side by side with the tile kernels (different tokens) */
+    LORA_CACHE_SMALL_SCRATCH = 32, /* scratch for up to 4 projections at a time instead of up to 64, staging for one part of an adapter:
+                                     see lora_cache_bytes_required */
     LORA_CACHE_DIRECT_FILL = 8    /* fills read pinned host memory from the repack kernel itself instead of copying it
                                      to a staging buffer first: about twice the fill rate on an idle device, but applies
                                      that run at the same time are slowed down much more (measured 1.6x against 1.1x) */
@@ -107,14 +109,18 @@ typedef struct {
  * model is 4 projections x 32 layers of this at 16 bit.)  0 on bad arguments. */
 size_t lora_adapter_bytes(int32_t h_in, int32_t h_out, int32_t rank, int32_t dtype);
 
-/* Bytes the caller must provide to lora_cache_create: slabs of every (layer,
- * projection, slot) + scratch + plan buffers + fill staging.  0 on a bad config. */
+/* Bytes of the pool: slabs of every (layer, projection, slot) + scratch + plan buffers + fill staging.  0 on a bad config.
+ * The scratch holds the intermediates of up to 64 projections that one list call works on at a time (as many as fit into
+ * 512 MB), up to 64 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
+ * most 48 MB of partial sums and staging for one part of an adapter: the same results, but list calls run 4
+ * projections at a time, launches with many one-token requests and split tiles of the fused product have less to work with, and staged fills travel part by part. */
 size_t lora_cache_bytes_required(const lora_cache_config_t *cfg);
 
 /* ---- pool life cycle ----------------------------------------------------------------- */
 
-/* Carve `dev_pool` (device, >= lora_cache_bytes_required bytes, 256-byte aligned,
- * caller-owned, must outlive the cache) into slabs and scratch, build the slot table.
+/* Carve `dev_pool` (device, 256-byte aligned, caller-owned, must outlive the cache) into slabs and scratch, build the
+ * slot table.  A pool of fewer than lora_cache_bytes_required bytes is taken as with LORA_CACHE_SMALL_SCRATCH, if it has the bytes
+ * that are required with that flag (LORA_E_NOMEM otherwise).
  * Uploads a small offset table (blocking).  With LORA_CACHE_HOST_ONLY, dev_pool may be
  * NULL and only the slot-table calls work. */
 int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev_pool_bytes, lora_cache_t **out);

@@ -167,6 +167,7 @@ struct lora_cache {
     std::vector<int32_t> class_rank, class_slots, class_first;
     int32_t n_layers = 0, n_slots = 0, dtype = 0, esize = 0;
     int32_t max_tokens = 0, max_segments = 0, n_user_plans = 0, mfma_min = 0, flags = 0;
+    bool small_scratch = false;  // the pool holds the scratch of a group of projections only
     bool mfma_min_auto = false;  // the configuration left the threshold to the library
     int32_t v_stride = 0;
     bool host_only = false;
@@ -257,9 +258,11 @@ bool config_ok(const lora_cache_config_t *cfg)
     return total_slots >= 1 && total_slots * (int64_t)LORA_MAX_RANK < (int64_t)1 << 31;
 }
 
-// Fills every layout field of `c` from the config; used by bytes_required and create alike.
-void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
+// Fills every layout field of `c` from the config; used by bytes_required and create alike.  small_scratch: what a group
+// of projections needs and no more -- no further sets, run tables and wide items for batches, staging for one part.
+void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_scratch)
 {
+    c.small_scratch = small_scratch;
     c.proj.assign(cfg->proj, cfg->proj + cfg->n_proj);
     c.class_rank.assign(cfg->class_rank, cfg->class_rank + cfg->n_classes);
     c.class_slots.assign(cfg->class_slots, cfg->class_slots + cfg->n_classes);
@@ -308,16 +311,17 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     // GEMV items: per token batch up to 32 shrink + 16 expand items; batches <= groups + tokens/4
     const size_t max_batches = (size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_BATCH + 1;
     const size_t max_items = max_tiles + max_batches * (LORA_MAX_RANK / 4 + 16);
-    const size_t max_wide = c.dtype != LORA_BF16 ? 0
+    const size_t max_wide = c.dtype != LORA_BF16 || small_scratch ? 0
                                                  : ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_SHRINK_TOKENS + 1) * (LORA_MAX_RANK / lora::GEMV_WIDE_ROWS) +
                                                        ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_TOKENS + 1) * 16;
+    const int n_tables = small_scratch ? SHRINK_VARIANT_BATCH : SHRINK_VARIANTS;
     c.plan_cap = align_up(sizeof(int32_t) * (size_t)c.max_tokens) + align_up(sizeof(lora_item_t) * max_items) +
-                 align_up(sizeof(int32_t) * max_batches) + 6 * ALIGN + align_up(sizeof(lora::GemvWideItem) * max_wide) +
+                 align_up(sizeof(int32_t) * max_batches) + 4 * ALIGN + (max_wide ? align_up(sizeof(lora::GemvWideItem) * max_wide) + 2 * ALIGN : 0) +
                  align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
                  align_up(sizeof(lora_item_t) * (max_tiles + (size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
-                 SHRINK_VARIANTS * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
+                 n_tables * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
     // fill staging: a buffer takes parts of an adapter until STAGE_BYTES (or the largest adapter) are in it
-    c.stage_cap = align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
+    c.stage_cap = small_scratch ? align_up(max_part) + ALIGN : align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
 
     size_t cur = align_up(c.layer_stride * (size_t)c.n_layers);
     c.off_counts = cur;
@@ -325,7 +329,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
     c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
-    c.n_sets = (int)std::min<size_t>(std::min<size_t>(lora::BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
+    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>(lora::BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
                                      std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / (c.v_set_bytes + c.vtag_set_bytes)));
     cur += c.v_set_bytes * c.n_sets;
     // partial sums of the tile shrink: two slots per run and projection; a launch has at most SHRINK_MAX_RUNS blocks
@@ -333,14 +337,16 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg)
     // least two of the parts a tile's k range is cut into)
     {
         const int64_t tiles = std::max<int64_t>(1, ((int64_t)c.max_tokens + LORA_TILE_TOKENS - 1) / LORA_TILE_TOKENS);
-        const int64_t runs = std::min<int64_t>(2 * SHRINK_MAX_RUNS, 16 * c.n_sets * tiles);
+        const int64_t runs = std::min<int64_t>((small_scratch ? 1 : 2) * SHRINK_MAX_RUNS, 16 * c.n_sets * tiles);
         c.vpart_rows = c.dtype == LORA_BF16 ? 2 * lora::SHRINK_SLOT_ROWS * runs : 0;
     }
     c.off_vpart = cur;
     c.vpart_bytes = align_up(sizeof(float) * (size_t)c.vpart_rows * c.v_stride);
     // (the fused linear kernel parks the sums of its split tiles in the same region: a round of 256 blocks that are all
     // parts of split tiles, 256 KB each; less for caches of small batches)
-    if (c.dtype == LORA_BF16) {
+    if (c.dtype == LORA_BF16 && small_scratch) {
+        c.vpart_bytes = std::max(c.vpart_bytes, std::min<size_t>((size_t)48 << 20, align_up(sizeof(float) * (size_t)c.v_stride * 8 * (size_t)c.max_tokens)));
+    } else if (c.dtype == LORA_BF16) {
         const size_t row_tiles = std::min<size_t>((size_t)c.max_tokens, (size_t)c.max_tokens / LORA_TILE_TOKENS + (size_t)c.max_segments) + 2;
         size_t col_tiles = 1;
         for (const auto &pr : c.proj) col_tiles = std::max(col_tiles, ((size_t)pr.h_out + 255) / 256);
@@ -726,7 +732,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // (lora_apply's own plans serve one projection: no wide items where that would not take them)
     int64_t n_wide = 0;
     for (int gi = 0; gi < w.n_groups; ++gi) n_wide += wide_shrink_items(w.groups[gi].n_tok, w.groups[gi].rank);
-    const bool make_wide = c.dtype == LORA_BF16 && (!p.internal || n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP);
+    const bool make_wide = c.dtype == LORA_BF16 && !c.small_scratch && (!p.internal || n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP);
     for (int gi = 0; gi < w.n_groups && make_wide; ++gi) {
         const lora_item_t &gr = w.groups[group_order[gi]];
         lora::GemvWideItem d{};
@@ -760,6 +766,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
         for (int v = 0; v < SHRINK_VARIANTS && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
             if (v > 0 && p.internal) break;  // (lora_apply's own plans serve one projection)
+            if (v >= SHRINK_VARIANT_BATCH && c.small_scratch) break;
             if (v == SHRINK_VARIANT_SMALL && T > LORA_STATIC_MAX_TOKENS) continue;  // lora_apply_plan_static refuses such a batch
             const int n = v >= SHRINK_VARIANT_SMALL ? 1 : v + 1;
             int64_t max_runs = v >= SHRINK_VARIANT_BATCH ? SHRINK_BATCH_RUNS[v - SHRINK_VARIANT_BATCH] : slots / 8 / n * 8;
@@ -937,7 +944,7 @@ size_t lora_cache_bytes_required(const lora_cache_config_t *cfg)
 {
     if (!config_ok(cfg)) return 0;
     lora_cache tmp;
-    compute_layout(tmp, cfg);
+    compute_layout(tmp, cfg, (cfg->flags & LORA_CACHE_SMALL_SCRATCH) != 0);
     return tmp.total;
 }
 
@@ -948,7 +955,8 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
     if (!config_ok(cfg)) return LORA_E_INVAL;
     lora_cache *c = new (std::nothrow) lora_cache;
     if (!c) return LORA_E_NOMEM;
-    compute_layout(*c, cfg);
+    compute_layout(*c, cfg, (cfg->flags & LORA_CACHE_SMALL_SCRATCH) != 0);
+    if (!c->host_only && dev_pool_bytes < c->total) compute_layout(*c, cfg, true);
     c->slots.resize(c->n_slots);
     for (int32_t s = 0; s < c->n_slots; ++s) {
         c->slots[s].cls = class_of_slot(*c, s);

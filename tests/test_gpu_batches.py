@@ -87,6 +87,50 @@ def test_batches_against_single_applies(batch, dtype, flags):
         pool.close()
 
 
+@pytest.mark.parametrize("batch", ["popular", "mixed"])
+@pytest.mark.parametrize("how", ["flag", "fewer bytes"])
+def test_small_scratch(batch, how, monkeypatch):
+    """A pool with the scratch of four projections, asked for or found too small for more: lists, single applies and the
+    fused product give what they give in a full pool; a byte less is refused."""
+    from paper_2411_17741_amd import binding as B0
+
+    required = B0.lora_cache_bytes_required
+    outs, sizes = [], []
+    for small in (False, True):
+        flags = 0
+        if small and how == "flag":
+            flags = B0.LORA_CACHE_SMALL_SCRATCH
+        elif small:
+            def fewer(cfg):
+                cfg.flags |= B0.LORA_CACHE_SMALL_SCRATCH
+                n = required(cfg)
+                cfg.flags &= ~B0.LORA_CACHE_SMALL_SCRATCH
+                return n
+            monkeypatch.setattr(B0, "lora_cache_bytes_required", fewer)
+        B, pool, plan, T, normal = _setup(*BATCHES[batch], 3, flags=flags)
+        sizes.append(pool.bytes)
+        try:
+            xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
+            x_of = lambda p: xs[0 if p < 6 else p - 5]
+            sh = torch.cuda.current_stream().cuda_stream
+            y = [[normal(T, h_out) for _i, h_out in PROJS] for _ in range(3)]
+            descs = B.make_descs([(l, p, x_of(p).data_ptr(), y[l][p].data_ptr()) for l in range(3) for p in range(len(PROJS))])
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, sh))
+            wt, z = normal(2240, 2112, sigma=0.05), torch.empty(T, 2240, dtype=torch.bfloat16, device="cuda")
+            B.check(B.lora_linear_plan(pool.handle, plan, 0, 8, xs[3].data_ptr(), wt.data_ptr(), z.data_ptr(), 2.0, sh))
+            pool.apply_plan(plan, 0, 8, xs[3], y[0][8], 2.0)
+            pool.check_fault()
+            outs.append([t for ys in y for t in ys] + [z])
+            if small:
+                rc, _h = B.lora_cache_create(pool.cfg, (pool.buf.data_ptr() + 255) // 256 * 256, pool.bytes - 1)
+                assert rc == B.LORA_E_NOMEM
+        finally:
+            pool.close()
+    assert sizes[1] < sizes[0]
+    for k, (got, want) in enumerate(zip(outs[1], outs[0])):
+        _same(got, want, "bf16", f"output {k}")
+
+
 @pytest.mark.parametrize("batch", ["decode", "mixed"])
 def test_entries_that_depend_on_earlier_ones(batch):
     """Each list in order: an output that is a later entry's input; a later output over an earlier input; one output twice;

@@ -208,6 +208,21 @@ def test_pool_bytes_account_for_every_slab():
     assert B.lora_cache_bytes_required(B.make_config(proj, 1, [256], [1], B.LORA_BF16, 64, 64)) == 0  # above LORA_MAX_RANK
 
 
+_SEVEN = [(4096, 4096)] * 4 + [(4096, 11008)] * 2 + [(11008, 4096)]
+
+
+# what these pools took before list calls ran in batches of more than four projections; such a pool is still enough
+@pytest.mark.parametrize("args,old", [
+    (([(4096, 4096)], 32, [8, 16, 32, 64, 128], [20] * 5, B.LORA_BF16, 64, 64, 2), 2610103808),
+    ((_SEVEN, 2, [8, 16, 32, 64, 128], [100] * 5, B.LORA_BF16, 18017, 256, 2), 7922951680),
+    (([(256, 256)], 1, [4, 8, 16], [2, 1, 1], B.LORA_F32, 16, 4, 2), 488448),
+    (([(5120, 5120), (5120, 13824), (13824, 5120)], 1, [64], [3], B.LORA_BF16, 16384, 16384, 0), 281333248),
+])
+def test_pool_of_the_small_scratch(args, old):
+    small = B.lora_cache_bytes_required(B.make_config(*args, flags=B.LORA_CACHE_SMALL_SCRATCH))
+    assert small <= old <= B.lora_cache_bytes_required(B.make_config(*args))
+
+
 def _host_cache(n_layers=2, n_proj=2, class_slots=(2, 1)):
     cfg = B.make_config([(64, 128)] * n_proj, n_layers, [8, 32], list(class_slots), B.LORA_BF16, 64, 16, flags=B.LORA_CACHE_HOST_ONLY)
     rc, h = B.lora_cache_create(cfg, 0, 0)
