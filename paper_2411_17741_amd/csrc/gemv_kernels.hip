@@ -468,7 +468,7 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
         if (unit >= b.m.n_units) return;
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
-        const uint32_t s = (b.supers[super >> 1] >> (16 * (super & 1))) & 0xffffu;
+        const uint32_t s = gemv_super(b.supers, super);
         gemv_expand_work<E>(use(s & 0xffu), load_item(b.ge + item), s >> 8, stage[w]);
     }
 }
@@ -735,7 +735,7 @@ __global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
         if (unit >= b.m.n_units) return;
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
-        const uint32_t s = (b.supers[super >> 1] >> (16 * (super & 1))) & 0xffffu;
+        const uint32_t s = gemv_super(b.supers, super);
         const GemvWideItem *p = b.wge + item;
         const ItemW it = load_wide(p);
         const GemvUse a = use(s & 0xffu);

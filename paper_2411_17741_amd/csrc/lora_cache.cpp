@@ -1563,6 +1563,56 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out)
     return LORA_OK;
 }
 
+static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
+
+// Block and unit numbers of a batch's GEMV launch for n projections, h_out[i] wide, with a plan's items or its wide items;
+// shared by the launch and lora_plan_dump.  `supers` comes in zeroed.
+static int gemv_batch_map(const lora_plan_t *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 2])
+{
+    m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
+    m.n_ge = (uint32_t)(wide ? p->n_wge : p->n_ge);
+    m.n_proj = (uint32_t)n;
+    m.by_xcd = m.n_gs >= lora::GEMV_BATCH_XCD_ITEMS;
+    m.shrink_blocks = m.by_xcd ? (m.n_gs + 7) & ~7u : m.n_gs;
+    m.div_shrink = lora::div24_of(m.shrink_blocks);
+    m.div_ge = lora::div24_of(m.n_ge);
+    int32_t n_super = 0;
+    for (int i = 0; i < n; ++i) {
+        if (supers_of(h_out[i]) > 255) return LORA_E_INVAL;  // as a group's launch
+        for (int32_t k = 0; k < supers_of(h_out[i]); ++k, ++n_super) {
+            if (n_super >= lora::GEMV_BATCH_MAX_SUPERS) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
+            supers[n_super >> 1] |= ((uint32_t)i | (uint32_t)k << 8) << (16 * (n_super & 1));
+        }
+    }
+    const int64_t units = (int64_t)m.n_ge * n_super;
+    if (units >= (1 << 24) || (int64_t)m.shrink_blocks * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
+    m.n_units = (uint32_t)units;
+    return LORA_OK;
+}
+
+static Scratch pool_scratch(lora_cache_t *c)
+{
+    return Scratch{c->pool + c->off_v, c->v_set_bytes, c->n_sets, c->pool + c->off_vpart, c->vpart_rows, false,
+                   c->pool + c->off_vtag, c->vtag_set_bytes, &c->tag_epoch, &c->cap_id, &c->cap_plan, &c->cap_sets};
+}
+
+// How many projections, and super-chunks of projections, a batch with plan p may have: the scratch's sets, the partial sums of the
+// smallest run table of the tile shrink, and the ranges of the GEMV launch's unit arithmetic.
+static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
+{
+    int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
+    if (p->n_tiles > 0) {
+        projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
+        projs = std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (up to a group's size there are tables of their own)
+    }
+    if (p->n_gs > 0) {
+        projs = std::max<int64_t>(1, std::min<int64_t>(projs, ((1 << 24) - 1) / (p->n_gs + 7)));
+        supers = std::min<int64_t>(supers, ((1 << 24) - 1) / std::max({1, p->n_ge, p->n_wge}));
+    }
+    max_projs = (int32_t)projs;
+    max_supers = (int32_t)supers;
+}
+
 int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units,
                    int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks)
 {
@@ -1668,6 +1718,53 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
         const int32_t off = nt, cnt = gemv_tokens(ge[item]);
         put_unit(LORA_UNIT_GEMV_EXPAND, off, cnt, ge[item].row, ge[item].rank, c0, c1, 0, ge[item].alpha);
     }
+    // the GEMV launch of a batch: every projection of up to two layers, with the items above and with the wide ones, as the
+    // kernels of a batch map blocks and units
+    const lora::GemvWideItem *wgs = reinterpret_cast<const lora::GemvWideItem *>(buf + p->off_wgs);
+    const lora::GemvWideItem *wge = reinterpret_cast<const lora::GemvWideItem *>(buf + p->off_wge);
+    const int32_t n_proj = (int32_t)c->proj.size();
+    int32_t widths[lora::BATCH_MAX_PROJS], entries = 0, supers_left, max_entries;
+    batch_limits(p, pool_scratch(c), max_entries, supers_left);
+    for (; entries < std::min(max_entries, std::min(c->n_layers, 2) * n_proj); ++entries) {
+        widths[entries] = c->proj[entries % n_proj].h_out;
+        supers_left -= supers_of(widths[entries]);
+        if (supers_left < 0) break;
+    }
+    for (int wide = 0; wide < 2; ++wide) {
+        lora::GemvBatchMap m{};
+        uint32_t supers[lora::GEMV_BATCH_MAX_SUPERS / 2] = {0};
+        if ((wide ? p->n_wgs : p->n_gs) == 0 || entries == 0 || gemv_batch_map(p, wide != 0, entries, widths, m, supers)) continue;
+        auto put = [&](int32_t kind, const lora::GemvItem *it, const lora::GemvWideItem *w, int32_t lo, int32_t hi, uint32_t e) {
+            const int32_t off = nt;
+            int32_t cnt = w ? w->n_tok : gemv_tokens(*it);
+            for (int32_t t = 0; w && t < cnt; ++t) put_tok(w->tok[t]);
+            put_unit(kind, off, cnt, w ? w->row : it->row, w ? w->rank : it->rank, lo, hi, (int32_t)e, w ? w->alpha : it->alpha);
+        };
+        for (uint32_t b = 0; b < m.n_proj * m.shrink_blocks; ++b) {
+            uint32_t e, item;
+            lora::gemv_batch_shrink(b, m, e, item);
+            if (item >= m.n_gs || (int32_t)e % n_proj != proj) continue;
+            if (wide) {
+                put(LORA_UNIT_WIDE_SHRINK, nullptr, wgs + item, wgs[item].a, wgs[item].a + lora::gemv_wide_rows(wgs[item].rank, wgs[item].a), e);
+            } else {
+                int32_t j0, n;
+                lora::gemv_shrink_rows(gs[item], j0, n);
+                put(LORA_UNIT_BATCH_SHRINK, gs + item, nullptr, j0, j0 + n, e);
+            }
+        }
+        for (uint32_t u = 0; u < m.n_units; ++u) {
+            uint32_t super, item;
+            lora::gemv_batch_unit(u, m, super, item);
+            const uint32_t e = lora::gemv_super(supers, super) & 0xffu, sc = lora::gemv_super(supers, super) >> 8;
+            if ((int32_t)e % n_proj != proj) continue;
+            int32_t c0, c1;
+            if (wide) lora::gemv_wide_cols(wge[item].rank, wge[item].a, (int32_t)sc, h_out, c0, c1);
+            else lora::gemv_expand_cols(ge[item], (int32_t)sc, h_out, c0, c1);
+            if (c0 >= c1) continue;
+            if (wide) put(LORA_UNIT_WIDE_EXPAND, nullptr, wge + item, c0, c1, e);
+            else put(LORA_UNIT_BATCH_EXPAND, ge + item, nullptr, c0, c1, e);
+        }
+    }
     for (int32_t i = 0; i < p->n_lin_tiles; ++i) {
         const int32_t off = nt;
         tile_tokens(lin_tiles[i], lin_tok);
@@ -1699,14 +1796,6 @@ constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
 // The same for a batch, whose shrink blocks are long done when its expand blocks are dispatched: one launch up to the range of the
 // unit arithmetic (64 requests on 32 projections, 15808 items: 167 against 180 us; 512 requests, 91328 items: 792 against 803 us).
 constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
-static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
-
-static Scratch pool_scratch(lora_cache_t *c)
-{
-    return Scratch{c->pool + c->off_v, c->v_set_bytes, c->n_sets, c->pool + c->off_vpart, c->vpart_rows, false,
-                   c->pool + c->off_vtag, c->vtag_set_bytes, &c->tag_epoch, &c->cap_id, &c->cap_plan, &c->cap_sets};
-}
-
 // The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
 // rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
 // SHRINK_BATCH_BLOCKS blocks.
@@ -1849,48 +1938,18 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
     const bool wide = gemv_wide(c, p, projs, n, n_groups);
     b.wgs = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wgs);
     b.wge = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wge);
-    b.m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
-    b.m.n_ge = (uint32_t)(wide ? p->n_wge : p->n_ge);
-    b.m.n_proj = (uint32_t)n;
-    b.m.by_xcd = b.m.n_gs >= lora::GEMV_BATCH_XCD_ITEMS;
-    b.m.shrink_blocks = b.m.by_xcd ? (b.m.n_gs + 7) & ~7u : b.m.n_gs;
-    b.m.div_shrink = lora::div24_of(b.m.shrink_blocks);
-    b.m.div_ge = lora::div24_of(b.m.n_ge);
-    int32_t n_super = 0;
+    int32_t widths[lora::BATCH_MAX_PROJS];
     for (int i = 0; i < n; ++i) {
         b.p[i] = projs[i];
-        if (supers_of(projs[i].h_out) > 255) return LORA_E_INVAL;  // as a group's launch
-        for (int32_t k = 0; k < supers_of(projs[i].h_out); ++k, ++n_super) {
-            if (n_super >= lora::GEMV_BATCH_MAX_SUPERS) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
-            b.supers[n_super >> 1] |= ((uint32_t)i | (uint32_t)k << 8) << (16 * (n_super & 1));
-        }
+        widths[i] = projs[i].h_out;
     }
-    const int64_t units = (int64_t)b.m.n_ge * n_super;
-    if (units >= (1 << 24) || (int64_t)b.m.shrink_blocks * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
-    b.m.n_units = (uint32_t)units;
+    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.supers)) return rc;
     if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_BATCH_ITEMS)) {
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         b.epoch = ++*sc.epoch;
     }
     HIP_TRY(lora::launch_gemv_batch(c->dtype, b, wide, st, tm, done));
     return LORA_OK;
-}
-
-// How many projections, and super-chunks of projections, a batch with plan p may have: the scratch's sets, the partial sums of the
-// smallest run table of the tile shrink, and the ranges of the GEMV launch's unit arithmetic.
-static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
-{
-    int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
-    if (p->n_tiles > 0) {
-        projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
-        projs = std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (up to a group's size there are tables of their own)
-    }
-    if (p->n_gs > 0) {
-        projs = std::max<int64_t>(1, std::min<int64_t>(projs, ((1 << 24) - 1) / (p->n_gs + 7)));
-        supers = std::min<int64_t>(supers, ((1 << 24) - 1) / std::max({1, p->n_ge, p->n_wge}));
-    }
-    max_projs = (int32_t)projs;
-    max_supers = (int32_t)supers;
 }
 
 // Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of

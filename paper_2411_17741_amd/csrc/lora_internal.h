@@ -216,6 +216,8 @@ inline __host__ __device__ void gemv_batch_unit(uint32_t u, const GemvBatchMap &
     super = div24(u, m.div_ge);
     item = u - super * m.n_ge;
 }
+// super-chunk number -> its projection | its number there << 8
+inline __host__ __device__ uint32_t gemv_super(const uint32_t *supers, uint32_t super) { return (supers[super >> 1] >> (16 * (super & 1))) & 0xffffu; }
 // Wide work items, for launches that fill the chip with them (bf16): a shrink item is up to GEMV_WIDE_ROWS stored rank rows
 // (8 or 16) and GEMV_WIDE_SHRINK_TOKENS tokens, an expand item the columns of a GemvItem and GEMV_WIDE_TOKENS tokens.  What bounds such
 // a launch is what the compute units take in (6 to 8 TB/s over all of them): per slab row the items of 4 rows and 4 tokens

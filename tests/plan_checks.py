@@ -10,6 +10,7 @@ oracle's `token_map` says (which slot, which rank) and cover the work once:
 * GEMV units: their tokens are the tokens of the oracle's groups; per token the shrink units cover
   rank rows [0, rank) exactly once (rows of the zero padding up to the next multiple of 8 at most
   once) and, per projection, the expand units cover columns [0, h_out) exactly once;
+  the same holds for the units of a list call's batch, entry by entry, with the items and with the wide items;
 * row units of the fused linear path: every token of the batch exactly once.
 """
 from __future__ import annotations
@@ -57,16 +58,14 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
         pieces = units[units["kind"] == B.LORA_UNIT_TILE_SHRINK]
         sums = units[units["kind"] == B.LORA_UNIT_TILE_SUM]
         tile_of_off = {int(u["tok_off"]): i for i, u in enumerate(tiles)}
-        for table in range(5):
+        for table in range(7):
             pc = pieces[(pieces["where"] >> 20) == table]
             sm = sums[(sums["where"] >> 20) == table]
             if len(tiles) == 0 or (table == 4 and T > B.LORA_STATIC_MAX_TOKENS):  # (no table for what the call refuses)
                 assert len(pc) == 0 and len(sm) == 0
                 continue
             runs = pc["where"] & 0xFFFFF
-            assert (np.diff(runs) >= 0).all() and runs.max() < 512 // (1 if table == 4 else table + 1)
-            if table == 4:
-                assert runs.max() < 128
+            assert (np.diff(runs) >= 0).all() and runs.max() < [512, 512 // 2, 512 // 3, 512 // 4, 128, 64, 32][table]
             cover = np.zeros((len(tiles), h_in), np.int8)
             slots_of_tile = [[] for _ in tiles]
             order = []
@@ -94,30 +93,43 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
                 got[i].append(int(u["alpha"]))
             assert got == slots_of_tile
 
-        # --- GEMV shrink: every (token, rank row) once
-        gs = units[units["kind"] == B.LORA_UNIT_GEMV_SHRINK]
-        cover = np.zeros((len(want_gemv), B.LORA_MAX_RANK), np.int32)
-        for u in gs:
-            same_entry(u)
-            assert 0 <= u["lo"] < u["hi"] <= (u["rank"] + 7) // 8 * 8
-            idx = [gemv_pos[int(t)] for t in toks_of(u)]  # KeyError: a token that is not on the GEMV path
-            assert len(set(idx)) == len(idx)
-            cover[idx, u["lo"] : u["hi"]] += 1
-        for i, t in enumerate(want_gemv):
-            r = tm_rank[t]
-            assert (cover[i, :r] == 1).all() and (cover[i, r:] <= 1).all() and (cover[i, (r + 7) // 8 * 8 :] == 0).all(), t
-        assert sorted(gs["where"]) == list(range(len(gs)))
+        # --- GEMV shrink: every (token, rank row) once; expand: every (token, output column) once.  The launch of this
+        # projection alone, and every entry of a batch, with either kind of items
+        def covers_once(gs, ge, max_rows, max_tok_s, max_tok_e):
+            cover = np.zeros((len(want_gemv), B.LORA_MAX_RANK), np.int32)
+            for u in gs:
+                same_entry(u)
+                assert 0 <= u["lo"] < u["hi"] <= (u["rank"] + 7) // 8 * 8 and u["hi"] - u["lo"] <= max_rows and u["n_tok"] <= max_tok_s
+                idx = [gemv_pos[int(t)] for t in toks_of(u)]  # KeyError: a token that is not on the GEMV path
+                assert len(set(idx)) == len(idx)
+                cover[idx, u["lo"] : u["hi"]] += 1
+            for i, t in enumerate(want_gemv):
+                r = tm_rank[t]
+                assert (cover[i, :r] == 1).all() and (cover[i, r:] <= 1).all() and (cover[i, (r + 7) // 8 * 8 :] == 0).all(), t
+            cover = np.zeros((len(want_gemv), h_out), np.int8)
+            for u in ge:
+                same_entry(u)
+                assert 0 <= u["lo"] < u["hi"] <= h_out and u["n_tok"] <= max_tok_e
+                idx = [gemv_pos[int(t)] for t in toks_of(u)]
+                assert len(set(idx)) == len(idx)
+                cover[idx, u["lo"] : u["hi"]] += 1
+            assert (cover == 1).all()
 
-        # --- GEMV expand: every (token, output column) once
+        gs = units[units["kind"] == B.LORA_UNIT_GEMV_SHRINK]
         ge = units[units["kind"] == B.LORA_UNIT_GEMV_EXPAND]
-        cover = np.zeros((len(want_gemv), h_out), np.int8)
-        for u in ge:
-            same_entry(u)
-            assert 0 <= u["lo"] < u["hi"] <= h_out
-            idx = [gemv_pos[int(t)] for t in toks_of(u)]
-            assert len(set(idx)) == len(idx)
-            cover[idx, u["lo"] : u["hi"]] += 1
-        assert (cover == 1).all()
+        covers_once(gs, ge, 4, 4, 4)
+        assert sorted(gs["where"]) == list(range(len(gs)))
+        for kinds, sizes in (((B.LORA_UNIT_BATCH_SHRINK, B.LORA_UNIT_BATCH_EXPAND), (4, 4, 4)),
+                             ((B.LORA_UNIT_WIDE_SHRINK, B.LORA_UNIT_WIDE_EXPAND), (16, 8, 16))):
+            bs, be = (units[units["kind"] == k] for k in kinds)
+            entries = sorted(set(int(e) for e in bs["where"]))
+            assert sorted(set(int(e) for e in be["where"])) == entries
+            if not want_gemv or (not bf16 and sizes[0] == 16):
+                assert not entries
+                continue
+            assert entries == [layer * len(projs) + p for layer in range(len(entries))] and 1 <= len(entries) <= 2
+            for e in entries:
+                covers_once(bs[bs["where"] == e], be[be["where"] == e], *sizes)
 
         # --- rows of the fused linear path: every token once, adapter tokens where the other lists have them
         lin = units[units["kind"] == B.LORA_UNIT_LINEAR_ROWS]

@@ -66,7 +66,7 @@ def test_indexer_matches_oracle_on_random_batches():
 # ---------------------------------------------------------------------------------------
 # The lists the kernels read (lora_plan_dump of a host-only cache: the staged copy of the plan), checked
 # against the oracle's token map through coverage properties -- no kernel item shape is restated here.
-def _host_plan_check(T, off, slot_of_seg, rank, projs, dtype=B.LORA_BF16, m0=0, seed=0):
+def _host_plan_check(T, off, slot_of_seg, rank, projs, dtype=B.LORA_BF16, m0=0, seed=0, layers=1):
     from plan_checks import check_plan_units
 
     slot_of_seg = np.asarray(slot_of_seg, np.int32)
@@ -87,7 +87,7 @@ def _host_plan_check(T, off, slot_of_seg, rank, projs, dtype=B.LORA_BF16, m0=0, 
         k = cls_of(name_rank[n])
         real[n] = int(nxt[k])
         nxt[k] += 1
-    cfg = B.make_config(projs, 1, class_rank, class_slots, dtype, max(1, T), max(1, len(slot_of_seg)), mfma_min_tokens=m0,
+    cfg = B.make_config(projs, layers, class_rank, class_slots, dtype, max(1, T), max(1, len(slot_of_seg)), mfma_min_tokens=m0,
                         flags=B.LORA_CACHE_HOST_ONLY)
     rc, h = B.lora_cache_create(cfg, 0, 0)
     assert rc == B.LORA_OK
@@ -126,7 +126,7 @@ def test_plan_work_units_on_random_batches():
         slot = rng.integers(-1, n_names, size=n_seg).astype(np.int32)
         rank = np.where(slot >= 0, name_rank[np.maximum(slot, 0)], 0).astype(np.int32)
         projs = [(64 * int(rng.integers(1, 5)), 64 * int(rng.choice([1, 2, 15, 16, 17, 33]))) for _ in range(int(rng.integers(1, 4)))]
-        _host_plan_check(int(off[-1]), off, slot, rank, projs, B.LORA_BF16, int(rng.choice([0, 1, 8, 16, 64])))
+        _host_plan_check(int(off[-1]), off, slot, rank, projs, B.LORA_BF16, int(rng.choice([0, 1, 8, 16, 64])), layers=1 + trial % 3)
 
 
 def test_plan_tile_shrink_pieces_on_random_prompt_batches():
