@@ -131,7 +131,7 @@ def test_small_scratch(batch, how, monkeypatch):
         _same(got, want, "bf16", f"output {k}")
 
 
-@pytest.mark.parametrize("batch", ["decode", "mixed"])
+@pytest.mark.parametrize("batch", ["decode", "decode, no tiles", "mixed"])
 def test_entries_that_depend_on_earlier_ones(batch):
     """Each list in order: an output that is a later entry's input; a later output over an earlier input; one output twice;
     an output that overlaps another's last row; an entry in place."""
@@ -151,10 +151,9 @@ def test_entries_that_depend_on_earlier_ones(batch):
             lambda t: [(0, 0, at(t[0]), at(t[1])), (1, 0, at(t[0]), at(t[1], T - 1)), (1, 1, at(t[1], T - 1), at(t[2]))],
             lambda t: [(0, 1, at(t[3]), at(t[2])), (0, 0, at(t[0]), at(t[0])), (1, 0, at(t[0]), at(t[1]))],
         ]
-        # (a token-by-token batch of one in-place entry reads its row while it writes it: a one-launch decode batch is left out)
+        # (in place with as many columns out as in: a token's row is written when all of its words are there, that is when
+        # everything that reads the row has read it)
         for n, make in enumerate(lists):
-            if batch == "decode" and n == 4:
-                continue
             want, got = fresh(n), fresh(n)
             for layer, p, x, y in make(want):
                 B.check(B.lora_apply_plan(pool.handle, plan, layer, p, x, y, 2.0, sh))
@@ -166,39 +165,87 @@ def test_entries_that_depend_on_earlier_ones(batch):
         pool.close()
 
 
-@pytest.mark.parametrize("batch", ["decode", "mixed"])
-def test_a_captured_batch_replays(batch):
-    B, pool, plan, T, normal = _setup(*BATCHES[batch], 3)
+def _replays_match(pool, xs, prepare, call, outputs):
+    """Captures call() and replays it with other activations each time, nothing enqueued on the cache in between: a replay that
+    took the hand-over words of the replay before for its own would give that one's results.  Every replay against the eager
+    call on the same activations, made before the capture."""
+    from paper_2411_17741_amd import binding as B
+
+    versions = [[x * f for x in xs] for f in (1.0, -0.5, 2.0, 1.0, 0.25)]
+    want = []
+    for v in versions:
+        for x, value in zip(xs, v):
+            x.copy_(value)
+        prepare()
+        call()
+        pool.check_fault()
+        want.append([t.clone() for t in outputs])
+    assert not torch.equal(want[0][0], want[1][0])
+    B.check(B.lora_cache_set_fencing(pool.handle, 0))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="thread_local"):
+        call()
+    B.check(B.lora_cache_set_fencing(pool.handle, 1))
+    for v, w in zip(versions, want):
+        for x, value in zip(xs, v):  # eager work between the replays
+            x.copy_(value)
+        prepare()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        pool.check_fault()
+        for k, (a, b) in enumerate(zip(outputs, w)):
+            assert torch.equal(a, b), f"output {k}"
+
+
+# items and wide items, several token counts and ranks, tiles beside them; 81 entries: two batches, the second with fewer
+# projections than the first
+@pytest.mark.parametrize("batch,layers", [("one token", 3), ("decode", 3), ("popular", 3), ("mixed", 3), ("one token", 9), ("decode", 9)])
+def test_a_captured_batch_replays(batch, layers):
+    B, pool, plan, T, normal = _setup(*BATCHES[batch], layers)
     try:
         xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
         x_of = lambda p: xs[0 if p < 6 else p - 5]
-        base = [[normal(T, h_out) for _i, h_out in PROJS] for _ in range(3)]
-        y = [[t.clone() for t in ys] for ys in base]
-        descs = B.make_descs([(l, p, x_of(p).data_ptr(), y[l][p].data_ptr()) for l in range(3) for p in range(len(PROJS))])
-        call = lambda: B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
-        call()
-        torch.cuda.synchronize()
-        B.check(B.lora_cache_set_fencing(pool.handle, 0))
-        g = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(g, capture_error_mode="thread_local"):
-            call()
-        B.check(B.lora_cache_set_fencing(pool.handle, 1))
-        restore = lambda: [t.copy_(b) for ys, bs in zip(y, base) for t, b in zip(ys, bs)]
-        for f in (1.0, -0.5, 2.0):
-            for x in xs:
-                x.mul_(f)  # eager work between the replays
-            restore()
-            torch.cuda.synchronize()
-            g.replay()
-            torch.cuda.synchronize()
-            got = [t.clone() for ys in y for t in ys]
-            restore()
-            call()
-            pool.check_fault()
-            for k, (a, b) in enumerate(zip(got, [t for ys in y for t in ys])):
-                assert torch.equal(a, b), f"entry {k}"
+        base = [normal(T, h_out) for _ in range(layers) for _i, h_out in PROJS]
+        y = [t.clone() for t in base]
+        descs = B.make_descs([(l, p, x_of(p).data_ptr(), y[l * len(PROJS) + p].data_ptr()) for l in range(layers) for p in range(len(PROJS))])
+        _replays_match(pool, xs, lambda: [t.copy_(b) for t, b in zip(y, base)],
+                       lambda: B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream)), y)
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("workspace", [True, False])
+@pytest.mark.parametrize("batch", ["one token", "mixed", "requests"])
+def test_a_captured_linear_replays(batch, workspace):
+    """The fused product's GEMV launch under capture: items, beside tiles, and wide items."""
+    if batch == "requests":
+        ranks, counts = _many_requests()
+        assert _wide_items(counts, ranks) >= 600  # wide from 512
+        B, pool, plan, T, normal = _setup(None, ranks, 1000, counts, 1)
+    else:
+        B, pool, plan, T, normal = _setup(*BATCHES[batch], 1)
+    try:
+        p = 3
+        h_in, h_out = PROJS[p]
+        x, wt, y = normal(T, h_in), normal(h_out, h_in, sigma=0.05), torch.empty(T, h_out, dtype=torch.bfloat16, device="cuda")
+        space = torch.empty(T * h_out, dtype=torch.float32, device="cuda")
+        _replays_match(pool, [x], lambda: y.fill_(float("nan")),
+                       lambda: B.check(B.lora_linear_plan(pool.handle, plan, 0, p, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0,
+                                                          torch.cuda.current_stream().cuda_stream, space.data_ptr() if workspace else 0,
+                                                          space.numel() * 4 if workspace else 0)), [y])
+    finally:
+        pool.close()
+
+
+def _many_requests():
+    ranks = [8, 16, 24, 32, 5, 12, 100, 128, 64, 33, 40, 72] * 12
+    return ranks, [1 + (5 * i) % 19 for i in range(len(ranks))]
+
+
+def _wide_items(counts, ranks):
+    """Wide shrink items (8 tokens, 16 stored rank rows) of so many one-token requests per slot."""
+    return sum(-(-n // 8) * -(-(-(-r // 8) * 8) // 16) for n, r in zip(counts, ranks))
 
 
 @pytest.mark.parametrize("workspace", [True, False])
@@ -206,8 +253,7 @@ def test_a_captured_batch_replays(batch):
 def test_linear_with_many_requests(n_prompt, workspace):
     """The adapter term of requests in numbers that take wide items, as fp32 into the workspace or into the zeroed rows,
     beside the tile shrink of a prompt or without one."""
-    ranks = [8, 16, 24, 32, 5, 12, 100, 128, 64, 33, 40, 72] * 8
-    counts = [1 + (5 * i) % 19 for i in range(len(ranks))]
+    ranks, counts = _many_requests()
     B, pool, plan, T, normal = _setup(None, ranks, 100 if n_prompt else 1000, counts, 1)
     pool.plan_destroy(plan)
     try:
@@ -217,6 +263,10 @@ def test_linear_with_many_requests(n_prompt, workspace):
             lens[7] = n_prompt  # one of the requests as a prompt, the last ones left out
             lens = lens[: len(slot) - n_prompt + 1]
             slot = slot[: len(lens)]
+        requests = np.bincount(slot, minlength=len(ranks))
+        if n_prompt:
+            requests[slot[7]] = 0  # (in tiles)
+        assert _wide_items(requests, ranks) >= 600  # wide from 512
         off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
         plan = pool.plan(int(off[-1]), off, slot, np.asarray(ranks, np.int32)[slot])
         T, p = int(off[-1]), 3

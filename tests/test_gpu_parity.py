@@ -422,8 +422,9 @@ def test_multi_apply_groups_projections_that_share_their_input():
 def test_applies_captured_in_a_graph_replay_correctly():
     """An apply of a plan captured into a HIP graph (fencing off, as the header asks) and replayed
     several times, with the activations changed by eager work between the replays: every replay
-    must give what the eager call gives.  (Under capture the GEMV part always takes the two-launch
-    form: the one-launch form numbers its launches, and a graph would freeze the number.)"""
+    must give what the eager call gives.  (The one-launch GEMV form numbers its launches and a graph freezes the number: the
+    words of the replay before must not pass for this one's.  So the eager results are made before the first
+    replay, and nothing is enqueued on the cache between two of them.)"""
     B, H = _mods()
     for inst, m0 in ((wl.decode(seed=2), 0), (wl.small_mixed(seed=3), 16)):
         pi = H.PooledInstance(inst, mfma_min_tokens=m0, flags=B.LORA_CACHE_FUSED_GEMV)
@@ -435,22 +436,28 @@ def test_applies_captured_in_a_graph_replay_correctly():
             plan = pi.pool.plan(inst.T, inst.seg_offsets, pi.seg_slot, pi.seg_rank)
             pi.pool.apply_plan(plan, 0, 0, xd, yd, inst.scale)  # eager once: fills are seen as done, kernels loaded
             torch.cuda.synchronize()
+            factors = (1.0, -0.5, 2.0, 1.0)
+            eager = []
+            for f in factors:
+                xd.copy_(H.to_device(wl.bf16_round(x * f), pi.dtype))
+                y_eager = base_d.clone()
+                pi.pool.apply_plan(plan, 0, 0, xd, y_eager, inst.scale)
+                pi.pool.check_fault()
+                eager.append(y_eager.float().cpu().numpy())
             B.check(B.lora_cache_set_fencing(h, 0))
             g = torch.cuda.CUDAGraph()
             with torch.cuda.graph(g, capture_error_mode="thread_local"):
                 pi.pool.apply_plan(plan, 0, 0, xd, yd, inst.scale)
             B.check(B.lora_cache_set_fencing(h, 1))
-            for rep, f in enumerate((1.0, -0.5, 2.0, 1.0)):
+            for rep, f in enumerate(factors):
                 xd.copy_(H.to_device(wl.bf16_round(x * f), pi.dtype))   # eager work between the replays
                 yd.copy_(base_d)
                 torch.cuda.synchronize()
                 g.replay()
                 torch.cuda.synchronize()
                 got = yd.float().cpu().numpy()
-                y_eager = base_d.clone()
-                pi.pool.apply_plan(plan, 0, 0, xd, y_eager, inst.scale)
                 pi.pool.check_fault()
-                assert np.array_equal(got, y_eager.float().cpu().numpy()), f"{inst.name}: replay {rep} differs from the eager apply"
+                assert np.array_equal(got, eager[rep]), f"{inst.name}: replay {rep} differs from the eager apply"
             ref = oracle.lora_apply(x, base, inst.seg_offsets, inst.seg_adapter, _oracle_adapters(inst, 0, inst.used_adapters()), inst.scale)
             _check(H.error_metrics(got, ref, base), "bf16", "last replay")
             pi.pool.plan_destroy(plan)
