@@ -61,8 +61,8 @@ enum {
     /* GEMV shrink and expand run as one launch with an in-kernel hand-over of the intermediate when
      * the batch's GEMV part is small (the launch in between then costs more than the hand-over),
      * else as two launches.  These two flags take the choice away: */
-    LORA_CACHE_FUSED_GEMV = 2,    /* always one launch (except under stream capture, where it is always two) */
-    LORA_CACHE_SPLIT_GEMV = 4,    /* always two launches (and no hand-over buffer in the pool) */
+    LORA_CACHE_FUSED_GEMV = 2,    /* always one launch */
+    LORA_CACHE_SPLIT_GEMV = 4,    /* always two launches */
     LORA_CACHE_NO_OVERLAP = 16,   /* every kernel of an apply on the caller's stream: by default the GEMV launch of a batch that
                                      also has tiles runs on a stream of the cache's own, forked off the caller's stream and
                                      joined to it again inside the call, side by side with the tile kernels (different tokens) */
@@ -357,7 +357,9 @@ int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32
 
 /* The same for a list of (layer, projection, x, base_out): the result is that of n calls of
  * lora_apply_plan in order on `stream` (one iteration's worth of applies with a single trip
- * through the binding).  Consecutive entries that do not depend on each other (no base_out overlaps
+ * through the binding), up to rounding: the fp32 sums of a tile's shrink are cut in other places when several
+ * projections share a launch, and the bf16 intermediate then rounds the other way once in a while.  The same list
+ * with the same plan gives the same bits every time.  Consecutive entries that do not depend on each other (no base_out overlaps
  * another entry's base_out or any entry's x) run as batches of up to 64: one launch per phase for all of them, and one
  * pass over x for those that read the same x (q, k, v; gate, up; up to 4 neighbours).  Nothing is
  * enqueued if any entry fails validation. */
@@ -411,8 +413,12 @@ int lora_cache_read_timing(lora_cache_t *c, double ms[LORA_K_COUNT], int64_t lau
 
 /* Blocks until `stream` is idle, then reports whether any kernel of this cache gave up a
  * bounded wait since the last call (*fault = 1; the outputs of that apply are then invalid)
- * and clears the flag.  The fused GEMV launch is the only kernel that waits; with a working
- * device the flag never rises.  The flag lives in pinned host memory that the kernel writes
+ * and clears the flag.  The one-launch GEMV form is the only kernel that waits: its expand
+ * wavefronts for the shrink blocks of the same launch, which come first in its grid and wait for nothing.  On a working device the
+ * flag does not rise as long as the one-launch forms of different caches are not on the device at the same time: two launches that are
+ * started together and each fill the chip could in principle hold each other's places until the bound (about 0.1 s).
+ * Callers who run several caches side by side can create them with LORA_CACHE_SPLIT_GEMV, under which nothing waits.
+ * The flag lives in pinned host memory that the kernel writes
  * directly, so applies also see it without any synchronisation: once it is up they return
  * LORA_E_FAULT until this call has cleared it. */
 int lora_cache_check_fault(lora_cache_t *c, void *stream, int32_t *fault);
