@@ -7,7 +7,9 @@ projection of every layer copy the pool holds, reading the adapters from the cac
 The layer copies are distinct memory and the activations rotate over several buffer sets, so
 that slabs and activations come from HBM and not from the 256 MB Infinity Cache.  Inputs are
 resident in HBM before the timed region starts.  value = tokens x layers / time: the rate at
-which tokens pass one layer's LoRA apply.
+which tokens pass one layer's LoRA apply when the layers' work is handed over as one list, whose
+entries here do not depend on each other and run as batches; config.forward_order is the time per
+layer of the same work one call at a time, as a forward pass has to make its calls.
 
 Prints ONE JSON line: tokens/s per layer, the roofline figure of the dominant kernel (HIP
 events around each kernel, in a second pass of the same steps) and the CPU oracle's rate on a
@@ -38,7 +40,8 @@ WORKLOAD_TEXT = {
 # HBM bytes per launch (one launch serves a batch of layers) from rocprofv3 counter runs of this same
 # script (FETCH_SIZE and WRITE_SIZE, each in a run of its own, scaled by what the same counters read for a plain
 # 256 MiB copy).  A counter run cannot happen inside this process, so the figures measured for the same workloads
-# are carried here; the line names their source, and they are left out when the flags change what is launched.
+# are carried here; the line names their source, and they are left out when a flag changes what a launch serves (the
+# number of layers and of activation sets among them: they decide how many projections a batch has).
 TRAFFIC_SOURCE = "profiles/kernel_traffic_all_workloads.txt"
 MEASURED_TRAFFIC = {("decode", "gemv_fused"): 378.9e6, ("decode_qkv", "gemv_fused"): 1115.9e6, ("prefill", "mfma_expand"): 971.1e6,
                     ("prefill", "mfma_shrink"): 589.7e6, ("mixed", "gemv_fused"): 1402.4e6, ("mixed", "mfma_expand"): 7961.2e6,
@@ -544,6 +547,32 @@ def run_workload(args, workload: str, steps: int = 0, cpu_baseline: bool = True,
     spread = {"p10": float(per_layer_us[int(0.1 * (steps - 1))]), "median": float(np.median(per_layer_us)),
               "p90": float(per_layer_us[int(0.9 * (steps - 1))])}
 
+    # the same work in the order of a forward pass, where a projection's input is computed from the outputs before it: one
+    # call per group of projections that read the same x, the next group's in a call of its own
+    groups = []
+    for l in range(n_layers):
+        for p in range(n_proj):
+            if p == 0 or inst.projs[p].x_key != inst.projs[p - 1].x_key:
+                groups.append([])
+            groups[-1].append((l, p, xs[l % n_sets][inst.projs[p].x_key].data_ptr(), ys[l % n_sets][p].data_ptr()))
+    group_descs = [B.make_descs(g) for g in groups]
+
+    def forward_step() -> None:
+        rc, plan = B.lora_plan_create(h, inst.T, inst.seg_offsets, pi.seg_slot, pi.seg_rank, sh)
+        B.check(rc, "lora_plan_create")
+        for d in group_descs:
+            B.check(B.lora_apply_plan_multi(h, plan, d, inst.scale, sh), "lora_apply_plan_multi")
+        B.check(B.lora_plan_destroy(h, plan))
+
+    for _ in range(max(1, args.warmup)):
+        forward_step()
+    torch.cuda.synchronize()
+    t_f = time.perf_counter()
+    for _ in range(steps):
+        forward_step()
+    torch.cuda.synchronize()
+    forward_order = {"us_per_layer": (time.perf_counter() - t_f) * 1e6 / steps / n_layers, "calls_per_layer": len(groups) // n_layers}
+
     # the applies of a step recorded into a HIP graph once and replayed (what a decode loop does with its iteration):
     # same kernels, no host work per launch.  One plan, made outside the capture; fencing off while capturing.
     graph_replay = None
@@ -631,12 +660,13 @@ def run_workload(args, workload: str, steps: int = 0, cpu_baseline: bool = True,
                 kbytes = sum(v[kind] for v in per_proj) * n_timed  # all projections, all timed layer passes
                 kernels[kind] = {"launches": int(n), "avg_us": ms * 1e3 / n, "algorithmic_bytes_per_launch": kbytes / n,
                                  "achieved_GBs": kbytes / (ms * 1e-3) / 1e9 if ms > 0 else None}
+        as_measured = args.gemv == "auto" and not (args.mfma_min_tokens or args.layers or args.sets) and args.tokens == 64 and args.adapters == 100
         dom = max(kernels, key=lambda k: kernels[k]["avg_us"] * kernels[k]["launches"])
         roofline = {
             "bound": "hbm", "kernel": dom, "achieved": kernels[dom]["achieved_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": kernels[dom]["achieved_GBs"] / HBM_PEAK_GBS,
-            "traffic": MEASURED_TRAFFIC.get((workload, dom)) if args.gemv == "auto" and not args.mfma_min_tokens else None,
-            "traffic_source": TRAFFIC_SOURCE if args.gemv == "auto" and not args.mfma_min_tokens and (workload, dom) in MEASURED_TRAFFIC else None,
+            "traffic": MEASURED_TRAFFIC.get((workload, dom)) if as_measured else None,
+            "traffic_source": TRAFFIC_SOURCE if as_measured and (workload, dom) in MEASURED_TRAFFIC else None,
             "avg_launch_us": kernels[dom]["avg_us"], "algorithmic_bytes_per_launch": kernels[dom]["algorithmic_bytes_per_launch"],
         }
 
@@ -719,7 +749,7 @@ def run_workload(args, workload: str, steps: int = 0, cpu_baseline: bool = True,
                    "pool_adapters": int(inst.n_adapters), "distinct_adapters": int(len(inst.used_adapters())), "layers_per_step": n_layers, "activation_sets": n_sets,
                    "library_limits": "h_in and h_out multiples of 64, rank 1..128",
                    "ms_per_layer": ms_per_layer, "us_per_layer_spread": spread, "cold_single_call_us": cold_call_us,
-                   "host_index_us": index_us, "host_plan_create_us": plan_us, "graph_replay": graph_replay,
+                   "host_index_us": index_us, "host_plan_create_us": plan_us, "graph_replay": graph_replay, "forward_order": forward_order,
                    "mfma_min_tokens": plan_info.mfma_min_tokens, "tiles": len(w["tiles"]), "gemv_shrink_items": plan_info.n_gemv_shrink_items, "gemv_groups": len(w["groups"])},
         "roofline": roofline,
         "cpu_baseline": cpu,
@@ -798,7 +828,7 @@ def main() -> int:
         rec = run_workload(args, name, 0, cpu_baseline=False)
         sub = {k: rec[k] for k in keep if rec.get(k) is not None}
         sub["workload"] = rec["config"]["workload"]
-        for k in ("tokens", "projections", "layers_per_step", "ms_per_layer", "distinct_adapters", "tiles", "gemv_shrink_items", "graph_replay"):
+        for k in ("tokens", "projections", "layers_per_step", "ms_per_layer", "distinct_adapters", "tiles", "gemv_shrink_items", "graph_replay", "forward_order"):
             if k in rec["config"]:
                 sub[k] = rec["config"][k]
         sub["tokens_per_s_per_layer"] = sub.pop("value")

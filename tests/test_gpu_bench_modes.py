@@ -35,6 +35,8 @@ def test_main_line_carries_roofline_and_kernel_times():
     r = d["roofline"]
     assert r["bound"] == "hbm" and r["peak"] == 8000.0 and r["unit"] == "GB/s" and abs(r["frac"] - r["achieved"] / r["peak"]) < 1e-9
     assert r["kernel"] == "gemv_fused" and r["avg_launch_us"] > 0
+    assert r["traffic"] is None and r["traffic_source"] is None  # measured on launches that serve more layers than four
+    assert d["config"]["forward_order"]["us_per_layer"] > 0 and d["config"]["forward_order"]["calls_per_layer"] == 1
     assert d["cpu_baseline"] is None   # switched off for this run; the default run times the oracle
 
 
