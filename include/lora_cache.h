@@ -111,7 +111,7 @@ size_t lora_adapter_bytes(int32_t h_in, int32_t h_out, int32_t rank, int32_t dty
 
 /* Bytes of the pool: slabs of every (layer, projection, slot) + scratch + plan buffers + fill staging.  0 on a bad config.
  * The scratch holds the intermediates of up to 64 projections that one list call works on at a time (as many as fit into
- * 512 MB), up to 64 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
+ * 512 MB), up to 85 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
  * most 48 MB of partial sums and staging for one part of an adapter: the same results, but list calls run 4
  * projections at a time, launches with many one-token requests and split tiles of the fused product have less to work with, and staged fills travel part by part. */
 size_t lora_cache_bytes_required(const lora_cache_config_t *cfg);
@@ -413,8 +413,9 @@ int lora_cache_read_timing(lora_cache_t *c, double ms[LORA_K_COUNT], int64_t lau
 
 /* Blocks until `stream` is idle, then reports whether any kernel of this cache gave up a
  * bounded wait since the last call (*fault = 1; the outputs of that apply are then invalid)
- * and clears the flag.  The one-launch GEMV form is the only kernel that waits: its expand
- * wavefronts for the shrink blocks of the same launch, which come first in its grid and wait for nothing.  On a working device the
+ * and clears the flag.  Two kernels wait: in the fused product the parts of a split tile for
+ * each other, but only once all of them are running; in the one-launch GEMV form the expand wavefronts for the shrink
+ * blocks of the same launch, which come first in its grid and wait for nothing.  On a working device the
  * flag does not rise as long as the one-launch forms of different caches are not on the device at the same time: two launches that are
  * started together and each fill the chip could in principle hold each other's places until the bound (about 0.1 s).
  * Callers who run several caches side by side can create them with LORA_CACHE_SPLIT_GEMV, under which nothing waits.

@@ -47,13 +47,15 @@
 //
 // One block fills a CU (its two stages take 128 KB of LDS), so a grid of N tiles runs in ceil(N / CUs) rounds and the
 // last round may be nearly empty (288 tiles on 256 CUs: a second round of 32).  The tiles of that last round are
-// therefore split along k into up to 4 parts, one block each (linear_split_shape).  Every part leaves its fp32
-// accumulators in a scratch area (device-scope atomic stores, past the per-XCD L2s) and counts itself in; the part that
-// finds all others counted adds their sums to its own and runs the adapter slab and the store, the others are done.
-// No block waits for another: what else is running on the device, and in which order the parts get their places, does
-// not matter.  (With parts that wait for each other and finish a share of the tile each, 304 tiles of 64 stages take 140 us
-// against 135 this way, and two such launches at the same time, of two caches on two streams, can fill the CUs with parts that wait
-// for parts that have no place.)
+// therefore split along k into up to 8 parts, one block each (linear_split_shape).  The parts of a tile finish it
+// together: each owns a share of every wavefront's rows, leaves its fp32 accumulators of the other shares in a scratch
+// area (device-scope atomic stores, past the per-XCD L2s), counts itself in, waits until all parts have, adds the other
+// parts' sums of its own share and runs the adapter slab and the store for it.  (With the last part to arrive finishing
+// the tile alone 384 tiles of 64 stages take 176 us, 160 us this way.)  But a part may wait only for parts that are
+// running: others may have no place on the device until this one leaves it, for instance beside a launch of another
+// cache that waits the same way.  So the parts count themselves in when they start, and the first to have its sums
+// decides: if all parts have started, they share the tile; if not, every part leaves all its sums and ends, and the last
+// to arrive finishes the tile alone.  Either way a row block's sums are added in the same order.
 #include <algorithm>
 #include <type_traits>
 
@@ -68,17 +70,19 @@ constexpr int L_HALF = 128 * LROW;              // 128 rows of x or Wt, 64 k: 16
 constexpr int L_LDS = 2 * 4 * L_HALF;           // two stages of x half 0, x half 1, Wt half 0, Wt half 1
 constexpr int SV_ROW = LORA_MAX_RANK * 2 + 16;  // bytes per row of the staged s.v
 static_assert(8 * 128 * 128 <= L_LDS && LBM * SV_ROW <= L_LDS, "s.v and the parked outputs use the stage buffers");
-constexpr int MAX_PARTS = 4;                    // of a split tile
+constexpr int MAX_PARTS = 8;                    // a wavefront's 128 rows are eight blocks of 16
 constexpr size_t PART_WORDS = LINEAR_SHARE_BYTES / sizeof(unsigned long long);
 }  // namespace
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
 // split of the last round: blocks [0, n_whole) work on whole tiles; block n_whole + parts * j + p on part p of tile n_whole + j
+constexpr uint32_t SPLIT_SHARED = 1, SPLIT_LAST = 2;
 struct LinearSplit {
     int n_whole, parts;           // parts = 1: no split
     unsigned long long *partial;  // [tile j][part][row block of 16: 8][column block of 16: 4][half 2][thread 512] 8-byte words
-    uint32_t *counts;             // [tile j]: parts that have left their sums; zero between launches
+    SplitState *state;            // [tile j], zero between launches
+    int32_t *fault;
 };
 
 // Tile number -> (row panel, column panel): groups of four row panels, column by column
@@ -97,56 +101,6 @@ __device__ __forceinline__ void section_end()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The accumulators of a part, left for whichever part finishes the tile (past the per-XCD L2s, which do not see each
-// other's writes).
-__device__ __forceinline__ void leave_sums(const floatx4 (&acc)[8][4], unsigned long long *dst, uint32_t tid)
-{
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb) {
-            const floatx4 c = acc[mb][nb];
-            const floatx2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
-            unsigned long long *d = dst + (mb * 4 + nb) * 2 * 512;
-            __hip_atomic_store(d + tid, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(d + 512 + tid, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-}
-
-// Adds the other P - 1 parts' sums to this part's, in the order of the parts: the result does not depend on which of them
-// came last.  A round requests 24 or 32 words per thread (128 KB a block: a trip past the caches takes about 2 us however
-// much it brings).
-template <int P> __device__ __forceinline__ void add_sums(floatx4 (&acc)[8][4], const unsigned long long *sums, int part, uint32_t tid)
-{
-    constexpr int CH = P == 2 ? 4 : P == 3 ? 2 : 1;  // row blocks of a round
-#pragma unroll
-    for (int c = 0; c < 8; c += CH) {
-        unsigned long long v[P - 1][CH][8];
-#pragma unroll
-        for (int q = 0; q < P - 1; ++q) {
-            const unsigned long long *src = sums + (size_t)(q + (q >= part)) * PART_WORDS + c * 8 * 512;
-#pragma unroll
-            for (int i = 0; i < CH * 8; ++i) v[q][i >> 3][i & 7] = __hip_atomic_load(src + i * 512 + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_sched_barrier(0);  // all requests of the round first
-#pragma unroll
-        for (int i = 0; i < CH * 8; ++i) {
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const float own = acc[c + (i >> 3)][(i & 7) >> 1][2 * (i & 1) + e];
-                float s = __builtin_bit_cast(floatx2, v[0][i >> 3][i & 7])[e];
-                if (part <= 1) s += own;  // (parts 0 and 1 alike: the order of two does not matter)
-#pragma unroll
-                for (int q = 1; q < P - 1; ++q) {
-                    s += __builtin_bit_cast(floatx2, v[q][i >> 3][i & 7])[e];
-                    if (part == q + 1) s += own;
-                }
-                acc[c + (i >> 3)][(i & 7) >> 1][2 * (i & 1) + e] = s;
-            }
-        }
-    }
-}
-
 __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
                                                            const DevItem *__restrict__ tiles, int n_rt, int n_mt, int n_nt, LinearSplit sp)
 {
@@ -159,6 +113,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         tail = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - sp.n_whole) / sp.parts);
         part = ((int)blockIdx.x - sp.n_whole) - tail * sp.parts;
         tile_no = sp.n_whole + tail;
+        if (tid == 0) __hip_atomic_fetch_add(&sp.state[tail].started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {  // XCD j takes a run of consecutive tiles
         const int j = (int)blockIdx.x & 7, q = sp.n_whole >> 3, r = sp.n_whole & 7;
         tile_no = j * q + min(j, r) + ((int)blockIdx.x >> 3);
@@ -291,25 +246,96 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests past the end: LDS is used for other things below
     __syncthreads();
 
-    // ---- a tile split along k: every part leaves its accumulators and counts itself in; the one that finds all others
-    // counted finishes the tile, the others are done
+    // ---- a tile split along k.  Row block mb of every wavefront (8 to a part's wavefront) belongs to part
+    // ((mb + 1) * parts - 1) / 8; its sum is that part's plus the others' in their order, whoever adds it up
+    int own_lo = 0, own_hi = 8;  // the row blocks this block finishes
     if (tail >= 0) {
+        SplitState *const st = sp.state + tail;
         unsigned long long *const sums = sp.partial + (size_t)tail * sp.parts * PART_WORDS;
-        leave_sums(acc, sums + part * PART_WORDS, threadIdx.x);
+        __shared__ uint32_t said;
+        if (tid == 0) {
+            const uint32_t all_run = __hip_atomic_load(&st->started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)sp.parts;
+            uint32_t way = 0;
+            const uint32_t mine = all_run ? SPLIT_SHARED : SPLIT_LAST;
+            if (__hip_atomic_compare_exchange_strong(&st->way, &way, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) way = mine;
+            said = way;
+        }
+        __syncthreads();
+        const bool shared = said == SPLIT_SHARED;
+        if (shared) own_lo = 8 * part / sp.parts, own_hi = 8 * (part + 1) / sp.parts;
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) {
+            if (shared && mb >= own_lo && mb < own_hi) continue;  // uniform
+            unsigned long long *const dst = sums + part * PART_WORDS + mb * 8 * 512;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) {
+                const floatx4 c = acc[mb][nb];
+                const floatx2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
+                __hip_atomic_store(dst + (nb * 2 + 0) * 512 + (uint32_t)tid, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(dst + (nb * 2 + 1) * 512 + (uint32_t)tid, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the stores above have been performed where every XCD sees them
         __syncthreads();
-        __shared__ uint32_t before;
-        if (tid == 0) before = __hip_atomic_fetch_add(sp.counts + tail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) {
+            uint32_t n = 1 + __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (shared) {  // (all parts are running, and a part waits for nothing before it has counted itself in)
+                for (int spin = 0; spin < (1 << 20) && n < (uint32_t)sp.parts; ++spin) {
+                    __builtin_amdgcn_s_sleep(8);
+                    n = __hip_atomic_load(&st->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (n < (uint32_t)sp.parts) __hip_atomic_store(sp.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // pinned host memory
+            }
+            said = n;
+        }
         __syncthreads();
-        if (before != (uint32_t)sp.parts - 1) return;  // (the whole block)
-        if (tid == 0) __hip_atomic_store(sp.counts + tail, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-        if (sp.parts == 2) add_sums<2>(acc, sums, part, threadIdx.x);
-        __builtin_amdgcn_sched_barrier(0);  // (mixed with each other the three take 150 bytes of scratch memory a lane)
-        if (sp.parts == 3) add_sums<3>(acc, sums, part, threadIdx.x);
-        __builtin_amdgcn_sched_barrier(0);
-        if (sp.parts == 4) add_sums<4>(acc, sums, part, threadIdx.x);
-        __builtin_amdgcn_sched_barrier(0);
+        const bool all_in = said == (uint32_t)sp.parts;
+        if (!shared && !all_in) return;  // (the whole block: a part that comes later finishes the tile)
+        if (all_in) {
+#pragma unroll
+            for (int mb = 0; mb < 8; ++mb) {
+                if (mb < own_lo || mb >= own_hi) continue;  // uniform
+                const int owner = ((mb + 1) * sp.parts - 1) >> 3;
+                floatx4 sum[4];
+                for (int i = 0; i < sp.parts; ++i) {
+                    const int q = i == 0 ? owner : i - 1 + (i - 1 >= owner);
+                    floatx4 v[4];
+                    if (q == part) {  // uniform
+#pragma unroll
+                        for (int nb = 0; nb < 4; ++nb) v[nb] = acc[mb][nb];
+                    } else {
+                        const unsigned long long *const src = sums + q * PART_WORDS + mb * 8 * 512;
+                        unsigned long long w8[8];
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) w8[j] = __hip_atomic_load(src + j * 512 + (uint32_t)tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const floatx2 f = __builtin_bit_cast(floatx2, w8[j]);
+                            v[j >> 1][2 * (j & 1)] = f[0];
+                            v[j >> 1][2 * (j & 1) + 1] = f[1];
+                        }
+                    }
+#pragma unroll
+                    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[nb][e] = i == 0 ? v[nb][e] : sum[nb][e] + v[nb][e];
+                }
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = sum[nb];
+            }
+        }
+        // the last to have read (or the only one) sets the state back for the next launch
+        __syncthreads();
+        if (tid == 0 && (!shared || __hip_atomic_fetch_add(&st->read, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)sp.parts - 1)) {
+            __hip_atomic_store(&st->started, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->way, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
+    // row blocks of row tile tl (0, 1 of the wavefront) that this block finishes
+    auto owns = [&](int mb) { return mb >= own_lo && mb < own_hi; };
+    auto owns_of = [&](int tl) { return own_lo < 4 * tl + 4 && own_hi > 4 * tl; };
 
     // ---- the adapter slab.  Bp operands of a row tile: granule 4ks + g (the 8 ranks a lane's operand holds,
     // contiguous per column; past the stored rank the last granule, which meets zeros of s.v), all four k
@@ -329,7 +355,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
                 bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(4 * ks + g, rs8 - 1) * a.h_out + col) * 8));
             }
     };
-    const bool live0 = mine0.rank != 0 && mine0.n_tok != 0, live1 = mine1.rank != 0 && mine1.n_tok != 0;  // wavefront-uniform
+    const bool live0 = mine0.rank != 0 && mine0.n_tok != 0 && owns_of(0), live1 = mine1.rank != 0 && mine1.n_tok != 0 && owns_of(1);  // wavefront-uniform
     bf16x8 bo[4][4];
     if (live0) load_bp(mine0, bo);
     // s.v of the block's rows to LDS as bf16 (zero past a tile's rank or end)
@@ -375,6 +401,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             if (ks < ks32) {
 #pragma unroll
                 for (int mbl = 0; mbl < 4; ++mbl) {
+                    if (!owns(4 * tl + mbl)) continue;  // uniform
                     const bf16x8 so = *reinterpret_cast<const bf16x8 *>(svr + mbl * 16 * SV_ROW + ks * 64);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
@@ -411,7 +438,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             tile_tokens_of(a.tok_list, t, ti4, dead_tok, tok4);
 #pragma unroll
             for (int mbl = 0; mbl < 4; ++mbl) {
-                if (ti4[mbl] >= t.n_tok) continue;
+                if (!owns(4 * tl + mbl) || ti4[mbl] >= t.n_tok) continue;
                 __bf16 *yr = y + (size_t)tok4[mbl] * a.h_out + n0 + 64 * cq + 4 * g;
                 floatx4 term[4];
                 if (a.y32) {
@@ -439,6 +466,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         }
 #pragma unroll
         for (int mbl = 0; mbl < 4; ++mbl) {
+            if (!owns(4 * tl + mbl)) continue;
             const int ti = 16 * mbl + m, row = 64 * tl + ti;
             unsigned char *pr = park + row * 128;
 #pragma unroll
@@ -465,7 +493,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 64 * tl + ti8[i];
-            if (ti8[i] < t.n_tok) {
+            if (owns(4 * tl + (i >> 1)) && ti8[i] < t.n_tok) {
                 const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((sl ^ ((row >> 1) & 7)) << 4));
                 // (a streaming store: the rows leave the caches as they are written instead of lying there dirty
                 // until the next kernel's loads push them out -- the tile shrink that follows runs 2 to 3 us shorter)
@@ -496,13 +524,10 @@ hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipS
 }
 
 // Parts the tiles of the last round are split into (1: none), and how many tiles that round has.  The number of parts
-// is the one with the shortest estimate, in stages of 1.1 us: ceil(tiles * parts / CUs) waves of n_k / parts stages
-// and about 8 more for a block's start and end, and the hand-over: 7 us a part for the block that reads the others' sums,
-// or, with many tiles, the time their bytes take (all parts' sums written and all but one part's read, past the caches:
-// 256 KB each at 2.8 TB/s).  Measured in us whole and in two, three and four parts: behind a whole round 16 tiles of 64 stages 160, 138, 132,
-// 130 (the whole launch), 48 tiles 158, 140, 135, 139, 28 tiles of 80 stages 305, 278, 270, 269, 32 tiles of 16 stages 65, 67, 68, 72; by
-// themselves 8 tiles of 64 stages 72, 53, 48, 46, 80 tiles 75, 61, 64, 96 tiles 76, 64, 128 tiles 77, 79, 48 tiles of 172 stages 168,
-// 109, 97, 84.
+// is the one with the shortest estimate, in stages of 1.33 us: ceil(tiles * parts / CUs) waves of n_k / parts stages
+// and about 8 more for a block's start and end, and the hand-over, whose bytes (512 KB for every part but one, written
+// and read past the caches) take 0.09 stages each at the 4.5 TB/s of memory.  (48 tiles of 64 stages behind a whole round: 45 us in five
+// parts, estimated 50; 136 tiles of 80 stages: 117 us in three parts, estimated 125, and whole 112, estimated 117.)
 // max_shares: what the scratch holds, in accumulator sets of a tile (LINEAR_SHARE_BYTES).
 static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares, int &parts, int &n_tail)
 {
@@ -510,15 +535,14 @@ static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares
     parts = 1;
     double best = 0;
     for (int p = 1; p <= MAX_PARTS && (p == 1 || (p * 4 <= n_k && (size_t)n_tail * p <= max_shares)); ++p) {
-        const double handover = p == 1 ? 0.0 : std::max(6.4 * p, 0.085 * n_tail * (2 * p - 1));
-        const double t = (double)((n_tail * p + n_cu - 1) / n_cu) * ((n_k + p - 1) / p + 8) + handover;
+        const double t = (double)((n_tail * p + n_cu - 1) / n_cu) * ((n_k + p - 1) / p + 8) + 0.09 * n_tail * (p - 1);
         if (p == 1 || t < best) best = t, parts = p;
     }
     if (parts == 1) n_tail = 0;
 }
 
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
-                               size_t split_scratch_bytes, uint32_t *split_counts, int n_split_counts, int n_cu,
+                               size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (n_rt <= 0) return hipSuccess;
@@ -532,8 +556,8 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem
     const int n_mt = (n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
     int parts, n_tail;
     linear_split_shape(n_tiles, a.h_in / LBK, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
-    if (n_tail > n_split_counts) parts = 1, n_tail = 0;
-    const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_counts};
+    if (n_tail > n_split_state) parts = 1, n_tail = 0;
+    const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;
     launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
              row_tiles, n_rt, n_mt, n_nt, sp);

@@ -39,7 +39,7 @@ constexpr int SHRINK_VARIANT_BATCH = SHRINK_VARIANT_SMALL + 1;
 constexpr int SHRINK_BATCH_RUNS[] = {64, 32};
 constexpr int SHRINK_VARIANTS = SHRINK_VARIANT_BATCH + 2;
 constexpr int SHRINK_BATCH_BLOCKS = 1024;  // a batch's launch has at most this many blocks, where a table is small enough
-constexpr int N_LINEAR_COUNTS = 1024;  // one count per split tile of lora_linear_plan (tiles of the last round: fewer than CUs)
+constexpr int N_LINEAR_SPLITS = 256;  // split tiles of lora_linear_plan (tiles of the last round: fewer than CUs)
 constexpr double TILE_PATH_FIXED_US = 25.0;          // what the three launches of the tile path cost beside their work
 constexpr double TILE_PATH_L2_BYTES_PER_US = 10e6;  // rate at which repeated passes over a slab come out of L2
 // Applies that run together in one batch each have their own copy of the intermediate (a set): as many sets as fit into
@@ -179,7 +179,7 @@ struct lora_cache {
     std::vector<size_t> proj_off;   // [n_proj] byte offset of the projection's slabs inside a layer
     std::vector<size_t> row_bytes;  // [n_proj] (h_in + h_out) * element size
     int64_t total_rows = 0;
-    size_t off_counts = 0, off_vpart = 0, off_vtag = 0, v_set_bytes = 0, vtag_set_bytes = 0;
+    size_t off_splits = 0, off_vpart = 0, off_vtag = 0, v_set_bytes = 0, vtag_set_bytes = 0;
     int n_sets = lora::GROUP_MAX_PROJS;  // copies of the intermediate buffers: projections of a batch
     uint32_t tag_epoch = 0;  // one-launch GEMV launches so far; the number the words of the latest one carry
     unsigned long long cap_id = 0;
@@ -324,8 +324,8 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     c.stage_cap = small_scratch ? align_up(max_part) + ALIGN : align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
 
     size_t cur = align_up(c.layer_stride * (size_t)c.n_layers);
-    c.off_counts = cur;
-    cur += align_up(sizeof(uint32_t) * N_LINEAR_COUNTS);
+    c.off_splits = cur;
+    cur += align_up(sizeof(lora::SplitState) * N_LINEAR_SPLITS);
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
     c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
@@ -342,15 +342,15 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     }
     c.off_vpart = cur;
     c.vpart_bytes = align_up(sizeof(float) * (size_t)c.vpart_rows * c.v_stride);
-    // (the fused linear kernel parks the sums of its split tiles in the same region: a round of 256 blocks that are all
-    // parts of split tiles, 256 KB each; less for caches of small batches)
+    // (the fused linear kernel parks the sums of its split tiles in the same region: a third more parts than a round of 256 blocks,
+    // 256 KB each; less for caches of small batches)
     if (c.dtype == LORA_BF16 && small_scratch) {
         c.vpart_bytes = std::max(c.vpart_bytes, std::min<size_t>((size_t)48 << 20, align_up(sizeof(float) * (size_t)c.v_stride * 8 * (size_t)c.max_tokens)));
     } else if (c.dtype == LORA_BF16) {
         const size_t row_tiles = std::min<size_t>((size_t)c.max_tokens, (size_t)c.max_tokens / LORA_TILE_TOKENS + (size_t)c.max_segments) + 2;
         size_t col_tiles = 1;
         for (const auto &pr : c.proj) col_tiles = std::max(col_tiles, ((size_t)pr.h_out + 255) / 256);
-        c.vpart_bytes = std::max(c.vpart_bytes, lora::LINEAR_SHARE_BYTES * std::min<size_t>(256, (row_tiles + 3) / 4 * col_tiles * 4));
+        c.vpart_bytes = std::max(c.vpart_bytes, lora::LINEAR_SHARE_BYTES * std::min<size_t>(340, (row_tiles + 3) / 4 * col_tiles * 8));
     }
     cur += c.vpart_bytes;
     // the GEMV phases hand their intermediate over as 64-bit words, one row per token and projection of a group
@@ -1007,7 +1007,7 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         hipHostGetDevicePointer(reinterpret_cast<void **>(&c->fault_dev), c->fault_host, 0) != hipSuccess ||
         (*c->fault_host = 0, false) ||
         hipMemset(c->pool + c->off_vtag, 0, c->vtag_set_bytes * c->n_sets) != hipSuccess ||
-        hipMemset(c->pool + c->off_counts, 0, sizeof(uint32_t) * N_LINEAR_COUNTS) != hipSuccess) {
+        hipMemset(c->pool + c->off_splits, 0, sizeof(lora::SplitState) * N_LINEAR_SPLITS) != hipSuccess) {
         g_last_hip = (int)hipGetLastError();
         delete c;
         return LORA_E_HIP;
@@ -2174,8 +2174,8 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     lin.tok_list = reinterpret_cast<const int32_t *>(p->dev + p->off_lin_tok);
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
     HIP_TRY(lora::launch_linear_tiles(lin, Wt, reinterpret_cast<const lora::DevItem *>(p->dev + p->off_lin_tiles), p->n_lin_tiles,
-                                      c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<uint32_t *>(c->pool + c->off_counts),
-                                      N_LINEAR_COUNTS, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));
+                                      c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
+                                      N_LINEAR_SPLITS, c->fault_dev, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));
     if (tm && f >= 0) HIP_TRY(hipEventRecord(c->fences[f].ev, st));
     const int64_t seq = ++c->apply_seq;
     ++c->stats.applies;

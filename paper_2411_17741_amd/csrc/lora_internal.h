@@ -358,11 +358,14 @@ hipError_t launch_mfma_expand(const TileBatch &tb, hipStream_t st, const KernelT
 // rank 0); a.tok_list must be the list the row tiles index; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]
 // The tiles of the grid's last, partly filled round are split along k over several blocks as far as split_scratch
-// (device; LINEAR_SHARE_BYTES for every part of a tile) and split_counts (device, zero between launches, one per split
-// tile) have room.
+// (device; LINEAR_SHARE_BYTES for every part of a tile) and split_state (device, zero between launches, one per split
+// tile) have room; fault: raised when the bounded wait for the other parts gives up.
+struct SplitState {
+    uint32_t started, way, arrived, read;  // parts that run, have left their sums, have read the others'; way: how the tile is finished
+};
 constexpr size_t LINEAR_SHARE_BYTES = (size_t)256 * 256 * sizeof(float);  // a tile's accumulators
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
-                               size_t split_scratch_bytes, uint32_t *split_counts, int n_split_counts, int n_cu,
+                               size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // a plan's work lists (bytes rounded up to 16) from pinned host memory as the device sees it to their place in the pool
 hipError_t launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st, hipEvent_t done);

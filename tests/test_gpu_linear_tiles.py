@@ -8,15 +8,16 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("lens,h_in,h_out", [
-    ([300], 4096, 1024),                     # 8 tiles of 256 x 256: three parts
-    ([300], 8192, 1024),                     # 8 tiles, 128 k stages: four parts
-    ([1000], 4160, 1280),                    # 25 tiles, 65 k stages: three parts
-    ([1, 700, 900, 2, 833], 2112, 1024),     # 44 tiles, 33 k stages: two parts
-    ([4000, 100], 4096, 1088),               # 85 tiles, the last column panel 64 wide: two parts
+    ([300], 4096, 1024),                     # 8 tiles of 256 x 256: eight parts
+    ([1000], 4160, 1280),                    # 25 tiles, 65 k stages: five parts
+    ([700], 11008, 2304),                    # 36 tiles, 172 k stages: seven parts
+    ([1, 700, 900, 2, 833], 2112, 1024),     # 44 tiles, 33 k stages: three parts
+    ([4000, 100], 4096, 1088),               # 85 tiles, the last column panel 64 wide: three parts
     ([3100], 2048, 2432),                    # 130 tiles: whole
     ([2000, 17], 4096, 4096),                # 144 tiles: whole
-    ([4096, 300], 2112, 4096),               # a whole round, then 32 tiles in two parts
-    ([16384, 190], 512, 1024),               # a whole round, then 8 whole tiles (eight k stages)
+    ([1700], 4096, 4096),                    # 128 tiles: two parts
+    ([4096, 300], 2112, 4096),               # a whole round, then 32 tiles in three parts
+    ([16384, 190], 512, 1024),               # a whole round, then 8 tiles in two parts (eight k stages)
     ([63], 64, 64),                          # one k stage
     ([65, 5], 192, 320),                     # three k stages
 ])
@@ -58,46 +59,86 @@ def test_linear_against_torch(lens, h_in, h_out):
         pool.close()
 
 
-def test_split_products_of_two_caches_at_the_same_time():
-    """64 tiles in four parts each: one such launch fills the chip with parts of split tiles, two side by side get their places
-    in whatever order, and whichever part of a tile comes last finishes it.  The results are those of one launch after
-    the other, bit for bit."""
+@pytest.mark.parametrize("T,h_in,h_out,tiles", [(300, 4096, 1024, 8), (700, 11008, 2304, 27), (1100, 4096, 4096, 80), (2048, 4096, 4096, 128)])
+def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
+    """What happens when a part is done before another has started, forced from the host: the tiles' state (16 bytes each,
+    behind the slabs: parts started, way, parts arrived, parts that have read) says so before the launch.  Bit for bit the
+    result of parts that share the tile; the state is back at zero."""
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
-    h_in, h, T, rank, n = 12288, 4096, 1000, 16, 12
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    pool = LoraPool([(h_in, h_out)], 1, [16], [1], B.LORA_BF16, max_tokens=T, max_segments=1)
+    try:
+        pool.fill(0, 1, 16, 1.0, 0, 0, normal(h_in, 16, sigma=0.02).cpu(), normal(16, h_out, sigma=0.02).cpu())
+        plan = pool.plan(T, np.asarray([0, T], np.int32), np.zeros(1, np.int32), np.full(1, 16, np.int32))
+        x, wt = normal(T, h_in), normal(h_out, h_in, sigma=0.02)
+        _rc, slab, n = B.lora_cache_slab(pool.handle, 0, 0, 0)
+        state = pool.buf[slab + n - pool.buf.data_ptr():][: 16 * tiles].view(torch.int32).view(tiles, 4)
+        assert (slab + n) % 256 == 0
+        outs = []
+        for way in (0, 2, 0, 2):
+            y = torch.full((T, h_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+            assert not state.any()
+            state[:, 1] = way
+            B.check(B.lora_linear_plan(pool.handle, plan, 0, 0, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0, torch.cuda.current_stream().cuda_stream))
+            pool.check_fault()
+            outs.append(y)
+        assert not state.any()
+        assert not outs[0].isnan().any()
+        for y in outs[1:]:
+            assert torch.equal(y, outs[0])
+    finally:
+        pool.close()
+
+
+def test_split_products_on_a_busy_device():
+    """Launches whose last round is all parts of split tiles (80 tiles of three parts) from two caches on two streams beside
+    matrix products on a third: parts get their places late and in whatever order, and a tile whose parts are not all running
+    when its first part is done is finished by the last of them alone.  The results are those of one launch by itself, bit
+    for bit."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    h, T, rank, n = 4096, 1100, 16, 24
     gen = torch.Generator(device="cuda").manual_seed(7)
     normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
-    A, Bm = normal(h_in, rank, sigma=0.02).cpu(), normal(rank, h, sigma=0.02).cpu()
-    x, wt = [normal(T, h_in) for _ in range(2)], [normal(h, h_in, sigma=0.02) for _ in range(2)]
+    A, Bm = normal(h, rank, sigma=0.02).cpu(), normal(rank, h, sigma=0.02).cpu()
+    x, wt = [normal(T, h) for _ in range(2)], [normal(h, h, sigma=0.02) for _ in range(2)]
     y = [[torch.empty(T, h, dtype=torch.bfloat16, device="cuda") for _ in range(n)] for _ in range(2)]
-    pools = [LoraPool([(h_in, h)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=1) for _ in range(2)]
-    streams = [torch.cuda.Stream() for _ in range(2)]
+    a, b, c = normal(2048, 2048), normal(2048, 2048), torch.empty(2048, 2048, dtype=torch.bfloat16, device="cuda")
+    pools = [LoraPool([(h, h)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=1) for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(3)]
     try:
         plans = []
         for q in pools:
             q.fill(0, 1, rank, 1.0, 0, 0, A, Bm)
             plans.append(q.plan(T, np.asarray([0, T], np.int32), np.zeros(1, np.int32), np.full(1, rank, np.int32)))
+        torch.mm(a, b, out=c)
         torch.cuda.synchronize()
 
-        def product(c, i, stream):
-            B.check(B.lora_linear_plan(pools[c].handle, plans[c], 0, 0, x[c].data_ptr(), wt[c].data_ptr(), y[c][i].data_ptr(), 2.0, stream.cuda_stream))
+        def product(k, i):
+            B.check(B.lora_linear_plan(pools[k].handle, plans[k], 0, 0, x[k].data_ptr(), wt[k].data_ptr(), y[k][i].data_ptr(), 2.0, streams[k].cuda_stream))
 
         want = []
-        for c in range(2):
-            product(c, 0, streams[c])
+        for k in range(2):
+            product(k, 0)
             torch.cuda.synchronize()
-            want.append(y[c][0].clone())
-            y[c][0].zero_()
+            want.append(y[k][0].clone())
+            y[k][0].zero_()
         torch.cuda.synchronize()
         for i in range(n):
-            for c in range(2):
-                product(c, i, streams[c])
+            with torch.cuda.stream(streams[2]):
+                for _ in range(4):
+                    torch.mm(a, b, out=c)
+            for k in range(2):
+                product(k, i)
         torch.cuda.synchronize()
-        for c in range(2):
-            pools[c].check_fault(streams[c])
+        for k in range(2):
+            pools[k].check_fault(streams[k])
             for i in range(n):
-                assert torch.equal(y[c][i], want[c]), (c, i)
+                assert torch.equal(y[k][i], want[k]), (k, i)
     finally:
         for q in pools:
             q.close()
