@@ -564,14 +564,16 @@ def run_workload(args, workload: str, steps: int = 0, cpu_baseline: bool = True,
             B.check(B.lora_apply_plan_multi(h, plan, d, inst.scale, sh), "lora_apply_plan_multi")
         B.check(B.lora_plan_destroy(h, plan))
 
-    for _ in range(max(1, args.warmup)):
-        forward_step()
-    torch.cuda.synchronize()
-    t_f = time.perf_counter()
-    for _ in range(steps):
-        forward_step()
-    torch.cuda.synchronize()
-    forward_order = {"us_per_layer": (time.perf_counter() - t_f) * 1e6 / steps / n_layers, "calls_per_layer": len(groups) // n_layers}
+    forward_order = None
+    if not args.no_forward_order:
+        for _ in range(max(1, args.warmup)):
+            forward_step()
+        torch.cuda.synchronize()
+        t_f = time.perf_counter()
+        for _ in range(steps):
+            forward_step()
+        torch.cuda.synchronize()
+        forward_order = {"us_per_layer": (time.perf_counter() - t_f) * 1e6 / steps / n_layers, "calls_per_layer": len(groups) // n_layers}
 
     # the applies of a step recorded into a HIP graph once and replayed (what a decode loop does with its iteration):
     # same kernels, no host work per launch.  One plan, made outside the capture; fencing off while capturing.
@@ -795,6 +797,7 @@ def main() -> int:
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-kernel-timing", action="store_true")
     ap.add_argument("--no-graph", action="store_true", help="skip the graph-replay timing of the step")
+    ap.add_argument("--no-forward-order", action="store_true", help="skip the timing of the step with one call per group of projections")
     ap.add_argument("--no-overlap", action="store_true", help="the GEMV launch of an apply behind its tile kernels instead of beside them (LORA_CACHE_NO_OVERLAP): "
                     "per-kernel durations of a trace then stand for the kernels alone")
     args = ap.parse_args()
