@@ -1,11 +1,11 @@
 // Base projection and adapter update in one matrix-core kernel for gfx950 (bf16 in, fp32 accumulate):
 //     y[t] = x[t] . W  +  s_i . v[t] . B_i          v[t] = x[t] . A_i from the shrink kernels
-// for row tiles of up to 64 tokens that share one adapter (or have none).  The adapter product enters
-// as one more slab of the contraction after the k loop over h_in, so the output is written once and
-// never read: the separate addition of the adapter result to the base output (paper section 3.1)
+// for the tokens of a batch in one list of rows, those of an adapter next to each other (LinearRows).  The adapter product enters
+// as one more slab of the contraction after the k loop over h_in, segment by segment of a block's rows, so the output is written once
+// and never read: the separate addition of the adapter result to the base output (paper section 3.1)
 // disappears.  This is the variant of the hot path whose roof is the matrix cores, not HBM.
 //
-// Block = 8 wavefronts on 256 rows (four row tiles) x 256 output columns; wavefront w owns the row half w/4 and the
+// Block = 8 wavefronts on 256 rows (four runs of 64) x 256 output columns; wavefront w owns the row half w/4 and the
 // column quarter w%4: 8 x 4 products of 16 x 16 (v_mfma_f32_16x16x32_bf16, 128 accumulator registers).  x rows
 // (gathered by token) and Wt rows (Wt[n][k] = W[k][n], the layout a linear layer keeps its weight in) are both
 // contiguous along k: a stage is 64 k of both, 64 KB, brought into LDS by global_load_lds_dwordx4 -- the load writes
@@ -14,7 +14,7 @@
 // What bounds the loop is that matrix cores, LDS and the load path each need most of a stage's time (products 0.85 us at
 // the peak rate, 192 KB of operand reads, 64 KB of loads): done one after the other by wavefronts in step, with a wait
 // for all loads at the stage's end, a stage took 2 us.  So the two wavefronts of a SIMD (w and w + 4) take turns: a
-// stage is two phases (row tile 0 and row tile 1 of the wavefront), a phase a *load section* -- the phase's operand
+// stage is two phases (run 0 and run 1 of the wavefront), a phase a *load section* -- the phase's operand
 // reads and the requests for later stages -- and a *product section* of 32 products, with a barrier behind each, and
 // wavefronts 4..7 run one section behind wavefronts 0..3.  The requests are counted, not drained: an LDS half (128 rows
 // of x or Wt) is requested three phases before it is read, as soon as the phase after its last read has begun, and a
@@ -35,11 +35,13 @@
 // operand -- so that a lane's four accumulator registers are four consecutive output columns of one
 // token: 8 bytes of bf16, parked in LDS and stored from there in whole 128-byte lines.
 // After the k loop the scaled intermediate s.v of the block's rows is staged in LDS as bf16 and every
-// wavefront adds, per row tile, the products with that tile's Bp, whose rank-packed layout gives the
-// row operand directly from global memory (a lane's 8 ranks are 16 contiguous bytes).
-// Tokens on the GEMV path sit in row tiles without an adapter; their adapter term is computed by the
-// GEMV kernels beforehand into the (zeroed) output rows, and this kernel adds it to the accumulators of
-// those rows before the one rounding of the stored value (row tiles marked a = 1).
+// wavefront adds, per segment of its rows, the products with that segment's Bp, whose rank-packed layout gives the
+// row operand directly from global memory (a lane's 8 ranks are 16 contiguous bytes); rows of other segments meet zeros.
+// (Rows without gaps, where every tile had 64 rows of its own: a 13B layer's batch 12 -> 10 row panels, 1936 -> 1804 us for its seven
+// projections; eight prompts at 4096 x 4096 19 -> 17 panels, 162 -> 154 us.)
+// The adapter term of tokens on the GEMV path is computed by the GEMV kernels beforehand into the workspace or the
+// (zeroed) output rows, and this kernel adds it to the accumulators of those rows (LinearList::add0 ..) before the one rounding
+// of the stored value.
 //
 // Block order.  Tiles are counted in groups of four row panels, a group column by column, and every XCD takes a run of
 // consecutive ones (block b runs on XCD b % 8): the 32 blocks of an XCD then share 4 row panels and 8 column panels
@@ -101,8 +103,22 @@ __device__ __forceinline__ void section_end()
     __builtin_amdgcn_sched_barrier(0);
 }
 
+// The s.v operand of the adapter product: of the 8 ranks of a lane the first n (what lies behind them was never written) of a row
+// of the segment, zeros for a row of another.  As masks of whole words: a stale NaN must not survive.
+__device__ __forceinline__ uint4 rank_mask(int n)
+{
+    auto word = [&](int j) { return n >= 2 * j + 2 ? 0xffffffffu : (n == 2 * j + 1 ? 0x0000ffffu : 0u); };
+    return make_uint4(word(0), word(1), word(2), word(3));
+}
+__device__ __forceinline__ bf16x8 sv_operand(const unsigned char *p, const uint4 &live, bool row_in)
+{
+    const uint4 v = *reinterpret_cast<const uint4 *>(p), z = make_uint4(0u, 0u, 0u, 0u);
+    const uint4 f = make_uint4(v.x & live.x, v.y & live.y, v.z & live.z, v.w & live.w);
+    return __builtin_bit_cast(bf16x8, row_in ? f : z);
+}
+
 __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
-                                                           const DevItem *__restrict__ tiles, int n_rt, int n_mt, int n_nt, LinearSplit sp)
+                                                           LinearList list, int n_mt, int n_nt, LinearSplit sp)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -122,21 +138,15 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     linear_tile(tile_no, n_mt, n_nt, bm, bn);
     const int n0 = bn * LBN;
 
-    // the four row tiles of the block (a missing one counts as empty), and the two of this wavefront's
-    // row half once more under fixed names (indexing the four by the wavefront number would put them
-    // in scratch memory)
-    auto get_tile = [&](int idx) {
-        DevItem t = tiles[min(idx, n_rt - 1)];
-        if (idx >= n_rt) {
-            t.n_tok = 0;
-            t.rank = 0;
-        }
+    // the two runs of 64 rows of this wavefront's row half (a missing one counts as empty)
+    auto get_rows = [&](int idx) {
+        LinearRows t = list.rows[min(idx, list.n_rt - 1)];
+        if (idx >= list.n_rt) t.n_tok = t.n_segs = 0;
         return t;
     };
-    const DevItem it0 = get_tile(4 * bm), it1 = get_tile(4 * bm + 1), it2 = get_tile(4 * bm + 2), it3 = get_tile(4 * bm + 3);
-    const DevItem mine0 = get_tile(4 * bm + 2 * rh), mine1 = get_tile(4 * bm + 2 * rh + 1);
-    auto tile_of = [&](int j) -> const DevItem & { return j == 0 ? it0 : j == 1 ? it1 : j == 2 ? it2 : it3; };  // j: compile-time
-    const int dead_tok = it0.tok0;  // rows past a tile's end read a live token's x; they are never stored
+    const LinearRows mine0 = get_rows(4 * bm + 2 * rh), mine1 = get_rows(4 * bm + 2 * rh + 1);
+    const int row0 = LBM * bm;  // the block's first row
+    const int dead_tok = list.rows[4 * bm].tok0;  // rows past the end read a live token's x; they are never stored
 
     const __bf16 *x = static_cast<const __bf16 *>(a.x);
     __bf16 *y = static_cast<__bf16 *>(a.y);
@@ -144,7 +154,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     // this block's stages of the k walk
     const int k_lo = tail < 0 ? 0 : n_k * part / sp.parts, k_hi = tail < 0 ? n_k : n_k * (part + 1) / sp.parts;
 
-    // Half h of x holds row tiles h and 2 + h of the block (phase h of row halves 0 and 1), half h of Wt columns
+    // Half h of x holds runs h and 2 + h of the block (phase h of row halves 0 and 1), half h of Wt columns
     // 64 c + 32 h .. +31 of the four column quarters c.  Loader: wavefront w brings LDS rows 16w + 8q + lane/8, q = 0, 1,
     // of every half: instruction q writes 8 rows x 128 bytes at the wavefront-uniform LDS address of its first row,
     // lane l to slot l%8 of row l/8, for which it fetches piece (l%8) ^ ((row/2) % 8) of the row
@@ -153,10 +163,10 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     const __bf16 *xg[2][2], *wg[2][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        const DevItem t = h ? mine1 : mine0;  // (the row tiles a wavefront loads from are those it works on)
+        const LinearRows t = h ? mine1 : mine0;  // (the runs a wavefront loads from are those it works on)
         const int ti[2] = {16 * cq + lr, 16 * cq + 8 + lr};
         int tok[2];
-        tile_tokens_of(a.tok_list, t, ti, dead_tok, tok);  // (rows past the tile's end repeat its last)
+        tile_tokens_of(list.tok, t, ti, dead_tok, tok);  // (rows past the run's end repeat its last)
         // h_out is a multiple of 64, so a run of 64 columns is inside or outside as a whole
         const int w_row = min(n0 + 64 * (w >> 1), a.h_out - 64) + 32 * h + 16 * (w & 1) + lr;
 #pragma unroll
@@ -333,20 +343,17 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             __hip_atomic_store(&st->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // row blocks of row tile tl (0, 1 of the wavefront) that this block finishes
+    // row blocks (of the wavefront's eight) that this block finishes
     auto owns = [&](int mb) { return mb >= own_lo && mb < own_hi; };
-    auto owns_of = [&](int tl) { return own_lo < 4 * tl + 4 && own_hi > 4 * tl; };
 
-    // ---- the adapter slab.  Bp operands of a row tile: granule 4ks + g (the 8 ranks a lane's operand holds,
-    // contiguous per column; past the stored rank the last granule, which meets zeros of s.v), all four k
-    // steps requested at once -- and for the wavefront's first tile before s.v is staged, so that the
-    // requests fly while the staging waits for its own loads.
-    auto bp_of = [&](const DevItem &t) {
-        return reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)t.row * a.row_bytes) + (size_t)rank_storage(t.rank) * a.h_in;
-    };
-    auto load_bp = [&](const DevItem &t, bf16x8(&bo)[4][4]) {
-        const int rs8 = rank_storage(max(t.rank, 1)) >> 3;
-        const __bf16 *Bp = bp_of(t);
+    // ---- the adapter slab, segment by segment of the wavefront's rows.  Bp operands: granule 4ks + g (the 8 ranks a lane's
+    // operand holds, contiguous per column; past the stored rank the last granule, which meets zeros of s.v), all four k
+    // steps requested at once -- and for the first segment before s.v is staged, so that the requests fly while the staging
+    // waits for its own loads.
+    bf16x8 bo[4][4];
+    auto load_bp = [&](const LinearSeg &t) {
+        const __bf16 *Bp = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)t.row * a.row_bytes) + (size_t)rank_storage(t.rank) * a.h_in;
+        const int rs8 = rank_storage(t.rank) >> 3;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -355,57 +362,56 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
                 bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(4 * ks + g, rs8 - 1) * a.h_out + col) * 8));
             }
     };
-    const bool live0 = mine0.rank != 0 && mine0.n_tok != 0 && owns_of(0), live1 = mine1.rank != 0 && mine1.n_tok != 0 && owns_of(1);  // wavefront-uniform
-    bf16x8 bo[4][4];
-    if (live0) load_bp(mine0, bo);
-    // s.v of the block's rows to LDS as bf16 (zero past a tile's rank or end)
-    unsigned char *sv = lds;
-    {
-        // chunk tid%16 (8 ranks) of rows tid/16 and tid/16 + 32 of each row tile that has an adapter: per tile the
-        // two token ids in one round, then both rows' pieces in one round (unconditional, from addresses inside v)
+    // (rows with an adapter product come first in the list)
+    const int seg0 = mine0.first_seg, seg1 = mine1.n_segs > 0 ? mine1.first_seg + mine1.n_segs : seg0 + mine0.n_segs;  // wavefront-uniform
+    LinearSeg seg = {};
+    if (seg0 < seg1) {
+        seg = list.segs[seg0];
+        load_bp(seg);
+    }
+    unsigned char *sv = lds;  // s.v of the block's rows as bf16
+    if (row0 < list.add0) {
+        // chunk tid % 16 (8 ranks) of rows tid / 16 + 32 i: the token ids in one round, then the pieces, four rows at a time
+        // (unconditional, from addresses inside v; what lies past a row's rank is masked where it is used)
         const int c8 = tid & 15, r0 = tid >> 4;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const DevItem &t = tile_of(jj);
-            if (t.rank == 0 || t.n_tok == 0) continue;  // uniform over the block; nothing of such a tile is read below
-            const int ks32 = (t.rank + 31) >> 5;        // k steps this tile's products will read
-            const int ti[2] = {r0, r0 + 32};
-            int tok[2];
-            tile_tokens_of(a.tok_list, t, ti, dead_tok, tok);
-            uint4 pc[2];  // s.v comes as bf16 from the shrink or the reduce (rows of the fp32 pitch)
+        for (int i0 = 0; i0 < 8; i0 += 4) {
+            int tok[4];
+            uint4 pc[4];
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                pc[h] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[h] * (2 * a.v_stride) + c8 * 8);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (c8 < 4 * ks32) {
-                    const bf16x8 f = __builtin_bit_cast(bf16x8, pc[h]);
-                    bf16x8 o;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) o[e] = (ti[h] < t.n_tok && c8 * 8 + e < t.rank) ? f[e] : (__bf16)0.f;
-                    *reinterpret_cast<bf16x8 *>(sv + (64 * jj + ti[h]) * SV_ROW + c8 * 16) = o;
-                }
+            for (int j = 0; j < 4; j += 2) {
+                const int ti[2] = {r0, r0 + 32};
+                int tk[2];
+                tile_tokens_of(list.tok, list.rows[min(4 * bm + (i0 + j) / 2, list.n_rt - 1)], ti, dead_tok, tk);
+                tok[j] = tk[0], tok[j + 1] = tk[1];
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)  // s.v comes as bf16 from the shrink or the reduce (rows of the fp32 pitch)
+                pc[j] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[j] * (2 * a.v_stride) + c8 * 8);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) *reinterpret_cast<uint4 *>(sv + (r0 + 32 * (i0 + j)) * SV_ROW + c8 * 16) = pc[j];
         }
     }
     __syncthreads();
-#pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-        const DevItem &t = tl ? mine1 : mine0;
-        if (!(tl ? live1 : live0)) continue;
-        if (tl == 1) load_bp(mine1, bo);
-        const int ks32 = (t.rank + 31) >> 5;
-        const unsigned char *svr = sv + (128 * rh + 64 * tl + m) * SV_ROW + g * 16;
+    for (int s = seg0; s < seg1; ++s) {
+        if (s > seg0) {
+            seg = list.segs[s];
+            load_bp(seg);
+        }
+        const int ks32 = (seg.rank + 31) >> 5;
+        const int lo = seg.r0 - row0 - 128 * rh, hi = seg.r1 - row0 - 128 * rh;  // its rows among the wavefront's 128
+        const unsigned char *svr = sv + (128 * rh + m) * SV_ROW + g * 16;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
             if (ks < ks32) {
+                const uint4 live = rank_mask(seg.rank - 32 * ks - 8 * g);
 #pragma unroll
-                for (int mbl = 0; mbl < 4; ++mbl) {
-                    if (!owns(4 * tl + mbl)) continue;  // uniform
-                    const bf16x8 so = *reinterpret_cast<const bf16x8 *>(svr + mbl * 16 * SV_ROW + ks * 64);
+                for (int mb = 0; mb < 8; ++mb) {
+                    if (!owns(mb) || 16 * mb + 16 <= lo || 16 * mb >= hi) continue;  // uniform
+                    const bf16x8 so = sv_operand(svr + mb * 16 * SV_ROW + ks * 64, live, 16 * mb + m >= lo && 16 * mb + m < hi);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
-                        acc[4 * tl + mbl][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[4 * tl + mbl][nb], 0, 0, 0);
+                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
                 }
             }
         }
@@ -417,52 +423,46 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     // wavefront parks its 128 x 64 outputs in LDS and stores whole 128-byte row pieces, 8 rows per
     // instruction (stored from the registers, an instruction would write 32 bytes to each of 16 rows).
     // Park layout, free of bank conflicts both ways: row r is 128 bytes, its 8-byte cell c sits at
-    // c ^ (2 * ((r/2) % 8)), i.e. its 16-byte slot s at s ^ ((r/2) % 8).  Row tiles whose rows already hold
-    // the adapter term (GEMV tokens) are few and go straight from the registers, the sum formed in fp32
-    // before the one rounding.
+    // c ^ (2 * ((r/2) % 8)), i.e. its 16-byte slot s at s ^ ((r/2) % 8).  Rows of GEMV tokens take their adapter term, computed
+    // beforehand, into the accumulators here, so that the sum is formed in fp32 before the one rounding.
     __syncthreads();  // every wavefront is done with the staged s.v
     unsigned char *park = lds + w * (128 * 128);
     const bool cols_live = n0 + 64 * cq < a.h_out;  // h_out is a multiple of 64
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 #pragma unroll
     for (int tl = 0; tl < 2; ++tl) {
-        const DevItem &t = tl ? mine1 : mine0;
+        const LinearRows &t = tl ? mine1 : mine0;
         if (t.n_tok == 0 || !cols_live) continue;  // wavefront-uniform
-        const bool add_y = t.rank == 0 && t.a == 1;
-        if (add_y) {
-            // rows whose adapter term is already in y (or, as fp32, at the same place of the workspace): the four
-            // token ids in one round, then per row block the four old values in one round and the four stores
+        if (t.tok_off < list.add1 && t.tok_off + t.n_tok > list.add0) {
+            // as fp32 at the same place of the workspace, or in y: the four token ids in one round, then per row block the four terms
             int ti4[4], tok4[4];
 #pragma unroll
             for (int mbl = 0; mbl < 4; ++mbl) ti4[mbl] = 16 * mbl + m;
-            tile_tokens_of(a.tok_list, t, ti4, dead_tok, tok4);
+            tile_tokens_of(list.tok, t, ti4, dead_tok, tok4);
 #pragma unroll
             for (int mbl = 0; mbl < 4; ++mbl) {
-                if (!owns(4 * tl + mbl) || ti4[mbl] >= t.n_tok) continue;
-                __bf16 *yr = y + (size_t)tok4[mbl] * a.h_out + n0 + 64 * cq + 4 * g;
+                if (!owns(4 * tl + mbl)) continue;
+                const int r = t.tok_off + ti4[mbl];
+                if (r < list.add0 || r >= list.add1) continue;
+                const size_t at = (size_t)tok4[mbl] * a.h_out + n0 + 64 * cq + 4 * g;
                 floatx4 term[4];
                 if (a.y32) {
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) term[nb] = *reinterpret_cast<const floatx4 *>(a.y32 + (yr - y) + 16 * nb);
+                    for (int nb = 0; nb < 4; ++nb) term[nb] = *reinterpret_cast<const floatx4 *>(a.y32 + at + 16 * nb);
                 } else {
                     bf16x4 old[4];
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) old[nb] = *reinterpret_cast<const bf16x4 *>(yr + 16 * nb);
+                    for (int nb = 0; nb < 4; ++nb) old[nb] = *reinterpret_cast<const bf16x4 *>(y + at + 16 * nb);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) term[nb][e] = (float)old[nb][e];
                 }
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb) {
-                    const floatx4 c = acc[4 * tl + mbl][nb];
-                    bf16x4 o;
+                for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(c[e] + term[nb][e]);
-                    *reinterpret_cast<bf16x4 *>(yr + 16 * nb) = o;
-                }
+                    for (int e = 0; e < 4; ++e) acc[4 * tl + mbl][nb][e] += term[nb][e];
             }
-            continue;
         }
 #pragma unroll
         for (int mbl = 0; mbl < 4; ++mbl) {
@@ -483,13 +483,13 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int tl = 0; tl < 2; ++tl) {
-        const DevItem &t = tl ? mine1 : mine0;
-        if (t.n_tok == 0 || !cols_live || (t.rank == 0 && t.a == 1)) continue;  // wavefront-uniform
+        const LinearRows &t = tl ? mine1 : mine0;
+        if (t.n_tok == 0 || !cols_live) continue;  // wavefront-uniform
         const int rl = lane >> 3, sl = lane & 7;
         int ti8[8], tok8[8];  // the rows' token ids all before the first store (a lookup between two stores makes the second wait for the first)
 #pragma unroll
         for (int i = 0; i < 8; ++i) ti8[i] = 8 * i + rl;
-        tile_tokens_of(a.tok_list, t, ti8, dead_tok, tok8);
+        tile_tokens_of(list.tok, t, ti8, dead_tok, tok8);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int row = 64 * tl + ti8[i];
@@ -541,11 +541,11 @@ static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares
     if (parts == 1) n_tail = 0;
 }
 
-hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
+hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearList &list, void *split_scratch,
                                size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
-    if (n_rt <= 0) return hipSuccess;
+    if (list.n_rt <= 0) return hipSuccess;
     static bool attr_set = false;
     if (!attr_set) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_tiles_kernel),
@@ -553,14 +553,14 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int n_mt = (n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
+    const int n_mt = (list.n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
     int parts, n_tail;
     linear_split_shape(n_tiles, a.h_in / LBK, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
     if (n_tail > n_split_state) parts = 1, n_tail = 0;
     const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;
     launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
-             row_tiles, n_rt, n_mt, n_nt, sp);
+             list, n_mt, n_nt, sp);
     return hipGetLastError();
 }
 

@@ -154,10 +154,9 @@ struct lora_plan {
     size_t off_tiles = 0, off_gs = 0, off_ge = 0, bytes = 0;
     int32_t n_wgs = 0, n_wge = 0;  // the GEMV work as wide items (bf16 caches)
     size_t off_wgs = 0, off_wge = 0;
-    // for lora_linear_plan: every token of the batch in row tiles -- the tiles above, then runs of up
-    // to 64 of the other tokens (rank 0) -- over a token list of its own
-    size_t off_lin_tok = 0, off_lin_tiles = 0;
-    int32_t n_lin_tiles = 0;
+    // for lora_linear_plan: the list of every token of the batch, its runs of rows and its segments (lora::LinearList)
+    size_t off_lin_tok = 0, off_lin_rows = 0, off_lin_segs = 0;
+    int32_t n_lin_rows = 0, n_lin_segs = 0;
     std::vector<int32_t> slots;        // distinct slots the batch names
     std::vector<uint32_t> generations;  // their generation at plan time
 };
@@ -317,8 +316,9 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     const int n_tables = small_scratch ? SHRINK_VARIANT_BATCH : SHRINK_VARIANTS;
     c.plan_cap = align_up(sizeof(int32_t) * (size_t)c.max_tokens) + align_up(sizeof(lora_item_t) * max_items) +
                  align_up(sizeof(int32_t) * max_batches) + 4 * ALIGN + (max_wide ? align_up(sizeof(lora::GemvWideItem) * max_wide) + 2 * ALIGN : 0) +
-                 align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
-                 align_up(sizeof(lora_item_t) * (max_tiles + (size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
+                 (c.dtype == LORA_BF16 ? align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
+                                             align_up(sizeof(lora::LinearRows) * ((size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
+                                             align_up(sizeof(lora::LinearSeg) * (size_t)c.max_segments) : 0) +
                  n_tables * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
     // fill staging: a buffer takes parts of an adapter until STAGE_BYTES (or the largest adapter) are in it
     c.stage_cap = small_scratch ? align_up(max_part) + ALIGN : align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
@@ -785,42 +785,45 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.off_tiles = align_up(sizeof(int32_t) * (size_t)w.n_tok_list);
     p.off_gs = p.off_tiles + align_up(sizeof(lora_item_t) * (size_t)w.n_tiles);
     p.off_ge = p.off_gs + align_up(sizeof(lora::GemvItem) * gs.size());
-    // row tiles of the whole batch (bf16 caches: lora_linear_plan): the tiles; then runs of up to 64
-    // of the tokens of the GEMV groups (marked a = 1: their output rows carry the adapter term when
-    // the base product is added); then runs of the tokens that name no adapter.  The token list is
-    // tok_list followed by the latter.
+    // the rows of lora_linear_plan (bf16 caches): tok_list, then the tokens that name no adapter
     std::vector<int32_t> lin_tok;
-    std::vector<lora::DevItem> lin_tiles;
+    std::vector<lora::LinearRows> lin_rows;
+    std::vector<lora::LinearSeg> lin_segs;
     if (c.dtype == LORA_BF16) {
         std::vector<uint8_t> named((size_t)T, 0);
         lin_tok.assign(w.tok_list, w.tok_list + w.n_tok_list);
         for (int32_t t : lin_tok) named[t] = 1;
         for (int32_t t = 0; t < T; ++t)
             if (!named[t]) lin_tok.push_back(t);
-        lin_tiles.resize(w.n_tiles);
-        std::memcpy(lin_tiles.data(), w.tiles, sizeof(lora::DevItem) * (size_t)w.n_tiles);  // stamped above
-        auto plain_runs = [&](int32_t from, int32_t to, int32_t mark) {
-            for (int32_t o = from; o < to; o += LORA_TILE_TOKENS) {
-                lora::DevItem d{};
-                d.tok_off = o;
-                d.n_tok = std::min<int32_t>(LORA_TILE_TOKENS, to - o);
-                d.a = mark;
-                d.tok0 = lin_tok[o];
-                d.consecutive = 1;
-                for (int32_t i = 1; i < d.n_tok; ++i)
-                    if (lin_tok[o + i] != d.tok0 + i) d.consecutive = 0;
-                lin_tiles.push_back(d);
-            }
-        };
-        plain_runs(p.n_tile_tok, w.n_tok_list, 1);
-        plain_runs(w.n_tok_list, (int32_t)lin_tok.size(), 0);
+        const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
+        for (int i = 0; i < w.n_tiles; ++i) {
+            const lora::DevItem &t = dev_tiles[i];
+            if (lin_segs.empty() || lin_segs.back().row != t.row) lin_segs.push_back(lora::LinearSeg{t.tok_off, t.tok_off, t.row, t.rank});
+            lin_segs.back().r1 = t.tok_off + t.n_tok;
+        }
+        size_t s = 0;
+        for (int32_t r = 0; r < T; r += LORA_TILE_TOKENS) {
+            lora::LinearRows d{};
+            d.tok_off = r;
+            d.n_tok = std::min<int32_t>(LORA_TILE_TOKENS, T - r);
+            d.tok0 = lin_tok[r];
+            d.consecutive = 1;
+            for (int32_t i = 1; i < d.n_tok; ++i)
+                if (lin_tok[r + i] != d.tok0 + i) d.consecutive = 0;
+            while (s < lin_segs.size() && lin_segs[s].r1 <= r) ++s;
+            d.first_seg = (int32_t)s;
+            for (size_t e = s; e < lin_segs.size() && lin_segs[e].r0 < r + d.n_tok; ++e) ++d.n_segs;
+            lin_rows.push_back(d);
+        }
     }
-    p.n_lin_tiles = (int32_t)lin_tiles.size();
+    p.n_lin_rows = (int32_t)lin_rows.size();
+    p.n_lin_segs = (int32_t)lin_segs.size();
     p.off_wgs = p.off_ge + align_up(sizeof(lora::GemvItem) * ge.size());
     p.off_wge = p.off_wgs + align_up(sizeof(lora::GemvWideItem) * wgs.size());
     p.off_lin_tok = p.off_wge + align_up(sizeof(lora::GemvWideItem) * wge.size());
-    p.off_lin_tiles = p.off_lin_tok + align_up(sizeof(int32_t) * lin_tok.size());
-    size_t bytes = p.off_lin_tiles + align_up(sizeof(lora::DevItem) * lin_tiles.size());
+    p.off_lin_rows = p.off_lin_tok + align_up(sizeof(int32_t) * lin_tok.size());
+    p.off_lin_segs = p.off_lin_rows + align_up(sizeof(lora::LinearRows) * lin_rows.size());
+    size_t bytes = p.off_lin_segs + align_up(sizeof(lora::LinearSeg) * lin_segs.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         p.shrink_runs[v] = shrink_runs[v].n_runs;
         p.shrink_pieces[v] = shrink_runs[v].any_pieces;
@@ -857,7 +860,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     if (!wgs.empty()) std::memcpy(p.pinned + p.off_wgs, wgs.data(), sizeof(lora::GemvWideItem) * wgs.size());
     if (!wge.empty()) std::memcpy(p.pinned + p.off_wge, wge.data(), sizeof(lora::GemvWideItem) * wge.size());
     if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
-    if (!lin_tiles.empty()) std::memcpy(p.pinned + p.off_lin_tiles, lin_tiles.data(), sizeof(lora::DevItem) * lin_tiles.size());
+    if (!lin_rows.empty()) std::memcpy(p.pinned + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
+    if (!lin_segs.empty()) std::memcpy(p.pinned + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         if (!shrink_runs[v].cuts.empty()) std::memcpy(p.pinned + p.off_cuts[v], shrink_runs[v].cuts.data(), sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
         if (!shrink_runs[v].sums.empty()) std::memcpy(p.pinned + p.off_sums[v], shrink_runs[v].sums.data(), sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
@@ -1633,7 +1637,8 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     const lora::GemvItem *gs = reinterpret_cast<const lora::GemvItem *>(buf + p->off_gs);
     const lora::GemvItem *ge = reinterpret_cast<const lora::GemvItem *>(buf + p->off_ge);
     const int32_t *lin_tok = reinterpret_cast<const int32_t *>(buf + p->off_lin_tok);
-    const lora::DevItem *lin_tiles = reinterpret_cast<const lora::DevItem *>(buf + p->off_lin_tiles);
+    const lora::LinearRows *lin_rows = reinterpret_cast<const lora::LinearRows *>(buf + p->off_lin_rows);
+    const lora::LinearSeg *lin_segs = reinterpret_cast<const lora::LinearSeg *>(buf + p->off_lin_segs);
 
     int32_t nu = 0, nt = 0;
     auto slot_of_row = [&](int32_t row) -> int32_t {
@@ -1765,12 +1770,34 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
             else put(LORA_UNIT_BATCH_EXPAND, ge + item, nullptr, c0, c1, e);
         }
     }
-    for (int32_t i = 0; i < p->n_lin_tiles; ++i) {
-        const int32_t off = nt;
-        tile_tokens(lin_tiles[i], lin_tok);
-        const bool tile = i < p->n_tiles;
-        put_unit(LORA_UNIT_LINEAR_ROWS, off, lin_tiles[i].n_tok, tile ? lin_tiles[i].row : -1, tile ? lin_tiles[i].rank : 0, 0, 0,
-                 tile ? 2 : lin_tiles[i].a, tile ? lin_tiles[i].alpha : 0.f);
+    // the rows of lora_linear_plan: per tile the rows that a segment makes of it (a row outside it is left out), then
+    // the others in runs
+    auto linear_row = [&](int32_t r) {
+        int32_t ti[1] = {r % LORA_TILE_TOKENS}, tok[1];
+        lora::tile_tokens_of(lin_tok, lin_rows[r / LORA_TILE_TOKENS], ti, -1, tok);
+        put_tok(tok[0]);
+    };
+    auto segment_of = [&](int32_t r) -> const lora::LinearSeg * {
+        const lora::LinearRows &lr = lin_rows[r / LORA_TILE_TOKENS];
+        for (int32_t s = lr.first_seg; s < lr.first_seg + lr.n_segs; ++s)
+            if (lin_segs[s].r0 <= r && r < lin_segs[s].r1) return lin_segs + s;
+        return nullptr;
+    };
+    for (int32_t i = 0; i < p->n_tiles && p->n_lin_rows > 0; ++i) {
+        const int32_t off = nt, r0 = tiles[i].tok_off;
+        const lora::LinearSeg *seg = segment_of(r0);
+        for (int32_t r = r0; r < r0 + tiles[i].n_tok; ++r)
+            if (seg && segment_of(r) == seg) linear_row(r);
+        put_unit(LORA_UNIT_LINEAR_ROWS, off, nt - off, seg ? seg->row : -1, seg ? seg->rank : 0, 0, 0, 2, tiles[i].alpha);
+    }
+    for (int32_t mark = 1; mark >= 0 && p->n_lin_rows > 0; --mark) {
+        const int32_t from = mark ? p->n_tile_tok : p->n_tok_list, to = mark ? p->n_tok_list : p->T;
+        for (int32_t r0 = from; r0 < to; r0 += LORA_TILE_TOKENS) {
+            const int32_t off = nt;
+            for (int32_t r = r0; r < std::min(to, r0 + LORA_TILE_TOKENS); ++r)
+                if (!segment_of(r)) linear_row(r);
+            put_unit(LORA_UNIT_LINEAR_ROWS, off, nt - off, -1, 0, 0, 0, mark, 0.f);
+        }
     }
     *n_units = nu;
     *n_toks = nt;
@@ -2170,11 +2197,11 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
             return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
-    lora::ApplyArgs lin = a;
-    lin.tok_list = reinterpret_cast<const int32_t *>(p->dev + p->off_lin_tok);
+    const lora::LinearList list{reinterpret_cast<const int32_t *>(p->dev + p->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(p->dev + p->off_lin_rows),
+                                reinterpret_cast<const lora::LinearSeg *>(p->dev + p->off_lin_segs),
+                                p->n_lin_rows, p->n_tile_tok, p->n_tok_list};
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
-    HIP_TRY(lora::launch_linear_tiles(lin, Wt, reinterpret_cast<const lora::DevItem *>(p->dev + p->off_lin_tiles), p->n_lin_tiles,
-                                      c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
+    HIP_TRY(lora::launch_linear_tiles(a, Wt, list, c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
                                       N_LINEAR_SPLITS, c->fault_dev, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));
     if (tm && f >= 0) HIP_TRY(hipEventRecord(c->fences[f].ev, st));
     const int64_t seq = ++c->apply_seq;

@@ -40,8 +40,8 @@ inline __host__ __device__ int32_t tile_token_of(const int32_t *tok_list, const 
 // Token ids of N rows of a tile in one round of lookups (none for a tile of consecutive tokens).  Rows past the
 // tile's last count as its last, the rows of an empty tile as token `dead`.  (A conditional lookup per row is a
 // branch per row in a kernel, and after each the compiler waits for every load and store still outstanding.)
-template <int N>
-inline __host__ __device__ void tile_tokens_of(const int32_t *tok_list, const DevItem &it, const int (&ti)[N], int32_t dead,
+template <int N, typename Item>
+inline __host__ __device__ void tile_tokens_of(const int32_t *tok_list, const Item &it, const int (&ti)[N], int32_t dead,
                                                int (&tok)[N])
 {
     if (it.n_tok <= 0) {
@@ -55,6 +55,23 @@ inline __host__ __device__ void tile_tokens_of(const int32_t *tok_list, const De
         for (int i = 0; i < N; ++i) tok[i] = tok_list[it.tok_off + (ti[i] < it.n_tok ? ti[i] : it.n_tok - 1)];
     }
 }
+
+// The rows of lora_linear_plan: every token of the batch in one list without gaps -- the tokens of the tiles, tile by tile, then
+// those of the GEMV groups, then those without an adapter -- cut into runs of LORA_TILE_TOKENS rows.  (Tiles padded to 64 rows of
+// their own made 2944 rows of a 13B layer's 2560 tokens, 12 row panels of 256 instead of 10.)  Rows of one slot
+// that follow each other are a segment, whichever run they fall into.
+struct LinearRows {
+    int32_t tok_off, n_tok;      // rows tok_off .. tok_off + n_tok of the list
+    int32_t consecutive, tok0;   // as in DevItem
+    int32_t first_seg, n_segs;   // the segments with rows among them
+    int32_t pad[2];
+};
+static_assert(sizeof(LinearRows) == 32, "read with one 32-byte scalar load");
+struct LinearSeg {
+    int32_t r0, r1;  // rows [r0, r1)
+    int32_t row;     // first storage row of the slot
+    int32_t rank;
+};
 
 // GEMV work item: a batch of up to GEMV_BATCH tokens of one slot, named directly so that the kernels
 // reach their data with one lookup.  A shrink item stands for GEMV_SHRINK_ROWS stored rank rows from
@@ -354,8 +371,15 @@ using TileBatch = TileBatchArgs<BATCH_MAX_PROJS>;
 static_assert(sizeof(TileBatch) <= 3500, "kernel arguments are at most 4 KB");
 hipError_t launch_mfma_shrink(const TileBatch &tb, hipStream_t st, const KernelTimer *tm);
 hipError_t launch_mfma_expand(const TileBatch &tb, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
-// y = x . Wt^T + adapter update for row tiles (tiles of the plan, then plain runs of the other tokens:
-// rank 0); a.tok_list must be the list the row tiles index; a.v holds the shrink results
+// What lora_linear_plan's kernels read of a plan (device): the list of rows, its runs, the segments of the rows with an adapter
+// product (rows [0, add0)), and the rows [add0, add1) whose adapter term has been computed beforehand.
+struct LinearList {
+    const int32_t *tok;
+    const LinearRows *rows;
+    const LinearSeg *segs;
+    int32_t n_rt, add0, add1;
+};
+// y = x . Wt^T + adapter update for the rows of the list; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]
 // The tiles of the grid's last, partly filled round are split along k over several blocks as far as split_scratch
 // (device; LINEAR_SHARE_BYTES for every part of a tile) and split_state (device, zero between launches, one per split
@@ -364,7 +388,7 @@ struct SplitState {
     uint32_t started, way, arrived, read;  // parts that run, have left their sums, have read the others'; way: how the tile is finished
 };
 constexpr size_t LINEAR_SHARE_BYTES = (size_t)256 * 256 * sizeof(float);  // a tile's accumulators
-hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const DevItem *row_tiles, int n_rt, void *split_scratch,
+hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearList &list, void *split_scratch,
                                size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // a plan's work lists (bytes rounded up to 16) from pinned host memory as the device sees it to their place in the pool

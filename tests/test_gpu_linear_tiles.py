@@ -59,6 +59,55 @@ def test_linear_against_torch(lens, h_in, h_out):
         pool.close()
 
 
+@pytest.mark.parametrize("h_in,h_out", [(192, 320), (1024, 1088), (4096, 256)])
+@pytest.mark.parametrize("lens", [
+    [8, 9, 15, 16, 17, 1, 1, 1, 31, 33],             # several slots in a run and in a block of 16 rows, GEMV and plain rows behind them
+    [60, 8, 64, 8, 120, 1, 1],                       # segments that end one run and begin the next
+    [250, 12, 250, 1, 8, 8, 8, 8, 8, 8, 8, 8, 1],    # across a panel of 256 rows
+    [1] * 70 + [8],                                  # GEMV rows over two runs, the first beside a tile
+])
+def test_rows_of_several_slots(lens, h_in, h_out):
+    """Neighbouring segments differ in slot and rank (some no multiple of 8); the rows of the intermediate hold NaN behind their ranks."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    ranks = [5, 128, 33, 16, 100]
+    gen = torch.Generator(device="cuda").manual_seed(h_in + len(lens))
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    T = sum(lens)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ones = [i for i, n in enumerate(lens) if n == 1]
+    slot = np.asarray([i % 5 if n > 1 else 5 + ones.index(i) % 30 for i, n in enumerate(lens)], np.int32)  # one-token requests: at most three of a slot
+    slot[ones[1::7]] = -1
+    rank_of = np.asarray(ranks + [ranks[i % 5] for i in range(30)])
+    A, Bm = [normal(h_in, r, sigma=0.02) for r in rank_of], [normal(r, h_out, sigma=0.02) for r in rank_of]
+    x, wt = normal(T, h_in), normal(h_out, h_in, sigma=0.02)
+    pool = LoraPool([(h_in, h_out)], 1, [128], [35], B.LORA_BF16, max_tokens=T, max_segments=len(lens), mfma_min_tokens=8)
+    try:
+        pool.buf.fill_(0xFF)  # NaN in every word that is not written: the next pool takes the same memory, and what has to be zero there it clears
+        pool.close()
+        pool = LoraPool([(h_in, h_out)], 1, [128], [35], B.LORA_BF16, max_tokens=T, max_segments=len(lens), mfma_min_tokens=8)
+        for i, r in enumerate(rank_of):
+            pool.fill(i, i + 1, int(r), 0.5 + i % 3, 0, 0, A[i].cpu(), Bm[i].cpu())
+        plan = pool.plan(T, off, slot, np.where(slot >= 0, rank_of[slot], 0).astype(np.int32))
+        ref = x.double() @ wt.double().t()
+        for g, s in enumerate(slot):
+            if s >= 0:
+                a, b = int(off[g]), int(off[g + 1])
+                ref[a:b] += 2.0 * (0.5 + s % 3) * (x[a:b].double() @ A[s].double()) @ Bm[s].double()
+        space = torch.full((T * h_out,), float("nan"), dtype=torch.float32, device="cuda")
+        for _ in range(2):
+            y = torch.full((T, h_out), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.check(B.lora_linear_plan(pool.handle, plan, 0, 0, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0,
+                                       torch.cuda.current_stream().cuda_stream, space.data_ptr(), space.numel() * 4))
+            pool.check_fault()
+            err, rms = (y.double() - ref).abs(), ref.pow(2).mean().sqrt()
+            assert bool((err <= 2.0**-8 * ref.abs() + 2.0**-7 * rms).all()), float((err / rms).max())  # as above
+            assert float((y.double() - ref).norm() / ref.norm()) < 4e-3
+    finally:
+        pool.close()
+
+
 @pytest.mark.parametrize("T,h_in,h_out,tiles", [(300, 4096, 1024, 8), (700, 11008, 2304, 27), (1100, 4096, 4096, 80), (2048, 4096, 4096, 128)])
 def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
     """What happens when a part is done before another has started, forced from the host: the tiles' state (16 bytes each,
