@@ -87,12 +87,24 @@ struct LinearSplit {
     int32_t *fault;
 };
 
-// Tile number -> (row panel, column panel): groups of four row panels, column by column
-__device__ __forceinline__ void linear_tile(int t, int n_mt, int n_nt, int &bm, int &bn)
+// Tile number -> (row panel, column panel): groups of H row panels, column by column
+template <int H> __device__ __forceinline__ void linear_tile(int t, int n_mt, int n_nt, int &bm, int &bn)
 {
-    const int per = 4 * n_nt, grp = t / per, rem = t - grp * per, height = min(4, n_mt - 4 * grp);
+    const int per = H * n_nt, grp = t / per, rem = t - grp * per, height = min(H, n_mt - H * grp);
     bn = rem / height;
-    bm = 4 * grp + (rem - bn * height);
+    bm = H * grp + (rem - bn * height);
+}
+
+// 16 bytes a lane from memory to LDS: lane l's to to_lds (the same in all lanes) + 16 l
+__device__ __forceinline__ void request16(const __bf16 *from, unsigned char *to_lds)
+{
+    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
+}
+
+// Waits until at most N of the wavefront's vector-memory requests are outstanding
+template <int N> __device__ __forceinline__ void wait_requests()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 // A barrier alone: what must be complete at it has been waited for by count
@@ -110,9 +122,9 @@ __device__ __forceinline__ uint4 rank_mask(int n)
     auto word = [&](int j) { return n >= 2 * j + 2 ? 0xffffffffu : (n == 2 * j + 1 ? 0x0000ffffu : 0u); };
     return make_uint4(word(0), word(1), word(2), word(3));
 }
-__device__ __forceinline__ bf16x8 sv_operand(const unsigned char *p, const uint4 &live, bool row_in)
+__device__ __forceinline__ bf16x8 sv_operand(const uint4 &v, const uint4 &live, bool row_in)
 {
-    const uint4 v = *reinterpret_cast<const uint4 *>(p), z = make_uint4(0u, 0u, 0u, 0u);
+    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
     const uint4 f = make_uint4(v.x & live.x, v.y & live.y, v.z & live.z, v.w & live.w);
     return __builtin_bit_cast(bf16x8, row_in ? f : z);
 }
@@ -135,7 +147,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         tile_no = j * q + min(j, r) + ((int)blockIdx.x >> 3);
     }
     int bm, bn;
-    linear_tile(tile_no, n_mt, n_nt, bm, bn);
+    linear_tile<4>(tile_no, n_mt, n_nt, bm, bn);
     const int n0 = bn * LBN;
 
     // the two runs of 64 rows of this wavefront's row half (a missing one counts as empty)
@@ -181,7 +193,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         unsigned char *dst = half_at(buf, which) + 16 * w * LROW;
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-            __builtin_amdgcn_global_load_lds(src[q] + k, (__attribute__((address_space(3))) void *)(dst + q * 8 * LROW), 16, 0, 0);
+            request16(src[q] + k, dst + q * 8 * LROW);
     };
 
     floatx4 acc[8][4];  // [block of 16 rows][block of 16 columns]
@@ -408,7 +420,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 #pragma unroll
                 for (int mb = 0; mb < 8; ++mb) {
                     if (!owns(mb) || 16 * mb + 16 <= lo || 16 * mb >= hi) continue;  // uniform
-                    const bf16x8 so = sv_operand(svr + mb * 16 * SV_ROW + ks * 64, live, 16 * mb + m >= lo && 16 * mb + m < hi);
+                    const bf16x8 so = sv_operand(*reinterpret_cast<const uint4 *>(svr + mb * 16 * SV_ROW + ks * 64), live, 16 * mb + m >= lo && 16 * mb + m < hi);
 #pragma unroll
                     for (int nb = 0; nb < 4; ++nb)
                         acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
@@ -505,6 +517,279 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// The same for launches that tiles of 256 x 256 leave the chip idle with (417 x 2048 x 2048: 16 tiles, split along k into 128 blocks of
+// 4 stages whose hand-over took most of 27 us): blocks of 4 wavefronts on 64 RM rows x 64 columns, wavefront w on the row half w / 2
+// and the column half w % 2.  Stages of 64 k of both operands travel through a ring of NST, NST - 1 of them on their way (requests counted, as
+// above), one barrier per stage; two or three blocks share a compute unit, and one multiplies while another waits.  What bounds it:
+// with few blocks the trip to memory, 0.27 us a stage with three on their way; with many what the units take in, 15 to 19 TB/s
+// of tiles that are re-read by every row and column of tiles.  Measured, 256 x 256 tiles -> this kernel: 64 x 4096 x 4096 30.9 -> 12.3 us, 417 x 2048 x 2048
+// 27.5 -> 12.3, 992 x 1024 x 1024 26.2 -> 8.1, 2283 x 1088 x 1088 28.1 -> 14.4, 1234 x 2048 x 2048 30.3 -> 20.3 (128 rows), 785 x 2560 x 2560
+// 32.4 -> 23.3 (128 rows); 1000 x 4096 x 4096 46.7 and 48.2.  Stages of 128 k (whole 256-byte rows) took the same time, tiles of 64 x 128 up to
+// a fifth more than 128 x 64, 128 x 128 with four wavefronts half more.
+// ---------------------------------------------------------------------------------------
+template <int RM, int NST>
+__global__ __launch_bounds__(256) void linear_small_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt, LinearList list, int n_mt, int n_nt, LinearSplit sp)
+{
+    constexpr int BM = 64 * RM, BN = 64, MB = 2 * RM, NB = 2;  // MB, NB: blocks of 16 rows and columns of a wavefront
+    constexpr int STAGE = (BM + BN) * LROW, PER = 2 * (RM + 1);  // PER: requests of a wavefront per stage
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int wr = w >> 1, wc = w & 1;
+    // XCD j (blocks j, j + 8, ...) takes a run of consecutive (tile, part) pairs
+    const int n_pos = n_mt * n_nt * sp.parts, j8 = (int)blockIdx.x & 7, q8 = n_pos >> 3, r8 = n_pos & 7;
+    const int pos = j8 * q8 + min(j8, r8) + ((int)blockIdx.x >> 3);
+    const int tile_no = pos / sp.parts, part = pos - tile_no * sp.parts;
+    int bm, bn;
+    linear_tile<16 / RM>(tile_no, n_mt, n_nt, bm, bn);
+    const int n0 = bn * BN, row0 = bm * BM;
+
+    LinearRows run[RM];
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {
+        run[i] = list.rows[min(RM * bm + i, list.n_rt - 1)];
+        if (RM * bm + i >= list.n_rt) run[i].n_tok = run[i].n_segs = 0;
+    }
+    const int dead_tok = run[0].tok0;
+    const __bf16 *x = static_cast<const __bf16 *>(a.x);
+    __bf16 *y = static_cast<__bf16 *>(a.y);
+    const int n_k = a.h_in / LBK, k_lo = n_k * part / sp.parts, n_st = n_k * (part + 1) / sp.parts - k_lo;
+
+    // Loader: request q of wavefront w brings rows 8 (w + 4 q) + lane / 8 of x, then of Wt: 8 rows x 128 bytes, lane l to slot l % 8, for
+    // which it fetches piece (l % 8) ^ ((row / 2) % 8)
+    const int lr = lane >> 3, piece = (lane & 7) ^ ((4 * (w & 1) + (lr >> 1)) & 7);
+    const __bf16 *src[PER];
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {
+        const int ti[2] = {8 * w + lr, 8 * w + 32 + lr};
+        int tok[2];
+        tile_tokens_of(list.tok, run[i], ti, dead_tok, tok);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) src[2 * i + q] = x + (size_t)tok[q] * a.h_in + piece * 8 + (size_t)k_lo * LBK;
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) src[2 * RM + q] = Wt + (size_t)(n0 + 32 * q + 8 * w + lr) * a.h_in + piece * 8 + (size_t)k_lo * LBK;  // (h_out is a multiple of 64)
+    auto load_stage = [&](int st, int slot) {
+        const int k = min(st, n_st - 1) * LBK;
+        unsigned char *dst = lds + slot * STAGE + 8 * w * LROW;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            request16(src[q] + k, dst + 32 * q * LROW);
+    };
+
+    floatx4 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int swz = (m >> 1) & 7;
+    auto multiply = [&](int slot) {
+        const unsigned char *xs = lds + slot * STAGE + (32 * RM * wr + m) * LROW, *ws = lds + slot * STAGE + (BM + 32 * wc + m) * LROW;
+        bf16x8 xo[MB][2], wo[NB][2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = ((4 * ks + g) ^ swz) << 4;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) xo[mb][ks] = *reinterpret_cast<const bf16x8 *>(xs + mb * 16 * LROW + at);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) wo[nb][ks] = *reinterpret_cast<const bf16x8 *>(ws + nb * 16 * LROW + at);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[nb][ks], xo[mb][ks], acc[mb][nb], 0, 0, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read when this wavefront is at the next barrier
+    };
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) load_stage(s, s);
+    int slot = 0, fill = NST - 1;
+    for (int st = 0; st < n_st - (NST - 1); ++st) {
+        wait_requests<PER *(NST - 2)>();
+        section_end();
+        load_stage(st + NST - 1, fill);  // the slot read before the barrier
+        multiply(slot);
+        fill = slot;
+        slot = slot + 1 == NST ? 0 : slot + 1;
+    }
+    // the last stages, with nothing left to request
+    auto last = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;  // stages behind this one
+        if (n_st <= LEFT) return;
+        wait_requests<PER * LEFT>();
+        section_end();
+        multiply(slot);
+        slot = slot + 1 == NST ? 0 : slot + 1;
+    };
+    if constexpr (NST > 3) last(std::integral_constant<int, 2>{});
+    if constexpr (NST > 2) last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 0>{});
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();  // LDS is used for other things below
+
+    // ---- a tile split along k: every part but the last to arrive leaves its sums and ends; nobody waits
+    if (sp.parts > 1) {
+        SplitState *const st = sp.state + tile_no;
+        unsigned long long *const sums = sp.partial + (size_t)tile_no * sp.parts * (BM * BN / 2);
+        __shared__ uint32_t said;
+        if (tid == 0) said = __hip_atomic_load(&st->arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        bool all_in = said == (uint32_t)sp.parts - 1;
+        if (!all_in) {  // uniform
+            unsigned long long *const dst = sums + (size_t)part * (BM * BN / 2) + tid;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const floatx4 c = acc[mb][nb];
+                    const floatx2 lo = {c[0], c[1]}, hi = {c[2], c[3]};
+                    __hip_atomic_store(dst + ((mb * NB + nb) * 2 + 0) * 256, __builtin_bit_cast(unsigned long long, lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(dst + ((mb * NB + nb) * 2 + 1) * 256, __builtin_bit_cast(unsigned long long, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // performed where every XCD sees them
+            __syncthreads();
+            if (tid == 0) said = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            all_in = said == (uint32_t)sp.parts - 1;
+            if (!all_in) return;  // the whole block
+        }
+        floatx4 sum[MB][NB];  // in the order of the parts, whoever adds them up
+        for (int q = 0; q < sp.parts; ++q) {
+            floatx4 v[MB][NB];
+            if (q == part) {  // uniform
+#pragma unroll
+                for (int i = 0; i < MB * NB; ++i) v[i / NB][i % NB] = acc[i / NB][i % NB];
+            } else {
+                const unsigned long long *const from = sums + (size_t)q * (BM * BN / 2) + tid;
+                unsigned long long w8[MB * NB * 2];
+#pragma unroll
+                for (int i = 0; i < MB * NB * 2; ++i) w8[i] = __hip_atomic_load(from + i * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int i = 0; i < MB * NB * 2; ++i) {
+                    const floatx2 f = __builtin_bit_cast(floatx2, w8[i]);
+                    v[i / 2 / NB][i / 2 % NB][2 * (i & 1)] = f[0];
+                    v[i / 2 / NB][i / 2 % NB][2 * (i & 1) + 1] = f[1];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MB * NB; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[i / NB][i % NB][e] = q == 0 ? v[i / NB][i % NB][e] : sum[i / NB][i % NB][e] + v[i / NB][i % NB][e];
+        }
+#pragma unroll
+        for (int i = 0; i < MB * NB; ++i) acc[i / NB][i % NB] = sum[i / NB][i % NB];
+        if (tid == 0) {
+            __hip_atomic_store(&st->started, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->way, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&st->read, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // ---- the adapter slab and the terms of GEMV rows, as above, with the operands straight from memory.  Row block mb of the
+    // wavefront: rows 32 RM wr + 16 mb + m of the block
+    int tok[MB];
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {  // (RM 1: row blocks 32 wr .. of the one run; RM 2: run wr)
+        if (RM == 2 && i != wr) continue;  // uniform
+        int ti[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) ti[mb] = (RM == 1 ? 32 * wr : 0) + 16 * mb + m;
+        tile_tokens_of(list.tok, run[i], ti, dead_tok, tok);
+    }
+    const int wrow = row0 + 32 * RM * wr, col0 = n0 + 32 * wc;  // the wavefront's first row and column
+    const int seg0 = run[0].first_seg, seg1 = RM == 2 && run[RM - 1].n_segs > 0 ? run[RM - 1].first_seg + run[RM - 1].n_segs : seg0 + run[0].n_segs;
+    for (int s = seg0; s < seg1; ++s) {
+        const LinearSeg seg = list.segs[s];
+        const int lo = seg.r0 - wrow, hi = seg.r1 - wrow;
+        if (hi <= 0 || lo >= 32 * RM) continue;  // uniform
+        const int rs = rank_storage(seg.rank), rs8 = rs >> 3, ks32 = (seg.rank + 31) >> 5;
+        const __bf16 *Bp = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)seg.row * a.row_bytes) + (size_t)rs * a.h_in;
+#pragma unroll
+        for (int k0 = 0; k0 < 4; k0 += 2) {  // two k steps at a time
+            if (k0 >= ks32) continue;  // uniform
+            bf16x8 bo[2][NB];
+            uint4 vo[2][MB];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const int gran = 4 * (k0 + ks) + g;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(gran, rs8 - 1) * a.h_out + col0 + 16 * nb + m) * 8));
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    vo[ks][mb] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[mb] * (2 * a.v_stride) + gran * 8);
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const uint4 live = rank_mask(seg.rank - 32 * (k0 + ks) - 8 * g);
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const bf16x8 so = sv_operand(vo[ks][mb], live, 16 * mb + m >= lo && 16 * mb + m < hi);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
+                }
+            }
+        }
+    }
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    if (wrow < list.add1 && wrow + 32 * RM > list.add0) {  // uniform
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const int r = wrow + 16 * mb + m;
+            if (r < list.add0 || r >= list.add1) continue;
+            const size_t at = (size_t)tok[mb] * a.h_out + col0 + 4 * g;
+            floatx4 term[NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                if (a.y32) {
+                    term[nb] = *reinterpret_cast<const floatx4 *>(a.y32 + at + 16 * nb);
+                } else {
+                    const bf16x4 old = *reinterpret_cast<const bf16x4 *>(y + at + 16 * nb);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) term[nb][e] = (float)old[e];
+                }
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[mb][nb][e] += term[nb][e];
+        }
+    }
+    // ---- store: parked in LDS (row r: 16-byte slot s at s ^ ((r / 2) % 8)), then whole rows of the tile
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int row = 32 * RM * wr + 16 * mb + m;
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[mb][nb][e];
+            *reinterpret_cast<bf16x4 *>(lds + row * (2 * BN) + (((8 * wc + 4 * nb + g) ^ (((row >> 1) & 7) << 1)) << 3)) = o;
+        }
+    constexpr int PASSES = 2 * RM;  // 32 rows each, 8 lanes to a row
+    const int sl = tid & 7, rl = tid >> 3;
+    int tok8[PASSES];
+#pragma unroll
+    for (int i = 0; i < RM; ++i) {
+        const int ti[2] = {rl, rl + 32};
+        int tk[2];
+        tile_tokens_of(list.tok, run[i], ti, dead_tok, tk);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) tok8[2 * i + p] = ti[p] < run[i].n_tok ? tk[p] : -1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int row = 32 * p + rl;
+        const uint4 v = *reinterpret_cast<const uint4 *>(lds + row * (2 * BN) + ((sl ^ ((row >> 1) & 7)) << 4));
+        typedef unsigned u32x4_nt __attribute__((ext_vector_type(4)));
+        const u32x4_nt vn = {v.x, v.y, v.z, v.w};
+        if (tok8[p] >= 0) __builtin_nontemporal_store(vn, reinterpret_cast<u32x4_nt *>(y + (size_t)tok8[p] * a.h_out + n0 + 8 * sl));
+    }
+}
+
 // y[token][0 .. h_out) = 0 for the listed tokens (the rows the GEMV expand then adds its term to)
 __global__ __launch_bounds__(256) void zero_rows_kernel(__bf16 *__restrict__ y, const int32_t *__restrict__ toks, int n, int h_out)
 {
@@ -529,7 +814,7 @@ hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipS
 // and read past the caches) take 0.09 stages each at the 4.5 TB/s of memory.  (48 tiles of 64 stages behind a whole round: 45 us in five
 // parts, estimated 50; 136 tiles of 80 stages: 117 us in three parts, estimated 125, and whole 112, estimated 117.)
 // max_shares: what the scratch holds, in accumulator sets of a tile (LINEAR_SHARE_BYTES).
-static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares, int &parts, int &n_tail)
+static double linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares, int &parts, int &n_tail)
 {
     n_tail = n_tiles % n_cu;
     parts = 1;
@@ -539,6 +824,33 @@ static void linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shares
         if (p == 1 || t < best) best = t, parts = p;
     }
     if (parts == 1) n_tail = 0;
+    return 1.33 * (best + (double)(n_tiles / n_cu) * (n_k + 8));
+}
+
+// Tiles of 64 RM x 64 (linear_small_kernel), n_k stages: estimated microseconds with the k range in `parts` parts.  4 us for a block's start and end; the
+// stages of a block at 0.27 us (64 rows) or 0.38 us (128 rows), or the bytes the units take in at 16 and 15 TB/s; a split's hand-over.
+static double small_estimate(int n_tiles, int n_k, int rm, int parts)
+{
+    const double stage = rm == 1 ? 0.27 : 0.38, bytes = (double)n_tiles * n_k * 64 * (rm + 1) * LROW, rate = rm == 1 ? 16e6 : 15e6;
+    const double hand_over = parts == 1 ? 0.0 : 1.5 + 0.5 * parts + (double)n_tiles * (parts - 1) * 64 * rm * 64 * 8 / 4.5e6;
+    return 4.0 + std::max(stage * ((n_k + parts - 1) / parts), bytes / rate) + hand_over;
+}
+
+template <int RM, int NST>
+static hipError_t launch_small(const ApplyArgs &a, const void *Wt, const LinearList &list, int parts, void *split_scratch, SplitState *split_state,
+                               hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+{
+    constexpr int LDS = NST * 64 * (RM + 1) * LROW;
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_small_kernel<RM, NST>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int n_mt = (list.n_rt + RM - 1) / RM, n_nt = a.h_out / 64;
+    const LinearSplit sp{0, parts, static_cast<unsigned long long *>(split_scratch), split_state, nullptr};
+    launch_k(tm, done, LORA_K_LINEAR, linear_small_kernel<RM, NST>, dim3(n_mt * n_nt * parts), dim3(256), LDS, st, a, static_cast<const __bf16 *>(Wt), list, n_mt, n_nt, sp);
+    return hipGetLastError();
 }
 
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearList &list, void *split_scratch,
@@ -546,6 +858,20 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearL
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (list.n_rt <= 0) return hipSuccess;
+    const int n_k = a.h_in / LBK, n_mt = (list.n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
+    int parts, n_tail;
+    // (the estimate reads 15 to 25 % more than 256 x 256 tiles take where the other kernel comes near them)
+    const double big = 0.85 * linear_split_shape(n_tiles, n_k, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
+    const int tiles64 = list.n_rt * (a.h_out / 64), tiles128 = (list.n_rt + 1) / 2 * (a.h_out / 64);
+    int p64 = 1;
+    for (int p = 2; p <= MAX_PARTS && split_scratch && tiles64 <= n_split_state && 4 * p <= n_k && (size_t)tiles64 * p * 64 * 64 * 4 <= split_scratch_bytes; ++p)
+        if (small_estimate(tiles64, n_k, 1, p) < small_estimate(tiles64, n_k, 1, p64)) p64 = p;
+    const double t64 = small_estimate(tiles64, n_k, 1, p64), t128 = small_estimate(tiles128, n_k, 2, 1);
+    if (t64 <= big && t64 <= t128) {  // (a ring of four where all blocks fit side by side with it: 992 x 1024 x 1024 8.1 us, 8.8 with three; 2283 x 1088 x 1088 17.0, 14.4 with three)
+        if (tiles64 * p64 <= 2 * n_cu) return launch_small<1, 4>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
+        return launch_small<1, 3>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
+    }
+    if (t128 <= big) return launch_small<2, 3>(a, Wt, list, 1, split_scratch, split_state, st, tm, done);
     static bool attr_set = false;
     if (!attr_set) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_tiles_kernel),
@@ -553,9 +879,6 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearL
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int n_mt = (list.n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
-    int parts, n_tail;
-    linear_split_shape(n_tiles, a.h_in / LBK, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
     if (n_tail > n_split_state) parts = 1, n_tail = 0;
     const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;

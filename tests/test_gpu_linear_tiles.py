@@ -59,12 +59,13 @@ def test_linear_against_torch(lens, h_in, h_out):
         pool.close()
 
 
-@pytest.mark.parametrize("h_in,h_out", [(192, 320), (1024, 1088), (4096, 256)])
+@pytest.mark.parametrize("h_in,h_out", [(64, 64), (192, 320), (1024, 1088), (1536, 1536), (4096, 256), (4096, 4096)])  # 4096 -> 256: split tiles of 64 x 64
 @pytest.mark.parametrize("lens", [
     [8, 9, 15, 16, 17, 1, 1, 1, 31, 33],             # several slots in a run and in a block of 16 rows, GEMV and plain rows behind them
     [60, 8, 64, 8, 120, 1, 1],                       # segments that end one run and begin the next
     [250, 12, 250, 1, 8, 8, 8, 8, 8, 8, 8, 8, 1],    # across a panel of 256 rows
     [1] * 70 + [8],                                  # GEMV rows over two runs, the first beside a tile
+    [700, 13, 8, 400, 1, 1, 1],                      # 1536 -> 1536: tiles of 128 x 64, an odd number of runs
 ])
 def test_rows_of_several_slots(lens, h_in, h_out):
     """Neighbouring segments differ in slot and rank (some no multiple of 8); the rows of the intermediate hold NaN behind their ranks."""
