@@ -104,6 +104,7 @@ if not os.path.exists(LIB_PATH):
 _lib = ctypes.CDLL(LIB_PATH)
 
 _i32p = POINTER(c_int32)
+_i32a = c_void_p  # an int32 array by its address (see _ptr)
 _SIGS = {
     "lora_adapter_bytes": (c_size_t, [c_int32, c_int32, c_int32, c_int32]),
     "lora_cache_bytes_required": (c_size_t, [POINTER(lora_cache_config_t)]),
@@ -126,18 +127,18 @@ _SIGS = {
     "lora_cache_resident_bytes": (c_int, [c_void_p, POINTER(c_size_t)]),
     "lora_cache_trim": (c_int, [c_void_p, c_size_t, POINTER(c_int64), c_int32, _i32p]),
     "lora_cache_slab": (c_int, [c_void_p, c_int32, c_int32, c_int32, POINTER(c_void_p), POINTER(c_size_t)]),
-    "lora_index": (c_int, [c_int32, _i32p, _i32p, _i32p, c_int32, c_int32, POINTER(lora_worklists_t)]),
+    "lora_index": (c_int, [c_int32, _i32a, _i32a, _i32a, c_int32, c_int32, POINTER(lora_worklists_t)]),
     "lora_worklists_free": (None, [POINTER(lora_worklists_t)]),
-    "lora_plan_create": (c_int, [c_void_p, c_int32, _i32p, _i32p, _i32p, c_int32, c_void_p, POINTER(c_void_p)]),
+    "lora_plan_create": (c_int, [c_void_p, c_int32, _i32a, _i32a, _i32a, c_int32, c_void_p, POINTER(c_void_p)]),
     "lora_plan_destroy": (c_int, [c_void_p, c_void_p]),
     "lora_plan_info": (c_int, [c_void_p, POINTER(lora_plan_info_t)]),
-    "lora_plan_dump": (c_int, [c_void_p, c_void_p, c_int32, POINTER(lora_plan_unit_t), c_int32, _i32p, _i32p, c_int32, _i32p]),
+    "lora_plan_dump": (c_int, [c_void_p, c_void_p, c_int32, POINTER(lora_plan_unit_t), c_int32, _i32p, _i32a, c_int32, _i32p]),
     "lora_apply_plan": (c_int, [c_void_p, c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_float, c_void_p]),
     "lora_apply_plan_static": (c_int, [c_void_p, c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_float, c_void_p]),
     "lora_apply_plan_multi": (c_int, [c_void_p, c_void_p, POINTER(lora_apply_desc_t), c_int32, c_float, c_void_p]),
     "lora_linear_plan": (c_int, [c_void_p, c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_void_p, c_float, c_void_p, c_size_t, c_void_p]),
     "lora_linear_workspace_bytes": (c_int, [c_void_p, c_void_p, c_int32, POINTER(c_size_t)]),
-    "lora_apply": (c_int, [c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_int32, _i32p, _i32p, _i32p, c_int32, c_float, c_void_p]),
+    "lora_apply": (c_int, [c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_int32, _i32a, _i32a, _i32a, c_int32, c_float, c_void_p]),
     "lora_cache_set_fencing": (c_int, [c_void_p, c_int32]),
     "lora_cache_set_timing": (c_int, [c_void_p, c_int32]),
     "lora_cache_read_timing": (c_int, [c_void_p, POINTER(ctypes.c_double), POINTER(c_int64)]),
@@ -181,8 +182,9 @@ def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
-def _ptr(a: np.ndarray):
-    return a.ctypes.data_as(_i32p)
+def _ptr(a: np.ndarray) -> int:
+    """Address of an array's first element (a ctypes pointer made by numpy costs 2 us a piece, a tenth of a small batch's call)."""
+    return a.__array_interface__["data"][0]
 
 
 def make_config(proj: Sequence[Sequence[int]], n_layers: int, class_rank: Sequence[int], class_slots: Sequence[int],

@@ -4,7 +4,6 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
-#include <unordered_map>
 #include <vector>
 
 #include "lora_internal.h"
@@ -13,6 +12,29 @@ namespace {
 
 struct ShortSeg {
     int32_t slot, seg;
+};
+
+// slot -> rank, for the check that every segment of a slot names the same rank
+class RankOf {
+    std::vector<int32_t> slots_, ranks_;
+    size_t mask_;
+
+public:
+    explicit RankOf(int32_t n)
+    {
+        size_t cap = 16;
+        while (cap < 2 * (size_t)n) cap *= 2;
+        slots_.assign(cap, -1);
+        ranks_.resize(cap);
+        mask_ = cap - 1;
+    }
+    bool agrees(int32_t slot, int32_t rank)  // slot >= 0; the first rank of a slot is the one that counts
+    {
+        size_t i = (size_t)((uint32_t)slot * 0x9E3779B1u) & mask_;
+        while (slots_[i] >= 0 && slots_[i] != slot) i = (i + 1) & mask_;
+        if (slots_[i] < 0) slots_[i] = slot, ranks_[i] = rank;
+        return ranks_[i] == rank;
+    }
 };
 
 template <typename T> T *dup(const std::vector<T> &v)
@@ -40,19 +62,20 @@ extern "C" int lora_index(int32_t T, const int32_t *seg_offsets, const int32_t *
     if (n_seg > 0 && (!seg_slot || !seg_rank)) return LORA_E_INVAL;
     if (seg_offsets[0] != 0 || seg_offsets[n_seg] != T) return LORA_E_INVAL;
 
-    std::unordered_map<int32_t, int32_t> rank_of;
+    RankOf rank_of(n_seg);
     for (int32_t g = 0; g < n_seg; ++g) {
         if (seg_offsets[g + 1] < seg_offsets[g]) return LORA_E_INVAL;
         if (seg_slot[g] < 0) continue;
         if (seg_rank[g] < 1 || seg_rank[g] > LORA_MAX_RANK) return LORA_E_INVAL;
-        auto ins = rank_of.emplace(seg_slot[g], seg_rank[g]);
-        if (!ins.second && ins.first->second != seg_rank[g]) return LORA_E_INVAL;
+        if (!rank_of.agrees(seg_slot[g], seg_rank[g])) return LORA_E_INVAL;
     }
 
     const int32_t TM = LORA_TILE_TOKENS;
     std::vector<int32_t> tile_tok, group_tok;
     std::vector<lora_item_t> tiles, groups;
     std::vector<ShortSeg> shorts;
+    shorts.reserve((size_t)n_seg);
+    group_tok.reserve((size_t)std::min(T, 4096));
 
     // long segments become runs of tiles straight away; the rest is bucketed by slot
     for (int32_t g = 0; g < n_seg; ++g) {

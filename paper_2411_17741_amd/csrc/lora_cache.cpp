@@ -514,66 +514,68 @@ bool shrink_pieces_of(const lora::DevItem *tiles, int n_tiles, int quanta, Shrin
 // once, the write of the result); a stage of 128 k takes it 1.4 us at rank 16, 1.6 us at rank 32, 1.9 us at rank 64 and
 // 2.6 us at rank 128 when the launch is long (x arrives at the rate the memory gives, the higher ranks add their At
 // loads).  The result is flat around these weights: a fixed amount of 3 to 6 stages and a stage offset of 30 to 60
-// gave the same launch times to within 1 %.  For a cost limit the sequence is walked once, every run taking pieces until
-// the limit is reached; the smallest limit that needs no more than max_runs runs is found by bisection.
+// gave the same launch times to within 1 %.
+// Tables of few runs, long ones: for a cost limit the sequence is walked once, every run taking pieces until the limit is reached; the limit starts
+// at an equal share of everything and grows by half a part or one percent until max_runs suffice.  Tables of many runs, a few parts each: one pass, run r
+// starts where r equal shares of the cost are behind it.  (That way the long ones end a part later, prefill batch 228.3 -> 229.4 us; a search for the limit in
+// all seven tables of a plan took 40 to 100 us of the host.)
+constexpr int SHRINK_SEARCH_RUNS = 128;
 void build_shrink_runs(const lora::DevItem *tiles, int n_tiles, int quanta, int max_runs, ShrinkRuns &out)
 {
-    constexpr int64_t MINP = lora::SHRINK_MIN_PARTS, PIECE = 6 * (44 + LORA_TILE_TOKENS + 16);  // six stages at rank 16
-    std::vector<int64_t> weight((size_t)n_tiles);
-    int64_t total = 0, w_max = 1;
-    for (int t = 0; t < n_tiles; ++t) {
-        weight[t] = 44 + (int64_t)tiles[t].n_tok + lora::rank_storage(tiles[t].rank);  // rank 128 : rank 16 = 1.9
-        total += weight[t] * quanta + PIECE;
-        w_max = std::max(w_max, weight[t]);
-    }
-    // one walk: the number of runs; their starts go to `cuts` when given
-    auto walk = [&](int64_t limit, std::vector<lora::ShrinkCut> *cuts) -> int64_t {
-        int t = 0, q = 0;
-        int64_t runs = 0;
-        while (t < n_tiles) {
-            if (cuts) cuts->push_back(lora::ShrinkCut{t, q});
-            ++runs;
-            int64_t cost = 0;
-            bool first = true;
-            while (t < n_tiles) {
-                const int64_t w = weight[t], rem = quanta - q;
-                if (cost + w * rem + PIECE <= limit) {  // the rest of the tile
-                    cost += w * rem + PIECE;
-                    ++t, q = 0, first = false;
-                    continue;
-                }
-                int64_t parts = (limit - cost - PIECE) / w;  // what still fits (rounded towards zero: never negative parts >= MINP)
-                if (parts < MINP) {
-                    if (!first) break;  // the run ends on the tile boundary
-                    parts = MINP;       // a run takes something
-                }
-                if (rem - parts < MINP) ++t, q = 0;  // no slivers: the rest of the tile
-                else q += (int)parts;
-                break;
+    constexpr int MINP = lora::SHRINK_MIN_PARTS;
+    constexpr double PIECE = 6 * (44 + LORA_TILE_TOKENS + 16);  // six stages at rank 16
+    auto weight = [&](int t) { return 44.0 + tiles[t].n_tok + lora::rank_storage(tiles[t].rank); };  // rank 128 : rank 16 = 1.9
+    double total = 0;
+    for (int t = 0; t < n_tiles; ++t) total += weight(t) * quanta + PIECE;
+    const double part = (total - n_tiles * PIECE) / ((double)n_tiles * quanta);  // the average part's cost
+    if (max_runs > SHRINK_SEARCH_RUNS) {
+        const double share = total / max_runs;
+        out.cuts.assign(1, lora::ShrinkCut{0, 0});
+        double before = 0, w = weight(0);  // cost of the tiles before tile t, weight of tile t
+        for (int r = 1, t = 0; r < max_runs; ++r) {
+            const double goal = share * r;
+            while (t < n_tiles && before + w * quanta + PIECE <= goal) {
+                before += w * quanta + PIECE;
+                if (++t < n_tiles) w = weight(t);
             }
+            const lora::ShrinkCut at = out.cuts.back();
+            lora::ShrinkCut cut{t, t < n_tiles ? (int)((goal - before) / w) : 0};
+            if (cut.part < MINP) cut.part = 0;
+            if (cut.tile < at.tile || (cut.tile == at.tile && cut.part < at.part + MINP)) cut = lora::ShrinkCut{at.tile, at.part + MINP};  // a run takes something
+            if (quanta - cut.part < MINP) cut = lora::ShrinkCut{cut.tile + 1, 0};  // no slivers: the rest of the tile
+            if (cut.tile >= n_tiles) break;
+            out.cuts.push_back(cut);
         }
-        return runs;
-    };
-    int64_t lo = w_max * std::min<int64_t>(MINP, quanta) + PIECE, hi = std::max(total, lo);  // hi: one run takes everything
-    while (hi - lo > hi / 128) {  // to within 1 % of the smallest limit
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (walk(mid, nullptr) <= max_runs) hi = mid;
-        else lo = mid + 1;
-    }
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        out.cuts.clear();
-        // second attempt (never needed as far as the walk goes): whole tiles only, as many per run as it takes
-        int64_t used;
-        if (attempt == 0) used = walk(hi, &out.cuts);
-        else {
-            const int per_run = (n_tiles + max_runs - 1) / max_runs;
-            for (int t = 0; t < n_tiles; t += per_run) out.cuts.push_back(lora::ShrinkCut{t, 0});
-            used = (int64_t)out.cuts.size();
+    } else {
+        for (double limit = std::max((total + 0.5 * max_runs * PIECE) / max_runs, MINP * part + PIECE);; limit += std::max(0.01 * limit, 0.5 * part)) {
+            int t = 0, q = 0;
+            out.cuts.clear();
+            while (t < n_tiles && (int)out.cuts.size() < max_runs) {
+                out.cuts.push_back(lora::ShrinkCut{t, q});
+                double left = limit;
+                for (bool first = true; t < n_tiles; first = false) {
+                    const double w = weight(t), rest = w * (quanta - q) + PIECE;
+                    if (rest <= left) {  // the rest of the tile
+                        left -= rest;
+                        ++t, q = 0;
+                        continue;
+                    }
+                    int parts = left > PIECE ? (int)((left - PIECE) / w) : 0;  // what still fits
+                    if (parts < MINP) {
+                        if (!first) break;  // the run ends on the tile boundary
+                        parts = MINP;       // a run takes something
+                    }
+                    if (quanta - q - parts < MINP) ++t, q = 0;  // no slivers: the rest of the tile
+                    else q += parts;
+                    break;
+                }
+            }
+            if (t >= n_tiles) break;  // (the limit that takes everything in one run is reached in the end)
         }
-        out.n_runs = (int)((used + 7) / 8 * 8);
-        out.cuts.resize((size_t)out.n_runs + 1, lora::ShrinkCut{n_tiles, 0});
-        if (used <= max_runs && shrink_pieces_of(tiles, n_tiles, quanta, out)) return;
     }
+    out.n_runs = (int)((out.cuts.size() + 7) / 8 * 8);
+    out.cuts.resize((size_t)out.n_runs + 1, lora::ShrinkCut{n_tiles, 0});
+    if (!shrink_pieces_of(tiles, n_tiles, quanta, out)) out.n_runs = 0;  // (cannot happen: the cuts rise)
 }
 
 // Wide items (up to 16 rank rows and 8 or 16 tokens) from so many wide shrink items of a launch up, for several groups and for one:
@@ -700,61 +702,21 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // the projection).
     // Groups in order of rising rank, whatever the caller's slot numbering (measured on the decode configuration:
     // 10.0 us per layer, 10.5 us with the order reversed).
-    std::vector<lora::GemvItem> gs, ge;
-    std::vector<lora::GemvWideItem> wgs, wge;  // the same work as wide items
     std::vector<int> group_order((size_t)w.n_groups);
     for (int i = 0; i < w.n_groups; ++i) group_order[i] = i;
     std::stable_sort(group_order.begin(), group_order.end(),
                      [&](int x, int y) { return lora::rank_storage(w.groups[x].rank) < lora::rank_storage(w.groups[y].rank); });
+    // how many there are (they are written straight to the staged copy further down)
+    int64_t n_gs = 0, n_ge = 0, n_wgs = 0, n_wge = 0;
     for (int gi = 0; gi < w.n_groups; ++gi) {
-        const lora_item_t &gr = w.groups[group_order[gi]];
-        lora::GemvItem d;
-        d.row = c.slot_row[gr.slot];
-        d.rank = gr.rank;
-        d.alpha = c.slots[gr.slot].alpha;
-        const int32_t nc = lora::gemv_expand_width(gr.rank);
-        for (int pass = 0; pass < 2; ++pass)
-            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += lora::GEMV_BATCH) {
-                for (int t = 0; t < lora::GEMV_BATCH; ++t) d.tok[t] = b0 + t < gr.n_tok ? w.tok_list[gr.tok_off + b0 + t] : -1;
-                if (pass == 0) {
-                    for (int32_t j0 = 0; j0 < lora::rank_storage(gr.rank); j0 += lora::GEMV_SHRINK_ROWS) {
-                        d.a = lora::gemv_pack_shrink(j0);
-                        gs.push_back(d);
-                    }
-                } else {
-                    for (int32_t col = 0; col < lora::GEMV_SUPER_COLS; col += nc) {
-                        d.a = lora::gemv_pack_expand(col);
-                        ge.push_back(d);
-                    }
-                }
-            }
+        const int32_t n = w.groups[gi].n_tok, rank = w.groups[gi].rank, batches = (n + lora::GEMV_BATCH - 1) / lora::GEMV_BATCH;
+        n_gs += (int64_t)batches * (lora::rank_storage(rank) / lora::GEMV_SHRINK_ROWS);
+        n_ge += (int64_t)batches * (lora::GEMV_SUPER_COLS / lora::gemv_expand_width(rank));
+        n_wgs += wide_shrink_items(n, rank);
+        n_wge += (int64_t)((n + lora::GEMV_WIDE_TOKENS - 1) / lora::GEMV_WIDE_TOKENS) * (lora::GEMV_SUPER_COLS / lora::gemv_wide_width(rank));
     }
-    // (lora_apply's own plans serve one projection: no wide items where that would not take them)
-    int64_t n_wide = 0;
-    for (int gi = 0; gi < w.n_groups; ++gi) n_wide += wide_shrink_items(w.groups[gi].n_tok, w.groups[gi].rank);
-    const bool make_wide = c.dtype == LORA_BF16 && !c.small_scratch && (!p.internal || n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP);
-    for (int gi = 0; gi < w.n_groups && make_wide; ++gi) {
-        const lora_item_t &gr = w.groups[group_order[gi]];
-        lora::GemvWideItem d{};
-        d.row = c.slot_row[gr.slot];
-        d.rank = gr.rank;
-        d.alpha = c.slots[gr.slot].alpha;
-        for (int pass = 0; pass < 2; ++pass) {
-            const int32_t most = pass == 0 ? lora::GEMV_WIDE_SHRINK_TOKENS : lora::GEMV_WIDE_TOKENS;
-            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += most) {
-                d.n_tok = std::min(most, gr.n_tok - b0);
-                for (int t = 0; t < lora::GEMV_WIDE_TOKENS; ++t) d.tok[t] = w.tok_list[gr.tok_off + b0 + (t < d.n_tok ? t : 0)];
-                if (pass == 0) {
-                    for (d.a = 0; d.a < lora::rank_storage(gr.rank); d.a += lora::GEMV_WIDE_ROWS) wgs.push_back(d);
-                } else {
-                    for (int32_t col = 0; col < lora::GEMV_SUPER_COLS; col += lora::gemv_wide_width(gr.rank)) {
-                        d.a = lora::gemv_pack_expand(col);
-                        wge.push_back(d);
-                    }
-                }
-            }
-        }
-    }
+    // the same work as wide items (lora_apply's own plans serve one projection: none where that would not take them)
+    if (c.dtype != LORA_BF16 || c.small_scratch || (p.internal && n_wgs < GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) n_wgs = n_wge = 0;
     stamp(w.tiles, w.n_tiles);
     // the tile shrink's run tables
     ShrinkRuns shrink_runs[SHRINK_VARIANTS];
@@ -778,13 +740,13 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.T = T;
     p.n_tok_list = w.n_tok_list;
     p.n_tiles = w.n_tiles;
-    p.n_gs = (int32_t)gs.size();
-    p.n_ge = (int32_t)ge.size();
-    p.n_wgs = (int32_t)wgs.size();
-    p.n_wge = (int32_t)wge.size();
+    p.n_gs = (int32_t)n_gs;
+    p.n_ge = (int32_t)n_ge;
+    p.n_wgs = (int32_t)n_wgs;
+    p.n_wge = (int32_t)n_wge;
     p.off_tiles = align_up(sizeof(int32_t) * (size_t)w.n_tok_list);
     p.off_gs = p.off_tiles + align_up(sizeof(lora_item_t) * (size_t)w.n_tiles);
-    p.off_ge = p.off_gs + align_up(sizeof(lora::GemvItem) * gs.size());
+    p.off_ge = p.off_gs + align_up(sizeof(lora::GemvItem) * (size_t)n_gs);
     // the rows of lora_linear_plan (bf16 caches): tok_list, then the tokens that name no adapter
     std::vector<int32_t> lin_tok;
     std::vector<lora::LinearRows> lin_rows;
@@ -818,9 +780,9 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     }
     p.n_lin_rows = (int32_t)lin_rows.size();
     p.n_lin_segs = (int32_t)lin_segs.size();
-    p.off_wgs = p.off_ge + align_up(sizeof(lora::GemvItem) * ge.size());
-    p.off_wge = p.off_wgs + align_up(sizeof(lora::GemvWideItem) * wgs.size());
-    p.off_lin_tok = p.off_wge + align_up(sizeof(lora::GemvWideItem) * wge.size());
+    p.off_wgs = p.off_ge + align_up(sizeof(lora::GemvItem) * (size_t)n_ge);
+    p.off_wge = p.off_wgs + align_up(sizeof(lora::GemvWideItem) * (size_t)n_wgs);
+    p.off_lin_tok = p.off_wge + align_up(sizeof(lora::GemvWideItem) * (size_t)n_wge);
     p.off_lin_rows = p.off_lin_tok + align_up(sizeof(int32_t) * lin_tok.size());
     p.off_lin_segs = p.off_lin_rows + align_up(sizeof(lora::LinearRows) * lin_rows.size());
     size_t bytes = p.off_lin_segs + align_up(sizeof(lora::LinearSeg) * lin_segs.size());
@@ -854,11 +816,47 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     }
     std::memcpy(p.pinned, w.tok_list, sizeof(int32_t) * (size_t)w.n_tok_list);
     std::memcpy(p.pinned + p.off_tiles, w.tiles, sizeof(lora_item_t) * (size_t)w.n_tiles);
+    {
+        lora::GemvItem *gs = reinterpret_cast<lora::GemvItem *>(p.pinned + p.off_gs), *ge = reinterpret_cast<lora::GemvItem *>(p.pinned + p.off_ge);
+        lora::GemvWideItem *wgs = reinterpret_cast<lora::GemvWideItem *>(p.pinned + p.off_wgs), *wge = reinterpret_cast<lora::GemvWideItem *>(p.pinned + p.off_wge);
+        for (int gi = 0; gi < w.n_groups; ++gi) {
+            const lora_item_t &gr = w.groups[group_order[gi]];
+            const int32_t *toks = w.tok_list + gr.tok_off, row = c.slot_row[gr.slot];
+            const float alpha = c.slots[gr.slot].alpha;
+            lora::GemvItem d;
+            d.row = row, d.rank = gr.rank, d.alpha = alpha;
+            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += lora::GEMV_BATCH) {
+                for (int t = 0; t < lora::GEMV_BATCH; ++t) d.tok[t] = b0 + t < gr.n_tok ? toks[b0 + t] : -1;
+                for (int32_t j0 = 0; j0 < lora::rank_storage(gr.rank); j0 += lora::GEMV_SHRINK_ROWS) {
+                    d.a = lora::gemv_pack_shrink(j0);
+                    *gs++ = d;
+                }
+                for (int32_t col = 0, nc = lora::gemv_expand_width(gr.rank); col < lora::GEMV_SUPER_COLS; col += nc) {
+                    d.a = lora::gemv_pack_expand(col);
+                    *ge++ = d;
+                }
+            }
+            if (n_wgs == 0) continue;
+            lora::GemvWideItem wd{};
+            wd.row = row, wd.rank = gr.rank, wd.alpha = alpha;
+            auto take = [&](int32_t b0, int32_t most) {
+                wd.n_tok = std::min(most, gr.n_tok - b0);
+                for (int t = 0; t < lora::GEMV_WIDE_TOKENS; ++t) wd.tok[t] = toks[b0 + (t < wd.n_tok ? t : 0)];
+            };
+            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += lora::GEMV_WIDE_SHRINK_TOKENS) {
+                take(b0, lora::GEMV_WIDE_SHRINK_TOKENS);
+                for (wd.a = 0; wd.a < lora::rank_storage(gr.rank); wd.a += lora::GEMV_WIDE_ROWS) *wgs++ = wd;
+            }
+            for (int32_t b0 = 0; b0 < gr.n_tok; b0 += lora::GEMV_WIDE_TOKENS) {
+                take(b0, lora::GEMV_WIDE_TOKENS);
+                for (int32_t col = 0, nc = lora::gemv_wide_width(gr.rank); col < lora::GEMV_SUPER_COLS; col += nc) {
+                    wd.a = lora::gemv_pack_expand(col);
+                    *wge++ = wd;
+                }
+            }
+        }
+    }
     lora_worklists_free(&w);
-    if (!gs.empty()) std::memcpy(p.pinned + p.off_gs, gs.data(), sizeof(lora::GemvItem) * gs.size());
-    if (!ge.empty()) std::memcpy(p.pinned + p.off_ge, ge.data(), sizeof(lora::GemvItem) * ge.size());
-    if (!wgs.empty()) std::memcpy(p.pinned + p.off_wgs, wgs.data(), sizeof(lora::GemvWideItem) * wgs.size());
-    if (!wge.empty()) std::memcpy(p.pinned + p.off_wge, wge.data(), sizeof(lora::GemvWideItem) * wge.size());
     if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
     if (!lin_rows.empty()) std::memcpy(p.pinned + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
     if (!lin_segs.empty()) std::memcpy(p.pinned + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
