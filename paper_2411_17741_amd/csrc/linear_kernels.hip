@@ -828,10 +828,12 @@ static double linear_split_shape(int n_tiles, int n_k, int n_cu, size_t max_shar
 }
 
 // Tiles of 64 RM x 64 (linear_small_kernel), n_k stages: estimated microseconds with the k range in `parts` parts.  4 us for a block's start and end; the
-// stages of a block at 0.27 us (64 rows) or 0.38 us (128 rows), or the bytes the units take in at 16 and 15 TB/s; a split's hand-over.
-static double small_estimate(int n_tiles, int n_k, int rm, int parts)
+// stages of a block at 0.27 us (64 rows) or 0.38 us (128 rows), or the bytes the units take in, at a rate that falls where an XCD's L2 does not hold
+// `l2_bytes`, x and its eighth of Wt (785 x 2560 x 2560, 5.6 MB, 128 rows: 23.3 us; 686 x 3264 x 3264, 7.2 MB: 38.2 us); a split's hand-over.
+static double small_estimate(int n_tiles, int n_k, int rm, int parts, double l2_bytes)
 {
-    const double stage = rm == 1 ? 0.27 : 0.38, bytes = (double)n_tiles * n_k * 64 * (rm + 1) * LROW, rate = rm == 1 ? 16e6 : 15e6;
+    const bool fits = l2_bytes < 6.5e6;
+    const double stage = rm == 1 ? 0.27 : 0.38, bytes = (double)n_tiles * n_k * 64 * (rm + 1) * LROW, rate = rm == 1 ? (fits ? 16e6 : 14e6) : (fits ? 15e6 : 12e6);
     const double hand_over = parts == 1 ? 0.0 : 1.5 + 0.5 * parts + (double)n_tiles * (parts - 1) * 64 * rm * 64 * 8 / 4.5e6;
     return 4.0 + std::max(stage * ((n_k + parts - 1) / parts), bytes / rate) + hand_over;
 }
@@ -863,10 +865,11 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearL
     // (the estimate reads 15 to 25 % more than 256 x 256 tiles take where the other kernel comes near them)
     const double big = 0.85 * linear_split_shape(n_tiles, n_k, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
     const int tiles64 = list.n_rt * (a.h_out / 64), tiles128 = (list.n_rt + 1) / 2 * (a.h_out / 64);
+    const double l2_bytes = 2.0 * a.h_in * (64.0 * list.n_rt + a.h_out / 8);
     int p64 = 1;
     for (int p = 2; p <= MAX_PARTS && split_scratch && tiles64 <= n_split_state && 4 * p <= n_k && (size_t)tiles64 * p * 64 * 64 * 4 <= split_scratch_bytes; ++p)
-        if (small_estimate(tiles64, n_k, 1, p) < small_estimate(tiles64, n_k, 1, p64)) p64 = p;
-    const double t64 = small_estimate(tiles64, n_k, 1, p64), t128 = small_estimate(tiles128, n_k, 2, 1);
+        if (small_estimate(tiles64, n_k, 1, p, l2_bytes) < small_estimate(tiles64, n_k, 1, p64, l2_bytes)) p64 = p;
+    const double t64 = small_estimate(tiles64, n_k, 1, p64, l2_bytes), t128 = small_estimate(tiles128, n_k, 2, 1, l2_bytes);
     if (t64 <= big && t64 <= t128) {  // (a ring of four where all blocks fit side by side with it: 992 x 1024 x 1024 8.1 us, 8.8 with three; 2283 x 1088 x 1088 17.0, 14.4 with three)
         if (tiles64 * p64 <= 2 * n_cu) return launch_small<1, 4>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
         return launch_small<1, 3>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
