@@ -40,8 +40,22 @@ constexpr int SHRINK_BATCH_RUNS[] = {64, 32};
 constexpr int SHRINK_VARIANTS = SHRINK_VARIANT_BATCH + 2;
 constexpr int SHRINK_BATCH_BLOCKS = 1024;  // a batch's launch has at most this many blocks, where a table is small enough
 constexpr int N_LINEAR_SPLITS = 256;  // split tiles of lora_linear_plan (tiles of the last round: fewer than CUs)
-constexpr double TILE_PATH_FIXED_US = 25.0;          // what the three launches of the tile path cost beside their work
-constexpr double TILE_PATH_L2_BYTES_PER_US = 10e6;  // rate at which repeated passes over a slab come out of L2
+// What the tokens of an adapter cost on the GEMV path and on the tile path, in microseconds of one projection's call (`width`: h_in + h_out): fitted
+// to calls of one to four prompts of 16 to 2300 tokens at ranks 8 to 128 and widths of 1024 to 4096 (GEMV / tiles measured: 77 tokens of rank 32 at 4096 6.0 / 11.0 us,
+// 430 of rank 32 11.9 / 11.5, 430 of rank 128 28.2 / 13.6, 1000 of rank 32 at 1024 12.6 / 10.6, 2300 of rank 8 at 2048 15.9 / 13.7).  Launches with
+// enough work for wide items take 0.45 (rank 128) to 1.3 (rank 8) times what the items of four tokens take, which the first formula stands for.
+constexpr double GEMV_FIXED_US = 4.0, TILE_FIXED_US = 10.5;
+constexpr double TILE_BESIDE_GEMV_US = 3.0;  // more, where a GEMV launch runs as well (200 one-token requests beside prompts of 300 / 1000 / 2048 tokens, GEMV 22.2 / 28.4 / 53.8, with tiles 24.9 / 29.1 / 48.6 us)
+double gemv_tokens_us(int32_t n_tok, int32_t rank, double width, bool wide)
+{
+    const double k = width / 2048.0;
+    return (n_tok + 3) / 4 * (0.004 + 0.0037 * k + rank * (0.00067 + 0.00023 * k)) * (wide ? std::min(1.3, 0.4 + 7.0 / rank) : 1.0);
+}
+double tile_tokens_us(int32_t n_tok, int32_t rank, double width) { return n_tok * width * (3.0 / 7e6 + 5.4e-9 * rank); }
+// Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
+// 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond (7B mixed batch 2020 us, 2044 on one stream; 13B 918 and 908;
+// 64 requests beside a prompt of 100 tokens 40.6 and 18.3; 224 beside 13670 prompt tokens, eight projections, 815 and 811).
+constexpr double FORK_MIN_TILE_BYTES = 4e9;
 // Applies that run together in one batch each have their own copy of the intermediate (a set): as many sets as fit into
 // BATCH_SCRATCH_BYTES (0.2 % of the card's memory), a group's at least.  64 one-token requests: 4 MB for 64 sets.
 constexpr size_t BATCH_SCRATCH_BYTES = (size_t)512 << 20;
@@ -156,6 +170,8 @@ struct lora_plan {
     size_t off_wgs = 0, off_wge = 0;
     // for lora_linear_plan: the list of every token of the batch, its runs of rows and its segments (lora::LinearList)
     size_t off_lin_tok = 0, off_lin_rows = 0, off_lin_segs = 0;
+    size_t off_direct = 0;  // units of a short tile shrink (0 of them: too many for that)
+    int32_t n_direct = 0;
     int32_t n_lin_rows = 0, n_lin_segs = 0;
     std::vector<int32_t> slots;        // distinct slots the batch names
     std::vector<uint32_t> generations;  // their generation at plan time
@@ -319,6 +335,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
                  (c.dtype == LORA_BF16 ? align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
                                              align_up(sizeof(lora::LinearRows) * ((size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
                                              align_up(sizeof(lora::LinearSeg) * (size_t)c.max_segments) : 0) +
+                 (c.dtype == LORA_BF16 && !small_scratch ? align_up(sizeof(lora::DevItem) * lora::DIRECT_MAX_UNITS) : 0) +
                  n_tables * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
     // fill staging: a buffer takes parts of an adapter until STAGE_BYTES (or the largest adapter) are in it
     c.stage_cap = small_scratch ? align_up(max_part) + ALIGN : align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
@@ -626,28 +643,31 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     int rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, c.mfma_min, &w);
     if (rc != LORA_OK) return rc;
     p.mfma_min_used = c.mfma_min;
-    // With the threshold left to the library: the tile path costs three more launches per apply
-    // (about 25 us), which a batch with only a few hundred tile tokens (the pooled tokens of a few
-    // hot adapters in a decode batch) does not earn back -- as GEMV groups those tokens cost one
-    // more pass over their slab per 4 tokens, out of L2.  So: estimate that cost; below the fixed
-    // cost of the tile launches everything stays GEMV; else the batch pays for the tile launches
+    // With the threshold left to the library: the tile path costs two launches more per apply, which a batch with few tile tokens does
+    // not earn back.  So: what its tokens cost either way; below, everything stays GEMV; else the batch pays for the tile launches
     // anyway and smaller pools of tokens become tiles too.
     if (c.mfma_min_auto && w.n_tiles > 0) {
         double mean_width = 0;
         for (const auto &pr : c.proj) mean_width += (double)pr.h_in + pr.h_out;
         mean_width /= (double)c.proj.size();
-        std::unordered_map<int32_t, std::pair<int64_t, int32_t>> of_slot;  // slot -> (tile tokens, rank)
+        std::unordered_map<int32_t, std::pair<int32_t, int32_t>> of_slot;  // slot -> (tile tokens, rank)
         for (int i = 0; i < w.n_tiles; ++i) {
             auto &e = of_slot[w.tiles[i].slot];
             e.first += w.tiles[i].n_tok;
             e.second = w.tiles[i].rank;
         }
-        double extra_bytes = 0;
-        for (const auto &kv : of_slot)
-            extra_bytes += (double)((kv.second.first + lora::GEMV_BATCH - 1) / lora::GEMV_BATCH) * kv.second.second * mean_width * c.esize;
-        const double gemv_us = extra_bytes / TILE_PATH_L2_BYTES_PER_US;
+        const bool other = w.n_groups > 0;
+        double gemv_us = other ? 0.0 : GEMV_FIXED_US, tile_us = TILE_FIXED_US + (other ? TILE_BESIDE_GEMV_US : 0.0);
+        int64_t n_wide = 0;
+        for (int i = 0; i < w.n_groups; ++i) n_wide += wide_shrink_items(w.groups[i].n_tok, w.groups[i].rank);
+        for (const auto &kv : of_slot) n_wide += wide_shrink_items(kv.second.first, kv.second.second);
+        const bool wide = c.dtype == LORA_BF16 && !c.small_scratch && n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP;
+        for (const auto &kv : of_slot) {
+            gemv_us += gemv_tokens_us(kv.second.first, kv.second.second, mean_width, wide);
+            tile_us += tile_tokens_us(kv.second.first, kv.second.second, mean_width);
+        }
         lora_worklists_free(&w);
-        p.mfma_min_used = gemv_us < TILE_PATH_FIXED_US ? 0 : LORA_MFMA_MIN_TOKENS_MIXED;
+        p.mfma_min_used = gemv_us < tile_us ? 0 : LORA_MFMA_MIN_TOKENS_MIXED;
         rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, p.mfma_min_used, &w);
         if (rc != LORA_OK) return rc;
     }
@@ -718,6 +738,26 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // the same work as wide items (lora_apply's own plans serve one projection: none where that would not take them)
     if (c.dtype != LORA_BF16 || c.small_scratch || (p.internal && n_wgs < GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) n_wgs = n_wge = 0;
     stamp(w.tiles, w.n_tiles);
+    // the units of a short tile shrink
+    std::vector<lora::DevItem> direct;
+    if (w.n_tiles > 0 && !c.small_scratch) {
+        int64_t n = 0;
+        auto blocks = [](int32_t v, int32_t by) { return (v + by - 1) / by; };
+        for (int i = 0; i < w.n_tiles && n <= lora::DIRECT_MAX_UNITS; ++i) {
+            const lora::DevItem &t = reinterpret_cast<const lora::DevItem *>(w.tiles)[i];
+            n += blocks(t.n_tok, lora::DIRECT_TOKENS) * blocks(t.rank, lora::DIRECT_ROWS);
+        }
+        for (int i = 0; i < w.n_tiles && n <= lora::DIRECT_MAX_UNITS; ++i) {
+            const lora::DevItem &t = reinterpret_cast<const lora::DevItem *>(w.tiles)[i];
+            for (int32_t o = 0; o < t.n_tok; o += lora::DIRECT_TOKENS) {
+                lora::DevItem d = t;
+                d.tok_off += o;
+                d.n_tok = std::min(lora::DIRECT_TOKENS, t.n_tok - o);
+                d.tok0 = w.tok_list[d.tok_off];
+                for (d.a = 0; d.a < t.rank; d.a += lora::DIRECT_ROWS) direct.push_back(d);
+            }
+        }
+    }
     // the tile shrink's run tables
     ShrinkRuns shrink_runs[SHRINK_VARIANTS];
     {
@@ -785,7 +825,9 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.off_lin_tok = p.off_wge + align_up(sizeof(lora::GemvWideItem) * (size_t)n_wge);
     p.off_lin_rows = p.off_lin_tok + align_up(sizeof(int32_t) * lin_tok.size());
     p.off_lin_segs = p.off_lin_rows + align_up(sizeof(lora::LinearRows) * lin_rows.size());
-    size_t bytes = p.off_lin_segs + align_up(sizeof(lora::LinearSeg) * lin_segs.size());
+    p.off_direct = p.off_lin_segs + align_up(sizeof(lora::LinearSeg) * lin_segs.size());
+    p.n_direct = (int32_t)direct.size();
+    size_t bytes = p.off_direct + align_up(sizeof(lora::DevItem) * direct.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         p.shrink_runs[v] = shrink_runs[v].n_runs;
         p.shrink_pieces[v] = shrink_runs[v].any_pieces;
@@ -859,6 +901,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     lora_worklists_free(&w);
     if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
     if (!lin_rows.empty()) std::memcpy(p.pinned + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
+    if (!direct.empty()) std::memcpy(p.pinned + p.off_direct, direct.data(), sizeof(lora::DevItem) * direct.size());
     if (!lin_segs.empty()) std::memcpy(p.pinned + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         if (!shrink_runs[v].cuts.empty()) std::memcpy(p.pinned + p.off_cuts[v], shrink_runs[v].cuts.data(), sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
@@ -1821,6 +1864,9 @@ constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
 // The same for a batch, whose shrink blocks are long done when its expand blocks are dispatched: one launch up to the range of the
 // unit arithmetic (64 requests on 32 projections, 15808 items: 167 against 180 us; 512 requests, 91328 items: 792 against 803 us).
 constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
+// A tile-shrink launch runs as mfma_shrink_direct_kernel up to so many bytes taken in by its units (64 h_in each): 4000 tokens of ranks 8 to 128, 4096 wide, one
+// projection (0.2 GB) 33.3 us per call against 37.4 through the run table, two (0.4 GB) 53.8 and 56.3, eight (1.8 GB) 209 and 181; 2048 wide, eight (0.9 GB) 106 and 107.
+constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 800000000;
 // The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
 // rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
 // SHRINK_BATCH_BLOCKS blocks.
@@ -1833,8 +1879,8 @@ static int shrink_variant(const lora_plan_t *p, int n, int64_t vpart_rows, bool 
         if (p->shrink_runs[v] * n <= SHRINK_BATCH_BLOCKS && 2 * (int64_t)lora::SHRINK_SLOT_ROWS * p->shrink_runs[v] * n <= vpart_rows) return v;
     return SHRINK_VARIANT_BATCH + 1;
 }
-// The tile kernels' arguments but for the projections; n: how many there are.
-static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, const Scratch &sc, float scale, lora::TileBatch &tb)
+// The tile kernels' arguments but for the projections; n: how many there are, sum_h_in: the sum of their input widths.
+static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_t sum_h_in, const Scratch &sc, float scale, lora::TileBatch &tb)
 {
     if (n < 1 || n > lora::BATCH_MAX_PROJS || n > sc.n_sets) return LORA_E_INVAL;
     const int v = shrink_variant(p, n, sc.vpart_rows, sc.small);
@@ -1846,6 +1892,8 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, const 
     tb.v_stride = c->v_stride;
     tb.any_pieces = p->shrink_pieces[v] ? 1 : 0;
     tb.scale = scale;
+    tb.direct = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_direct);
+    tb.n_direct = p->n_direct * 2 * (lora::DIRECT_TOKENS + lora::DIRECT_ROWS) * sum_h_in <= DIRECT_SHRINK_MAX_BYTES ? p->n_direct : 0;
     tb.tiles = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_tiles);
     tb.cuts = reinterpret_cast<const lora::ShrinkCut *>(p->dev + p->off_cuts[v]);
     tb.sums = reinterpret_cast<const lora::ShrinkSum *>(p->dev + p->off_sums[v]);
@@ -2006,7 +2054,12 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
     lora::TileBatch tb;
-    if (const int rc_s = tile_setup(c, p, n, sc, scale, tb)) return rc_s;
+    int64_t sum_h_in = 0, sum_h_out = 0;
+    for (int i = 0; i < n; ++i) {
+        sum_h_in += c->proj[descs[i].proj].h_in;
+        sum_h_out += c->proj[descs[i].proj].h_out;
+    }
+    if (const int rc_s = tile_setup(c, p, n, sum_h_in, sc, scale, tb)) return rc_s;
     // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
     int n_groups = 0;
     uint8_t first[lora::BATCH_MAX_PROJS];
@@ -2020,10 +2073,11 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         }
     }
     // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
-    // scratch: when a batch has both, the GEMV launch goes to the cache's side stream, forked off here and
+    // scratch: when a batch has enough of both, the GEMV launch goes to the cache's side stream, forked off here and
     // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
     // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
-    const bool fork = p->n_tiles > 0 && p->n_gs > 0 && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
+    const double tile_bytes = (double)p->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
+    const bool fork = p->n_tiles > 0 && p->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
     hipStream_t gemv_st = st;
     if (fork) {
         HIP_TRY(hipEventRecord(c->ev_fork, st));
@@ -2181,7 +2235,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     const int32_t n_gemv_tok = p->n_tok_list - p->n_tile_tok;
     if (p->n_tiles > 0) {
         lora::TileBatch tb;
-        if (const int rc_s = tile_setup(c, p, 1, pool_scratch(c), scale, tb)) return rc_s;
+        if (const int rc_s = tile_setup(c, p, 1, a.h_in, pool_scratch(c), scale, tb)) return rc_s;
         tb.p[0] = bp;
         tb.group[0] = 1u << 8;
         HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));

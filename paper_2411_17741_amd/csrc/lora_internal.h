@@ -345,6 +345,10 @@ inline __host__ __device__ int32_t shrink_part_stage(int32_t part, int32_t quant
     return (int32_t)(((int64_t)part * n_st + quanta / 2) / quanta);
 }
 constexpr int SHRINK_STAGE_K = 128;
+// The tile shrink of a launch too short for runs (a few hundred tokens): a block per (projection, unit), a unit being 16 tokens of a
+// tile x 16 rank rows over the whole of h_in, so that nothing is left to add up.  A unit is a DevItem of its tokens with a = its first rank row.
+constexpr int DIRECT_TOKENS = 16, DIRECT_ROWS = 16;
+constexpr int DIRECT_MAX_UNITS = 2048;  // of a plan; with more it carries none
 // The projections one launch of the tile kernels serves, and the run table the shrink works through for each of them:
 // projections that read the same x are neighbours (a group); projection i's intermediate lies v_set floats behind that of
 // i - 1, its partial sums part_set floats (2 * n_runs slots of SHRINK_SLOT_ROWS rows).
@@ -356,6 +360,8 @@ struct TileBatchHead {
     int32_t any_pieces;       // some tile is worked on in pieces: the reduce launch is needed
     float scale;
     const DevItem *tiles;     // device, n_tiles
+    const DevItem *direct;    // device, n_direct units; n_direct = 0: the launch works through the run table
+    int32_t n_direct;
     const ShrinkCut *cuts;    // device, n_runs + 1
     const ShrinkSum *sums;    // device, n_tiles
     const int32_t *tok_list;  // device

@@ -341,6 +341,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// shrink of a short launch: a block of W wavefronts per (projection, unit of 16 tokens x 16 rank rows), the wavefronts split k.  With the
+// kernel above such a launch leaves every tile in pieces of a few stages, 9 to 12 us, and 4 to 6 us more to add them up; what it waits
+// for is the trip to memory, so here a wavefront keeps three stages of 64 k of its own on their way in LDS (requests that write LDS
+// themselves, waited for by count; 8 rows x 128 bytes each), meets no barrier before the end, and the block writes the result itself.
+// x is taken in once per 16 rank rows and At once per 16 tokens: for short launches only.
+// LDS rows of a stage as in linear_kernels.hip: 16-byte slot s of row r holds piece s ^ ((r / 2) % 8).
+// ---------------------------------------------------------------------------------------
+namespace {
+constexpr int DK = 64, DROW = DK * 2, DSTAGE = 32 * DROW, DRING = 4;  // 16 rows of x, 16 of At
+}  // namespace
+
+__device__ __forceinline__ void request_to_lds(const __bf16 *from, unsigned char *to_lds)  // lane l's 16 bytes to to_lds + 16 l
+{
+    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
+}
+template <int N> __device__ __forceinline__ void wait_for_all_but()  // the latest N requests
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <int N, int W>
+__global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArgs<N> tb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    // XCD j (blocks j, j + 8, ...) takes a run of consecutive (projection, unit) pairs
+    const int n = tb.n_direct * tb.n, j8 = (int)blockIdx.x & 7, pos = j8 * (n >> 3) + min(j8, n & 7) + ((int)blockIdx.x >> 3);
+    const int pj = pos / tb.n_direct;
+    const DevItem it = tb.direct[pos - pj * tb.n_direct];
+    const ApplyArgs a = tile_args(tb, pj);
+    const int rs = rank_storage(it.rank);
+    const __bf16 *At = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)it.row * a.row_bytes);
+    const int n_k = a.h_in / DK, k_lo = n_k * w / W, n_st = n_k * (w + 1) / W - k_lo;
+
+    const int lr = lane >> 3, ls = lane & 7;
+    const __bf16 *src[4];
+    {
+        const int ti[2] = {lr, 8 + lr};
+        int tok[2];
+        tile_tokens(a, it, ti, tok);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int piece = ls ^ ((4 * q + (lr >> 1)) & 7);
+            src[q] = static_cast<const __bf16 *>(a.x) + (size_t)tok[q] * a.h_in + (size_t)k_lo * DK + piece * 8;
+            src[2 + q] = At + (size_t)min(it.a + 8 * q + lr, rs - 1) * a.h_in + (size_t)k_lo * DK + piece * 8;  // rows past the stored rank: never written
+        }
+    }
+    unsigned char *const mine = ring + w * (DRING * DSTAGE);
+    auto request = [&](int st, int slot) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) request_to_lds(src[q] + st * DK, mine + slot * DSTAGE + q * 8 * DROW);
+    };
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int slot) {
+        const unsigned char *s = mine + slot * DSTAGE + m * DROW;
+        bf16x8 xo[2], ao[2];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = ((4 * ks + g) ^ ((m >> 1) & 7)) << 4;
+            xo[ks] = *reinterpret_cast<const bf16x8 *>(s + at);
+            ao[ks] = *reinterpret_cast<const bf16x8 *>(s + 16 * DROW + at);
+        }
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[ks], ao[ks], acc, 0, 0, 0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // read before the slot is requested again
+    };
+#pragma unroll
+    for (int s = 0; s < DRING - 1; ++s)
+        if (s < n_st) request(s, s);
+    int slot = 0;
+    for (int st = 0; st < n_st - (DRING - 1); ++st) {
+        request(st + DRING - 1, (slot + DRING - 1) % DRING);
+        wait_for_all_but<4 * (DRING - 1)>();
+        multiply(slot);
+        slot = (slot + 1) % DRING;
+    }
+    auto last = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;  // stages behind this one
+        if (n_st <= LEFT) return;
+        wait_for_all_but<4 * LEFT>();
+        multiply(slot);
+        slot = (slot + 1) % DRING;
+    };
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 0>{});
+    static_assert(DRING == 4, "the walk's last stages");
+
+    // add the wavefronts' sums (in a part of the ring that the wavefront alone has used); entry (token, rank row) of thread tid: token tid / 16, row tid % 16
+    float *const sums = reinterpret_cast<float *>(mine);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sums[(4 * g + r) * 16 + m] = acc[r];
+    __syncthreads();
+    if (tid >= 256) return;
+    const int ti = tid >> 4, jr = it.a + (tid & 15);
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < W; ++q) v += reinterpret_cast<const float *>(ring + q * (DRING * DSTAGE))[tid];
+    const int tix[1] = {ti};
+    int tok[1];
+    tile_tokens(a, it, tix, tok);
+    if (ti < it.n_tok && jr < it.rank) reinterpret_cast<__bf16 *>(a.v)[(size_t)tok[0] * (2 * a.v_stride) + jr] = (__bf16)(a.scale * it.alpha * v);
+}
+
 // V[token][0..rank) = sum over the tile's pieces of their partial sums, for the tiles worked on in pieces.
 // (Atomic adds into V instead cost about 30 us per launch: device-scope fp32 atomics execute at the memory side.)
 template <int N>
@@ -618,8 +724,29 @@ template <typename F> static void with_batch_size(const TileBatch &tb, F go)
 // k ranges are multiples of the 128-element stage.
 hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const KernelTimer *tm)
 {
-    if (batch.n_tiles <= 0 || batch.n <= 0 || batch.n_runs <= 0) return hipSuccess;
-    if (batch.n > BATCH_MAX_PROJS || batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
+    if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
+    if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
+    if (batch.n_direct > 0) {
+        hipError_t e = hipSuccess;
+        with_batch_size(batch, [&](const auto &tb) {
+            constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
+            auto go = [&](auto w_tag) {
+                constexpr int W = decltype(w_tag)::value, LDS = W * DRING * DSTAGE;
+                static bool attr_set = false;
+                if (!attr_set) {
+                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(mfma_shrink_direct_kernel<N, W>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+                    if (e != hipSuccess) return;
+                    attr_set = true;
+                }
+                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W>, dim3(tb.n_direct * tb.n), dim3(64 * W), LDS, st, tb);
+            };
+            if (tb.n_direct * tb.n <= 256) go(std::integral_constant<int, 8>{});  // (a block to a compute unit)
+            else go(std::integral_constant<int, 4>{});
+        });
+        return e != hipSuccess ? e : hipGetLastError();
+    }
+    if (batch.n_runs <= 0) return hipSuccess;
+    if (batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
     with_batch_size(batch, [&](const auto &tb) {
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
         launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), 0, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
