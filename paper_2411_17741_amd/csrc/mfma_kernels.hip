@@ -504,14 +504,15 @@ __global__ __launch_bounds__(256) void mfma_reduce_kernel(TileBatchArgs<N> tb)
 // 16 bytes of each of many rows, and every 128-byte line would be fetched by two instructions,
 // which stalls L1 on the second): the wavefront parks its fp32 products in LDS and goes over
 // base_out with 8 lanes per token row, whole 128-byte lines per instruction, for the load (issued
-// one pass ahead), the add and the store.
-// Register use of a group's launch is held to three blocks per CU (the V operands are re-read from LDS in every pass
-// rather than kept): with two, short launches of a few hundred blocks leave CUs idle at the end (one prompt of 700 tokens,
-// call by call: 391 us instead of 371).  A batch's launch is long and takes two blocks per CU: fewer rows of base_out are in flight at
-// once, and memory serves them faster (13B mixed batch 922 -> 862 us).
+// three passes ahead), the add and the store.
+// A compute unit holds two blocks and asks for 8 wavefronts x three passes x 4 KB of base_out ahead of what it is adding to (one pass ahead, 32 KB, is less than
+// the rate of the memory times its latency), and a wavefront asks for nothing past its run: its place on the unit is held until the last answer is there.
+// Measured on the 7B mixed batch (one pass ahead and on past the run 2003 us): the requests past the run left out 1911, two passes ahead 1890, three 1866, four 1860;
+// the prefill batch 234, 223, 221, 219; a prompt of 1200 tokens projection by projection 391 -> 365 (three blocks per unit there before).
 // ---------------------------------------------------------------------------------------
 namespace {
 constexpr int CS_ROW = 64 * 4 + 16;  // bytes per token row of a wavefront's parked products (padded)
+constexpr int AHEAD = 3;             // passes of base_out on their way (the loop below is written for it)
 }
 
 // KS: MFMA k steps of 32 ranks.  As in the shrink, global loads are unconditional from clamped
@@ -573,8 +574,10 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
             for (int b = 0; b < 4; ++b) d[ks][b] = *reinterpret_cast<const uint4 *>(bg[ks] + (size_t)(nw0 + 16 * b) * 8);
     };
 
-    uint4 yr[2][4];
+    uint4 yr[AHEAD + 1][4];
     uint4 br[KS][4];
+    // columns past h_out: this wavefront's share of the block ends
+    const int my_pass = min(n_pass, (a.h_out - col0 + 127) / 128);
 
     // stage s.V (written as bf16 by the shrink or the reduce): vs[token][rank].  A thread's KS pieces (8 ranks of one
     // token each) are all requested before the first is used: taken one after the other, each with its own trip to
@@ -597,6 +600,9 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
         __builtin_amdgcn_sched_barrier(0);  // keep the scheduler from trading loads in flight for registers
         load_y(0, yr[0]);
         load_b(min(col0, a.h_out - 64), br);
+#pragma unroll
+        for (int p = 1; p < AHEAD; ++p)
+            if (p < my_pass) load_y(p, yr[p]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
@@ -613,12 +619,12 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
     if (!half_live) return;  // this token half is empty (no barrier follows)
     unsigned char *my_cs = cs[w];
 
-    // one pass of 128 columns; PAR = cp % 2 is a compile-time constant so that the base_out double
-    // buffer stays in registers
-    auto pass = [&](auto par_tag, int cp) {
-        constexpr int PAR = decltype(par_tag)::value;
+    // one pass of 128 columns; AT = cp % (AHEAD + 1) is a compile-time constant so that the base_out buffers
+    // stay in registers
+    auto pass = [&](auto at_tag, int cp) {
+        constexpr int AT = decltype(at_tag)::value;
         const int nw0 = col0 + cp * 128;
-        load_y(cp + 1, yr[PAR ^ 1]);  // next pass's base_out, ahead of this pass's products
+        if (cp + AHEAD < my_pass) load_y(cp + AHEAD, yr[(AT + AHEAD) % (AHEAD + 1)]);  // ahead of this pass's products
 
         floatx4 acc[4][2];
 #pragma unroll
@@ -635,7 +641,7 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
                 acc[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, b0, acc[b][0], 0, 0, 0);
                 acc[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, b1, acc[b][1], 0, 0, 0);
             }
-        load_b(min(nw0 + 128, a.h_out - 64), br);  // next pass's Bp, into the registers just used
+        if (cp + 1 < my_pass) load_b(min(nw0 + 128, a.h_out - 64), br);  // next pass's Bp, into the registers just used
 
         // park the products: lane (g, m) holds, for block b and token block tb, columns 16b + 4g .. +3 of token 16tb + m
 #pragma unroll
@@ -651,7 +657,7 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
             const float4 p1 = *reinterpret_cast<const float4 *>(&my_cs[(8 * i + rt) * CS_ROW + rc * 32 + 16]);
             float f[8];
             Chunk<__bf16> c;
-            c.v = yr[PAR][i];
+            c.v = yr[AT][i];
             unpack_chunk(c, f);
             bf16x8 o;
             o[0] = (__bf16)(f[0] + p0.x); o[1] = (__bf16)(f[1] + p0.y); o[2] = (__bf16)(f[2] + p0.z); o[3] = (__bf16)(f[3] + p0.w);
@@ -661,11 +667,15 @@ __device__ __forceinline__ void mfma_expand_body(const ApplyArgs &a, const DevIt
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();  // the next pass overwrites the parked products
     };
-    // columns past h_out: this wavefront's share of the block ends (the loads ahead were clamped)
-    const int my_pass = min(n_pass, (a.h_out - col0 + 127) / 128);
-    for (int cp = 0; cp < my_pass; cp += 2) {
+    for (int cp = 0;; cp += AHEAD + 1) {
+        if (cp >= my_pass) break;
         pass(std::integral_constant<int, 0>{}, cp);
-        if (cp + 1 < my_pass) pass(std::integral_constant<int, 1>{}, cp + 1);
+        if (cp + 1 >= my_pass) break;
+        pass(std::integral_constant<int, 1>{}, cp + 1);
+        if (cp + 2 >= my_pass) break;
+        pass(std::integral_constant<int, 2>{}, cp + 2);
+        if (cp + 3 >= my_pass) break;
+        pass(std::integral_constant<int, 3>{}, cp + 3);
     }
 }
 
@@ -680,7 +690,7 @@ template <int N> struct ExpandShape {
     int32_t runs[N];     // per projection: passes of 128 columns per run | blocks per tile (a multiple of 8) << 8
 };
 template <int N>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(N > GROUP_MAX_PROJS ? 2 : 3, N > GROUP_MAX_PROJS ? 2 : 3))) void mfma_expand_kernel(TileBatchArgs<N> tb, ExpandShape<N> sh)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_expand_kernel(TileBatchArgs<N> tb, ExpandShape<N> sh)
 {
     __shared__ __attribute__((aligned(16))) unsigned char vs[LORA_TILE_TOKENS * VS_ROW];
     __shared__ __attribute__((aligned(16))) unsigned char cs[4][32 * CS_ROW];
@@ -756,9 +766,8 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
     return hipGetLastError();
 }
 
-// Longest column run, in passes: in a batch eight runs to a tile whenever that is possible -- one per XCD -- (7B mixed batch 2056 us
-// with 8 passes, 2005 with 16; 13B 862 and 832), in a group's launch, which a few tiles have to spread over the chip, shorter.
-constexpr int EXPAND_PASSES_BATCH = 16, EXPAND_PASSES_GROUP = 8;
+// Longest column run, in passes (7B mixed batch 1898 us with 4, 1866 with 8, 1887 with 16).
+constexpr int EXPAND_PASSES = 8;
 hipError_t launch_mfma_expand(const TileBatch &batch, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
@@ -766,7 +775,7 @@ hipError_t launch_mfma_expand(const TileBatch &batch, hipStream_t st, const Kern
     // blocks per tile: the multiple of 8 that keeps a run within the limit; shorter runs (at least two passes) where that leaves the launch below 512 blocks (two per CU)
     int32_t shape[BATCH_MAX_PROJS];
     int64_t total = 0;
-    for (int passes = batch.n > GROUP_MAX_PROJS ? EXPAND_PASSES_BATCH : EXPAND_PASSES_GROUP;; passes >>= 1) {
+    for (int passes = EXPAND_PASSES;; passes >>= 1) {
         int64_t live = 0;
         total = 0;
         for (int i = 0; i < batch.n; ++i) {
