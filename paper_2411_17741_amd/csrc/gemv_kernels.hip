@@ -451,8 +451,8 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
     __shared__ float red[4][16];
     __shared__ __attribute__((aligned(16))) uint32_t stage[4][sizeof(E) == 2 ? TB * 64 : TB * 128];
     const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
-    auto use = [&](uint32_t proj) {
-        const BatchProj &q = b.p[proj];
+    auto use = [&](uint32_t proj, uint32_t &first_super) {
+        const BatchProj q = gemv_entry_proj(b.p[proj], first_super);
         return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * (int64_t)sizeof(E), static_cast<const char *>(q.x), static_cast<char *>(q.y), nullptr,
                        b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
     };
@@ -460,7 +460,8 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
         uint32_t item, proj;
         gemv_batch_shrink(blockIdx.x, b.m, proj, item);
         if (item >= b.m.n_gs) return;
-        gemv_shrink_work<E>(use(proj), load_item(b.gs + item), red);
+        uint32_t first;
+        gemv_shrink_work<E>(use(proj, first), load_item(b.gs + item), red);
     } else {
         if (b.m.phase == 1) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -468,8 +469,9 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
         if (unit >= b.m.n_units) return;
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
-        const uint32_t s = gemv_super(b.supers, super);
-        gemv_expand_work<E>(use(s & 0xffu), load_item(b.ge + item), s >> 8, stage[w]);
+        uint32_t first;
+        const GemvUse a = use(gemv_super(b.supers, super), first);
+        gemv_expand_work<E>(a, load_item(b.ge + item), super - first, stage[w]);
     }
 }
 
@@ -711,8 +713,8 @@ __global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[WIDE_LDS];
     const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
-    auto use = [&](uint32_t proj) {
-        const BatchProj &q = b.p[proj];
+    auto use = [&](uint32_t proj, uint32_t &first_super) {
+        const BatchProj q = gemv_entry_proj(b.p[proj], first_super);
         return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * 2, static_cast<const char *>(q.x), static_cast<char *>(q.y), b.y32,
                        b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
     };
@@ -722,7 +724,8 @@ __global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
         if (item >= b.m.n_gs) return;
         const GemvWideItem *p = b.wgs + item;
         const ItemW it = load_wide(p);
-        const GemvUse a = use(proj);
+        uint32_t first;
+        const GemvUse a = use(proj, first);
         const bool q4 = gemv_wide_rows(it.rank, it.a) == GEMV_WIDE_ROWS;  // uniform over the block, as n_tok
         if (it.n_tok == 1) q4 ? gemv_wide_shrink<1, 4>(a, it, p, lds) : gemv_wide_shrink<1, 2>(a, it, p, lds);
         else if (it.n_tok == 2) q4 ? gemv_wide_shrink<2, 4>(a, it, p, lds) : gemv_wide_shrink<2, 2>(a, it, p, lds);
@@ -735,12 +738,12 @@ __global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
         if (unit >= b.m.n_units) return;
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
-        const uint32_t s = gemv_super(b.supers, super);
+        uint32_t first;
+        const GemvUse a = use(gemv_super(b.supers, super), first);
         const GemvWideItem *p = b.wge + item;
         const ItemW it = load_wide(p);
-        const GemvUse a = use(s & 0xffu);
         int c0, c1;
-        gemv_wide_cols(it.rank, it.a, (int)(s >> 8), a.h_out, c0, c1);
+        gemv_wide_cols(it.rank, it.a, (int)(super - first), a.h_out, c0, c1);
         if (c0 >= c1) return;
         uint32_t *vb = reinterpret_cast<uint32_t *>(lds) + w * GEMV_WIDE_TOKENS * WIDE_V_ROW;
         const int rs8 = rank_storage(it.rank) >> 3;  // uniform over the wavefront

@@ -346,7 +346,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
     c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
-    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>(lora::BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
+    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>(lora::GEMV_BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
                                      std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / (c.v_set_bytes + c.vtag_set_bytes)));
     cur += c.v_set_bytes * c.n_sets;
     // partial sums of the tile shrink: two slots per run and projection; a launch has at most SHRINK_MAX_RUNS blocks
@@ -1611,8 +1611,9 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out)
 static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
 
 // Block and unit numbers of a batch's GEMV launch for n projections, h_out[i] wide, with a plan's items or its wide items;
-// shared by the launch and lora_plan_dump.  `supers` comes in zeroed.
-static int gemv_batch_map(const lora_plan_t *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 2])
+// shared by the launch and lora_plan_dump.  `supers` comes in zeroed; first[i]: number of projection i's first super-chunk.
+static int gemv_batch_map(const lora_plan_t *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 4],
+                          uint32_t (&first)[lora::GEMV_BATCH_MAX_PROJS])
 {
     m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
     m.n_ge = (uint32_t)(wide ? p->n_wge : p->n_ge);
@@ -1624,9 +1625,10 @@ static int gemv_batch_map(const lora_plan_t *p, bool wide, int n, const int32_t 
     int32_t n_super = 0;
     for (int i = 0; i < n; ++i) {
         if (supers_of(h_out[i]) > 255) return LORA_E_INVAL;  // as a group's launch
+        first[i] = (uint32_t)n_super;
         for (int32_t k = 0; k < supers_of(h_out[i]); ++k, ++n_super) {
             if (n_super >= lora::GEMV_BATCH_MAX_SUPERS) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
-            supers[n_super >> 1] |= ((uint32_t)i | (uint32_t)k << 8) << (16 * (n_super & 1));
+            supers[n_super >> 2] |= (uint32_t)i << (8 * (n_super & 3));
         }
     }
     const int64_t units = (int64_t)m.n_ge * n_super;
@@ -1647,6 +1649,7 @@ static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_p
 {
     int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
     if (p->n_tiles > 0) {
+        projs = std::min<int64_t>(projs, lora::BATCH_MAX_PROJS);
         projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
         projs = std::max<int64_t>(projs, lora::GROUP_MAX_PROJS);  // (up to a group's size there are tables of their own)
     }
@@ -1769,7 +1772,7 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     const lora::GemvWideItem *wgs = reinterpret_cast<const lora::GemvWideItem *>(buf + p->off_wgs);
     const lora::GemvWideItem *wge = reinterpret_cast<const lora::GemvWideItem *>(buf + p->off_wge);
     const int32_t n_proj = (int32_t)c->proj.size();
-    int32_t widths[lora::BATCH_MAX_PROJS], entries = 0, supers_left, max_entries;
+    int32_t widths[lora::GEMV_BATCH_MAX_PROJS], entries = 0, supers_left, max_entries;
     batch_limits(p, pool_scratch(c), max_entries, supers_left);
     for (; entries < std::min(max_entries, std::min(c->n_layers, 2) * n_proj); ++entries) {
         widths[entries] = c->proj[entries % n_proj].h_out;
@@ -1778,8 +1781,8 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     }
     for (int wide = 0; wide < 2; ++wide) {
         lora::GemvBatchMap m{};
-        uint32_t supers[lora::GEMV_BATCH_MAX_SUPERS / 2] = {0};
-        if ((wide ? p->n_wgs : p->n_gs) == 0 || entries == 0 || gemv_batch_map(p, wide != 0, entries, widths, m, supers)) continue;
+        uint32_t supers[lora::GEMV_BATCH_MAX_SUPERS / 4] = {0}, first[lora::GEMV_BATCH_MAX_PROJS];
+        if ((wide ? p->n_wgs : p->n_gs) == 0 || entries == 0 || gemv_batch_map(p, wide != 0, entries, widths, m, supers, first)) continue;
         auto put = [&](int32_t kind, const lora::GemvItem *it, const lora::GemvWideItem *w, int32_t lo, int32_t hi, uint32_t e) {
             const int32_t off = nt;
             int32_t cnt = w ? w->n_tok : gemv_tokens(*it);
@@ -1801,8 +1804,11 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
         for (uint32_t u = 0; u < m.n_units; ++u) {
             uint32_t super, item;
             lora::gemv_batch_unit(u, m, super, item);
-            const uint32_t e = lora::gemv_super(supers, super) & 0xffu, sc = lora::gemv_super(supers, super) >> 8;
+            uint32_t e = lora::gemv_super(supers, super), sc;
             if ((int32_t)e % n_proj != proj) continue;
+            const lora::BatchProj q = lora::gemv_entry_proj(lora::gemv_entry({nullptr, nullptr, nullptr, c->proj[proj].h_in, widths[e]}, first[e]), sc);
+            sc = super - sc;
+            if (q.h_out != h_out) continue;  // (what the kernels decode is this projection's width)
             int32_t c0, c1;
             if (wide) lora::gemv_wide_cols(wge[item].rank, wge[item].a, (int32_t)sc, h_out, c0, c1);
             else lora::gemv_expand_cols(ge[item], (int32_t)sc, h_out, c0, c1);
@@ -2011,12 +2017,11 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
     const bool wide = gemv_wide(c, p, projs, n, n_groups);
     b.wgs = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wgs);
     b.wge = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wge);
-    int32_t widths[lora::BATCH_MAX_PROJS];
-    for (int i = 0; i < n; ++i) {
-        b.p[i] = projs[i];
-        widths[i] = projs[i].h_out;
-    }
-    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.supers)) return rc;
+    int32_t widths[lora::GEMV_BATCH_MAX_PROJS];
+    uint32_t first[lora::GEMV_BATCH_MAX_PROJS];
+    for (int i = 0; i < n; ++i) widths[i] = projs[i].h_out;
+    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.supers, first)) return rc;
+    for (int i = 0; i < n; ++i) b.p[i] = lora::gemv_entry(projs[i], first[i]);
     if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_BATCH_ITEMS)) {
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         b.epoch = ++*sc.epoch;
@@ -2059,17 +2064,19 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         sum_h_in += c->proj[descs[i].proj].h_in;
         sum_h_out += c->proj[descs[i].proj].h_out;
     }
-    if (const int rc_s = tile_setup(c, p, n, sum_h_in, sc, scale, tb)) return rc_s;
+    if (p->n_tiles > 0)
+        if (const int rc_s = tile_setup(c, p, n, sum_h_in, sc, scale, tb)) return rc_s;
     // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
     int n_groups = 0;
-    uint8_t first[lora::BATCH_MAX_PROJS];
+    uint8_t first[lora::GEMV_BATCH_MAX_PROJS];
+    lora::BatchProj projs[lora::GEMV_BATCH_MAX_PROJS];
     for (int i = 0; i < n; i += group_n[i]) first[n_groups++] = (uint8_t)i;
     std::stable_sort(first, first + n_groups, [&](uint8_t g, uint8_t h) { return c->proj[descs[g].proj].h_in > c->proj[descs[h].proj].h_in; });
     for (int g = 0, i = 0; g < n_groups; ++g) {
         const int size = group_n[first[g]], at = i;
         for (int k = 0; k < size; ++k, ++i) {
-            tb.p[i] = batch_proj(c, descs[first[g] + k]);
-            tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
+            projs[i] = batch_proj(c, descs[first[g] + k]);
+            if (p->n_tiles > 0) tb.p[i] = projs[i], tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
         }
     }
     // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
@@ -2106,12 +2113,12 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
     const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, tb.p, n, 1) ? enqueue_gemv(c, p, tb.p, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
-                                       : enqueue_gemv_batch(c, p, tb.p, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
+    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, projs, n, 1) ? enqueue_gemv(c, p, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
+                                       : enqueue_gemv_batch(c, p, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
     // the updates of base_out
-    HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
+    if (p->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
     for (int i = 0; i < n; ++i) {
         const int64_t seq = ++c->apply_seq;
         ++c->stats.applies;
@@ -2286,8 +2293,8 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         bool meets(const Range &o) const { return lo < o.hi && o.lo < hi; }
     };
     const size_t e = c->esize;
-    Range in[lora::BATCH_MAX_PROJS], out[lora::BATCH_MAX_PROJS];  // inputs of the batch's groups, outputs of its entries
-    uint8_t group_n[lora::BATCH_MAX_PROJS];
+    Range in[lora::GEMV_BATCH_MAX_PROJS], out[lora::GEMV_BATCH_MAX_PROJS];  // distinct inputs of the batch's groups; outputs of its entries, by address (they do not overlap)
+    uint8_t group_n[lora::GEMV_BATCH_MAX_PROJS];
     const Scratch scratch = pool_scratch(c);
     int32_t max_projs, max_supers;
     batch_limits(p, scratch, max_projs, max_supers);
@@ -2299,19 +2306,25 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
             const char *x0 = static_cast<const char *>(d.x), *y0 = static_cast<const char *>(d.base_out);
             const Range x{x0, x0 + (size_t)p->T * pr.h_in * e}, y{y0, y0 + (size_t)p->T * pr.h_out * e};
             const bool same_x = m > 0 && d.x == descs[i + m - 1].x && pr.h_in == c->proj[descs[i + m - 1].proj].h_in;
-            bool ok = !y.meets(x);
-            for (int32_t k = 0; k < n_in && ok; ++k) ok = !in[k].meets(y);
-            for (int32_t k = 0; k < m && ok; ++k) ok = !out[k].meets(y) && (same_x || !out[k].meets(x));
+            auto behind = [&](const Range &r) { return std::upper_bound(out, out + m, r.lo, [](const char *lo, const Range &o) { return lo < o.hi; }); };  // the first output that ends behind r.lo
+            auto meets_out = [&](const Range &r) { const Range *o = behind(r); return o != out + m && o->lo < r.hi; };
+            bool ok = !y.meets(x) && !meets_out(y) && (same_x || !meets_out(x)), known = false;
+            for (int32_t k = 0; k < n_in && ok; ++k) {
+                ok = !in[k].meets(y);
+                known |= in[k].lo == x.lo && in[k].hi == x.hi;
+            }
             supers += supers_of(pr.h_out);
             const bool joins_only_group = same_x && last == 0 && m < lora::GROUP_MAX_PROJS;
             if (m > 0 && (!ok || (supers > max_supers && !joins_only_group))) break;
-            out[m] = y;
+            Range *const at = out + (behind(y) - out);
+            std::copy_backward(at, out + m, out + m + 1);
+            *at = y;
             if (same_x && group_n[last] < lora::GROUP_MAX_PROJS) {
                 ++group_n[last];
             } else {
                 last = m;
                 group_n[m] = 1;
-                in[n_in++] = x;
+                if (!known) in[n_in++] = x;
             }
             if (!ok) {
                 ++m;

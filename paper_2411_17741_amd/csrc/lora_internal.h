@@ -121,7 +121,8 @@ inline __host__ __device__ void gemv_expand_cols(const GemvItem &it, int32_t sc,
 
 // A batch: the projections one launch serves.  They do not depend on each other (no output overlaps another entry's
 // output or any entry's input), so that every phase is one launch for all of them.
-constexpr int BATCH_MAX_PROJS = 64;
+constexpr int BATCH_MAX_PROJS = 64;        // of a batch with tiles
+constexpr int GEMV_BATCH_MAX_PROJS = 120;  // of a batch with GEMV work alone
 struct BatchProj {
     const char *proj_base;    // device: first slab of this (layer, projection)
     const void *x;            // device [T][h_in]
@@ -210,7 +211,7 @@ inline __host__ __device__ uint32_t div24(uint32_t v, Div24 d) { return (uint32_
 // The GEMV launch of a batch (several groups of projections, each with its own x).  Blocks
 // [0, n_proj * shrink_blocks) are the shrink blocks, projection by projection; expand units go super-chunk by
 // super-chunk of all projections, items innermost.
-constexpr int GEMV_BATCH_MAX_SUPERS = 512;
+constexpr int GEMV_BATCH_MAX_SUPERS = 768;
 struct GemvBatchMap {
     uint32_t n_gs, n_ge, n_proj, n_units;  // n_units = n_ge * super-chunks of all projections
     uint32_t shrink_blocks;                // per projection: n_gs, or (by_xcd) n_gs rounded up to a multiple of 8
@@ -233,8 +234,42 @@ inline __host__ __device__ void gemv_batch_unit(uint32_t u, const GemvBatchMap &
     super = div24(u, m.div_ge);
     item = u - super * m.n_ge;
 }
-// super-chunk number -> its projection | its number there << 8
-inline __host__ __device__ uint32_t gemv_super(const uint32_t *supers, uint32_t super) { return (supers[super >> 1] >> (16 * (super & 1))) & 0xffffu; }
+// super-chunk number -> its projection (four to a word)
+inline __host__ __device__ uint32_t gemv_super(const uint32_t *supers, uint32_t super) { return (supers[super >> 2] >> (8 * (super & 3))) & 0xffu; }
+// A projection of the launch in 24 bytes, so that the arguments (4 KB at most) hold one request's projections of 17 layers of a 7B model in one launch: three addresses
+// (48 bits) and, in the 16 bits above each, a third of h_in / 64 (22 bits) | h_out / 64 (12 bits) | number of its first super-chunk (14 bits).
+struct GemvEntry {
+    uint64_t w[3];  // x, y, proj_base
+};
+inline GemvEntry gemv_entry(const BatchProj &p, uint32_t first_super)
+{
+    const uint64_t f = (uint64_t)(p.h_in / 64) | (uint64_t)(p.h_out / 64) << 22 | (uint64_t)first_super << 34, low = ((uint64_t)1 << 48) - 1;
+    const uint64_t a[3] = {reinterpret_cast<uint64_t>(p.x), reinterpret_cast<uint64_t>(p.y), reinterpret_cast<uint64_t>(p.proj_base)};
+    GemvEntry e;
+    for (int i = 0; i < 3; ++i) e.w[i] = (a[i] & low) | (f >> 16 * i & 0xffff) << 48;
+    return e;
+}
+// an address as a pointer to global memory (from a bare integer the compiler makes one to any memory: flat loads, +1 % on decode launches)
+inline __host__ __device__ char *global_pointer(uint64_t address)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return (char *)(__attribute__((address_space(1))) char *)address;
+#else
+    return reinterpret_cast<char *>(address);
+#endif
+}
+inline __host__ __device__ BatchProj gemv_entry_proj(const GemvEntry &e, uint32_t &first_super)
+{
+    const uint64_t low = ((uint64_t)1 << 48) - 1, f = e.w[0] >> 48 | (e.w[1] >> 48) << 16 | (e.w[2] >> 48) << 32;
+    BatchProj p;
+    p.x = global_pointer(e.w[0] & low);
+    p.y = global_pointer(e.w[1] & low);
+    p.proj_base = global_pointer(e.w[2] & low);
+    p.h_in = (int32_t)(f & 0x3fffff) * 64;
+    p.h_out = (int32_t)(f >> 22 & 0xfff) * 64;
+    first_super = (uint32_t)(f >> 34);
+    return p;
+}
 // Wide work items, for launches that fill the chip with them (bf16): a shrink item is up to GEMV_WIDE_ROWS stored rank rows
 // (8 or 16) and GEMV_WIDE_SHRINK_TOKENS tokens, an expand item the columns of a GemvItem and GEMV_WIDE_TOKENS tokens.  What bounds such
 // a launch is what the compute units take in (6 to 8 TB/s over all of them): per slab row the items of 4 rows and 4 tokens
@@ -266,8 +301,8 @@ struct GemvBatch {
     uint32_t epoch;           // as in GemvArgs
     float scale;
     GemvBatchMap m;
-    uint32_t supers[GEMV_BATCH_MAX_SUPERS / 2];  // per super-chunk its projection | its number there << 8, two to a word
-    BatchProj p[BATCH_MAX_PROJS];
+    uint32_t supers[GEMV_BATCH_MAX_SUPERS / 4];  // per super-chunk its projection
+    GemvEntry p[GEMV_BATCH_MAX_PROJS];
 };
 static_assert(sizeof(GemvBatch) <= 3900, "kernel arguments are at most 4 KB");
 
