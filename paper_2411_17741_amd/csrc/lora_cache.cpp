@@ -1871,8 +1871,9 @@ constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
 // unit arithmetic (64 requests on 32 projections, 15808 items: 167 against 180 us; 512 requests, 91328 items: 792 against 803 us).
 constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
 // A tile-shrink launch runs as mfma_shrink_direct_kernel up to so many bytes taken in by its units (64 h_in each): 4000 tokens of ranks 8 to 128, 4096 wide, one
-// projection (0.2 GB) 33.3 us per call against 37.4 through the run table, two (0.4 GB) 53.8 and 56.3, eight (1.8 GB) 209 and 181; 2048 wide, eight (0.9 GB) 106 and 107.
-constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 800000000;
+// projection (0.22 GB) 33.3 us per call against 37.4 through the run table; 2300 tokens, mostly of rank 128 (0.27 GB), 67 against 60; eight prompts of ranks 16 to 128 with the
+// base product (0.34 GB) 159 against 155.
+constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
 // rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
 // SHRINK_BATCH_BLOCKS blocks.
