@@ -52,6 +52,13 @@ double gemv_tokens_us(int32_t n_tok, int32_t rank, double width, bool wide)
     return (n_tok + 3) / 4 * (0.004 + 0.0037 * k + rank * (0.00067 + 0.00023 * k)) * (wide ? std::min(1.3, 0.4 + 7.0 / rank) : 1.0);
 }
 double tile_tokens_us(int32_t n_tok, int32_t rank, double width) { return n_tok * width * (3.0 / 7e6 + 5.4e-9 * rank); }
+// A tile-shrink launch runs as mfma_shrink_direct_kernel up to so many bytes taken in by its units (64 h_in each): 4000 tokens of ranks 8 to 128, 4096 wide, one
+// projection (0.22 GB) 33.3 us per call against 37.4 through the run table; 2300 tokens, mostly of rank 128 (0.27 GB), 67 against 60; eight prompts of ranks 16 to 128 with the
+// base product (0.34 GB) 159 against 155.
+constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
+// lora_apply's lists, used by one launch, are read where the host writes them (pinned memory, over the link) up to so many wavefronts that read an item: no upload
+// launch.  16 fp32 tokens 17.2 -> 13.5 us a call, 16 requests 12.6 -> 10.5, 64 requests at 4096 x 4096 (about 2000 wavefronts) 15 -> 12, 200 requests (about 6000) 24 -> 19.5.
+constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond (7B mixed batch 2020 us, 2044 on one stream; 13B 918 and 908;
 // 64 requests beside a prompt of 100 tokens 40.6 and 18.3; 224 beside 13670 prompt tokens, eight projections, 815 and 811).
@@ -152,6 +159,7 @@ struct lora_plan {
     char *dev = nullptr;
     char *pinned = nullptr;
     const char *pinned_dev = nullptr;  // the same as the device sees it
+    const char *lists = nullptr;       // where the kernels read the lists: dev, or pinned_dev
     hipEvent_t ev_upload = nullptr;
     bool upload_pending = false;
     int32_t last_use = -1;  // fence of the latest call that used the plan
@@ -633,6 +641,12 @@ int32_t free_fence(lora_cache &c)
     return (int32_t)c.fences.size() - 1;
 }
 
+// the units a tile shrink of projections with sum_h_in input columns runs as, 0: through the run table
+int32_t direct_shrink(int32_t n_units, int64_t sum_h_in)
+{
+    return n_units * 2 * (lora::DIRECT_TOKENS + lora::DIRECT_ROWS) * sum_h_in <= DIRECT_SHRINK_MAX_BYTES ? n_units : 0;
+}
+
 // Validates a batch against the slot table and writes its work lists into plan `p`
 // (pinned copy + upload on `st`).
 int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
@@ -766,8 +780,10 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         p.shrink_quanta = std::max(1, std::min(quanta, 1 << 14));
         const int64_t slots = std::min<int64_t>(SHRINK_MAX_RUNS, 2 * (int64_t)c.n_cu);
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
+        int32_t widest = 0;
+        for (const auto &pr : c.proj) widest = std::max(widest, pr.h_in);
         for (int v = 0; v < SHRINK_VARIANTS && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
-            if (v > 0 && p.internal) break;  // (lora_apply's own plans serve one projection)
+            if (p.internal && (v > 0 || direct_shrink((int32_t)direct.size(), widest) > 0)) break;  // (lora_apply's own plans serve one projection)
             if (v >= SHRINK_VARIANT_BATCH && c.small_scratch) break;
             if (v == SHRINK_VARIANT_SMALL && T > LORA_STATIC_MAX_TOKENS) continue;  // lora_apply_plan_static refuses such a batch
             const int n = v >= SHRINK_VARIANT_SMALL ? 1 : v + 1;
@@ -791,7 +807,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     std::vector<int32_t> lin_tok;
     std::vector<lora::LinearRows> lin_rows;
     std::vector<lora::LinearSeg> lin_segs;
-    if (c.dtype == LORA_BF16) {
+    if (c.dtype == LORA_BF16 && !p.internal) {
         std::vector<uint8_t> named((size_t)T, 0);
         lin_tok.assign(w.tok_list, w.tok_list + w.n_tok_list);
         for (int32_t t : lin_tok) named[t] = 1;
@@ -856,6 +872,15 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         }
         p.upload_pending = false;
     }
+    if (!c.host_only && p.lists == p.pinned_dev && p.last_use >= 0) {  // an earlier apply may still be reading it there
+        const hipError_t e = hipEventSynchronize(c.fences[p.last_use].ev);
+        if (e != hipSuccess) {
+            lora_worklists_free(&w);
+            g_last_hip = (int)e;
+            return LORA_E_HIP;
+        }
+        hold_fence(c, p.last_use, -1);
+    }
     std::memcpy(p.pinned, w.tok_list, sizeof(int32_t) * (size_t)w.n_tok_list);
     std::memcpy(p.pinned + p.off_tiles, w.tiles, sizeof(lora_item_t) * (size_t)w.n_tiles);
     {
@@ -909,7 +934,16 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     }
     p.bytes = bytes;
     p.build_seq = ++c.plan_builds;
-    if (!c.host_only && bytes) {
+    p.lists = p.dev;
+    int64_t waves = 4 * n_gs;  // of a launch for the widest projection
+    {
+        int32_t supers = 0;
+        for (const auto &pr : c.proj) supers = std::max(supers, (pr.h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS);
+        waves += n_ge * supers;
+    }
+    if (!c.host_only && p.internal && c.fencing && p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES) {
+        p.lists = p.pinned_dev;
+    } else if (!c.host_only && bytes) {
         if (p.last_use >= 0) {
             HIP_TRY(hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0));
             hold_fence(c, p.last_use, -1);
@@ -1870,10 +1904,6 @@ constexpr int FUSED_GEMV_MAX_ITEMS = 8192;
 // The same for a batch, whose shrink blocks are long done when its expand blocks are dispatched: one launch up to the range of the
 // unit arithmetic (64 requests on 32 projections, 15808 items: 167 against 180 us; 512 requests, 91328 items: 792 against 803 us).
 constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
-// A tile-shrink launch runs as mfma_shrink_direct_kernel up to so many bytes taken in by its units (64 h_in each): 4000 tokens of ranks 8 to 128, 4096 wide, one
-// projection (0.22 GB) 33.3 us per call against 37.4 through the run table; 2300 tokens, mostly of rank 128 (0.27 GB), 67 against 60; eight prompts of ranks 16 to 128 with the
-// base product (0.34 GB) 159 against 155.
-constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
 // rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
 // SHRINK_BATCH_BLOCKS blocks.
@@ -1893,18 +1923,18 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_
     const int v = shrink_variant(p, n, sc.vpart_rows, sc.small);
     tb.n = n;
     tb.n_runs = p->shrink_runs[v];
-    if (p->n_tiles > 0 && tb.n_runs == 0) return LORA_E_STATE;  // the plan carries no such table
+    tb.n_direct = direct_shrink(p->n_direct, sum_h_in);
+    if (p->n_tiles > 0 && tb.n_runs == 0 && tb.n_direct == 0) return LORA_E_STATE;  // the plan carries no such table
     tb.quanta = p->shrink_quanta;
     tb.n_tiles = p->n_tiles;
     tb.v_stride = c->v_stride;
     tb.any_pieces = p->shrink_pieces[v] ? 1 : 0;
     tb.scale = scale;
-    tb.direct = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_direct);
-    tb.n_direct = p->n_direct * 2 * (lora::DIRECT_TOKENS + lora::DIRECT_ROWS) * sum_h_in <= DIRECT_SHRINK_MAX_BYTES ? p->n_direct : 0;
-    tb.tiles = reinterpret_cast<const lora::DevItem *>(p->dev + p->off_tiles);
-    tb.cuts = reinterpret_cast<const lora::ShrinkCut *>(p->dev + p->off_cuts[v]);
-    tb.sums = reinterpret_cast<const lora::ShrinkSum *>(p->dev + p->off_sums[v]);
-    tb.tok_list = reinterpret_cast<const int32_t *>(p->dev);
+    tb.direct = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_direct);
+    tb.tiles = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_tiles);
+    tb.cuts = reinterpret_cast<const lora::ShrinkCut *>(p->lists + p->off_cuts[v]);
+    tb.sums = reinterpret_cast<const lora::ShrinkSum *>(p->lists + p->off_sums[v]);
+    tb.tok_list = reinterpret_cast<const int32_t *>(p->lists);
     tb.v = reinterpret_cast<float *>(sc.v);
     tb.part = reinterpret_cast<float *>(sc.vpart);
     const int64_t rows_per_proj = 2 * (int64_t)lora::SHRINK_SLOT_ROWS * tb.n_runs;
@@ -1934,7 +1964,7 @@ static int clear_words_for_capture(lora_cache_t *c, lora_plan_t *p, int n, hipSt
     if (cs == hipStreamCaptureStatusNone) return LORA_OK;
     const bool covered = cap == *sc.cap_id && p->build_seq == *sc.cap_plan && n <= *sc.cap_sets;
     if (!covered) {
-        const int32_t *toks = reinterpret_cast<const int32_t *>(p->dev) + p->n_tile_tok;
+        const int32_t *toks = reinterpret_cast<const int32_t *>(p->lists) + p->n_tile_tok;
         HIP_TRY(lora::launch_gemv_clear(c->dtype, reinterpret_cast<unsigned long long *>(sc.vtag), sc.vtag_set_bytes / sizeof(unsigned long long), n, toks,
                                         p->n_tok_list - p->n_tile_tok, st));
     }
@@ -1959,8 +1989,8 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *
     lora::GemvArgs ga{};
     lora::GemvMap gm{};
     ga.x = a[0].x;
-    gm.gs = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_gs);
-    gm.ge = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_ge);
+    gm.gs = reinterpret_cast<const lora::GemvItem *>(p->lists + p->off_gs);
+    gm.ge = reinterpret_cast<const lora::GemvItem *>(p->lists + p->off_ge);
     gm.n_gs = (uint32_t)p->n_gs;
     gm.n_proj_phase = (uint32_t)n;
     ga.fault = c->fault_dev;
@@ -2008,16 +2038,16 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
 {
     if (p->n_gs <= 0) return LORA_OK;
     lora::GemvBatch b{};
-    b.gs = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_gs);
-    b.ge = reinterpret_cast<const lora::GemvItem *>(p->dev + p->off_ge);
+    b.gs = reinterpret_cast<const lora::GemvItem *>(p->lists + p->off_gs);
+    b.ge = reinterpret_cast<const lora::GemvItem *>(p->lists + p->off_ge);
     b.vw = reinterpret_cast<unsigned long long *>(sc.vtag);
     b.vw_set = sc.vtag_set_bytes / sizeof(unsigned long long);
     b.y32 = y32;
     b.fault = c->fault_dev;
     b.scale = scale;
     const bool wide = gemv_wide(c, p, projs, n, n_groups);
-    b.wgs = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wgs);
-    b.wge = reinterpret_cast<const lora::GemvWideItem *>(p->dev + p->off_wge);
+    b.wgs = reinterpret_cast<const lora::GemvWideItem *>(p->lists + p->off_wgs);
+    b.wge = reinterpret_cast<const lora::GemvWideItem *>(p->lists + p->off_wge);
     int32_t widths[lora::GEMV_BATCH_MAX_PROJS];
     uint32_t first[lora::GEMV_BATCH_MAX_PROJS];
     for (int i = 0; i < n; ++i) widths[i] = projs[i].h_out;
@@ -2226,7 +2256,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     lora::ApplyArgs a;
     a.proj_base = bp.proj_base;
     a.row_bytes = (int64_t)c->row_bytes[proj];
-    a.tok_list = reinterpret_cast<const int32_t *>(p->dev);
+    a.tok_list = reinterpret_cast<const int32_t *>(p->lists);
     a.x = x;
     a.y = y;
     a.v = reinterpret_cast<float *>(c->pool + c->off_v);
@@ -2257,8 +2287,8 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
             return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
-    const lora::LinearList list{reinterpret_cast<const int32_t *>(p->dev + p->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(p->dev + p->off_lin_rows),
-                                reinterpret_cast<const lora::LinearSeg *>(p->dev + p->off_lin_segs),
+    const lora::LinearList list{reinterpret_cast<const int32_t *>(p->lists + p->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(p->lists + p->off_lin_rows),
+                                reinterpret_cast<const lora::LinearSeg *>(p->lists + p->off_lin_segs),
                                 p->n_lin_rows, p->n_tile_tok, p->n_tok_list};
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
     HIP_TRY(lora::launch_linear_tiles(a, Wt, list, c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
