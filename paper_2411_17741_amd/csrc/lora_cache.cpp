@@ -169,7 +169,7 @@ struct lora_plan {
     // the tile shrink's run tables (cuts, then the tiles' piece records), per variant
     int32_t shrink_quanta = 1;
     int32_t shrink_runs[SHRINK_VARIANTS] = {0};
-    bool shrink_pieces[SHRINK_VARIANTS] = {false};
+    bool shrink_pieces[SHRINK_VARIANTS] = {false}, shrink_pairs[SHRINK_VARIANTS] = {false};
     size_t off_cuts[SHRINK_VARIANTS] = {0}, off_sums[SHRINK_VARIANTS] = {0};
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     uint64_t build_seq = 0;     // changes whenever the plan's lists are rebuilt
@@ -190,6 +190,7 @@ struct lora_cache {
     std::vector<int32_t> class_rank, class_slots, class_first;
     int32_t n_layers = 0, n_slots = 0, dtype = 0, esize = 0;
     int32_t max_tokens = 0, max_segments = 0, n_user_plans = 0, mfma_min = 0, flags = 0;
+    int32_t direct_max = 0;      // units of a short tile shrink that a plan has room for
     bool small_scratch = false;  // the pool holds the scratch of a group of projections only
     bool mfma_min_auto = false;  // the configuration left the threshold to the library
     int32_t v_stride = 0;
@@ -337,13 +338,19 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     const size_t max_wide = c.dtype != LORA_BF16 || small_scratch ? 0
                                                  : ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_SHRINK_TOKENS + 1) * (LORA_MAX_RANK / lora::GEMV_WIDE_ROWS) +
                                                        ((size_t)c.max_segments + (size_t)c.max_tokens / lora::GEMV_WIDE_TOKENS + 1) * 16;
+    // units of a short tile shrink: no more than a launch of the narrowest projection may have, nor than the tokens make
+    size_t narrowest = SIZE_MAX;
+    for (const auto &pr : c.proj) narrowest = std::min(narrowest, (size_t)pr.h_in);
+    c.direct_max = c.dtype != LORA_BF16 || small_scratch ? 0
+                       : (int32_t)std::min({(size_t)lora::DIRECT_MAX_UNITS, (size_t)DIRECT_SHRINK_MAX_BYTES / (64 * narrowest),
+                                            ((size_t)c.max_tokens / lora::DIRECT_TOKENS + max_tiles) * (LORA_MAX_RANK / lora::DIRECT_ROWS)});
     const int n_tables = small_scratch ? SHRINK_VARIANT_BATCH : SHRINK_VARIANTS;
     c.plan_cap = align_up(sizeof(int32_t) * (size_t)c.max_tokens) + align_up(sizeof(lora_item_t) * max_items) +
                  align_up(sizeof(int32_t) * max_batches) + 4 * ALIGN + (max_wide ? align_up(sizeof(lora::GemvWideItem) * max_wide) + 2 * ALIGN : 0) +
                  (c.dtype == LORA_BF16 ? align_up(sizeof(int32_t) * (size_t)c.max_tokens) +
                                              align_up(sizeof(lora::LinearRows) * ((size_t)c.max_tokens / LORA_TILE_TOKENS + 2)) +
                                              align_up(sizeof(lora::LinearSeg) * (size_t)c.max_segments) : 0) +
-                 (c.dtype == LORA_BF16 && !small_scratch ? align_up(sizeof(lora::DevItem) * lora::DIRECT_MAX_UNITS) : 0) +
+                 align_up(sizeof(lora::DevItem) * (size_t)c.direct_max) +
                  n_tables * (align_up(sizeof(lora::ShrinkCut) * (SHRINK_MAX_RUNS + 1)) + align_up(sizeof(lora::ShrinkSum) * max_tiles));
     // fill staging: a buffer takes parts of an adapter until STAGE_BYTES (or the largest adapter) are in it
     c.stage_cap = small_scratch ? align_up(max_part) + ALIGN : align_up(std::max(max_part, std::min(STAGE_BYTES, (size_t)c.class_rank[n_cls - 1] * row_sum * c.n_layers)));
@@ -509,11 +516,12 @@ struct ShrinkRuns {
     std::vector<lora::ShrinkSum> sums;
     int n_runs = 0;
     bool any_pieces = false;
+    bool any_pairs = false;  // two whole tiles of one slot follow each other in some run
 };
 bool shrink_pieces_of(const lora::DevItem *tiles, int n_tiles, int quanta, ShrinkRuns &out)
 {
     out.sums.assign((size_t)n_tiles, lora::ShrinkSum{0, 0});
-    out.any_pieces = false;
+    out.any_pieces = out.any_pairs = false;
     for (int r = 0; r < out.n_runs; ++r) {
         const lora::ShrinkCut from = out.cuts[r], to = out.cuts[r + 1];
         const int last_tile = std::min(to.part > 0 ? to.tile : to.tile - 1, n_tiles - 1);
@@ -526,11 +534,11 @@ bool shrink_pieces_of(const lora::DevItem *tiles, int n_tiles, int quanta, Shrin
             else if (slot != 2 * (sm.first_slot / 2 + sm.n_pieces)) return false;  // (cannot happen: later pieces start their runs)
             ++sm.n_pieces;
             if (sm.n_pieces > 1) out.any_pieces = true;
+            out.any_pairs |= lo == 0 && hi == quanta && t + 1 < to.tile && tiles[t + 1].row == tiles[t].row;  // (as mfma_shrink_kernel asks)
         }
     }
     for (int t = 0; t < n_tiles; ++t)
         if (out.sums[t].n_pieces < 1) return false;
-    (void)tiles;
     return true;
 }
 // Runs of about equal cost, at most max_runs of them (a multiple of 8).  A piece costs its parts times its tile's
@@ -754,14 +762,14 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     stamp(w.tiles, w.n_tiles);
     // the units of a short tile shrink
     std::vector<lora::DevItem> direct;
-    if (w.n_tiles > 0 && !c.small_scratch) {
+    if (w.n_tiles > 0) {
         int64_t n = 0;
         auto blocks = [](int32_t v, int32_t by) { return (v + by - 1) / by; };
-        for (int i = 0; i < w.n_tiles && n <= lora::DIRECT_MAX_UNITS; ++i) {
+        for (int i = 0; i < w.n_tiles && n <= c.direct_max; ++i) {
             const lora::DevItem &t = reinterpret_cast<const lora::DevItem *>(w.tiles)[i];
             n += blocks(t.n_tok, lora::DIRECT_TOKENS) * blocks(t.rank, lora::DIRECT_ROWS);
         }
-        for (int i = 0; i < w.n_tiles && n <= lora::DIRECT_MAX_UNITS; ++i) {
+        for (int i = 0; i < w.n_tiles && n <= c.direct_max; ++i) {
             const lora::DevItem &t = reinterpret_cast<const lora::DevItem *>(w.tiles)[i];
             for (int32_t o = 0; o < t.n_tok; o += lora::DIRECT_TOKENS) {
                 lora::DevItem d = t;
@@ -847,6 +855,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         p.shrink_runs[v] = shrink_runs[v].n_runs;
         p.shrink_pieces[v] = shrink_runs[v].any_pieces;
+        p.shrink_pairs[v] = shrink_runs[v].any_pairs;
         p.off_cuts[v] = bytes;
         bytes += align_up(sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
         p.off_sums[v] = bytes;
@@ -1929,6 +1938,7 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_
     tb.n_tiles = p->n_tiles;
     tb.v_stride = c->v_stride;
     tb.any_pieces = p->shrink_pieces[v] ? 1 : 0;
+    tb.any_pairs = p->shrink_pairs[v] ? 1 : 0;
     tb.scale = scale;
     tb.direct = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_direct);
     tb.tiles = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_tiles);

@@ -393,6 +393,7 @@ struct TileBatchHead {
     int32_t n_runs, quanta;   // n_runs: a multiple of 8 (run r is worked on by XCD r / (n_runs / 8))
     int32_t n_tiles, v_stride;
     int32_t any_pieces;       // some tile is worked on in pieces: the reduce launch is needed
+    int32_t any_pairs;        // some run has two whole tiles of one slot behind each other: the kernel that works on two at a time
     float scale;
     const DevItem *tiles;     // device, n_tiles
     const DevItem *direct;    // device, n_direct units; n_direct = 0: the launch works through the run table

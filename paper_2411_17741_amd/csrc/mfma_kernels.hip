@@ -277,6 +277,131 @@ __device__ __forceinline__ void mfma_shrink_body(const ApplyArgs &a, const DevIt
     }
 }
 
+__device__ __forceinline__ void request_to_lds(const __bf16 *from, unsigned char *to_lds)  // lane l's 16 bytes to to_lds + 16 l
+{
+    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
+}
+template <int N> __device__ __forceinline__ void wait_for_all_but()  // the latest N requests
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Two whole tiles of one slot that follow each other in a run, side by side: At is taken in once for both.  What a long launch is bound by is what misses
+// L2, and At misses it once per tile (7B mixed batch: 2 GB of x, 2 GB of At): 1871 -> 1807 us for the batch's list.  x and At travel through LDS alone (requests that
+// write it, waited for by count, one barrier per stage of 64 k), since the registers of the body above do not hold two tiles; for a single tile this
+// form is no faster (prefill batch 216.8 against 220.8 us, 7B mixed 1871 against 1893).
+// A ring slot is a stage: 128 rows of x, then 16 NB rows of At (NB: rank blocks of 16), rows of 128 bytes, 16-byte slot s of row r holding piece s ^ ((r / 2) % 8).
+// Wavefront w makes four requests of x rows and 2 NB / 4 of At (the first two wavefronts one more where that is odd), a request being 8 rows, and
+// multiplies token block w of both tiles with every rank block.
+constexpr int SKD = 64, SROW = SKD * 2;        // k elements of a stage and the bytes of a row
+constexpr int RING_BYTES = 3 * (64 + 128) * SROW;  // two slots at rank 128, three to five below: two blocks to a compute unit
+static_assert(SK % SKD == 0 && RING_BYTES >= NSTAGE * LORA_TILE_TOKENS * XROW, "pieces are whole stages; the other body's ring is the same memory");
+template <int NB>
+__device__ __forceinline__ void mfma_shrink_pair(const ApplyArgs &a, const DevItem (&it)[2], int st_begin, int n_st, int phase, unsigned char *ring)
+{
+    constexpr int TT = 2, SLOT = (64 * TT + 16 * NB) * SROW, NST = RING_BYTES / SLOT, PER_AT = NB / 2, PX = 2 * TT;  // PER_AT, PX: requests of every wavefront
+    constexpr bool ODD = NB % 2 != 0;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int rs = rank_storage(it[0].rank);
+    const __bf16 *At = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)it[0].row * a.row_bytes);
+    const int lr = lane >> 3, piece = (lane & 7) ^ ((4 * (w & 1) + (lr >> 1)) & 7);
+    const bool more = ODD && w < 2;
+    const __bf16 *src[PX + PER_AT + ODD];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+        const int ti[2] = {8 * w + lr, 32 + 8 * w + lr};
+        int tok[2];
+        tile_tokens(a, it[t], ti, tok);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) src[2 * t + q] = static_cast<const __bf16 *>(a.x) + (size_t)tok[q] * a.h_in;
+    }
+#pragma unroll
+    for (int q = 0; q < PER_AT + ODD; ++q) src[PX + q] = At + (size_t)min(8 * (w + 4 * q) + lr, rs - 1) * a.h_in;
+    auto request = [&](int st, int slot) {  // (the walk over k starts at another stage in every block, as above)
+        int s = st + phase;
+        s -= s >= n_st ? n_st : 0;
+        const int k = (st_begin + s) * SKD + piece * 8;
+        unsigned char *dst = ring + slot * SLOT + 8 * w * SROW;
+#pragma unroll
+        for (int q = 0; q < PX; ++q) request_to_lds(src[q] + k, dst + 32 * q * SROW);
+#pragma unroll
+        for (int q = 0; q < PER_AT; ++q) request_to_lds(src[PX + q] + k, dst + (64 * TT + 32 * q) * SROW);
+        if (more) request_to_lds(src[PX + PER_AT + ODD - 1] + k, dst + (64 * TT + 32 * PER_AT) * SROW);
+    };
+    floatx4 acc[TT][NB];
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int slot) {
+        const unsigned char *xs = ring + slot * SLOT + (16 * w + m) * SROW, *as = ring + slot * SLOT + (64 * TT + m) * SROW;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = ((4 * ks + g) ^ ((m >> 1) & 7)) << 4;
+            bf16x8 xo[TT];
+#pragma unroll
+            for (int t = 0; t < TT; ++t) xo[t] = *reinterpret_cast<const bf16x8 *>(xs + 64 * t * SROW + at);
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const bf16x8 ao = *reinterpret_cast<const bf16x8 *>(as + 16 * q * SROW + at);
+#pragma unroll
+                for (int t = 0; t < TT; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[t], ao, acc[t][q], 0, 0, 0);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read when this wavefront is at the next barrier
+    };
+    auto wait = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;
+        if (more) wait_for_all_but<LEFT *(PX + 1 + PER_AT)>();
+        else wait_for_all_but<LEFT *(PX + PER_AT)>();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s)
+        if (s < n_st) request(s, s);
+    int slot = 0, fill = NST - 1;
+    for (int st = 0; st < n_st - (NST - 1); ++st) {
+        wait(std::integral_constant<int, NST - 2>{});
+        request(st + NST - 1, fill);
+        multiply(slot);
+        fill = slot;
+        slot = slot + 1 == NST ? 0 : slot + 1;
+    }
+    auto last = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;
+        if constexpr (LEFT < NST - 1) {
+            if (n_st <= LEFT) return;
+            wait(left_tag);
+            multiply(slot);
+            slot = slot + 1 == NST ? 0 : slot + 1;
+        }
+    };
+    last(std::integral_constant<int, 3>{});
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 0>{});
+    static_assert(NST >= 2 && NST <= 5, "the walk's last stages");
+    __bf16 *const out16 = reinterpret_cast<__bf16 *>(a.v);
+    const float s_v = a.scale * it[0].alpha;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+        int ti[4], rows[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ti[r] = rows[r] = 16 * w + 4 * g + r;
+        tile_tokens(a, it[t], ti, rows);
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int jr = 16 * q + m;
+                if (ti[r] < it[t].n_tok && jr < it[t].rank) out16[(size_t)rows[r] * (2 * a.v_stride) + jr] = (__bf16)(s_v * acc[t][q][r]);
+            }
+    }
+}
+
 // the arguments of one projection of the batch
 template <int N>
 __device__ __forceinline__ ApplyArgs tile_args(const TileBatchArgs<N> &tb, int pj)
@@ -296,13 +421,14 @@ __device__ __forceinline__ ApplyArgs tile_args(const TileBatchArgs<N> &tb, int p
     return a;
 }
 
-template <int N>
+template <int N, bool PAIRS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_shrink_kernel(const ShrinkCut *__restrict__ cuts, const DevItem *__restrict__ tiles, int runs_per_xcd, int n_proj, int quanta,
                                                                                                         int n_tiles, TileBatchArgs<N> tb)
 {
     // (the scalars in front are fields of tb: leading arguments arrive in registers with the wavefront)
-    __shared__ __attribute__((aligned(16))) unsigned char xs[NSTAGE][LORA_TILE_TOKENS * XROW];
-    static_assert(sizeof(xs) >= 4 * 4 * 3 * 4 * 64 * 4, "the sum over the wavefronts' k parts reuses the x ring");
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
+    unsigned char(*const xs)[LORA_TILE_TOKENS * XROW] = reinterpret_cast<unsigned char(*)[LORA_TILE_TOKENS * XROW]>(ring);
+    static_assert(NSTAGE * LORA_TILE_TOKENS * XROW >= 4 * 4 * 3 * 4 * 64 * 4, "the sum over the wavefronts' k parts reuses the x ring");
 
     // XCD j = blockIdx % 8 works on the runs [j * runs_per_xcd, (j + 1) * runs_per_xcd) of every group, group by group;
     // its i-th block of a group on (run, projection) number i, projection innermost: the blocks that read the same part
@@ -332,7 +458,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                              ? nullptr
                              : tb.part + (size_t)pj * tb.part_set + (size_t)shrink_slot(run, from.tile, tile) * SHRINK_SLOT_ROWS * a.v_stride;
         const int NB = (it.rank + 15) >> 4;
-        if (NB > 4) mfma_shrink_body<true, 2>(a, it, k_begin, k_end, phase, my_part, xs);
+        DevItem next{};
+        if constexpr (PAIRS) next = tiles[min(tile + 1, n_tiles - 1)];
+        if (PAIRS && !my_part && tile + 1 < to.tile && next.row == it.row) {  // (the next tile is a whole one of this run too; uniform over the block)
+            const DevItem two[2] = {it, next};
+            const int stages = (k_end - k_begin) / SKD, at = phase * (SK / SKD);
+            switch (NB) {
+            case 1: mfma_shrink_pair<1>(a, two, k_begin / SKD, stages, at, ring); break;
+            case 2: mfma_shrink_pair<2>(a, two, k_begin / SKD, stages, at, ring); break;
+            case 3: mfma_shrink_pair<3>(a, two, k_begin / SKD, stages, at, ring); break;
+            case 4: mfma_shrink_pair<4>(a, two, k_begin / SKD, stages, at, ring); break;
+            case 5:
+            case 6: mfma_shrink_pair<6>(a, two, k_begin / SKD, stages, at, ring); break;
+            default: mfma_shrink_pair<8>(a, two, k_begin / SKD, stages, at, ring); break;
+            }
+            ++tile;
+        } else if (NB > 4) mfma_shrink_body<true, 2>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 4) mfma_shrink_body<true, 1>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 3) mfma_shrink_body<false, 3>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 2) mfma_shrink_body<false, 2>(a, it, k_begin, k_end, phase, my_part, xs);
@@ -352,15 +493,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 namespace {
 constexpr int DK = 64, DROW = DK * 2, DSTAGE = 32 * DROW, DRING = 4;  // 16 rows of x, 16 of At
 }  // namespace
-
-__device__ __forceinline__ void request_to_lds(const __bf16 *from, unsigned char *to_lds)  // lane l's 16 bytes to to_lds + 16 l
-{
-    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
-}
-template <int N> __device__ __forceinline__ void wait_for_all_but()  // the latest N requests
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
 
 template <int N, int W>
 __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArgs<N> tb)
@@ -736,8 +868,8 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
 {
     if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
     if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
     if (batch.n_direct > 0) {
-        hipError_t e = hipSuccess;
         with_batch_size(batch, [&](const auto &tb) {
             constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
             auto go = [&](auto w_tag) {
@@ -759,11 +891,23 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
     if (batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
     with_batch_size(batch, [&](const auto &tb) {
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
-        launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), 0, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
-                 tb.quanta, tb.n_tiles, tb);
+        auto go = [&](auto pairs_tag) {
+            constexpr bool PAIRS = decltype(pairs_tag)::value;
+            constexpr int LDS = PAIRS ? RING_BYTES : NSTAGE * LORA_TILE_TOKENS * XROW;
+            static bool attr_set = false;
+            if (!attr_set) {
+                e = hipFuncSetAttribute(reinterpret_cast<const void *>(mfma_shrink_kernel<N, PAIRS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+                if (e != hipSuccess) return;
+                attr_set = true;
+            }
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N, PAIRS>, dim3(tb.n_runs * tb.n), dim3(256), LDS, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
+                     tb.quanta, tb.n_tiles, tb);
+        };
+        if (tb.any_pairs) go(std::true_type{});  // (a kernel of its own: beside the other body it costs launches without pairs 1 %)
+        else go(std::false_type{});
         if (tb.any_pieces) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel<N>, dim3(tb.n_tiles * 8, tb.n), dim3(256), 0, st, tb);
     });
-    return hipGetLastError();
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 // Longest column run, in passes (7B mixed batch 1898 us with 4, 1866 with 8, 1887 with 16).
