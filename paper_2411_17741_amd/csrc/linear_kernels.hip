@@ -36,7 +36,7 @@
 // token: 8 bytes of bf16, parked in LDS and stored from there in whole 128-byte lines.
 // After the k loop the scaled intermediate s.v of the block's rows is staged in LDS as bf16 and every
 // wavefront adds, per segment of its rows, the products with that segment's Bp, whose rank-packed layout gives the
-// row operand directly from global memory (a lane's 8 ranks are 16 contiguous bytes); rows of other segments meet zeros.
+// row operand directly from global memory (a lane's 8 ranks are 16 contiguous bytes); rows of other segments keep their sums.
 // (Rows without gaps, where every tile had 64 rows of its own: a 13B layer's batch 12 -> 10 row panels, 1936 -> 1804 us for its seven
 // projections; eight prompts at 4096 x 4096 19 -> 17 panels, 162 -> 154 us.)
 // The adapter term of tokens on the GEMV path is computed by the GEMV kernels beforehand into the workspace or the
@@ -115,18 +115,25 @@ __device__ __forceinline__ void section_end()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// The s.v operand of the adapter product: of the 8 ranks of a lane the first n (what lies behind them was never written) of a row
-// of the segment, zeros for a row of another.  As masks of whole words: a stale NaN must not survive.
+// The s.v operand of the adapter product: of the 8 ranks of a lane the first n (what lies behind them was never written).  As masks of
+// whole words: a stale NaN must not survive.
 __device__ __forceinline__ uint4 rank_mask(int n)
 {
     auto word = [&](int j) { return n >= 2 * j + 2 ? 0xffffffffu : (n == 2 * j + 1 ? 0x0000ffffu : 0u); };
     return make_uint4(word(0), word(1), word(2), word(3));
 }
-__device__ __forceinline__ bf16x8 sv_operand(const uint4 &v, const uint4 &live, bool row_in)
+__device__ __forceinline__ bf16x8 sv_operand(const uint4 &v, const uint4 &live)
 {
-    const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-    const uint4 f = make_uint4(v.x & live.x, v.y & live.y, v.z & live.z, v.w & live.w);
-    return __builtin_bit_cast(bf16x8, row_in ? f : z);
+    return __builtin_bit_cast(bf16x8, make_uint4(v.x & live.x, v.y & live.y, v.z & live.z, v.w & live.w));
+}
+// Where a block of 16 rows has rows of several segments, those outside the segment whose products have just been added get back what they had: lane
+// (m, g) holds sums of row m alone, and an infinity or NaN in the segment's weights would come through a row of zeros as NaN.
+template <int NB> __device__ __forceinline__ void keep_rows_outside(floatx4 (&acc)[NB], const floatx4 (&had)[NB], bool row_in)
+{
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[nb][e] = row_in ? acc[nb][e] : had[nb][e];
 }
 
 __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
@@ -413,19 +420,27 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
         const int ks32 = (seg.rank + 31) >> 5;
         const int lo = seg.r0 - row0 - 128 * rh, hi = seg.r1 - row0 - 128 * rh;  // its rows among the wavefront's 128
         const unsigned char *svr = sv + (128 * rh + m) * SV_ROW + g * 16;
+        uint4 live[4];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks < ks32) {
-                const uint4 live = rank_mask(seg.rank - 32 * ks - 8 * g);
+        for (int ks = 0; ks < 4; ++ks) live[ks] = rank_mask(seg.rank - 32 * ks - 8 * g);
 #pragma unroll
-                for (int mb = 0; mb < 8; ++mb) {
-                    if (!owns(mb) || 16 * mb + 16 <= lo || 16 * mb >= hi) continue;  // uniform
-                    const bf16x8 so = sv_operand(*reinterpret_cast<const uint4 *>(svr + mb * 16 * SV_ROW + ks * 64), live, 16 * mb + m >= lo && 16 * mb + m < hi);
+        for (int mb = 0; mb < 8; ++mb) {
+            const int r0 = 16 * mb, r = r0 + m;
+            if (!owns(mb) || r0 + 16 <= lo || r0 >= hi) continue;  // uniform
+            const bool whole = lo <= r0 && r0 + 16 <= hi;  // uniform
+            floatx4 had[4];
+            if (!whole) {
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb)
-                        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
-                }
+                for (int nb = 0; nb < 4; ++nb) had[nb] = acc[mb][nb];
             }
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                if (ks >= ks32) continue;
+                const bf16x8 so = sv_operand(*reinterpret_cast<const uint4 *>(svr + mb * 16 * SV_ROW + ks * 64), live[ks]);
+#pragma unroll
+                for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
+            }
+            if (!whole) keep_rows_outside<4>(acc[mb], had, lo <= r && r < hi);
         }
     }
 
@@ -527,9 +542,10 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 // 27.5 -> 12.3, 992 x 1024 x 1024 26.2 -> 8.1, 2283 x 1088 x 1088 28.1 -> 14.4, 1234 x 2048 x 2048 30.3 -> 20.3 (128 rows), 785 x 2560 x 2560
 // 32.4 -> 23.3 (128 rows); 1000 x 4096 x 4096 46.7 and 48.2.  Stages of 128 k (whole 256-byte rows) took the same time, tiles of 64 x 128 up to
 // a fifth more than 128 x 64, 128 x 128 with four wavefronts half more.
+// (The wavefronts per SIMD are those that LDS leaves room for; told of more, the compiler moves the sums between register files in every stage, 785 x 2560 x 2560 29.1 -> 30.3 us.)
 // ---------------------------------------------------------------------------------------
 template <int RM, int NST>
-__global__ __launch_bounds__(256) void linear_small_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt, LinearList list, int n_mt, int n_nt, LinearSplit sp)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, RM == 1 ? 3 : 2))) void linear_small_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt, LinearList list, int n_mt, int n_nt, LinearSplit sp)
 {
     constexpr int BM = 64 * RM, BN = 64, MB = 2 * RM, NB = 2;  // MB, NB: blocks of 16 rows and columns of a wavefront
     constexpr int STAGE = (BM + BN) * LROW, PER = 2 * (RM + 1);  // PER: requests of a wavefront per stage
@@ -722,14 +738,18 @@ __global__ __launch_bounds__(256) void linear_small_kernel(ApplyArgs a, const __
                     vo[ks][mb] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[mb] * (2 * a.v_stride) + gran * 8);
             }
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                const uint4 live = rank_mask(seg.rank - 32 * (k0 + ks) - 8 * g);
+            for (int mb = 0; mb < MB; ++mb) {
+                const int r = 16 * mb + m;
+                floatx4 had[NB];
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    const bf16x8 so = sv_operand(vo[ks][mb], live, 16 * mb + m >= lo && 16 * mb + m < hi);
+                for (int nb = 0; nb < NB; ++nb) had[nb] = acc[mb][nb];
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const bf16x8 so = sv_operand(vo[ks][mb], rank_mask(seg.rank - 32 * (k0 + ks) - 8 * g));
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
                 }
+                keep_rows_outside<NB>(acc[mb], had, lo <= r && r < hi);  // (in every block: behind a branch the loads above would be made one block at a time, 28.5 -> 29.3 us at 785 x 2560 x 2560)
             }
         }
     }

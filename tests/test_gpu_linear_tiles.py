@@ -109,6 +109,63 @@ def test_rows_of_several_slots(lens, h_in, h_out):
         pool.close()
 
 
+@pytest.mark.parametrize("lens,h_in,h_out", [
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 1024, 1088),   # tiles of 64 x 64
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 4096, 256),    # of 64 x 64, split along k
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 512, 11072),   # of 64 x 64, more of them than fit side by side with a ring of four
+    ([700, 13, 8, 400, 1, 1, 1], 1536, 1536),            # of 128 x 64
+    ([700, 13, 8, 400, 1, 1, 1], 4096, 4096),            # of 256 x 256, split along k
+    ([250, 12, 250, 1, 8, 8, 8, 8, 8, 8, 8, 8, 1, 2500], 2048, 2432),  # of 256 x 256, whole
+])
+def test_infinities_stay_with_their_adapter(lens, h_in, h_out):
+    """Infinities and NaN in one adapter's B: the rows of every other segment, of the requests on the GEMV path and of those without
+    an adapter are bit for bit what they are beside the same adapter with finite weights, whichever block of 16 rows they share
+    with it; so are its own rows in the columns that are finite."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    ranks = [5, 128, 33, 16, 100]
+    gen = torch.Generator(device="cuda").manual_seed(h_in + len(lens))
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    T = sum(lens)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ones = [i for i, n in enumerate(lens) if n == 1]
+    slot = np.asarray([i % 5 if n > 1 else 5 + ones.index(i) for i, n in enumerate(lens)], np.int32)
+    slot[ones[1:2]] = -1
+    rank_of = np.asarray(ranks + [ranks[i % 5] for i in range(len(ones))])
+    A, Bm = [normal(h_in, r, sigma=0.02) for r in rank_of], [normal(r, h_out, sigma=0.02) for r in rank_of]
+    x, wt = normal(T, h_in), normal(h_out, h_in, sigma=0.02)
+    space = torch.empty(T * h_out, dtype=torch.float32, device="cuda")
+    slot_of_token = torch.as_tensor(np.repeat(slot, lens), device="cuda")
+    pool = LoraPool([(h_in, h_out)], 1, [128], [len(rank_of)], B.LORA_BF16, max_tokens=T, max_segments=len(lens), mfma_min_tokens=8)
+    try:
+        def product(bad):
+            for i, r in enumerate(rank_of):
+                w = Bm[i].clone()
+                if i == bad:
+                    w[0, 0::4], w[-1, 1::4], w[r // 2, 2::4] = float("inf"), float("nan"), float("-inf")
+                B.lora_cache_release_slot(pool.handle, i)
+                pool.fill(i, i + 1, int(r), 1.0, 0, 0, A[i].cpu(), w.cpu())
+            torch.cuda.synchronize()
+            plan = pool.plan(T, off, slot, np.where(slot >= 0, rank_of[slot], 0).astype(np.int32))
+            y = torch.full((T, h_out), 7.0, dtype=torch.bfloat16, device="cuda")
+            B.check(B.lora_linear_plan(pool.handle, plan, 0, 0, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0,
+                                       torch.cuda.current_stream().cuda_stream, space.data_ptr(), space.numel() * 4))
+            pool.check_fault()
+            pool.plan_destroy(plan)
+            return y
+
+        want = product(-1)
+        assert bool(want.isfinite().all())
+        for bad in sorted({int(s) for s in slot if 0 <= s < 5}):
+            got, own = product(bad), slot_of_token == bad
+            assert torch.equal(got[~own], want[~own]), f"{int((got[~own] != want[~own]).sum())} values beside slot {bad}"
+            assert torch.equal(got[own][:, 3::4], want[own][:, 3::4])
+            assert not bool(got[own][:, 1::4].isfinite().any())
+    finally:
+        pool.close()
+
+
 @pytest.mark.parametrize("T,h_in,h_out,tiles", [(300, 4096, 1024, 8), (700, 11008, 2304, 27), (1100, 4096, 4096, 80), (2048, 4096, 4096, 128)])
 def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
     """What happens when a part is done before another has started, forced from the host: the tiles' state (16 bytes each,
