@@ -858,20 +858,24 @@ static double small_estimate(int n_tiles, int n_k, int rm, int parts, double l2_
     return 4.0 + std::max(stage * ((n_k + parts - 1) / parts), bytes / rate) + hand_over;
 }
 
+template <int RM, int NST> constexpr int small_lds = NST * 64 * (RM + 1) * LROW;
+
+hipError_t prepare_linear_kernels()
+{
+    hipError_t e = allow_lds(linear_tiles_kernel, L_LDS);
+    if (e == hipSuccess) e = allow_lds(linear_small_kernel<1, 4>, small_lds<1, 4>);
+    if (e == hipSuccess) e = allow_lds(linear_small_kernel<1, 3>, small_lds<1, 3>);
+    if (e == hipSuccess) e = allow_lds(linear_small_kernel<2, 3>, small_lds<2, 3>);
+    return e;
+}
+
 template <int RM, int NST>
 static hipError_t launch_small(const ApplyArgs &a, const void *Wt, const LinearList &list, int parts, void *split_scratch, SplitState *split_state,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
-    constexpr int LDS = NST * 64 * (RM + 1) * LROW;
-    static bool attr_set = false;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_small_kernel<RM, NST>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
     const int n_mt = (list.n_rt + RM - 1) / RM, n_nt = a.h_out / 64;
     const LinearSplit sp{0, parts, static_cast<unsigned long long *>(split_scratch), split_state, nullptr};
-    launch_k(tm, done, LORA_K_LINEAR, linear_small_kernel<RM, NST>, dim3(n_mt * n_nt * parts), dim3(256), LDS, st, a, static_cast<const __bf16 *>(Wt), list, n_mt, n_nt, sp);
+    launch_k(tm, done, LORA_K_LINEAR, linear_small_kernel<RM, NST>, dim3(n_mt * n_nt * parts), dim3(256), small_lds<RM, NST>, st, a, static_cast<const __bf16 *>(Wt), list, n_mt, n_nt, sp);
     return hipGetLastError();
 }
 
@@ -895,13 +899,6 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearL
         return launch_small<1, 3>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
     }
     if (t128 <= big) return launch_small<2, 3>(a, Wt, list, 1, split_scratch, split_state, st, tm, done);
-    static bool attr_set = false;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(linear_tiles_kernel),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, L_LDS);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
     if (n_tail > n_split_state) parts = 1, n_tail = 0;
     const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
     const int blocks = n_tiles - n_tail + n_tail * parts;

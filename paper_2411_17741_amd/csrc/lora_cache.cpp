@@ -1088,6 +1088,15 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         delete c;
         return rc_s;
     }
+    if (c->dtype == LORA_BF16) {
+        hipError_t e = lora::prepare_mfma_kernels();
+        if (e == hipSuccess) e = lora::prepare_linear_kernels();
+        if (e != hipSuccess) {
+            g_last_hip = (int)e;
+            delete c;
+            return LORA_E_HIP;
+        }
+    }
 
     int rc = LORA_OK;
     // the tagged words must not carry a future launch number by accident: numbers start at 1

@@ -411,6 +411,14 @@ template <int N> struct TileBatchArgs : TileBatchHead {  // as the kernels take 
 };
 using TileBatch = TileBatchArgs<BATCH_MAX_PROJS>;
 static_assert(sizeof(TileBatch) <= 3500, "kernel arguments are at most 4 KB");
+// The LDS that the kernels of a file ask for at launch, made known on the current device: by every cache for its own (each device has
+// limits of its own, and threads that create caches or make calls meanwhile share nothing).
+template <typename K> hipError_t allow_lds(K *kernel, int bytes)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+hipError_t prepare_mfma_kernels();
+hipError_t prepare_linear_kernels();
 hipError_t launch_mfma_shrink(const TileBatch &tb, hipStream_t st, const KernelTimer *tm);
 hipError_t launch_mfma_expand(const TileBatch &tb, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // What lora_linear_plan's kernels read of a plan (device): the list of rows, its runs, the segments of the rows with an adapter

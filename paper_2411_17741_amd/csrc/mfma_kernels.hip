@@ -863,29 +863,40 @@ template <typename F> static void with_batch_size(const TileBatch &tb, F go)
     go(g);
 }
 
+template <int W> constexpr int direct_lds = W *DRING *DSTAGE;
+template <bool PAIRS> constexpr int shrink_lds = PAIRS ? RING_BYTES : NSTAGE * LORA_TILE_TOKENS * XROW;
+
+// A kernel's limit of LDS belongs to the device that is current when it is set
+template <int N> static hipError_t prepare_shrinks()
+{
+    hipError_t e = allow_lds(mfma_shrink_direct_kernel<N, 4>, direct_lds<4>);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_direct_kernel<N, 8>, direct_lds<8>);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N, false>, shrink_lds<false>);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N, true>, shrink_lds<true>);
+    return e;
+}
+hipError_t prepare_mfma_kernels()
+{
+    const hipError_t e = prepare_shrinks<GROUP_MAX_PROJS>();
+    return e == hipSuccess ? prepare_shrinks<BATCH_MAX_PROJS>() : e;
+}
+
 // k ranges are multiples of the 128-element stage.
 hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const KernelTimer *tm)
 {
     if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
     if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
-    hipError_t e = hipSuccess;
     if (batch.n_direct > 0) {
         with_batch_size(batch, [&](const auto &tb) {
             constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
             auto go = [&](auto w_tag) {
-                constexpr int W = decltype(w_tag)::value, LDS = W * DRING * DSTAGE;
-                static bool attr_set = false;
-                if (!attr_set) {
-                    e = hipFuncSetAttribute(reinterpret_cast<const void *>(mfma_shrink_direct_kernel<N, W>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-                    if (e != hipSuccess) return;
-                    attr_set = true;
-                }
-                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W>, dim3(tb.n_direct * tb.n), dim3(64 * W), LDS, st, tb);
+                constexpr int W = decltype(w_tag)::value;
+                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W>, dim3(tb.n_direct * tb.n), dim3(64 * W), direct_lds<W>, st, tb);
             };
             if (tb.n_direct * tb.n <= 256) go(std::integral_constant<int, 8>{});  // (a block to a compute unit)
             else go(std::integral_constant<int, 4>{});
         });
-        return e != hipSuccess ? e : hipGetLastError();
+        return hipGetLastError();
     }
     if (batch.n_runs <= 0) return hipSuccess;
     if (batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
@@ -893,21 +904,14 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
         auto go = [&](auto pairs_tag) {
             constexpr bool PAIRS = decltype(pairs_tag)::value;
-            constexpr int LDS = PAIRS ? RING_BYTES : NSTAGE * LORA_TILE_TOKENS * XROW;
-            static bool attr_set = false;
-            if (!attr_set) {
-                e = hipFuncSetAttribute(reinterpret_cast<const void *>(mfma_shrink_kernel<N, PAIRS>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-                if (e != hipSuccess) return;
-                attr_set = true;
-            }
-            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N, PAIRS>, dim3(tb.n_runs * tb.n), dim3(256), LDS, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N, PAIRS>, dim3(tb.n_runs * tb.n), dim3(256), shrink_lds<PAIRS>, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
                      tb.quanta, tb.n_tiles, tb);
         };
         if (tb.any_pairs) go(std::true_type{});  // (a kernel of its own: beside the other body it costs launches without pairs 1 %)
         else go(std::false_type{});
         if (tb.any_pieces) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel<N>, dim3(tb.n_tiles * 8, tb.n), dim3(256), 0, st, tb);
     });
-    return e != hipSuccess ? e : hipGetLastError();
+    return hipGetLastError();
 }
 
 // Longest column run, in passes (7B mixed batch 1898 us with 4, 1866 with 8, 1887 with 16).

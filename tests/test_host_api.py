@@ -32,6 +32,17 @@ def test_library_exports_every_declared_symbol():
     assert sorted(B.EXPORTS) == names
 
 
+def test_launchers_remember_nothing_for_the_whole_process():
+    """What a kernel needs to be launched is set for the device of each cache (its limit of LDS is the device's own), not once per
+    process by whichever call comes first: no variable of a function outlives its call in the files that launch kernels."""
+    csrc = os.path.join(os.path.dirname(B.__file__), "csrc")
+    for name in sorted(os.listdir(csrc)):
+        if name.endswith((".hip", ".cpp")):
+            src = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(csrc, name)).read(), flags=re.S)
+            kept = re.findall(r"^[ \t]+static (?!constexpr|const |_?assert)[^\n(]*;", src, flags=re.M)
+            assert not kept, (name, kept)
+
+
 # ---------------------------------------------------------------------------------------
 def _index_both(T, off, slot, rank, m0):
     rc, got = B.lora_index(T, off, slot, rank, m0)
