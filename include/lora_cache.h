@@ -119,8 +119,8 @@ size_t lora_cache_bytes_required(const lora_cache_config_t *cfg);
 /* ---- pool life cycle ----------------------------------------------------------------- */
 
 /* Carve `dev_pool` (device, 256-byte aligned, caller-owned, must outlive the cache) into slabs and scratch, build the
- * slot table.  A pool of fewer than lora_cache_bytes_required bytes is taken as with LORA_CACHE_SMALL_SCRATCH, if it has the bytes
- * that are required with that flag (LORA_E_NOMEM otherwise).
+ * slot table.  A pool of fewer than lora_cache_bytes_required bytes is taken with scratch for fewer projections at a time, as
+ * many as it has room for, and at the least as with LORA_CACHE_SMALL_SCRATCH (LORA_E_NOMEM if it has not the bytes that are required with that flag).
  * Uploads a small offset table (blocking).  With LORA_CACHE_HOST_ONLY, dev_pool may be
  * NULL and only the slot-table calls work. */
 int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev_pool_bytes, lora_cache_t **out);

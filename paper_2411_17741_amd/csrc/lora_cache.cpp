@@ -284,7 +284,8 @@ bool config_ok(const lora_cache_config_t *cfg)
 
 // Fills every layout field of `c` from the config; used by bytes_required and create alike.  small_scratch: what a group
 // of projections needs and no more -- no further sets, run tables and wide items for batches, staging for one part.
-void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_scratch)
+// max_sets: sets for batches at most; direct: plans have room for the units of a short tile shrink.
+void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_scratch, int max_sets = lora::GEMV_BATCH_MAX_PROJS, bool direct = true)
 {
     c.small_scratch = small_scratch;
     c.proj.assign(cfg->proj, cfg->proj + cfg->n_proj);
@@ -341,7 +342,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     // units of a short tile shrink: no more than a launch of the narrowest projection may have, nor than the tokens make
     size_t narrowest = SIZE_MAX;
     for (const auto &pr : c.proj) narrowest = std::min(narrowest, (size_t)pr.h_in);
-    c.direct_max = c.dtype != LORA_BF16 || small_scratch ? 0
+    c.direct_max = c.dtype != LORA_BF16 || small_scratch || !direct ? 0
                        : (int32_t)std::min({(size_t)lora::DIRECT_MAX_UNITS, (size_t)DIRECT_SHRINK_MAX_BYTES / (64 * narrowest),
                                             ((size_t)c.max_tokens / lora::DIRECT_TOKENS + max_tiles) * (LORA_MAX_RANK / lora::DIRECT_ROWS)});
     const int n_tables = small_scratch ? SHRINK_VARIANT_BATCH : SHRINK_VARIANTS;
@@ -361,7 +362,7 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
     c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
-    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>(lora::GEMV_BATCH_MAX_PROJS, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
+    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>((size_t)max_sets, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
                                      std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / (c.v_set_bytes + c.vtag_set_bytes)));
     cur += c.v_set_bytes * c.n_sets;
     // partial sums of the tile shrink: two slots per run and projection; a launch has at most SHRINK_MAX_RUNS blocks
@@ -393,6 +394,23 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     c.off_stage = cur;
     cur += c.stage_cap * N_STAGES;
     c.total = cur;
+}
+
+// The layout for a pool of fewer bytes than are required: fewer sets for batches (down to those of a batch with tiles), then without the units of
+// a short tile shrink and with as many sets as there is room for, then the small scratch.
+void fit_layout(lora_cache &c, const lora_cache_config_t *cfg, size_t bytes)
+{
+    if (!(cfg->flags & LORA_CACHE_SMALL_SCRATCH)) {
+        for (int direct = 1; direct >= 0; --direct)
+            for (int sets = direct ? c.n_sets : std::min(c.n_sets, lora::BATCH_MAX_PROJS); sets >= (direct ? lora::BATCH_MAX_PROJS : lora::GROUP_MAX_PROJS); --sets) {
+                lora_cache t;
+                compute_layout(t, cfg, false, sets, direct != 0);
+                if (t.total > bytes) continue;
+                compute_layout(c, cfg, false, sets, direct != 0);
+                return;
+            }
+    }
+    compute_layout(c, cfg, true);
 }
 
 char *slab_ptr(const lora_cache &c, int32_t layer, int32_t proj, int32_t slot)
@@ -1044,7 +1062,7 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
     lora_cache *c = new (std::nothrow) lora_cache;
     if (!c) return LORA_E_NOMEM;
     compute_layout(*c, cfg, (cfg->flags & LORA_CACHE_SMALL_SCRATCH) != 0);
-    if (!c->host_only && dev_pool_bytes < c->total) compute_layout(*c, cfg, true);
+    if (!c->host_only && dev_pool_bytes < c->total) fit_layout(*c, cfg, dev_pool_bytes);
     c->slots.resize(c->n_slots);
     for (int32_t s = 0; s < c->n_slots; ++s) {
         c->slots[s].cls = class_of_slot(*c, s);

@@ -131,6 +131,46 @@ def test_small_scratch(batch, how, monkeypatch):
         _same(got, want, "bf16", f"output {k}")
 
 
+@pytest.mark.parametrize("batch", ["popular", "mixed"])
+def test_a_pool_with_room_for_fewer_sets(batch, monkeypatch):
+    """A pool of fewer bytes than are required runs lists as batches of as many projections as it has room for, not four at a time:
+    a byte short, and 14 sets short.  The results are those of a full pool."""
+    from paper_2411_17741_amd import binding as B0
+
+    required = B0.lora_cache_bytes_required
+
+    def smallest(cfg):
+        cfg.flags |= B0.LORA_CACHE_SMALL_SCRATCH
+        n = required(cfg)
+        cfg.flags &= ~B0.LORA_CACHE_SMALL_SCRATCH
+        return n
+
+    sizes = [required, lambda cfg: required(cfg) - 1, lambda cfg: required(cfg) - 14 * 1024 * cfg.max_tokens, smallest]  # (a set has 1 KB per token)
+    entries, outs = [], []
+    for size in sizes:
+        monkeypatch.setattr(B0, "lora_cache_bytes_required", size)
+        B, pool, plan, T, normal = _setup(*BATCHES[batch], 2)
+        try:
+            xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
+            y = [normal(T, h_out) for _ in range(2) for _i, h_out in PROJS]
+            descs = B.make_descs([(l, p, xs[0 if p < 6 else p - 5].data_ptr(), y[l * len(PROJS) + p].data_ptr()) for l in range(2) for p in range(len(PROJS))])
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
+            pool.check_fault()
+            n = 0
+            for p in range(len(PROJS)):  # entries of the first batch
+                rc, units, _toks = B.lora_plan_dump(pool.handle, plan, p)
+                assert rc == B.LORA_OK
+                n += len(set(int(w) for w in units[units["kind"] == B.LORA_UNIT_BATCH_SHRINK]["where"]))
+            entries.append(n)
+            outs.append(y)
+        finally:
+            pool.close()
+    assert entries[0] == 18 and entries[1] == 18 and 4 < entries[2] < 18 and entries[3] == 4, entries
+    for y in outs[1:]:
+        for k, (got, want) in enumerate(zip(y, outs[0])):
+            _same(got, want, "bf16", f"output {k}")
+
+
 @pytest.mark.parametrize("batch", ["decode", "decode, no tiles", "mixed"])
 def test_entries_that_depend_on_earlier_ones(batch):
     """Each list in order: an output that is a later entry's input; a later output over an earlier input; one output twice;
