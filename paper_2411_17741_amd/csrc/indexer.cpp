@@ -18,19 +18,20 @@ struct ShortSeg {
 class RankOf {
     std::vector<int32_t> slots_, ranks_;
     size_t mask_;
+    int shift_ = 28;
 
 public:
     explicit RankOf(int32_t n)
     {
         size_t cap = 16;
-        while (cap < 2 * (size_t)n) cap *= 2;
+        while (cap < 2 * (size_t)n) cap *= 2, --shift_;
         slots_.assign(cap, -1);
         ranks_.resize(cap);
         mask_ = cap - 1;
     }
     bool agrees(int32_t slot, int32_t rank)  // slot >= 0; the first rank of a slot is the one that counts
     {
-        size_t i = (size_t)((uint32_t)slot * 0x9E3779B1u) & mask_;
+        size_t i = (size_t)(((uint32_t)slot * 0x9E3779B1u) >> shift_);  // the product's high bits: its low ones are alike for slots a power of two apart
         while (slots_[i] >= 0 && slots_[i] != slot) i = (i + 1) & mask_;
         if (slots_[i] < 0) slots_[i] = slot, ranks_[i] = rank;
         return ranks_[i] == rank;

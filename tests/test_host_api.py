@@ -74,6 +74,24 @@ def test_indexer_matches_oracle_on_random_batches():
         _index_both(int(off[-1]), off, slot, rank, m0)
 
 
+def test_indexing_time_does_not_depend_on_how_slots_are_numbered():
+    """60000 one-token segments, each of a slot of its own: slots a power of two apart take no longer than neighbours (they took three
+    times as long when they met in the table that checks their ranks)."""
+    import time
+
+    n, best = 60000, []
+    for step in (1, 1 << 10, 1 << 15):
+        off, slot, rank = np.arange(n + 1, dtype=np.int32), np.arange(n, dtype=np.int32) * step, np.full(n, 16, np.int32)
+        times = []
+        for _ in range(4):
+            t = time.perf_counter()
+            rc, got = B.lora_index(n, off, slot, rank, 0)
+            times.append(time.perf_counter() - t)
+            assert rc == B.LORA_OK and len(got["groups"]) == n
+        best.append(min(times))
+    assert max(best) < 2 * best[0], best
+
+
 # ---------------------------------------------------------------------------------------
 # The lists the kernels read (lora_plan_dump of a host-only cache: the staged copy of the plan), checked
 # against the oracle's token map through coverage properties -- no kernel item shape is restated here.
