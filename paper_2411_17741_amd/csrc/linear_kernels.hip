@@ -879,31 +879,37 @@ static hipError_t launch_small(const ApplyArgs &a, const void *Wt, const LinearL
     return hipGetLastError();
 }
 
+LinearShape linear_shape(int n_rt, int h_in, int h_out, size_t split_scratch_bytes, int n_split_state, int n_cu)
+{
+    const int n_k = h_in / LBK, n_tiles = (n_rt + 3) / 4 * ((h_out + LBN - 1) / LBN);
+    int parts, n_tail;
+    // (the estimate reads 15 to 25 % more than 256 x 256 tiles take where the other kernel comes near them)
+    const double big = 0.85 * linear_split_shape(n_tiles, n_k, n_cu, split_scratch_bytes / LINEAR_SHARE_BYTES, parts, n_tail);
+    const int tiles64 = n_rt * (h_out / 64), tiles128 = (n_rt + 1) / 2 * (h_out / 64);
+    const double l2_bytes = 2.0 * h_in * (64.0 * n_rt + h_out / 8);
+    int p64 = 1;
+    for (int p = 2; p <= MAX_PARTS && tiles64 <= n_split_state && 4 * p <= n_k && (size_t)tiles64 * p * 64 * 64 * 4 <= split_scratch_bytes; ++p)
+        if (small_estimate(tiles64, n_k, 1, p, l2_bytes) < small_estimate(tiles64, n_k, 1, p64, l2_bytes)) p64 = p;
+    const double t64 = small_estimate(tiles64, n_k, 1, p64, l2_bytes), t128 = small_estimate(tiles128, n_k, 2, 1, l2_bytes);
+    // (a ring of four where all blocks fit side by side with it: 992 x 1024 x 1024 8.1 us, 8.8 with three; 2283 x 1088 x 1088 17.0, 14.4 with three)
+    if (t64 <= big && t64 <= t128) return {64, tiles64 * p64 <= 2 * n_cu ? 4 : 3, tiles64, p64 > 1 ? tiles64 : 0, p64};
+    if (t128 <= big) return {128, 3, tiles128, 0, 1};
+    if (n_tail > n_split_state) parts = 1, n_tail = 0;
+    return {LBM, 2, n_tiles, n_tail, parts};
+}
+
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearList &list, void *split_scratch,
                                size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (list.n_rt <= 0) return hipSuccess;
-    const int n_k = a.h_in / LBK, n_mt = (list.n_rt + 3) / 4, n_nt = (a.h_out + LBN - 1) / LBN, n_tiles = n_mt * n_nt;
-    int parts, n_tail;
-    // (the estimate reads 15 to 25 % more than 256 x 256 tiles take where the other kernel comes near them)
-    const double big = 0.85 * linear_split_shape(n_tiles, n_k, n_cu, split_scratch ? split_scratch_bytes / LINEAR_SHARE_BYTES : 0, parts, n_tail);
-    const int tiles64 = list.n_rt * (a.h_out / 64), tiles128 = (list.n_rt + 1) / 2 * (a.h_out / 64);
-    const double l2_bytes = 2.0 * a.h_in * (64.0 * list.n_rt + a.h_out / 8);
-    int p64 = 1;
-    for (int p = 2; p <= MAX_PARTS && split_scratch && tiles64 <= n_split_state && 4 * p <= n_k && (size_t)tiles64 * p * 64 * 64 * 4 <= split_scratch_bytes; ++p)
-        if (small_estimate(tiles64, n_k, 1, p, l2_bytes) < small_estimate(tiles64, n_k, 1, p64, l2_bytes)) p64 = p;
-    const double t64 = small_estimate(tiles64, n_k, 1, p64, l2_bytes), t128 = small_estimate(tiles128, n_k, 2, 1, l2_bytes);
-    if (t64 <= big && t64 <= t128) {  // (a ring of four where all blocks fit side by side with it: 992 x 1024 x 1024 8.1 us, 8.8 with three; 2283 x 1088 x 1088 17.0, 14.4 with three)
-        if (tiles64 * p64 <= 2 * n_cu) return launch_small<1, 4>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
-        return launch_small<1, 3>(a, Wt, list, p64, split_scratch, split_state, st, tm, done);
-    }
-    if (t128 <= big) return launch_small<2, 3>(a, Wt, list, 1, split_scratch, split_state, st, tm, done);
-    if (n_tail > n_split_state) parts = 1, n_tail = 0;
-    const LinearSplit sp{n_tiles - n_tail, parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
-    const int blocks = n_tiles - n_tail + n_tail * parts;
-    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(blocks), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
-             list, n_mt, n_nt, sp);
+    const LinearShape sh = linear_shape(list.n_rt, a.h_in, a.h_out, split_scratch_bytes, n_split_state, n_cu);
+    if (sh.rows == 64 && sh.ring == 4) return launch_small<1, 4>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
+    if (sh.rows == 64) return launch_small<1, 3>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
+    if (sh.rows == 128) return launch_small<2, 3>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
+    const LinearSplit sp{sh.tiles - sh.split, sh.parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
+    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(sp.n_whole + sh.split * sh.parts), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
+             list, (list.n_rt + 3) / 4, (a.h_out + LBN - 1) / LBN, sp);
     return hipGetLastError();
 }
 

@@ -1778,6 +1778,14 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
         tile_tokens(tiles[i], tok_list);
         put_unit(LORA_UNIT_TILE, tile_off[i], tiles[i].n_tok, tiles[i].row, tiles[i].rank, 0, 0, 0, tiles[i].alpha);
     }
+    // the units of a short tile shrink
+    const lora::DevItem *direct = reinterpret_cast<const lora::DevItem *>(buf + p->off_direct);
+    for (int32_t i = 0; i < p->n_direct; ++i) {
+        const int32_t off = nt;
+        tile_tokens(direct[i], tok_list);
+        put_unit(LORA_UNIT_DIRECT_SHRINK, off, direct[i].n_tok, direct[i].row, direct[i].rank, direct[i].a, std::min(direct[i].a + lora::DIRECT_ROWS, direct[i].rank),
+                 direct_shrink(p->n_direct, c->proj[proj].h_in) > 0 ? 1 : 0, direct[i].alpha);
+    }
     // the tile shrink's pieces for this projection's h_in, per run table, walked as the kernel walks them; and the
     // scratch slots the reduce adds up per tile
     for (int v = 0; v < SHRINK_VARIANTS && p->n_tiles > 0; ++v) {
@@ -1915,6 +1923,10 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
                 if (!segment_of(r)) linear_row(r);
             put_unit(LORA_UNIT_LINEAR_ROWS, off, nt - off, -1, 0, 0, 0, mark, 0.f);
         }
+    }
+    if (p->n_lin_rows > 0) {
+        const lora::LinearShape sh = lora::linear_shape(p->n_lin_rows, c->proj[proj].h_in, c->proj[proj].h_out, c->vpart_bytes, N_LINEAR_SPLITS, c->n_cu);
+        put_unit(LORA_UNIT_LINEAR_SHAPE, nt, 0, -1, 0, sh.rows, sh.tiles, sh.split << 8 | sh.parts, (float)sh.ring);
     }
     *n_units = nu;
     *n_toks = nt;

@@ -11,6 +11,8 @@ oracle's `token_map` says (which slot, which rank) and cover the work once:
   rank rows [0, rank) exactly once (rows of the zero padding up to the next multiple of 8 at most
   once) and, per projection, the expand units cover columns [0, h_out) exactly once;
   the same holds for the units of a list call's batch, entry by entry, with the items and with the wide items;
+* units of a short tile shrink: every (tile token, rank row) once, in units of at most 16 x 16, and they are marked as what a call works
+  through exactly where it takes in no more than 225 MB that way;
 * row units of the fused linear path: every token of the batch exactly once.
 """
 from __future__ import annotations
@@ -51,6 +53,25 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
             assert list(toks_of(u)) == wt and (u["slot"], u["rank"]) == (slot, rank)
             assert 1 <= u["n_tok"] <= B.LORA_TILE_TOKENS
             same_entry(u)
+
+        # --- short tile shrink
+        direct = units[units["kind"] == B.LORA_UNIT_DIRECT_SHRINK]
+        if len(direct):
+            cover = np.zeros((T, B.LORA_MAX_RANK), np.int8)
+            for u in direct:
+                same_entry(u)
+                assert u["n_tok"] <= 16 and 0 <= u["lo"] < u["hi"] <= u["lo"] + 16 and u["hi"] <= u["rank"] and u["lo"] % 16 == 0
+                assert len(set(toks_of(u))) == u["n_tok"]
+                cover[toks_of(u), u["lo"] : u["hi"]] += 1
+            in_tiles = np.asarray(sorted(t for tk in want_tile_toks for t in tk), np.int64)
+            want_cover = np.zeros_like(cover)
+            for t in in_tiles:
+                want_cover[t, : tm_rank[t]] = 1
+            assert (cover == want_cover).all()
+            assert (direct["where"] == (len(direct) * 64 * h_in <= 225000000)).all()
+        elif len(tiles) and bf16:  # none: more than a plan has room for
+            n = sum(-(-len(tk) // 16) * -(-int(r) // 16) for tk, (_o, _n, _s, r, _t, _l) in zip(want_tile_toks, want["tiles"]))
+            assert n > 2048 or n * 64 * min(i for i, _o in projs) > 225000000
 
         # --- tile shrink: under every run table the pieces of a tile cover its input columns [0, h_in) once, in pieces
         # of whole 128-column stages; runs are walked in order, each at most a tail, whole tiles and a head; pieces that
