@@ -7,21 +7,37 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("lens,h_in,h_out", [
-    ([300], 4096, 1024),                     # 8 tiles of 256 x 256: eight parts
-    ([1000], 4160, 1280),                    # 25 tiles, 65 k stages: five parts
-    ([700], 11008, 2304),                    # 36 tiles, 172 k stages: seven parts
-    ([1, 700, 900, 2, 833], 2112, 1024),     # 44 tiles, 33 k stages: three parts
-    ([4000, 100], 4096, 1088),               # 85 tiles, the last column panel 64 wide: three parts
-    ([3100], 2048, 2432),                    # 130 tiles: whole
-    ([2000, 17], 4096, 4096),                # 144 tiles: whole
-    ([1700], 4096, 4096),                    # 128 tiles: two parts
-    ([4096, 300], 2112, 4096),               # a whole round, then 32 tiles in three parts
-    ([16384, 190], 512, 1024),               # a whole round, then 8 tiles in two parts (eight k stages)
-    ([63], 64, 64),                          # one k stage
-    ([65, 5], 192, 320),                     # three k stages
+def _shape(B, pool, plan):
+    """(rows of a tile, stages of a ring, tiles, tiles split along k, parts of each) of the plan's product of projection 0"""
+    rc, units, _toks = B.lora_plan_dump(pool.handle, plan, 0)
+    assert rc == B.LORA_OK
+    (u,) = units[units["kind"] == B.LORA_UNIT_LINEAR_SHAPE]
+    return int(u["lo"]), int(u["alpha"]), int(u["hi"]), int(u["where"]) >> 8, int(u["where"]) & 255
+
+
+# (the shape on 256 compute units: on another part these cases test what they reach there)
+@pytest.mark.parametrize("lens,h_in,h_out,shape", [
+    ([300], 4096, 1024, (64, 4, 80, 80, 3)),                  # tiles of 64 x 64, split along k
+    ([1000], 4160, 1280, (64, 4, 320, 0, 1)),                 # of 64 x 64, 65 k stages
+    ([1, 100, 30], 512, 11072, (64, 3, 519, 0, 1)),           # of 64 x 64, more than fit side by side with a ring of four
+    ([1, 700, 900, 2, 833], 2112, 1024, (128, 3, 320, 0, 1)), # of 128 x 64, 33 k stages, an odd number of runs
+    ([740], 8256, 1024, (256, 2, 12, 12, 8)),                 # eight parts, 129 k stages
+    ([700], 11008, 2304, (256, 2, 27, 27, 8)),                # eight parts, 172 k stages
+    ([700], 6208, 1536, (256, 2, 18, 18, 7)),                 # seven parts, 97 k stages
+    ([500], 8256, 3072, (256, 2, 36, 36, 6)),                 # six parts, 129 k stages
+    ([1300], 4160, 1536, (256, 2, 36, 36, 5)),                # five parts, 65 k stages
+    ([2300], 4160, 1088, (256, 2, 50, 50, 4)),                # four parts, the last column panel 64 wide
+    ([1300], 2112, 2560, (256, 2, 60, 60, 3)),                # three parts, 33 k stages
+    ([4000, 100], 4096, 1088, (256, 2, 85, 85, 3)),           # three parts, the last column panel 64 wide
+    ([3100], 2048, 2432, (256, 2, 130, 0, 1)),                # whole
+    ([2000, 17], 4096, 4096, (256, 2, 128, 128, 2)),          # two parts
+    ([1700], 4096, 4096, (256, 2, 112, 112, 2)),              # two parts
+    ([4096, 300], 2112, 4096, (256, 2, 288, 32, 3)),          # a whole round, then 32 tiles in three parts
+    ([16384, 190], 512, 1024, (256, 2, 260, 4, 2)),           # a whole round, then 4 tiles in two parts (eight k stages)
+    ([63], 64, 64, (64, 4, 2, 0, 1)),                         # one k stage
+    ([65, 5], 192, 320, (64, 4, 10, 0, 1)),                   # three k stages
 ])
-def test_linear_against_torch(lens, h_in, h_out):
+def test_linear_against_torch(lens, h_in, h_out, shape):
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
@@ -39,6 +55,7 @@ def test_linear_against_torch(lens, h_in, h_out):
         for i, r in enumerate(ranks):
             pool.fill(i, i + 1, r, 0.5 + i, 0, 0, A[i].cpu(), Bm[i].cpu())
         plan = pool.plan(T, off, slot, np.where(slot >= 0, np.asarray(ranks)[slot], 0).astype(np.int32))
+        assert _shape(B, pool, plan) == shape or torch.cuda.get_device_properties(0).multi_processor_count != 256
         space = torch.empty(T * h_out, dtype=torch.float32, device="cuda")
         ref = x.double() @ wt.double().t()
         for g, s in enumerate(slot):
@@ -109,15 +126,15 @@ def test_rows_of_several_slots(lens, h_in, h_out):
         pool.close()
 
 
-@pytest.mark.parametrize("lens,h_in,h_out", [
-    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 1024, 1088),   # tiles of 64 x 64
-    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 4096, 256),    # of 64 x 64, split along k
-    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 512, 11072),   # of 64 x 64, more of them than fit side by side with a ring of four
-    ([700, 13, 8, 400, 1, 1, 1], 1536, 1536),            # of 128 x 64
-    ([700, 13, 8, 400, 1, 1, 1], 4096, 4096),            # of 256 x 256, split along k
-    ([250, 12, 250, 1, 8, 8, 8, 8, 8, 8, 8, 8, 1, 2500], 2048, 2432),  # of 256 x 256, whole
+@pytest.mark.parametrize("lens,h_in,h_out,shape", [
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 1024, 1088, (64, 4, 1)),   # tiles of 64 x 64
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 4096, 256, (64, 4, 5)),    # of 64 x 64, split along k
+    ([8, 9, 15, 16, 17, 1, 1, 1, 31, 33], 512, 11072, (64, 3, 1)),   # of 64 x 64, more of them than fit side by side with a ring of four
+    ([700, 13, 8, 400, 1, 1, 1], 1536, 1536, (128, 3, 1)),           # of 128 x 64
+    ([700, 13, 8, 400, 1, 1, 1], 4096, 4096, (256, 2, 3)),           # of 256 x 256, split along k
+    ([250, 12, 250, 1, 8, 8, 8, 8, 8, 8, 8, 8, 1, 2500], 2048, 2432, (256, 2, 1)),  # of 256 x 256, whole
 ])
-def test_infinities_stay_with_their_adapter(lens, h_in, h_out):
+def test_infinities_stay_with_their_adapter(lens, h_in, h_out, shape):
     """Infinities and NaN in one adapter's B: the rows of every other segment, of the requests on the GEMV path and of those without
     an adapter are bit for bit what they are beside the same adapter with finite weights, whichever block of 16 rows they share
     with it; so are its own rows in the columns that are finite."""
@@ -148,6 +165,8 @@ def test_infinities_stay_with_their_adapter(lens, h_in, h_out):
                 pool.fill(i, i + 1, int(r), 1.0, 0, 0, A[i].cpu(), w.cpu())
             torch.cuda.synchronize()
             plan = pool.plan(T, off, slot, np.where(slot >= 0, rank_of[slot], 0).astype(np.int32))
+            rows, ring, _tiles, _split, parts = _shape(B, pool, plan)
+            assert (rows, ring, parts) == shape or torch.cuda.get_device_properties(0).multi_processor_count != 256
             y = torch.full((T, h_out), 7.0, dtype=torch.bfloat16, device="cuda")
             B.check(B.lora_linear_plan(pool.handle, plan, 0, 0, x.data_ptr(), wt.data_ptr(), y.data_ptr(), 2.0,
                                        torch.cuda.current_stream().cuda_stream, space.data_ptr(), space.numel() * 4))
@@ -166,7 +185,7 @@ def test_infinities_stay_with_their_adapter(lens, h_in, h_out):
         pool.close()
 
 
-@pytest.mark.parametrize("T,h_in,h_out,tiles", [(300, 4096, 1024, 8), (700, 11008, 2304, 27), (1100, 4096, 4096, 80), (2048, 4096, 4096, 128)])
+@pytest.mark.parametrize("T,h_in,h_out,tiles", [(760, 8256, 1024, 12), (700, 11008, 2304, 27), (1100, 4096, 4096, 80), (2048, 4096, 4096, 128)])
 def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
     """What happens when a part is done before another has started, forced from the host: the tiles' state (16 bytes each,
     behind the slabs: parts started, way, parts arrived, parts that have read) says so before the launch.  Bit for bit the
@@ -180,6 +199,7 @@ def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
     try:
         pool.fill(0, 1, 16, 1.0, 0, 0, normal(h_in, 16, sigma=0.02).cpu(), normal(16, h_out, sigma=0.02).cpu())
         plan = pool.plan(T, np.asarray([0, T], np.int32), np.zeros(1, np.int32), np.full(1, 16, np.int32))
+        assert _shape(B, pool, plan)[::2] == (256, tiles, _shape(B, pool, plan)[4]) and _shape(B, pool, plan)[3] == tiles
         x, wt = normal(T, h_in), normal(h_out, h_in, sigma=0.02)
         _rc, slab, n = B.lora_cache_slab(pool.handle, 0, 0, 0)
         state = pool.buf[slab + n - pool.buf.data_ptr():][: 16 * tiles].view(torch.int32).view(tiles, 4)
@@ -200,28 +220,30 @@ def test_tiles_finished_by_the_last_part_alone(T, h_in, h_out, tiles):
         pool.close()
 
 
-def test_split_products_on_a_busy_device():
+@pytest.mark.parametrize("T,h,h_out,shape", [(1100, 4096, 4096, (256, 2, 80, 80, 3)), (300, 4096, 1024, (64, 4, 80, 80, 3))])
+def test_split_products_on_a_busy_device(T, h, h_out, shape):
     """Launches whose last round is all parts of split tiles (80 tiles of three parts) from two caches on two streams beside
     matrix products on a third: parts get their places late and in whatever order, and a tile whose parts are not all running
-    when its first part is done is finished by the last of them alone.  The results are those of one launch by itself, bit
-    for bit."""
+    when its first part is done is finished by the last of them alone (tiles of 64 x 64 always are: there the last part may
+    find the others' sums before it has left its own, or after).  The results are those of one launch by itself, bit for bit."""
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
-    h, T, rank, n = 4096, 1100, 16, 24
+    rank, n = 16, 24
     gen = torch.Generator(device="cuda").manual_seed(7)
     normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
-    A, Bm = normal(h, rank, sigma=0.02).cpu(), normal(rank, h, sigma=0.02).cpu()
-    x, wt = [normal(T, h) for _ in range(2)], [normal(h, h, sigma=0.02) for _ in range(2)]
-    y = [[torch.empty(T, h, dtype=torch.bfloat16, device="cuda") for _ in range(n)] for _ in range(2)]
+    A, Bm = normal(h, rank, sigma=0.02).cpu(), normal(rank, h_out, sigma=0.02).cpu()
+    x, wt = [normal(T, h) for _ in range(2)], [normal(h_out, h, sigma=0.02) for _ in range(2)]
+    y = [[torch.empty(T, h_out, dtype=torch.bfloat16, device="cuda") for _ in range(n)] for _ in range(2)]
     a, b, c = normal(2048, 2048), normal(2048, 2048), torch.empty(2048, 2048, dtype=torch.bfloat16, device="cuda")
-    pools = [LoraPool([(h, h)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=1) for _ in range(2)]
+    pools = [LoraPool([(h, h_out)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=1) for _ in range(2)]
     streams = [torch.cuda.Stream() for _ in range(3)]
     try:
         plans = []
         for q in pools:
             q.fill(0, 1, rank, 1.0, 0, 0, A, Bm)
             plans.append(q.plan(T, np.asarray([0, T], np.int32), np.zeros(1, np.int32), np.full(1, rank, np.int32)))
+        assert _shape(B, pools[0], plans[0]) == shape or torch.cuda.get_device_properties(0).multi_processor_count != 256
         torch.mm(a, b, out=c)
         torch.cuda.synchronize()
 
