@@ -62,7 +62,8 @@ def _same(got, want, dtype, what):
 def test_batches_against_single_applies(batch, dtype, flags):
     from paper_2411_17741_amd import binding as B0
 
-    layers = 9  # 81 entries: more than a batch holds
+    layers = 14
+    assert layers * len(PROJS) > 120  # more than a batch holds, of GEMV work alone or with tiles
     fl = B0.LORA_CACHE_SPLIT_GEMV if flags == "split" else 0
     B, pool, plan, T, normal = _setup(*BATCHES[batch], layers, dtype, fl)
     try:
@@ -238,14 +239,16 @@ def _replays_match(pool, xs, prepare, call, outputs):
             assert torch.equal(a, b), f"output {k}"
 
 
-# items and wide items, several token counts and ranks, tiles beside them; 81 entries: two batches, the second with fewer
-# projections than the first
-@pytest.mark.parametrize("batch,layers", [("one token", 3), ("decode", 3), ("popular", 3), ("mixed", 3), ("one token", 9), ("decode", 9)])
+# items and wide items, several token counts and ranks, tiles beside them; 126 entries: two batches at least, the second with fewer projections than
+# the first (120 of GEMV work alone, then 6)
+@pytest.mark.parametrize("batch,layers", [("one token", 3), ("decode", 3), ("popular", 3), ("mixed", 3), ("one token", 14), ("decode, no tiles", 14),
+                                          ("popular", 14), ("decode", 14)])
 def test_a_captured_batch_replays(batch, layers):
     B, pool, plan, T, normal = _setup(*BATCHES[batch], layers)
     try:
         xs = [normal(T, 512), normal(T, 192), normal(T, 1088), normal(T, 2112)]
         x_of = lambda p: xs[0 if p < 6 else p - 5]
+        assert layers == 3 or layers * len(PROJS) > 120
         base = [normal(T, h_out) for _ in range(layers) for _i, h_out in PROJS]
         y = [t.clone() for t in base]
         descs = B.make_descs([(l, p, x_of(p).data_ptr(), y[l * len(PROJS) + p].data_ptr()) for l in range(layers) for p in range(len(PROJS))])
