@@ -327,3 +327,50 @@ def test_linear_with_many_requests(n_prompt, workspace):
             _same(y, want, "bf16", f"prompt {n_prompt}, workspace {workspace}")
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("split", [False, True])
+def test_a_list_large_enough_for_the_side_stream(split):
+    """From 4 GB of the tile tokens' activations and outputs in a batch up the GEMV launch runs beside the tile kernels: eager and replayed,
+    with the GEMV phases as one launch and as two, bit for bit what the same kernels give on one stream."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    h, layers, ranks = 4096, 32, [16, 128, 40, 8]
+    lens = [1800, 1800, 1801] + [1] * 90
+    slot = np.asarray([i % 4 if i % 7 != 6 else -1 for i in range(len(lens))], np.int32)
+    T = sum(lens)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda", dtype=torch.bfloat16).mul_(sigma)
+    A, Bm = [normal(h, r, sigma=0.02).cpu() for r in ranks], [normal(r, h, sigma=0.02).cpu() for r in ranks]
+    x = normal(T, h)
+    base = normal(layers, T, h)
+    y = base.clone()
+    outs = []
+    for flags in (B.LORA_CACHE_NO_OVERLAP, 0):
+        flags |= B.LORA_CACHE_SPLIT_GEMV if split else 0
+        pool = LoraPool([(h, h)], layers, [128], [4], B.LORA_BF16, max_tokens=T, max_segments=len(lens), mfma_min_tokens=100, flags=flags)
+        try:
+            for layer in range(layers):
+                for s, r in enumerate(ranks):
+                    pool.fill(s, s + 1, r, 0.5 + s, layer, 0, A[s], Bm[s])
+            torch.cuda.synchronize()
+            plan = pool.plan(T, off, slot, np.where(slot >= 0, np.asarray(ranks)[slot], 0).astype(np.int32))
+            rc, units, _toks = B.lora_plan_dump(pool.handle, plan, 0)
+            assert rc == B.LORA_OK and (units["kind"] == B.LORA_UNIT_GEMV_SHRINK).any()
+            n_tile = int(units[units["kind"] == B.LORA_UNIT_TILE]["n_tok"].sum())
+            runs = units[(units["kind"] == B.LORA_UNIT_TILE_SHRINK) & (units["where"] >> 20 == 6)]["where"] & 0xFFFFF
+            assert layers * 2 * n_tile * 3 * h >= 4e9 and runs.max() < 32  # the 32 projections are one batch: 1024 runs
+            descs = B.make_descs([(layer, 0, x.data_ptr(), y[layer].data_ptr()) for layer in range(layers)])
+            call = lambda: B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
+            y.copy_(base)
+            call()
+            torch.cuda.synchronize()
+            pool.check_fault()
+            outs.append(y.clone())
+            if not flags & B.LORA_CACHE_NO_OVERLAP:
+                _replays_match(pool, [x], lambda: y.copy_(base), call, [y])
+        finally:
+            pool.close()
+    assert torch.equal(outs[0], outs[1]) and not torch.equal(outs[0], base)
