@@ -63,10 +63,11 @@ enum {
      * else as two launches.  These two flags take the choice away: */
     LORA_CACHE_FUSED_GEMV = 2,    /* always one launch */
     LORA_CACHE_SPLIT_GEMV = 4,    /* always two launches */
-    LORA_CACHE_NO_OVERLAP = 16,   /* every kernel of an apply on the caller's stream: by default the GEMV launch of a batch that
-                                     also has tiles runs on a stream of the cache's own, forked off the caller's stream and
-                                     joined to it again inside the call, side by side with the tile kernels (different tokens) */
-    LORA_CACHE_SMALL_SCRATCH = 32, /* scratch for up to 4 projections at a time instead of up to 64, staging for one part of an adapter:
+    LORA_CACHE_NO_OVERLAP = 16,   /* every kernel of an apply on the caller's stream: by default the GEMV launch of a batch whose
+                                     tile kernels have some milliseconds of work (4 GB of activations and outputs) runs on a stream
+                                     of the cache's own, forked off the caller's stream and joined to it again inside the call,
+                                     side by side with the tile kernels (different tokens) */
+    LORA_CACHE_SMALL_SCRATCH = 32, /* scratch for up to 4 projections at a time instead of up to 120, staging for one part of an adapter:
                                      see lora_cache_bytes_required */
     LORA_CACHE_DIRECT_FILL = 8    /* fills read pinned host memory from the repack kernel itself instead of copying it
                                      to a staging buffer first: about twice the fill rate on an idle device, but applies
@@ -110,7 +111,7 @@ typedef struct {
 size_t lora_adapter_bytes(int32_t h_in, int32_t h_out, int32_t rank, int32_t dtype);
 
 /* Bytes of the pool: slabs of every (layer, projection, slot) + scratch + plan buffers + fill staging.  0 on a bad config.
- * The scratch holds the intermediates of up to 64 projections that one list call works on at a time (as many as fit into
+ * The scratch holds the intermediates of up to 120 projections that one list call works on at a time (as many as fit into
  * 512 MB), up to 85 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
  * most 48 MB of partial sums and staging for one part of an adapter: the same results, but list calls run 4
  * projections at a time, launches with many one-token requests and split tiles of the fused product have less to work with, and staged fills travel part by part. */
@@ -298,8 +299,8 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out);
  * the TILE units and the tokens of the GEMV units partition the batch's tokens that have an
  * adapter; every unit names the slot and rank of its tokens' segments; for every GEMV token the
  * SHRINK units cover rank rows [0, rank) exactly once and the EXPAND units cover output columns
- * [0, h_out) exactly once; the LINEAR_ROWS units (bf16 caches: the row tiles of lora_linear_plan)
- * cover every token of the batch exactly once; for every tile and run table the TILE_SHRINK units
+ * [0, h_out) exactly once; the LINEAR_ROWS units (bf16 caches: the rows of lora_linear_plan,
+ * per tile those that take its adapter's products, then the others) cover every token of the batch exactly once; for every tile and run table the TILE_SHRINK units
  * (the pieces the tile's input columns are worked on in) cover [0, h_in) exactly once, the pieces
  * that are not whole tiles leave their partial sums in distinct scratch slots, and the TILE_SUM
  * units (the slots the reduce kernel adds up for the tile) name exactly those slots.
@@ -381,8 +382,9 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
  * the batch; tokens without an adapter get x[t] . W.  Wt is the device weight [h_out][h_in], bf16 --
  * W transposed, the layout a linear layer keeps its weight in; y [T][h_out] is written only (it
  * need not hold anything on entry, and must not overlap x).  The shrink runs as in lora_apply_plan;
- * then one matrix-core kernel computes the base product over row tiles of 64 tokens and adds the
- * adapter product of the tiles as one more slab of the contraction.  Tokens on the GEMV path get their
+ * then one matrix-core kernel computes the base product over one list of all tokens, those of an adapter next to each other,
+ * and adds the adapter products of the tile tokens as one more slab of the contraction (a row takes the products of its own adapter
+ * alone, whatever rows are beside it).  Tokens on the GEMV path get their
  * adapter term from the GEMV kernels beforehand, and the matrix-core kernel adds it to their rows
  * before the one rounding of the output: as fp32 through `workspace` (device, caller-owned, 16-byte
  * aligned, at least lora_linear_workspace_bytes() bytes: T * h_out floats when the plan has GEMV

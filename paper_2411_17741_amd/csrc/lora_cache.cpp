@@ -57,11 +57,13 @@ double tile_tokens_us(int32_t n_tok, int32_t rank, double width) { return n_tok 
 // base product (0.34 GB) 159 against 155.
 constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // lora_apply's lists, used by one launch, are read where the host writes them (pinned memory, over the link) up to so many wavefronts that read an item: no upload
-// launch.  16 fp32 tokens 17.2 -> 13.5 us a call, 16 requests 12.6 -> 10.5, 64 requests at 4096 x 4096 (about 2000 wavefronts) 15 -> 12, 200 requests (about 6000) 24 -> 19.5.
+// launch.  us a call with the upload and without: 16 fp32 tokens 16.5 and 8.4, 16 requests at 4096 x 4096 16.0 and 8.2, 64 requests (about 2000 wavefronts) 18.5 and 10.5, 200 requests
+// (about 6000) 23.4 and 12.4.  So too while the link is busy: 64 requests beside copies or staged fills 19 and 12.3, beside fills by a kernel that reads host memory 139 and 101.
 constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
-// 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond (7B mixed batch 2020 us, 2044 on one stream; 13B 918 and 908;
-// 64 requests beside a prompt of 100 tokens 40.6 and 18.3; 224 beside 13670 prompt tokens, eight projections, 815 and 811).
+// 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
+// twice that 3507 and 3568, one layer (2.4 GB) 968 and 954; 13B with four prompts of 512 (1.6 GB) 876 and 797, with 5120 prompt tokens (4 GB) 1188 and 1200; 64 requests beside a prompt of
+// 100 tokens 40.6 and 18.3.  Above the line q alone or q, k, v, o lose: 1417 and 1393 (7B, 4 layers), 512 requests beside 16000 prompt tokens 2769 and 2651.
 constexpr double FORK_MIN_TILE_BYTES = 4e9;
 // Applies that run together in one batch each have their own copy of the intermediate (a set): as many sets as fit into
 // BATCH_SCRATCH_BYTES (0.2 % of the card's memory), a group's at least.  64 one-token requests: 4 MB for 64 sets.

@@ -294,7 +294,7 @@ template <int N> __device__ __forceinline__ void wait_for_all_but()  // the late
 // Wavefront w makes four requests of x rows and 2 NB / 4 of At (the first two wavefronts one more where that is odd), a request being 8 rows, and
 // multiplies token block w of both tiles with every rank block.
 constexpr int SKD = 64, SROW = SKD * 2;        // k elements of a stage and the bytes of a row
-constexpr int RING_BYTES = 3 * (64 + 128) * SROW;  // two slots at rank 128, three to five below: two blocks to a compute unit
+constexpr int RING_BYTES = 3 * (64 + 128) * SROW;  // two slots from rank 65 up, three from 17, four below: two blocks to a compute unit
 static_assert(SK % SKD == 0 && RING_BYTES >= NSTAGE * LORA_TILE_TOKENS * XROW, "pieces are whole stages; the other body's ring is the same memory");
 template <int NB>
 __device__ __forceinline__ void mfma_shrink_pair(const ApplyArgs &a, const DevItem (&it)[2], int st_begin, int n_st, int phase, unsigned char *ring)
@@ -379,11 +379,10 @@ __device__ __forceinline__ void mfma_shrink_pair(const ApplyArgs &a, const DevIt
             slot = slot + 1 == NST ? 0 : slot + 1;
         }
     };
-    last(std::integral_constant<int, 3>{});
     last(std::integral_constant<int, 2>{});
     last(std::integral_constant<int, 1>{});
     last(std::integral_constant<int, 0>{});
-    static_assert(NST >= 2 && NST <= 5, "the walk's last stages");
+    static_assert(NST >= 2 && NST <= 4, "the walk's last stages");
     __bf16 *const out16 = reinterpret_cast<__bf16 *>(a.v);
     const float s_v = a.scale * it[0].alpha;
 #pragma unroll
