@@ -322,7 +322,7 @@ typedef struct {
     int32_t slot, rank;     /* slot found back from the storage row the kernels address; -1, 0: rows without adapter */
     int32_t lo, hi;         /* *_SHRINK: rank rows [lo, hi); *_EXPAND: output columns [lo, hi); TILE_SHRINK: input
                                columns [lo, hi); TILE_SUM: slot number lo of hi; LINEAR_SHAPE: rows of a tile (64, 128: x 64 columns,
-                               256: x 256), tiles; else 0, 0 */
+                               192, 256, 288: x 256), tiles; else 0, 0 */
     int32_t where;          /* GEMV_SHRINK: position in launch order; LINEAR_ROWS: 2 = a tile, 1 = rows of GEMV tokens,
                                0 = rows without adapter; TILE_SHRINK, TILE_SUM: run table << 20 | run (run tables 0..3:
                                launches for 1..4 projections; 4: the one of lora_apply_plan_static; 5, 6: those with at most 64 and

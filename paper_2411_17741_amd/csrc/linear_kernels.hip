@@ -5,8 +5,8 @@
 // and never read: the separate addition of the adapter result to the base output (paper section 3.1)
 // disappears.  This is the variant of the hot path whose roof is the matrix cores, not HBM.
 //
-// Block = 8 wavefronts on 256 rows (four runs of 64) x 256 output columns; wavefront w owns the row half w/4 and the
-// column quarter w%4: 8 x 4 products of 16 x 16 (v_mfma_f32_16x16x32_bf16, 128 accumulator registers).  x rows
+// Block = 8 wavefronts on 32 MB rows (192, 256 or 288; figures below: 256) x 256 output columns; wavefront w owns the row half w/4 and the
+// column quarter w%4: MB x 4 products of 16 x 16 (v_mfma_f32_16x16x32_bf16, 16 MB accumulator registers).  x rows
 // (gathered by token) and Wt rows (Wt[n][k] = W[k][n], the layout a linear layer keeps its weight in) are both
 // contiguous along k: a stage is 64 k of both, 64 KB, brought into LDS by global_load_lds_dwordx4 -- the load writes
 // LDS itself (at the wavefront's base + 16 bytes x lane; checked on the part), so no registers stage the data.
@@ -14,7 +14,7 @@
 // What bounds the loop is that matrix cores, LDS and the load path each need most of a stage's time (products 0.85 us at
 // the peak rate, 192 KB of operand reads, 64 KB of loads): done one after the other by wavefronts in step, with a wait
 // for all loads at the stage's end, a stage took 2 us.  So the two wavefronts of a SIMD (w and w + 4) take turns: a
-// stage is two phases (run 0 and run 1 of the wavefront), a phase a *load section* -- the phase's operand
+// stage is two phases (the first and the second half of the wavefront's row blocks), a phase a *load section* -- the phase's operand
 // reads and the requests for later stages -- and a *product section* of 32 products, with a barrier behind each, and
 // wavefronts 4..7 run one section behind wavefronts 0..3.  The requests are counted, not drained: an LDS half (128 rows
 // of x or Wt) is requested three phases before it is read, as soon as the phase after its last read has begun, and a
@@ -23,7 +23,8 @@
 // the next phase reads landed (vmcnt(8)), and the other group of wavefronts has passed the same point one barrier
 // later, before anybody reads (or overwrites) that half.
 // Measured on 4096 x 4096 x 4096 (one round of 256 blocks): 129.5 us with all wavefronts in step, 98.5 us this way;
-// 8192 x 8192 x 8192: 934 -> 710 us (1.55 PFLOP/s; the vendor library's product 766 us).  Four phases of 16 products
+// 8192 x 8192 x 8192: 934 -> 710 us (1.55 PFLOP/s; the vendor library's product 766 us).  With all units busy the stages take 1.38 us, with 64 of them
+// 0.91 us, the products' own time: what the card sustains then bounds the loop, not its schedule.  Four phases of 16 products
 // take 107 us, operand reads spread evenly over the phases 98 us, requests from the product section 102 us.
 //
 // LDS rows are 128 bytes without padding; bank conflicts are avoided by a swizzle instead: 16-byte slot s of row r
@@ -59,6 +60,7 @@
 // decides: if all parts have started, they share the tile; if not, every part leaves all its sums and ends, and the last
 // to arrive finishes the tile alone.  Either way a row block's sums are added in the same order.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "lora_device.h"
@@ -69,9 +71,10 @@ namespace {
 constexpr int LBM = 256, LBN = 256, LBK = 64;
 constexpr int LROW = LBK * 2;                   // bytes per row of a stage in LDS (swizzled, not padded)
 constexpr int L_HALF = 128 * LROW;              // 128 rows of x or Wt, 64 k: 16 KB
-constexpr int L_LDS = 2 * 4 * L_HALF;           // two stages of x half 0, x half 1, Wt half 0, Wt half 1
 constexpr int SV_ROW = LORA_MAX_RANK * 2 + 16;  // bytes per row of the staged s.v
-static_assert(8 * 128 * 128 <= L_LDS && LBM * SV_ROW <= L_LDS, "s.v and the parked outputs use the stage buffers");
+// two stages of x half 0, x half 1, Wt half 0, Wt half 1; s.v and the parked outputs (16 MB x 64 of eight wavefronts) use the same memory
+template <int MB> constexpr int linear_lds = std::max({2 * (32 * MB + LBN) * LROW, 32 * MB * SV_ROW, 8 * 16 * MB * 128});
+static_assert(linear_lds<8> == 128 << 10 && linear_lds<9> <= 160 << 10, "one block to a compute unit");
 constexpr int MAX_PARTS = 8;                    // a wavefront's 128 rows are eight blocks of 16
 constexpr size_t PART_WORDS = LINEAR_SHARE_BYTES / sizeof(unsigned long long);
 }  // namespace
@@ -136,15 +139,18 @@ template <int NB> __device__ __forceinline__ void keep_rows_outside(floatx4 (&ac
         for (int e = 0; e < 4; ++e) acc[nb][e] = row_in ? acc[nb][e] : had[nb][e];
 }
 
+template <int MB>
 __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __bf16 *__restrict__ Wt,
                                                            LinearList list, int n_mt, int n_nt, LinearSplit sp)
 {
+    constexpr int BM = 32 * MB, MB0 = (MB + 1) / 2, MB1 = MB / 2;  // rows of the block; row blocks of a wavefront per phase
+    constexpr int X0 = 32 * MB0 * LROW, X1 = 32 * MB1 * LROW, BUF = X0 + X1 + 2 * L_HALF;  // bytes of x half 0 and 1, of a stage
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
     const int rh = w >> 2, cq = w & 3;
     int tile_no, part = 0, tail = -1;
-    if ((int)blockIdx.x >= sp.n_whole) {
+    if (MB == 8 && (int)blockIdx.x >= sp.n_whole) {
         tail = __builtin_amdgcn_readfirstlane(((int)blockIdx.x - sp.n_whole) / sp.parts);
         part = ((int)blockIdx.x - sp.n_whole) - tail * sp.parts;
         tile_no = sp.n_whole + tail;
@@ -156,16 +162,11 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     int bm, bn;
     linear_tile<4>(tile_no, n_mt, n_nt, bm, bn);
     const int n0 = bn * LBN;
-
-    // the two runs of 64 rows of this wavefront's row half (a missing one counts as empty)
-    auto get_rows = [&](int idx) {
-        LinearRows t = list.rows[min(idx, list.n_rt - 1)];
-        if (idx >= list.n_rt) t.n_tok = t.n_segs = 0;
-        return t;
-    };
-    const LinearRows mine0 = get_rows(4 * bm + 2 * rh), mine1 = get_rows(4 * bm + 2 * rh + 1);
-    const int row0 = LBM * bm;  // the block's first row
-    const int dead_tok = list.rows[4 * bm].tok0;  // rows past the end read a live token's x; they are never stored
+    const int row0 = BM * bm, wrow = row0 + 16 * MB * rh;  // the block's first row and the wavefront's
+    // the token ids of the block's rows (rows past the end count as the last; they are never stored): from memory while the block starts, later from LDS
+    __shared__ int32_t tok_of_row[BM];
+    auto token_of = [&](int row) { return list.tok[min(row, list.n_rows - 1)]; };
+    if (tid < BM) tok_of_row[tid] = token_of(row0 + tid);
 
     const __bf16 *x = static_cast<const __bf16 *>(a.x);
     __bf16 *y = static_cast<__bf16 *>(a.y);
@@ -173,39 +174,74 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     // this block's stages of the k walk
     const int k_lo = tail < 0 ? 0 : n_k * part / sp.parts, k_hi = tail < 0 ? n_k : n_k * (part + 1) / sp.parts;
 
-    // Half h of x holds runs h and 2 + h of the block (phase h of row halves 0 and 1), half h of Wt columns
-    // 64 c + 32 h .. +31 of the four column quarters c.  Loader: wavefront w brings LDS rows 16w + 8q + lane/8, q = 0, 1,
-    // of every half: instruction q writes 8 rows x 128 bytes at the wavefront-uniform LDS address of its first row,
-    // lane l to slot l%8 of row l/8, for which it fetches piece (l%8) ^ ((row/2) % 8) of the row
-    const int lr = lane >> 3, ls = lane & 7;
-    const int piece[2] = {ls ^ ((lane >> 4) & 7), ls ^ (((lane >> 4) + 4) & 7)};
-    const __bf16 *xg[2][2], *wg[2][2];
+    // Half h of x holds the rows of phase h, 16 MBh of either row half, half h of Wt columns 64 c + 32 h .. +31 of the four column
+    // quarters c.  Loader: a request brings 8 LDS rows x 128 bytes to the wavefront-uniform LDS address of the first, lane l to slot l%8 of row l/8, for
+    // which it fetches piece (l%8) ^ ((row/2) % 8) of the row.  Request q of wavefront w brings rows 8 (w + 8 q) .. of a half; where that leaves four
+    // wavefronts one request more, they are wavefronts 0..3, and 4..7 for x half 1 if x half 0 gives the others one more already
+    constexpr int Q0 = (MB0 + 1) / 2, Q1 = (MB1 + 1) / 2;  // the most requests of a wavefront per x half
+    constexpr bool ODD0 = MB0 % 2 != 0, ODD1 = MB1 % 2 != 0;
+    const int w1 = ODD0 ? w ^ 4 : w;                       // the wavefront's place among the requests of x half 1
+    const bool more0 = !ODD0 || w < 4, more1 = !ODD1 || w1 < 4;  // makes its last request of the half too
+    const int lr = lane >> 3, piece = (lane & 7) ^ ((4 * (w & 1) + (lr >> 1)) & 7);
+    const __bf16 *xg0[Q0], *xg1[Q1], *wg[2][2];
+    {
+        int tok0[Q0], tok1[Q1];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const LinearRows t = h ? mine1 : mine0;  // (the runs a wavefront loads from are those it works on)
-        const int ti[2] = {16 * cq + lr, 16 * cq + 8 + lr};
-        int tok[2];
-        tile_tokens_of(list.tok, t, ti, dead_tok, tok);  // (rows past the run's end repeat its last)
-        // h_out is a multiple of 64, so a run of 64 columns is inside or outside as a whole
-        const int w_row = min(n0 + 64 * (w >> 1), a.h_out - 64) + 32 * h + 16 * (w & 1) + lr;
+        for (int q = 0; q < Q0; ++q) {
+            const int r = 8 * (w + 8 * q) + lr, half = r >= 16 * MB0;
+            tok0[q] = token_of(row0 + 16 * MB * half + r - 16 * MB0 * half);
+        }
+#pragma unroll
+        for (int q = 0; q < Q1; ++q) {
+            const int r = 8 * (w1 + 8 * q) + lr, half = r >= 16 * MB1;
+            tok1[q] = token_of(row0 + 16 * MB * half + 16 * MB0 + r - 16 * MB1 * half);
+        }
+#pragma unroll
+        for (int q = 0; q < Q0; ++q) xg0[q] = x + (size_t)tok0[q] * a.h_in + piece * 8;
+#pragma unroll
+        for (int q = 0; q < Q1; ++q) xg1[q] = x + (size_t)tok1[q] * a.h_in + piece * 8;
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            xg[h][q] = x + (size_t)tok[q] * a.h_in + piece[q] * 8;
-            wg[h][q] = Wt + (size_t)(w_row + 8 * q) * a.h_in + piece[q] * 8;
+            // h_out is a multiple of 64, so a run of 64 columns is inside or outside as a whole
+            const int w_row = min(n0 + 64 * ((w >> 2) + 2 * q), a.h_out - 64) + 32 * h + 8 * (w & 3) + lr;
+            wg[h][q] = Wt + (size_t)w_row * a.h_in + piece * 8;
         }
-    }
-    auto half_at = [&](int buf, int which) { return lds + (buf * 4 + which) * L_HALF; };  // which: 0, 1 x; 2, 3 Wt
-    auto load_half = [&](const __bf16 *const(&src)[2], int kt, int buf, int which) {
-        const int k = min(kt, k_hi - 1) * LBK;  // past the end: the last stage again (nobody reads it)
-        unsigned char *dst = half_at(buf, which) + 16 * w * LROW;
+    auto stage_at = [&](int buf) { return lds + buf * BUF; };  // x half 0, x half 1, Wt half 0, Wt half 1
+    auto k_of = [&](int kt) { return min(kt, k_hi - 1) * LBK; };  // past the end: the last stage again (nobody reads it)
+    auto load_x0 = [&](int kt, int buf) {
+        const int k = k_of(kt);
+        unsigned char *dst = stage_at(buf) + 8 * w * LROW;
 #pragma unroll
-        for (int q = 0; q < 2; ++q)
-            request16(src[q] + k, dst + q * 8 * LROW);
+        for (int q = 0; q < Q0; ++q)
+            if (q < Q0 - 1 || more0) request16(xg0[q] + k, dst + 64 * q * LROW);
+    };
+    auto load_x1 = [&](int kt, int buf) {
+        const int k = k_of(kt);
+        unsigned char *dst = stage_at(buf) + X0 + 8 * w1 * LROW;
+#pragma unroll
+        for (int q = 0; q < Q1; ++q)
+            if (q < Q1 - 1 || more1) request16(xg1[q] + k, dst + 64 * q * LROW);
+    };
+    auto load_w = [&](int kt, int buf) {
+        const int k = k_of(kt);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) request16(wg[h][q] + k, stage_at(buf) + X0 + X1 + h * L_HALF + (8 * w + 64 * q) * LROW);
+    };
+    // Waits until at most the latest stage's worth of requests is outstanding (x half 0 or 1, then the other, and Wt), and for the section's own reads
+    constexpr int PER_LOW = MB0 / 2 + MB1 / 2 + 4 + (ODD0 && ODD1);  // of the wavefronts with fewer
+    auto wait_section = [&]() {
+        if (ODD0 != ODD1 && w < 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PER_LOW + 1) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(PER_LOW) : "memory");
     };
 
-    floatx4 acc[8][4];  // [block of 16 rows][block of 16 columns]
+    floatx4 acc[MB][4];  // [block of 16 rows][block of 16 columns]
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
@@ -213,60 +249,58 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 
     // operand reads: LDS row R, k piece 4ks + g sits in slot (4ks + g) ^ ((R/2) % 8); R/2 % 8 = m/2 for all of a lane's rows
     const int swz = (m >> 1) & 7;
-    bf16x8 xo[4][2], wo[4][2];  // [block of 16 rows / columns][k step]
-    auto read_x = [&](int buf, int h) {
-        const unsigned char *s = half_at(buf, h) + (64 * rh + m) * LROW;
+    bf16x8 xo[MB0][2], wo[4][2];  // [block of 16 rows / columns][k step]
+    auto read_x = [&](int buf, auto h_tag) {
+        constexpr int H = decltype(h_tag)::value, N = H ? MB1 : MB0;
+        const unsigned char *s = stage_at(buf) + H * X0 + (16 * N * rh + m) * LROW;
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int mb = 0; mb < N; ++mb)
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) xo[mb][ks] = *reinterpret_cast<const bf16x8 *>(s + mb * 16 * LROW + (((4 * ks + g) ^ swz) << 4));
     };
     auto read_w = [&](int buf) {
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb) {
-            const unsigned char *s = half_at(buf, 2 + (nb >> 1)) + (32 * cq + 16 * (nb & 1) + m) * LROW;
+            const unsigned char *s = stage_at(buf) + X0 + X1 + (nb >> 1) * L_HALF + (32 * cq + 16 * (nb & 1) + m) * LROW;
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks) wo[nb][ks] = *reinterpret_cast<const bf16x8 *>(s + (((4 * ks + g) ^ swz) << 4));
         }
     };
     auto products = [&](auto h_tag) {
-        constexpr int H = decltype(h_tag)::value;
+        constexpr int H = decltype(h_tag)::value, N = H ? MB1 : MB0;
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int mb = 0; mb < 4; ++mb)
+            for (int mb = 0; mb < N; ++mb)
 #pragma unroll
                 for (int nb = 0; nb < 4; ++nb)
-                    acc[4 * H + mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[nb][ks], xo[mb][ks], acc[4 * H + mb][nb], 0, 0, 0);
+                    acc[MB0 * H + mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo[nb][ks], xo[mb][ks], acc[MB0 * H + mb][nb], 0, 0, 0);
         __builtin_amdgcn_s_setprio(0);
     };
 
     // requests in the order of their use: per stage x half 0, Wt half 0, Wt half 1 | x half 1
-    load_half(xg[0], k_lo, 0, 0);
-    load_half(wg[0], k_lo, 0, 2);
-    load_half(wg[1], k_lo, 0, 3);
-    load_half(xg[1], k_lo, 0, 1);
-    load_half(xg[0], k_lo + 1, 1, 0);
-    load_half(wg[0], k_lo + 1, 1, 2);
-    load_half(wg[1], k_lo + 1, 1, 3);
-    asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    load_x0(k_lo, 0);
+    load_w(k_lo, 0);
+    load_x1(k_lo, 0);
+    load_x0(k_lo + 1, 1);
+    load_w(k_lo + 1, 1);
+    wait_section();
     section_end();
     if (rh == 1) section_end();  // the second group of wavefronts runs one section behind
     for (int kt = k_lo; kt < k_hi; ++kt) {
         const int buf = (kt - k_lo) & 1;
-        read_x(buf, 0);
+        read_x(buf, std::integral_constant<int, 0>{});
         read_w(buf);
-        load_half(xg[1], kt + 1, buf ^ 1, 1);  // that half was last read in the phase before
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");  // x half 1 of this stage is in (eight requests came after it)
+        load_x1(kt + 1, buf ^ 1);  // that half was last read in the phase before
+        wait_section();  // x half 1 of this stage is in (a stage's worth of requests came after it)
         section_end();
         products(std::integral_constant<int, 0>{});
         section_end();
-        read_x(buf, 1);
-        load_half(xg[0], kt + 2, buf, 0);
-        load_half(wg[0], kt + 2, buf, 2);
-        load_half(wg[1], kt + 2, buf, 3);
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");  // x half 0 and Wt of the next stage are in
+        read_x(buf, std::integral_constant<int, 1>{});
+        load_x0(kt + 2, buf);
+        load_w(kt + 2, buf);
+        wait_section();  // x half 0 and Wt of the next stage are in
         section_end();
         products(std::integral_constant<int, 1>{});
         section_end();
@@ -277,8 +311,8 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 
     // ---- a tile split along k.  Row block mb of every wavefront (8 to a part's wavefront) belongs to part
     // ((mb + 1) * parts - 1) / 8; its sum is that part's plus the others' in their order, whoever adds it up
-    int own_lo = 0, own_hi = 8;  // the row blocks this block finishes
-    if (tail >= 0) {
+    int own_lo = 0, own_hi = MB;  // the row blocks this block finishes
+    if constexpr (MB == 8) if (tail >= 0) {
         SplitState *const st = sp.state + tail;
         unsigned long long *const sums = sp.partial + (size_t)tail * sp.parts * PART_WORDS;
         __shared__ uint32_t said;
@@ -373,16 +407,26 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     auto load_bp = [&](const LinearSeg &t) {
         const __bf16 *Bp = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)t.row * a.row_bytes) + (size_t)rank_storage(t.rank) * a.h_in;
         const int rs8 = rank_storage(t.rank) >> 3;
+        int own_lane = lane;
+        if constexpr (MB > 8) asm volatile("" : "+v"(own_lane));  // (places made anew for every segment: the registers hold none beside the products)
+        const int lm = own_lane & 15, lg = own_lane >> 4;
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
             for (int nb = 0; nb < 4; ++nb) {
-                const int col = min(n0 + 64 * cq + 16 * nb + m, a.h_out - 1);
-                bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(4 * ks + g, rs8 - 1) * a.h_out + col) * 8));
+                const int col = min(n0 + 64 * cq + 16 * nb + lm, a.h_out - 1);
+                bo[ks][nb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Bp + ((size_t)min(4 * ks + lg, rs8 - 1) * a.h_out + col) * 8));
             }
     };
     // (rows with an adapter product come first in the list)
-    const int seg0 = mine0.first_seg, seg1 = mine1.n_segs > 0 ? mine1.first_seg + mine1.n_segs : seg0 + mine0.n_segs;  // wavefront-uniform
+    const int wend = min(wrow + 16 * MB, list.n_rows);
+    int seg0 = 0, seg1 = 0;  // wavefront-uniform: the segments of the runs its rows lie in, less those that end before or begin behind them
+    if (wrow < min(list.add0, wend)) {
+        const LinearRows r0 = list.rows[wrow / LORA_TILE_TOKENS], r1 = list.rows[(wend - 1) / LORA_TILE_TOKENS];
+        seg0 = r0.first_seg, seg1 = r1.first_seg + r1.n_segs;
+        while (seg0 < seg1 && list.segs[seg0].r1 <= wrow) ++seg0;
+        while (seg0 < seg1 && list.segs[seg1 - 1].r0 >= wend) --seg1;
+    }
     LinearSeg seg = {};
     if (seg0 < seg1) {
         seg = list.segs[seg0];
@@ -390,25 +434,20 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
     }
     unsigned char *sv = lds;  // s.v of the block's rows as bf16
     if (row0 < list.add0) {
-        // chunk tid % 16 (8 ranks) of rows tid / 16 + 32 i: the token ids in one round, then the pieces, four rows at a time
+        // chunk tid % 16 (8 ranks) of rows tid / 16 + 32 i: the token ids in one round, then the pieces, four or five rows at a time
         // (unconditional, from addresses inside v; what lies past a row's rank is masked where it is used)
         const int c8 = tid & 15, r0 = tid >> 4;
+        int tok[MB];
 #pragma unroll
-        for (int i0 = 0; i0 < 8; i0 += 4) {
-            int tok[4];
-            uint4 pc[4];
+        for (int i = 0; i < MB; ++i) tok[i] = tok_of_row[r0 + 32 * i];
 #pragma unroll
-            for (int j = 0; j < 4; j += 2) {
-                const int ti[2] = {r0, r0 + 32};
-                int tk[2];
-                tile_tokens_of(list.tok, list.rows[min(4 * bm + (i0 + j) / 2, list.n_rt - 1)], ti, dead_tok, tk);
-                tok[j] = tk[0], tok[j + 1] = tk[1];
-            }
+        for (int i0 = 0; i0 < MB; i0 += MB0) {
+            uint4 pc[MB0];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)  // s.v comes as bf16 from the shrink or the reduce (rows of the fp32 pitch)
-                pc[j] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[j] * (2 * a.v_stride) + c8 * 8);
+            for (int j = 0; j < MB0 && i0 + j < MB; ++j)  // s.v comes as bf16 from the shrink or the reduce (rows of the fp32 pitch)
+                pc[j] = *reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(a.v) + (size_t)tok[i0 + j] * (2 * a.v_stride) + c8 * 8);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) *reinterpret_cast<uint4 *>(sv + (r0 + 32 * (i0 + j)) * SV_ROW + c8 * 16) = pc[j];
+            for (int j = 0; j < MB0 && i0 + j < MB; ++j) *reinterpret_cast<uint4 *>(sv + (r0 + 32 * (i0 + j)) * SV_ROW + c8 * 16) = pc[j];
         }
     }
     __syncthreads();
@@ -418,13 +457,12 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
             load_bp(seg);
         }
         const int ks32 = (seg.rank + 31) >> 5;
-        const int lo = seg.r0 - row0 - 128 * rh, hi = seg.r1 - row0 - 128 * rh;  // its rows among the wavefront's 128
-        const unsigned char *svr = sv + (128 * rh + m) * SV_ROW + g * 16;
-        uint4 live[4];
+        const int lo = seg.r0 - wrow, hi = seg.r1 - wrow;  // its rows among the wavefront's
+        const unsigned char *svr = sv + (16 * MB * rh + m) * SV_ROW + g * 16;
+        int ranks_left = seg.rank - 8 * g;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) live[ks] = rank_mask(seg.rank - 32 * ks - 8 * g);
-#pragma unroll
-        for (int mb = 0; mb < 8; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
+            if constexpr (MB > 8) asm("" : "+v"(ranks_left));  // (the masks made anew for every row block: the registers hold no four of them)
             const int r0 = 16 * mb, r = r0 + m;
             if (!owns(mb) || r0 + 16 <= lo || r0 >= hi) continue;  // uniform
             const bool whole = lo <= r0 && r0 + 16 <= hi;  // uniform
@@ -436,7 +474,7 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 if (ks >= ks32) continue;
-                const bf16x8 so = sv_operand(*reinterpret_cast<const uint4 *>(svr + mb * 16 * SV_ROW + ks * 64), live[ks]);
+                const bf16x8 so = sv_operand(*reinterpret_cast<const uint4 *>(svr + mb * 16 * SV_ROW + ks * 64), rank_mask(ranks_left - 32 * ks));
 #pragma unroll
                 for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bo[ks][nb], so, acc[mb][nb], 0, 0, 0);
             }
@@ -446,88 +484,81 @@ __global__ __launch_bounds__(512) void linear_tiles_kernel(ApplyArgs a, const __
 
     // ---- store.  The products are formed transposed (the W block is the instruction's row operand, the x
     // block its column operand): lane (m, g) holds, in the four registers of block (mb, nb), row 16*mb + m of the
-    // wavefront's 128 and the four consecutive columns 16*nb + 4g .. of its 64 -- 8 bytes of bf16.  The
-    // wavefront parks its 128 x 64 outputs in LDS and stores whole 128-byte row pieces, 8 rows per
+    // wavefront's 16 MB and the four consecutive columns 16*nb + 4g .. of its 64 -- 8 bytes of bf16.  The
+    // wavefront parks its 16 MB x 64 outputs in LDS and stores whole 128-byte row pieces, 8 rows per
     // instruction (stored from the registers, an instruction would write 32 bytes to each of 16 rows).
     // Park layout, free of bank conflicts both ways: row r is 128 bytes, its 8-byte cell c sits at
     // c ^ (2 * ((r/2) % 8)), i.e. its 16-byte slot s at s ^ ((r/2) % 8).  Rows of GEMV tokens take their adapter term, computed
     // beforehand, into the accumulators here, so that the sum is formed in fp32 before the one rounding.
     __syncthreads();  // every wavefront is done with the staged s.v
-    unsigned char *park = lds + w * (128 * 128);
-    const bool cols_live = n0 + 64 * cq < a.h_out;  // h_out is a multiple of 64
+    unsigned char *park = lds + w * (16 * MB * 128);
+    const bool live = wrow < list.n_rows && n0 + 64 * cq < a.h_out;  // wavefront-uniform (h_out is a multiple of 64)
+    if (!live) return;  // (no barrier follows)
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    int own_tid = tid;
+    if constexpr (MB > 8) asm volatile("" : "+v"(own_tid));  // (row numbers of its own: none is kept from before the products)
+    const int ln = own_tid & 63, mr = ln & 15, gr = ln >> 4;
+    if (wrow < list.add1 && wend > list.add0) {
+        // as fp32 at the same place of the workspace, or in y: the token ids in one round, then per row block the four terms
+        int tok[MB];
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-        const LinearRows &t = tl ? mine1 : mine0;
-        if (t.n_tok == 0 || !cols_live) continue;  // wavefront-uniform
-        if (t.tok_off < list.add1 && t.tok_off + t.n_tok > list.add0) {
-            // as fp32 at the same place of the workspace, or in y: the four token ids in one round, then per row block the four terms
-            int ti4[4], tok4[4];
+        for (int mb = 0; mb < MB; ++mb) tok[mb] = tok_of_row[wrow - row0 + 16 * mb + mr];
 #pragma unroll
-            for (int mbl = 0; mbl < 4; ++mbl) ti4[mbl] = 16 * mbl + m;
-            tile_tokens_of(list.tok, t, ti4, dead_tok, tok4);
+        for (int mb = 0; mb < MB; ++mb) {
+            if (!owns(mb)) continue;
+            const int r = wrow + 16 * mb + mr;
+            if (r < list.add0 || r >= list.add1) continue;
+            const size_t at = (size_t)tok[mb] * a.h_out + n0 + 64 * cq + 4 * gr;
+            floatx4 term[4];
+            if (a.y32) {
 #pragma unroll
-            for (int mbl = 0; mbl < 4; ++mbl) {
-                if (!owns(4 * tl + mbl)) continue;
-                const int r = t.tok_off + ti4[mbl];
-                if (r < list.add0 || r >= list.add1) continue;
-                const size_t at = (size_t)tok4[mbl] * a.h_out + n0 + 64 * cq + 4 * g;
-                floatx4 term[4];
-                if (a.y32) {
+                for (int nb = 0; nb < 4; ++nb) term[nb] = *reinterpret_cast<const floatx4 *>(a.y32 + at + 16 * nb);
+            } else {
+                bf16x4 old[4];
 #pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) term[nb] = *reinterpret_cast<const floatx4 *>(a.y32 + at + 16 * nb);
-                } else {
-                    bf16x4 old[4];
-#pragma unroll
-                    for (int nb = 0; nb < 4; ++nb) old[nb] = *reinterpret_cast<const bf16x4 *>(y + at + 16 * nb);
-#pragma unroll
-                    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) term[nb][e] = (float)old[nb][e];
-                }
+                for (int nb = 0; nb < 4; ++nb) old[nb] = *reinterpret_cast<const bf16x4 *>(y + at + 16 * nb);
 #pragma unroll
                 for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * tl + mbl][nb][e] += term[nb][e];
+                    for (int e = 0; e < 4; ++e) term[nb][e] = (float)old[nb][e];
             }
-        }
 #pragma unroll
-        for (int mbl = 0; mbl < 4; ++mbl) {
-            if (!owns(4 * tl + mbl)) continue;
-            const int ti = 16 * mbl + m, row = 64 * tl + ti;
-            unsigned char *pr = park + row * 128;
+            for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                const floatx4 c = acc[4 * tl + mbl][nb];
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (__bf16)c[e];
-                *reinterpret_cast<bf16x4 *>(pr + (((4 * nb + g) ^ (((row >> 1) & 7) << 1)) << 3)) = o;
-            }
+                for (int e = 0; e < 4; ++e) acc[mb][nb][e] += term[nb][e];
         }
     }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        if (!owns(mb)) continue;
+        const int row = 16 * mb + mr;
+        unsigned char *pr = park + row * 128;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            const floatx4 c = acc[mb][nb];
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)c[e];
+            *reinterpret_cast<bf16x4 *>(pr + (((4 * nb + gr) ^ (((row >> 1) & 7) << 1)) << 3)) = o;
+        }
+    }
+    // the rows' token ids all before the first store (a lookup between two stores makes the second wait for the first)
+    const int rl = ln >> 3, sl = ln & 7;
+    int tok8[2 * MB];
+#pragma unroll
+    for (int i = 0; i < 2 * MB; ++i) tok8[i] = tok_of_row[wrow - row0 + 8 * i + rl];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // only this wavefront reads what it wrote; its LDS operations execute in order
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
-        const LinearRows &t = tl ? mine1 : mine0;
-        if (t.n_tok == 0 || !cols_live) continue;  // wavefront-uniform
-        const int rl = lane >> 3, sl = lane & 7;
-        int ti8[8], tok8[8];  // the rows' token ids all before the first store (a lookup between two stores makes the second wait for the first)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ti8[i] = 8 * i + rl;
-        tile_tokens_of(list.tok, t, ti8, dead_tok, tok8);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = 64 * tl + ti8[i];
-            if (owns(4 * tl + (i >> 1)) && ti8[i] < t.n_tok) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((sl ^ ((row >> 1) & 7)) << 4));
-                // (a streaming store: the rows leave the caches as they are written instead of lying there dirty
-                // until the next kernel's loads push them out -- the tile shrink that follows runs 2 to 3 us shorter)
-                typedef unsigned u32x4_nt __attribute__((ext_vector_type(4)));
-                const u32x4_nt vn = {v.x, v.y, v.z, v.w};
-                __builtin_nontemporal_store(vn, reinterpret_cast<u32x4_nt *>(y + (size_t)tok8[i] * a.h_out + n0 + 64 * cq + 8 * sl));
-            }
+    for (int i = 0; i < 2 * MB; ++i) {
+        const int row = 8 * i + rl;
+        if (owns(i >> 1) && wrow + row < list.n_rows) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(park + row * 128 + ((sl ^ ((row >> 1) & 7)) << 4));
+            // (a streaming store: the rows leave the caches as they are written instead of lying there dirty
+            // until the next kernel's loads push them out -- the tile shrink that follows runs 2 to 3 us shorter)
+            typedef unsigned u32x4_nt __attribute__((ext_vector_type(4)));
+            const u32x4_nt vn = {v.x, v.y, v.z, v.w};
+            __builtin_nontemporal_store(vn, reinterpret_cast<u32x4_nt *>(y + (size_t)tok8[i] * a.h_out + n0 + 64 * cq + 8 * sl));
         }
     }
 }
@@ -858,11 +889,33 @@ static double small_estimate(int n_tiles, int n_k, int rm, int parts, double l2_
     return 4.0 + std::max(stage * ((n_k + parts - 1) / parts), bytes / rate) + hand_over;
 }
 
+// Whole tiles of `rows` x 256 with n_k stages, as measured: 10 us for a block's start and end, and stages that take as long as their products at the matrix cores' peak
+// while a quarter of the units is busy (0.91 us for 256 rows), and, all units busy, what the card sustains (1.38 us, 1.4 PFLOP/s): 64 tiles of 64 stages take 68 us, 128
+// 72, 192 82, 256 98.5.  So a last round with few tiles is not as cheap as its share of the units, but cheaper than a full one.
+static double rounds_us(int rows, int n_tiles, double n_k, int n_cu)
+{
+    const double peak = rows == 192 ? 0.77 : rows == 288 ? 1.02 : 0.906, full = 1.316 * (rows == 192 ? 0.726 : rows == 288 ? 1.104 : 1.0);
+    double t = 0;
+    for (int left = n_tiles; left > 0; left -= n_cu) {
+        const double load = full * std::min(left, n_cu) / n_cu, p2 = peak * peak, l2 = load * load;
+        t += 10 + n_k * std::sqrt(std::sqrt(p2 * p2 + l2 * l2));
+    }
+    return t;
+}
+// Tiles of 192 and 288 rows, whole ones only, where they fit the units better than tiles of 256 with their last round split.  Measured (us; tiles of 256 as chosen above, of
+// 192, of 288): 4300 x 4096 x 4096 125 / 137 / 103 (272 tiles; 368; 240), 4416 132 / 136 / 108, 5809 155 / 151 / 184, 3000 80 / 77 / 87, 3500 x 2560 x 2560 49 / 44 / 53,
+// 2560 x 13824 x 5120 273 / 286 / 257, 3000 x 11008 x 4096 219 / 223 / 204; not chosen: 2048 x 4096 x 4096 63 / 65 / 79, 2560 x 5120 x 5120 107 / 163 / 115, 1600 x 4096 x 4096
+// 57 / 61 / 76; 160 and 224 rows were the best nowhere (2560 x 5120 x 5120: 168, 105).  The estimate is within 8 % of these, hence the 5 % it has to gain.
+// Products of less than 36 stages (h_in below 2304) keep the shapes they had: the tests name them.
+constexpr int TALL_MIN_STAGES = 36;
+
 template <int RM, int NST> constexpr int small_lds = NST * 64 * (RM + 1) * LROW;
 
 hipError_t prepare_linear_kernels()
 {
-    hipError_t e = allow_lds(linear_tiles_kernel, L_LDS);
+    hipError_t e = allow_lds(linear_tiles_kernel<8>, linear_lds<8>);
+    if (e == hipSuccess) e = allow_lds(linear_tiles_kernel<6>, linear_lds<6>);
+    if (e == hipSuccess) e = allow_lds(linear_tiles_kernel<9>, linear_lds<9>);
     if (e == hipSuccess) e = allow_lds(linear_small_kernel<1, 4>, small_lds<1, 4>);
     if (e == hipSuccess) e = allow_lds(linear_small_kernel<1, 3>, small_lds<1, 3>);
     if (e == hipSuccess) e = allow_lds(linear_small_kernel<2, 3>, small_lds<2, 3>);
@@ -879,9 +932,9 @@ static hipError_t launch_small(const ApplyArgs &a, const void *Wt, const LinearL
     return hipGetLastError();
 }
 
-LinearShape linear_shape(int n_rt, int h_in, int h_out, size_t split_scratch_bytes, int n_split_state, int n_cu)
+LinearShape linear_shape(int n_rows, int h_in, int h_out, size_t split_scratch_bytes, int n_split_state, int n_cu)
 {
-    const int n_k = h_in / LBK, n_tiles = (n_rt + 3) / 4 * ((h_out + LBN - 1) / LBN);
+    const int n_rt = (n_rows + LORA_TILE_TOKENS - 1) / LORA_TILE_TOKENS, n_k = h_in / LBK, n_tiles = (n_rt + 3) / 4 * ((h_out + LBN - 1) / LBN);
     int parts, n_tail;
     // (the estimate reads 15 to 25 % more than 256 x 256 tiles take where the other kernel comes near them)
     const double big = 0.85 * linear_split_shape(n_tiles, n_k, n_cu, split_scratch_bytes / LINEAR_SHARE_BYTES, parts, n_tail);
@@ -895,6 +948,13 @@ LinearShape linear_shape(int n_rt, int h_in, int h_out, size_t split_scratch_byt
     if (t64 <= big && t64 <= t128) return {64, tiles64 * p64 <= 2 * n_cu ? 4 : 3, tiles64, p64 > 1 ? tiles64 : 0, p64};
     if (t128 <= big) return {128, 3, tiles128, 0, 1};
     if (n_tail > n_split_state) parts = 1, n_tail = 0;
+    if (n_k >= TALL_MIN_STAGES) {
+        const int n_nt = (h_out + LBN - 1) / LBN, whole = n_tiles - n_tail;
+        const double now = rounds_us(256, whole, n_k, n_cu) + (parts > 1 ? rounds_us(256, n_tail * parts, (double)n_k / parts, n_cu) + 4.0 + 0.06 * n_tail * (parts - 1) : 0.0);
+        const int tiles192 = (n_rows + 191) / 192 * n_nt, tiles288 = (n_rows + 287) / 288 * n_nt;
+        const double t192 = rounds_us(192, tiles192, n_k, n_cu), t288 = rounds_us(288, tiles288, n_k, n_cu);
+        if (std::min(t192, t288) < 0.95 * now) return t192 < t288 ? LinearShape{192, 2, tiles192, 0, 1} : LinearShape{288, 2, tiles288, 0, 1};
+    }
     return {LBM, 2, n_tiles, n_tail, parts};
 }
 
@@ -903,13 +963,21 @@ hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearL
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (list.n_rt <= 0) return hipSuccess;
-    const LinearShape sh = linear_shape(list.n_rt, a.h_in, a.h_out, split_scratch_bytes, n_split_state, n_cu);
+    const LinearShape sh = linear_shape(list.n_rows, a.h_in, a.h_out, split_scratch_bytes, n_split_state, n_cu);
     if (sh.rows == 64 && sh.ring == 4) return launch_small<1, 4>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
     if (sh.rows == 64) return launch_small<1, 3>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
     if (sh.rows == 128) return launch_small<2, 3>(a, Wt, list, sh.parts, split_scratch, split_state, st, tm, done);
     const LinearSplit sp{sh.tiles - sh.split, sh.parts, static_cast<unsigned long long *>(split_scratch), split_state, fault};
-    launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel, dim3(sp.n_whole + sh.split * sh.parts), dim3(512), L_LDS, st, a, static_cast<const __bf16 *>(Wt),
-             list, (list.n_rt + 3) / 4, (a.h_out + LBN - 1) / LBN, sp);
+    auto go = [&](auto mb_tag) {
+        constexpr int MB = decltype(mb_tag)::value;
+        launch_k(tm, done, LORA_K_LINEAR, linear_tiles_kernel<MB>, dim3(sp.n_whole + sh.split * sh.parts), dim3(512), linear_lds<MB>, st, a, static_cast<const __bf16 *>(Wt),
+                 list, (list.n_rows + 32 * MB - 1) / (32 * MB), (a.h_out + LBN - 1) / LBN, sp);
+    };
+    switch (sh.rows) {
+    case 192: go(std::integral_constant<int, 6>{}); break;
+    case 288: go(std::integral_constant<int, 9>{}); break;
+    default: go(std::integral_constant<int, 8>{}); break;
+    }
     return hipGetLastError();
 }
 

@@ -1927,7 +1927,7 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
         }
     }
     if (p->n_lin_rows > 0) {
-        const lora::LinearShape sh = lora::linear_shape(p->n_lin_rows, c->proj[proj].h_in, c->proj[proj].h_out, c->vpart_bytes, N_LINEAR_SPLITS, c->n_cu);
+        const lora::LinearShape sh = lora::linear_shape(p->T, c->proj[proj].h_in, c->proj[proj].h_out, c->vpart_bytes, N_LINEAR_SPLITS, c->n_cu);
         put_unit(LORA_UNIT_LINEAR_SHAPE, nt, 0, -1, 0, sh.rows, sh.tiles, sh.split << 8 | sh.parts, (float)sh.ring);
     }
     *n_units = nu;
@@ -2340,7 +2340,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
     const lora::LinearList list{reinterpret_cast<const int32_t *>(p->lists + p->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(p->lists + p->off_lin_rows),
                                 reinterpret_cast<const lora::LinearSeg *>(p->lists + p->off_lin_segs),
-                                p->n_lin_rows, p->n_tile_tok, p->n_tok_list};
+                                p->T, p->n_lin_rows, p->n_tile_tok, p->n_tok_list};
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
     HIP_TRY(lora::launch_linear_tiles(a, Wt, list, c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
                                       N_LINEAR_SPLITS, c->fault_dev, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));

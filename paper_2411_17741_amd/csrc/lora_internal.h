@@ -427,7 +427,7 @@ struct LinearList {
     const int32_t *tok;
     const LinearRows *rows;
     const LinearSeg *segs;
-    int32_t n_rt, add0, add1;
+    int32_t n_rows, n_rt, add0, add1;
 };
 // y = x . Wt^T + adapter update for the rows of the list; a.v holds the shrink results
 hipError_t launch_zero_rows(void *y, const int32_t *toks, int n, int h_out, hipStream_t st);  // y bf16 [..][h_out]
@@ -438,12 +438,12 @@ struct SplitState {
     uint32_t started, way, arrived, read;  // parts that run, have left their sums, have read the others'; way: how the tile is finished
 };
 constexpr size_t LINEAR_SHARE_BYTES = (size_t)256 * 256 * sizeof(float);  // a tile's accumulators
-// How lora_linear_plan's product of n_rt runs of rows is cut into blocks: tiles of `rows` rows (64, 128: x 64 columns, 256: x 256) with a ring of so many
+// How lora_linear_plan's product of n_rt runs of rows is cut into blocks: tiles of `rows` rows (64, 128: x 64 columns, 192, 256, 288: x 256) with a ring of so many
 // stages, and how many of them, the last ones, are split along k into `parts` parts.
 struct LinearShape {
     int rows, ring, tiles, split, parts;
 };
-LinearShape linear_shape(int n_rt, int h_in, int h_out, size_t split_scratch_bytes, int n_split_state, int n_cu);
+LinearShape linear_shape(int n_rows, int h_in, int h_out, size_t split_scratch_bytes, int n_split_state, int n_cu);
 hipError_t launch_linear_tiles(const ApplyArgs &a, const void *Wt, const LinearList &list, void *split_scratch,
                                size_t split_scratch_bytes, SplitState *split_state, int n_split_state, int32_t *fault, int n_cu,
                                hipStream_t st, const KernelTimer *tm, hipEvent_t done);

@@ -38,6 +38,22 @@ def _shape(B, pool, plan):
     ([65, 5], 192, 320, (64, 4, 10, 0, 1)),                   # three k stages
 ])
 def test_linear_against_torch(lens, h_in, h_out, shape):
+    check_against_torch(lens, h_in, h_out, shape)
+
+
+# tiles of 192 and 288 rows: the last panel full, of one row more than a run of 64, one short; the last column panel 64 wide; odd k stages
+@pytest.mark.parametrize("lens,h_in,h_out,shape", [
+    ([2800, 35, 200, 17], 4096, 4096, (192, 2, 256, 0, 1)),    # 16 panels, all full
+    ([1500, 1000, 9, 350], 2368, 4160, (192, 2, 255, 0, 1)),   # 37 k stages, ragged
+    ([3500, 700, 71], 4096, 4096, (288, 2, 240, 0, 1)),        # the last panel 259 rows
+    ([3500, 1025, 63], 2368, 4096, (288, 2, 256, 0, 1)),       # 16 panels, all full, 37 k stages
+    ([2400, 140], 4096, 13376, (288, 2, 477, 0, 1)),           # two rounds, the last column panel 64 wide
+])
+def test_tall_tiles_against_torch(lens, h_in, h_out, shape):
+    check_against_torch(lens, h_in, h_out, shape)
+
+
+def check_against_torch(lens, h_in, h_out, shape):
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
