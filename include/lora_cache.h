@@ -310,25 +310,26 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out);
  * many as fit a batch) that belong to this projection, with the one kind of items and with the other (bf16 caches).  For each entry they
  * cover what the GEMV units cover, once.  The DIRECT_SHRINK units (up to 16 tokens of a tile x 16 rank rows over all input columns), if the plan
  * has any, are what a launch short enough works through in place of the pieces; they cover every token and rank row of every
- * tile once.  LINEAR_SHAPE says how lora_linear_plan cuts this projection's product into blocks.
+ * tile once.  The PANEL_SHRINK units (up to 192 rows of a slot x up to three projections that read the same x) are what most longer launches work through: for a group
+ * of 1 to 4 projections they cover every tile's tokens once per projection.  LINEAR_SHAPE says how lora_linear_plan cuts this projection's product into blocks.
  * Writes at most cap_units units and cap_toks tokens; *n_units and *n_toks return the full counts
  * (call with zero capacities to size the arrays). */
 enum { LORA_UNIT_TILE = 0, LORA_UNIT_GEMV_SHRINK = 1, LORA_UNIT_GEMV_EXPAND = 2, LORA_UNIT_LINEAR_ROWS = 3, LORA_UNIT_TILE_SHRINK = 4, LORA_UNIT_TILE_SUM = 5,
        LORA_UNIT_BATCH_SHRINK = 6, LORA_UNIT_BATCH_EXPAND = 7, LORA_UNIT_WIDE_SHRINK = 8, LORA_UNIT_WIDE_EXPAND = 9,
-       LORA_UNIT_DIRECT_SHRINK = 10, LORA_UNIT_LINEAR_SHAPE = 11 };
+       LORA_UNIT_DIRECT_SHRINK = 10, LORA_UNIT_LINEAR_SHAPE = 11, LORA_UNIT_PANEL_SHRINK = 12 };
 typedef struct {
     int32_t kind;
     int32_t tok_off, n_tok; /* the unit's tokens: toks[tok_off .. tok_off + n_tok) */
     int32_t slot, rank;     /* slot found back from the storage row the kernels address; -1, 0: rows without adapter */
     int32_t lo, hi;         /* *_SHRINK: rank rows [lo, hi); *_EXPAND: output columns [lo, hi); TILE_SHRINK: input
                                columns [lo, hi); TILE_SUM: slot number lo of hi; LINEAR_SHAPE: rows of a tile (64, 128: x 64 columns,
-                               192, 256, 288: x 256), tiles; else 0, 0 */
+                               192, 256, 288: x 256), tiles; PANEL_SHRINK: projections [lo, hi) of the group; else 0, 0 */
     int32_t where;          /* GEMV_SHRINK: position in launch order; LINEAR_ROWS: 2 = a tile, 1 = rows of GEMV tokens,
                                0 = rows without adapter; TILE_SHRINK, TILE_SUM: run table << 20 | run (run tables 0..3:
                                launches for 1..4 projections; 4: the one of lora_apply_plan_static; 5, 6: those with at most 64 and
                                32 runs per projection, for batches of more than 4); BATCH_*, WIDE_*: the batch's entry, layer *
                                n_proj + proj; DIRECT_SHRINK: 1 if a call for this projection alone works through them; LINEAR_SHAPE: tiles split
-                               along the input columns << 8 | parts of each; TILE: 0 */
+                               along the input columns << 8 | parts of each; PANEL_SHRINK: projections of the group; TILE: 0 */
     float alpha;            /* the cache entry's own factor as the kernels will apply it; TILE_SHRINK, TILE_SUM: the
                                scratch slot of the partial sum (-1: the piece is the whole tile and leaves none); LINEAR_SHAPE: stages of a ring */
 } lora_plan_unit_t;

@@ -90,7 +90,7 @@ class lora_worklists_t(ctypes.Structure):
 
 LORA_UNIT_TILE, LORA_UNIT_GEMV_SHRINK, LORA_UNIT_GEMV_EXPAND, LORA_UNIT_LINEAR_ROWS, LORA_UNIT_TILE_SHRINK, LORA_UNIT_TILE_SUM = 0, 1, 2, 3, 4, 5
 LORA_UNIT_BATCH_SHRINK, LORA_UNIT_BATCH_EXPAND, LORA_UNIT_WIDE_SHRINK, LORA_UNIT_WIDE_EXPAND = 6, 7, 8, 9
-LORA_UNIT_DIRECT_SHRINK, LORA_UNIT_LINEAR_SHAPE = 10, 11
+LORA_UNIT_DIRECT_SHRINK, LORA_UNIT_LINEAR_SHAPE, LORA_UNIT_PANEL_SHRINK = 10, 11, 12
 
 
 class lora_plan_unit_t(ctypes.Structure):

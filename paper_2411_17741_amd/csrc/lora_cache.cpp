@@ -171,7 +171,7 @@ struct lora_plan {
     // the tile shrink's run tables (cuts, then the tiles' piece records), per variant
     int32_t shrink_quanta = 1;
     int32_t shrink_runs[SHRINK_VARIANTS] = {0};
-    bool shrink_pieces[SHRINK_VARIANTS] = {false}, shrink_pairs[SHRINK_VARIANTS] = {false};
+    bool shrink_pieces[SHRINK_VARIANTS] = {false};
     size_t off_cuts[SHRINK_VARIANTS] = {0}, off_sums[SHRINK_VARIANTS] = {0};
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     uint64_t build_seq = 0;     // changes whenever the plan's lists are rebuilt
@@ -182,6 +182,12 @@ struct lora_plan {
     size_t off_lin_tok = 0, off_lin_rows = 0, off_lin_segs = 0;
     size_t off_direct = 0;  // units of a short tile shrink (0 of them: too many for that)
     int32_t n_direct = 0;
+    size_t off_panels = 0;  // panels of a long tile shrink
+    int32_t n_panels = 0;
+    lora::PanelClasses panel_classes{};
+    int32_t panel_count[lora::PANEL_ROWS / 64 + 1][9] = {{0}};  // by runs of 64 rows and rank blocks
+    double panel_sum_bytes = 0;  // of one slice's sums, written and read
+    int64_t tile_rows = 0;       // rows the run table's kernel takes in per stage: 64 and the rank of every tile
     int32_t n_lin_rows = 0, n_lin_segs = 0;
     std::vector<int32_t> slots;        // distinct slots the batch names
     std::vector<uint32_t> generations;  // their generation at plan time
@@ -536,12 +542,11 @@ struct ShrinkRuns {
     std::vector<lora::ShrinkSum> sums;
     int n_runs = 0;
     bool any_pieces = false;
-    bool any_pairs = false;  // two whole tiles of one slot follow each other in some run
 };
 bool shrink_pieces_of(const lora::DevItem *tiles, int n_tiles, int quanta, ShrinkRuns &out)
 {
     out.sums.assign((size_t)n_tiles, lora::ShrinkSum{0, 0});
-    out.any_pieces = out.any_pairs = false;
+    out.any_pieces = false;
     for (int r = 0; r < out.n_runs; ++r) {
         const lora::ShrinkCut from = out.cuts[r], to = out.cuts[r + 1];
         const int last_tile = std::min(to.part > 0 ? to.tile : to.tile - 1, n_tiles - 1);
@@ -554,7 +559,6 @@ bool shrink_pieces_of(const lora::DevItem *tiles, int n_tiles, int quanta, Shrin
             else if (slot != 2 * (sm.first_slot / 2 + sm.n_pieces)) return false;  // (cannot happen: later pieces start their runs)
             ++sm.n_pieces;
             if (sm.n_pieces > 1) out.any_pieces = true;
-            out.any_pairs |= lo == 0 && hi == quanta && t + 1 < to.tile && tiles[t + 1].row == tiles[t].row;  // (as mfma_shrink_kernel asks)
         }
     }
     for (int t = 0; t < n_tiles; ++t)
@@ -800,6 +804,44 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
             }
         }
     }
+    // the panels of a long tile shrink: neighbouring tiles of a slot put together, cut into equal parts of at most lora::PANEL_ROWS rows
+    std::vector<lora::DevItem> panels;
+    if (c.dtype == LORA_BF16) {
+        const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
+        for (int i = 0; i < w.n_tiles;) {
+            int32_t n = 0;
+            int j = i;
+            for (; j < w.n_tiles && dev_tiles[j].row == dev_tiles[i].row && dev_tiles[j].tok_off == dev_tiles[i].tok_off + n; ++j) n += dev_tiles[j].n_tok;
+            const int32_t parts = (n + lora::PANEL_ROWS - 1) / lora::PANEL_ROWS, rows = ((n + parts - 1) / parts + 15) / 16 * 16;
+            for (int32_t o = 0; o < n; o += rows) {
+                lora::DevItem d = dev_tiles[i];
+                d.tok_off += o;
+                d.n_tok = std::min(rows, n - o);
+                d.tok0 = w.tok_list[d.tok_off];
+                d.consecutive = 1;
+                for (int32_t r = 1; r < d.n_tok && d.consecutive; ++r) d.consecutive = w.tok_list[d.tok_off + r] == d.tok0 + r;
+                panels.push_back(d);
+            }
+            i = j;
+        }
+        auto runs_of = [](const lora::DevItem &d) { return (d.n_tok + 63) / 64; };
+        auto key = [&](const lora::DevItem &d) {
+            const int runs = runs_of(d), nb = lora::panel_rank_blocks(d.rank);
+            return std::make_pair(lora::panel_projs(runs, nb), -(64 * runs + 16 * nb));
+        };
+        std::stable_sort(panels.begin(), panels.end(), [&](const lora::DevItem &x, const lora::DevItem &y) { return key(x) < key(y); });
+        p.panel_classes = lora::PanelClasses{};
+        std::memset(p.panel_count, 0, sizeof(p.panel_count));
+        p.panel_sum_bytes = 0;
+        for (const auto &d : panels) {
+            const int runs = runs_of(d), nb = lora::panel_rank_blocks(d.rank);
+            for (int k = lora::panel_projs(runs, nb) - 1; k < 3; ++k) ++p.panel_classes.end[k];
+            ++p.panel_count[runs][nb];
+            p.panel_sum_bytes += 8.0 * d.n_tok * lora::rank_storage(d.rank);
+        }
+        p.tile_rows = 0;
+        for (int i = 0; i < w.n_tiles; ++i) p.tile_rows += LORA_TILE_TOKENS + (lora::rank_storage(dev_tiles[i].rank) + 15) / 16 * 16;
+    }
     // the tile shrink's run tables
     ShrinkRuns shrink_runs[SHRINK_VARIANTS];
     {
@@ -875,12 +917,15 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         p.shrink_runs[v] = shrink_runs[v].n_runs;
         p.shrink_pieces[v] = shrink_runs[v].any_pieces;
-        p.shrink_pairs[v] = shrink_runs[v].any_pairs;
         p.off_cuts[v] = bytes;
         bytes += align_up(sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
         p.off_sums[v] = bytes;
         bytes += align_up(sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
     }
+    if (bytes + align_up(sizeof(lora::DevItem) * panels.size()) > c.plan_cap) panels.clear();  // (the plan does without)
+    p.off_panels = bytes;
+    p.n_panels = (int32_t)panels.size();
+    bytes += align_up(sizeof(lora::DevItem) * panels.size());
     if (bytes > c.plan_cap) {
         lora_worklists_free(&w);
         return LORA_E_NOMEM;
@@ -956,6 +1001,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
     if (!lin_rows.empty()) std::memcpy(p.pinned + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
     if (!direct.empty()) std::memcpy(p.pinned + p.off_direct, direct.data(), sizeof(lora::DevItem) * direct.size());
+    if (!panels.empty()) std::memcpy(p.pinned + p.off_panels, panels.data(), sizeof(lora::DevItem) * panels.size());
     if (!lin_segs.empty()) std::memcpy(p.pinned + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
         if (!shrink_runs[v].cuts.empty()) std::memcpy(p.pinned + p.off_cuts[v], shrink_runs[v].cuts.data(), sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
@@ -1788,6 +1834,16 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
         put_unit(LORA_UNIT_DIRECT_SHRINK, off, direct[i].n_tok, direct[i].row, direct[i].rank, direct[i].a, std::min(direct[i].a + lora::DIRECT_ROWS, direct[i].rank),
                  direct_shrink(p->n_direct, c->proj[proj].h_in) > 0 ? 1 : 0, direct[i].alpha);
     }
+    // the blocks of the shrink by panels, for groups of 1 to 4 projections, as the kernel maps them
+    const lora::DevItem *panels = reinterpret_cast<const lora::DevItem *>(buf + p->off_panels);
+    for (int gn = 1; gn <= lora::GROUP_MAX_PROJS; ++gn)
+        for (int b = 0; b < 8 * lora::panel_blocks(p->panel_classes, gn) && p->n_panels > 0; ++b) {
+            int panel, first, n;
+            if (!lora::panel_of_block(p->panel_classes, gn, b & 7, b >> 3, p->n_panels, panel, first, n)) continue;
+            const int32_t off = nt;
+            tile_tokens(panels[panel], tok_list);
+            put_unit(LORA_UNIT_PANEL_SHRINK, off, panels[panel].n_tok, panels[panel].row, panels[panel].rank, first, first + n, gn, panels[panel].alpha);
+        }
     // the tile shrink's pieces for this projection's h_in, per run table, walked as the kernel walks them; and the
     // scratch slots the reduce adds up per tile
     for (int v = 0; v < SHRINK_VARIANTS && p->n_tiles > 0; ++v) {
@@ -1979,7 +2035,6 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_
     tb.n_tiles = p->n_tiles;
     tb.v_stride = c->v_stride;
     tb.any_pieces = p->shrink_pieces[v] ? 1 : 0;
-    tb.any_pairs = p->shrink_pairs[v] ? 1 : 0;
     tb.scale = scale;
     tb.direct = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_direct);
     tb.tiles = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_tiles);
@@ -1988,11 +2043,69 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_
     tb.tok_list = reinterpret_cast<const int32_t *>(p->lists);
     tb.v = reinterpret_cast<float *>(sc.v);
     tb.part = reinterpret_cast<float *>(sc.vpart);
+    tb.v_set = sc.v_set_bytes / sizeof(float);
+    tb.n_panels = 0;
     const int64_t rows_per_proj = 2 * (int64_t)lora::SHRINK_SLOT_ROWS * tb.n_runs;
     if (rows_per_proj * n > sc.vpart_rows) return LORA_E_NOMEM;
     tb.v_set = sc.v_set_bytes / sizeof(float);
     tb.part_set = (uint64_t)rows_per_proj * c->v_stride;
     return LORA_OK;
+}
+// The shrink of a launch by panels, where that is the shorter way, and into how many k slices: estimates in microseconds, fitted to launches of one to four projections and lists of four
+// layers, 900 to 22000 tokens in prompts of 60 to 2048 at ranks 16, 128 and 8 to 128, 2048 and 4096 wide (shrink and reduce of 154 of them by the run tables take 1.17 times
+// what they take by the way chosen here in the geometric mean; the best number of slices would make it 1.185).
+// By panels: a block takes 3 us and 2.1 ns per stage and row of it; what the blocks take in comes at 8.3 TB/s, x alone at 6.8; slices have to be added up.
+// By the run table: 11 us with the reduce, 64 + rank rows per tile and stage at 9.8 TB/s.
+static void choose_panels(const lora_cache_t *c, const lora_plan_t *p, const Scratch &sc, lora::TileBatch &tb)
+{
+    if (tb.n_direct > 0 || p->n_panels <= 0 || sc.small) return;
+    struct Kind {  // groups alike
+        int n_k, gn, many;
+    } kinds[8];
+    int n_kinds = 0, least_k = INT32_MAX;
+    for (int i = 0; i < tb.n;) {
+        const int n_k = tb.p[i].h_in / 64, gn = (int)(tb.group[i] >> 8);
+        least_k = std::min(least_k, n_k);
+        int k = 0;
+        while (k < n_kinds && (kinds[k].n_k != n_k || kinds[k].gn != gn)) ++k;
+        if (k == 8) k = 7;  // (a cache has few widths: the rest counts as the last kind)
+        else if (k == n_kinds) kinds[n_kinds++] = Kind{n_k, gn, 0};
+        ++kinds[k].many;
+        i += gn;
+    }
+    double blocks = 0, stage_rows = 0, longest = 0, x_bytes = 0, run_bytes = 0;  // stage_rows: of all blocks, longest: of one
+    for (int k = 0; k < n_kinds; ++k) {
+        const Kind &q = kinds[k];
+        for (int runs = 1; runs <= lora::PANEL_ROWS / 64; ++runs)
+            for (int nb = 1; nb <= 8; ++nb) {
+                const int count = p->panel_count[runs][nb];
+                if (count == 0) continue;
+                const int np = lora::panel_projs(runs, nb), full = q.gn / np, rest = q.gn % np;
+                blocks += (double)q.many * count * (full + (rest > 0));
+                stage_rows += (double)q.many * count * q.n_k * ((full + (rest > 0)) * 64 * runs + q.gn * 16 * nb);
+                longest = std::max(longest, (double)q.n_k * (64 * runs + 16 * nb * std::min(np, q.gn)));
+            }
+        x_bytes += (double)q.many * q.n_k * 128 * p->n_tile_tok;
+        run_bytes += (double)q.many * q.gn * q.n_k * 128 * p->tile_rows;
+    }
+    int best = 0;
+    double best_us = 11 + std::max(run_bytes / 9.8e6, x_bytes / 5.8e6);
+    for (int S : {1, 2, 3, 4, 6, 8, 12, 16}) {
+        if (S > 1 && (least_k < 4 * S || (int64_t)S * tb.n * p->n_tile_tok > sc.vpart_rows)) break;
+        const double n = blocks * S, avg = 3 + 0.0021 * stage_rows / n, all = n * avg / c->n_cu;
+        double us = std::max({3 + 0.0021 * longest / S, 3 + stage_rows * 128 / 8.3e6, 3 + x_bytes / 6.8e6});
+        if (n > 2 * c->n_cu) us = std::max(us, all + 0.8 * avg);
+        else if (n > c->n_cu) us = std::max(us, 1.63 * avg);
+        us += 1.5 + (S > 1 ? 4 + S * tb.n * p->panel_sum_bytes / 7e6 : 0);
+        if (us < best_us) best_us = us, best = S;
+    }
+    if (best == 0) return;
+    for (int i = 0; i < tb.n; ++i) tb.slices[i] = (uint8_t)best;
+    tb.panels = reinterpret_cast<const lora::DevItem *>(p->lists + p->off_panels);
+    tb.n_rows = p->n_tile_tok;
+    tb.n_panels = p->n_panels;
+    tb.classes = p->panel_classes;
+    tb.part_set = (uint64_t)best * tb.n_rows * c->v_stride;
 }
 static lora::BatchProj batch_proj(const lora_cache_t *c, const lora_apply_desc_t &d)
 {
@@ -2161,6 +2274,7 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
             if (p->n_tiles > 0) tb.p[i] = projs[i], tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
         }
     }
+    if (p->n_tiles > 0) choose_panels(c, p, sc, tb);
     // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
     // scratch: when a batch has enough of both, the GEMV launch goes to the cache's side stream, forked off here and
     // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
@@ -2327,6 +2441,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         if (const int rc_s = tile_setup(c, p, 1, a.h_in, pool_scratch(c), scale, tb)) return rc_s;
         tb.p[0] = bp;
         tb.group[0] = 1u << 8;
+        choose_panels(c, p, pool_scratch(c), tb);
         HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
     if (n_gemv_tok > 0) {

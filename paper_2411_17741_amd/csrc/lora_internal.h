@@ -384,6 +384,46 @@ constexpr int SHRINK_STAGE_K = 128;
 // tile x 16 rank rows over the whole of h_in, so that nothing is left to add up.  A unit is a DevItem of its tokens with a = its first rank row.
 constexpr int DIRECT_TOKENS = 16, DIRECT_ROWS = 16;
 constexpr int DIRECT_MAX_UNITS = 2048;  // of a plan; with more it carries none
+// The tile shrink of a long launch: a block per (panel, k slice, up to three projections that read the same x).  A panel is a DevItem of up to PANEL_ROWS rows of one slot.
+// A block's stage of 64 k holds the panel's rows (whole runs of 64) and the rank blocks of its projections, as many projections as fit into PANEL_SLOT_ROWS rows.  A plan's
+// panels come in falling order of their rows there for one projection, so those that take one projection per block come first, then two, then three.
+constexpr int PANEL_ROWS = 192, PANEL_SLOT_ROWS = 416;
+inline __host__ __device__ constexpr int panel_rank_blocks(int rank) { return rank > 96 ? 8 : rank > 64 ? 6 : rank > 32 ? 4 : rank > 16 ? 2 : 1; }  // of 16, as the kernel's bodies come
+inline __host__ __device__ constexpr int panel_projs(int runs, int rank_blocks)  // runs of 64 rows
+{
+    return (PANEL_SLOT_ROWS - 64 * runs) / (16 * rank_blocks) >= 3 ? 3 : (PANEL_SLOT_ROWS - 64 * runs) / (16 * rank_blocks);
+}
+struct PanelClasses {
+    int32_t end[3];  // panels before end[c] take at most c + 1 projections per block
+};
+// of the panels [lo, hi) those with number xcd modulo 8
+inline __host__ __device__ int panel_count(int lo, int hi, int xcd) { return (hi + 7 - xcd) / 8 - (lo + 7 - xcd) / 8; }
+// blocks of an XCD for one slice of a group of gn projections: the most that any XCD has
+inline __host__ __device__ int panel_blocks(const PanelClasses &c, int gn)
+{
+    int most = 0;
+    for (int xcd = 0; xcd < 8; ++xcd) {
+        const int n = panel_count(0, c.end[0], xcd) * gn + panel_count(c.end[0], c.end[1], xcd) * ((gn + 1) / 2) + panel_count(c.end[1], c.end[2], xcd) * ((gn + 2) / 3);
+        most = n > most ? n : most;
+    }
+    return most;
+}
+// block i of such a slice on XCD xcd -> panel and its projections [first, first + n) of the group; false: nothing to do
+inline __host__ __device__ bool panel_of_block(const PanelClasses &c, int gn, int xcd, int i, int n_panels, int &panel, int &first, int &n)
+{
+    for (int k = 0, lo = 0; k < 3; lo = c.end[k], ++k) {
+        const int per = (gn + k) / (k + 1), blocks = panel_count(lo, c.end[k], xcd) * per;
+        if (i < blocks) {
+            const int nth = i / per;
+            panel = (lo + 7 - xcd) / 8 * 8 + xcd + 8 * nth;
+            first = (i - nth * per) * (k + 1);
+            n = gn - first < k + 1 ? gn - first : k + 1;
+            return panel < n_panels;
+        }
+        i -= blocks;
+    }
+    return false;
+}
 // The projections one launch of the tile kernels serves, and the run table the shrink works through for each of them:
 // projections that read the same x are neighbours (a group); projection i's intermediate lies v_set floats behind that of
 // i - 1, its partial sums part_set floats (2 * n_runs slots of SHRINK_SLOT_ROWS rows).
@@ -393,11 +433,13 @@ struct TileBatchHead {
     int32_t n_runs, quanta;   // n_runs: a multiple of 8 (run r is worked on by XCD r / (n_runs / 8))
     int32_t n_tiles, v_stride;
     int32_t any_pieces;       // some tile is worked on in pieces: the reduce launch is needed
-    int32_t any_pairs;        // some run has two whole tiles of one slot behind each other: the kernel that works on two at a time
     float scale;
     const DevItem *tiles;     // device, n_tiles
     const DevItem *direct;    // device, n_direct units; n_direct = 0: the launch works through the run table
     int32_t n_direct;
+    const DevItem *panels;    // device, n_panels panels; n_panels = 0: not by panels
+    int32_t n_panels;
+    int32_t n_rows;           // rows of all panels
     const ShrinkCut *cuts;    // device, n_runs + 1
     const ShrinkSum *sums;    // device, n_tiles
     const int32_t *tok_list;  // device
@@ -409,8 +451,18 @@ template <int N> struct TileBatchArgs : TileBatchHead {  // as the kernels take 
     uint32_t group[N];  // of projection i: first projection of its group | projections of the group << 8
     BatchProj p[N];
 };
-using TileBatch = TileBatchArgs<BATCH_MAX_PROJS>;
-static_assert(sizeof(TileBatch) <= 3500, "kernel arguments are at most 4 KB");
+struct TileBatch : TileBatchArgs<BATCH_MAX_PROJS> {  // as a launcher takes it
+    PanelClasses classes;
+    uint8_t slices[BATCH_MAX_PROJS];  // k slices of projection i's panels (of all projections of a group)
+};
+// blocks of the panels' launch: per group (in the order of the projections) where its blocks end, of one XCD, and first projection | projections << 8 | slices << 16 |
+// the XCD that its first panel falls to << 24; per projection its slices
+template <int N> struct PanelShape {
+    int32_t end[N];
+    uint32_t group[N];
+    uint8_t slices[N];
+};
+static_assert(sizeof(TileBatchArgs<BATCH_MAX_PROJS>) + sizeof(PanelShape<BATCH_MAX_PROJS>) <= 3900, "kernel arguments are at most 4 KB");
 // The LDS that the kernels of a file ask for at launch, made known on the current device: by every cache for its own (each device has
 // limits of its own, and threads that create caches or make calls meanwhile share nothing).
 template <typename K> hipError_t allow_lds(K *kernel, int bytes)

@@ -286,120 +286,7 @@ template <int N> __device__ __forceinline__ void wait_for_all_but()  // the late
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Two whole tiles of one slot that follow each other in a run, side by side: At is taken in once for both.  What a long launch is bound by is what misses
-// L2, and At misses it once per tile (7B mixed batch: 2 GB of x, 2 GB of At): 1871 -> 1807 us for the batch's list.  x and At travel through LDS alone (requests that
-// write it, waited for by count, one barrier per stage of 64 k), since the registers of the body above do not hold two tiles; for a single tile this
-// form is no faster (prefill batch 216.8 against 220.8 us, 7B mixed 1871 against 1893).
-// A ring slot is a stage: 128 rows of x, then 16 NB rows of At (NB: rank blocks of 16), rows of 128 bytes, 16-byte slot s of row r holding piece s ^ ((r / 2) % 8).
-// Wavefront w makes four requests of x rows and 2 NB / 4 of At (the first two wavefronts one more where that is odd), a request being 8 rows, and
-// multiplies token block w of both tiles with every rank block.
-constexpr int SKD = 64, SROW = SKD * 2;        // k elements of a stage and the bytes of a row
-constexpr int RING_BYTES = 3 * (64 + 128) * SROW;  // two slots from rank 65 up, three from 17, four below: two blocks to a compute unit
-static_assert(SK % SKD == 0 && RING_BYTES >= NSTAGE * LORA_TILE_TOKENS * XROW, "pieces are whole stages; the other body's ring is the same memory");
-template <int NB>
-__device__ __forceinline__ void mfma_shrink_pair(const ApplyArgs &a, const DevItem (&it)[2], int st_begin, int n_st, int phase, unsigned char *ring)
-{
-    constexpr int TT = 2, SLOT = (64 * TT + 16 * NB) * SROW, NST = RING_BYTES / SLOT, PER_AT = NB / 2, PX = 2 * TT;  // PER_AT, PX: requests of every wavefront
-    constexpr bool ODD = NB % 2 != 0;
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int m = lane & 15, g = lane >> 4;
-    const int rs = rank_storage(it[0].rank);
-    const __bf16 *At = reinterpret_cast<const __bf16 *>(a.proj_base + (int64_t)it[0].row * a.row_bytes);
-    const int lr = lane >> 3, piece = (lane & 7) ^ ((4 * (w & 1) + (lr >> 1)) & 7);
-    const bool more = ODD && w < 2;
-    const __bf16 *src[PX + PER_AT + ODD];
-#pragma unroll
-    for (int t = 0; t < TT; ++t) {
-        const int ti[2] = {8 * w + lr, 32 + 8 * w + lr};
-        int tok[2];
-        tile_tokens(a, it[t], ti, tok);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) src[2 * t + q] = static_cast<const __bf16 *>(a.x) + (size_t)tok[q] * a.h_in;
-    }
-#pragma unroll
-    for (int q = 0; q < PER_AT + ODD; ++q) src[PX + q] = At + (size_t)min(8 * (w + 4 * q) + lr, rs - 1) * a.h_in;
-    auto request = [&](int st, int slot) {  // (the walk over k starts at another stage in every block, as above)
-        int s = st + phase;
-        s -= s >= n_st ? n_st : 0;
-        const int k = (st_begin + s) * SKD + piece * 8;
-        unsigned char *dst = ring + slot * SLOT + 8 * w * SROW;
-#pragma unroll
-        for (int q = 0; q < PX; ++q) request_to_lds(src[q] + k, dst + 32 * q * SROW);
-#pragma unroll
-        for (int q = 0; q < PER_AT; ++q) request_to_lds(src[PX + q] + k, dst + (64 * TT + 32 * q) * SROW);
-        if (more) request_to_lds(src[PX + PER_AT + ODD - 1] + k, dst + (64 * TT + 32 * PER_AT) * SROW);
-    };
-    floatx4 acc[TT][NB];
-#pragma unroll
-    for (int t = 0; t < TT; ++t)
-#pragma unroll
-        for (int q = 0; q < NB; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
-    auto multiply = [&](int slot) {
-        const unsigned char *xs = ring + slot * SLOT + (16 * w + m) * SROW, *as = ring + slot * SLOT + (64 * TT + m) * SROW;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int at = ((4 * ks + g) ^ ((m >> 1) & 7)) << 4;
-            bf16x8 xo[TT];
-#pragma unroll
-            for (int t = 0; t < TT; ++t) xo[t] = *reinterpret_cast<const bf16x8 *>(xs + 64 * t * SROW + at);
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const bf16x8 ao = *reinterpret_cast<const bf16x8 *>(as + 16 * q * SROW + at);
-#pragma unroll
-                for (int t = 0; t < TT; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[t], ao, acc[t][q], 0, 0, 0);
-            }
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read when this wavefront is at the next barrier
-    };
-    auto wait = [&](auto left_tag) {
-        constexpr int LEFT = decltype(left_tag)::value;
-        if (more) wait_for_all_but<LEFT *(PX + 1 + PER_AT)>();
-        else wait_for_all_but<LEFT *(PX + PER_AT)>();
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s)
-        if (s < n_st) request(s, s);
-    int slot = 0, fill = NST - 1;
-    for (int st = 0; st < n_st - (NST - 1); ++st) {
-        wait(std::integral_constant<int, NST - 2>{});
-        request(st + NST - 1, fill);
-        multiply(slot);
-        fill = slot;
-        slot = slot + 1 == NST ? 0 : slot + 1;
-    }
-    auto last = [&](auto left_tag) {
-        constexpr int LEFT = decltype(left_tag)::value;
-        if constexpr (LEFT < NST - 1) {
-            if (n_st <= LEFT) return;
-            wait(left_tag);
-            multiply(slot);
-            slot = slot + 1 == NST ? 0 : slot + 1;
-        }
-    };
-    last(std::integral_constant<int, 2>{});
-    last(std::integral_constant<int, 1>{});
-    last(std::integral_constant<int, 0>{});
-    static_assert(NST >= 2 && NST <= 4, "the walk's last stages");
-    __bf16 *const out16 = reinterpret_cast<__bf16 *>(a.v);
-    const float s_v = a.scale * it[0].alpha;
-#pragma unroll
-    for (int t = 0; t < TT; ++t) {
-        int ti[4], rows[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) ti[r] = rows[r] = 16 * w + 4 * g + r;
-        tile_tokens(a, it[t], ti, rows);
-#pragma unroll
-        for (int q = 0; q < NB; ++q)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int jr = 16 * q + m;
-                if (ti[r] < it[t].n_tok && jr < it[t].rank) out16[(size_t)rows[r] * (2 * a.v_stride) + jr] = (__bf16)(s_v * acc[t][q][r]);
-            }
-    }
-}
+constexpr int SKD = 64, SROW = SKD * 2;  // k elements of a stage of the kernels below, and the bytes of a row
 
 // the arguments of one projection of the batch
 template <int N>
@@ -420,7 +307,7 @@ __device__ __forceinline__ ApplyArgs tile_args(const TileBatchArgs<N> &tb, int p
     return a;
 }
 
-template <int N, bool PAIRS>
+template <int N>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_shrink_kernel(const ShrinkCut *__restrict__ cuts, const DevItem *__restrict__ tiles, int runs_per_xcd, int n_proj, int quanta,
                                                                                                         int n_tiles, TileBatchArgs<N> tb)
 {
@@ -457,22 +344,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                              ? nullptr
                              : tb.part + (size_t)pj * tb.part_set + (size_t)shrink_slot(run, from.tile, tile) * SHRINK_SLOT_ROWS * a.v_stride;
         const int NB = (it.rank + 15) >> 4;
-        DevItem next{};
-        if constexpr (PAIRS) next = tiles[min(tile + 1, n_tiles - 1)];
-        if (PAIRS && !my_part && tile + 1 < to.tile && next.row == it.row) {  // (the next tile is a whole one of this run too; uniform over the block)
-            const DevItem two[2] = {it, next};
-            const int stages = (k_end - k_begin) / SKD, at = phase * (SK / SKD);
-            switch (NB) {
-            case 1: mfma_shrink_pair<1>(a, two, k_begin / SKD, stages, at, ring); break;
-            case 2: mfma_shrink_pair<2>(a, two, k_begin / SKD, stages, at, ring); break;
-            case 3: mfma_shrink_pair<3>(a, two, k_begin / SKD, stages, at, ring); break;
-            case 4: mfma_shrink_pair<4>(a, two, k_begin / SKD, stages, at, ring); break;
-            case 5:
-            case 6: mfma_shrink_pair<6>(a, two, k_begin / SKD, stages, at, ring); break;
-            default: mfma_shrink_pair<8>(a, two, k_begin / SKD, stages, at, ring); break;
-            }
-            ++tile;
-        } else if (NB > 4) mfma_shrink_body<true, 2>(a, it, k_begin, k_end, phase, my_part, xs);
+        if (NB > 4) mfma_shrink_body<true, 2>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 4) mfma_shrink_body<true, 1>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 3) mfma_shrink_body<false, 3>(a, it, k_begin, k_end, phase, my_part, xs);
         else if (NB == 2) mfma_shrink_body<false, 2>(a, it, k_begin, k_end, phase, my_part, xs);
@@ -576,6 +448,254 @@ __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArg
     int tok[1];
     tile_tokens(a, it, tix, tok);
     if (ti < it.n_tok && jr < it.rank) reinterpret_cast<__bf16 *>(a.v)[(size_t)tok[0] * (2 * a.v_stride) + jr] = (__bf16)(a.scale * it.alpha * v);
+}
+
+// ---------------------------------------------------------------------------------------
+// shrink of a longer launch: a block of 8 wavefronts per (panel, k slice, up to three projections that read the same x), a panel being up to 192 rows of one slot (the tiles of
+// a prompt put together again).
+// What bounded the kernel above there is what misses L2: At once per tile of 64 rows, and x once per projection, since the blocks of q, k and v drift apart by more than an L2 holds of what
+// 32 units have on their way (7B mixed batch: 2.9 GB fetched, 1.7 of them x; 1.65 GB this way).  Here At comes in once per panel and x once per group, and a launch is then bound by what
+// the units take in (45 to 60 bytes per ns each), or by the memory where many small ranks make x nearly everything.
+// x and At travel through an LDS ring of three to six stages of 64 k that the requests write themselves, waited for by count, one barrier per stage.  A ring slot: 64 TT rows of x, then 16 NB
+// rows of At per projection (NB: rank blocks of 16), rows of 128 bytes, 16-byte slot s of row r holding piece s ^ ((r / 2) % 8).  Wavefront w multiplies every fourth row block with one half of
+// the rank blocks: with all of them per wavefront and two row blocks each, the operand reads out of LDS took longer than the loads (7B mixed batch 491 us, 443 this way).
+// 192 rows: with 256 three projections of rank 64 leave no room for three stages.  The panels are dealt out to the XCDs one by one, the costliest first: in runs of neighbours per XCD, as
+// the kernel above takes its tiles, some XCDs got most of the rank-128 panels (443 -> 338 us); a panel's blocks, if it has several, run side by side on one XCD.
+// Measured, shrink and reduce of a launch, run table -> panels: 7B mixed batch (14 projections) 491 -> 338 us, eight prompts on q of eight layers 89 -> 75, 13B batch 100 -> 82;
+// q, k, v of 17650 tokens in 100 prompts 99.6 -> 78.8, of 8485 in 20 prompts 45 -> 38 (three slices); one projection of 4291 tokens 20.2 -> 19.3 (six slices).
+// ---------------------------------------------------------------------------------------
+namespace {
+constexpr int PANEL_RING = 156 << 10;  // of the 160 KB of a unit: one block to a unit
+static_assert(PANEL_SLOT_ROWS * SROW * 3 <= PANEL_RING, "three stages at least");
+}
+struct PanelArgs {
+    const __bf16 *x, *at0;
+    int64_t at1, at2;  // At of the block's projections: the first, and how many elements further the others lie
+    const int32_t *tok_list;
+    __bf16 *v;    // of the first projection; the next lie v_set floats further
+    float *part;  // the slice's sums of the panel, as v; null: the slice is everything, the result goes to v
+    uint64_t v_set, part_set;
+    int h_in, v_stride;
+    float scale;
+};
+template <int TT, int NB, int NP>
+__device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevItem &it, int st_begin, int n_st, int phase, unsigned char *ring)
+{
+    constexpr int NBT = NB * NP;  // rank blocks of all projections
+    constexpr int SLOT = (64 * TT + 16 * NBT) * SROW, FIT = PANEL_RING / SLOT, NST = FIT < 6 ? FIT : 6, PER_AT = NBT / 4;
+    // a wavefront's products: TT row blocks (every fourth) with half of the rank blocks; where there is but one of those, half of the row blocks
+    constexpr bool ODD = NBT % 4 != 0, HALF_ROWS = NBT == 1;
+    constexpr int RB = HALF_ROWS ? (TT + 1) / 2 : TT, NQ = (NBT + 1) / 2, STEP = HALF_ROWS ? 8 : 4;  // STEP: between a wavefront's row blocks
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int rs = rank_storage(it.rank);
+    const int lr = lane >> 3, piece = (lane & 7) ^ ((4 * (w & 1) + (lr >> 1)) & 7);
+    const bool more = ODD && w < 2 * (NBT % 4);
+    const __bf16 *src[TT + PER_AT + ODD];
+    {
+        int ti[TT], tok[TT];
+#pragma unroll
+        for (int q = 0; q < TT; ++q) ti[q] = 8 * w + 64 * q + lr;
+        tile_tokens_of(a.tok_list, it, ti, it.tok0, tok);  // (rows past the panel's end repeat its last)
+#pragma unroll
+        for (int q = 0; q < TT; ++q) src[q] = a.x + (size_t)tok[q] * a.h_in;
+    }
+#pragma unroll
+    for (int q = 0; q < PER_AT + ODD; ++q) {
+        const int grp = min(w + 8 * q, 2 * NBT - 1), pj = NP == 1 ? 0 : grp / (2 * NB), r = 8 * (grp - 2 * NB * pj) + lr;  // (wavefront-uniform but for lr)
+        const __bf16 *at = a.at0;
+        if constexpr (NP > 1) at += pj == 1 ? a.at1 : 0;
+        if constexpr (NP > 2) at += pj == 2 ? a.at2 : 0;
+        src[TT + q] = at + (size_t)min(r, rs - 1) * a.h_in;  // (rows past the stored rank: never written)
+    }
+    auto request = [&](int st, int slot) {
+        int s = st + phase;
+        s -= s >= n_st ? n_st : 0;
+        const int k = (st_begin + s) * SKD + piece * 8;
+        unsigned char *dst = ring + slot * SLOT + 8 * w * SROW;
+#pragma unroll
+        for (int q = 0; q < TT; ++q) request_to_lds(src[q] + k, dst + 64 * q * SROW);
+#pragma unroll
+        for (int q = 0; q < PER_AT; ++q) request_to_lds(src[TT + q] + k, dst + (64 * TT + 64 * q) * SROW);
+        if (more) request_to_lds(src[TT + PER_AT + ODD - 1] + k, dst + (64 * TT + 64 * PER_AT) * SROW);
+    };
+    floatx4 acc[RB][NQ];
+#pragma unroll
+    for (int t = 0; t < RB; ++t)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[t][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int rb0 = w % STEP, q0 = HALF_ROWS ? 0 : (w >> 2) * NQ;
+    auto row_live = [&](int t) { return RB * STEP == 4 * TT || rb0 + STEP * t < 4 * TT; };  // (uniform)
+    auto rank_live = [&](int q) { return NQ * 2 == NBT || HALF_ROWS || q0 + q < NBT; };
+    auto multiply = [&](int slot) {
+        const unsigned char *xs = ring + slot * SLOT + (16 * rb0 + m) * SROW, *as = ring + slot * SLOT + (64 * TT + 16 * q0 + m) * SROW;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const int at = ((4 * ks + g) ^ ((m >> 1) & 7)) << 4;
+            bf16x8 xo[RB];
+#pragma unroll
+            for (int t = 0; t < RB; ++t) xo[t] = *reinterpret_cast<const bf16x8 *>(xs + (row_live(t) ? 16 * STEP * t : 0) * SROW + at);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const bf16x8 ao = *reinterpret_cast<const bf16x8 *>(as + (rank_live(q) ? 16 * q : 0) * SROW + at);
+#pragma unroll
+                for (int t = 0; t < RB; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[t], ao, acc[t][q], 0, 0, 0);
+            }
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read when this wavefront is at the next barrier
+    };
+    auto wait = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;
+        if (more) wait_for_all_but<LEFT *(TT + 1 + PER_AT)>();
+        else wait_for_all_but<LEFT *(TT + PER_AT)>();
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s)
+        if (s < n_st) request(s, s);
+    int slot = 0, fill = NST - 1;
+    for (int st = 0; st < n_st - (NST - 1); ++st) {
+        wait(std::integral_constant<int, NST - 2>{});
+        request(st + NST - 1, fill);
+        multiply(slot);
+        fill = slot;
+        slot = slot + 1 == NST ? 0 : slot + 1;
+    }
+    auto last = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;
+        if constexpr (LEFT < NST - 1) {
+            if (n_st <= LEFT) return;
+            wait(left_tag);
+            multiply(slot);
+            slot = slot + 1 == NST ? 0 : slot + 1;
+        }
+    };
+    last(std::integral_constant<int, 4>{});
+    last(std::integral_constant<int, 3>{});
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 0>{});
+    static_assert(NST >= 3 && NST <= 6, "the walk's last stages");
+    const float s_v = a.scale * it.alpha;
+    int ti[4 * RB], rows[4 * RB];
+#pragma unroll
+    for (int t = 0; t < RB; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ti[4 * t + r] = 16 * (rb0 + STEP * t) + 4 * g + r;
+    if (!a.part) tile_tokens_of(a.tok_list, it, ti, it.tok0, rows);
+#pragma unroll
+    for (int t = 0; t < RB; ++t) {
+        if (!row_live(t)) continue;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if (!rank_live(q)) continue;
+            const int qq = q0 + q, pj = NP == 1 ? 0 : qq / NB, jr = 16 * (qq - NB * pj) + m;  // a rank block of projection pj (wavefront-uniform)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 4 * t + r;
+                if (ti[i] < it.n_tok && jr < it.rank) {
+                    if (a.part) a.part[pj * a.part_set + (size_t)ti[i] * a.v_stride + jr] = acc[t][q][r];
+                    else a.v[2 * pj * a.v_set + (size_t)rows[i] * (2 * a.v_stride) + jr] = (__bf16)(s_v * acc[t][q][r]);
+                }
+            }
+        }
+    }
+}
+
+template <int N>
+__global__ __launch_bounds__(512) void mfma_panel_kernel(const DevItem *panels, int n_panels, PanelClasses cls, PanelShape<N> sh, TileBatchArgs<N> tb)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
+    // XCD j = blockIdx % 8 works on every eighth panel of every group of projections, group by group (the groups of long rows first) and slice by slice, the blocks of a panel side by side
+    const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
+    int gi = 0;  // the first group whose blocks end behind this one
+#pragma unroll
+    for (int step = N / 2; step > 0; step >>= 1)
+        if (local >= sh.end[gi + step - 1]) gi += step;
+    const uint32_t grp = sh.group[gi];
+    const int g0 = (int)(grp & 0xffu), gn = (int)(grp >> 8 & 0xffu), slices = (int)(grp >> 16 & 0xffu);
+    const int begin = gi ? sh.end[gi - 1] : 0, in_group = local - begin, per_slice = (sh.end[gi] - begin) / slices;
+    const int slice = in_group / per_slice;
+    const int turn = (int)(grp >> 24) + slice * n_panels;  // the panels are dealt out on and on, not from XCD 0 again for every slice
+    int panel, first, n;
+    if (!panel_of_block(cls, gn, (xcd - turn) & 7, in_group - slice * per_slice, n_panels, panel, first, n)) return;  // padding
+    const DevItem it = panels[panel];
+    const int pj = g0 + first;
+    auto at_of = [&](int i) {
+        const BatchProj &p = tb.p[pj + i];
+        return reinterpret_cast<const __bf16 *>(p.proj_base + (int64_t)it.row * (p.h_in + p.h_out) * 2);
+    };
+    PanelArgs a;
+    a.x = static_cast<const __bf16 *>(tb.p[pj].x);
+    a.at0 = at_of(0), a.at1 = at_of(n > 1 ? 1 : 0) - a.at0, a.at2 = at_of(n > 2 ? 2 : 0) - a.at0;
+    a.tok_list = tb.tok_list;
+    a.v = reinterpret_cast<__bf16 *>(tb.v + (size_t)pj * tb.v_set);
+    a.part = slices == 1 ? nullptr : tb.part + (size_t)pj * tb.part_set + ((size_t)slice * tb.n_rows + it.tok_off) * tb.v_stride;
+    a.v_set = tb.v_set, a.part_set = tb.part_set;
+    a.h_in = tb.p[pj].h_in, a.v_stride = tb.v_stride;
+    a.scale = tb.scale;
+    const int n_k = a.h_in / SKD, k_lo = n_k * slice / slices, n_st = n_k * (slice + 1) / slices - k_lo;
+    const int phase = (int)((unsigned)(it.row * 5 + g0 * 7) % (unsigned)n_st);
+    const int nb = panel_rank_blocks(it.rank), tt = (it.n_tok + 63) >> 6;
+    auto go = [&](auto tt_tag, auto nb_tag) __attribute__((always_inline)) {
+        constexpr int T = decltype(tt_tag)::value, B = decltype(nb_tag)::value, MOST = panel_projs(T, B);
+        if constexpr (MOST >= 3) if (n == 3) return mfma_panel_body<T, B, 3>(a, it, k_lo, n_st, phase, ring);
+        if constexpr (MOST >= 2) if (n == 2) return mfma_panel_body<T, B, 2>(a, it, k_lo, n_st, phase, ring);
+        mfma_panel_body<T, B, 1>(a, it, k_lo, n_st, phase, ring);
+    };
+    auto with_rows = [&](auto tt_tag) __attribute__((always_inline)) {
+        if (nb == 8) go(tt_tag, std::integral_constant<int, 8>{});
+        else if (nb == 6) go(tt_tag, std::integral_constant<int, 6>{});
+        else if (nb == 4) go(tt_tag, std::integral_constant<int, 4>{});
+        else if (nb == 2) go(tt_tag, std::integral_constant<int, 2>{});
+        else go(tt_tag, std::integral_constant<int, 1>{});
+    };
+    if (tt == 3) with_rows(std::integral_constant<int, 3>{});
+    else if (tt == 2) with_rows(std::integral_constant<int, 2>{});
+    else with_rows(std::integral_constant<int, 1>{});
+}
+
+// V[token][0..rank) = the sum of the slices' sums, for the rows of all panels.  Bound by its two trips to memory (the panel, then the sums): 4 to 9 us
+template <int N>
+__global__ __launch_bounds__(256) void mfma_panel_sum_kernel(const DevItem *panels, PanelShape<N> sh, TileBatchArgs<N> tb)
+{
+    // a block per (panel, 32 rows, projection); a thread sums one float4 column of four rows
+    constexpr int PER = PANEL_ROWS / 32;
+    const int pj = (int)blockIdx.y, slices = sh.slices[pj];
+    if (slices == 1) return;
+    const int panel = blockIdx.x / PER, part = blockIdx.x - panel * PER;
+    const DevItem it = panels[panel];
+    const int t0 = part * 32 + (threadIdx.x >> 5), j4 = threadIdx.x & 31;
+    if ((part * 32 >= it.n_tok) | (j4 * 4 >= rank_storage(it.rank))) return;
+    const int pitch = tb.v_stride >> 2;
+    const float4 *src = reinterpret_cast<const float4 *>(tb.part + (size_t)pj * tb.part_set) + (size_t)it.tok_off * pitch + j4;
+    int ti[4], tok[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ti[i] = t0 + 8 * i;
+    tile_tokens_of(tb.tok_list, it, ti, it.tok0, tok);
+    float4 sum[4];
+    for (int s = 0; s < slices; ++s) {
+        float4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = src[((size_t)s * tb.n_rows + min(ti[i], it.n_tok - 1)) * pitch];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (s == 0) sum[i] = v[i];
+            else sum[i].x += v[i].x, sum[i].y += v[i].y, sum[i].z += v[i].z, sum[i].w += v[i].w;
+        }
+    }
+    const float s_v = tb.scale * it.alpha;
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    __bf16 *const out = reinterpret_cast<__bf16 *>(tb.v + (size_t)pj * tb.v_set);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (ti[i] >= it.n_tok) continue;
+        bf16x4_t o;
+        o[0] = (__bf16)(s_v * sum[i].x), o[1] = (__bf16)(s_v * sum[i].y), o[2] = (__bf16)(s_v * sum[i].z), o[3] = (__bf16)(s_v * sum[i].w);
+        reinterpret_cast<bf16x4_t *>(out + (size_t)tok[i] * (2 * tb.v_stride))[j4] = o;
+    }
 }
 
 // V[token][0..rank) = sum over the tile's pieces of their partial sums, for the tiles worked on in pieces.
@@ -850,7 +970,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <typename F> static void with_batch_size(const TileBatch &tb, F go)
 {
     if (tb.n > GROUP_MAX_PROJS) {
-        go(tb);
+        go(static_cast<const TileBatchArgs<BATCH_MAX_PROJS> &>(tb));
         return;
     }
     TileBatchArgs<GROUP_MAX_PROJS> g;
@@ -863,15 +983,15 @@ template <typename F> static void with_batch_size(const TileBatch &tb, F go)
 }
 
 template <int W> constexpr int direct_lds = W *DRING *DSTAGE;
-template <bool PAIRS> constexpr int shrink_lds = PAIRS ? RING_BYTES : NSTAGE * LORA_TILE_TOKENS * XROW;
+constexpr int SHRINK_LDS = NSTAGE * LORA_TILE_TOKENS * XROW;
 
 // A kernel's limit of LDS belongs to the device that is current when it is set
 template <int N> static hipError_t prepare_shrinks()
 {
     hipError_t e = allow_lds(mfma_shrink_direct_kernel<N, 4>, direct_lds<4>);
     if (e == hipSuccess) e = allow_lds(mfma_shrink_direct_kernel<N, 8>, direct_lds<8>);
-    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N, false>, shrink_lds<false>);
-    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N, true>, shrink_lds<true>);
+    if (e == hipSuccess) e = allow_lds(mfma_panel_kernel<N>, PANEL_RING);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N>, SHRINK_LDS);
     return e;
 }
 hipError_t prepare_mfma_kernels()
@@ -897,17 +1017,33 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
         });
         return hipGetLastError();
     }
+    if (batch.n_panels > 0) {
+        with_batch_size(batch, [&](const auto &tb) {
+            constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
+            PanelShape<N> sh;
+            int end = 0, groups = 0, before = 0;  // before: slices of the groups before
+            bool sums = false;
+            for (int i = 0; i < tb.n; ++groups) {
+                const int gn = (int)(batch.group[i] >> 8);
+                sh.group[groups] = (uint32_t)i | (uint32_t)gn << 8 | (uint32_t)batch.slices[i] << 16 | (uint32_t)(before * tb.n_panels & 7) << 24;
+                before += batch.slices[i];
+                sh.end[groups] = end += panel_blocks(batch.classes, gn) * batch.slices[i];
+                for (int k = 0; k < gn; ++k, ++i) sh.slices[i] = batch.slices[i];
+                sums |= sh.slices[i - 1] > 1;
+            }
+            for (int g = groups; g < N; ++g) sh.end[g] = end, sh.group[g] = sh.group[groups - 1];
+            for (int i = tb.n; i < N; ++i) sh.slices[i] = 1;
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N>, dim3(8 * end), dim3(512), PANEL_RING, st, tb.panels, tb.n_panels, batch.classes, sh, tb);
+            if (sums) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_panel_sum_kernel<N>, dim3(tb.n_panels * (PANEL_ROWS / 32), tb.n), dim3(256), 0, st, tb.panels, sh, tb);
+        });
+        return hipGetLastError();
+    }
     if (batch.n_runs <= 0) return hipSuccess;
     if (batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
     with_batch_size(batch, [&](const auto &tb) {
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
-        auto go = [&](auto pairs_tag) {
-            constexpr bool PAIRS = decltype(pairs_tag)::value;
-            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N, PAIRS>, dim3(tb.n_runs * tb.n), dim3(256), shrink_lds<PAIRS>, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
-                     tb.quanta, tb.n_tiles, tb);
-        };
-        if (tb.any_pairs) go(std::true_type{});  // (a kernel of its own: beside the other body it costs launches without pairs 1 %)
-        else go(std::false_type{});
+        launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), SHRINK_LDS, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
+                 tb.quanta, tb.n_tiles, tb);
         if (tb.any_pieces) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel<N>, dim3(tb.n_tiles * 8, tb.n), dim3(256), 0, st, tb);
     });
     return hipGetLastError();
