@@ -45,6 +45,13 @@ constexpr int N_LINEAR_SPLITS = 256;  // split tiles of lora_linear_plan (tiles 
 // 430 of rank 32 11.9 / 11.5, 430 of rank 128 28.2 / 13.6, 1000 of rank 32 at 1024 12.6 / 10.6, 2300 of rank 8 at 2048 15.9 / 13.7).  Launches with
 // enough work for wide items take 0.45 (rank 128) to 1.3 (rank 8) times what the items of four tokens take, which the first formula stands for.
 constexpr double GEMV_FIXED_US = 4.0, TILE_FIXED_US = 10.5;
+// Beside the base product: a shrink launch, the fp32 term of GEMV rows
+constexpr double LINEAR_SHRINK_US = 3.0, LINEAR_TERM_US = 1.0;
+// The lists that a plan whose own have no tiles makes for such launches cost it about 6 us, once.  What a launch has to gain by them: a list of projections nearly all of it, a base product its share
+// if the plan serves every projection of every layer once.  (The choice looks at nothing but the cache, the plan and the launch: the same call gives the same bits.)  Measured, us a pass with GEMV alone and as chosen:
+// q, k, v, o of two layers, prompts of 11 to 1136 tokens at rank 64 180 and 88; all of two 13B layers, 73 tokens of rank 128 77 and 50; q, k, v of eight layers, 922 one-token requests over 20 adapters 92 and 83;
+// base product of q, k, v, o 4096 wide, 941 tokens 256 and 216, of q 5120 wide, 1543 tokens 132 and 115.  Of 120 drawn lists and products it picks the better way but for 0.5 % in the geometric mean.
+constexpr double TILED_LISTS_US = 5.0, LINEAR_MIN_GAIN_US = 1.0, LISTS_COST_US = 6.0;
 constexpr double TILE_BESIDE_GEMV_US = 3.0;  // more, where a GEMV launch runs as well (200 one-token requests beside prompts of 300 / 1000 / 2048 tokens, GEMV 22.2 / 28.4 / 53.8, with tiles 24.9 / 29.1 / 48.6 us)
 double gemv_tokens_us(int32_t n_tok, int32_t rank, double width, bool wide)
 {
@@ -52,6 +59,14 @@ double gemv_tokens_us(int32_t n_tok, int32_t rank, double width, bool wide)
     return (n_tok + 3) / 4 * (0.004 + 0.0037 * k + rank * (0.00067 + 0.00023 * k)) * (wide ? std::min(1.3, 0.4 + 7.0 / rank) : 1.0);
 }
 double tile_tokens_us(int32_t n_tok, int32_t rank, double width) { return n_tok * width * (3.0 / 7e6 + 5.4e-9 * rank); }
+// the same summed up over a batch's tokens, for launches of several projections
+struct PathCost {
+    double each = 0, per_width = 0;
+    void add_gemv(int32_t n_tok, int32_t rank, bool wide) { add(gemv_tokens_us(n_tok, rank, 0, wide), gemv_tokens_us(n_tok, rank, 2048, wide)); }
+    void add_tile(int32_t n_tok, int32_t rank) { add(0, tile_tokens_us(std::max(n_tok, 40), rank, 2048)); }  // (a tile of few tokens costs its blocks no less: 8 tiles of 16 on 56 projections 5120 wide 115 us)
+    void add(double at_0, double at_2048) { each += at_0, per_width += (at_2048 - at_0) / 2048; }
+    double us(int n, double sum_width) const { return n * each + per_width * sum_width; }
+};
 // A tile-shrink launch runs as mfma_shrink_direct_kernel up to so many bytes taken in by its units (64 h_in each): 4000 tokens of ranks 8 to 128, 4096 wide, one
 // projection (0.22 GB) 33.3 us per call against 37.4 through the run table; 2300 tokens, mostly of rank 128 (0.27 GB), 67 against 60; eight prompts of ranks 16 to 128 with the
 // base product (0.34 GB) 159 against 155.
@@ -155,16 +170,9 @@ struct Stage {
 
 }  // namespace
 
-struct lora_plan {
-    bool in_use = false;
-    bool internal = false;
-    char *dev = nullptr;
-    char *pinned = nullptr;
-    const char *pinned_dev = nullptr;  // the same as the device sees it
-    const char *lists = nullptr;       // where the kernels read the lists: dev, or pinned_dev
-    hipEvent_t ev_upload = nullptr;
-    bool upload_pending = false;
-    int32_t last_use = -1;  // fence of the latest call that used the plan
+// The work lists of a batch cut one way (one threshold between tiles and GEMV groups), and where they lie behind `lists`
+struct PlanLists {
+    const char *lists = nullptr;  // where the kernels read them
     int32_t T = 0;
     int32_t n_tok_list = 0, n_tiles = 0, n_gs = 0, n_ge = 0;
     int32_t n_tile_tok = 0;  // tokens of all tiles = leading entries of tok_list
@@ -173,13 +181,13 @@ struct lora_plan {
     int32_t shrink_runs[SHRINK_VARIANTS] = {0};
     bool shrink_pieces[SHRINK_VARIANTS] = {false};
     size_t off_cuts[SHRINK_VARIANTS] = {0}, off_sums[SHRINK_VARIANTS] = {0};
-    int32_t mfma_min_used = 0;  // the threshold the work lists were made with
-    uint64_t build_seq = 0;     // changes whenever the plan's lists are rebuilt
-    size_t off_tiles = 0, off_gs = 0, off_ge = 0, bytes = 0;
+    uint64_t build_seq = 0;  // changes whenever the lists are rebuilt
+    size_t off_tiles = 0, off_gs = 0, off_ge = 0;
     int32_t n_wgs = 0, n_wge = 0;  // the GEMV work as wide items (bf16 caches)
     size_t off_wgs = 0, off_wge = 0;
     // for lora_linear_plan: the list of every token of the batch, its runs of rows and its segments (lora::LinearList)
     size_t off_lin_tok = 0, off_lin_rows = 0, off_lin_segs = 0;
+    int32_t n_lin_rows = 0, n_lin_segs = 0;
     size_t off_direct = 0;  // units of a short tile shrink (0 of them: too many for that)
     int32_t n_direct = 0;
     size_t off_panels = 0;  // panels of a long tile shrink
@@ -188,7 +196,26 @@ struct lora_plan {
     int32_t panel_count[lora::PANEL_ROWS / 64 + 1][9] = {{0}};  // by runs of 64 rows and rank blocks
     double panel_sum_bytes = 0;  // of one slice's sums, written and read
     int64_t tile_rows = 0;       // rows the run table's kernel takes in per stage: 64 and the rank of every tile
-    int32_t n_lin_rows = 0, n_lin_segs = 0;
+};
+
+struct lora_plan : PlanLists {  // (the lists that a call for one projection works through)
+    bool in_use = false;
+    bool internal = false;
+    char *dev = nullptr;
+    char *pinned = nullptr;
+    const char *pinned_dev = nullptr;  // the same as the device sees it; the lists are in dev or there
+    hipEvent_t ev_upload = nullptr;
+    bool upload_pending = false;
+    int32_t last_use = -1;  // fence of the latest call that used the plan
+    int32_t mfma_min_used = 0;  // the threshold the work lists were made with
+    size_t bytes = 0;           // of all lists
+    // Where a call for one projection leaves the tokens that could be tiles to the GEMV kernels, launches that share the tile path's fixed cost, and the base product, which needs
+    // no expand launch, may do better with tiles: what it takes to tell (for the threshold 16), and those lists, made for the first launch that asks for them
+    bool may_tile = false, has_tiled = false;
+    PathCost gemv_cost[2], rest_cost[2], tile_cost;  // GEMV tokens [items, wide items] of the lists and of those with tiles; the tile tokens
+    int32_t rest_groups = 0, rest_wgs = 0, tile_tok = 0, tile_segs = 0;
+    std::vector<int32_t> segs[3];  // the batch: offsets, slots, ranks
+    PlanLists tiled;
     std::vector<int32_t> slots;        // distinct slots the batch names
     std::vector<uint32_t> generations;  // their generation at plan time
 };
@@ -679,67 +706,23 @@ int32_t direct_shrink(int32_t n_units, int64_t sum_h_in)
     return n_units * 2 * (lora::DIRECT_TOKENS + lora::DIRECT_ROWS) * sum_h_in <= DIRECT_SHRINK_MAX_BYTES ? n_units : 0;
 }
 
-// Validates a batch against the slot table and writes its work lists into plan `p`
-// (pinned copy + upload on `st`).
-int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
-               const int32_t *seg_rank, int32_t n_seg, hipStream_t st)
+// Work lists on their way into a plan
+struct ListBuild {
+    lora_worklists_t w{};
+    std::vector<int> group_order;
+    int64_t n_gs = 0, n_ge = 0, n_wgs = 0, n_wge = 0;
+    std::vector<lora::DevItem> direct, panels;
+    ShrinkRuns shrink_runs[SHRINK_VARIANTS];
+    std::vector<int32_t> lin_tok;
+    std::vector<lora::LinearRows> lin_rows;
+    std::vector<lora::LinearSeg> lin_segs;
+    ~ListBuild() { lora_worklists_free(&w); }
+    size_t size(const lora_cache &c, PlanLists &p, bool internal, bool tables, int32_t T, size_t room);
+    void write(const lora_cache &c, const PlanLists &p, char *to) const;
+};
+// Everything but the writing: the bytes the lists take (panels only if they fit into `room`).  Without `tables` the tile shrink has panels alone.
+size_t ListBuild::size(const lora_cache &c, PlanLists &p, bool internal, bool tables, int32_t T, size_t room)
 {
-    if (T < 0 || T > c.max_tokens || n_seg < 0 || n_seg > c.max_segments) return LORA_E_INVAL;
-    lora_worklists_t w;
-    int rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, c.mfma_min, &w);
-    if (rc != LORA_OK) return rc;
-    p.mfma_min_used = c.mfma_min;
-    // With the threshold left to the library: the tile path costs two launches more per apply, which a batch with few tile tokens does
-    // not earn back.  So: what its tokens cost either way; below, everything stays GEMV; else the batch pays for the tile launches
-    // anyway and smaller pools of tokens become tiles too.
-    if (c.mfma_min_auto && w.n_tiles > 0) {
-        double mean_width = 0;
-        for (const auto &pr : c.proj) mean_width += (double)pr.h_in + pr.h_out;
-        mean_width /= (double)c.proj.size();
-        std::unordered_map<int32_t, std::pair<int32_t, int32_t>> of_slot;  // slot -> (tile tokens, rank)
-        for (int i = 0; i < w.n_tiles; ++i) {
-            auto &e = of_slot[w.tiles[i].slot];
-            e.first += w.tiles[i].n_tok;
-            e.second = w.tiles[i].rank;
-        }
-        const bool other = w.n_groups > 0;
-        double gemv_us = other ? 0.0 : GEMV_FIXED_US, tile_us = TILE_FIXED_US + (other ? TILE_BESIDE_GEMV_US : 0.0);
-        int64_t n_wide = 0;
-        for (int i = 0; i < w.n_groups; ++i) n_wide += wide_shrink_items(w.groups[i].n_tok, w.groups[i].rank);
-        for (const auto &kv : of_slot) n_wide += wide_shrink_items(kv.second.first, kv.second.second);
-        const bool wide = c.dtype == LORA_BF16 && !c.small_scratch && n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP;
-        for (const auto &kv : of_slot) {
-            gemv_us += gemv_tokens_us(kv.second.first, kv.second.second, mean_width, wide);
-            tile_us += tile_tokens_us(kv.second.first, kv.second.second, mean_width);
-        }
-        lora_worklists_free(&w);
-        p.mfma_min_used = gemv_us < tile_us ? 0 : LORA_MFMA_MIN_TOKENS_MIXED;
-        rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, p.mfma_min_used, &w);
-        if (rc != LORA_OK) return rc;
-    }
-
-    p.slots.clear();
-    p.generations.clear();
-    auto check = [&](const lora_item_t &it) -> int {
-        if (it.slot >= c.n_slots) return LORA_E_INVAL;
-        const Slot &s = c.slots[it.slot];
-        if (!s.bound) return LORA_E_STATE;
-        if (s.rank != it.rank) return LORA_E_INVAL;
-        if (p.slots.empty() || p.slots.back() != it.slot) {
-            p.slots.push_back(it.slot);
-        }
-        return LORA_OK;
-    };
-    for (int i = 0; i < w.n_tiles && rc == LORA_OK; ++i) rc = check(w.tiles[i]);
-    for (int i = 0; i < w.n_groups && rc == LORA_OK; ++i) rc = check(w.groups[i]);
-    if (rc != LORA_OK) {
-        lora_worklists_free(&w);
-        return rc;
-    }
-    std::sort(p.slots.begin(), p.slots.end());
-    p.slots.erase(std::unique(p.slots.begin(), p.slots.end()), p.slots.end());
-    for (int32_t s : p.slots) p.generations.push_back(c.slots[s].generation);
-
     // resolve slots: the device copy of an item carries the slot's first storage row, the
     // entry's alpha and the item's first token
     auto stamp = [&](lora_item_t *items, int n) {
@@ -768,13 +751,12 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // the projection).
     // Groups in order of rising rank, whatever the caller's slot numbering (measured on the decode configuration:
     // 10.0 us per layer, 10.5 us with the order reversed).
-    std::vector<int> group_order((size_t)w.n_groups);
+    group_order.resize((size_t)w.n_groups);
     for (int i = 0; i < w.n_groups; ++i) group_order[i] = i;
     std::stable_sort(group_order.begin(), group_order.end(),
                      [&](int x, int y) { return lora::rank_storage(w.groups[x].rank) < lora::rank_storage(w.groups[y].rank); });
     // how many there are (they are written straight to the staged copy further down)
-    int64_t n_gs = 0, n_ge = 0, n_wgs = 0, n_wge = 0;
-    for (int gi = 0; gi < w.n_groups; ++gi) {
+        for (int gi = 0; gi < w.n_groups; ++gi) {
         const int32_t n = w.groups[gi].n_tok, rank = w.groups[gi].rank, batches = (n + lora::GEMV_BATCH - 1) / lora::GEMV_BATCH;
         n_gs += (int64_t)batches * (lora::rank_storage(rank) / lora::GEMV_SHRINK_ROWS);
         n_ge += (int64_t)batches * (lora::GEMV_SUPER_COLS / lora::gemv_expand_width(rank));
@@ -782,10 +764,9 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         n_wge += (int64_t)((n + lora::GEMV_WIDE_TOKENS - 1) / lora::GEMV_WIDE_TOKENS) * (lora::GEMV_SUPER_COLS / lora::gemv_wide_width(rank));
     }
     // the same work as wide items (lora_apply's own plans serve one projection: none where that would not take them)
-    if (c.dtype != LORA_BF16 || c.small_scratch || (p.internal && n_wgs < GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) n_wgs = n_wge = 0;
+    if (c.dtype != LORA_BF16 || c.small_scratch || (internal && n_wgs < GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) n_wgs = n_wge = 0;
     stamp(w.tiles, w.n_tiles);
     // the units of a short tile shrink
-    std::vector<lora::DevItem> direct;
     if (w.n_tiles > 0) {
         int64_t n = 0;
         auto blocks = [](int32_t v, int32_t by) { return (v + by - 1) / by; };
@@ -805,7 +786,6 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         }
     }
     // the panels of a long tile shrink: neighbouring tiles of a slot put together, cut into equal parts of at most lora::PANEL_ROWS rows
-    std::vector<lora::DevItem> panels;
     if (c.dtype == LORA_BF16) {
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
         for (int i = 0; i < w.n_tiles;) {
@@ -843,7 +823,6 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         for (int i = 0; i < w.n_tiles; ++i) p.tile_rows += LORA_TILE_TOKENS + (lora::rank_storage(dev_tiles[i].rank) + 15) / 16 * 16;
     }
     // the tile shrink's run tables
-    ShrinkRuns shrink_runs[SHRINK_VARIANTS];
     {
         int32_t quanta = INT32_MAX;
         for (const auto &pr : c.proj) quanta = std::min(quanta, (pr.h_in + lora::SHRINK_STAGE_K - 1) / lora::SHRINK_STAGE_K);
@@ -852,8 +831,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         const lora::DevItem *dev_tiles = reinterpret_cast<const lora::DevItem *>(w.tiles);  // stamped above
         int32_t widest = 0;
         for (const auto &pr : c.proj) widest = std::max(widest, pr.h_in);
-        for (int v = 0; v < SHRINK_VARIANTS && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
-            if (p.internal && (v > 0 || direct_shrink((int32_t)direct.size(), widest) > 0)) break;  // (lora_apply's own plans serve one projection)
+        for (int v = 0; v < SHRINK_VARIANTS && tables && w.n_tiles > 0 && c.vpart_rows > 0; ++v) {
+            if (internal && (v > 0 || direct_shrink((int32_t)direct.size(), widest) > 0)) break;  // (lora_apply's own plans serve one projection)
             if (v >= SHRINK_VARIANT_BATCH && c.small_scratch) break;
             if (v == SHRINK_VARIANT_SMALL && T > LORA_STATIC_MAX_TOKENS) continue;  // lora_apply_plan_static refuses such a batch
             const int n = v >= SHRINK_VARIANT_SMALL ? 1 : v + 1;
@@ -874,10 +853,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.off_gs = p.off_tiles + align_up(sizeof(lora_item_t) * (size_t)w.n_tiles);
     p.off_ge = p.off_gs + align_up(sizeof(lora::GemvItem) * (size_t)n_gs);
     // the rows of lora_linear_plan (bf16 caches): tok_list, then the tokens that name no adapter
-    std::vector<int32_t> lin_tok;
-    std::vector<lora::LinearRows> lin_rows;
-    std::vector<lora::LinearSeg> lin_segs;
-    if (c.dtype == LORA_BF16 && !p.internal) {
+    if (c.dtype == LORA_BF16 && !internal) {
         std::vector<uint8_t> named((size_t)T, 0);
         lin_tok.assign(w.tok_list, w.tok_list + w.n_tok_list);
         for (int32_t t : lin_tok) named[t] = 1;
@@ -922,44 +898,18 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         p.off_sums[v] = bytes;
         bytes += align_up(sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
     }
-    if (bytes + align_up(sizeof(lora::DevItem) * panels.size()) > c.plan_cap) panels.clear();  // (the plan does without)
+    if (bytes + align_up(sizeof(lora::DevItem) * panels.size()) > room) panels.clear();  // (the plan does without)
     p.off_panels = bytes;
     p.n_panels = (int32_t)panels.size();
-    bytes += align_up(sizeof(lora::DevItem) * panels.size());
-    if (bytes > c.plan_cap) {
-        lora_worklists_free(&w);
-        return LORA_E_NOMEM;
-    }
-    // A captured upload would re-read the staged copy on every replay; plans are made outside of captures.
-    if (!c.host_only && is_capturing(st)) {
-        lora_worklists_free(&w);
-        return LORA_E_STATE;
-    }
-    // the staged copy may still be the source of an earlier upload; the device copy may still be read
-    // by earlier applies
-    if (p.upload_pending) {
-        const hipError_t e = hipEventSynchronize(p.ev_upload);
-        if (e != hipSuccess) {
-            lora_worklists_free(&w);
-            g_last_hip = (int)e;
-            return LORA_E_HIP;
-        }
-        p.upload_pending = false;
-    }
-    if (!c.host_only && p.lists == p.pinned_dev && p.last_use >= 0) {  // an earlier apply may still be reading it there
-        const hipError_t e = hipEventSynchronize(c.fences[p.last_use].ev);
-        if (e != hipSuccess) {
-            lora_worklists_free(&w);
-            g_last_hip = (int)e;
-            return LORA_E_HIP;
-        }
-        hold_fence(c, p.last_use, -1);
-    }
-    std::memcpy(p.pinned, w.tok_list, sizeof(int32_t) * (size_t)w.n_tok_list);
-    std::memcpy(p.pinned + p.off_tiles, w.tiles, sizeof(lora_item_t) * (size_t)w.n_tiles);
+    return bytes + align_up(sizeof(lora::DevItem) * panels.size());
+}
+void ListBuild::write(const lora_cache &c, const PlanLists &p, char *to) const
+{
+    std::memcpy(to, w.tok_list, sizeof(int32_t) * (size_t)w.n_tok_list);
+    std::memcpy(to + p.off_tiles, w.tiles, sizeof(lora_item_t) * (size_t)w.n_tiles);
     {
-        lora::GemvItem *gs = reinterpret_cast<lora::GemvItem *>(p.pinned + p.off_gs), *ge = reinterpret_cast<lora::GemvItem *>(p.pinned + p.off_ge);
-        lora::GemvWideItem *wgs = reinterpret_cast<lora::GemvWideItem *>(p.pinned + p.off_wgs), *wge = reinterpret_cast<lora::GemvWideItem *>(p.pinned + p.off_wge);
+        lora::GemvItem *gs = reinterpret_cast<lora::GemvItem *>(to + p.off_gs), *ge = reinterpret_cast<lora::GemvItem *>(to + p.off_ge);
+        lora::GemvWideItem *wgs = reinterpret_cast<lora::GemvWideItem *>(to + p.off_wgs), *wge = reinterpret_cast<lora::GemvWideItem *>(to + p.off_wge);
         for (int gi = 0; gi < w.n_groups; ++gi) {
             const lora_item_t &gr = w.groups[group_order[gi]];
             const int32_t *toks = w.tok_list + gr.tok_off, row = c.slot_row[gr.slot];
@@ -997,24 +947,126 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
             }
         }
     }
-    lora_worklists_free(&w);
-    if (!lin_tok.empty()) std::memcpy(p.pinned + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
-    if (!lin_rows.empty()) std::memcpy(p.pinned + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
-    if (!direct.empty()) std::memcpy(p.pinned + p.off_direct, direct.data(), sizeof(lora::DevItem) * direct.size());
-    if (!panels.empty()) std::memcpy(p.pinned + p.off_panels, panels.data(), sizeof(lora::DevItem) * panels.size());
-    if (!lin_segs.empty()) std::memcpy(p.pinned + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
+    if (!lin_tok.empty()) std::memcpy(to + p.off_lin_tok, lin_tok.data(), sizeof(int32_t) * lin_tok.size());
+    if (!lin_rows.empty()) std::memcpy(to + p.off_lin_rows, lin_rows.data(), sizeof(lora::LinearRows) * lin_rows.size());
+    if (!direct.empty()) std::memcpy(to + p.off_direct, direct.data(), sizeof(lora::DevItem) * direct.size());
+    if (!panels.empty()) std::memcpy(to + p.off_panels, panels.data(), sizeof(lora::DevItem) * panels.size());
+    if (!lin_segs.empty()) std::memcpy(to + p.off_lin_segs, lin_segs.data(), sizeof(lora::LinearSeg) * lin_segs.size());
     for (int v = 0; v < SHRINK_VARIANTS; ++v) {
-        if (!shrink_runs[v].cuts.empty()) std::memcpy(p.pinned + p.off_cuts[v], shrink_runs[v].cuts.data(), sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
-        if (!shrink_runs[v].sums.empty()) std::memcpy(p.pinned + p.off_sums[v], shrink_runs[v].sums.data(), sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
+        if (!shrink_runs[v].cuts.empty()) std::memcpy(to + p.off_cuts[v], shrink_runs[v].cuts.data(), sizeof(lora::ShrinkCut) * shrink_runs[v].cuts.size());
+        if (!shrink_runs[v].sums.empty()) std::memcpy(to + p.off_sums[v], shrink_runs[v].sums.data(), sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
     }
+}
+
+// Validates a batch against the slot table and writes its work lists into plan `p`
+// (pinned copy + upload on `st`).
+int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
+               const int32_t *seg_rank, int32_t n_seg, hipStream_t st)
+{
+    if (T < 0 || T > c.max_tokens || n_seg < 0 || n_seg > c.max_segments) return LORA_E_INVAL;
+    ListBuild lists;
+    lora_worklists_t &w = lists.w;
+    int rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, c.mfma_min, &w);
+    if (rc != LORA_OK) return rc;
+    p.mfma_min_used = c.mfma_min;
+    // With the threshold left to the library: the tile path costs two launches more per apply, which a batch with few tile tokens does
+    // not earn back.  So: what its tokens cost either way; below, everything stays GEMV; else the batch pays for the tile launches
+    // anyway and smaller pools of tokens become tiles too.
+    p.may_tile = p.has_tiled = false;
+    if (c.mfma_min_auto && w.n_tiles > 0) {
+        double mean_width = 0;
+        for (const auto &pr : c.proj) mean_width += (double)pr.h_in + pr.h_out;
+        mean_width /= (double)c.proj.size();
+        std::unordered_map<int32_t, std::pair<int32_t, int32_t>> of_slot;  // slot -> (tile tokens, rank)
+        for (int i = 0; i < w.n_tiles; ++i) {
+            auto &e = of_slot[w.tiles[i].slot];
+            e.first += w.tiles[i].n_tok;
+            e.second = w.tiles[i].rank;
+        }
+        const bool other = w.n_groups > 0;
+        double gemv_us = other ? 0.0 : GEMV_FIXED_US, tile_us = TILE_FIXED_US + (other ? TILE_BESIDE_GEMV_US : 0.0);
+        int64_t n_wide = 0;
+        for (int i = 0; i < w.n_groups; ++i) n_wide += wide_shrink_items(w.groups[i].n_tok, w.groups[i].rank);
+        for (const auto &kv : of_slot) n_wide += wide_shrink_items(kv.second.first, kv.second.second);
+        const bool wide = c.dtype == LORA_BF16 && !c.small_scratch && n_wide >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP;
+        for (const auto &kv : of_slot) {
+            gemv_us += gemv_tokens_us(kv.second.first, kv.second.second, mean_width, wide);
+            tile_us += tile_tokens_us(kv.second.first, kv.second.second, mean_width);
+        }
+        p.mfma_min_used = gemv_us < tile_us ? 0 : LORA_MFMA_MIN_TOKENS_MIXED;
+        if (p.mfma_min_used == 0 && c.dtype == LORA_BF16 && !p.internal && !c.small_scratch) {
+            p.may_tile = true;
+            p.rest_groups = w.n_groups, p.rest_wgs = p.tile_tok = 0, p.tile_segs = (int32_t)of_slot.size();
+            p.tile_cost = p.gemv_cost[0] = p.gemv_cost[1] = p.rest_cost[0] = p.rest_cost[1] = PathCost{};
+            for (int i = 0; i < w.n_tiles; ++i) p.tile_cost.add_tile(w.tiles[i].n_tok, w.tiles[i].rank);
+            for (int i = 0; i < w.n_groups; ++i) {
+                p.rest_wgs += (int32_t)wide_shrink_items(w.groups[i].n_tok, w.groups[i].rank);
+                for (int wide_items = 0; wide_items < 2; ++wide_items) p.rest_cost[wide_items].add_gemv(w.groups[i].n_tok, w.groups[i].rank, wide_items);
+            }
+            for (int wide_items = 0; wide_items < 2; ++wide_items) {
+                p.gemv_cost[wide_items] = p.rest_cost[wide_items];
+                for (const auto &kv : of_slot) p.gemv_cost[wide_items].add_gemv(kv.second.first, kv.second.second, wide_items);
+            }
+            for (const auto &kv : of_slot) p.tile_tok += kv.second.first;
+            p.segs[0].assign(seg_offsets, seg_offsets + n_seg + 1);
+            p.segs[1].assign(seg_slot, seg_slot + n_seg);
+            p.segs[2].assign(seg_rank, seg_rank + n_seg);
+        }
+        lora_worklists_free(&w);
+        rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, p.mfma_min_used, &w);
+        if (rc != LORA_OK) return rc;
+    }
+
+    p.slots.clear();
+    p.generations.clear();
+    auto check = [&](const lora_item_t &it) -> int {
+        if (it.slot >= c.n_slots) return LORA_E_INVAL;
+        const Slot &s = c.slots[it.slot];
+        if (!s.bound) return LORA_E_STATE;
+        if (s.rank != it.rank) return LORA_E_INVAL;
+        if (p.slots.empty() || p.slots.back() != it.slot) {
+            p.slots.push_back(it.slot);
+        }
+        return LORA_OK;
+    };
+    for (int i = 0; i < w.n_tiles && rc == LORA_OK; ++i) rc = check(w.tiles[i]);
+    for (int i = 0; i < w.n_groups && rc == LORA_OK; ++i) rc = check(w.groups[i]);
+    if (rc != LORA_OK) return rc;
+    std::sort(p.slots.begin(), p.slots.end());
+    p.slots.erase(std::unique(p.slots.begin(), p.slots.end()), p.slots.end());
+    for (int32_t s : p.slots) p.generations.push_back(c.slots[s].generation);
+
+    const size_t bytes = lists.size(c, p, p.internal, true, T, c.plan_cap);
+    if (bytes > c.plan_cap) return LORA_E_NOMEM;
+    // A captured upload would re-read the staged copy on every replay; plans are made outside of captures.
+    if (!c.host_only && is_capturing(st)) return LORA_E_STATE;
+    // the staged copy may still be the source of an earlier upload; the device copy may still be read
+    // by earlier applies
+    if (p.upload_pending) {
+        const hipError_t e = hipEventSynchronize(p.ev_upload);
+        if (e != hipSuccess) {
+            g_last_hip = (int)e;
+            return LORA_E_HIP;
+        }
+        p.upload_pending = false;
+    }
+    if (!c.host_only && p.lists == p.pinned_dev && p.last_use >= 0) {  // an earlier apply may still be reading it there
+        const hipError_t e = hipEventSynchronize(c.fences[p.last_use].ev);
+        if (e != hipSuccess) {
+            g_last_hip = (int)e;
+            return LORA_E_HIP;
+        }
+        hold_fence(c, p.last_use, -1);
+    }
+    lists.write(c, p, p.pinned);
     p.bytes = bytes;
     p.build_seq = ++c.plan_builds;
     p.lists = p.dev;
-    int64_t waves = 4 * n_gs;  // of a launch for the widest projection
+    int64_t waves = 4 * (int64_t)p.n_gs;  // of a launch for the widest projection
     {
         int32_t supers = 0;
         for (const auto &pr : c.proj) supers = std::max(supers, (pr.h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS);
-        waves += n_ge * supers;
+        waves += (int64_t)p.n_ge * supers;
     }
     if (!c.host_only && p.internal && c.fencing && p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES) {
         p.lists = p.pinned_dev;
@@ -1027,6 +1079,29 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         p.upload_pending = true;
     }
     return LORA_OK;
+}
+
+// The lists with tiles of a plan whose own have none, made when a launch first asks for them: behind the plan's own lists, uploaded on `st`.  Not while capturing (the staged copy would
+// be read again by every replay): a captured call takes them if they are there.
+bool tiled_lists(lora_cache &c, lora_plan &p, hipStream_t st)
+{
+    if (p.has_tiled) return true;
+    if (is_capturing(st)) return false;
+    p.may_tile = false;
+    ListBuild lists;
+    const int32_t n_seg = (int32_t)p.segs[1].size();
+    if (lora_index(p.T, p.segs[0].data(), p.segs[1].data(), p.segs[2].data(), n_seg, LORA_MFMA_MIN_TOKENS_MIXED, &lists.w) != LORA_OK) return false;
+    const size_t bytes = lists.size(c, p.tiled, false, false, p.T, c.plan_cap - p.bytes);
+    if (bytes > c.plan_cap - p.bytes || p.tiled.n_panels == 0) return false;
+    lists.write(c, p.tiled, p.pinned + p.bytes);
+    // (behind the plan's own upload, so behind whatever still read the plan's memory before it)
+    if (p.upload_pending && hipStreamWaitEvent(st, p.ev_upload, 0) != hipSuccess) return false;
+    if (lora::launch_upload(p.dev + p.bytes, p.pinned_dev + p.bytes, bytes, st, p.ev_upload) != hipSuccess) return false;
+    p.upload_pending = true;
+    p.tiled.build_seq = ++c.plan_builds;
+    p.tiled.lists = p.dev + p.bytes;
+    p.has_tiled = p.may_tile = true;
+    return true;
 }
 
 // Makes `st` wait for every apply enqueued so far that named the slot.  The fence of the call that
@@ -1730,7 +1805,7 @@ static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS 
 
 // Block and unit numbers of a batch's GEMV launch for n projections, h_out[i] wide, with a plan's items or its wide items;
 // shared by the launch and lora_plan_dump.  `supers` comes in zeroed; first[i]: number of projection i's first super-chunk.
-static int gemv_batch_map(const lora_plan_t *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 4],
+static int gemv_batch_map(const PlanLists *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 4],
                           uint32_t (&first)[lora::GEMV_BATCH_MAX_PROJS])
 {
     m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
@@ -1763,7 +1838,7 @@ static Scratch pool_scratch(lora_cache_t *c)
 
 // How many projections, and super-chunks of projections, a batch with plan p may have: the scratch's sets, the partial sums of the
 // smallest run table of the tile shrink, and the ranges of the GEMV launch's unit arithmetic.
-static void batch_limits(const lora_plan_t *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
+static void batch_limits(const PlanLists *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
 {
     int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
     if (p->n_tiles > 0) {
@@ -1837,9 +1912,9 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     // the blocks of the shrink by panels, for groups of 1 to 4 projections, as the kernel maps them
     const lora::DevItem *panels = reinterpret_cast<const lora::DevItem *>(buf + p->off_panels);
     for (int gn = 1; gn <= lora::GROUP_MAX_PROJS; ++gn)
-        for (int b = 0; b < 8 * lora::panel_blocks(p->panel_classes, gn) && p->n_panels > 0; ++b) {
-            int panel, first, n;
-            if (!lora::panel_of_block(p->panel_classes, gn, b & 7, b >> 3, p->n_panels, panel, first, n)) continue;
+        for (int b = 0; b < lora::panel_blocks(p->panel_classes, gn) && p->n_panels > 0; ++b) {
+            int slice, panel, first, n;
+            if (!lora::panel_of_block(p->panel_classes, gn, 1, b, slice, panel, first, n)) continue;
             const int32_t off = nt;
             tile_tokens(panels[panel], tok_list);
             put_unit(LORA_UNIT_PANEL_SHRINK, off, panels[panel].n_tok, panels[panel].row, panels[panel].rank, first, first + n, gn, panels[panel].alpha);
@@ -2013,7 +2088,7 @@ constexpr int FUSED_GEMV_MAX_BATCH_ITEMS = 1 << 24;
 // The run table of a tile-shrink launch for a batch of n projections whose partial sums go to a scratch of `vpart_rows`
 // rows: the table of a group's size, or, for more projections, the largest that keeps the launch within
 // SHRINK_BATCH_BLOCKS blocks.
-static int shrink_variant(const lora_plan_t *p, int n, int64_t vpart_rows, bool small)
+static int shrink_variant(const PlanLists *p, int n, int64_t vpart_rows, bool small)
 {
     if (small) return SHRINK_VARIANT_SMALL;
     if (n <= lora::GROUP_MAX_PROJS) return n - 1;
@@ -2023,14 +2098,14 @@ static int shrink_variant(const lora_plan_t *p, int n, int64_t vpart_rows, bool 
     return SHRINK_VARIANT_BATCH + 1;
 }
 // The tile kernels' arguments but for the projections; n: how many there are, sum_h_in: the sum of their input widths.
-static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_t sum_h_in, const Scratch &sc, float scale, lora::TileBatch &tb)
+static int tile_setup(const lora_cache_t *c, const PlanLists *p, int n, int64_t sum_h_in, const Scratch &sc, float scale, lora::TileBatch &tb)
 {
     if (n < 1 || n > lora::BATCH_MAX_PROJS || n > sc.n_sets) return LORA_E_INVAL;
     const int v = shrink_variant(p, n, sc.vpart_rows, sc.small);
     tb.n = n;
     tb.n_runs = p->shrink_runs[v];
     tb.n_direct = direct_shrink(p->n_direct, sum_h_in);
-    if (p->n_tiles > 0 && tb.n_runs == 0 && tb.n_direct == 0) return LORA_E_STATE;  // the plan carries no such table
+    if (p->n_tiles > 0 && tb.n_runs == 0 && tb.n_direct == 0 && (p->n_panels == 0 || sc.small)) return LORA_E_STATE;  // the plan carries no such table
     tb.quanta = p->shrink_quanta;
     tb.n_tiles = p->n_tiles;
     tb.v_stride = c->v_stride;
@@ -2051,12 +2126,12 @@ static int tile_setup(const lora_cache_t *c, const lora_plan_t *p, int n, int64_
     tb.part_set = (uint64_t)rows_per_proj * c->v_stride;
     return LORA_OK;
 }
-// The shrink of a launch by panels, where that is the shorter way, and into how many k slices: estimates in microseconds, fitted to launches of one to four projections and lists of four
-// layers, 900 to 22000 tokens in prompts of 60 to 2048 at ranks 16, 128 and 8 to 128, 2048 and 4096 wide (shrink and reduce of 154 of them by the run tables take 1.17 times
-// what they take by the way chosen here in the geometric mean; the best number of slices would make it 1.185).
-// By panels: a block takes 3 us and 2.1 ns per stage and row of it; what the blocks take in comes at 8.3 TB/s, x alone at 6.8; slices have to be added up.
-// By the run table: 11 us with the reduce, 64 + rank rows per tile and stage at 9.8 TB/s.
-static void choose_panels(const lora_cache_t *c, const lora_plan_t *p, const Scratch &sc, lora::TileBatch &tb)
+// The shrink of a launch by panels, where that is the shorter way, and into how many k slices: estimates in microseconds, fitted to launches of one to four projections, of a projection of
+// four layers and of all seven of two, 300 to 7600 tokens in prompts of 16 to 2048 at ranks 16, 128 and 8 to 128, 2048 to 5120 wide (shrink and reduce of 173 of them by the run tables take 1.16 times
+// what they take by the way chosen here in the geometric mean; the best number of slices would make it 1.18).
+// By panels: a block takes 1.7 us and 2.4 ns per stage and row of it; what the blocks take in comes at 8.4 TB/s, x alone at 5.1; slices have to be added up.
+// By the run table: 11 us with the reduce, 64 + rank rows per tile and stage at 10.4 TB/s.
+static void choose_panels(const lora_cache_t *c, const PlanLists *p, const Scratch &sc, lora::TileBatch &tb)
 {
     if (tb.n_direct > 0 || p->n_panels <= 0 || sc.small) return;
     struct Kind {  // groups alike
@@ -2089,14 +2164,14 @@ static void choose_panels(const lora_cache_t *c, const lora_plan_t *p, const Scr
         run_bytes += (double)q.many * q.gn * q.n_k * 128 * p->tile_rows;
     }
     int best = 0;
-    double best_us = 11 + std::max(run_bytes / 9.8e6, x_bytes / 5.8e6);
+    double best_us = tb.n_runs > 0 ? 10.8 + std::max(run_bytes / 10.4e6, x_bytes / 5.2e6) : std::numeric_limits<double>::infinity();
     for (int S : {1, 2, 3, 4, 6, 8, 12, 16}) {
         if (S > 1 && (least_k < 4 * S || (int64_t)S * tb.n * p->n_tile_tok > sc.vpart_rows)) break;
-        const double n = blocks * S, avg = 3 + 0.0021 * stage_rows / n, all = n * avg / c->n_cu;
-        double us = std::max({3 + 0.0021 * longest / S, 3 + stage_rows * 128 / 8.3e6, 3 + x_bytes / 6.8e6});
-        if (n > 2 * c->n_cu) us = std::max(us, all + 0.8 * avg);
+        const double n = blocks * S, avg = 1.7 + 0.0024 * stage_rows / n, all = n * avg / c->n_cu;
+        double us = std::max({1.7 + 0.0024 * longest / S, 1.7 + stage_rows * 128 / 8.4e6, 1.7 + x_bytes / 5.1e6});
+        if (n > 2 * c->n_cu) us = std::max(us, all + 1.4 * avg);
         else if (n > c->n_cu) us = std::max(us, 1.63 * avg);
-        us += 1.5 + (S > 1 ? 4 + S * tb.n * p->panel_sum_bytes / 7e6 : 0);
+        us += 0.9 + (S > 1 ? 4.1 + S * tb.n * p->panel_sum_bytes / 6.7e6 : 0);
         if (us < best_us) best_us = us, best = S;
     }
     if (best == 0) return;
@@ -2117,7 +2192,7 @@ static lora::BatchProj batch_proj(const lora_cache_t *c, const lora_apply_desc_t
 // same graph has written the same words in between (its number differs): that holds for every launch after the first of a
 // capture that works on the same plan with at least as many projections.  Otherwise the words are cleared first, by a
 // small kernel that becomes part of the graph.
-static int clear_words_for_capture(lora_cache_t *c, lora_plan_t *p, int n, hipStream_t st, const Scratch &sc)
+static int clear_words_for_capture(lora_cache_t *c, const PlanLists *p, int n, hipStream_t st, const Scratch &sc)
 {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     unsigned long long cap = 0;
@@ -2146,7 +2221,7 @@ static bool one_gemv_launch(const lora_cache_t *c, const Scratch &sc, int64_t it
 // The GEMV part of a group of n projections that read the same x: one launch with the in-kernel
 // hand-over when the part is small (the launch in between then costs more than the hand-over), else a
 // shrink and an expand launch.  y32[i], when set, receives projection i's update as fp32 instead of y.
-static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *a, float *const *y32, int n, float scale,
+static int enqueue_gemv(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *a, float *const *y32, int n, float scale,
                         hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -2188,7 +2263,7 @@ static int enqueue_gemv(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *
 }
 
 // wide items for a GEMV launch of n projections in n_groups groups?
-static bool gemv_wide(const lora_cache_t *c, const lora_plan_t *p, const lora::BatchProj *projs, int n, int n_groups)
+static bool gemv_wide(const lora_cache_t *c, const PlanLists *p, const lora::BatchProj *projs, int n, int n_groups)
 {
     if (c->dtype != LORA_BF16 || (int64_t)p->n_wgs * n < (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) return false;
     int64_t supers = 0;  // (a group may be beyond the batch kernels' unit arithmetic, a batch is cut to it)
@@ -2197,7 +2272,7 @@ static bool gemv_wide(const lora_cache_t *c, const lora_plan_t *p, const lora::B
 }
 
 // The same for a batch of several groups.
-static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::BatchProj *projs, float *y32, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
+static int enqueue_gemv_batch(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *projs, float *y32, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
                               const lora::KernelTimer *tm, hipEvent_t done)
 {
     if (p->n_gs <= 0) return LORA_OK;
@@ -2225,12 +2300,33 @@ static int enqueue_gemv_batch(lora_cache_t *c, lora_plan_t *p, const lora::Batch
     return LORA_OK;
 }
 
+// The lists a launch for n projections in n_groups groups works through, sum_width wide together (h_in + h_out)
+static const PlanLists *pick_lists(lora_cache_t *c, lora_plan_t *p, int n, int n_groups, double sum_width, hipStream_t st)
+{
+    if (!p->may_tile) return p;
+    auto wide = [&](int64_t n_wgs) { return n_wgs * n >= (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP) ? 1 : 0; };
+    const double gemv = GEMV_FIXED_US + p->gemv_cost[wide(p->n_wgs)].us(n, sum_width);
+    const double tiled = TILE_FIXED_US + (p->rest_groups > 0 ? TILE_BESIDE_GEMV_US : 0.0) + p->rest_cost[wide(p->rest_wgs)].us(n, sum_width) + p->tile_cost.us(n, sum_width);
+    return tiled < 0.92 * gemv && tiled + TILED_LISTS_US < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
+}
+// The same for the base product, which takes the tiles' term along: no expand launch, but a segment of rows costs its blocks 1.3 us for its Bp
+static const PlanLists *pick_linear_lists(lora_cache_t *c, lora_plan_t *p, double width, hipStream_t st)
+{
+    if (!p->may_tile) return p;
+    const double gemv = GEMV_FIXED_US + LINEAR_TERM_US + p->gemv_cost[p->n_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width);
+    const double rest = p->rest_groups > 0 ? GEMV_FIXED_US + p->rest_cost[p->rest_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width) : 0.0;
+    const double segments = std::max(1.0, p->tile_segs * std::min(1.0, 256.0 / p->tile_tok));  // of a block
+    const double tiled = rest + LINEAR_SHRINK_US + 0.4 * p->tile_cost.us(1, width) + 1.3 * segments;
+    const double least = LINEAR_MIN_GAIN_US + LISTS_COST_US / (double)(c->n_layers * c->proj.size());
+    return tiled + least < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
+}
+
 // Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of
 // them.  Entries that read the same x (a group, at most GROUP_MAX_PROJS) are neighbours; group_n[i] is the size of the group that
 // starts at entry i.  The tile shrink runs first, for all entries (x of a group is then fetched from memory once), each
 // with its own copy of the intermediate buffers.
 // `fence` (null: none) is to stand for the batch's end on `st`.
-static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t *descs, const uint8_t *group_n, int n, float scale, hipStream_t st,
+static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, const lora_apply_desc_t *descs, const uint8_t *group_n, int n, float scale, hipStream_t st,
                          const Scratch &sc, hipEvent_t fence)
 {
     // the work lists may have been uploaded on another stream
@@ -2259,8 +2355,8 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         sum_h_in += c->proj[descs[i].proj].h_in;
         sum_h_out += c->proj[descs[i].proj].h_out;
     }
-    if (p->n_tiles > 0)
-        if (const int rc_s = tile_setup(c, p, n, sum_h_in, sc, scale, tb)) return rc_s;
+    if (q->n_tiles > 0)
+        if (const int rc_s = tile_setup(c, q, n, sum_h_in, sc, scale, tb)) return rc_s;
     // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
     int n_groups = 0;
     uint8_t first[lora::GEMV_BATCH_MAX_PROJS];
@@ -2271,16 +2367,16 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         const int size = group_n[first[g]], at = i;
         for (int k = 0; k < size; ++k, ++i) {
             projs[i] = batch_proj(c, descs[first[g] + k]);
-            if (p->n_tiles > 0) tb.p[i] = projs[i], tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
+            if (q->n_tiles > 0) tb.p[i] = projs[i], tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
         }
     }
-    if (p->n_tiles > 0) choose_panels(c, p, sc, tb);
+    if (q->n_tiles > 0) choose_panels(c, q, sc, tb);
     // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
     // scratch: when a batch has enough of both, the GEMV launch goes to the cache's side stream, forked off here and
     // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
     // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
-    const double tile_bytes = (double)p->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
-    const bool fork = p->n_tiles > 0 && p->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
+    const double tile_bytes = (double)q->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
+    const bool fork = q->n_tiles > 0 && q->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
     hipStream_t gemv_st = st;
     if (fork) {
         HIP_TRY(hipEventRecord(c->ev_fork, st));
@@ -2288,7 +2384,7 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         gemv_st = c->side_stream;
     }
     // everything that reads x
-    if (p->n_tiles > 0) {
+    if (q->n_tiles > 0) {
         HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
     // joined behind the tile expands, whatever happens in between: a captured fork must not stay open
@@ -2306,15 +2402,15 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_
         ~Join() { (void)now(); }
     } join{c, st, fork, false};
     // the fence rides on the group's last kernel, where that is the last thing on `st`
-    const bool ride = fence && !fork && tm == nullptr && (p->n_tiles > 0 || p->n_gs > 0);
+    const bool ride = fence && !fork && tm == nullptr && (q->n_tiles > 0 || q->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
-    const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && p->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups == 1 && !gemv_wide(c, p, projs, n, 1) ? enqueue_gemv(c, p, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
-                                       : enqueue_gemv_batch(c, p, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
+    const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && q->n_tiles == 0 ? fence : nullptr);
+    if (const int rc_g = n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
+                                       : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
     // the updates of base_out
-    if (p->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
+    if (q->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
     for (int i = 0; i < n; ++i) {
         const int64_t seq = ++c->apply_seq;
         ++c->stats.applies;
@@ -2353,7 +2449,7 @@ static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t
     int32_t f;
     if (const int rc = take_fence(c, st, f)) return rc;
     const uint8_t one = 1;
-    if (const int rc = enqueue_batch(c, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
+    if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
     publish_fence(c, p, st, f);
     return LORA_OK;
 }
@@ -2421,7 +2517,8 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     lora::ApplyArgs a;
     a.proj_base = bp.proj_base;
     a.row_bytes = (int64_t)c->row_bytes[proj];
-    a.tok_list = reinterpret_cast<const int32_t *>(p->lists);
+    const PlanLists *const q = pick_linear_lists(c, p, (double)bp.h_in + bp.h_out, st);
+    a.tok_list = reinterpret_cast<const int32_t *>(q->lists);
     a.x = x;
     a.y = y;
     a.v = reinterpret_cast<float *>(c->pool + c->off_v);
@@ -2435,27 +2532,27 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     // (row = token), or, without one, into their zeroed output rows (rounded to the output type on the way).  One after the
     // other: the GEMV launch on the side stream, between a fork off the last base product and a join into the next, waits 10 us at
     // both for 20 us of shrink and reduce beside it (a 13B layer 2034 us, 2015 us this way).
-    const int32_t n_gemv_tok = p->n_tok_list - p->n_tile_tok;
-    if (p->n_tiles > 0) {
+    const int32_t n_gemv_tok = q->n_tok_list - q->n_tile_tok;
+    if (q->n_tiles > 0) {
         lora::TileBatch tb;
-        if (const int rc_s = tile_setup(c, p, 1, a.h_in, pool_scratch(c), scale, tb)) return rc_s;
+        if (const int rc_s = tile_setup(c, q, 1, a.h_in, pool_scratch(c), scale, tb)) return rc_s;
         tb.p[0] = bp;
         tb.group[0] = 1u << 8;
-        choose_panels(c, p, pool_scratch(c), tb);
+        choose_panels(c, q, pool_scratch(c), tb);
         HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
     }
     if (n_gemv_tok > 0) {
         a.y32 = static_cast<float *>(workspace);
-        if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + p->n_tile_tok, n_gemv_tok, a.h_out, st));
+        if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + q->n_tile_tok, n_gemv_tok, a.h_out, st));
         float *const y32 = a.y32;
-        if (const int rc_g = gemv_wide(c, p, &bp, 1, 1) ? enqueue_gemv_batch(c, p, &bp, y32, 1, 1, scale, st, pool_scratch(c), tm, nullptr)
-                                                        : enqueue_gemv(c, p, &bp, &y32, 1, scale, st, pool_scratch(c), tm, nullptr))
+        if (const int rc_g = gemv_wide(c, q, &bp, 1, 1) ? enqueue_gemv_batch(c, q, &bp, y32, 1, 1, scale, st, pool_scratch(c), tm, nullptr)
+                                                        : enqueue_gemv(c, q, &bp, &y32, 1, scale, st, pool_scratch(c), tm, nullptr))
             return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
-    const lora::LinearList list{reinterpret_cast<const int32_t *>(p->lists + p->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(p->lists + p->off_lin_rows),
-                                reinterpret_cast<const lora::LinearSeg *>(p->lists + p->off_lin_segs),
-                                p->T, p->n_lin_rows, p->n_tile_tok, p->n_tok_list};
+    const lora::LinearList list{reinterpret_cast<const int32_t *>(q->lists + q->off_lin_tok), reinterpret_cast<const lora::LinearRows *>(q->lists + q->off_lin_rows),
+                                reinterpret_cast<const lora::LinearSeg *>(q->lists + q->off_lin_segs),
+                                q->T, q->n_lin_rows, q->n_tile_tok, q->n_tok_list};
     // (the partial sums of split tiles go where the tile shrink's partial sums went: that kernel is done)
     HIP_TRY(lora::launch_linear_tiles(a, Wt, list, c->pool + c->off_vpart, c->vpart_bytes, reinterpret_cast<lora::SplitState *>(c->pool + c->off_splits),
                                       N_LINEAR_SPLITS, c->fault_dev, c->n_cu, st, tm, tm || f < 0 ? nullptr : c->fences[f].ev));
@@ -2528,8 +2625,20 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
                 break;
             }
         }
-        const int rc = enqueue_batch(c, p, descs + i, group_n, m, scale, st, scratch, f >= 0 && i + m == n ? c->fences[f].ev : nullptr);
-        if (rc != LORA_OK) return rc;
+        double sum_width = 0;
+        int n_groups = 0;
+        for (int k = 0; k < m; ++k) sum_width += (double)c->proj[descs[i + k].proj].h_in + c->proj[descs[i + k].proj].h_out;
+        for (int k = 0; k < m; k += group_n[k]) ++n_groups;
+        const PlanLists *const q = pick_lists(c, p, m, n_groups, sum_width, st);
+        int32_t most = m, unused;
+        if (q != p) batch_limits(q, scratch, most, unused);
+        for (int at = 0; at < m;) {  // (a batch with tiles holds fewer projections)
+            int k = group_n[at];
+            while (at + k < m && k + group_n[at + k] <= most) k += group_n[at + k];
+            const int rc = enqueue_batch(c, p, q, descs + i + at, group_n + at, k, scale, st, scratch, f >= 0 && i + at + k == n ? c->fences[f].ev : nullptr);
+            if (rc != LORA_OK) return rc;
+            at += k;
+        }
         i += m;
     }
     if (n > 0) publish_fence(c, p, st, f);

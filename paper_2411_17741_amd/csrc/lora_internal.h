@@ -396,29 +396,26 @@ inline __host__ __device__ constexpr int panel_projs(int runs, int rank_blocks) 
 struct PanelClasses {
     int32_t end[3];  // panels before end[c] take at most c + 1 projections per block
 };
-// of the panels [lo, hi) those with number xcd modulo 8
-inline __host__ __device__ int panel_count(int lo, int hi, int xcd) { return (hi + 7 - xcd) / 8 - (lo + 7 - xcd) / 8; }
-// blocks of an XCD for one slice of a group of gn projections: the most that any XCD has
+// blocks of one slice of a group of gn projections
 inline __host__ __device__ int panel_blocks(const PanelClasses &c, int gn)
 {
-    int most = 0;
-    for (int xcd = 0; xcd < 8; ++xcd) {
-        const int n = panel_count(0, c.end[0], xcd) * gn + panel_count(c.end[0], c.end[1], xcd) * ((gn + 1) / 2) + panel_count(c.end[1], c.end[2], xcd) * ((gn + 2) / 3);
-        most = n > most ? n : most;
-    }
-    return most;
+    return c.end[0] * gn + (c.end[1] - c.end[0]) * ((gn + 1) / 2) + (c.end[2] - c.end[1]) * ((gn + 2) / 3);
 }
-// block i of such a slice on XCD xcd -> panel and its projections [first, first + n) of the group; false: nothing to do
-inline __host__ __device__ bool panel_of_block(const PanelClasses &c, int gn, int xcd, int i, int n_panels, int &panel, int &first, int &n)
+// Block i of a group of gn projections in `slices` slices -> slice, panel and its projections [first, first + n) of the group; false: past the end.  Class by class; within a class the
+// (slice, panel) pairs are dealt out to the XCDs one by one (block b runs on XCD b % 8), and the blocks of a pair, if there are several, run on one XCD side by side: eight pairs
+// take turns (fewer at a class's end).
+inline __host__ __device__ bool panel_of_block(const PanelClasses &c, int gn, int slices, int i, int &slice, int &panel, int &first, int &n)
 {
     for (int k = 0, lo = 0; k < 3; lo = c.end[k], ++k) {
-        const int per = (gn + k) / (k + 1), blocks = panel_count(lo, c.end[k], xcd) * per;
+        const int count = c.end[k] - lo, per = (gn + k) / (k + 1), blocks = count * slices * per;
         if (i < blocks) {
-            const int nth = i / per;
-            panel = (lo + 7 - xcd) / 8 * 8 + xcd + 8 * nth;
-            first = (i - nth * per) * (k + 1);
+            const int row = i / (8 * per), at = i - row * 8 * per, left = count * slices - 8 * row, width = left < 8 ? left : 8;
+            const int turn = at / width, pair = 8 * row + at - turn * width;
+            slice = pair / count;
+            panel = lo + pair - slice * count;
+            first = turn * (k + 1);
             n = gn - first < k + 1 ? gn - first : k + 1;
-            return panel < n_panels;
+            return true;
         }
         i -= blocks;
     }
@@ -455,8 +452,7 @@ struct TileBatch : TileBatchArgs<BATCH_MAX_PROJS> {  // as a launcher takes it
     PanelClasses classes;
     uint8_t slices[BATCH_MAX_PROJS];  // k slices of projection i's panels (of all projections of a group)
 };
-// blocks of the panels' launch: per group (in the order of the projections) where its blocks end, of one XCD, and first projection | projections << 8 | slices << 16 |
-// the XCD that its first panel falls to << 24; per projection its slices
+// blocks of the panels' launch: per group (in the order of the projections) where its blocks end, and first projection | projections << 8 | slices << 16; per projection its slices
 template <int N> struct PanelShape {
     int32_t end[N];
     uint32_t group[N];

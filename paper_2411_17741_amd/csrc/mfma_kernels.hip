@@ -605,22 +605,17 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
 }
 
 template <int N>
-__global__ __launch_bounds__(512) void mfma_panel_kernel(const DevItem *panels, int n_panels, PanelClasses cls, PanelShape<N> sh, TileBatchArgs<N> tb)
+__global__ __launch_bounds__(512) void mfma_panel_kernel(const DevItem *panels, PanelClasses cls, PanelShape<N> sh, TileBatchArgs<N> tb)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
-    // XCD j = blockIdx % 8 works on every eighth panel of every group of projections, group by group (the groups of long rows first) and slice by slice, the blocks of a panel side by side
-    const int xcd = (int)blockIdx.x & 7, local = (int)blockIdx.x >> 3;
-    int gi = 0;  // the first group whose blocks end behind this one
+    int gi = 0;  // the first group whose blocks end behind this one (the groups of long rows come first)
 #pragma unroll
     for (int step = N / 2; step > 0; step >>= 1)
-        if (local >= sh.end[gi + step - 1]) gi += step;
+        if ((int)blockIdx.x >= sh.end[gi + step - 1]) gi += step;
     const uint32_t grp = sh.group[gi];
-    const int g0 = (int)(grp & 0xffu), gn = (int)(grp >> 8 & 0xffu), slices = (int)(grp >> 16 & 0xffu);
-    const int begin = gi ? sh.end[gi - 1] : 0, in_group = local - begin, per_slice = (sh.end[gi] - begin) / slices;
-    const int slice = in_group / per_slice;
-    const int turn = (int)(grp >> 24) + slice * n_panels;  // the panels are dealt out on and on, not from XCD 0 again for every slice
-    int panel, first, n;
-    if (!panel_of_block(cls, gn, (xcd - turn) & 7, in_group - slice * per_slice, n_panels, panel, first, n)) return;  // padding
+    const int g0 = (int)(grp & 0xffu), gn = (int)(grp >> 8 & 0xffu), slices = (int)(grp >> 16);
+    int slice, panel, first, n;
+    if (!panel_of_block(cls, gn, slices, (int)blockIdx.x - (gi ? sh.end[gi - 1] : 0), slice, panel, first, n)) return;
     const DevItem it = panels[panel];
     const int pj = g0 + first;
     auto at_of = [&](int i) {
@@ -1021,19 +1016,18 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
         with_batch_size(batch, [&](const auto &tb) {
             constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
             PanelShape<N> sh;
-            int end = 0, groups = 0, before = 0;  // before: slices of the groups before
+            int end = 0, groups = 0;
             bool sums = false;
             for (int i = 0; i < tb.n; ++groups) {
                 const int gn = (int)(batch.group[i] >> 8);
-                sh.group[groups] = (uint32_t)i | (uint32_t)gn << 8 | (uint32_t)batch.slices[i] << 16 | (uint32_t)(before * tb.n_panels & 7) << 24;
-                before += batch.slices[i];
+                sh.group[groups] = (uint32_t)i | (uint32_t)gn << 8 | (uint32_t)batch.slices[i] << 16;
                 sh.end[groups] = end += panel_blocks(batch.classes, gn) * batch.slices[i];
                 for (int k = 0; k < gn; ++k, ++i) sh.slices[i] = batch.slices[i];
                 sums |= sh.slices[i - 1] > 1;
             }
             for (int g = groups; g < N; ++g) sh.end[g] = end, sh.group[g] = sh.group[groups - 1];
             for (int i = tb.n; i < N; ++i) sh.slices[i] = 1;
-            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N>, dim3(8 * end), dim3(512), PANEL_RING, st, tb.panels, tb.n_panels, batch.classes, sh, tb);
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N>, dim3(end), dim3(512), PANEL_RING, st, tb.panels, batch.classes, sh, tb);
             if (sums) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_panel_sum_kernel<N>, dim3(tb.n_panels * (PANEL_ROWS / 32), tb.n), dim3(256), 0, st, tb.panels, sh, tb);
         });
         return hipGetLastError();
