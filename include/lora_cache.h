@@ -67,7 +67,7 @@ enum {
                                      tile kernels have some milliseconds of work (4 GB of activations and outputs) runs on a stream
                                      of the cache's own, forked off the caller's stream and joined to it again inside the call,
                                      side by side with the tile kernels (different tokens) */
-    LORA_CACHE_SMALL_SCRATCH = 32, /* scratch for up to 4 projections at a time instead of up to 120, staging for one part of an adapter:
+    LORA_CACHE_SMALL_SCRATCH = 32, /* scratch for up to 4 projections at a time instead of up to 224, staging for one part of an adapter:
                                      see lora_cache_bytes_required */
     LORA_CACHE_DIRECT_FILL = 8    /* fills read pinned host memory from the repack kernel itself instead of copying it
                                      to a staging buffer first: about twice the fill rate on an idle device, but applies
@@ -112,7 +112,7 @@ size_t lora_adapter_bytes(int32_t h_in, int32_t h_out, int32_t rank, int32_t dty
 
 /* Bytes of the pool: slabs of every (layer, projection, slot) + scratch + plan buffers + fill staging.  0 on a bad config.
  * The scratch holds the intermediates of up to 120 projections that one list call works on at a time (as many as fit into
- * 512 MB), up to 85 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
+ * 512 MB; up to 224 as far as those fit into 64 MB), up to 85 MB of partial sums and two staging buffers of up to 16 MB.  With LORA_CACHE_SMALL_SCRATCH it is that of 4 projections, at
  * most 48 MB of partial sums and staging for one part of an adapter: the same results, but list calls run 4
  * projections at a time, launches with many one-token requests and split tiles of the fused product have less to work with, and staged fills travel part by part. */
 size_t lora_cache_bytes_required(const lora_cache_config_t *cfg);
@@ -367,7 +367,7 @@ int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32
  * through the binding), up to rounding: the fp32 sums of a tile's shrink are cut in other places when several
  * projections share a launch, and the bf16 intermediate then rounds the other way once in a while.  The same list
  * with the same plan gives the same bits every time.  Consecutive entries that do not depend on each other (no base_out overlaps
- * another entry's base_out or any entry's x) run as batches of up to 64 (120 where the plan has no tiles): one launch per phase for all of them, and one
+ * another entry's base_out or any entry's x) run as batches of up to 64 (120 where the plan has no tiles, 224 where they are of at most eight of the cache's projections besides): one launch per phase for all of them, and one
  * pass over x for those that read the same x (q, k, v; gate, up; up to 4 neighbours).  Nothing is
  * enqueued if any entry fails validation. */
 typedef struct {

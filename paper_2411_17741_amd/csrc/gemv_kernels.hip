@@ -445,14 +445,16 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
 
 // The same for a batch of groups (GemvBatch): every projection brings its own x.  What a launch of one group costs beside
 // its bytes -- the gap to the kernel before it, the ramp, the hand-over at its end, 5 to 6 us -- is paid once per batch.
-template <typename E>
-__global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
+__device__ __forceinline__ const GemvItem *items_of(const GemvBatch &b, bool shrink) { return shrink ? b.gs : b.ge; }
+__device__ __forceinline__ const GemvItem *items_of(const GemvLong &b, bool shrink) { return static_cast<const GemvItem *>(shrink ? b.shrink_items : b.expand_items); }
+template <typename E, typename Batch>
+__global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b)
 {
     __shared__ float red[4][16];
     __shared__ __attribute__((aligned(16))) uint32_t stage[4][sizeof(E) == 2 ? TB * 64 : TB * 128];
     const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
     auto use = [&](uint32_t proj, uint32_t &first_super) {
-        const BatchProj q = gemv_entry_proj(b.p[proj], first_super);
+        const BatchProj q = gemv_batch_proj(b, proj, first_super);
         return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * (int64_t)sizeof(E), static_cast<const char *>(q.x), static_cast<char *>(q.y), nullptr,
                        b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
     };
@@ -461,7 +463,7 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
         gemv_batch_shrink(blockIdx.x, b.m, proj, item);
         if (item >= b.m.n_gs) return;
         uint32_t first;
-        gemv_shrink_work<E>(use(proj, first), load_item(b.gs + item), red);
+        gemv_shrink_work<E>(use(proj, first), load_item(items_of(b, true) + item), red);
     } else {
         if (b.m.phase == 1) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -470,8 +472,8 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(GemvBatch b)
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
         uint32_t first;
-        const GemvUse a = use(gemv_super(b.supers, super), first);
-        gemv_expand_work<E>(a, load_item(b.ge + item), super - first, stage[w]);
+        const GemvUse a = use(gemv_batch_super(b, super), first);
+        gemv_expand_work<E>(a, load_item(items_of(b, false) + item), super - first, stage[w]);
     }
 }
 
@@ -709,20 +711,25 @@ __device__ __forceinline__ void gemv_wide_expand(const GemvUse &a, const ItemW i
     }
 }
 
-__global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
+__device__ __forceinline__ const GemvWideItem *wide_items_of(const GemvBatch &b, bool shrink) { return shrink ? b.wgs : b.wge; }
+__device__ __forceinline__ const GemvWideItem *wide_items_of(const GemvLong &b, bool shrink) { return static_cast<const GemvWideItem *>(shrink ? b.shrink_items : b.expand_items); }
+__device__ __forceinline__ float *y32_of(const GemvBatch &b) { return b.y32; }
+__device__ __forceinline__ float *y32_of(const GemvLong &) { return nullptr; }
+template <typename Batch>
+__global__ __launch_bounds__(256, 4) void gemv_wide_kernel(Batch b)
 {
     __shared__ __attribute__((aligned(16))) unsigned char lds[WIDE_LDS];
     const uint32_t n_shrink = b.m.phase == 2 ? 0u : b.m.n_proj * b.m.shrink_blocks;
     auto use = [&](uint32_t proj, uint32_t &first_super) {
-        const BatchProj q = gemv_entry_proj(b.p[proj], first_super);
-        return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * 2, static_cast<const char *>(q.x), static_cast<char *>(q.y), b.y32,
+        const BatchProj q = gemv_batch_proj(b, proj, first_super);
+        return GemvUse{q.proj_base, (int64_t)(q.h_in + q.h_out) * 2, static_cast<const char *>(q.x), static_cast<char *>(q.y), y32_of(b),
                        b.vw + proj * b.vw_set, b.fault, q.h_in, q.h_out, b.epoch, b.scale};
     };
     if (blockIdx.x < n_shrink) {
         uint32_t item, proj;
         gemv_batch_shrink(blockIdx.x, b.m, proj, item);
         if (item >= b.m.n_gs) return;
-        const GemvWideItem *p = b.wgs + item;
+        const GemvWideItem *p = wide_items_of(b, true) + item;
         const ItemW it = load_wide(p);
         uint32_t first;
         const GemvUse a = use(proj, first);
@@ -739,8 +746,8 @@ __global__ __launch_bounds__(256, 4) void gemv_wide_kernel(GemvBatch b)
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
         uint32_t first;
-        const GemvUse a = use(gemv_super(b.supers, super), first);
-        const GemvWideItem *p = b.wge + item;
+        const GemvUse a = use(gemv_batch_super(b, super), first);
+        const GemvWideItem *p = wide_items_of(b, false) + item;
         const ItemW it = load_wide(p);
         int c0, c1;
         gemv_wide_cols(it.rank, it.a, (int)(super - first), a.h_out, c0, c1);
@@ -801,17 +808,17 @@ hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+template <typename Batch> static hipError_t launch_batch(int dtype, const Batch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (b.m.n_gs == 0 || b.m.n_ge == 0 || b.m.n_proj == 0) return hipSuccess;
-    if ((wide && dtype != LORA_BF16) || (b.y32 && !(wide && b.m.n_proj == 1))) return hipErrorInvalidValue;
+    if (wide && dtype != LORA_BF16) return hipErrorInvalidValue;
     const unsigned n_shrink = b.m.n_proj * b.m.shrink_blocks, n_expand = (b.m.n_units + 3) / 4;
     auto go = [&](uint32_t phase, unsigned blocks, int kind, hipEvent_t ev) {
-        GemvBatch q = b;
+        Batch q = b;
         q.m.phase = phase;
-        if (wide) launch_k(tm, ev, kind, gemv_wide_kernel, dim3(blocks), dim3(256), 0, st, q);
-        else if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, q);
-        else launch_k(tm, ev, kind, gemv_batch_kernel<float>, dim3(blocks), dim3(256), 0, st, q);
+        if (wide) launch_k(tm, ev, kind, gemv_wide_kernel<Batch>, dim3(blocks), dim3(256), 0, st, q);
+        else if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch>, dim3(blocks), dim3(256), 0, st, q);
+        else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch>, dim3(blocks), dim3(256), 0, st, q);
     };
     if (b.epoch) {
         go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
@@ -821,5 +828,12 @@ hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream
     }
     return hipGetLastError();
 }
+
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+{
+    if (b.y32 && !(wide && b.m.n_proj == 1)) return hipErrorInvalidValue;
+    return launch_batch(dtype, b, wide, st, tm, done);
+}
+hipError_t launch_gemv_long(int dtype, const GemvLong &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done) { return launch_batch(dtype, b, wide, st, tm, done); }
 
 }  // namespace lora

@@ -83,6 +83,8 @@ constexpr double FORK_MIN_TILE_BYTES = 4e9;
 // Applies that run together in one batch each have their own copy of the intermediate (a set): as many sets as fit into
 // BATCH_SCRATCH_BYTES (0.2 % of the card's memory), a group's at least.  64 one-token requests: 4 MB for 64 sets.
 constexpr size_t BATCH_SCRATCH_BYTES = (size_t)512 << 20;
+// Sets past GEMV_BATCH_MAX_PROJS as far as all of them stay within this: 224 up to 290 tokens
+constexpr size_t LONG_SCRATCH_BYTES = (size_t)64 << 20;
 
 size_t align_up(size_t v, size_t a = ALIGN) { return (v + a - 1) / a * a; }
 
@@ -320,7 +322,7 @@ bool config_ok(const lora_cache_config_t *cfg)
 // Fills every layout field of `c` from the config; used by bytes_required and create alike.  small_scratch: what a group
 // of projections needs and no more -- no further sets, run tables and wide items for batches, staging for one part.
 // max_sets: sets for batches at most; direct: plans have room for the units of a short tile shrink.
-void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_scratch, int max_sets = lora::GEMV_BATCH_MAX_PROJS, bool direct = true)
+void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_scratch, int max_sets = lora::GEMV_LONG_MAX_PROJS, bool direct = true)
 {
     c.small_scratch = small_scratch;
     c.proj.assign(cfg->proj, cfg->proj + cfg->n_proj);
@@ -397,15 +399,18 @@ void compute_layout(lora_cache &c, const lora_cache_config_t *cfg, bool small_sc
     c.off_v = cur;
     c.v_set_bytes = align_up(sizeof(float) * (size_t)c.max_tokens * c.v_stride);
     c.vtag_set_bytes = align_up(lora::gemv_handover_bytes(c.dtype, c.max_tokens));
-    c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min<size_t>(std::min<size_t>((size_t)max_sets, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS),
-                                     std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / (c.v_set_bytes + c.vtag_set_bytes)));
+    {  // (sets past a common batch's are for launches that their own cost matters to: few tokens)
+        const size_t set = c.v_set_bytes + c.vtag_set_bytes, room = std::max<size_t>(lora::GROUP_MAX_PROJS, BATCH_SCRATCH_BYTES / set);
+        const size_t most = std::max(std::min<size_t>(lora::GEMV_BATCH_MAX_PROJS, room), std::min<size_t>(lora::GEMV_LONG_MAX_PROJS, LONG_SCRATCH_BYTES / set));
+        c.n_sets = small_scratch ? lora::GROUP_MAX_PROJS : (int)std::min({(size_t)max_sets, (size_t)c.n_layers * c.proj.size() + lora::GROUP_MAX_PROJS, most});
+    }
     cur += c.v_set_bytes * c.n_sets;
     // partial sums of the tile shrink: two slots per run and projection; a launch has at most SHRINK_MAX_RUNS blocks
     // for a group whatever its size, twice that for a batch, and a batch of few tiles has few runs (a piece is at
     // least two of the parts a tile's k range is cut into)
     {
         const int64_t tiles = std::max<int64_t>(1, ((int64_t)c.max_tokens + LORA_TILE_TOKENS - 1) / LORA_TILE_TOKENS);
-        const int64_t runs = std::min<int64_t>((small_scratch ? 1 : 2) * SHRINK_MAX_RUNS, 16 * c.n_sets * tiles);
+        const int64_t runs = std::min<int64_t>((small_scratch ? 1 : 2) * SHRINK_MAX_RUNS, 16 * std::min(c.n_sets, lora::GEMV_BATCH_MAX_PROJS) * tiles);
         c.vpart_rows = c.dtype == LORA_BF16 ? 2 * lora::SHRINK_SLOT_ROWS * runs : 0;
     }
     c.off_vpart = cur;
@@ -756,7 +761,7 @@ size_t ListBuild::size(const lora_cache &c, PlanLists &p, bool internal, bool ta
     std::stable_sort(group_order.begin(), group_order.end(),
                      [&](int x, int y) { return lora::rank_storage(w.groups[x].rank) < lora::rank_storage(w.groups[y].rank); });
     // how many there are (they are written straight to the staged copy further down)
-        for (int gi = 0; gi < w.n_groups; ++gi) {
+    for (int gi = 0; gi < w.n_groups; ++gi) {
         const int32_t n = w.groups[gi].n_tok, rank = w.groups[gi].rank, batches = (n + lora::GEMV_BATCH - 1) / lora::GEMV_BATCH;
         n_gs += (int64_t)batches * (lora::rank_storage(rank) / lora::GEMV_SHRINK_ROWS);
         n_ge += (int64_t)batches * (lora::GEMV_SUPER_COLS / lora::gemv_expand_width(rank));
@@ -1804,9 +1809,8 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out)
 static int32_t supers_of(int32_t h_out) { return (h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS; }
 
 // Block and unit numbers of a batch's GEMV launch for n projections, h_out[i] wide, with a plan's items or its wide items;
-// shared by the launch and lora_plan_dump.  `supers` comes in zeroed; first[i]: number of projection i's first super-chunk.
-static int gemv_batch_map(const PlanLists *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t (&supers)[lora::GEMV_BATCH_MAX_SUPERS / 4],
-                          uint32_t (&first)[lora::GEMV_BATCH_MAX_PROJS])
+// shared by the launches and lora_plan_dump.  `marks` comes in zeroed: the projection of every step-th super-chunk, four to a word; first[i]: number of projection i's first super-chunk.
+static int gemv_batch_map(const PlanLists *p, bool wide, int n, const int32_t *h_out, lora::GemvBatchMap &m, uint32_t *marks, int32_t max_supers, int step, uint32_t *first)
 {
     m.n_gs = (uint32_t)(wide ? p->n_wgs : p->n_gs);
     m.n_ge = (uint32_t)(wide ? p->n_wge : p->n_ge);
@@ -1819,10 +1823,10 @@ static int gemv_batch_map(const PlanLists *p, bool wide, int n, const int32_t *h
     for (int i = 0; i < n; ++i) {
         if (supers_of(h_out[i]) > 255) return LORA_E_INVAL;  // as a group's launch
         first[i] = (uint32_t)n_super;
-        for (int32_t k = 0; k < supers_of(h_out[i]); ++k, ++n_super) {
-            if (n_super >= lora::GEMV_BATCH_MAX_SUPERS) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
-            supers[n_super >> 2] |= (uint32_t)i << (8 * (n_super & 3));
-        }
+        const int32_t end = n_super + supers_of(h_out[i]);
+        if (end > max_supers) return LORA_E_INVAL;  // (the caller cuts batches by batch_limits)
+        for (int32_t k = (n_super + step - 1) / step; k * step < end; ++k) marks[k >> 2] |= (uint32_t)i << (8 * (k & 3));
+        n_super = end;
     }
     const int64_t units = (int64_t)m.n_ge * n_super;
     if (units >= (1 << 24) || (int64_t)m.shrink_blocks * n >= (1 << 24)) return LORA_E_INVAL;  // beyond the kernels' unit arithmetic
@@ -1838,9 +1842,10 @@ static Scratch pool_scratch(lora_cache_t *c)
 
 // How many projections, and super-chunks of projections, a batch with plan p may have: the scratch's sets, the partial sums of the
 // smallest run table of the tile shrink, and the ranges of the GEMV launch's unit arithmetic.
-static void batch_limits(const PlanLists *p, const Scratch &sc, int32_t &max_projs, int32_t &max_supers)
+static void batch_limits(const PlanLists *p, const Scratch &sc, bool long_batch, int32_t &max_projs, int32_t &max_supers)
 {
-    int64_t projs = sc.n_sets, supers = lora::GEMV_BATCH_MAX_SUPERS;
+    int64_t projs = std::min(sc.n_sets, long_batch ? lora::GEMV_LONG_MAX_PROJS : lora::GEMV_BATCH_MAX_PROJS);
+    int64_t supers = long_batch ? lora::GEMV_LONG_MAX_SUPERS : lora::GEMV_BATCH_MAX_SUPERS;
     if (p->n_tiles > 0) {
         projs = std::min<int64_t>(projs, lora::BATCH_MAX_PROJS);
         projs = std::min(projs, sc.vpart_rows / (2 * lora::SHRINK_SLOT_ROWS * std::max<int64_t>(1, p->shrink_runs[SHRINK_VARIANTS - 1])));
@@ -1984,7 +1989,7 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     const lora::GemvWideItem *wge = reinterpret_cast<const lora::GemvWideItem *>(buf + p->off_wge);
     const int32_t n_proj = (int32_t)c->proj.size();
     int32_t widths[lora::GEMV_BATCH_MAX_PROJS], entries = 0, supers_left, max_entries;
-    batch_limits(p, pool_scratch(c), max_entries, supers_left);
+    batch_limits(p, pool_scratch(c), false, max_entries, supers_left);
     for (; entries < std::min(max_entries, std::min(c->n_layers, 2) * n_proj); ++entries) {
         widths[entries] = c->proj[entries % n_proj].h_out;
         supers_left -= supers_of(widths[entries]);
@@ -1993,7 +1998,7 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     for (int wide = 0; wide < 2; ++wide) {
         lora::GemvBatchMap m{};
         uint32_t supers[lora::GEMV_BATCH_MAX_SUPERS / 4] = {0}, first[lora::GEMV_BATCH_MAX_PROJS];
-        if ((wide ? p->n_wgs : p->n_gs) == 0 || entries == 0 || gemv_batch_map(p, wide != 0, entries, widths, m, supers, first)) continue;
+        if ((wide ? p->n_wgs : p->n_gs) == 0 || entries == 0 || gemv_batch_map(p, wide != 0, entries, widths, m, supers, lora::GEMV_BATCH_MAX_SUPERS, 1, first)) continue;
         auto put = [&](int32_t kind, const lora::GemvItem *it, const lora::GemvWideItem *w, int32_t lo, int32_t hi, uint32_t e) {
             const int32_t off = nt;
             int32_t cnt = w ? w->n_tok : gemv_tokens(*it);
@@ -2268,7 +2273,7 @@ static bool gemv_wide(const lora_cache_t *c, const PlanLists *p, const lora::Bat
     if (c->dtype != LORA_BF16 || (int64_t)p->n_wgs * n < (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP)) return false;
     int64_t supers = 0;  // (a group may be beyond the batch kernels' unit arithmetic, a batch is cut to it)
     for (int i = 0; i < n; ++i) supers += supers_of(projs[i].h_out);
-    return supers <= lora::GEMV_BATCH_MAX_SUPERS && supers * p->n_wge < (1 << 24);
+    return supers <= lora::GEMV_LONG_MAX_SUPERS && (n_groups > 1 || supers <= lora::GEMV_BATCH_MAX_SUPERS) && supers * p->n_wge < (1 << 24);
 }
 
 // The same for a batch of several groups.
@@ -2290,7 +2295,7 @@ static int enqueue_gemv_batch(lora_cache_t *c, const PlanLists *p, const lora::B
     int32_t widths[lora::GEMV_BATCH_MAX_PROJS];
     uint32_t first[lora::GEMV_BATCH_MAX_PROJS];
     for (int i = 0; i < n; ++i) widths[i] = projs[i].h_out;
-    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.supers, first)) return rc;
+    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.supers, lora::GEMV_BATCH_MAX_SUPERS, 1, first)) return rc;
     for (int i = 0; i < n; ++i) b.p[i] = lora::gemv_entry(projs[i], first[i]);
     if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_BATCH_ITEMS)) {
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
@@ -2300,14 +2305,69 @@ static int enqueue_gemv_batch(lora_cache_t *c, const PlanLists *p, const lora::B
     return LORA_OK;
 }
 
+// A batch of more projections or super-chunks than GemvBatch holds, entries as the caller gave them (their addresses are what `projs` says)?
+static bool gemv_long(const lora_cache_t *c, const PlanLists *p, const lora_apply_desc_t *descs, int n)
+{
+    int32_t kinds[lora::GEMV_LONG_KINDS], n_kinds = 0;
+    int64_t supers = 0;
+    for (int i = 0; i < n; ++i) {
+        supers += supers_of(c->proj[descs[i].proj].h_out);
+        int k = 0;
+        while (k < n_kinds && kinds[k] != descs[i].proj) ++k;
+        if (k == lora::GEMV_LONG_KINDS) return false;
+        if (k == n_kinds) kinds[n_kinds++] = descs[i].proj;
+    }
+    return p->n_tiles == 0 && p->n_gs > 0 && n <= lora::GEMV_LONG_MAX_PROJS && supers <= lora::GEMV_LONG_MAX_SUPERS && c->n_layers <= 1 << 21 &&
+           (n > lora::GEMV_BATCH_MAX_PROJS || supers > lora::GEMV_BATCH_MAX_SUPERS);
+}
+static int enqueue_gemv_long(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *projs, const lora_apply_desc_t *const *descs, int n, int n_groups, float scale, hipStream_t st,
+                             const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
+{
+    lora::GemvLong b{};
+    const bool wide = gemv_wide(c, p, projs, n, n_groups);
+    b.shrink_items = p->lists + (wide ? p->off_wgs : p->off_gs);
+    b.expand_items = p->lists + (wide ? p->off_wge : p->off_ge);
+    b.vw = reinterpret_cast<unsigned long long *>(sc.vtag);
+    b.vw_set = sc.vtag_set_bytes / sizeof(unsigned long long);
+    b.fault = c->fault_dev;
+    b.scale = scale;
+    b.pool = c->pool;
+    b.layer_stride = c->layer_stride;
+    int32_t widths[lora::GEMV_LONG_MAX_PROJS], kinds[lora::GEMV_LONG_KINDS], n_kinds = 0;
+    uint32_t first[lora::GEMV_LONG_MAX_PROJS];
+    for (int i = 0; i < n; ++i) widths[i] = projs[i].h_out;
+    if (const int rc = gemv_batch_map(p, wide, n, widths, b.m, b.marks, lora::GEMV_LONG_MAX_SUPERS, lora::GEMV_LONG_STEP, first)) return rc;
+    for (int i = 0; i < n; ++i) {
+        const lora_apply_desc_t &d = *descs[i];
+        int k = 0;
+        while (k < n_kinds && kinds[k] != d.proj) ++k;
+        if (k == lora::GEMV_LONG_KINDS) return LORA_E_INVAL;  // (cannot happen: gemv_long)
+        if (k == n_kinds) {
+            kinds[n_kinds++] = d.proj;
+            b.off_h_out[k] = (uint64_t)c->proj_off[d.proj] | (uint64_t)(projs[i].h_out / 64) << 48;
+            b.h_in[k] = projs[i].h_in;
+        }
+        b.p[i] = lora::gemv_long_entry(d.x, d.base_out, (uint32_t)k, (uint32_t)d.layer, first[i]);
+    }
+    if (one_gemv_launch(c, sc, (int64_t)p->n_gs * n, FUSED_GEMV_MAX_BATCH_ITEMS)) {
+        if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
+        b.epoch = ++*sc.epoch;
+    }
+    HIP_TRY(lora::launch_gemv_long(c->dtype, b, wide, st, tm, done));
+    return LORA_OK;
+}
+
 // The lists a launch for n projections in n_groups groups works through, sum_width wide together (h_in + h_out)
 static const PlanLists *pick_lists(lora_cache_t *c, lora_plan_t *p, int n, int n_groups, double sum_width, hipStream_t st)
 {
     if (!p->may_tile) return p;
     auto wide = [&](int64_t n_wgs) { return n_wgs * n >= (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP) ? 1 : 0; };
     const double gemv = GEMV_FIXED_US + p->gemv_cost[wide(p->n_wgs)].us(n, sum_width);
-    const double tiled = TILE_FIXED_US + (p->rest_groups > 0 ? TILE_BESIDE_GEMV_US : 0.0) + p->rest_cost[wide(p->rest_wgs)].us(n, sum_width) + p->tile_cost.us(n, sum_width);
-    return tiled < 0.92 * gemv && tiled + TILED_LISTS_US < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
+    // More projections than a batch of tiles holds pay for its launches again, and long lists take less than estimated as GEMV: 224 projections of a 7B model, 32 requests of one adapter of rank 16
+    // 108 us with tiles and 85 without, 48 of two 238 and 187; 2048 wide, 64 of two of rank 8 101 and 80; 256 requests of four 524 and 880
+    const int launches = (n + lora::BATCH_MAX_PROJS - 1) / lora::BATCH_MAX_PROJS;
+    const double tiled = launches * (TILE_FIXED_US + (p->rest_groups > 0 ? TILE_BESIDE_GEMV_US : 0.0)) + p->rest_cost[wide(p->rest_wgs)].us(n, sum_width) + p->tile_cost.us(n, sum_width);
+    return tiled < (n > lora::GEMV_BATCH_MAX_PROJS ? 0.75 : 0.92) * gemv && tiled + TILED_LISTS_US < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
 }
 // The same for the base product, which takes the tiles' term along: no expand launch, but a segment of rows costs its blocks 1.3 us for its Bp
 static const PlanLists *pick_linear_lists(lora_cache_t *c, lora_plan_t *p, double width, hipStream_t st)
@@ -2359,14 +2419,16 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         if (const int rc_s = tile_setup(c, q, n, sum_h_in, sc, scale, tb)) return rc_s;
     // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
     int n_groups = 0;
-    uint8_t first[lora::GEMV_BATCH_MAX_PROJS];
-    lora::BatchProj projs[lora::GEMV_BATCH_MAX_PROJS];
+    uint8_t first[lora::GEMV_LONG_MAX_PROJS];
+    lora::BatchProj projs[lora::GEMV_LONG_MAX_PROJS];
+    const lora_apply_desc_t *at_desc[lora::GEMV_LONG_MAX_PROJS];
     for (int i = 0; i < n; i += group_n[i]) first[n_groups++] = (uint8_t)i;
     std::stable_sort(first, first + n_groups, [&](uint8_t g, uint8_t h) { return c->proj[descs[g].proj].h_in > c->proj[descs[h].proj].h_in; });
     for (int g = 0, i = 0; g < n_groups; ++g) {
         const int size = group_n[first[g]], at = i;
         for (int k = 0; k < size; ++k, ++i) {
-            projs[i] = batch_proj(c, descs[first[g] + k]);
+            at_desc[i] = &descs[first[g] + k];
+            projs[i] = batch_proj(c, *at_desc[i]);
             if (q->n_tiles > 0) tb.p[i] = projs[i], tb.group[i] = (uint32_t)at | (uint32_t)size << 8;
         }
     }
@@ -2405,7 +2467,8 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
     const bool ride = fence && !fork && tm == nullptr && (q->n_tiles > 0 || q->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && q->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
+    if (const int rc_g = n_groups > 1 && gemv_long(c, q, descs, n) ? enqueue_gemv_long(c, q, projs, at_desc, n, n_groups, scale, gemv_st, sc, tm, gemv_done)
+                                       : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
                                        : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
         return rc_g;
     join.rides = join_rides;
@@ -2587,11 +2650,11 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         bool meets(const Range &o) const { return lo < o.hi && o.lo < hi; }
     };
     const size_t e = c->esize;
-    Range in[lora::GEMV_BATCH_MAX_PROJS], out[lora::GEMV_BATCH_MAX_PROJS];  // distinct inputs of the batch's groups; outputs of its entries, by address (they do not overlap)
-    uint8_t group_n[lora::GEMV_BATCH_MAX_PROJS];
+    Range in[lora::GEMV_LONG_MAX_PROJS], out[lora::GEMV_LONG_MAX_PROJS];  // distinct inputs of the batch's groups; outputs of its entries, by address (they do not overlap)
+    uint8_t group_n[lora::GEMV_LONG_MAX_PROJS];
     const Scratch scratch = pool_scratch(c);
     int32_t max_projs, max_supers;
-    batch_limits(p, scratch, max_projs, max_supers);
+    batch_limits(p, scratch, p->n_tiles == 0, max_projs, max_supers);
     for (int32_t i = 0; i < n;) {
         int32_t m = 0, n_in = 0, last = 0, supers = 0;  // last: entry the latest group starts at
         for (; i + m < n && m < max_projs; ++m) {
@@ -2630,11 +2693,14 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         for (int k = 0; k < m; ++k) sum_width += (double)c->proj[descs[i + k].proj].h_in + c->proj[descs[i + k].proj].h_out;
         for (int k = 0; k < m; k += group_n[k]) ++n_groups;
         const PlanLists *const q = pick_lists(c, p, m, n_groups, sum_width, st);
-        int32_t most = m, unused;
-        if (q != p) batch_limits(q, scratch, most, unused);
-        for (int at = 0; at < m;) {  // (a batch with tiles holds fewer projections)
-            int k = group_n[at];
-            while (at + k < m && k + group_n[at + k] <= most) k += group_n[at + k];
+        int32_t most = m, most_supers = INT32_MAX;
+        if (q != p || (p->n_tiles == 0 && !gemv_long(c, q, descs + i, m))) batch_limits(q, scratch, false, most, most_supers);
+        for (int at = 0; at < m;) {  // (a batch with tiles holds fewer projections, one of more kinds of projections than a long one tells apart too)
+            int k = 0;
+            for (int32_t left = most_supers; at + k < m; k += group_n[at + k]) {
+                for (int e = 0; e < group_n[at + k]; ++e) left -= supers_of(c->proj[descs[i + at + k + e].proj].h_out);
+                if (k > 0 && (k + group_n[at + k] > most || left < 0)) break;
+            }
             const int rc = enqueue_batch(c, p, q, descs + i + at, group_n + at, k, scale, st, scratch, f >= 0 && i + at + k == n ? c->fences[f].ev : nullptr);
             if (rc != LORA_OK) return rc;
             at += k;
