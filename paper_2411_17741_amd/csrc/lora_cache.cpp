@@ -47,8 +47,10 @@ constexpr int N_LINEAR_SPLITS = 256;  // split tiles of lora_linear_plan (tiles 
 constexpr double GEMV_FIXED_US = 4.0, TILE_FIXED_US = 10.5;
 // Beside the base product: a shrink launch, the fp32 term of GEMV rows
 constexpr double LINEAR_SHRINK_US = 3.0, LINEAR_TERM_US = 1.0;
-// The lists that a plan whose own have no tiles makes for such launches cost it about 6 us, once.  What a launch has to gain by them: a list of projections nearly all of it, a base product its share
-// if the plan serves every projection of every layer once.  (The choice looks at nothing but the cache, the plan and the launch: the same call gives the same bits.)  Measured, us a pass with GEMV alone and as chosen:
+// A plan whose own lists have no tiles is made with lists for such launches besides, where one can gain by them: 1 to 4 us more on the host (one prompt of 77 tokens 8.2 and 9.1, three of 5 to 400 tokens
+// 11.7 and 15.6), in the same upload.  What a launch has to gain by them was fitted to lists with an upload of their own, 6 us: a list of projections nearly all of it, a base product its share if the plan
+// serves every projection of every layer once.  (The choice looks at nothing but the cache, the plan and the launch, and the lists are there from the start: the same call gives the same
+// bits, captured or not.)  Measured, us a pass with GEMV alone and as chosen:
 // q, k, v, o of two layers, prompts of 11 to 1136 tokens at rank 64 180 and 88; all of two 13B layers, 73 tokens of rank 128 77 and 50; q, k, v of eight layers, 922 one-token requests over 20 adapters 92 and 83;
 // base product of q, k, v, o 4096 wide, 941 tokens 256 and 216, of q 5120 wide, 1543 tokens 132 and 115.  Of 120 drawn lists and products it picks the better way but for 0.5 % in the geometric mean.
 constexpr double TILED_LISTS_US = 5.0, LINEAR_MIN_GAIN_US = 1.0, LISTS_COST_US = 6.0;
@@ -210,14 +212,14 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     bool upload_pending = false;
     int32_t last_use = -1;  // fence of the latest call that used the plan
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
-    size_t bytes = 0;           // of all lists
+    size_t bytes = 0;           // of these lists
     // Where a call for one projection leaves the tokens that could be tiles to the GEMV kernels, launches that share the tile path's fixed cost, and the base product, which needs
-    // no expand launch, may do better with tiles: what it takes to tell (for the threshold 16), and those lists, made for the first launch that asks for them
-    bool may_tile = false, has_tiled = false;
+    // no expand launch, may do better with tiles: what it takes to tell (for the threshold 16), and the lists for them, behind the plan's own, where some launch can gain by them
+    bool has_tiled = false;
     PathCost gemv_cost[2], rest_cost[2], tile_cost;  // GEMV tokens [items, wide items] of the lists and of those with tiles; the tile tokens
     int32_t rest_groups = 0, rest_wgs = 0, tile_tok = 0, tile_segs = 0;
-    std::vector<int32_t> segs[3];  // the batch: offsets, slots, ranks
     PlanLists tiled;
+    size_t tiled_bytes = 0;
     std::vector<int32_t> slots;        // distinct slots the batch names
     std::vector<uint32_t> generations;  // their generation at plan time
 };
@@ -963,6 +965,49 @@ void ListBuild::write(const lora_cache &c, const PlanLists &p, char *to) const
     }
 }
 
+// Does a launch for n projections in n_groups groups, sum_width wide together (h_in + h_out), gain by the lists with tiles?
+bool list_takes_tiles(const lora_plan &p, int n, int n_groups, double sum_width)
+{
+    auto wide = [&](int64_t n_wgs) { return n_wgs * n >= (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP) ? 1 : 0; };
+    const double gemv = GEMV_FIXED_US + p.gemv_cost[wide(p.n_wgs)].us(n, sum_width);
+    // More projections than a batch of tiles holds pay for its launches again, and long lists take less than estimated as GEMV: 224 projections of a 7B model, 32 requests of one adapter of rank 16
+    // 108 us with tiles and 85 without, 48 of two 238 and 187; 2048 wide, 64 of two of rank 8 101 and 80; 256 requests of four 524 and 880
+    const int launches = (n + lora::BATCH_MAX_PROJS - 1) / lora::BATCH_MAX_PROJS;
+    const double tiled = launches * (TILE_FIXED_US + (p.rest_groups > 0 ? TILE_BESIDE_GEMV_US : 0.0)) + p.rest_cost[wide(p.rest_wgs)].us(n, sum_width) + p.tile_cost.us(n, sum_width);
+    return tiled < (n > lora::GEMV_BATCH_MAX_PROJS ? 0.75 : 0.92) * gemv && tiled + TILED_LISTS_US < gemv;
+}
+// The same for the base product, which takes the tiles' term along: no expand launch, but a segment of rows costs its blocks 1.3 us for its Bp
+bool product_takes_tiles(const lora_cache &c, const lora_plan &p, double width)
+{
+    const double gemv = GEMV_FIXED_US + LINEAR_TERM_US + p.gemv_cost[p.n_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width);
+    const double rest = p.rest_groups > 0 ? GEMV_FIXED_US + p.rest_cost[p.rest_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width) : 0.0;
+    const double segments = std::max(1.0, p.tile_segs * std::min(1.0, 256.0 / p.tile_tok));  // of a block
+    const double tiled = rest + LINEAR_SHRINK_US + 0.4 * p.tile_cost.us(1, width) + 1.3 * segments;
+    const double least = LINEAR_MIN_GAIN_US + LISTS_COST_US / (double)(c.n_layers * c.proj.size());
+    return tiled + least < gemv;
+}
+// Does any launch of the cache's projections?  Either estimate rises evenly with the projections and their widths as long as the kind of GEMV items stays, so the ends say it:
+// the narrowest and the widest projection, as many as a batch with tiles or the cache has, and as many as still take no wide items.
+bool some_launch_takes_tiles(const lora_cache &c, const lora_plan &p)
+{
+    double ends[2] = {std::numeric_limits<double>::infinity(), 0};
+    for (const auto &pr : c.proj) {
+        const double width = (double)pr.h_in + pr.h_out;
+        ends[0] = std::min(ends[0], width), ends[1] = std::max(ends[1], width);
+    }
+    const int64_t most = std::min<int64_t>(lora::BATCH_MAX_PROJS, (int64_t)c.n_layers * (int64_t)c.proj.size());
+    auto below_wide = [&](int64_t n_wgs, int64_t from, int64_t up_to) { return n_wgs > 0 ? std::max<int64_t>(1, std::min(up_to, (from - 1) / n_wgs)) : up_to; };
+    for (double width : ends) {
+        if (product_takes_tiles(c, p, width)) return true;
+        for (int64_t n : {most, below_wide(p.n_wgs, GEMV_WIDE_MIN_ITEMS, most), below_wide(p.rest_wgs, GEMV_WIDE_MIN_ITEMS, most)})
+            if (list_takes_tiles(p, (int)n, 2, n * width)) return true;
+        const int64_t group = std::min<int64_t>(most, lora::GROUP_MAX_PROJS);
+        for (int64_t n : {group, below_wide(p.n_wgs, GEMV_WIDE_MIN_ITEMS_ONE_GROUP, group), below_wide(p.rest_wgs, GEMV_WIDE_MIN_ITEMS_ONE_GROUP, group)})
+            if (list_takes_tiles(p, (int)n, 1, n * width)) return true;
+    }
+    return false;
+}
+
 // Validates a batch against the slot table and writes its work lists into plan `p`
 // (pinned copy + upload on `st`).
 int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
@@ -977,7 +1022,9 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     // With the threshold left to the library: the tile path costs two launches more per apply, which a batch with few tile tokens does
     // not earn back.  So: what its tokens cost either way; below, everything stays GEMV; else the batch pays for the tile launches
     // anyway and smaller pools of tokens become tiles too.
-    p.may_tile = p.has_tiled = false;
+    bool may_tile = false;
+    p.has_tiled = false;
+    p.tiled_bytes = 0;
     if (c.mfma_min_auto && w.n_tiles > 0) {
         double mean_width = 0;
         for (const auto &pr : c.proj) mean_width += (double)pr.h_in + pr.h_out;
@@ -1000,7 +1047,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         }
         p.mfma_min_used = gemv_us < tile_us ? 0 : LORA_MFMA_MIN_TOKENS_MIXED;
         if (p.mfma_min_used == 0 && c.dtype == LORA_BF16 && !p.internal && !c.small_scratch) {
-            p.may_tile = true;
+            may_tile = true;
             p.rest_groups = w.n_groups, p.rest_wgs = p.tile_tok = 0, p.tile_segs = (int32_t)of_slot.size();
             p.tile_cost = p.gemv_cost[0] = p.gemv_cost[1] = p.rest_cost[0] = p.rest_cost[1] = PathCost{};
             for (int i = 0; i < w.n_tiles; ++i) p.tile_cost.add_tile(w.tiles[i].n_tok, w.tiles[i].rank);
@@ -1013,9 +1060,6 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
                 for (const auto &kv : of_slot) p.gemv_cost[wide_items].add_gemv(kv.second.first, kv.second.second, wide_items);
             }
             for (const auto &kv : of_slot) p.tile_tok += kv.second.first;
-            p.segs[0].assign(seg_offsets, seg_offsets + n_seg + 1);
-            p.segs[1].assign(seg_slot, seg_slot + n_seg);
-            p.segs[2].assign(seg_rank, seg_rank + n_seg);
         }
         lora_worklists_free(&w);
         rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, p.mfma_min_used, &w);
@@ -1043,6 +1087,15 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
 
     const size_t bytes = lists.size(c, p, p.internal, true, T, c.plan_cap);
     if (bytes > c.plan_cap) return LORA_E_NOMEM;
+    ListBuild tiled;  // (a plan without room for them, or for their panels, does without)
+    if (may_tile && some_launch_takes_tiles(c, p)) {
+        rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, LORA_MFMA_MIN_TOKENS_MIXED, &tiled.w);
+        if (rc != LORA_OK) return rc;
+        const size_t room = c.plan_cap - bytes;
+        p.tiled_bytes = tiled.size(c, p.tiled, false, false, T, room);
+        p.has_tiled = p.tiled_bytes <= room && p.tiled.n_panels > 0;
+        if (!p.has_tiled) p.tiled_bytes = 0;
+    }
     // A captured upload would re-read the staged copy on every replay; plans are made outside of captures.
     if (!c.host_only && is_capturing(st)) return LORA_E_STATE;
     // the staged copy may still be the source of an earlier upload; the device copy may still be read
@@ -1067,6 +1120,11 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.bytes = bytes;
     p.build_seq = ++c.plan_builds;
     p.lists = p.dev;
+    if (p.has_tiled) {
+        tiled.write(c, p.tiled, p.pinned + bytes);
+        p.tiled.build_seq = ++c.plan_builds;
+        if (!c.host_only) p.tiled.lists = p.dev + bytes;
+    }
     int64_t waves = 4 * (int64_t)p.n_gs;  // of a launch for the widest projection
     {
         int32_t supers = 0;
@@ -1080,33 +1138,10 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
             HIP_TRY(hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0));
             hold_fence(c, p.last_use, -1);
         }
-        HIP_TRY(lora::launch_upload(p.dev, p.pinned_dev, bytes, st, p.ev_upload));
+        HIP_TRY(lora::launch_upload(p.dev, p.pinned_dev, bytes + p.tiled_bytes, st, p.ev_upload));
         p.upload_pending = true;
     }
     return LORA_OK;
-}
-
-// The lists with tiles of a plan whose own have none, made when a launch first asks for them: behind the plan's own lists, uploaded on `st`.  Not while capturing (the staged copy would
-// be read again by every replay): a captured call takes them if they are there.
-bool tiled_lists(lora_cache &c, lora_plan &p, hipStream_t st)
-{
-    if (p.has_tiled) return true;
-    if (is_capturing(st)) return false;
-    p.may_tile = false;
-    ListBuild lists;
-    const int32_t n_seg = (int32_t)p.segs[1].size();
-    if (lora_index(p.T, p.segs[0].data(), p.segs[1].data(), p.segs[2].data(), n_seg, LORA_MFMA_MIN_TOKENS_MIXED, &lists.w) != LORA_OK) return false;
-    const size_t bytes = lists.size(c, p.tiled, false, false, p.T, c.plan_cap - p.bytes);
-    if (bytes > c.plan_cap - p.bytes || p.tiled.n_panels == 0) return false;
-    lists.write(c, p.tiled, p.pinned + p.bytes);
-    // (behind the plan's own upload, so behind whatever still read the plan's memory before it)
-    if (p.upload_pending && hipStreamWaitEvent(st, p.ev_upload, 0) != hipSuccess) return false;
-    if (lora::launch_upload(p.dev + p.bytes, p.pinned_dev + p.bytes, bytes, st, p.ev_upload) != hipSuccess) return false;
-    p.upload_pending = true;
-    p.tiled.build_seq = ++c.plan_builds;
-    p.tiled.lists = p.dev + p.bytes;
-    p.has_tiled = p.may_tile = true;
-    return true;
 }
 
 // Makes `st` wait for every apply enqueued so far that named the slot.  The fence of the call that
@@ -2357,28 +2392,14 @@ static int enqueue_gemv_long(lora_cache_t *c, const PlanLists *p, const lora::Ba
     return LORA_OK;
 }
 
-// The lists a launch for n projections in n_groups groups works through, sum_width wide together (h_in + h_out)
-static const PlanLists *pick_lists(lora_cache_t *c, lora_plan_t *p, int n, int n_groups, double sum_width, hipStream_t st)
+// The lists a launch for n projections in n_groups groups works through, sum_width wide together (h_in + h_out), and those of the base product
+static const PlanLists *pick_lists(const lora_plan_t *p, int n, int n_groups, double sum_width)
 {
-    if (!p->may_tile) return p;
-    auto wide = [&](int64_t n_wgs) { return n_wgs * n >= (n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP) ? 1 : 0; };
-    const double gemv = GEMV_FIXED_US + p->gemv_cost[wide(p->n_wgs)].us(n, sum_width);
-    // More projections than a batch of tiles holds pay for its launches again, and long lists take less than estimated as GEMV: 224 projections of a 7B model, 32 requests of one adapter of rank 16
-    // 108 us with tiles and 85 without, 48 of two 238 and 187; 2048 wide, 64 of two of rank 8 101 and 80; 256 requests of four 524 and 880
-    const int launches = (n + lora::BATCH_MAX_PROJS - 1) / lora::BATCH_MAX_PROJS;
-    const double tiled = launches * (TILE_FIXED_US + (p->rest_groups > 0 ? TILE_BESIDE_GEMV_US : 0.0)) + p->rest_cost[wide(p->rest_wgs)].us(n, sum_width) + p->tile_cost.us(n, sum_width);
-    return tiled < (n > lora::GEMV_BATCH_MAX_PROJS ? 0.75 : 0.92) * gemv && tiled + TILED_LISTS_US < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
+    return p->has_tiled && list_takes_tiles(*p, n, n_groups, sum_width) ? &p->tiled : p;
 }
-// The same for the base product, which takes the tiles' term along: no expand launch, but a segment of rows costs its blocks 1.3 us for its Bp
-static const PlanLists *pick_linear_lists(lora_cache_t *c, lora_plan_t *p, double width, hipStream_t st)
+static const PlanLists *pick_linear_lists(const lora_cache_t *c, const lora_plan_t *p, double width)
 {
-    if (!p->may_tile) return p;
-    const double gemv = GEMV_FIXED_US + LINEAR_TERM_US + p->gemv_cost[p->n_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width);
-    const double rest = p->rest_groups > 0 ? GEMV_FIXED_US + p->rest_cost[p->rest_wgs >= GEMV_WIDE_MIN_ITEMS_ONE_GROUP].us(1, width) : 0.0;
-    const double segments = std::max(1.0, p->tile_segs * std::min(1.0, 256.0 / p->tile_tok));  // of a block
-    const double tiled = rest + LINEAR_SHRINK_US + 0.4 * p->tile_cost.us(1, width) + 1.3 * segments;
-    const double least = LINEAR_MIN_GAIN_US + LISTS_COST_US / (double)(c->n_layers * c->proj.size());
-    return tiled + least < gemv && tiled_lists(*c, *p, st) ? &p->tiled : p;
+    return p->has_tiled && product_takes_tiles(*c, *p, width) ? &p->tiled : p;
 }
 
 // Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of
@@ -2580,7 +2601,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     lora::ApplyArgs a;
     a.proj_base = bp.proj_base;
     a.row_bytes = (int64_t)c->row_bytes[proj];
-    const PlanLists *const q = pick_linear_lists(c, p, (double)bp.h_in + bp.h_out, st);
+    const PlanLists *const q = pick_linear_lists(c, p, (double)bp.h_in + bp.h_out);
     a.tok_list = reinterpret_cast<const int32_t *>(q->lists);
     a.x = x;
     a.y = y;
@@ -2692,7 +2713,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         int n_groups = 0;
         for (int k = 0; k < m; ++k) sum_width += (double)c->proj[descs[i + k].proj].h_in + c->proj[descs[i + k].proj].h_out;
         for (int k = 0; k < m; k += group_n[k]) ++n_groups;
-        const PlanLists *const q = pick_lists(c, p, m, n_groups, sum_width, st);
+        const PlanLists *const q = pick_lists(p, m, n_groups, sum_width);
         int32_t most = m, most_supers = INT32_MAX;
         if (q != p || (p->n_tiles == 0 && !gemv_long(c, q, descs + i, m))) batch_limits(q, scratch, false, most, most_supers);
         for (int at = 0; at < m;) {  // (a batch with tiles holds fewer projections, one of more kinds of projections than a long one tells apart too)

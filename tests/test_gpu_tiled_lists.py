@@ -1,5 +1,5 @@
-"""Plans whose calls for one projection leave everything to the GEMV kernels, in launches that take tiles: lists of many projections (more than a batch with tiles holds), the base
-product, and captures before any call has made the lists with tiles."""
+"""Plans whose calls for one projection leave everything to the GEMV kernels, in launches that take tiles: lists of many projections (more than a batch with tiles holds) and the base
+product, called and captured."""
 import numpy as np
 import pytest
 import torch
@@ -118,32 +118,43 @@ def test_base_product(lens, h_in, h_out):
 
 
 @pytest.mark.parametrize("first", ["capture", "eager"])
-def test_captured(first):
-    """A capture before any call takes the lists that are there, one behind an eager call those with tiles; every replay gives the same bits."""
-    c = Case(LENS[0], 512, 1024, 40)
+@pytest.mark.parametrize("call", ["list", "base product"])
+def test_captured(call, first):
+    """The same call gives the same bits, whether it is captured before any other, behind one, or not at all; every replay does."""
+    product = call == "base product"
+    c = Case([200, 90, 77], 2048, 1024, 8) if product else Case(LENS[0], 512, 1024, 40)
     try:
-        want = None
+        B, space = c.B, torch.empty(c.T * 1024, dtype=torch.float32, device="cuda")
+
+        def go(y):
+            stream = torch.cuda.current_stream().cuda_stream
+            if product:
+                B.check(B.lora_linear_plan(c.pool.handle, c.plan, 0, 0, c.x[0].data_ptr(), c.wt.data_ptr(), y.data_ptr(), 2.0, stream, space.data_ptr(), space.numel() * 4))
+            else:
+                c.apply_list(y, stream)
+
         y = c.base.clone()
+        eager = c.base.clone()
         if first == "eager":
-            c.apply_list(y)
-            want = y.clone()
+            go(eager)
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
-            c.apply_list(y, torch.cuda.current_stream().cuda_stream)
+            go(y)
         outs = []
         for i in range(4):
             y.copy_(c.base)
-            if i == 2:
-                c.apply_list(c.base.clone())  # eager work in between
+            if i == 2 and first == "capture":
+                go(eager)  # eager work in between
             graph.replay()
             torch.cuda.synchronize()
             outs.append(y.clone())
         c.pool.check_fault()
         for o in outs:
-            assert torch.equal(o, outs[0])
-        assert want is None or torch.equal(outs[0], want)
-        for layer in (0, 39):
-            c.check(outs[0][layer], layer, c.base[layer])
+            assert torch.equal(o, eager)
+        kinds = c.kernels(lambda: go(c.base.clone()))
+        assert ("mfma_shrink" in kinds) and (product or "mfma_expand" in kinds)  # the lists with tiles
+        for layer in () if product else (0, 39):
+            c.check(eager[layer], layer, c.base[layer])
     finally:
         c.pool.close()
