@@ -2402,6 +2402,30 @@ static const PlanLists *pick_linear_lists(const lora_cache_t *c, const lora_plan
     return p->has_tiled && product_takes_tiles(*c, *p, width) ? &p->tiled : p;
 }
 
+// What a call needs of other streams: the plan's lists and its slots' weights.  A captured call waits here, on the host: a wait on an event from outside the capture does not become
+// part of the graph, whose replays may run before that event.  (The event of a stream that is not the null stream can be asked about and waited for while this thread captures
+// only in relaxed mode; elsewhere the capture is invalidated.)
+static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st)
+{
+    int capturing = -1;  // not known yet
+    auto wait = [&](hipEvent_t ev, bool &pending) {
+        if (capturing < 0) capturing = is_capturing(st);
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return hipErrorStreamCaptureUnsupported;
+        hipError_t e = capturing ? hipEventSynchronize(ev) : hipEventQuery(ev);
+        if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e == hipSuccess) pending = false;
+        else e = hipStreamWaitEvent(st, ev, 0);
+        return e;
+    };
+    if (p->upload_pending) HIP_TRY(wait(p->ev_upload, p->upload_pending));
+    for (int32_t sl : p->slots) {
+        Slot &s = c->slots[sl];
+        if (s.fill_pending) HIP_TRY(wait(s.fill_ev, s.fill_pending));
+    }
+    return LORA_OK;
+}
+
 // Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of
 // them.  Entries that read the same x (a group, at most GROUP_MAX_PROJS) are neighbours; group_n[i] is the size of the group that
 // starts at entry i.  The tile shrink runs first, for all entries (x of a group is then fetched from memory once), each
@@ -2410,24 +2434,7 @@ static const PlanLists *pick_linear_lists(const lora_cache_t *c, const lora_plan
 static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, const lora_apply_desc_t *descs, const uint8_t *group_n, int n, float scale, hipStream_t st,
                          const Scratch &sc, hipEvent_t fence)
 {
-    // the work lists may have been uploaded on another stream
-    if (p->upload_pending) {
-        if (is_capturing(st)) {  // a wait on an event from outside the capture would not become part of the graph
-            HIP_TRY(hipEventSynchronize(p->ev_upload));
-            p->upload_pending = false;
-        } else if (hipEventQuery(p->ev_upload) == hipSuccess) {
-            p->upload_pending = false;
-        } else {
-            HIP_TRY(hipStreamWaitEvent(st, p->ev_upload, 0));
-        }
-    }
-    for (int32_t sl : p->slots) {
-        Slot &s = c->slots[sl];
-        if (s.fill_pending) {
-            if (hipEventQuery(s.fill_ev) == hipSuccess) s.fill_pending = false;
-            else HIP_TRY(hipStreamWaitEvent(st, s.fill_ev, 0));
-        }
-    }
+    if (const int rc = wait_for_inputs(c, p, st)) return rc;
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
     lora::TileBatch tb;
@@ -2587,14 +2594,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     if (p->T > 0 && (!Wt || !aligned16(Wt))) return LORA_E_INVAL;
     if (p->T == 0) return LORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (p->upload_pending) HIP_TRY(hipStreamWaitEvent(st, p->ev_upload, 0));
-    for (int32_t sl : p->slots) {
-        Slot &s = c->slots[sl];
-        if (s.fill_pending) {
-            if (hipEventQuery(s.fill_ev) == hipSuccess) s.fill_pending = false;
-            else HIP_TRY(hipStreamWaitEvent(st, s.fill_ev, 0));
-        }
-    }
+    if (const int rc_w = wait_for_inputs(c, p, st)) return rc_w;
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
     const lora::BatchProj bp = batch_proj(c, {layer, proj, x, y});

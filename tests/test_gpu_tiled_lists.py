@@ -158,3 +158,47 @@ def test_captured(call, first):
             c.check(eager[layer], layer, c.base[layer])
     finally:
         c.pool.close()
+
+
+@pytest.mark.parametrize("call", ["list", "base product"])
+def test_captured_behind_uploads_of_another_stream(call):
+    """A plan and a slot's weights that another stream still has before it when the call is captured: they are there for the replays, which nothing orders behind that stream."""
+    product = call == "base product"
+    c = Case([200, 90, 77], 2048, 1024, 8) if product else Case(LENS[0], 512, 1024, 40)
+    try:
+        B, space = c.B, torch.empty(c.T * 1024, dtype=torch.float32, device="cuda")
+        other, mine, graph = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+
+        def go(y, stream):
+            if product:
+                B.check(B.lora_linear_plan(c.pool.handle, c.plan, 0, 0, c.x[0].data_ptr(), c.wt.data_ptr(), y.data_ptr(), 2.0, stream, space.data_ptr(), space.numel() * 4))
+            else:
+                c.apply_list(y, stream)
+
+        y, busy = c.base.clone(), torch.randn(4096, 4096, device="cuda")
+        c.pool.plan_destroy(c.plan)
+        B.check(B.lora_cache_release_slot(c.pool.handle, 0))
+        c.A[0], c.Bm[0] = -c.A[0], c.Bm[0] * 2  # slot 0 is filled anew
+        a, b = c.A[0].cpu().pin_memory(), c.Bm[0].cpu().pin_memory()
+        parts = B.make_fill_parts([(layer, 0, a.data_ptr(), b.data_ptr()) for layer in range(c.n_layers)])
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            for _ in range(40):
+                busy @ busy
+            B.check(B.lora_cache_fill_slot_parts(c.pool.handle, 0, 99, int(c.rank_of[0]), 0.5, parts, other.cuda_stream))
+            c.plan = c.pool.plan(c.T, c.off, c.slot, c.rank_of[c.slot])
+            assert not other.query()
+        with torch.cuda.stream(mine):
+            graph.capture_begin(capture_error_mode="thread_local")
+            go(y, mine.cuda_stream)
+            graph.capture_end()
+            graph.replay()
+        torch.cuda.synchronize()
+        eager = c.base.clone()
+        go(eager, c.stream)
+        c.pool.check_fault()
+        assert torch.equal(y, eager)
+        for layer in () if product else range(c.n_layers):
+            c.check(y[layer], layer, c.base[layer])
+    finally:
+        c.pool.close()
