@@ -286,13 +286,15 @@ int lora_plan_create(lora_cache_t *c, int32_t T, const int32_t *seg_offsets, con
 int lora_plan_destroy(lora_cache_t *c, lora_plan_t *p);
 
 /* What a plan holds: the threshold its work lists were made with (lora_index with the same
- * arrays and this threshold returns the same lists; 0 = no tiles) and their sizes. */
+ * arrays and this threshold returns the same lists; 0 = no tiles) and their sizes.  These are the lists that a call for one
+ * projection works through.  With the threshold left to the library, a plan of a bf16 cache whose own lists have no tiles may hold others, made with the threshold
+ * LORA_MFMA_MIN_TOKENS_MIXED: lists and lora_linear_plan take them where they gain by it (lora_plan_dump_tiled shows them). */
 typedef struct {
     int32_t T, mfma_min_tokens, n_tiles, n_tile_tokens, n_gemv_shrink_items, n_gemv_expand_items;
 } lora_plan_info_t;
 int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out);
 
-/* For tests and tools: the units of work the kernels will execute for a plan on projection `proj`,
+/* For tests and tools: the units of work the kernels will execute for a plan on projection `proj` when they work through the plan's own lists,
  * decoded from the very buffer the kernels read (the device copy, fetched back with a blocking
  * copy; the staged host copy for a LORA_CACHE_HOST_ONLY cache) by the routines the kernels
  * themselves decode their work items with.  The slot/segment indexing is correct when:
@@ -311,30 +313,36 @@ int lora_plan_info(const lora_plan_t *p, lora_plan_info_t *out);
  * cover what the GEMV units cover, once.  The DIRECT_SHRINK units (up to 16 tokens of a tile x 16 rank rows over all input columns), if the plan
  * has any, are what a launch short enough works through in place of the pieces; they cover every token and rank row of every
  * tile once.  The PANEL_SHRINK units (up to 192 rows of a slot x up to three projections that read the same x) are what most longer launches work through: for a group
- * of 1 to 4 projections they cover every tile's tokens once per projection.  LINEAR_SHAPE says how lora_linear_plan cuts this projection's product into blocks.
+ * of 1 to 4 projections they cover every tile's tokens once per projection.  SHRINK_WAY says by which of the three a launch for 1 to 4 projections like this one
+ * that read the same x works.  LINEAR_SHAPE says how lora_linear_plan cuts this projection's product into blocks.
  * Writes at most cap_units units and cap_toks tokens; *n_units and *n_toks return the full counts
  * (call with zero capacities to size the arrays). */
 enum { LORA_UNIT_TILE = 0, LORA_UNIT_GEMV_SHRINK = 1, LORA_UNIT_GEMV_EXPAND = 2, LORA_UNIT_LINEAR_ROWS = 3, LORA_UNIT_TILE_SHRINK = 4, LORA_UNIT_TILE_SUM = 5,
        LORA_UNIT_BATCH_SHRINK = 6, LORA_UNIT_BATCH_EXPAND = 7, LORA_UNIT_WIDE_SHRINK = 8, LORA_UNIT_WIDE_EXPAND = 9,
-       LORA_UNIT_DIRECT_SHRINK = 10, LORA_UNIT_LINEAR_SHAPE = 11, LORA_UNIT_PANEL_SHRINK = 12 };
+       LORA_UNIT_DIRECT_SHRINK = 10, LORA_UNIT_LINEAR_SHAPE = 11, LORA_UNIT_PANEL_SHRINK = 12, LORA_UNIT_SHRINK_WAY = 13 };
 typedef struct {
     int32_t kind;
     int32_t tok_off, n_tok; /* the unit's tokens: toks[tok_off .. tok_off + n_tok) */
     int32_t slot, rank;     /* slot found back from the storage row the kernels address; -1, 0: rows without adapter */
     int32_t lo, hi;         /* *_SHRINK: rank rows [lo, hi); *_EXPAND: output columns [lo, hi); TILE_SHRINK: input
                                columns [lo, hi); TILE_SUM: slot number lo of hi; LINEAR_SHAPE: rows of a tile (64, 128: x 64 columns,
-                               192, 256, 288: x 256), tiles; PANEL_SHRINK: projections [lo, hi) of the group; else 0, 0 */
+                               192, 256, 288: x 256), tiles; PANEL_SHRINK: projections [lo, hi) of the group; SHRINK_WAY: 0 by
+                               the DIRECT_SHRINK units, 1 by a run table, 2 by panels, and into how many slices of the input columns these go; else 0, 0 */
     int32_t where;          /* GEMV_SHRINK: position in launch order; LINEAR_ROWS: 2 = a tile, 1 = rows of GEMV tokens,
                                0 = rows without adapter; TILE_SHRINK, TILE_SUM: run table << 20 | run (run tables 0..3:
                                launches for 1..4 projections; 4: the one of lora_apply_plan_static; 5, 6: those with at most 64 and
                                32 runs per projection, for batches of more than 4); BATCH_*, WIDE_*: the batch's entry, layer *
                                n_proj + proj; DIRECT_SHRINK: 1 if a call for this projection alone works through them; LINEAR_SHAPE: tiles split
-                               along the input columns << 8 | parts of each; PANEL_SHRINK: projections of the group; TILE: 0 */
+                               along the input columns << 8 | parts of each; PANEL_SHRINK, SHRINK_WAY: projections of the group; TILE: 0 */
     float alpha;            /* the cache entry's own factor as the kernels will apply it; TILE_SHRINK, TILE_SUM: the
                                scratch slot of the partial sum (-1: the piece is the whole tile and leaves none); LINEAR_SHAPE: stages of a ring */
 } lora_plan_unit_t;
 int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units,
                    int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks);
+/* The same for the lists with tiles that a plan holds besides its own (no units if it holds none); they come without run tables: launches shrink by
+ * DIRECT_SHRINK units or by panels. */
+int lora_plan_dump_tiled(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units,
+                         int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks);
 
 /* base_out[t] += scale*alpha*(x[t].A).B for the planned batch; x [T][h_in] and base_out
  * [T][h_out] are device, row-major, contiguous, element type cfg.dtype.  Asynchronous on

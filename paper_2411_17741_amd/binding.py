@@ -90,7 +90,7 @@ class lora_worklists_t(ctypes.Structure):
 
 LORA_UNIT_TILE, LORA_UNIT_GEMV_SHRINK, LORA_UNIT_GEMV_EXPAND, LORA_UNIT_LINEAR_ROWS, LORA_UNIT_TILE_SHRINK, LORA_UNIT_TILE_SUM = 0, 1, 2, 3, 4, 5
 LORA_UNIT_BATCH_SHRINK, LORA_UNIT_BATCH_EXPAND, LORA_UNIT_WIDE_SHRINK, LORA_UNIT_WIDE_EXPAND = 6, 7, 8, 9
-LORA_UNIT_DIRECT_SHRINK, LORA_UNIT_LINEAR_SHAPE, LORA_UNIT_PANEL_SHRINK = 10, 11, 12
+LORA_UNIT_DIRECT_SHRINK, LORA_UNIT_LINEAR_SHAPE, LORA_UNIT_PANEL_SHRINK, LORA_UNIT_SHRINK_WAY = 10, 11, 12, 13
 
 
 class lora_plan_unit_t(ctypes.Structure):
@@ -134,6 +134,7 @@ _SIGS = {
     "lora_plan_destroy": (c_int, [c_void_p, c_void_p]),
     "lora_plan_info": (c_int, [c_void_p, POINTER(lora_plan_info_t)]),
     "lora_plan_dump": (c_int, [c_void_p, c_void_p, c_int32, POINTER(lora_plan_unit_t), c_int32, _i32p, _i32a, c_int32, _i32p]),
+    "lora_plan_dump_tiled": (c_int, [c_void_p, c_void_p, c_int32, POINTER(lora_plan_unit_t), c_int32, _i32p, _i32a, c_int32, _i32p]),
     "lora_apply_plan": (c_int, [c_void_p, c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_float, c_void_p]),
     "lora_apply_plan_static": (c_int, [c_void_p, c_void_p, c_int32, c_int32, c_void_p, c_void_p, c_float, c_void_p]),
     "lora_apply_plan_multi": (c_int, [c_void_p, c_void_p, POINTER(lora_apply_desc_t), c_int32, c_float, c_void_p]),
@@ -462,13 +463,22 @@ def lora_plan_info(plan):
 
 def lora_plan_dump(cache, plan, proj: int):
     """-> (status, units as a numpy record array with the fields of lora_plan_unit_t, tokens as an int32 array)"""
+    return _dump(_lib.lora_plan_dump, cache, plan, proj)
+
+
+def lora_plan_dump_tiled(cache, plan, proj: int):
+    """The same of the lists with tiles that a plan may hold besides its own."""
+    return _dump(_lib.lora_plan_dump_tiled, cache, plan, proj)
+
+
+def _dump(dump, cache, plan, proj):
     nu, nt = c_int32(0), c_int32(0)
-    rc = _lib.lora_plan_dump(cache, plan, proj, None, 0, ctypes.byref(nu), None, 0, ctypes.byref(nt))
+    rc = dump(cache, plan, proj, None, 0, ctypes.byref(nu), None, 0, ctypes.byref(nt))
     if rc != LORA_OK:
         return rc, None, None
     units = (lora_plan_unit_t * max(1, nu.value))()
     toks = np.zeros(max(1, nt.value), np.int32)
-    rc = _lib.lora_plan_dump(cache, plan, proj, units, nu.value, ctypes.byref(nu), _ptr(toks), nt.value, ctypes.byref(nt))
+    rc = dump(cache, plan, proj, units, nu.value, ctypes.byref(nu), _ptr(toks), nt.value, ctypes.byref(nt))
     if rc != LORA_OK:
         return rc, None, None
     rec = np.frombuffer(units, dtype=np.dtype([(n, np.int32) for n in ("kind", "tok_off", "n_tok", "slot", "rank", "lo", "hi", "where")] + [("alpha", np.float32)]), count=nu.value).copy()

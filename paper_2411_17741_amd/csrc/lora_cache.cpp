@@ -1894,19 +1894,29 @@ static void batch_limits(const PlanLists *p, const Scratch &sc, bool long_batch,
     max_supers = (int32_t)supers;
 }
 
-int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units,
-                   int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks)
+static int tile_setup(const lora_cache_t *c, const PlanLists *p, int n, int64_t sum_h_in, const Scratch &sc, float scale, lora::TileBatch &tb);
+static void choose_panels(const lora_cache_t *c, const PlanLists *p, const Scratch &sc, lora::TileBatch &tb);
+
+// The units of a plan's own lists, or of those with tiles that it has besides
+static int dump_units(lora_cache_t *c, const lora_plan_t *plan, bool tiled, int32_t proj, lora_plan_unit_t *units, int32_t cap_units, int32_t *n_units, int32_t *toks, int32_t cap_toks,
+                      int32_t *n_toks)
 {
-    if (!c || !p || !p->in_use || !n_units || !n_toks || proj < 0 || proj >= (int32_t)c->proj.size() || cap_units < 0 ||
+    if (!c || !plan || !plan->in_use || !n_units || !n_toks || proj < 0 || proj >= (int32_t)c->proj.size() || cap_units < 0 ||
         cap_toks < 0 || (cap_units > 0 && !units) || (cap_toks > 0 && !toks))
         return LORA_E_INVAL;
+    if (tiled && !plan->has_tiled) {
+        *n_units = *n_toks = 0;
+        return LORA_OK;
+    }
+    const PlanLists *const p = tiled ? &plan->tiled : plan;
+    const size_t at = tiled ? plan->bytes : 0, bytes = tiled ? plan->tiled_bytes : plan->bytes;
     // the bytes the kernels read
     std::vector<char> copy;
-    const char *buf = p->pinned;
+    const char *buf = plan->pinned + at;
     if (!c->host_only) {
-        copy.resize(p->bytes);
-        if (p->upload_pending) HIP_TRY(hipEventSynchronize(p->ev_upload));
-        if (p->bytes) HIP_TRY(hipMemcpy(copy.data(), p->dev, p->bytes, hipMemcpyDeviceToHost));
+        copy.resize(bytes);
+        if (plan->upload_pending) HIP_TRY(hipEventSynchronize(plan->ev_upload));
+        if (bytes) HIP_TRY(hipMemcpy(copy.data(), plan->dev + at, bytes, hipMemcpyDeviceToHost));
         buf = copy.data();
     }
     const int32_t *tok_list = reinterpret_cast<const int32_t *>(buf);
@@ -1959,6 +1969,15 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
             tile_tokens(panels[panel], tok_list);
             put_unit(LORA_UNIT_PANEL_SHRINK, off, panels[panel].n_tok, panels[panel].row, panels[panel].rank, first, first + n, gn, panels[panel].alpha);
         }
+    // how a launch for 1 to 4 such projections that read the same x does the shrink
+    for (int gn = 1; gn <= lora::GROUP_MAX_PROJS && p->n_tiles > 0; ++gn) {
+        lora::TileBatch tb;
+        const Scratch sc = pool_scratch(c);
+        if (tile_setup(c, p, gn, (int64_t)gn * c->proj[proj].h_in, sc, 1.f, tb) != LORA_OK) continue;
+        for (int i = 0; i < gn; ++i) tb.p[i].h_in = c->proj[proj].h_in, tb.group[i] = (uint32_t)gn << 8;
+        choose_panels(c, p, sc, tb);
+        put_unit(LORA_UNIT_SHRINK_WAY, nt, 0, -1, 0, tb.n_direct > 0 ? 0 : tb.n_panels > 0 ? 2 : 1, tb.n_panels > 0 ? tb.slices[0] : 1, gn, 0.f);
+    }
     // the tile shrink's pieces for this projection's h_in, per run table, walked as the kernel walks them; and the
     // scratch slots the reduce adds up per tile
     for (int v = 0; v < SHRINK_VARIANTS && p->n_tiles > 0; ++v) {
@@ -2104,6 +2123,16 @@ int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_pla
     *n_units = nu;
     *n_toks = nt;
     return LORA_OK;
+}
+
+int lora_plan_dump(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units, int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks)
+{
+    return dump_units(c, p, false, proj, units, cap_units, n_units, toks, cap_toks, n_toks);
+}
+
+int lora_plan_dump_tiled(lora_cache_t *c, const lora_plan_t *p, int32_t proj, lora_plan_unit_t *units, int32_t cap_units, int32_t *n_units, int32_t *toks, int32_t cap_toks, int32_t *n_toks)
+{
+    return dump_units(c, p, true, proj, units, cap_units, n_units, toks, cap_toks, n_toks);
 }
 
 static int validate_apply(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t proj, const void *x, void *base_out)

@@ -13,7 +13,10 @@ oracle's `token_map` says (which slot, which rank) and cover the work once:
   the same holds for the units of a list call's batch, entry by entry, with the items and with the wide items;
 * units of a short tile shrink: every (tile token, rank row) once, in units of at most 16 x 16, and they are marked as what a call works
   through exactly where it takes in no more than 225 MB that way;
+* units of a shrink by panels: per number of projections that share it, every tile's tokens once per projection;
 * row units of the fused linear path: every token of the batch exactly once.
+
+The same holds for the lists with tiles that a plan holds besides its own (`lora_plan_dump_tiled`, threshold 8), which have no run tables.
 """
 from __future__ import annotations
 
@@ -23,10 +26,13 @@ import oracle
 from paper_2411_17741_amd import binding as B
 
 
-def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alpha_of_slot, bf16=True):
-    """projs: [(h_in, h_out)]; alpha_of_slot: dict slot -> alpha.  Returns a dict of counts."""
+def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alpha_of_slot, bf16=True, tiled=False):
+    """projs: [(h_in, h_out)]; alpha_of_slot: dict slot -> alpha; tiled: of the lists with tiles besides the plan's own.  Returns a dict of counts."""
     rc, info = B.lora_plan_info(plan)
     assert rc == B.LORA_OK
+    if tiled:
+        assert info.n_tiles == 0
+        info.mfma_min_tokens = B.LORA_MFMA_MIN_TOKENS_MIXED
     tm_slot, tm_rank = (np.asarray(v, np.int64) for v in oracle.token_map(T, seg_offsets, seg_slot, seg_rank))
     want = oracle.index(T, seg_offsets, seg_slot, seg_rank, info.mfma_min_tokens)
     want_tile_toks = [want["tok_list"][o : o + n] for (o, n, *_r) in want["tiles"]]
@@ -34,7 +40,7 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
     gemv_pos = {t: i for i, t in enumerate(want_gemv)}
     counts = {}
     for p, (h_in, h_out) in enumerate(projs):
-        rc, units, toks = B.lora_plan_dump(cache, plan, p)
+        rc, units, toks = (B.lora_plan_dump_tiled if tiled else B.lora_plan_dump)(cache, plan, p)
         assert rc == B.LORA_OK
         assert (units["tok_off"] >= 0).all() and (units["tok_off"] + units["n_tok"] <= len(toks)).all()
         assert ((toks >= 0) & (toks < T)).all()
@@ -48,7 +54,7 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
 
         # --- tiles: the oracle's, in order
         tiles = units[units["kind"] == B.LORA_UNIT_TILE]
-        assert len(tiles) == len(want["tiles"]) == info.n_tiles
+        assert len(tiles) == len(want["tiles"]) and (len(tiles) > 0 if tiled else len(tiles) == info.n_tiles)
         for u, wt, (_, _, slot, rank, _, _) in zip(tiles, want_tile_toks, want["tiles"]):
             assert list(toks_of(u)) == wt and (u["slot"], u["rank"]) == (slot, rank)
             assert 1 <= u["n_tok"] <= B.LORA_TILE_TOKENS
@@ -73,6 +79,21 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
             n = sum(-(-len(tk) // 16) * -(-int(r) // 16) for tk, (_o, _n, _s, r, _t, _l) in zip(want_tile_toks, want["tiles"]))
             assert n > 2048 or n * 64 * min(i for i, _o in projs) > 225000000
 
+        # --- shrink by panels: every tile token once per projection of a group of 1 to 4
+        panels = units[units["kind"] == B.LORA_UNIT_PANEL_SHRINK]
+        ways = units[units["kind"] == B.LORA_UNIT_SHRINK_WAY]
+        assert list(ways["where"]) == ([1, 2, 3, 4] if len(tiles) else [])
+        assert ((ways["lo"] == 0) == np.asarray([bool(len(direct)) and len(direct) * 64 * h_in * n <= 225000000 for n in ways["where"]])).all()
+        assert len(panels) > 0 or not (ways["lo"] == 2).any()
+        assert not (tiled and (ways["lo"] == 1).any())
+        for gn in range(1, 5) if len(panels) else ():
+            cover = np.zeros((gn, T), np.int32)
+            for u in panels[panels["where"] == gn]:
+                same_entry(u)
+                assert u["n_tok"] <= 192 and 0 <= u["lo"] < u["hi"] <= gn
+                cover[u["lo"] : u["hi"], toks_of(u)] += 1
+            assert cover.sum() == gn * sum(len(tk) for tk in want_tile_toks) and (cover[:, [t for tk in want_tile_toks for t in tk]] == 1).all()
+
         # --- tile shrink: under every run table the pieces of a tile cover its input columns [0, h_in) once, in pieces
         # of whole 128-column stages; runs are walked in order, each at most a tail, whole tiles and a head; pieces that
         # are not whole tiles leave partial sums in slots of their own, and the reduce adds up exactly those
@@ -82,7 +103,7 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
         for table in range(7):
             pc = pieces[(pieces["where"] >> 20) == table]
             sm = sums[(sums["where"] >> 20) == table]
-            if len(tiles) == 0 or (table == 4 and T > B.LORA_STATIC_MAX_TOKENS):  # (no table for what the call refuses)
+            if len(tiles) == 0 or tiled or (table == 4 and T > B.LORA_STATIC_MAX_TOKENS):  # (no table for what the call refuses)
                 assert len(pc) == 0 and len(sm) == 0
                 continue
             runs = pc["where"] & 0xFFFFF

@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from plan_checks import check_plan_units
+
 pytestmark = pytest.mark.gpu
 RANKS = [16, 100, 5, 64]
 
@@ -68,6 +70,8 @@ def test_lists(lens, n_layers):
         y = c.base.clone()
         kinds = c.kernels(lambda: c.apply_list(y))
         assert "mfma_expand" in kinds
+        # what the kernels read, as the device holds it
+        check_plan_units(c.pool.handle, c.plan, c.T, c.off, c.slot, c.rank_of[c.slot], [c.shape], {s: 0.5 + s / 4 for s in range(16)}, tiled=True)
         for layer in range(n_layers):
             c.check(y[layer], layer, c.base[layer])
         again = c.base.clone()
