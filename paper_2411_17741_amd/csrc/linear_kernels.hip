@@ -906,8 +906,9 @@ static double rounds_us(int rows, int n_tiles, double n_k, int n_cu)
 // 192, of 288): 4300 x 4096 x 4096 125 / 137 / 103 (272 tiles; 368; 240), 4416 132 / 136 / 108, 5809 155 / 151 / 184, 3000 80 / 77 / 87, 3500 x 2560 x 2560 49 / 44 / 53,
 // 2560 x 13824 x 5120 273 / 286 / 257, 3000 x 11008 x 4096 219 / 223 / 204; not chosen: 2048 x 4096 x 4096 63 / 65 / 79, 2560 x 5120 x 5120 107 / 163 / 115, 1600 x 4096 x 4096
 // 57 / 61 / 76; 160 and 224 rows were the best nowhere (2560 x 5120 x 5120: 168, 105).  The estimate is within 8 % of these, hence the 5 % it has to gain.
-// Products of less than 36 stages (h_in below 2304) keep the shapes they had: the tests name them.
-constexpr int TALL_MIN_STAGES = 36;
+// Few stages are no exception: of 150 drawn products (500 to 9000 rows, 768 to 11500 columns) 90 of 12 to 35 stages take 1.092 times less in the geometric mean than with tiles of 256 alone (the best of the
+// three each time 1.095), 60 of 3 to 11 stages 1.049 (1.070), and none that left 256 got slower: 4396 x 2112 x 4096 82.7 / 78.2 / 61.7, 5082 x 1024 x 3584 56.4 / 48.8 / 37.3, 4527 x 1536 x 2496 39.2 / 35.1 / 41.8,
+// 7095 x 576 x 2368 43.3 / 35.6 / 27.5.
 
 template <int RM, int NST> constexpr int small_lds = NST * 64 * (RM + 1) * LROW;
 
@@ -948,13 +949,11 @@ LinearShape linear_shape(int n_rows, int h_in, int h_out, size_t split_scratch_b
     if (t64 <= big && t64 <= t128) return {64, tiles64 * p64 <= 2 * n_cu ? 4 : 3, tiles64, p64 > 1 ? tiles64 : 0, p64};
     if (t128 <= big) return {128, 3, tiles128, 0, 1};
     if (n_tail > n_split_state) parts = 1, n_tail = 0;
-    if (n_k >= TALL_MIN_STAGES) {
-        const int n_nt = (h_out + LBN - 1) / LBN, whole = n_tiles - n_tail;
-        const double now = rounds_us(256, whole, n_k, n_cu) + (parts > 1 ? rounds_us(256, n_tail * parts, (double)n_k / parts, n_cu) + 4.0 + 0.06 * n_tail * (parts - 1) : 0.0);
-        const int tiles192 = (n_rows + 191) / 192 * n_nt, tiles288 = (n_rows + 287) / 288 * n_nt;
-        const double t192 = rounds_us(192, tiles192, n_k, n_cu), t288 = rounds_us(288, tiles288, n_k, n_cu);
-        if (std::min(t192, t288) < 0.95 * now) return t192 < t288 ? LinearShape{192, 2, tiles192, 0, 1} : LinearShape{288, 2, tiles288, 0, 1};
-    }
+    const int n_nt = (h_out + LBN - 1) / LBN, whole = n_tiles - n_tail;
+    const double now = rounds_us(256, whole, n_k, n_cu) + (parts > 1 ? rounds_us(256, n_tail * parts, (double)n_k / parts, n_cu) + 4.0 + 0.06 * n_tail * (parts - 1) : 0.0);
+    const int tiles192 = (n_rows + 191) / 192 * n_nt, tiles288 = (n_rows + 287) / 288 * n_nt;
+    const double t192 = rounds_us(192, tiles192, n_k, n_cu), t288 = rounds_us(288, tiles288, n_k, n_cu);
+    if (std::min(t192, t288) < 0.95 * now) return t192 < t288 ? LinearShape{192, 2, tiles192, 0, 1} : LinearShape{288, 2, tiles288, 0, 1};
     return {LBM, 2, n_tiles, n_tail, parts};
 }
 
