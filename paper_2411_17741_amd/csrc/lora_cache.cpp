@@ -905,7 +905,9 @@ size_t ListBuild::size(const lora_cache &c, PlanLists &p, bool internal, bool ta
         p.off_sums[v] = bytes;
         bytes += align_up(sizeof(lora::ShrinkSum) * shrink_runs[v].sums.size());
     }
-    if (bytes + align_up(sizeof(lora::DevItem) * panels.size()) > room) panels.clear();  // (the plan does without)
+    // (A plan's own lists have room for them: compute_layout counts 48 GEMV items for every fourth token, tokens in tiles make none, and there are no more panels than tiles.
+    // Lists with tiles besides the plan's own may find none behind it; the plan then does without them.)
+    if (bytes + align_up(sizeof(lora::DevItem) * panels.size()) > room) panels.clear();
     p.off_panels = bytes;
     p.n_panels = (int32_t)panels.size();
     return bytes + align_up(sizeof(lora::DevItem) * panels.size());

@@ -84,7 +84,7 @@ def check_plan_units(cache, plan, T, seg_offsets, seg_slot, seg_rank, projs, alp
         ways = units[units["kind"] == B.LORA_UNIT_SHRINK_WAY]
         assert list(ways["where"]) == ([1, 2, 3, 4] if len(tiles) else [])
         assert ((ways["lo"] == 0) == np.asarray([bool(len(direct)) and len(direct) * 64 * h_in * n <= 225000000 for n in ways["where"]])).all()
-        assert len(panels) > 0 or not (ways["lo"] == 2).any()
+        assert (len(panels) > 0) == (len(tiles) > 0)  # (a plan has room for them whatever its batch)
         assert not (tiled and (ways["lo"] == 1).any())
         for gn in range(1, 5) if len(panels) else ():
             cover = np.zeros((gn, T), np.int32)

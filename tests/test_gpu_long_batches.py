@@ -22,6 +22,11 @@ CASES = {  # projections, layers, requests per slot, ranks
     "requests for fewer sets": (SEVEN, 32, [120, 150, 80], [16, 8, 32]),
 }
 
+# GEMV launches of a list: those of more than 224 entries or 1536 super-chunks take another, those of nine kinds run in batches of 120, and so do those of tokens for which there
+# are no more sets; a list of 225 leaves one entry over
+LAUNCHES = {case: 1 for case in CASES}
+LAUNCHES |= {"225 entries": 2, "231 entries": 2, "more super-chunks than a launch": 2, "requests for fewer sets": 2, "nine kinds": 3}
+
 
 def _setup(case, dtype, flags):
     from paper_2411_17741_amd import binding as B
@@ -62,16 +67,17 @@ def _check(got, want, dtype):
         assert bool((err <= rel * w.abs() + floor * rms).all()), f"entry {k}: {float((err / rms).max())}"
 
 
-@pytest.mark.parametrize("dtype,flags", [("bf16", "auto"), ("bf16", "split"), ("f32", "auto")])
-@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("dtype,flags,case", [(d, "auto", c) for d in ("bf16", "f32") for c in CASES] + [("bf16", "split", c) for c in ("224 entries", "wide items")])
 def test_lists_against_single_calls(case, dtype, flags):
-    if flags == "split" and case not in ("224 entries", "wide items"):
-        pytest.skip("two launches: one case of either kind of items")
     B, pool, plan, descs, _base, want, y, _xs = _setup(case, dtype, flags)
     try:
+        B.lora_cache_set_timing(pool.handle, 1)
         B.check(B.lora_apply_plan_multi(pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
         torch.cuda.synchronize()
         pool.check_fault()
+        rc, t = B.lora_cache_read_timing(pool.handle)
+        assert rc == B.LORA_OK
+        assert {k: n for k, (_ms, n) in t.items() if n} == {k: LAUNCHES[case] for k in (["gemv_shrink", "gemv_expand"] if flags == "split" else ["gemv_fused"])}
         _check(y, want, dtype)
     finally:
         pool.close()

@@ -206,3 +206,58 @@ def test_captured_behind_uploads_of_another_stream(call):
             c.check(y[layer], layer, c.base[layer])
     finally:
         c.pool.close()
+
+
+@pytest.mark.parametrize("first", ["list", "base product"])
+def test_calls_on_a_second_stream(first):
+    """The lists' upload is behind work of the stream that made the plan; a call on another stream waits for it."""
+    c = Case([200, 90, 77], 2048, 1024, 8)
+    try:
+        B, space = c.B, torch.empty(c.T * 1024, dtype=torch.float32, device="cuda")
+
+        def product(y, stream):
+            B.check(B.lora_linear_plan(c.pool.handle, c.plan, 0, 0, c.x[0].data_ptr(), c.wt.data_ptr(), y.data_ptr(), 2.0, stream, space.data_ptr(), space.numel() * 4))
+
+        go = (lambda y, s: c.apply_list(y, s)) if first == "list" else product
+        want = c.base.clone()
+        go(want, c.stream)
+        kinds = c.kernels(lambda: go(c.base.clone(), c.stream))
+        assert "mfma_shrink" in kinds
+        y, busy = c.base.clone(), torch.randn(4096, 4096, device="cuda")
+        c.pool.plan_destroy(c.plan)
+        other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(other):
+            for _ in range(40):
+                busy @ busy
+            c.plan = c.pool.plan(c.T, c.off, c.slot, c.rank_of[c.slot])
+            assert not other.query()
+        go(y, mine.cuda_stream)
+        torch.cuda.synchronize()
+        c.pool.check_fault()
+        assert torch.equal(y, want)
+    finally:
+        c.pool.close()
+
+
+@pytest.mark.parametrize("short", [1, 8, 30])
+def test_a_pool_of_fewer_bytes(short, monkeypatch):
+    """A byte short, and 8 and 30 of 44 sets (1 KB a token each): lists run in smaller batches, with tiles where a batch still gains by them (14 entries do not)."""
+    from paper_2411_17741_amd import binding as B0
+
+    required = B0.lora_cache_bytes_required
+    monkeypatch.setattr(B0, "lora_cache_bytes_required", lambda cfg: required(cfg) - (1 if short == 1 else short * 1024 * cfg.max_tokens))
+    c = Case(LENS[0], 512, 1024, 40)
+    try:
+        y = c.base.clone()
+        c.B.lora_cache_set_timing(c.pool.handle, 1)
+        c.apply_list(y)
+        torch.cuda.synchronize()
+        c.pool.check_fault()
+        rc, t = c.B.lora_cache_read_timing(c.pool.handle)
+        expands, gemv = t["mfma_expand"][1], t["gemv_fused"][1]
+        assert rc == c.B.LORA_OK and (expands, gemv > 1) == {1: (1, False), 8: (1, True), 30: (0, True)}[short], t
+        for layer in range(c.n_layers):
+            c.check(y[layer], layer, c.base[layer])
+    finally:
+        c.pool.close()

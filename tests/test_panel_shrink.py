@@ -54,7 +54,7 @@ def test_every_row_once_per_projection(lens):
 @pytest.mark.parametrize("h_in", [64, 320, 1088, 2560, 8256])
 @pytest.mark.parametrize("lens", [
     [2000, 1201, 833, 400, 385, 1409, 1, 1, 1] * 2 + [9, 24] * 3,  # panels of 129 to 192 rows; pools of one-token requests beside them
-    [193, 65, 64, 63, 129, 1, 577, 192, 128, 191] * 12,        # every number of runs of 64, full, one more, one less; gathered panels
+    [193, 65, 64, 63, 129, 1, 577, 192, 128, 191] * 12,        # pools of several segments; gathered panels
     [1] * 3000 + [300] * 30,                                   # gathered panels of many requests
 ])
 def test_against_torch(lens, h_in):
@@ -96,5 +96,100 @@ def test_against_torch(lens, h_in):
                 assert bool(((y[p].double() - ref).abs() <= 1.125 * 2.0**-8 * (ref.abs() + rounding)).all()), (p, list(entries))
             for p in set(range(n)) - set(entries):
                 assert torch.equal(y[p], base[p])
+    finally:
+        pool.close()
+
+
+# Crossed: a slot for every length and rank.  A block's body is one of (runs of 64 rows, rank blocks, projections), in one slice or in several
+CROSS_RANKS = RANKS + [32, 80]
+CROSS = [  # lengths, width, more than one slice
+    ([9, 63, 64, 65, 100, 128, 129, 191, 192], 64, False),
+    ([9, 63, 64, 65, 100, 128, 129, 191, 192], 320, False),
+    ([9, 63, 65, 129, 191], 2560, True),
+    ([64, 128, 192], 4160, True),
+    ([33, 100, 177], 8256, True),
+]
+
+
+def _crossed(lens):
+    pairs = [(n, r) for n in lens for r in CROSS_RANKS]
+    order = np.random.default_rng(len(lens)).permutation(len(pairs))
+    off = np.concatenate([[0], np.cumsum([pairs[i][0] for i in order])]).astype(np.int32)
+    return off, order.astype(np.int32), np.asarray([r for _n, r in pairs], np.int32)
+
+
+def _check_bodies(handle, plan, sliced):
+    """Launches for 1 to 4 projections that read the same x run by panels, and between them reach every body."""
+    rc, units, _toks = B.lora_plan_dump(handle, plan, 0)
+    assert rc == B.LORA_OK
+    ways = units[units["kind"] == B.LORA_UNIT_SHRINK_WAY]
+    assert list(ways["where"]) == [1, 2, 3, 4]
+    reached = set()
+    for w in ways:
+        if w["lo"] == 2 and (w["hi"] > 1) == sliced:
+            for u in units[(units["kind"] == B.LORA_UNIT_PANEL_SHRINK) & (units["where"] == w["where"])]:
+                reached.add((-(-int(u["n_tok"]) // 64), next(n for n in (1, 2, 4, 6, 8) if 16 * n >= u["rank"]), int(u["hi"] - u["lo"])))
+    every = {(runs, nb, n) for runs in (1, 2, 3) for nb in (1, 2, 4, 6, 8) for n in range(1, min(3, (416 - 64 * runs) // (16 * nb)) + 1)}
+    assert reached == every, every - reached
+
+
+@pytest.mark.parametrize("lens,h_in,sliced", CROSS)
+def test_every_body_is_reached(lens, h_in, sliced):
+    off, slot, ranks = _crossed(lens)
+    cfg = B.make_config([(h_in, 64)] * 4, 1, [128], [len(ranks)], B.LORA_BF16, int(off[-1]), len(slot), mfma_min_tokens=8, flags=B.LORA_CACHE_HOST_ONLY)
+    rc, h = B.lora_cache_create(cfg, 0, 0)
+    assert rc == B.LORA_OK
+    for s, r in enumerate(ranks):
+        assert all(B.lora_cache_fill_slot(h, s, s + 1, int(r), 1.0, 0, p, 0, 0) == B.LORA_OK for p in range(4))
+    rc, plan = B.lora_plan_create(h, int(off[-1]), off, slot, ranks[slot])
+    assert rc == B.LORA_OK
+    _check_bodies(h, plan, sliced)  # (of 256 compute units)
+    assert B.lora_plan_destroy(h, plan) == B.LORA_OK and B.lora_cache_destroy(h) == B.LORA_OK
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,h_in,sliced", CROSS)
+def test_every_body_against_torch(lens, h_in, sliced):
+    from paper_2411_17741_amd.pool import LoraPool
+
+    off, slot, ranks = _crossed(lens)
+    T, h_out, n = int(off[-1]), 64, len(ranks)
+    gen = torch.Generator(device="cuda").manual_seed(h_in)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    x = normal(T, h_in)
+    A = [[normal(h_in, r, sigma=0.02) for r in CROSS_RANKS] for _ in range(4)]
+    Bm = [normal(r, h_out, sigma=0.02) for r in CROSS_RANKS]
+    host_a, host_b = [[a.cpu().pin_memory() for a in row] for row in A], [b.cpu().pin_memory() for b in Bm]
+    make = lambda: LoraPool([(h_in, h_out)] * 4, 1, [128], [n], B.LORA_BF16, max_tokens=T, max_segments=n, mfma_min_tokens=8)
+    pool = make()
+    try:
+        pool.buf.fill_(0xFF)  # NaN in every word that is not written: the next pool takes the same memory
+        pool.close()
+        pool = make()
+        stream = torch.cuda.current_stream().cuda_stream
+        for s in range(n):
+            k = s % len(CROSS_RANKS)
+            parts = B.make_fill_parts([(0, p, host_a[p][k].data_ptr(), host_b[k].data_ptr()) for p in range(4)])
+            B.check(B.lora_cache_fill_slot_parts(pool.handle, s, s + 1, int(ranks[s]), 0.5 + s / 64, parts, stream))
+        plan = pool.plan(T, off, slot, ranks[slot])
+        if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+            _check_bodies(pool.handle, plan, sliced)
+        base = normal(4, T, h_out)
+        slot_of_token = torch.as_tensor(np.repeat(slot, np.diff(off)), device="cuda")
+        factor = 2.0 * (0.5 + slot_of_token.double() / 64)
+        ref, rounding = base.double(), torch.zeros(4, T, h_out, dtype=torch.float64, device="cuda")
+        for p in range(4):
+            for k in range(len(CROSS_RANKS)):
+                at = slot_of_token % len(CROSS_RANKS) == k
+                v = factor[at, None] * (x[at].double() @ A[p][k].double())
+                ref[p, at] += v @ Bm[k].double()
+                rounding[p, at] = v.abs() @ Bm[k].double().abs()
+        for gn in range(1, 5):
+            y = base.clone()
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, B.make_descs([(0, p, x.data_ptr(), y[p].data_ptr()) for p in range(gn)]), 2.0, stream))
+            pool.check_fault()
+            # the rounding of the output (2^-8 of its value) and that of every entry of s.v (2^-8 of its term); an eighth more for the sums in fp32
+            assert bool(((y[:gn].double() - ref[:gn]).abs() <= 1.125 * 2.0**-8 * (ref[:gn].abs() + rounding[:gn])).all()), gn
+            assert torch.equal(y[gn:], base[gn:])
     finally:
         pool.close()
