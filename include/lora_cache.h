@@ -375,7 +375,8 @@ int lora_apply_plan_static(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32
  * through the binding), up to rounding: the fp32 sums of a tile's shrink are cut in other places when several
  * projections share a launch, and the bf16 intermediate then rounds the other way once in a while.  The same list
  * with the same plan gives the same bits every time, captured or not.  Consecutive entries that do not depend on each other (no base_out overlaps
- * another entry's base_out or any entry's x) run as batches of up to 64 (120 where the plan has no tiles, 224 where they are of at most eight of the cache's projections besides): one launch per phase for all of them, and one
+ * another entry's base_out or any entry's x) run as batches of up to 64 (120 where the plan has no tiles, 224 where they are of at most eight of the
+ * cache's projections besides): one launch per phase for all of them, and one
  * pass over x for those that read the same x (q, k, v; gate, up; up to 4 neighbours).  Nothing is
  * enqueued if any entry fails validation. */
 typedef struct {

@@ -98,18 +98,6 @@ template <int H> __device__ __forceinline__ void linear_tile(int t, int n_mt, in
     bm = H * grp + (rem - bn * height);
 }
 
-// 16 bytes a lane from memory to LDS: lane l's to to_lds (the same in all lanes) + 16 l
-__device__ __forceinline__ void request16(const __bf16 *from, unsigned char *to_lds)
-{
-    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
-}
-
-// Waits until at most N of the wavefront's vector-memory requests are outstanding
-template <int N> __device__ __forceinline__ void wait_requests()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // A barrier alone: what must be complete at it has been waited for by count
 __device__ __forceinline__ void section_end()
 {
@@ -906,9 +894,9 @@ static double rounds_us(int rows, int n_tiles, double n_k, int n_cu)
 // 192, of 288): 4300 x 4096 x 4096 125 / 137 / 103 (272 tiles; 368; 240), 4416 132 / 136 / 108, 5809 155 / 151 / 184, 3000 80 / 77 / 87, 3500 x 2560 x 2560 49 / 44 / 53,
 // 2560 x 13824 x 5120 273 / 286 / 257, 3000 x 11008 x 4096 219 / 223 / 204; not chosen: 2048 x 4096 x 4096 63 / 65 / 79, 2560 x 5120 x 5120 107 / 163 / 115, 1600 x 4096 x 4096
 // 57 / 61 / 76; 160 and 224 rows were the best nowhere (2560 x 5120 x 5120: 168, 105).  The estimate is within 8 % of these, hence the 5 % it has to gain.
-// Few stages are no exception: of 150 drawn products (500 to 9000 rows, 768 to 11500 columns) 90 of 12 to 35 stages take 1.092 times less in the geometric mean than with tiles of 256 alone (the best of the
-// three each time 1.095), 60 of 3 to 11 stages 1.049 (1.070), and none that left 256 got slower: 4396 x 2112 x 4096 82.7 / 78.2 / 61.7, 5082 x 1024 x 3584 56.4 / 48.8 / 37.3, 4527 x 1536 x 2496 39.2 / 35.1 / 41.8,
-// 7095 x 576 x 2368 43.3 / 35.6 / 27.5.
+// Few stages are no exception.  Of 150 drawn products (500 to 9000 rows, 768 to 11500 columns) 90 of 12 to 35 stages take 1.092 times less in the geometric mean than with
+// tiles of 256 alone (the best of the three each time 1.095), 60 of 3 to 11 stages 1.049 (1.070), and none that left 256 got slower: 4396 x 2112 x 4096 82.7 / 78.2 / 61.7,
+// 5082 x 1024 x 3584 56.4 / 48.8 / 37.3, 4527 x 1536 x 2496 39.2 / 35.1 / 41.8, 7095 x 576 x 2368 43.3 / 35.6 / 27.5.
 
 template <int RM, int NST> constexpr int small_lds = NST * 64 * (RM + 1) * LROW;
 

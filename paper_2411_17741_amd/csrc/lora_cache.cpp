@@ -47,14 +47,16 @@ constexpr int N_LINEAR_SPLITS = 256;  // split tiles of lora_linear_plan (tiles 
 constexpr double GEMV_FIXED_US = 4.0, TILE_FIXED_US = 10.5;
 // Beside the base product: a shrink launch, the fp32 term of GEMV rows
 constexpr double LINEAR_SHRINK_US = 3.0, LINEAR_TERM_US = 1.0;
-// A plan whose own lists have no tiles is made with lists for such launches besides, where one can gain by them: 1 to 4 us more on the host (one prompt of 77 tokens 8.2 and 9.1, three of 5 to 400 tokens
-// 11.7 and 15.6), in the same upload.  What a launch has to gain by them was fitted to lists with an upload of their own, 6 us: a list of projections nearly all of it, a base product its share if the plan
-// serves every projection of every layer once.  (The choice looks at nothing but the cache, the plan and the launch, and the lists are there from the start: the same call gives the same
-// bits, captured or not.)  Measured, us a pass with GEMV alone and as chosen:
-// q, k, v, o of two layers, prompts of 11 to 1136 tokens at rank 64 180 and 88; all of two 13B layers, 73 tokens of rank 128 77 and 50; q, k, v of eight layers, 922 one-token requests over 20 adapters 92 and 83;
-// base product of q, k, v, o 4096 wide, 941 tokens 256 and 216, of q 5120 wide, 1543 tokens 132 and 115.  Of 120 drawn lists and products it picks the better way but for 0.5 % in the geometric mean.
+// A plan whose own lists have no tiles is made with lists for such launches besides, where one can gain by them: 1 to 4 us more on the host (one prompt of 77 tokens
+// 8.2 and 9.1, three of 5 to 400 tokens 11.7 and 15.6), in the same upload.  What a launch has to gain by them was fitted to lists with an upload of their own, 6 us: a list
+// of projections nearly all of it, a base product its share if the plan serves every projection of every layer once.  (The choice looks at nothing but the cache, the plan
+// and the launch, and the lists are there from the start: the same call gives the same bits, captured or not.)  Measured, us a pass with GEMV alone and as chosen:
+// q, k, v, o of two layers, prompts of 11 to 1136 tokens at rank 64 180 and 88; all of two 13B layers, 73 tokens of rank 128 77 and 50; q, k, v of eight layers, 922
+// one-token requests over 20 adapters 92 and 83; base product of q, k, v, o 4096 wide, 941 tokens 256 and 216, of q 5120 wide, 1543 tokens 132 and 115.  Of 120 drawn
+// lists and products it picks the better way but for 0.5 % in the geometric mean.
 constexpr double TILED_LISTS_US = 5.0, LINEAR_MIN_GAIN_US = 1.0, LISTS_COST_US = 6.0;
-constexpr double TILE_BESIDE_GEMV_US = 3.0;  // more, where a GEMV launch runs as well (200 one-token requests beside prompts of 300 / 1000 / 2048 tokens, GEMV 22.2 / 28.4 / 53.8, with tiles 24.9 / 29.1 / 48.6 us)
+// More, where a GEMV launch runs as well (200 one-token requests beside prompts of 300 / 1000 / 2048 tokens, GEMV 22.2 / 28.4 / 53.8, with tiles 24.9 / 29.1 / 48.6 us)
+constexpr double TILE_BESIDE_GEMV_US = 3.0;
 double gemv_tokens_us(int32_t n_tok, int32_t rank, double width, bool wide)
 {
     const double k = width / 2048.0;
@@ -65,7 +67,8 @@ double tile_tokens_us(int32_t n_tok, int32_t rank, double width) { return n_tok 
 struct PathCost {
     double each = 0, per_width = 0;
     void add_gemv(int32_t n_tok, int32_t rank, bool wide) { add(gemv_tokens_us(n_tok, rank, 0, wide), gemv_tokens_us(n_tok, rank, 2048, wide)); }
-    void add_tile(int32_t n_tok, int32_t rank) { add(0, tile_tokens_us(std::max(n_tok, 40), rank, 2048)); }  // (a tile of few tokens costs its blocks no less: 8 tiles of 16 on 56 projections 5120 wide 115 us)
+    // (a tile of few tokens costs its blocks no less: 8 tiles of 16 on 56 projections 5120 wide 115 us)
+    void add_tile(int32_t n_tok, int32_t rank) { add(0, tile_tokens_us(std::max(n_tok, 40), rank, 2048)); }
     void add(double at_0, double at_2048) { each += at_0, per_width += (at_2048 - at_0) / 2048; }
     double us(int n, double sum_width) const { return n * each + per_width * sum_width; }
 };

@@ -153,4 +153,16 @@ __device__ __forceinline__ void wave_fold(float (&v)[N])
     (void)m;
 }
 
+// 16 bytes a lane from memory to LDS: lane l's to to_lds (the same in all lanes) + 16 l
+__device__ __forceinline__ void request16(const __bf16 *from, unsigned char *to_lds)
+{
+    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
+}
+
+// Waits until at most N of the wavefront's vector-memory requests are outstanding
+template <int N> __device__ __forceinline__ void wait_requests()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 }  // namespace lora

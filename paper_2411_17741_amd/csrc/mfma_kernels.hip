@@ -277,15 +277,6 @@ __device__ __forceinline__ void mfma_shrink_body(const ApplyArgs &a, const DevIt
     }
 }
 
-__device__ __forceinline__ void request_to_lds(const __bf16 *from, unsigned char *to_lds)  // lane l's 16 bytes to to_lds + 16 l
-{
-    __builtin_amdgcn_global_load_lds(from, (__attribute__((address_space(3))) void *)to_lds, 16, 0, 0);
-}
-template <int N> __device__ __forceinline__ void wait_for_all_but()  // the latest N requests
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 constexpr int SKD = 64, SROW = SKD * 2;  // k elements of a stage of the kernels below, and the bytes of a row
 
 // the arguments of one projection of the batch
@@ -396,7 +387,7 @@ __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArg
     unsigned char *const mine = ring + w * (DRING * DSTAGE);
     auto request = [&](int st, int slot) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) request_to_lds(src[q] + st * DK, mine + slot * DSTAGE + q * 8 * DROW);
+        for (int q = 0; q < 4; ++q) request16(src[q] + st * DK, mine + slot * DSTAGE + q * 8 * DROW);
     };
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
     auto multiply = [&](int slot) {
@@ -418,14 +409,14 @@ __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArg
     int slot = 0;
     for (int st = 0; st < n_st - (DRING - 1); ++st) {
         request(st + DRING - 1, (slot + DRING - 1) % DRING);
-        wait_for_all_but<4 * (DRING - 1)>();
+        wait_requests<4 * (DRING - 1)>();
         multiply(slot);
         slot = (slot + 1) % DRING;
     }
     auto last = [&](auto left_tag) {
         constexpr int LEFT = decltype(left_tag)::value;  // stages behind this one
         if (n_st <= LEFT) return;
-        wait_for_all_but<4 * LEFT>();
+        wait_requests<4 * LEFT>();
         multiply(slot);
         slot = (slot + 1) % DRING;
     };
@@ -514,10 +505,10 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
         const int k = (st_begin + s) * SKD + piece * 8;
         unsigned char *dst = ring + slot * SLOT + 8 * w * SROW;
 #pragma unroll
-        for (int q = 0; q < TT; ++q) request_to_lds(src[q] + k, dst + 64 * q * SROW);
+        for (int q = 0; q < TT; ++q) request16(src[q] + k, dst + 64 * q * SROW);
 #pragma unroll
-        for (int q = 0; q < PER_AT; ++q) request_to_lds(src[TT + q] + k, dst + (64 * TT + 64 * q) * SROW);
-        if (more) request_to_lds(src[TT + PER_AT + ODD - 1] + k, dst + (64 * TT + 64 * PER_AT) * SROW);
+        for (int q = 0; q < PER_AT; ++q) request16(src[TT + q] + k, dst + (64 * TT + 64 * q) * SROW);
+        if (more) request16(src[TT + PER_AT + ODD - 1] + k, dst + (64 * TT + 64 * PER_AT) * SROW);
     };
     floatx4 acc[RB][NQ];
 #pragma unroll
@@ -546,8 +537,8 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
     };
     auto wait = [&](auto left_tag) {
         constexpr int LEFT = decltype(left_tag)::value;
-        if (more) wait_for_all_but<LEFT *(TT + 1 + PER_AT)>();
-        else wait_for_all_but<LEFT *(TT + PER_AT)>();
+        if (more) wait_requests<LEFT *(TT + 1 + PER_AT)>();
+        else wait_requests<LEFT *(TT + PER_AT)>();
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("s_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);

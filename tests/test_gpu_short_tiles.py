@@ -54,8 +54,8 @@ def test_short_tile_launches(lens, h_in, h_out, n_layers):
 @pytest.mark.parametrize("h_in", [64, 192, 448])  # 1, 3 and 7 stages of 64 k
 @pytest.mark.parametrize("ranks", [(8, 33, 80), (24, 64, 128), (16, 96, 5)])  # one to eight blocks of 16 rank rows
 def test_whole_tiles_of_a_slot_in_pairs(h_in, ranks):
-    """A list of 40 projections over 133 tiles: runs of four whole tiles each, worked on two at a time where they are of one slot; prompts with an odd
-    number of tiles and ragged ends, and a pool of one-token requests of one slot."""
+    """A list of 40 projections over 133 tiles, whole tiles of a slot behind each other: prompts with an odd number of tiles and ragged ends, and a pool of
+    one-token requests of one slot."""
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 

@@ -193,3 +193,42 @@ def test_every_body_against_torch(lens, h_in, sliced):
             assert torch.equal(y[gn:], base[gn:])
     finally:
         pool.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,ranks,by_table", [
+    ([101, 101], [128, 128], [3, 4]),
+    ([150, 149, 148, 149], [128] * 4, [1]),
+    ([60, 59, 58, 57], [128, 120, 97, 128], [3, 4]),
+])
+def test_launches_that_the_run_table_takes(lens, ranks, by_table):
+    """Long input rows and few tiles: neither the short launch's units nor panels; by_table: for how many projections that read the same x."""
+    from paper_2411_17741_amd.pool import LoraPool
+
+    h_in, h_out, T, n = 13824, 128, sum(lens), len(lens)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    A, Bm = [[normal(h_in, r, sigma=0.01) for r in ranks] for _ in range(4)], [normal(r, h_out, sigma=0.02) for r in ranks]
+    x, base = normal(T, h_in), normal(4, T, h_out)
+    pool = LoraPool([(h_in, h_out)] * 4, 1, [128], [n], B.LORA_BF16, max_tokens=T, max_segments=n, mfma_min_tokens=8)
+    try:
+        for s in range(n):
+            for p in range(4):
+                pool.fill(s, s + 1, ranks[s], 0.5 + s, 0, p, A[p][s].cpu(), Bm[s].cpu())
+        plan = pool.plan(T, off, np.arange(n, dtype=np.int32), np.asarray(ranks, np.int32))
+        rc, units, _toks = B.lora_plan_dump(pool.handle, plan, 0)
+        ways = units[units["kind"] == B.LORA_UNIT_SHRINK_WAY]
+        assert rc == B.LORA_OK and (list(ways[ways["lo"] == 1]["where"]) == by_table or torch.cuda.get_device_properties(0).multi_processor_count != 256)
+        for gn in by_table:
+            y = base.clone()
+            B.check(B.lora_apply_plan_multi(pool.handle, plan, B.make_descs([(0, p, x.data_ptr(), y[p].data_ptr()) for p in range(gn)]), 2.0, torch.cuda.current_stream().cuda_stream))
+            pool.check_fault()
+            for p in range(gn):
+                for s in range(n):
+                    a, b = int(off[s]), int(off[s + 1])
+                    v = 2.0 * (0.5 + s) * (x[a:b].double() @ A[p][s].double())
+                    ref, rounding = base[p, a:b].double() + v @ Bm[s].double(), v.abs() @ Bm[s].double().abs()
+                    assert bool(((y[p, a:b].double() - ref).abs() <= 1.125 * 2.0**-8 * (ref.abs() + rounding)).all()), (gn, p, s)  # as above
+    finally:
+        pool.close()
