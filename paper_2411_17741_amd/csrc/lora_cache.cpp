@@ -5,6 +5,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <optional>
 #include <unordered_map>
 #include <vector>
 
@@ -1092,12 +1093,13 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
 
     const size_t bytes = lists.size(c, p, p.internal, true, T, c.plan_cap);
     if (bytes > c.plan_cap) return LORA_E_NOMEM;
-    ListBuild tiled;  // (a plan without room for them, or for their panels, does without)
+    std::optional<ListBuild> tiled;  // (a plan without room for them, or for their panels, does without)
     if (may_tile && some_launch_takes_tiles(c, p)) {
-        rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, LORA_MFMA_MIN_TOKENS_MIXED, &tiled.w);
+        tiled.emplace();
+        rc = lora_index(T, seg_offsets, seg_slot, seg_rank, n_seg, LORA_MFMA_MIN_TOKENS_MIXED, &tiled->w);
         if (rc != LORA_OK) return rc;
         const size_t room = c.plan_cap - bytes;
-        p.tiled_bytes = tiled.size(c, p.tiled, false, false, T, room);
+        p.tiled_bytes = tiled->size(c, p.tiled, false, false, T, room);
         p.has_tiled = p.tiled_bytes <= room && p.tiled.n_panels > 0;
         if (!p.has_tiled) p.tiled_bytes = 0;
     }
@@ -1126,7 +1128,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     p.build_seq = ++c.plan_builds;
     p.lists = p.dev;
     if (p.has_tiled) {
-        tiled.write(c, p.tiled, p.pinned + bytes);
+        tiled->write(c, p.tiled, p.pinned + bytes);
         p.tiled.build_seq = ++c.plan_builds;
         if (!c.host_only) p.tiled.lists = p.dev + bytes;
     }
