@@ -992,8 +992,9 @@ bool product_takes_tiles(const lora_cache &c, const lora_plan &p, double width)
     const double least = LINEAR_MIN_GAIN_US + LISTS_COST_US / (double)(c.n_layers * c.proj.size());
     return tiled + least < gemv;
 }
-// Does any launch of the cache's projections?  Either estimate rises evenly with the projections and their widths as long as the kind of GEMV items stays, so the ends say it:
-// the narrowest and the widest projection, as many as a batch with tiles or the cache has, and as many as still take no wide items.
+// Does any launch of the cache's projections?  Either estimate rises evenly with the projections and their widths as long as the number of launches and the kind of GEMV items stay, so the
+// ends say it: the narrowest and the widest projection, as many as one and two batches with tiles take before more is asked of a list (and the scratch has sets for), and as many as
+// still take no wide items.
 bool some_launch_takes_tiles(const lora_cache &c, const lora_plan &p)
 {
     double ends[2] = {std::numeric_limits<double>::infinity(), 0};
@@ -1001,16 +1002,17 @@ bool some_launch_takes_tiles(const lora_cache &c, const lora_plan &p)
         const double width = (double)pr.h_in + pr.h_out;
         ends[0] = std::min(ends[0], width), ends[1] = std::max(ends[1], width);
     }
-    const int64_t most = std::min<int64_t>(lora::BATCH_MAX_PROJS, (int64_t)c.n_layers * (int64_t)c.proj.size());
-    auto below_wide = [&](int64_t n_wgs, int64_t from, int64_t up_to) { return n_wgs > 0 ? std::max<int64_t>(1, std::min(up_to, (from - 1) / n_wgs)) : up_to; };
-    for (double width : ends) {
-        if (product_takes_tiles(c, p, width)) return true;
-        for (int64_t n : {most, below_wide(p.n_wgs, GEMV_WIDE_MIN_ITEMS, most), below_wide(p.rest_wgs, GEMV_WIDE_MIN_ITEMS, most)})
-            if (list_takes_tiles(p, (int)n, 2, n * width)) return true;
-        const int64_t group = std::min<int64_t>(most, lora::GROUP_MAX_PROJS);
-        for (int64_t n : {group, below_wide(p.n_wgs, GEMV_WIDE_MIN_ITEMS_ONE_GROUP, group), below_wide(p.rest_wgs, GEMV_WIDE_MIN_ITEMS_ONE_GROUP, group)})
-            if (list_takes_tiles(p, (int)n, 1, n * width)) return true;
-    }
+    auto list_gains = [&](int limit, int n_groups, double width) {
+        const int most = std::min(limit, c.n_sets);
+        const int from = n_groups > 1 ? GEMV_WIDE_MIN_ITEMS : GEMV_WIDE_MIN_ITEMS_ONE_GROUP;
+        auto below_wide = [&](int32_t n_wgs) { return n_wgs > 0 ? std::max(1, std::min(most, (from - 1) / n_wgs)) : most; };
+        for (int n : {most, below_wide(p.n_wgs), below_wide(p.rest_wgs)})
+            if (list_takes_tiles(p, n, n_groups, n * width)) return true;
+        return false;
+    };
+    for (double width : ends)
+        if (product_takes_tiles(c, p, width) || list_gains(lora::GROUP_MAX_PROJS, 1, width) || list_gains(lora::BATCH_MAX_PROJS, 2, width) || list_gains(lora::GEMV_BATCH_MAX_PROJS, 2, width))
+            return true;
     return false;
 }
 

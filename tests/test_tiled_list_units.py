@@ -41,7 +41,7 @@ def test_units(lens, slot, ranks):
 @pytest.mark.parametrize("why,kw", [
     ("no tokens for a tile", dict(lens=[15] * 4, slot=[0, 1, 2, 3], ranks=[16] * 4, projs=LAYER, layers=8)),
     ("tiles of its own", dict(lens=[900, 800], slot=[0, 1], ranks=[128, 64], projs=LAYER, layers=8)),
-    ("one small projection: nothing gains", dict(lens=[77], slot=[0], ranks=[8], projs=[(256, 256)], layers=1)),
+    ("few tokens of a small projection: nothing gains", dict(lens=[16], slot=[0], ranks=[4], projs=[(64, 64)], layers=1)),
     ("a threshold of the caller's", dict(lens=[77], slot=[0], ranks=[32], projs=LAYER, layers=8, mfma_min_tokens=100)),
     ("fp32", dict(lens=[77], slot=[0], ranks=[32], projs=LAYER, layers=8, dtype=B.LORA_F32)),
     ("small scratch", dict(lens=[77], slot=[0], ranks=[32], projs=LAYER, layers=8, flags=B.LORA_CACHE_HOST_ONLY | B.LORA_CACHE_SMALL_SCRATCH)),
