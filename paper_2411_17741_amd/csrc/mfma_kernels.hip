@@ -450,6 +450,8 @@ __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArg
 // x and At travel through an LDS ring of three to six stages of 64 k that the requests write themselves, waited for by count, one barrier per stage.  A ring slot: 64 TT rows of x, then 16 NB
 // rows of At per projection (NB: rank blocks of 16), rows of 128 bytes, 16-byte slot s of row r holding piece s ^ ((r / 2) % 8).  Wavefront w multiplies every fourth row block with one half of
 // the rank blocks: with all of them per wavefront and two row blocks each, the operand reads out of LDS took longer than the loads (7B mixed batch 491 us, 443 this way).
+// What it takes in from behind L2 bounds it: eight prompts on q of eight layers, 281 MB of x and 122 of At, 76 us; x alone 55 to 58, without products 75; one stage less on its way, or more of x by
+// rings of their own for x and At, gains nothing, whole 256-byte pieces of the rows take longer (68 us for x alone).
 // 192 rows: with 256 three projections of rank 64 leave no room for three stages.  The panels are dealt out to the XCDs one by one, the costliest first: in runs of neighbours per XCD, as
 // the kernel above takes its tiles, some XCDs got most of the rank-128 panels (443 -> 338 us); a panel's blocks, if it has several, run side by side on one XCD.
 // Measured, shrink and reduce of a launch, run table -> panels: 7B mixed batch (14 projections) 491 -> 338 us, eight prompts on q of eight layers 89 -> 75, 13B batch 100 -> 82;
@@ -518,21 +520,39 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
     const int rb0 = w % STEP, q0 = HALF_ROWS ? 0 : (w >> 2) * NQ;
     auto row_live = [&](int t) { return RB * STEP == 4 * TT || rb0 + STEP * t < 4 * TT; };  // (uniform)
     auto rank_live = [&](int q) { return NQ * 2 == NBT || HALF_ROWS || q0 + q < NBT; };
-    auto multiply = [&](int slot) {
+    // the operands of a stage's two k steps: those of one are read while the products of the one before run.  (All of a stage's reads first and its products behind them, the wavefronts being in
+    // step, left LDS and the matrix cores waiting for each other: 13B batch 836 -> 834 us, 7B mixed batch 1675 -> 1671.  It is little: a launch without any products takes 75 us where this
+    // one takes 76, see above.)
+    bf16x8 xo[2][RB], ao[2][NQ];
+    auto read = [&](int slot, auto ks_tag) {
+        constexpr int KS = decltype(ks_tag)::value;
         const unsigned char *xs = ring + slot * SLOT + (16 * rb0 + m) * SROW, *as = ring + slot * SLOT + (64 * TT + 16 * q0 + m) * SROW;
+        const int at = ((4 * KS + g) ^ ((m >> 1) & 7)) << 4;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int at = ((4 * ks + g) ^ ((m >> 1) & 7)) << 4;
-            bf16x8 xo[RB];
+        for (int t = 0; t < RB; ++t) xo[KS][t] = *reinterpret_cast<const bf16x8 *>(xs + (row_live(t) ? 16 * STEP * t : 0) * SROW + at);
 #pragma unroll
-            for (int t = 0; t < RB; ++t) xo[t] = *reinterpret_cast<const bf16x8 *>(xs + (row_live(t) ? 16 * STEP * t : 0) * SROW + at);
+        for (int q = 0; q < NQ; ++q) ao[KS][q] = *reinterpret_cast<const bf16x8 *>(as + (rank_live(q) ? 16 * q : 0) * SROW + at);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto products = [&](auto ks_tag) {
+        constexpr int KS = decltype(ks_tag)::value;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const bf16x8 ao = *reinterpret_cast<const bf16x8 *>(as + (rank_live(q) ? 16 * q : 0) * SROW + at);
+        for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                for (int t = 0; t < RB; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[t], ao, acc[t][q], 0, 0, 0);
-            }
-        }
+            for (int t = 0; t < RB; ++t) acc[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xo[KS][t], ao[KS][q], acc[t][q], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using step0 = std::integral_constant<int, 0>;
+    using step1 = std::integral_constant<int, 1>;
+#pragma unroll
+    for (int t = 0; t < RB; ++t) xo[1][t] = bf16x8{};  // (the products before the first stage add nothing)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) ao[1][q] = bf16x8{};
+    auto multiply = [&](int slot) {
+        read(slot, step0{});
+        products(step1{});  // of the stage before
+        read(slot, step1{});
+        products(step0{});
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot has been read when this wavefront is at the next barrier
     };
     auto wait = [&](auto left_tag) {
@@ -569,6 +589,7 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
     last(std::integral_constant<int, 1>{});
     last(std::integral_constant<int, 0>{});
     static_assert(NST >= 3 && NST <= 6, "the walk's last stages");
+    products(step1{});
     const float s_v = a.scale * it.alpha;
     int ti[4 * RB], rows[4 * RB];
 #pragma unroll
