@@ -416,6 +416,14 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
     }
 }
 
+// the part of block `block` in the copy of a plan's lists
+__device__ __forceinline__ void copy_lists(const ListCopy &c, uint32_t block)
+{
+    if (block < c.first_block) return;  // (a wavefront past the last unit)
+    const uint32_t i = (block - c.first_block) * 256u + threadIdx.x;
+    if (i < c.pieces) static_cast<uint4 *>(c.to)[i] = static_cast<const uint4 *>(c.from)[i];
+}
+
 template <typename E>
 __device__ __forceinline__ void gemv_shrink_work(const GemvUse &a, const ItemU it, float (*red)[16])
 {
@@ -456,10 +464,11 @@ __device__ __forceinline__ void gemv_expand_work(const GemvUse &a, const ItemU i
 // per wavefront.  Shrink blocks come first in the grid and wait for nothing, so waiting expand
 // wavefronts cannot starve them; waits are bounded all the same.
 // ---------------------------------------------------------------------------------------
-template <typename E>
+// Copy: nothing, or the ListCopy of lists that blocks behind the others copy (ListCopy)
+template <typename E, typename... Copy>
 __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const GemvItem *ge, uint32_t n_gs, uint32_t n_proj_phase, int32_t ue0,
                                                    int32_t ue1, int32_t ue2, int32_t ue3, uint32_t n_super_packed, uint32_t sm0, uint32_t sm1,
-                                                   uint32_t sm2, uint32_t sm3, GemvArgs a)
+                                                   uint32_t sm2, uint32_t sm3, GemvArgs a, Copy... copy)
 {
     // (the scalars in front are the fields of GemvMap one by one: the leading arguments of a kernel arrive in
     // registers with the wavefront)
@@ -480,7 +489,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
         const GemvMap m{gs, ge, n_gs, n_proj_phase, {ue0, ue1, ue2, ue3}, n_super_packed, {sm0, sm1, sm2, sm3}};
-        if (unit >= (uint32_t)ue3) return;  // (entries past the group repeat its last)
+        if (unit >= (uint32_t)ue3) return (copy_lists(copy, blockIdx.x), ...);  // (entries past the group repeat its last)
         uint32_t proj, item, sc;
         gemv_expand_unit(unit, m, proj, item, sc);
         gemv_expand_work<E>(use(proj), load_item(ge + item), sc, stage[w]);
@@ -491,8 +500,8 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
 // its bytes -- the gap to the kernel before it, the ramp, the hand-over at its end, 5 to 6 us -- is paid once per batch.
 __device__ __forceinline__ const GemvItem *items_of(const GemvBatch &b, bool shrink) { return shrink ? b.gs : b.ge; }
 __device__ __forceinline__ const GemvItem *items_of(const GemvLong &b, bool shrink) { return static_cast<const GemvItem *>(shrink ? b.shrink_items : b.expand_items); }
-template <typename E, typename Batch>
-__global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b)
+template <typename E, typename Batch, typename... Copy>
+__global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b, Copy... copy)
 {
     __shared__ float red[4][16];
     __shared__ __attribute__((aligned(16))) uint32_t stage[4][sizeof(E) == 2 ? TB * 64 : TB * 128];
@@ -512,7 +521,7 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b)
         if (b.m.phase == 1) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
-        if (unit >= b.m.n_units) return;
+        if (unit >= b.m.n_units) return (copy_lists(copy, blockIdx.x), ...);
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
         uint32_t first;
@@ -829,21 +838,29 @@ hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, uint64_t vw_set,
     return hipGetLastError();
 }
 
-hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+static unsigned copy_blocks(const ListCopy &c) { return (c.pieces + 255) / 256; }
+
+hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     const int n_proj = (int)(m.n_proj_phase & 0xffu);
     if (m.n_gs == 0 || a.n_ge <= 0 || n_proj <= 0) return hipSuccess;
     const int n_shrink = n_proj * (int)m.n_gs, n_expand = (m.unit_end[GEMV_MAX_PROJS - 1] + 3) / 4;
-    auto go = [&](uint32_t phase, int blocks, int kind, hipEvent_t ev) {
-        const uint32_t pp = (uint32_t)n_proj | (phase << 8);
-        if (dtype == LORA_BF16)
-            launch_k(tm, ev, kind, gemv_kernel<__bf16>, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
-                     m.unit_end[2], m.unit_end[3], m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a);
-        else
-            launch_k(tm, ev, kind, gemv_kernel<float>, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, pp, m.unit_end[0], m.unit_end[1],
-                     m.unit_end[2], m.unit_end[3], m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a);
+    auto go_with = [&](auto kernel, uint32_t phase, int blocks, int kind, hipEvent_t ev, auto... more) {
+        launch_k(tm, ev, kind, kernel, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, (uint32_t)n_proj | (phase << 8), m.unit_end[0], m.unit_end[1], m.unit_end[2], m.unit_end[3],
+                 m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a, more...);
     };
-    if (a.epoch) {
+    auto go = [&](uint32_t phase, int blocks, int kind, hipEvent_t ev) {
+        if (dtype == LORA_BF16) go_with(gemv_kernel<__bf16>, phase, blocks, kind, ev);
+        else go_with(gemv_kernel<float>, phase, blocks, kind, ev);
+    };
+    if (copy.pieces) {
+        if (!a.epoch) return hipErrorInvalidValue;
+        ListCopy c = copy;
+        c.first_block = (uint32_t)(n_shrink + n_expand);
+        const int blocks = n_shrink + n_expand + (int)copy_blocks(c);
+        if (dtype == LORA_BF16) go_with(gemv_kernel<__bf16, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
+        else go_with(gemv_kernel<float, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
+    } else if (a.epoch) {
         go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
     } else {
         go(1u, n_shrink, LORA_K_GEMV_SHRINK, nullptr);
@@ -852,15 +869,21 @@ hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream
     return hipGetLastError();
 }
 
-template <typename Batch> static hipError_t launch_batch(int dtype, const Batch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+template <typename Batch> static hipError_t launch_batch(int dtype, const Batch &b, bool wide, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (b.m.n_gs == 0 || b.m.n_ge == 0 || b.m.n_proj == 0) return hipSuccess;
-    if (wide && dtype != LORA_BF16) return hipErrorInvalidValue;
+    if ((wide && dtype != LORA_BF16) || (copy.pieces && (wide || !b.epoch))) return hipErrorInvalidValue;
     const unsigned n_shrink = b.m.n_proj * b.m.shrink_blocks, n_expand = (b.m.n_units + 3) / 4;
     auto go = [&](uint32_t phase, unsigned blocks, int kind, hipEvent_t ev) {
         Batch q = b;
         q.m.phase = phase;
-        if (wide) launch_k(tm, ev, kind, gemv_wide_kernel<Batch>, dim3(blocks), dim3(256), 0, st, q);
+        if (copy.pieces) {
+            ListCopy c = copy;
+            c.first_block = blocks;
+            const dim3 grid(blocks + copy_blocks(c));
+            if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
+            else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
+        } else if (wide) launch_k(tm, ev, kind, gemv_wide_kernel<Batch>, dim3(blocks), dim3(256), 0, st, q);
         else if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch>, dim3(blocks), dim3(256), 0, st, q);
         else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch>, dim3(blocks), dim3(256), 0, st, q);
     };
@@ -873,11 +896,14 @@ template <typename Batch> static hipError_t launch_batch(int dtype, const Batch 
     return hipGetLastError();
 }
 
-hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     if (b.y32 && !(wide && b.m.n_proj == 1)) return hipErrorInvalidValue;
-    return launch_batch(dtype, b, wide, st, tm, done);
+    return launch_batch(dtype, b, wide, copy, st, tm, done);
 }
-hipError_t launch_gemv_long(int dtype, const GemvLong &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done) { return launch_batch(dtype, b, wide, st, tm, done); }
+hipError_t launch_gemv_long(int dtype, const GemvLong &b, bool wide, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
+{
+    return launch_batch(dtype, b, wide, copy, st, tm, done);
+}
 
 }  // namespace lora

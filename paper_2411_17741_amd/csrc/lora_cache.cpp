@@ -80,6 +80,8 @@ constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // lora_apply's lists, used by one launch, are read where the host writes them (pinned memory, over the link) up to so many wavefronts that read an item: no upload
 // launch.  us a call with the upload and without: 16 fp32 tokens 16.5 and 8.4, 16 requests at 4096 x 4096 16.0 and 8.2, 64 requests (about 2000 wavefronts) 18.5 and 10.5, 200 requests
 // (about 6000) 23.4 and 12.4.  So too while the link is busy: 64 requests beside copies or staged fills 19 and 12.3, beside fills by a kernel that reads host memory 139 and 101.
+// The first launch of a plan does the same and copies the lists for those that follow, in blocks of its own (lora_plan_create, then us a pass: one request on all 224 projections of a 7B
+// model 25.7 and 20.9; a prompt of 77 tokens call by call 271 and 255).  With more wavefronts, wide items or tiles the lists are uploaded ahead of it (64 requests on q of 32 layers, 65000 wavefronts).
 constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
@@ -214,6 +216,11 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     const char *pinned_dev = nullptr;  // the same as the device sees it; the lists are in dev or there
     hipEvent_t ev_upload = nullptr;
     bool upload_pending = false;
+    // Lists that are still where the host wrote them alone (`deferred`): the first launch that works through them copies them, and reads them there.  That launch is covered by
+    // the fence of its call (upload_fence, -1: none), on upload_stream
+    bool deferred = false, copying = false;
+    int32_t upload_fence = -1;
+    hipStream_t upload_stream = nullptr;
     int32_t last_use = -1;  // fence of the latest call that used the plan
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     size_t bytes = 0;           // of these lists
@@ -260,7 +267,7 @@ struct lora_cache {
     std::vector<Slot> slots;
     std::unordered_map<int64_t, int32_t> id2slot;
     std::vector<lora_plan> plans;  // user plans first, then the internal ring
-    uint64_t internal_next = 0, plan_builds = 0;
+    uint64_t internal_next = 0, plan_builds = 0, user_next = 0;
     Stage stage[N_STAGES];
     bool direct_fill = false;
     uint64_t stage_next = 0;
@@ -1016,6 +1023,20 @@ bool some_launch_takes_tiles(const lora_cache &c, const lora_plan &p)
     return false;
 }
 
+// The upload of a plan's lists on `st`, behind what may still read those that lie there.
+hipError_t upload_lists(lora_cache &c, lora_plan &p, hipStream_t st)
+{
+    if (p.last_use >= 0) {
+        const hipError_t e = hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0);
+        if (e != hipSuccess) return e;
+        hold_fence(c, p.last_use, -1);
+    }
+    const hipError_t e = lora::launch_upload(p.dev, p.pinned_dev, p.bytes + p.tiled_bytes, st, p.ev_upload);
+    p.upload_pending |= e == hipSuccess;
+    p.deferred = e != hipSuccess;
+    return e;
+}
+
 // Validates a batch against the slot table and writes its work lists into plan `p`
 // (pinned copy + upload on `st`).
 int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
@@ -1117,6 +1138,15 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         }
         p.upload_pending = false;
     }
+    if (p.upload_fence >= 0) {  // the launch that read the staged copy and copied it
+        const hipError_t e = hipEventSynchronize(c.fences[p.upload_fence].ev);
+        if (e != hipSuccess) {
+            g_last_hip = (int)e;
+            return LORA_E_HIP;
+        }
+        hold_fence(c, p.upload_fence, -1);
+    }
+    p.deferred = false;
     if (!c.host_only && p.lists == p.pinned_dev && p.last_use >= 0) {  // an earlier apply may still be reading it there
         const hipError_t e = hipEventSynchronize(c.fences[p.last_use].ev);
         if (e != hipSuccess) {
@@ -1140,15 +1170,13 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         for (const auto &pr : c.proj) supers = std::max(supers, (pr.h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS);
         waves += (int64_t)p.n_ge * supers;
     }
-    if (!c.host_only && p.internal && c.fencing && p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES) {
+    const bool from_pinned = !c.host_only && c.fencing && p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
+    if (from_pinned && p.internal) {
         p.lists = p.pinned_dev;
+    } else if (from_pinned && bytes && c.n_user_plans > 1 && c.side_stream) {  // (one plan alone would have to wait for its own launch before it is made anew)
+        p.deferred = true;
     } else if (!c.host_only && bytes) {
-        if (p.last_use >= 0) {
-            HIP_TRY(hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0));
-            hold_fence(c, p.last_use, -1);
-        }
-        HIP_TRY(lora::launch_upload(p.dev, p.pinned_dev, bytes + p.tiled_bytes, st, p.ev_upload));
-        p.upload_pending = true;
+        HIP_TRY(upload_lists(c, p, st));
     }
     return LORA_OK;
 }
@@ -1317,8 +1345,8 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         fail(hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming));
     }
     std::fill(c->ring, c->ring + N_APPLY_EVENTS, -1);
-    // what the ring, the plans and a few streams hold; more streams, more events
-    for (size_t i = 0; i < N_APPLY_EVENTS + c->plans.size() + 8 && rc == LORA_OK; ++i) {
+    // what the ring, the plans (their latest use, the copy of their lists) and a few streams hold; more streams, more events
+    for (size_t i = 0; i < N_APPLY_EVENTS + 2 * c->plans.size() + 8 && rc == LORA_OK; ++i) {
         hipEvent_t ev = nullptr;
         fail(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
         if (ev) c->fences.push_back({ev, 0});
@@ -1817,14 +1845,14 @@ int lora_plan_create(lora_cache_t *c, int32_t T, const int32_t *seg_offsets, con
     if (!c || !out) return LORA_E_INVAL;
     *out = nullptr;
     lora_plan *p = nullptr;
-    for (int i = 0; i < c->n_user_plans; ++i)
-        if (!c->plans[i].in_use) {
-            p = &c->plans[i];
-            break;
-        }
+    for (int i = 0; i < c->n_user_plans && !p; ++i) {  // in turns: making one waits for the upload of the lists it held before
+        lora_plan &q = c->plans[(c->user_next + i) % c->n_user_plans];
+        if (!q.in_use) p = &q;
+    }
     if (!p) return LORA_E_NOMEM;
     const int rc = build_plan(*c, *p, T, seg_offsets, seg_slot, seg_rank, n_seg, static_cast<hipStream_t>(stream));
     if (rc != LORA_OK) return rc;
+    c->user_next = (uint64_t)(p - c->plans.data()) + 1;
     p->in_use = true;
     *out = p;
     return LORA_OK;
@@ -1922,9 +1950,10 @@ static int dump_units(lora_cache_t *c, const lora_plan_t *plan, bool tiled, int3
     // the bytes the kernels read
     std::vector<char> copy;
     const char *buf = plan->pinned + at;
-    if (!c->host_only) {
+    if (!c->host_only && !plan->deferred) {
         copy.resize(bytes);
         if (plan->upload_pending) HIP_TRY(hipEventSynchronize(plan->ev_upload));
+        if (plan->upload_fence >= 0) HIP_TRY(hipEventSynchronize(c->fences[plan->upload_fence].ev));
         if (bytes) HIP_TRY(hipMemcpy(copy.data(), plan->dev + at, bytes, hipMemcpyDeviceToHost));
         buf = copy.data();
     }
@@ -2300,7 +2329,7 @@ static bool one_gemv_launch(const lora_cache_t *c, const Scratch &sc, int64_t it
 // hand-over when the part is small (the launch in between then costs more than the hand-over), else a
 // shrink and an expand launch.  y32[i], when set, receives projection i's update as fp32 instead of y.
 static int enqueue_gemv(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *a, float *const *y32, int n, float scale,
-                        hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
+                        hipStream_t st, const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done, const lora::ListCopy &copy)
 {
     if (p->n_gs <= 0) return LORA_OK;
     lora::GemvArgs ga{};
@@ -2336,7 +2365,7 @@ static int enqueue_gemv(lora_cache_t *c, const PlanLists *p, const lora::BatchPr
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         ga.epoch = ++*sc.epoch;
     }
-    HIP_TRY(lora::launch_gemv(c->dtype, gm, ga, st, tm, done));
+    HIP_TRY(lora::launch_gemv(c->dtype, gm, ga, copy, st, tm, done));
     return LORA_OK;
 }
 
@@ -2351,7 +2380,7 @@ static bool gemv_wide(const lora_cache_t *c, const PlanLists *p, const lora::Bat
 
 // The same for a batch of several groups.
 static int enqueue_gemv_batch(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *projs, float *y32, int n, int n_groups, float scale, hipStream_t st, const Scratch &sc,
-                              const lora::KernelTimer *tm, hipEvent_t done)
+                              const lora::KernelTimer *tm, hipEvent_t done, const lora::ListCopy &copy)
 {
     if (p->n_gs <= 0) return LORA_OK;
     lora::GemvBatch b{};
@@ -2374,7 +2403,7 @@ static int enqueue_gemv_batch(lora_cache_t *c, const PlanLists *p, const lora::B
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         b.epoch = ++*sc.epoch;
     }
-    HIP_TRY(lora::launch_gemv_batch(c->dtype, b, wide, st, tm, done));
+    HIP_TRY(lora::launch_gemv_batch(c->dtype, b, wide, copy, st, tm, done));
     return LORA_OK;
 }
 
@@ -2394,7 +2423,7 @@ static bool gemv_long(const lora_cache_t *c, const PlanLists *p, const lora_appl
            (n > lora::GEMV_BATCH_MAX_PROJS || supers > lora::GEMV_BATCH_MAX_SUPERS);
 }
 static int enqueue_gemv_long(lora_cache_t *c, const PlanLists *p, const lora::BatchProj *projs, const lora_apply_desc_t *const *descs, int n, int n_groups, float scale, hipStream_t st,
-                             const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done)
+                             const Scratch &sc, const lora::KernelTimer *tm, hipEvent_t done, const lora::ListCopy &copy)
 {
     lora::GemvLong b{};
     const bool wide = gemv_wide(c, p, projs, n, n_groups);
@@ -2426,7 +2455,7 @@ static int enqueue_gemv_long(lora_cache_t *c, const PlanLists *p, const lora::Ba
         if (const int rc = clear_words_for_capture(c, p, n, st, sc)) return rc;
         b.epoch = ++*sc.epoch;
     }
-    HIP_TRY(lora::launch_gemv_long(c->dtype, b, wide, st, tm, done));
+    HIP_TRY(lora::launch_gemv_long(c->dtype, b, wide, copy, st, tm, done));
     return LORA_OK;
 }
 
@@ -2443,9 +2472,23 @@ static const PlanLists *pick_linear_lists(const lora_cache_t *c, const lora_plan
 // What a call needs of other streams: the plan's lists and its slots' weights.  A captured call waits here, on the host: a wait on an event from outside the capture does not become
 // part of the graph, whose replays may run before that event.  (The event of a stream that is not the null stream can be asked about and waited for while this thread captures
 // only in relaxed mode; elsewhere the capture is invalidated.)
-static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st)
+// copies: the launch this is for copies the plan's lists itself; else lists that are still with the host are uploaded here (for a captured call on the side stream: the upload is no part of the graph).
+static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool copies)
 {
     int capturing = -1;  // not known yet
+    if (copies) {
+        if (p->last_use >= 0) {
+            HIP_TRY(hipStreamWaitEvent(st, c->fences[p->last_use].ev, 0));
+            hold_fence(*c, p->last_use, -1);
+        }
+    } else if (p->deferred) {
+        capturing = is_capturing(st);
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return LORA_E_HIP;
+        const hipError_t e = upload_lists(*c, *p, capturing ? c->side_stream : st);
+        if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
+        HIP_TRY(e);
+    }
     auto wait = [&](hipEvent_t ev, bool &pending) {
         if (capturing < 0) capturing = is_capturing(st);
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -2457,6 +2500,12 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st)
         return e;
     };
     if (p->upload_pending) HIP_TRY(wait(p->ev_upload, p->upload_pending));
+    if (p->upload_fence >= 0) {
+        if (capturing < 0) capturing = is_capturing(st);
+        bool pending = true;
+        if (capturing || st != p->upload_stream) HIP_TRY(wait(c->fences[p->upload_fence].ev, pending));
+        if (!pending) hold_fence(*c, p->upload_fence, -1);
+    }
     for (int32_t sl : p->slots) {
         Slot &s = c->slots[sl];
         if (s.fill_pending) HIP_TRY(wait(s.fill_ev, s.fill_pending));
@@ -2470,17 +2519,33 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st)
 // with its own copy of the intermediate buffers.
 // `fence` (null: none) is to stand for the batch's end on `st`.
 static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, const lora_apply_desc_t *descs, const uint8_t *group_n, int n, float scale, hipStream_t st,
-                         const Scratch &sc, hipEvent_t fence)
+                         const Scratch &sc, hipEvent_t fence, bool fenced)
 {
-    if (const int rc = wait_for_inputs(c, p, st)) return rc;
-    const lora::KernelTimer timer{c, timer_pair};
-    const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
-    lora::TileBatch tb;
-    int64_t sum_h_in = 0, sum_h_out = 0;
+    int64_t sum_h_in = 0, sum_h_out = 0, sum_supers = 0;
     for (int i = 0; i < n; ++i) {
         sum_h_in += c->proj[descs[i].proj].h_in;
         sum_h_out += c->proj[descs[i].proj].h_out;
+        sum_supers += supers_of(c->proj[descs[i].proj].h_out);
     }
+    // lists that are still with the host travel with this launch, if it is one of GEMV work that a fence will stand for and not too many wavefronts read them over the link
+    const bool copies = p->deferred && fenced && !c->timing && q == p && q->n_gs > 0 && 4 * (int64_t)q->n_gs * n + q->n_ge * sum_supers <= PINNED_LISTS_MAX_WAVES &&
+                        (int64_t)q->n_wgs * n < GEMV_WIDE_MIN_ITEMS && one_gemv_launch(c, sc, (int64_t)q->n_gs * n, FUSED_GEMV_MAX_ITEMS);
+    if (const int rc = wait_for_inputs(c, p, st, copies)) return rc;
+    struct Lists {  // where this launch reads them
+        lora_plan *p;
+        ~Lists()
+        {
+            if (p) p->lists = p->dev;
+        }
+    } lists{copies ? p : nullptr};
+    lora::ListCopy copy{};
+    if (copies) {
+        p->lists = p->pinned_dev;
+        copy.to = p->dev, copy.from = p->pinned_dev, copy.pieces = (uint32_t)((p->bytes + p->tiled_bytes + 15) / 16);
+    }
+    const lora::KernelTimer timer{c, timer_pair};
+    const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
+    lora::TileBatch tb;
     if (q->n_tiles > 0)
         if (const int rc_s = tile_setup(c, q, n, sum_h_in, sc, scale, tb)) return rc_s;
     // groups of long rows first: their shrink blocks take the longest, and the launch should not end with them
@@ -2533,10 +2598,15 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
     const bool ride = fence && !fork && tm == nullptr && (q->n_tiles > 0 || q->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && q->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups > 1 && gemv_long(c, q, descs, n) ? enqueue_gemv_long(c, q, projs, at_desc, n, n_groups, scale, gemv_st, sc, tm, gemv_done)
-                                       : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done)
-                                       : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done))
+    if (const int rc_g = n_groups > 1 && gemv_long(c, q, descs, n) ? enqueue_gemv_long(c, q, projs, at_desc, n, n_groups, scale, gemv_st, sc, tm, gemv_done, copy)
+                                       : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done, copy)
+                                       : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done, copy))
         return rc_g;
+    if (copies) {
+        p->deferred = false;
+        p->copying = true;  // until a fence stands for it
+        p->upload_stream = st;
+    }
     join.rides = join_rides;
     // the updates of base_out
     if (q->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
@@ -2570,6 +2640,17 @@ static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32
     c->ring_seq[seq % N_APPLY_EVENTS] = seq;
     hold_fence(*c, c->stream_fence.try_emplace(st, -1).first->second, f);
     hold_fence(*c, p->last_use, f);
+    if (p->copying) {
+        p->copying = false;
+        hold_fence(*c, p->upload_fence, f);
+    }
+}
+// a call that fails has no fence to stand for a launch of it that copies the plan's lists
+static int after_failed_copy(lora_plan_t *p, hipStream_t st, int rc)
+{
+    if (p->copying) (void)hipStreamSynchronize(st);
+    p->copying = false;
+    return rc;
 }
 
 // one projection as a call with a fence of its own
@@ -2578,7 +2659,7 @@ static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t
     int32_t f;
     if (const int rc = take_fence(c, st, f)) return rc;
     const uint8_t one = 1;
-    if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev)) return rc;
+    if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return after_failed_copy(p, st, rc);
     publish_fence(c, p, st, f);
     return LORA_OK;
 }
@@ -2632,7 +2713,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     if (p->T > 0 && (!Wt || !aligned16(Wt))) return LORA_E_INVAL;
     if (p->T == 0) return LORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (const int rc_w = wait_for_inputs(c, p, st)) return rc_w;
+    if (const int rc_w = wait_for_inputs(c, p, st, false)) return rc_w;
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
     const lora::BatchProj bp = batch_proj(c, {layer, proj, x, y});
@@ -2667,8 +2748,8 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         a.y32 = static_cast<float *>(workspace);
         if (!a.y32) HIP_TRY(lora::launch_zero_rows(y, a.tok_list + q->n_tile_tok, n_gemv_tok, a.h_out, st));
         float *const y32 = a.y32;
-        if (const int rc_g = gemv_wide(c, q, &bp, 1, 1) ? enqueue_gemv_batch(c, q, &bp, y32, 1, 1, scale, st, pool_scratch(c), tm, nullptr)
-                                                        : enqueue_gemv(c, q, &bp, &y32, 1, scale, st, pool_scratch(c), tm, nullptr))
+        if (const int rc_g = gemv_wide(c, q, &bp, 1, 1) ? enqueue_gemv_batch(c, q, &bp, y32, 1, 1, scale, st, pool_scratch(c), tm, nullptr, {})
+                                                        : enqueue_gemv(c, q, &bp, &y32, 1, scale, st, pool_scratch(c), tm, nullptr, {}))
             return rc_g;
     }
     // base product of every token + adapter product of the tiles (+ the term just computed for the others)
@@ -2760,8 +2841,8 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
                 for (int e = 0; e < group_n[at + k]; ++e) left -= supers_of(c->proj[descs[i + at + k + e].proj].h_out);
                 if (k > 0 && (k + group_n[at + k] > most || left < 0)) break;
             }
-            const int rc = enqueue_batch(c, p, q, descs + i + at, group_n + at, k, scale, st, scratch, f >= 0 && i + at + k == n ? c->fences[f].ev : nullptr);
-            if (rc != LORA_OK) return rc;
+            const int rc = enqueue_batch(c, p, q, descs + i + at, group_n + at, k, scale, st, scratch, f >= 0 && i + at + k == n ? c->fences[f].ev : nullptr, f >= 0);
+            if (rc != LORA_OK) return after_failed_copy(p, st, rc);
             at += k;
         }
         i += m;

@@ -119,6 +119,14 @@ inline __host__ __device__ void gemv_expand_cols(const GemvItem &it, int32_t sc,
     gemv_cols(gemv_expand_width(it.rank), it.a, sc, h_out, c0, c1);
 }
 
+// A plan's work lists on their way from pinned host memory to the pool, by blocks behind those of the plan's first launch, which itself reads them where the host wrote them: no launch of their own
+struct ListCopy {
+    void *to;          // device
+    const void *from;  // pinned host memory as the device sees it
+    uint32_t pieces;   // of 16 bytes; 0: nothing to copy
+    uint32_t first_block;
+};
+
 // A batch: the projections one launch serves.  They do not depend on each other (no output overlaps another entry's
 // output or any entry's input), so that every phase is one launch for all of them.
 constexpr int BATCH_MAX_PROJS = 64;        // of a batch with tiles
@@ -400,9 +408,10 @@ inline void launch_k(const KernelTimer *tm, hipEvent_t done, int kind, K kernel,
 // launches (all asynchronous on `st`); dtype is LORA_F32 or LORA_BF16; tm and done may be null (done: see launch_k)
 // GEMV shrink and expand of the group's projections: phase 0 as one launch (a.epoch != 0: the expand
 // wavefronts wait for the hand-over words to carry that number), phases 1 and 2 as two
-hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
-hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
-hipError_t launch_gemv_long(int dtype, const GemvLong &b, bool wide, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+// copy (pieces 0: none): lists that the launch copies, in phase 0 and without wide items only, by kernels of their own (the others take 0.2 to 0.4 % longer with the branch in them)
+hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+hipError_t launch_gemv_batch(int dtype, const GemvBatch &b, bool wide, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
+hipError_t launch_gemv_long(int dtype, const GemvLong &b, bool wide, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // bytes of one projection's hand-over words for max_tokens tokens
 size_t gemv_handover_bytes(int dtype, int64_t max_tokens);
 // zeroes the hand-over words of tokens toks[0 .. n) (device list) in `sets` sets from `vw` on, vw_set words apart

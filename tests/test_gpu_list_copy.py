@@ -1,0 +1,164 @@
+"""Plans whose lists travel with their first launch: on other streams than the plan's, captured, followed at once by other plans and other streams, and where the first launch cannot take
+them along."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+H, N_L = 512, 6
+
+
+class Batch:
+    """A pool of 9 adapters, and batches of one-token requests (and a short prompt) over them."""
+
+    def __init__(self, dtype="bf16", n_plans=2, flags=0, extra=()):
+        from paper_2411_17741_amd import binding as B
+        from paper_2411_17741_amd.pool import LoraPool
+
+        self.B, self.dt = B, torch.bfloat16 if dtype == "bf16" else torch.float32
+        self.ranks = [8, 16, 5, 64, 128, 33, 8, 100, 24]
+        gen = torch.Generator(device="cuda").manual_seed(3)
+        self.normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).to(self.dt)
+        self.pool = LoraPool([(H, H)] + list(extra), N_L, [128], [9], B.LORA_BF16 if dtype == "bf16" else B.LORA_F32, max_tokens=256, max_segments=256, n_plans=n_plans, flags=flags)
+        self.A, self.Bm = [self.normal(H, r, sigma=0.05) for r in self.ranks], [self.normal(r, H, sigma=0.05) for r in self.ranks]
+        for layer in range(N_L):
+            for i, r in enumerate(self.ranks):
+                self.pool.fill(i, i + 1, r, 1.0, layer, 0, self.A[i].cpu(), self.Bm[i].cpu())
+        torch.cuda.synchronize()
+        self.x = self.normal(256, H)
+
+    def segs(self, slots):
+        slots = np.asarray(slots, np.int32)
+        return len(slots), np.arange(len(slots) + 1, dtype=np.int32), slots, np.asarray(self.ranks, np.int32)[slots]
+
+    def expect(self, base, slots, times=1):
+        y = base.double().clone()
+        for t, s in enumerate(slots):
+            for _ in range(times):
+                y[t] += 2.0 * (self.x[t].double() @ self.A[s].double()) @ self.Bm[s].double()
+        return y
+
+    def close_to(self, y, ref, times=1):
+        # every pass rounds the output once and s.v once: 2^-8 of values of the size of the result and a little above
+        rel = float((y.double() - ref).norm() / ref.norm())
+        assert rel < (4e-3 * times if self.dt == torch.bfloat16 else 1e-5), rel
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_plans_in_a_row(dtype):
+    """Plan after plan, each applied on a stream of its own and then at once on another one; a destroyed plan's memory goes to the next but one."""
+    b = Batch(dtype)
+    try:
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        rng = np.random.default_rng(1)
+        done = []
+        torch.cuda.synchronize()
+        for i in range(40):
+            slots = rng.integers(0, 9, rng.integers(1, 60))
+            base = b.normal(len(slots), H)
+            y1, y2 = base.clone(), base.clone()
+            torch.cuda.synchronize()
+            plan = b.pool.plan(*b.segs(slots), stream=s1 if i % 3 == 0 else None)
+            x = b.x[: len(slots)].contiguous()
+            b.pool.apply_plan(plan, i % N_L, 0, x, y1, 2.0, stream=s1 if i % 2 else s2)
+            b.pool.apply_plan(plan, (i + 1) % N_L, 0, x, y2, 2.0, stream=s2 if i % 2 else s1)
+            b.pool.plan_destroy(plan)
+            done.append((x, y1, y2, base, slots))
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        for _x, y1, y2, base, slots in done:
+            ref = b.expect(base, slots)
+            b.close_to(y1, ref)
+            assert torch.equal(y1, y2)
+    finally:
+        b.pool.close()
+
+
+@pytest.mark.parametrize("n_list", [1, 6, 24])
+def test_first_use_as_a_list(n_list):
+    """One projection, a list that takes the lists along, one of more wavefronts than read them over the link."""
+    b = Batch()
+    try:
+        slots = np.arange(200 if n_list == 24 else 30) % 9
+        base = b.normal(len(slots), H)
+        x = b.x[: len(slots)].contiguous()
+        for _ in range(3):
+            plan = b.pool.plan(*b.segs(slots))
+            y = [base.clone() for _ in range(n_list)]
+            descs = b.B.make_descs([(i % N_L, 0, x.data_ptr(), y[i].data_ptr()) for i in range(n_list)])
+            b.B.check(b.B.lora_apply_plan_multi(b.pool.handle, plan, descs, 2.0, torch.cuda.current_stream().cuda_stream))
+            b.pool.apply_plan(plan, 0, 0, x, y[0], 2.0)  # out of the copied lists
+            b.pool.plan_destroy(plan)
+            b.close_to(y[0], b.expect(base, slots, 2), 2)
+            ref = b.expect(base, slots)
+            for t in y[1:]:
+                b.close_to(t, ref)
+        b.pool.check_fault()
+    finally:
+        b.pool.close()
+
+
+@pytest.mark.parametrize("used", [False, True])
+@pytest.mark.parametrize("n_plans", [1, 2])
+def test_captured(used, n_plans):
+    """A plan first used in a capture (its lists are then no part of the graph), or in an eager call before; replays with other plans' work in between."""
+    b = Batch(n_plans=n_plans)
+    try:
+        slots, other = np.arange(40) % 9, (np.arange(25) * 4) % 9
+        base = b.normal(40, H)
+        x, y = b.x[:40].contiguous(), base.clone()
+        plan = b.pool.plan(*b.segs(slots))
+        if used:
+            b.pool.apply_plan(plan, 1, 0, x, base.clone(), 2.0)
+        stream = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            b.pool.apply_plan(plan, 0, 0, x, y, 2.0, stream=stream)
+        for i in range(4):
+            y.copy_(base)
+            if n_plans > 1 and i % 2:
+                yo = b.normal(25, H)
+                p2 = b.pool.plan(*b.segs(other))
+                b.pool.apply_plan(p2, 0, 0, b.x[:25].contiguous(), yo, 2.0)
+                b.pool.plan_destroy(p2)
+            graph.replay()
+            torch.cuda.synchronize()
+            b.close_to(y, b.expect(base, slots))
+        b.pool.check_fault()
+    finally:
+        b.pool.close()
+
+
+def test_other_first_uses():
+    """First used by a base product, with fencing off, in a cache without a side stream, and dumped before and after its first use."""
+    for flags in (0, None):
+        b = Batch(flags=0 if flags == 0 else __import__("paper_2411_17741_amd.binding", fromlist=["x"]).LORA_CACHE_NO_OVERLAP)
+        try:
+            slots = np.arange(50) % 9
+            x, base = b.x[:50].contiguous(), b.normal(50, H)
+            W = b.normal(H, H, sigma=0.05)
+            plan = b.pool.plan(*b.segs(slots))
+            rc, before, toks = b.B.lora_plan_dump(b.pool.handle, plan, 0)
+            y = torch.empty_like(base)
+            space = torch.empty(50 * H, dtype=torch.float32, device="cuda")
+            b.B.check(b.B.lora_linear_plan(b.pool.handle, plan, 0, 0, x.data_ptr(), W.data_ptr(), y.data_ptr(), 2.0, torch.cuda.current_stream().cuda_stream, space.data_ptr(), space.numel() * 4))
+            ref = b.expect((x.double() @ W.double().T), slots)
+            b.close_to(y, ref)
+            b.pool.plan_destroy(plan)
+            plan = b.pool.plan(*b.segs(slots))
+            b.B.check(b.B.lora_cache_set_fencing(b.pool.handle, 0))
+            y = base.clone()
+            b.pool.apply_plan(plan, 0, 0, x, y, 2.0)
+            b.B.check(b.B.lora_cache_set_fencing(b.pool.handle, 1))
+            b.close_to(y, b.expect(base, slots))
+            b.pool.plan_destroy(plan)
+            plan = b.pool.plan(*b.segs(slots))
+            y = base.clone()
+            b.pool.apply_plan(plan, 0, 0, x, y, 2.0)
+            rc, after, toks2 = b.B.lora_plan_dump(b.pool.handle, plan, 0)
+            assert np.array_equal(before, after) and np.array_equal(toks, toks2)
+            b.close_to(y, b.expect(base, slots))
+            b.pool.check_fault()
+        finally:
+            b.pool.close()
