@@ -280,8 +280,8 @@ void lora_worklists_free(lora_worklists_t *w);
 /* Index a batch once and keep its work lists on the device, so that the same batch can
  * be applied to every projection of every layer of the iteration.  Checks every named
  * slot against the slot table (exists, bound, seg_rank equals its rank).  The upload is
- * enqueued on `stream`, or, for a plan of one-token requests and short prompts, part of the first launch that
- * works through its lists; the host arrays may be reused on return. */
+ * enqueued on `stream`, or part of the first launch that works through the lists, as the plan's size
+ * and the cache's options have it; the host arrays may be reused on return. */
 int lora_plan_create(lora_cache_t *c, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
                      const int32_t *seg_rank, int32_t n_seg, void *stream, lora_plan_t **out);
 int lora_plan_destroy(lora_cache_t *c, lora_plan_t *p);

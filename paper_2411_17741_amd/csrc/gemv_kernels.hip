@@ -416,14 +416,6 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
     }
 }
 
-// the part of block `block` in the copy of a plan's lists
-__device__ __forceinline__ void copy_lists(const ListCopy &c, uint32_t block)
-{
-    if (block < c.first_block) return;  // (a wavefront past the last unit)
-    const uint32_t i = (block - c.first_block) * 256u + threadIdx.x;
-    if (i < c.pieces) static_cast<uint4 *>(c.to)[i] = static_cast<const uint4 *>(c.from)[i];
-}
-
 template <typename E>
 __device__ __forceinline__ void gemv_shrink_work(const GemvUse &a, const ItemU it, float (*red)[16])
 {
@@ -489,7 +481,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
         const GemvMap m{gs, ge, n_gs, n_proj_phase, {ue0, ue1, ue2, ue3}, n_super_packed, {sm0, sm1, sm2, sm3}};
-        if (unit >= (uint32_t)ue3) return (copy_lists(copy, blockIdx.x), ...);  // (entries past the group repeat its last)
+        if (unit >= (uint32_t)ue3) return (copy_lists(copy, blockIdx.x, 256), ...);  // (entries past the group repeat its last)
         uint32_t proj, item, sc;
         gemv_expand_unit(unit, m, proj, item, sc);
         gemv_expand_work<E>(use(proj), load_item(ge + item), sc, stage[w]);
@@ -521,7 +513,7 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b, Copy... copy)
         if (b.m.phase == 1) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t unit = (blockIdx.x - n_shrink) * 4 + w;
-        if (unit >= b.m.n_units) return (copy_lists(copy, blockIdx.x), ...);
+        if (unit >= b.m.n_units) return (copy_lists(copy, blockIdx.x, 256), ...);
         uint32_t super, item;
         gemv_batch_unit(unit, b.m, super, item);
         uint32_t first;
@@ -838,8 +830,6 @@ hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, uint64_t vw_set,
     return hipGetLastError();
 }
 
-static unsigned copy_blocks(const ListCopy &c) { return (c.pieces + 255) / 256; }
-
 hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     const int n_proj = (int)(m.n_proj_phase & 0xffu);
@@ -857,7 +847,7 @@ hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, const Lis
         if (!a.epoch) return hipErrorInvalidValue;
         ListCopy c = copy;
         c.first_block = (uint32_t)(n_shrink + n_expand);
-        const int blocks = n_shrink + n_expand + (int)copy_blocks(c);
+        const int blocks = n_shrink + n_expand + (int)copy_blocks(c, 256);
         if (dtype == LORA_BF16) go_with(gemv_kernel<__bf16, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
         else go_with(gemv_kernel<float, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
     } else if (a.epoch) {
@@ -880,7 +870,7 @@ template <typename Batch> static hipError_t launch_batch(int dtype, const Batch 
         if (copy.pieces) {
             ListCopy c = copy;
             c.first_block = blocks;
-            const dim3 grid(blocks + copy_blocks(c));
+            const dim3 grid(blocks + copy_blocks(c, 256));
             if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
             else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
         } else if (wide) launch_k(tm, ev, kind, gemv_wide_kernel<Batch>, dim3(blocks), dim3(256), 0, st, q);

@@ -83,6 +83,9 @@ constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // The first launch of a plan does the same and copies the lists for those that follow, in blocks of its own (lora_plan_create, then us a pass: one request on all 224 projections of a 7B
 // model 25.7 and 20.9; a prompt of 77 tokens call by call 271 and 255).  With more wavefronts, wide items or tiles the lists are uploaded ahead of it (64 requests on q of 32 layers, 65000 wavefronts).
 constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
+// So too a tile shrink of up to so many tiles over its projections, all the lists of a plan being copied then: eight prompts on q of eight layers 190.5 -> 187.1 us a pass, the 13B batch
+// 834 -> 828, its base products 1701 -> 1694.
+constexpr int64_t PINNED_LISTS_MAX_TILES = 2048;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
 // twice that 3507 and 3568, one layer (2.4 GB) 968 and 954; 13B with four prompts of 512 (1.6 GB) 876 and 797, with 5120 prompt tokens (4 GB) 1188 and 1200; 64 requests beside a prompt of
@@ -1170,10 +1173,10 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         for (const auto &pr : c.proj) supers = std::max(supers, (pr.h_out + lora::GEMV_SUPER_COLS - 1) / lora::GEMV_SUPER_COLS);
         waves += (int64_t)p.n_ge * supers;
     }
-    const bool from_pinned = !c.host_only && c.fencing && p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
-    if (from_pinned && p.internal) {
+    const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
+    if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (from_pinned && bytes && c.n_user_plans > 1 && c.side_stream) {  // (one plan alone would have to wait for its own launch before it is made anew)
+    } else if (!c.host_only && c.fencing && !p.internal && (few_waves || p.n_tiles > 0) && bytes && c.n_user_plans > 1 && c.side_stream) {  // (one plan alone would have to wait for its own launch before it is made anew)
         p.deferred = true;
     } else if (!c.host_only && bytes) {
         HIP_TRY(upload_lists(c, p, st));
@@ -2477,10 +2480,7 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
 {
     int capturing = -1;  // not known yet
     if (copies) {
-        if (p->last_use >= 0) {
-            HIP_TRY(hipStreamWaitEvent(st, c->fences[p->last_use].ev, 0));
-            hold_fence(*c, p->last_use, -1);
-        }
+        if (p->last_use >= 0) HIP_TRY(hipStreamWaitEvent(st, c->fences[p->last_use].ev, 0));  // (what may still read the lists that lie there)
     } else if (p->deferred) {
         capturing = is_capturing(st);
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -2513,6 +2513,16 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
     return LORA_OK;
 }
 
+// may a tile shrink of n projections, sum_h_in input columns together, be the launch that lists travel with?
+static bool shrink_copies(const PlanLists *q, int n, int64_t sum_h_in)
+{
+    return q->n_tiles > 0 && (int64_t)q->n_tiles * n <= PINNED_LISTS_MAX_TILES && 4 * (int64_t)direct_shrink(q->n_direct, sum_h_in) * n <= PINNED_LISTS_MAX_WAVES;
+}
+static lora::ListCopy list_copy(const lora_plan_t *p)
+{
+    return lora::ListCopy{p->dev, p->pinned_dev, (uint32_t)((p->bytes + p->tiled_bytes + 15) / 16), 0};
+}
+
 // Applies descs[0 .. n), n <= the scratch's sets, that do not depend on each other: every phase is one launch for all of
 // them.  Entries that read the same x (a group, at most GROUP_MAX_PROJS) are neighbours; group_n[i] is the size of the group that
 // starts at entry i.  The tile shrink runs first, for all entries (x of a group is then fetched from memory once), each
@@ -2527,24 +2537,29 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         sum_h_out += c->proj[descs[i].proj].h_out;
         sum_supers += supers_of(c->proj[descs[i].proj].h_out);
     }
-    // lists that are still with the host travel with this launch, if it is one of GEMV work that a fence will stand for and not too many wavefronts read them over the link
-    const bool copies = p->deferred && fenced && !c->timing && q == p && q->n_gs > 0 && 4 * (int64_t)q->n_gs * n + q->n_ge * sum_supers <= PINNED_LISTS_MAX_WAVES &&
-                        (int64_t)q->n_wgs * n < GEMV_WIDE_MIN_ITEMS && one_gemv_launch(c, sc, (int64_t)q->n_gs * n, FUSED_GEMV_MAX_ITEMS);
+    // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
+    // scratch: when a batch has enough of both, the GEMV launch goes to the cache's side stream, forked off here and
+    // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
+    // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
+    const lora::KernelTimer timer{c, timer_pair};
+    const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
+    const double tile_bytes = (double)q->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
+    const bool fork = q->n_tiles > 0 && q->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
+    // Lists that are still with the host travel with the first launch, if a fence will stand for it: a tile shrink, unless the GEMV launch runs beside it, or a GEMV launch of not too many
+    // wavefronts that read them over the link
+    const bool gemv_copies = q == p && q->n_tiles == 0 && q->n_gs > 0 && 4 * (int64_t)q->n_gs * n + q->n_ge * sum_supers <= PINNED_LISTS_MAX_WAVES &&
+                             (int64_t)q->n_wgs * n < GEMV_WIDE_MIN_ITEMS && one_gemv_launch(c, sc, (int64_t)q->n_gs * n, FUSED_GEMV_MAX_ITEMS);
+    const bool copies = p->deferred && fenced && !c->timing && (q->n_tiles > 0 ? !fork && shrink_copies(q, n, sum_h_in) : gemv_copies);
     if (const int rc = wait_for_inputs(c, p, st, copies)) return rc;
-    struct Lists {  // where this launch reads them
+    struct Lists {  // where a GEMV launch that copies them reads them
         lora_plan *p;
         ~Lists()
         {
             if (p) p->lists = p->dev;
         }
-    } lists{copies ? p : nullptr};
-    lora::ListCopy copy{};
-    if (copies) {
-        p->lists = p->pinned_dev;
-        copy.to = p->dev, copy.from = p->pinned_dev, copy.pieces = (uint32_t)((p->bytes + p->tiled_bytes + 15) / 16);
-    }
-    const lora::KernelTimer timer{c, timer_pair};
-    const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
+    } lists{copies && gemv_copies ? p : nullptr};
+    const lora::ListCopy copy = copies ? list_copy(p) : lora::ListCopy{};
+    if (lists.p) p->lists = p->pinned_dev;
     lora::TileBatch tb;
     if (q->n_tiles > 0)
         if (const int rc_s = tile_setup(c, q, n, sum_h_in, sc, scale, tb)) return rc_s;
@@ -2564,12 +2579,6 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         }
     }
     if (q->n_tiles > 0) choose_panels(c, q, sc, tb);
-    // The GEMV launch and the tile kernels of a batch work on different tokens (rows of base_out) with different
-    // scratch: when a batch has enough of both, the GEMV launch goes to the cache's side stream, forked off here and
-    // joined again behind the tile expands (also under stream capture, where fork and join become edges of the graph).
-    // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
-    const double tile_bytes = (double)q->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
-    const bool fork = q->n_tiles > 0 && q->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
     hipStream_t gemv_st = st;
     if (fork) {
         HIP_TRY(hipEventRecord(c->ev_fork, st));
@@ -2577,9 +2586,17 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         gemv_st = c->side_stream;
     }
     // everything that reads x
+    auto copied = [&]() {
+        if (!copies) return;
+        p->deferred = false;
+        p->copying = true;  // until a fence stands for it
+        p->upload_stream = st;
+    };
     if (q->n_tiles > 0) {
-        HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
+        HIP_TRY(lora::launch_mfma_shrink(tb, copy, st, tm));
+        copied();
     }
+    const lora::ListCopy gemv_copy = lists.p ? copy : lora::ListCopy{};
     // joined behind the tile expands, whatever happens in between: a captured fork must not stay open
     struct Join {
         lora_cache_t *c;
@@ -2598,15 +2615,11 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
     const bool ride = fence && !fork && tm == nullptr && (q->n_tiles > 0 || q->n_gs > 0);
     const bool join_rides = fork && !is_capturing(st);
     const hipEvent_t gemv_done = join_rides ? c->ev_join : (ride && q->n_tiles == 0 ? fence : nullptr);
-    if (const int rc_g = n_groups > 1 && gemv_long(c, q, descs, n) ? enqueue_gemv_long(c, q, projs, at_desc, n, n_groups, scale, gemv_st, sc, tm, gemv_done, copy)
-                                       : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done, copy)
-                                       : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done, copy))
+    if (const int rc_g = n_groups > 1 && gemv_long(c, q, descs, n) ? enqueue_gemv_long(c, q, projs, at_desc, n, n_groups, scale, gemv_st, sc, tm, gemv_done, gemv_copy)
+                                       : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done, gemv_copy)
+                                       : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done, gemv_copy))
         return rc_g;
-    if (copies) {
-        p->deferred = false;
-        p->copying = true;  // until a fence stands for it
-        p->upload_stream = st;
-    }
+    if (lists.p) copied();
     join.rides = join_rides;
     // the updates of base_out
     if (q->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
@@ -2646,20 +2659,24 @@ static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32
     }
 }
 // a call that fails has no fence to stand for a launch of it that copies the plan's lists
-static int after_failed_copy(lora_plan_t *p, hipStream_t st, int rc)
-{
-    if (p->copying) (void)hipStreamSynchronize(st);
-    p->copying = false;
-    return rc;
-}
+struct CopyGuard {
+    lora_plan_t *p;
+    hipStream_t st;
+    ~CopyGuard()
+    {
+        if (p->copying) (void)hipStreamSynchronize(st);
+        p->copying = false;
+    }
+};
 
 // one projection as a call with a fence of its own
 static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t &d, float scale, hipStream_t st, const Scratch &sc)
 {
     int32_t f;
     if (const int rc = take_fence(c, st, f)) return rc;
+    const CopyGuard guard{p, st};
     const uint8_t one = 1;
-    if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return after_failed_copy(p, st, rc);
+    if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return rc;
     publish_fence(c, p, st, f);
     return LORA_OK;
 }
@@ -2713,7 +2730,6 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     if (p->T > 0 && (!Wt || !aligned16(Wt))) return LORA_E_INVAL;
     if (p->T == 0) return LORA_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (const int rc_w = wait_for_inputs(c, p, st, false)) return rc_w;
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
     const lora::BatchProj bp = batch_proj(c, {layer, proj, x, y});
@@ -2731,6 +2747,9 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     a.scale = scale;
     int32_t f;
     if (const int rc_f = take_fence(c, st, f)) return rc_f;
+    const CopyGuard guard{p, st};
+    const bool copies = p->deferred && f >= 0 && !c->timing && shrink_copies(q, 1, a.h_in);  // (as in enqueue_batch)
+    if (const int rc_w = wait_for_inputs(c, p, st, copies)) return rc_w;
     // shrink of the tiles (x is read, v written), then the adapter term of the GEMV tokens: as fp32 into the caller's workspace
     // (row = token), or, without one, into their zeroed output rows (rounded to the output type on the way).  One after the
     // other: the GEMV launch on the side stream, between a fork off the last base product and a join into the next, waits 10 us at
@@ -2742,7 +2761,12 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         tb.p[0] = bp;
         tb.group[0] = 1u << 8;
         choose_panels(c, q, pool_scratch(c), tb);
-        HIP_TRY(lora::launch_mfma_shrink(tb, st, tm));
+        HIP_TRY(lora::launch_mfma_shrink(tb, copies ? list_copy(p) : lora::ListCopy{}, st, tm));
+        if (copies) {
+            p->deferred = false;
+            p->copying = true;
+            p->upload_stream = st;
+        }
     }
     if (n_gemv_tok > 0) {
         a.y32 = static_cast<float *>(workspace);
@@ -2781,6 +2805,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
     }
     int32_t f;
     if (const int rc_f = take_fence(c, st, f)) return rc_f;
+    const CopyGuard guard{p, st};
     // Entries that do not depend on each other go as one batch: no output of the batch may overlap an input of it (an
     // earlier entry's: it may not have been read yet; a later one's: it would be read too early) or another output (both
     // would be updated from what was there before).  Within a batch neighbours that read the same x (q, k, v; gate, up)
@@ -2842,7 +2867,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
                 if (k > 0 && (k + group_n[at + k] > most || left < 0)) break;
             }
             const int rc = enqueue_batch(c, p, q, descs + i + at, group_n + at, k, scale, st, scratch, f >= 0 && i + at + k == n ? c->fences[f].ev : nullptr, f >= 0);
-            if (rc != LORA_OK) return after_failed_copy(p, st, rc);
+            if (rc != LORA_OK) return rc;
             at += k;
         }
         i += m;

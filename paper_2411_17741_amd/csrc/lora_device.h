@@ -165,4 +165,12 @@ template <int N> __device__ __forceinline__ void wait_requests()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The part of block `block` (of `threads` threads) in the copy of a plan's lists; nothing for blocks before the copy's
+__device__ __forceinline__ void copy_lists(const ListCopy &c, uint32_t block, uint32_t threads)
+{
+    if (block < c.first_block) return;
+    const uint32_t i = (block - c.first_block) * threads + threadIdx.x;
+    if (i < c.pieces) static_cast<uint4 *>(c.to)[i] = static_cast<const uint4 *>(c.from)[i];
+}
+
 }  // namespace lora

@@ -126,6 +126,9 @@ struct ListCopy {
     uint32_t pieces;   // of 16 bytes; 0: nothing to copy
     uint32_t first_block;
 };
+inline uint32_t copy_blocks(const ListCopy &c, uint32_t threads) { return (c.pieces + threads - 1) / threads; }
+// a pointer into the lists in the pool as one to the same place where the host wrote them
+template <typename T> inline const T *where_written(const ListCopy &c, const T *p) { return reinterpret_cast<const T *>(static_cast<const char *>(c.from) + (reinterpret_cast<const char *>(p) - static_cast<const char *>(c.to))); }
 
 // A batch: the projections one launch serves.  They do not depend on each other (no output overlaps another entry's
 // output or any entry's input), so that every phase is one launch for all of them.
@@ -543,7 +546,8 @@ template <typename K> hipError_t allow_lds(K *kernel, int bytes)
 }
 hipError_t prepare_mfma_kernels();
 hipError_t prepare_linear_kernels();
-hipError_t launch_mfma_shrink(const TileBatch &tb, hipStream_t st, const KernelTimer *tm);
+// copy (pieces 0: none): lists that the launch copies, as in the GEMV launches; tb's pointers are those into the pool
+hipError_t launch_mfma_shrink(const TileBatch &tb, const ListCopy &copy, hipStream_t st, const KernelTimer *tm);
 hipError_t launch_mfma_expand(const TileBatch &tb, hipStream_t st, const KernelTimer *tm, hipEvent_t done);
 // What lora_linear_plan's kernels read of a plan (device): the list of rows, its runs, the segments of the rows with an adapter
 // product (rows [0, add0)), and the rows [add0, add1) whose adapter term has been computed beforehand.

@@ -298,10 +298,13 @@ __device__ __forceinline__ ApplyArgs tile_args(const TileBatchArgs<N> &tb, int p
     return a;
 }
 
-template <int N>
+// Copy (of the three kernels of the shrink): nothing, or the ListCopy of lists that blocks behind the others copy
+template <int N, typename... Copy>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void mfma_shrink_kernel(const ShrinkCut *__restrict__ cuts, const DevItem *__restrict__ tiles, int runs_per_xcd, int n_proj, int quanta,
-                                                                                                        int n_tiles, TileBatchArgs<N> tb)
+                                                                                                        int n_tiles, TileBatchArgs<N> tb, Copy... copy)
 {
+    if constexpr (sizeof...(Copy) > 0)
+        if ((... || (blockIdx.x >= copy.first_block))) return (copy_lists(copy, blockIdx.x, 256), ...);
     // (the scalars in front are fields of tb: leading arguments arrive in registers with the wavefront)
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     unsigned char(*const xs)[LORA_TILE_TOKENS * XROW] = reinterpret_cast<unsigned char(*)[LORA_TILE_TOKENS * XROW]>(ring);
@@ -356,9 +359,11 @@ namespace {
 constexpr int DK = 64, DROW = DK * 2, DSTAGE = 32 * DROW, DRING = 4;  // 16 rows of x, 16 of At
 }  // namespace
 
-template <int N, int W>
-__global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArgs<N> tb)
+template <int N, int W, typename... Copy>
+__global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArgs<N> tb, Copy... copy)
 {
+    if constexpr (sizeof...(Copy) > 0)
+        if ((... || (blockIdx.x >= copy.first_block))) return (copy_lists(copy, blockIdx.x, 64 * W), ...);
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, g = lane >> 4;
@@ -616,9 +621,11 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
     }
 }
 
-template <int N>
-__global__ __launch_bounds__(512) void mfma_panel_kernel(const DevItem *panels, PanelClasses cls, PanelShape<N> sh, TileBatchArgs<N> tb)
+template <int N, typename... Copy>
+__global__ __launch_bounds__(512) void mfma_panel_kernel(const DevItem *panels, PanelClasses cls, PanelShape<N> sh, TileBatchArgs<N> tb, Copy... copy)
 {
+    if constexpr (sizeof...(Copy) > 0)
+        if ((... || (blockIdx.x >= copy.first_block))) return (copy_lists(copy, blockIdx.x, 512), ...);
     extern __shared__ __attribute__((aligned(16))) unsigned char ring[];
     int gi = 0;  // the first group whose blocks end behind this one (the groups of long rows come first)
 #pragma unroll
@@ -989,6 +996,11 @@ template <typename F> static void with_batch_size(const TileBatch &tb, F go)
     go(g);
 }
 
+static ListCopy copy_behind(ListCopy c, unsigned blocks)
+{
+    c.first_block = blocks;
+    return c;
+}
 template <int W> constexpr int direct_lds = W *DRING *DSTAGE;
 constexpr int SHRINK_LDS = NSTAGE * LORA_TILE_TOKENS * XROW;
 
@@ -997,8 +1009,12 @@ template <int N> static hipError_t prepare_shrinks()
 {
     hipError_t e = allow_lds(mfma_shrink_direct_kernel<N, 4>, direct_lds<4>);
     if (e == hipSuccess) e = allow_lds(mfma_shrink_direct_kernel<N, 8>, direct_lds<8>);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_direct_kernel<N, 4, ListCopy>, direct_lds<4>);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_direct_kernel<N, 8, ListCopy>, direct_lds<8>);
     if (e == hipSuccess) e = allow_lds(mfma_panel_kernel<N>, PANEL_RING);
+    if (e == hipSuccess) e = allow_lds(mfma_panel_kernel<N, ListCopy>, PANEL_RING);
     if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N>, SHRINK_LDS);
+    if (e == hipSuccess) e = allow_lds(mfma_shrink_kernel<N, ListCopy>, SHRINK_LDS);
     return e;
 }
 hipError_t prepare_mfma_kernels()
@@ -1008,7 +1024,7 @@ hipError_t prepare_mfma_kernels()
 }
 
 // k ranges are multiples of the 128-element stage.
-hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const KernelTimer *tm)
+hipError_t launch_mfma_shrink(const TileBatch &batch, const ListCopy &copy, hipStream_t st, const KernelTimer *tm)
 {
     if (batch.n_tiles <= 0 || batch.n <= 0) return hipSuccess;
     if (batch.n > BATCH_MAX_PROJS) return hipErrorInvalidValue;
@@ -1017,7 +1033,15 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
             constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
             auto go = [&](auto w_tag) {
                 constexpr int W = decltype(w_tag)::value;
-                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W>, dim3(tb.n_direct * tb.n), dim3(64 * W), direct_lds<W>, st, tb);
+                const unsigned blocks = (unsigned)(tb.n_direct * tb.n);
+                if (copy.pieces) {
+                    auto first = tb;  // (this launch reads the lists where the host wrote them)
+                    first.direct = where_written(copy, tb.direct), first.tok_list = where_written(copy, tb.tok_list);
+                    launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W, ListCopy>, dim3(blocks + copy_blocks(copy, 64 * W)), dim3(64 * W), direct_lds<W>, st, first,
+                             copy_behind(copy, blocks));
+                } else {
+                    launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_direct_kernel<N, W>, dim3(blocks), dim3(64 * W), direct_lds<W>, st, tb);
+                }
             };
             if (tb.n_direct * tb.n <= 256) go(std::integral_constant<int, 8>{});  // (a block to a compute unit)
             else go(std::integral_constant<int, 4>{});
@@ -1039,7 +1063,14 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
             }
             for (int g = groups; g < N; ++g) sh.end[g] = end, sh.group[g] = sh.group[groups - 1];
             for (int i = tb.n; i < N; ++i) sh.slices[i] = 1;
-            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N>, dim3(end), dim3(512), PANEL_RING, st, tb.panels, batch.classes, sh, tb);
+            if (copy.pieces) {
+                auto first = tb;
+                first.panels = where_written(copy, tb.panels), first.tok_list = where_written(copy, tb.tok_list);
+                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N, ListCopy>, dim3(end + copy_blocks(copy, 512)), dim3(512), PANEL_RING, st, first.panels, batch.classes, sh, first,
+                         copy_behind(copy, (unsigned)end));
+            } else {
+                launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_panel_kernel<N>, dim3(end), dim3(512), PANEL_RING, st, tb.panels, batch.classes, sh, tb);
+            }
             if (sums) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_panel_sum_kernel<N>, dim3(tb.n_panels * (PANEL_ROWS / 32), tb.n), dim3(256), 0, st, tb.panels, sh, tb);
         });
         return hipGetLastError();
@@ -1048,8 +1079,14 @@ hipError_t launch_mfma_shrink(const TileBatch &batch, hipStream_t st, const Kern
     if (batch.n_runs % 8 != 0 || batch.quanta < 1) return hipErrorInvalidValue;
     with_batch_size(batch, [&](const auto &tb) {
         constexpr int N = sizeof(tb.p) / sizeof(tb.p[0]);
-        launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), SHRINK_LDS, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n,
-                 tb.quanta, tb.n_tiles, tb);
+        if (copy.pieces) {
+            auto first = tb;
+            first.cuts = where_written(copy, tb.cuts), first.tiles = where_written(copy, tb.tiles), first.tok_list = where_written(copy, tb.tok_list);
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N, ListCopy>, dim3(tb.n_runs * tb.n + copy_blocks(copy, 256)), dim3(256), SHRINK_LDS, st, first.cuts, first.tiles, tb.n_runs / 8,
+                     tb.n, tb.quanta, tb.n_tiles, first, copy_behind(copy, (unsigned)(tb.n_runs * tb.n)));
+        } else {
+            launch_k(tm, nullptr, LORA_K_MFMA_SHRINK, mfma_shrink_kernel<N>, dim3(tb.n_runs * tb.n), dim3(256), SHRINK_LDS, st, tb.cuts, tb.tiles, tb.n_runs / 8, tb.n, tb.quanta, tb.n_tiles, tb);
+        }
         if (tb.any_pieces) launch_k(tm, nullptr, LORA_K_MFMA_REDUCE, mfma_reduce_kernel<N>, dim3(tb.n_tiles * 8, tb.n), dim3(256), 0, st, tb);
     });
     return hipGetLastError();

@@ -162,3 +162,75 @@ def test_other_first_uses():
             b.pool.check_fault()
         finally:
             b.pool.close()
+
+
+@pytest.mark.parametrize("small", [False, True])  # the run table's kernel where there are no panels
+@pytest.mark.parametrize("lens", [[16], [70, 200, 33], [900, 1, 1, 640, 17]])  # units of 16 tokens; with tokens that are no tiles; panels or the run table
+@pytest.mark.parametrize("first", ["apply", "list", "linear", "static", "captured"])
+def test_plans_with_tiles(first, lens, small):
+    """A plan with tiles: its lists travel with the tile shrink that is its first launch; everything behind it reads the copy."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    ranks, n, T, n_layers = [64, 128, 8, 33, 16], len(lens), sum(lens), 3
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    A, Bm = [normal(H, r, sigma=0.05) for r in ranks], [normal(r, H, sigma=0.05) for r in ranks]
+    x, base, W = normal(T, H), normal(T, H), normal(H, H, sigma=0.05)
+    pool = LoraPool([(H, H)], n_layers, [128], [5], B.LORA_BF16, max_tokens=T, max_segments=n, mfma_min_tokens=8, flags=B.LORA_CACHE_SMALL_SCRATCH if small else 0)
+    try:
+        for layer in range(n_layers):
+            for i, r in enumerate(ranks):
+                pool.fill(i, i + 1, r, 1.0, layer, 0, A[i].cpu(), Bm[i].cpu())
+        delta = torch.zeros(T, H, dtype=torch.float64, device="cuda")
+        for i in range(n):
+            a, b = int(off[i]), int(off[i + 1])
+            delta[a:b] = 2.0 * (x[a:b].double() @ A[i].double()) @ Bm[i].double()
+        st = torch.cuda.current_stream().cuda_stream
+        space = torch.empty(T * H, dtype=torch.float32, device="cuda")
+        plans = []
+        for turn in range(3):  # (the third plan lies where the first lay)
+            plan = pool.plan(T, off, np.arange(n, dtype=np.int32), np.asarray(ranks[:n], np.int32))
+            out = [base.clone() for _ in range(n_layers)]
+            ref = [base.double() + delta] * n_layers
+
+            def use(how):
+                if how == "apply":
+                    pool.apply_plan(plan, 0, 0, x, out[0], 2.0)
+                elif how == "static":
+                    B.check(B.lora_apply_plan_static(pool.handle, plan, 0, 0, x.data_ptr(), out[0].data_ptr(), 2.0, st))
+                elif how == "list":
+                    B.check(B.lora_apply_plan_multi(pool.handle, plan, B.make_descs([(l, 0, x.data_ptr(), out[l].data_ptr()) for l in range(n_layers)]), 2.0, st))
+                else:
+                    B.check(B.lora_linear_plan(pool.handle, plan, 0, 0, x.data_ptr(), W.data_ptr(), out[0].data_ptr(), 2.0, st, space.data_ptr(), space.numel() * 4))
+
+            if first == "captured":
+                graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+                torch.cuda.synchronize()
+                with torch.cuda.graph(graph, stream=stream):
+                    pool.apply_plan(plan, 0, 0, x, out[0], 2.0, stream=stream)
+                for _ in range(3):
+                    out[0].copy_(base)
+                    graph.replay()
+                    torch.cuda.synchronize()
+            else:
+                use(first)
+            count = n_layers if first == "list" else 1
+            if first == "linear":
+                ref = [x.double() @ W.double().T + delta]
+            for y, r in zip(out[:count], ref):
+                rel = float((y.double() - r).norm() / r.norm())
+                assert rel < 4e-3, (turn, rel)  # the rounding of the output and of s.v, 2^-9 each on the mean and more
+            again = [y.clone() for y in out]
+            for y in out:
+                y.copy_(base)
+            use("apply" if first == "captured" else first)  # out of the copied lists: the same bits
+            for y, z in zip(out[:count], again):
+                assert torch.equal(y, z)
+            if len(plans) == 1:
+                pool.plan_destroy(plans.pop())
+            plans.append(plan)
+        pool.check_fault()
+    finally:
+        pool.close()
