@@ -184,9 +184,16 @@ def _i32(a) -> np.ndarray:
     return np.ascontiguousarray(a, dtype=np.int32)
 
 
+_from_buffer, _addressof = ctypes.c_char.from_buffer, ctypes.addressof
+
+
 def _ptr(a: np.ndarray) -> int:
-    """Address of an array's first element (a ctypes pointer made by numpy costs 2 us a piece, a tenth of a small batch's call)."""
-    return a.__array_interface__["data"][0]
+    """Address of an array's first element.  A small batch's call hands over three of them: a ctypes pointer made by numpy costs 2 us a piece, the array interface 0.95, the buffer's address 0.3
+    (16 fp32 tokens in one call 12.4 -> 11.3 us, 10.9 -> 9.9 in a faster process); empty and read-only arrays have no such buffer."""
+    try:
+        return _addressof(_from_buffer(a))
+    except (TypeError, ValueError):
+        return a.__array_interface__["data"][0]
 
 
 def make_config(proj: Sequence[Sequence[int]], n_layers: int, class_rank: Sequence[int], class_slots: Sequence[int],
