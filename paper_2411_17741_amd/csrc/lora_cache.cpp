@@ -84,7 +84,7 @@ constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // model 25.7 and 20.9; a prompt of 77 tokens call by call 271 and 255).  With more wavefronts, wide items or tiles the lists are uploaded ahead of it (64 requests on q of 32 layers, 65000 wavefronts).
 constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
 // So too a tile shrink of up to so many tiles over its projections, all the lists of a plan being copied then: eight prompts on q of eight layers 190.5 -> 187.1 us a pass, the 13B batch
-// 834 -> 828, its base products 1701 -> 1694.
+// 834 -> 828, its base products 1701 -> 1694; lora_apply on a prompt of 1200 tokens of rank 32, four calls 94 -> 73, on eight prompts 193 -> 182.
 constexpr int64_t PINNED_LISTS_MAX_TILES = 2048;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
@@ -1176,7 +1176,8 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
     if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (!c.host_only && c.fencing && !p.internal && (few_waves || p.n_tiles > 0) && bytes && c.n_user_plans > 1 && c.side_stream) {  // (one plan alone would have to wait for its own launch before it is made anew)
+    } else if (!c.host_only && c.fencing && c.side_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || c.n_user_plans > 1)) {
+        // (one plan alone would have to wait for its own launch before it is made anew)
         p.deferred = true;
     } else if (!c.host_only && bytes) {
         HIP_TRY(upload_lists(c, p, st));

@@ -234,3 +234,26 @@ def test_plans_with_tiles(first, lens, small):
         pool.check_fault()
     finally:
         pool.close()
+
+
+def test_one_call_with_tiles():
+    """lora_apply on batches with tiles, call after call with nothing in between: its plans' memory goes round every four calls."""
+    b = Batch()
+    try:
+        rng = np.random.default_rng(5)
+        done = []
+        for i in range(14):
+            lens = rng.integers(1, 90, rng.integers(1, 4))
+            slot = rng.permutation(9)[: len(lens)].astype(np.int32)
+            T = int(lens.sum())
+            x, base = b.x[:T].contiguous(), b.normal(T, H)
+            y = base.clone()
+            off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+            b.pool.apply(i % N_L, 0, x, y, off, slot, np.asarray(b.ranks, np.int32)[slot], 2.0)
+            done.append((y, base, np.repeat(slot, lens)))
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        for y, base, slots in done:
+            b.close_to(y, b.expect(base, slots))
+    finally:
+        b.pool.close()
