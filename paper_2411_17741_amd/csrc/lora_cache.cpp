@@ -220,10 +220,9 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     hipEvent_t ev_upload = nullptr;
     bool upload_pending = false;
     // Lists that are still where the host wrote them alone (`deferred`): the first launch that works through them copies them, and reads them there.  That launch is covered by
-    // the fence of its call (upload_fence, -1: none), on upload_stream
+    // the fence of its call (upload_fence, -1: none); copying: enqueued by the call that runs now, whose fence is not published yet
     bool deferred = false, copying = false;
     int32_t upload_fence = -1;
-    hipStream_t upload_stream = nullptr;
     int32_t last_use = -1;  // fence of the latest call that used the plan
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     size_t bytes = 0;           // of these lists
@@ -2502,9 +2501,8 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
     };
     if (p->upload_pending) HIP_TRY(wait(p->ev_upload, p->upload_pending));
     if (p->upload_fence >= 0) {
-        if (capturing < 0) capturing = is_capturing(st);
         bool pending = true;
-        if (capturing || st != p->upload_stream) HIP_TRY(wait(c->fences[p->upload_fence].ev, pending));
+        HIP_TRY(wait(c->fences[p->upload_fence].ev, pending));
         if (!pending) hold_fence(*c, p->upload_fence, -1);
     }
     for (int32_t sl : p->slots) {
@@ -2591,7 +2589,6 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         if (!copies) return;
         p->deferred = false;
         p->copying = true;  // until a fence stands for it
-        p->upload_stream = st;
     };
     if (q->n_tiles > 0) {
         HIP_TRY(lora::launch_mfma_shrink(tb, copy, st, tm));
@@ -2766,7 +2763,6 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         if (copies) {
             p->deferred = false;
             p->copying = true;
-            p->upload_stream = st;
         }
     }
     if (n_gemv_tok > 0) {
