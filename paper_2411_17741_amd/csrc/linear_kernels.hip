@@ -24,7 +24,8 @@
 // later, before anybody reads (or overwrites) that half.
 // Measured on 4096 x 4096 x 4096 (one round of 256 blocks): 129.5 us with all wavefronts in step, 98.5 us this way;
 // 8192 x 8192 x 8192: 934 -> 710 us (1.55 PFLOP/s; the vendor library's product 766 us).  With all units busy the stages take 1.38 us, with 64 of them
-// 0.91 us, the products' own time: what the card sustains then bounds the loop, not its schedule.  Four phases of 16 products
+// 0.91 us, the products' own time: what the card sustains then bounds the loop, not its schedule.  It is power: the same launches on zeros
+// take 485 us at 8192 x 8192 x 8192 (2.27 PFLOP/s; 689 on normal values, same card) and 66 at 4096 x 4096 x 4096 (91).  Four phases of 16 products
 // take 107 us, operand reads spread evenly over the phases 98 us, requests from the product section 102 us.
 //
 // LDS rows are 128 bytes without padding; bank conflicts are avoided by a swizzle instead: 16-byte slot s of row r

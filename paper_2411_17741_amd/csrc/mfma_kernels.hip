@@ -457,7 +457,7 @@ __global__ __launch_bounds__(64 * W) void mfma_shrink_direct_kernel(TileBatchArg
 // the rank blocks: with all of them per wavefront and two row blocks each, the operand reads out of LDS took longer than the loads (7B mixed batch 491 us, 443 this way).
 // What it takes in from behind L2 bounds it: eight prompts on q of eight layers, 281 MB of x and 122 of At, 76 us; x alone 55 to 58, without products 75; one stage less on its way, or more of x by
 // rings of their own for x and At, gains nothing, whole 256-byte pieces of the rows take longer (68 us for x alone).
-// 192 rows: with 256 three projections of rank 64 leave no room for three stages.  The panels are dealt out to the XCDs one by one, the costliest first: in runs of neighbours per XCD, as
+// 192 rows: with 256 three projections of rank 64 leave no room for three stages.  The panels are dealt out to the XCDs two neighbours at a time, the costliest first: in runs of neighbours per XCD, as
 // the kernel above takes its tiles, some XCDs got most of the rank-128 panels (443 -> 338 us); a panel's blocks, if it has several, run side by side on one XCD.
 // Measured, shrink and reduce of a launch, run table -> panels: 7B mixed batch (14 projections) 491 -> 338 us, eight prompts on q of eight layers 89 -> 75, 13B batch 100 -> 82;
 // q, k, v of 17650 tokens in 100 prompts 99.6 -> 78.8, of 8485 in 20 prompts 45 -> 38 (three slices); one projection of 4291 tokens 20.2 -> 19.3 (six slices).
