@@ -279,6 +279,8 @@ struct lora_cache {
     // and a join event (default priority, like every stream here)
     hipStream_t side_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    // Uploads that a captured call needs and that must not become part of the graph.  Not the side stream's: one that a captured call has forked to stays in the capture until that ends, joined or not
+    hipStream_t upload_stream = nullptr;
     int device = 0;  // the device that was current at lora_cache_create
     int n_cu = 256;  // its compute units
     bool fencing = true;
@@ -1175,7 +1177,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
     if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (!c.host_only && c.fencing && c.side_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || c.n_user_plans > 1)) {
+    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || c.n_user_plans > 1)) {
         // (one plan alone would have to wait for its own launch before it is made anew)
         p.deferred = true;
     } else if (!c.host_only && bytes) {
@@ -1358,6 +1360,7 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         fail(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
         fail(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
         fail(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
+        fail(hipStreamCreateWithFlags(&c->upload_stream, hipStreamNonBlocking));
     }
     if (rc != LORA_OK) {
         lora_cache_destroy(c);
@@ -1383,6 +1386,7 @@ int lora_cache_destroy(lora_cache_t *c)
         if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
         if (c->ev_join) (void)hipEventDestroy(c->ev_join);
         if (c->side_stream) (void)hipStreamDestroy(c->side_stream);
+        if (c->upload_stream) (void)hipStreamDestroy(c->upload_stream);
         if (c->fault_host) (void)hipHostFree(c->fault_host);
         for (auto &s : c->slots)
             if (s.fill_ev) (void)hipEventDestroy(s.fill_ev);
@@ -2475,7 +2479,7 @@ static const PlanLists *pick_linear_lists(const lora_cache_t *c, const lora_plan
 // What a call needs of other streams: the plan's lists and its slots' weights.  A captured call waits here, on the host: a wait on an event from outside the capture does not become
 // part of the graph, whose replays may run before that event.  (The event of a stream that is not the null stream can be asked about and waited for while this thread captures
 // only in relaxed mode; elsewhere the capture is invalidated.)
-// copies: the launch this is for copies the plan's lists itself; else lists that are still with the host are uploaded here (for a captured call on the side stream: the upload is no part of the graph).
+// copies: the launch this is for copies the plan's lists itself; else lists that are still with the host are uploaded here (for a captured call on a stream that is in no capture: the upload is no part of the graph).
 static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool copies)
 {
     int capturing = -1;  // not known yet
@@ -2485,7 +2489,7 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
         capturing = is_capturing(st);
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return LORA_E_HIP;
-        const hipError_t e = upload_lists(*c, *p, capturing ? c->side_stream : st);
+        const hipError_t e = upload_lists(*c, *p, capturing ? c->upload_stream : st);
         if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
         HIP_TRY(e);
     }

@@ -257,3 +257,74 @@ def test_one_call_with_tiles():
             b.close_to(y, b.expect(base, slots))
     finally:
         b.pool.close()
+
+
+def test_two_plans_in_one_capture():
+    """Two plans first used in one capture, the first by a batch whose GEMV launch is forked to the side stream (4 GB of tile tokens' activations and outputs and more), which is in
+    the capture from then on; the second plan called before any replay, and replays beside eager calls."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    h, n_layers, prompt, rank = 8192, 32, 2700, 16
+    assert prompt * 2 * n_layers * 3 * h >= 4e9
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    normal = lambda *s, sigma=1.0: torch.randn(*s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    T = prompt + 4
+    pool = LoraPool([(h, h)], n_layers, [rank], [3], B.LORA_BF16, max_tokens=T, max_segments=8, n_plans=4)
+    try:
+        A, Bm = [normal(h, rank, sigma=0.02) for _ in range(3)], [normal(rank, h, sigma=0.05) for _ in range(3)]
+        for i in range(3):
+            a, b = A[i].cpu(), Bm[i].cpu()
+            for layer in range(n_layers):
+                pool.fill(i, i + 1, rank, 1.0, layer, 0, a, b)
+        x = normal(T, h)
+        large, small = torch.zeros(n_layers, T, h, dtype=torch.bfloat16, device="cuda"), torch.zeros(5, h, dtype=torch.bfloat16, device="cuda")
+        torch.cuda.synchronize()
+        p1 = pool.plan(T, [0, prompt, T - 3, T - 2, T - 1, T], [0, 1, 2, 1, 2], [rank] * 5)
+        p2 = pool.plan(5, [0, 1, 2, 3, 4, 5], [2, 1, 0, 2, 1], [rank] * 5)
+        descs = B.make_descs([(layer, 0, x.data_ptr(), large[layer].data_ptr()) for layer in range(n_layers)])
+
+        def go(st, which=3):
+            if which & 1:
+                B.check(B.lora_apply_plan_multi(pool.handle, p1, descs, 2.0, st))
+            if which & 2:
+                pool.apply_plan(p2, 3, 0, x[:5], small, 2.0, stream=torch.cuda.ExternalStream(st) if st else None)
+
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.stream(stream):
+            graph.capture_begin(capture_error_mode="thread_local")
+            go(stream.cuda_stream)
+            graph.capture_end()
+        now = torch.cuda.current_stream().cuda_stream
+        go(now, 2)  # (before any replay)
+        torch.cuda.synchronize()
+        ref = torch.stack([2.0 * (x[t].double() @ A[s].double()) @ Bm[s].double() for t, s in enumerate([2, 1, 0, 2, 1])])
+        assert float((small.double() - ref).norm() / ref.norm()) < 4e-3  # the roundings of the output and of s.v
+        want_small = small.clone()
+        for i in range(3):
+            large.zero_(), small.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            if i == 0:
+                got = large.clone()
+            assert torch.equal(small, want_small) and torch.equal(large, got)
+            small.zero_()
+            go(now, 2)
+            torch.cuda.synchronize()
+            assert torch.equal(small, want_small)
+        large.zero_()
+        go(now, 1)
+        torch.cuda.synchronize()
+        pool.check_fault()
+        assert torch.equal(large, got)  # captured and eager: the same bits
+        B.lora_cache_set_timing(pool.handle, 1)
+        go(now, 1)
+        torch.cuda.synchronize()
+        rc, t = B.lora_cache_read_timing(pool.handle)
+        assert rc == B.LORA_OK and t["mfma_expand"][1] == 1 and t["gemv_fused"][1] >= 1, t  # one batch of them all
+        for layer in (0, n_layers - 1):
+            for t0, t1, s in ((0, prompt, 0), (prompt, T - 3, 1), (T - 3, T - 2, 2)):
+                r = 2.0 * (x[t0:t1].double() @ A[s].double()) @ Bm[s].double()
+                assert float((got[layer, t0:t1].double() - r).norm() / r.norm()) < 4e-3
+    finally:
+        pool.close()
