@@ -281,7 +281,10 @@ void lora_worklists_free(lora_worklists_t *w);
  * be applied to every projection of every layer of the iteration.  Checks every named
  * slot against the slot table (exists, bound, seg_rank equals its rank).  The upload is
  * enqueued on `stream`, or part of the first launch that works through the lists, as the plan's size
- * and the cache's options have it; the host arrays may be reused on return. */
+ * and the cache's options have it; the host arrays may be reused on return.
+ * Plans take turns in the memory of the cache's n_plans plans.  Blocks the host while the lists that lay there before
+ * are still on their way: until their upload is done or, where they travelled with a launch, the call it was part of; they travel so only
+ * if another plan was free when theirs was made. */
 int lora_plan_create(lora_cache_t *c, int32_t T, const int32_t *seg_offsets, const int32_t *seg_slot,
                      const int32_t *seg_rank, int32_t n_seg, void *stream, lora_plan_t **out);
 int lora_plan_destroy(lora_cache_t *c, lora_plan_t *p);

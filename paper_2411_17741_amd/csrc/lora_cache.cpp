@@ -1027,6 +1027,13 @@ bool some_launch_takes_tiles(const lora_cache &c, const lora_plan &p)
     return false;
 }
 
+// Is there a user plan to make next while the lists of `p` travel with a call?  Where `p` is the only one that is not held, making it anew would have to wait for that call, and
+// host and device would take turns; an upload ahead of the call is long done by then.
+bool another_free(const lora_cache &c, const lora_plan &p)
+{
+    return std::any_of(c.plans.begin(), c.plans.begin() + c.n_user_plans, [&](const lora_plan &q) { return &q != &p && !q.in_use; });
+}
+
 // The upload of a plan's lists on `st`, behind what may still read those that lie there.
 hipError_t upload_lists(lora_cache &c, lora_plan &p, hipStream_t st)
 {
@@ -1177,8 +1184,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
     if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || c.n_user_plans > 1)) {
-        // (one plan alone would have to wait for its own launch before it is made anew)
+    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || another_free(c, p))) {
         p.deferred = true;
     } else if (!c.host_only && bytes) {
         HIP_TRY(upload_lists(c, p, st));

@@ -328,3 +328,41 @@ def test_two_plans_in_one_capture():
                 assert float((got[layer, t0:t1].double() - r).norm() / r.norm()) < 4e-3
     finally:
         pool.close()
+
+
+@pytest.mark.parametrize("held", [1, 3])
+def test_the_only_free_plan(held):
+    """All plans but one are held: making that one again and again does not wait for the calls that used it last."""
+    b = Batch(n_plans=held + 1)
+    try:
+        keep = [b.pool.plan(*b.segs([i])) for i in range(held)]
+        busy, stream = torch.randn(4096, 4096, device="cuda"), torch.cuda.Stream()
+        out = []
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            for i in range(3):
+                slots = (np.arange(20 + i) * (i + 1)) % 9
+                base = b.normal(len(slots), H)
+                x, y = b.x[: len(slots)].contiguous(), base.clone()
+                plan = b.pool.plan(*b.segs(slots))
+                if i == 0:  # (its upload is not behind this)
+                    for _ in range(60):
+                        busy @ busy
+                b.pool.apply_plan(plan, 0, 0, x, y, 2.0)
+                b.pool.plan_destroy(plan)
+                out.append((x, y, base, slots))
+                if i == 0:
+                    plan = b.pool.plan(*b.segs(slots))
+                    assert not stream.query()  # the call is still to come
+                    b.pool.plan_destroy(plan)
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        for _x, y, base, slots in out:
+            b.close_to(y, b.expect(base, slots))
+        for i, plan in enumerate(keep):
+            base = b.normal(1, H)
+            y = base.clone()
+            b.pool.apply_plan(plan, 1, 0, b.x[:1].contiguous(), y, 2.0)
+            b.close_to(y, b.expect(base, [i]))
+    finally:
+        b.pool.close()
