@@ -224,6 +224,7 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     bool deferred = false, copying = false;
     int32_t upload_fence = -1;
     int32_t last_use = -1;  // fence of the latest call that used the plan
+    bool unfenced = false;  // calls without a fence (captured, or with fencing off) have read lists in dev, and no upload in the order of a caller's stream has come since
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     size_t bytes = 0;           // of these lists
     // Where a call for one projection leaves the tokens that could be tiles to the GEMV kernels, launches that share the tile path's fixed cost, and the base product, which needs
@@ -1184,10 +1185,12 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
     if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || another_free(c, p))) {
+    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || another_free(c, p)) && !p.unfenced) {
+        // (what calls without a fence, a graph's replays say, may still read there is overwritten in the order of `st` and no other)
         p.deferred = true;
     } else if (!c.host_only && bytes) {
         HIP_TRY(upload_lists(c, p, st));
+        p.unfenced = false;
     }
     return LORA_OK;
 }
@@ -2646,10 +2649,13 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
 
 // The event that is to stand for the end of a call that enqueues applies on `st`: fills that come later and uploads
 // into the same plan wait for it.  None (-1) without fencing and under capture.
-static int take_fence(lora_cache_t *c, hipStream_t st, int32_t &f)
+static int take_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32_t &f)
 {
     f = -1;
-    if (!c->fencing || is_capturing(st)) return LORA_OK;
+    if (!c->fencing || is_capturing(st)) {
+        p->unfenced = true;
+        return LORA_OK;
+    }
     f = free_fence(*c);
     return f < 0 ? LORA_E_HIP : LORA_OK;
 }
@@ -2681,7 +2687,7 @@ struct CopyGuard {
 static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t &d, float scale, hipStream_t st, const Scratch &sc)
 {
     int32_t f;
-    if (const int rc = take_fence(c, st, f)) return rc;
+    if (const int rc = take_fence(c, p, st, f)) return rc;
     const CopyGuard guard{p, st};
     const uint8_t one = 1;
     if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return rc;
@@ -2754,7 +2760,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     a.v_stride = c->v_stride;
     a.scale = scale;
     int32_t f;
-    if (const int rc_f = take_fence(c, st, f)) return rc_f;
+    if (const int rc_f = take_fence(c, p, st, f)) return rc_f;
     const CopyGuard guard{p, st};
     const bool copies = p->deferred && f >= 0 && !c->timing && shrink_copies(q, 1, a.h_in);  // (as in enqueue_batch)
     if (const int rc_w = wait_for_inputs(c, p, st, copies)) return rc_w;
@@ -2811,7 +2817,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         if (rc != LORA_OK) return rc;
     }
     int32_t f;
-    if (const int rc_f = take_fence(c, st, f)) return rc_f;
+    if (const int rc_f = take_fence(c, p, st, f)) return rc_f;
     const CopyGuard guard{p, st};
     // Entries that do not depend on each other go as one batch: no output of the batch may overlap an input of it (an
     // earlier entry's: it may not have been read yet; a later one's: it would be read too early) or another output (both

@@ -366,3 +366,43 @@ def test_the_only_free_plan(held):
             b.close_to(y, b.expect(base, [i]))
     finally:
         b.pool.close()
+
+
+@pytest.mark.parametrize("how", ["captured", "static"])
+def test_memory_that_a_graph_reads(how):
+    """A graph's replay is still to come on the stream that the plan's memory is made anew on; the new plan is first used on another stream, by a capture or with scratch of its own."""
+    b = Batch(n_plans=3)
+    try:
+        slots, other = np.arange(40) % 9, (np.arange(37) * 5 + 1) % 9
+        x, busy = b.x[:40].contiguous(), torch.randn(4096, 4096, device="cuda")
+        base, base2 = b.normal(40, H), b.normal(37, H)
+        y, y2 = base.clone(), base2.clone()
+        s1, s2, graph, graph2 = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        plan = b.pool.plan(*b.segs(slots), stream=s1)
+        with torch.cuda.graph(graph, stream=s1):
+            b.pool.apply_plan(plan, 0, 0, x, y, 2.0, stream=s1)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s1):
+            for _ in range(60):
+                busy @ busy
+            graph.replay()
+        b.pool.plan_destroy(plan)
+        for _ in range(2):  # the other two
+            b.pool.plan_destroy(b.pool.plan(*b.segs(slots), stream=s1))
+        plan2 = b.pool.plan(*b.segs(other), stream=s1)
+        assert plan2.value == plan.value and not s1.query()
+        if how == "captured":
+            with torch.cuda.stream(s2):
+                graph2.capture_begin(capture_error_mode="thread_local")
+                b.pool.apply_plan(plan2, 1, 0, x[:37], y2, 2.0, stream=s2)
+                graph2.capture_end()
+                graph2.replay()
+        else:
+            b.B.check(b.B.lora_apply_plan_static(b.pool.handle, plan2, 1, 0, x.data_ptr(), y2.data_ptr(), 2.0, s2.cuda_stream))
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        b.close_to(y, b.expect(base, slots))
+        b.close_to(y2, b.expect(base2, other))
+    finally:
+        b.pool.close()
