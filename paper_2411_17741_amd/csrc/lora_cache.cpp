@@ -223,7 +223,7 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     // the fence of its call (upload_fence, -1: none); copying: enqueued by the call that runs now, whose fence is not published yet
     bool deferred = false, copying = false;
     int32_t upload_fence = -1;
-    int32_t last_use = -1;  // fence of the latest call that used the plan
+    int32_t last_use[2] = {-1, -1};  // fences of the latest calls that used the plan, with the pool's scratch and with the fixed one (they may overlap)
     bool unfenced = false;  // calls without a fence (captured, or with fencing off) have read lists in dev, and no upload in the order of a caller's stream has come since
     int32_t mfma_min_used = 0;  // the threshold the work lists were made with
     size_t bytes = 0;           // of these lists
@@ -1035,14 +1035,24 @@ bool another_free(const lora_cache &c, const lora_plan &p)
     return std::any_of(c.plans.begin(), c.plans.begin() + c.n_user_plans, [&](const lora_plan &q) { return &q != &p && !q.in_use; });
 }
 
+// What is enqueued on `st` from here on comes behind the calls that may still read the lists in p.dev.
+hipError_t wait_for_uses(lora_cache &c, const lora_plan &p, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    for (int32_t f : p.last_use)
+        if (f >= 0 && e == hipSuccess) e = hipStreamWaitEvent(st, c.fences[f].ev, 0);
+    return e;
+}
+void forget_uses(lora_cache &c, lora_plan &p)
+{
+    for (int32_t &f : p.last_use) hold_fence(c, f, -1);
+}
+
 // The upload of a plan's lists on `st`, behind what may still read those that lie there.
 hipError_t upload_lists(lora_cache &c, lora_plan &p, hipStream_t st)
 {
-    if (p.last_use >= 0) {
-        const hipError_t e = hipStreamWaitEvent(st, c.fences[p.last_use].ev, 0);
-        if (e != hipSuccess) return e;
-        hold_fence(c, p.last_use, -1);
-    }
+    if (const hipError_t e = wait_for_uses(c, p, st)) return e;
+    forget_uses(c, p);
     const hipError_t e = lora::launch_upload(p.dev, p.pinned_dev, p.bytes + p.tiled_bytes, st, p.ev_upload);
     p.upload_pending |= e == hipSuccess;
     p.deferred = e != hipSuccess;
@@ -1159,13 +1169,10 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
         hold_fence(c, p.upload_fence, -1);
     }
     p.deferred = false;
-    if (!c.host_only && p.lists == p.pinned_dev && p.last_use >= 0) {  // an earlier apply may still be reading it there
-        const hipError_t e = hipEventSynchronize(c.fences[p.last_use].ev);
-        if (e != hipSuccess) {
-            g_last_hip = (int)e;
-            return LORA_E_HIP;
-        }
-        hold_fence(c, p.last_use, -1);
+    if (!c.host_only && p.lists == p.pinned_dev) {  // an earlier apply may still be reading it there
+        for (int32_t f : p.last_use)
+            if (f >= 0) HIP_TRY(hipEventSynchronize(c.fences[f].ev));
+        forget_uses(c, p);
     }
     lists.write(c, p, p.pinned);
     p.bytes = bytes;
@@ -1359,8 +1366,8 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         fail(hipEventCreateWithFlags(&c->stage[i].ev, hipEventDisableTiming));
     }
     std::fill(c->ring, c->ring + N_APPLY_EVENTS, -1);
-    // what the ring, the plans (their latest use, the copy of their lists) and a few streams hold; more streams, more events
-    for (size_t i = 0; i < N_APPLY_EVENTS + 2 * c->plans.size() + 8 && rc == LORA_OK; ++i) {
+    // what the ring, the plans (their latest uses, the copy of their lists) and a few streams hold; more streams, more events
+    for (size_t i = 0; i < N_APPLY_EVENTS + 3 * c->plans.size() + 8 && rc == LORA_OK; ++i) {
         hipEvent_t ev = nullptr;
         fail(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
         if (ev) c->fences.push_back({ev, 0});
@@ -2493,7 +2500,7 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
 {
     int capturing = -1;  // not known yet
     if (copies) {
-        if (p->last_use >= 0) HIP_TRY(hipStreamWaitEvent(st, c->fences[p->last_use].ev, 0));  // (what may still read the lists that lie there)
+        HIP_TRY(wait_for_uses(*c, *p, st));
     } else if (p->deferred) {
         capturing = is_capturing(st);
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -2659,14 +2666,14 @@ static int take_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32_t &
     f = free_fence(*c);
     return f < 0 ? LORA_E_HIP : LORA_OK;
 }
-static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32_t f)
+static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32_t f, bool fixed_scratch = false)
 {
     if (f < 0) return;
     const int64_t seq = c->apply_seq;
     hold_fence(*c, c->ring[seq % N_APPLY_EVENTS], f);
     c->ring_seq[seq % N_APPLY_EVENTS] = seq;
     hold_fence(*c, c->stream_fence.try_emplace(st, -1).first->second, f);
-    hold_fence(*c, p->last_use, f);
+    hold_fence(*c, p->last_use[fixed_scratch], f);
     if (p->copying) {
         p->copying = false;
         hold_fence(*c, p->upload_fence, f);
@@ -2691,7 +2698,7 @@ static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t
     const CopyGuard guard{p, st};
     const uint8_t one = 1;
     if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return rc;
-    publish_fence(c, p, st, f);
+    publish_fence(c, p, st, f, sc.small);
     return LORA_OK;
 }
 

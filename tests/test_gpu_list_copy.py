@@ -406,3 +406,38 @@ def test_memory_that_a_graph_reads(how):
         b.close_to(y2, b.expect(base2, other))
     finally:
         b.pool.close()
+
+
+@pytest.mark.parametrize("n_plans", [1, 2])  # the new lists uploaded; copied by a launch
+def test_a_call_with_fixed_scratch_still_to_come(n_plans):
+    """A plan's latest call is over, one before it with scratch of its own is still to come on another stream: the next plan in its memory leaves it its lists."""
+    b = Batch(n_plans=n_plans)
+    try:
+        slots, other = np.arange(40) % 9, (np.arange(37) * 5 + 1) % 9
+        x, busy = b.x[:40].contiguous(), torch.randn(4096, 4096, device="cuda")
+        base = b.normal(40, H)
+        y = [base.clone() for _ in range(4)]
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        plan = b.pool.plan(*b.segs(slots), stream=s2)
+        torch.cuda.synchronize()
+        b.pool.apply_plan(plan, 0, 0, x, y[0], 2.0, stream=s2)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s1):
+            for _ in range(60):
+                busy @ busy
+        b.B.check(b.B.lora_apply_plan_static(b.pool.handle, plan, 1, 0, x.data_ptr(), y[1].data_ptr(), 2.0, s1.cuda_stream))
+        b.pool.apply_plan(plan, 2, 0, x, y[2], 2.0, stream=s2)
+        s2.synchronize()
+        b.pool.plan_destroy(plan)
+        for _ in range(n_plans - 1):
+            b.pool.plan_destroy(b.pool.plan(*b.segs(slots), stream=s2))
+        again = b.pool.plan(*b.segs(other), stream=s2)
+        assert again.value == plan.value and not s1.query()
+        b.pool.apply_plan(again, 3, 0, x[:37], y[3][:37], 2.0, stream=s2)
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        for i in range(3):
+            b.close_to(y[i], b.expect(base, slots))
+        b.close_to(y[3][:37], b.expect(base[:37], other))
+    finally:
+        b.pool.close()
