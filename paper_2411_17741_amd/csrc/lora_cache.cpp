@@ -108,7 +108,7 @@ struct Scratch {
     int n_sets;
     char *vpart;
     int64_t vpart_rows;        // rows of the partial-sum scratch, shared by the projections of a group
-    bool small;                // the scratch holds the partial sums of the small run table only
+    bool small;                // the fixed scratch, which holds the partial sums of the small run table only
     char *vtag;                // hand-over words of the GEMV phases, one set per projection of a group
     size_t vtag_set_bytes;
     uint32_t *epoch;           // host counter of the one-launch GEMV launches that have used vtag
@@ -166,6 +166,7 @@ struct Slot {
     float alpha = 1.f;
     int32_t refcount = 0;
     int64_t use_count = 0, last_used = 0;
+    int64_t last_by[2] = {0, 0};  // last_used by calls with the pool's scratch and by those with the fixed one (they may overlap)
     double req_freq = 0;   // requests that used the entry, halved every policy.freq_window requests
     int64_t req_last = 0;  // number of the last such request
     uint32_t generation = 0;  // bumped whenever the slot is bound to another adapter or evicted
@@ -1202,18 +1203,21 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     return LORA_OK;
 }
 
-// Makes `st` wait for every apply enqueued so far that named the slot.  The fence of the call that
-// used it last sits in a ring; once that entry has been taken over by a later call, the latest fence
+// Makes `st` wait for every apply enqueued so far that named the slot.  The fences of the calls that
+// used it last (with either scratch) sit in a ring; once such an entry has been taken over by a later call, the latest fence
 // of every stream that ever ran applies stands in (stream order covers the older ones).
 int wait_for_applies(lora_cache &c, const Slot &s, hipStream_t st)
 {
-    if (!c.fencing || s.last_used <= 0) return LORA_OK;
-    const int e = (int)(s.last_used % N_APPLY_EVENTS);
-    if (c.ring_seq[e] == s.last_used) {
-        HIP_TRY(hipStreamWaitEvent(st, c.fences[c.ring[e]].ev, 0));
-    } else {
-        for (const auto &kv : c.stream_fence) HIP_TRY(hipStreamWaitEvent(st, c.fences[kv.second].ev, 0));
+    if (!c.fencing) return LORA_OK;
+    bool all = false;
+    for (int64_t used : s.last_by) {
+        const int e = (int)(used % N_APPLY_EVENTS);
+        if (used <= 0) continue;
+        if (c.ring_seq[e] == used) HIP_TRY(hipStreamWaitEvent(st, c.fences[c.ring[e]].ev, 0));
+        else all = true;
     }
+    if (all)
+        for (const auto &kv : c.stream_fence) HIP_TRY(hipStreamWaitEvent(st, c.fences[kv.second].ev, 0));
     return LORA_OK;
 }
 
@@ -2645,7 +2649,7 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         const int64_t seq = ++c->apply_seq;
         ++c->stats.applies;
         for (int32_t sl : p->slots) {
-            c->slots[sl].last_used = seq;
+            c->slots[sl].last_used = c->slots[sl].last_by[sc.small] = seq;
             ++c->slots[sl].use_count;
         }
     }
@@ -2807,7 +2811,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     const int64_t seq = ++c->apply_seq;
     ++c->stats.applies;
     for (int32_t sl : p->slots) {
-        c->slots[sl].last_used = seq;
+        c->slots[sl].last_used = c->slots[sl].last_by[0] = seq;
         ++c->slots[sl].use_count;
     }
     publish_fence(c, p, st, f);

@@ -49,3 +49,42 @@ def test_upload_and_refill_wait_for_applies_on_another_stream(lens, m0, timed):
             pool.close()
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
     assert outs[0][0].abs().max() > 0 and outs[0][1].abs().max() > 0
+
+
+def test_refill_waits_for_a_call_with_fixed_scratch_still_to_come():
+    """The slot's latest apply is over, one before it with scratch of its own is still to come on another stream: a refill leaves it its weights."""
+    from paper_2411_17741_amd import binding as B
+    from paper_2411_17741_amd.pool import LoraPool
+
+    h, T, rank = 512, 24, 16
+    gen = torch.Generator().manual_seed(4)
+    A, Bm = ([torch.randn(*s, generator=gen).mul_(0.05).bfloat16().pin_memory() for _ in range(2)] for s in ((h, rank), (rank, h)))
+    x = torch.randn(T, h, generator=gen).bfloat16().cuda()
+    pool = LoraPool([(h, h)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=T, n_plans=1)
+    try:
+        pool.fill(0, 1, rank, 1.0, 0, 0, A[0], Bm[0], pin=False)
+        y, busy = torch.zeros(4, T, h, dtype=torch.bfloat16, device="cuda"), torch.randn(4096, 4096, device="cuda")
+        s1, s2, s3 = (torch.cuda.Stream() for _ in range(3))
+        plan = pool.plan(T, np.arange(T + 1), np.zeros(T, np.int32), np.full(T, rank, np.int32))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s1):
+            for _ in range(60):
+                busy @ busy
+        B.check(B.lora_apply_plan_static(pool.handle, plan, 0, 0, x.data_ptr(), y[0].data_ptr(), 2.0, s1.cuda_stream))
+        pool.apply_plan(plan, 0, 0, x, y[1], 2.0, stream=s2)
+        s2.synchronize()
+        pool.plan_destroy(plan)
+        B.check(B.lora_cache_release_slot(pool.handle, 0))
+        pool.fill(0, 2, rank, 1.0, 0, 0, A[1], Bm[1], stream=s3, pin=False)
+        assert not s1.query()
+        torch.cuda.synchronize()
+        plan = pool.plan(T, np.arange(T + 1), np.zeros(T, np.int32), np.full(T, rank, np.int32))
+        pool.apply_plan(plan, 0, 0, x, y[2], 2.0)
+        torch.cuda.synchronize()
+        pool.check_fault()
+        assert torch.equal(y[0], y[1]) and not torch.equal(y[0], y[2])
+        for i, w in ((0, 0), (2, 1)):
+            ref = 2.0 * (x.double() @ A[w].cuda().double()) @ Bm[w].cuda().double()
+            assert float((y[i].double() - ref).norm() / ref.norm()) < 4e-3  # the roundings of the output and of s.v
+    finally:
+        pool.close()
