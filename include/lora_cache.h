@@ -279,9 +279,11 @@ void lora_worklists_free(lora_worklists_t *w);
 
 /* Index a batch once and keep its work lists on the device, so that the same batch can
  * be applied to every projection of every layer of the iteration.  Checks every named
- * slot against the slot table (exists, bound, seg_rank equals its rank).  The upload is
- * enqueued on `stream`, or part of the first launch that works through the lists, as the plan's size
- * and the cache's options have it; the host arrays may be reused on return.
+ * slot against the slot table (exists, bound, seg_rank equals its rank).  The lists are
+ * uploaded on `stream`, or travel with the first launch that works through them, as the plan's size
+ * and the cache's options have it (if that turns out to be a launch that cannot take them, they are uploaded ahead of it on its stream; for a captured
+ * one on a stream of the cache's, waited for by the host).  A caller who makes plans ahead on a stream without applies has them uploaded
+ * there.  The host arrays may be reused on return.
  * Plans take turns in the memory of the cache's n_plans plans.  Blocks the host while the lists that lay there before
  * are still on their way: until their upload is done or, where they travelled with a launch, the call it was part of; they travel so only
  * if another plan was free when theirs was made. */

@@ -730,6 +730,17 @@ int32_t direct_shrink(int32_t n_units, int64_t sum_h_in)
     return n_units * 2 * (lora::DIRECT_TOKENS + lora::DIRECT_ROWS) * sum_h_in <= DIRECT_SHRINK_MAX_BYTES ? n_units : 0;
 }
 
+// may a tile shrink of n projections, sum_h_in input columns together, be the launch that lists travel with?
+bool shrink_copies(const PlanLists *q, int n, int64_t sum_h_in)
+{
+    return q->n_tiles > 0 && (int64_t)q->n_tiles * n <= PINNED_LISTS_MAX_TILES && 4 * (int64_t)direct_shrink(q->n_direct, sum_h_in) * n <= PINNED_LISTS_MAX_WAVES;
+}
+// does the GEMV launch of a batch of projections go to the side stream, if there is one?
+bool gemv_beside_tiles(const lora_cache &c, const PlanLists *q, int64_t sum_h_in, int64_t sum_h_out)
+{
+    return q->n_tiles > 0 && q->n_gs > 0 && (double)q->n_tile_tok * c.esize * (double)(sum_h_in + 2 * sum_h_out) >= FORK_MIN_TILE_BYTES;
+}
+
 // Work lists on their way into a plan
 struct ListBuild {
     lora_worklists_t w{};
@@ -1049,6 +1060,17 @@ void forget_uses(lora_cache &c, lora_plan &p)
     for (int32_t &f : p.last_use) hold_fence(c, f, -1);
 }
 
+// Are a plan's lists left with the host until the first launch that works through them, which copies them (or is preceded by their upload, if it is a launch that cannot)?  Only where a call for
+// one of the cache's projections makes such a launch.  Not on a stream that no apply has run on when others have: whoever makes plans on a stream of their own wants the lists in the
+// pool by the time a call needs them.  And not over lists that calls without a fence, a graph's replays say, may still read: nothing but the order of `st` is known to keep from them.
+bool lists_travel(const lora_cache &c, const lora_plan &p, bool few_waves, hipStream_t st)
+{
+    if (!c.fencing || !c.upload_stream || p.bytes == 0 || p.unfenced) return false;
+    if (!p.internal && (!another_free(c, p) || (!c.stream_fence.empty() && c.stream_fence.count(st) == 0))) return false;
+    if (p.n_tiles == 0) return few_waves && c.fused_gemv != 0 && p.n_wgs < GEMV_WIDE_MIN_ITEMS;
+    return std::any_of(c.proj.begin(), c.proj.end(), [&](const lora_proj_t &pr) { return shrink_copies(&p, 1, pr.h_in) && !gemv_beside_tiles(c, &p, pr.h_in, pr.h_out); });
+}
+
 // The upload of a plan's lists on `st`, behind what may still read those that lie there.
 hipError_t upload_lists(lora_cache &c, lora_plan &p, hipStream_t st)
 {
@@ -1193,8 +1215,7 @@ int build_plan(lora_cache &c, lora_plan &p, int32_t T, const int32_t *seg_offset
     const bool few_waves = p.n_tiles == 0 && waves <= PINNED_LISTS_MAX_WAVES;
     if (!c.host_only && c.fencing && p.internal && few_waves) {
         p.lists = p.pinned_dev;
-    } else if (!c.host_only && c.fencing && c.upload_stream && bytes && (p.n_tiles > 0 || few_waves) && (p.internal || another_free(c, p)) && !p.unfenced) {
-        // (what calls without a fence, a graph's replays say, may still read there is overwritten in the order of `st` and no other)
+    } else if (!c.host_only && lists_travel(c, p, few_waves, st)) {
         p.deferred = true;
     } else if (!c.host_only && bytes) {
         HIP_TRY(upload_lists(c, p, st));
@@ -2536,11 +2557,6 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
     return LORA_OK;
 }
 
-// may a tile shrink of n projections, sum_h_in input columns together, be the launch that lists travel with?
-static bool shrink_copies(const PlanLists *q, int n, int64_t sum_h_in)
-{
-    return q->n_tiles > 0 && (int64_t)q->n_tiles * n <= PINNED_LISTS_MAX_TILES && 4 * (int64_t)direct_shrink(q->n_direct, sum_h_in) * n <= PINNED_LISTS_MAX_WAVES;
-}
 static lora::ListCopy list_copy(const lora_plan_t *p)
 {
     return lora::ListCopy{p->dev, p->pinned_dev, (uint32_t)((p->bytes + p->tiled_bytes + 15) / 16), 0};
@@ -2566,8 +2582,7 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
     // Not while kernels are being timed: a kernel's duration is then its own, not that of two kernels sharing the memory.
     const lora::KernelTimer timer{c, timer_pair};
     const lora::KernelTimer *tm = c->timing && !is_capturing(st) ? &timer : nullptr;
-    const double tile_bytes = (double)q->n_tile_tok * c->esize * (double)(sum_h_in + 2 * sum_h_out);
-    const bool fork = q->n_tiles > 0 && q->n_gs > 0 && tile_bytes >= FORK_MIN_TILE_BYTES && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
+    const bool fork = gemv_beside_tiles(*c, q, sum_h_in, sum_h_out) && c->side_stream != nullptr && c->side_stream != st && tm == nullptr;
     // Lists that are still with the host travel with the first launch, if a fence will stand for it: a tile shrink, unless the GEMV launch runs beside it, or a GEMV launch of not too many
     // wavefronts that read them over the link
     const bool gemv_copies = q == p && q->n_tiles == 0 && q->n_gs > 0 && 4 * (int64_t)q->n_gs * n + q->n_ge * sum_supers <= PINNED_LISTS_MAX_WAVES &&

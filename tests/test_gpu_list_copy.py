@@ -441,3 +441,38 @@ def test_a_call_with_fixed_scratch_still_to_come(n_plans):
         b.close_to(y[3][:37], b.expect(base[:37], other))
     finally:
         b.pool.close()
+
+
+@pytest.mark.parametrize("why,lens", [("own stream", [1] * 50), ("own stream", [200, 56]), ("split", [1] * 50)])
+def test_lists_made_ahead_on_another_stream(why, lens):
+    """Plans made on a stream without applies, and lists that no launch can take along: uploaded on the stream of lora_plan_create, which calls on other streams wait for."""
+    from paper_2411_17741_amd import binding as B
+
+    b = Batch(flags=B.LORA_CACHE_SPLIT_GEMV if why == "split" else 0)
+    try:
+        T, n = sum(lens), len(lens)
+        slot = (np.arange(n) % 9).astype(np.int32)
+        segs = T, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), slot, np.asarray(b.ranks, np.int32)[slot]
+        x, base, busy = b.x[:T].contiguous(), b.normal(T, H), torch.randn(4096, 4096, device="cuda")
+        y, y0, done = base.clone(), base.clone(), torch.cuda.Event()
+        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        if why == "own stream":
+            plan = b.pool.plan(*segs, stream=s2)
+            b.pool.apply_plan(plan, 0, 0, x, y0, 2.0, stream=s2)
+            b.pool.plan_destroy(plan)
+            torch.cuda.synchronize()
+        with torch.cuda.stream(s1):
+            for _ in range(60):
+                busy @ busy
+            done.record()
+        plan = b.pool.plan(*segs, stream=s1)
+        b.pool.apply_plan(plan, 1, 0, x, y, 2.0, stream=s2)
+        assert not done.query()
+        s2.synchronize()
+        assert done.query()
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        b.close_to(y, b.expect(base, np.repeat(slot, lens)))
+    finally:
+        b.pool.close()
