@@ -46,7 +46,8 @@ class Batch:
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_plans_in_a_row(dtype):
-    """Plan after plan, each applied on a stream of its own and then at once on another one; a destroyed plan's memory goes to the next but one."""
+    """Plan after plan, each applied on a stream of its own and then at once on another one, there with the fixed scratch (two calls with the pool's would have to be ordered); a destroyed
+    plan's memory goes to the next but one."""
     b = Batch(dtype)
     try:
         s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
@@ -61,7 +62,7 @@ def test_plans_in_a_row(dtype):
             plan = b.pool.plan(*b.segs(slots), stream=s1 if i % 3 == 0 else None)
             x = b.x[: len(slots)].contiguous()
             b.pool.apply_plan(plan, i % N_L, 0, x, y1, 2.0, stream=s1 if i % 2 else s2)
-            b.pool.apply_plan(plan, (i + 1) % N_L, 0, x, y2, 2.0, stream=s2 if i % 2 else s1)
+            b.B.check(b.B.lora_apply_plan_static(b.pool.handle, plan, (i + 1) % N_L, 0, x.data_ptr(), y2.data_ptr(), 2.0, (s2 if i % 2 else s1).cuda_stream))
             b.pool.plan_destroy(plan)
             done.append((x, y1, y2, base, slots))
         torch.cuda.synchronize()
