@@ -221,7 +221,7 @@ struct lora_plan : PlanLists {  // (the lists that a call for one projection wor
     hipEvent_t ev_upload = nullptr;
     bool upload_pending = false;
     // Lists that are still where the host wrote them alone (`deferred`): the first launch that works through them copies them, and reads them there.  That launch is covered by
-    // the fence of its call (upload_fence, -1: none); copying: enqueued by the call that runs now, whose fence is not published yet
+    // the fence of its call (upload_fence, -1: none); copying: the call that runs now has got to it, its fence is not published yet
     bool deferred = false, copying = false;
     int32_t upload_fence = -1;
     int32_t last_use[2] = {-1, -1};  // fences of the latest calls that used the plan, with the pool's scratch and with the fixed one (they may overlap)
@@ -1077,7 +1077,8 @@ hipError_t upload_lists(lora_cache &c, lora_plan &p, hipStream_t st)
     if (const hipError_t e = wait_for_uses(c, p, st)) return e;
     forget_uses(c, p);
     const hipError_t e = lora::launch_upload(p.dev, p.pinned_dev, p.bytes + p.tiled_bytes, st, p.ev_upload);
-    p.upload_pending |= e == hipSuccess;
+    if (e == hipSuccess) p.upload_pending = true;
+    else (void)hipStreamSynchronize(st);  // (the error may be an earlier call's, and the launch on its way)
     p.deferred = e != hipSuccess;
     return e;
 }
@@ -2624,14 +2625,10 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
         gemv_st = c->side_stream;
     }
     // everything that reads x
-    auto copied = [&]() {
-        if (!copies) return;
-        p->deferred = false;
-        p->copying = true;  // until a fence stands for it
-    };
+    if (copies) p->copying = true;  // until a fence stands for the launch (which may be on its way although the runtime returns an error: one that an earlier call of the thread has left)
     if (q->n_tiles > 0) {
         HIP_TRY(lora::launch_mfma_shrink(tb, copy, st, tm));
-        copied();
+        if (copies) p->deferred = false;
     }
     const lora::ListCopy gemv_copy = lists.p ? copy : lora::ListCopy{};
     // joined behind the tile expands, whatever happens in between: a captured fork must not stay open
@@ -2656,7 +2653,7 @@ static int enqueue_batch(lora_cache_t *c, lora_plan_t *p, const PlanLists *q, co
                                        : n_groups == 1 && !gemv_wide(c, q, projs, n, 1) ? enqueue_gemv(c, q, projs, nullptr, n, scale, gemv_st, sc, tm, gemv_done, gemv_copy)
                                        : enqueue_gemv_batch(c, q, projs, nullptr, n, n_groups, scale, gemv_st, sc, tm, gemv_done, gemv_copy))
         return rc_g;
-    if (lists.p) copied();
+    if (lists.p) p->deferred = false;
     join.rides = join_rides;
     // the updates of base_out
     if (q->n_tiles > 0) HIP_TRY(lora::launch_mfma_expand(tb, st, tm, ride ? fence : nullptr));
@@ -2698,14 +2695,17 @@ static void publish_fence(lora_cache_t *c, lora_plan_t *p, hipStream_t st, int32
         hold_fence(*c, p->upload_fence, f);
     }
 }
-// a call that fails has no fence to stand for a launch of it that copies the plan's lists
-struct CopyGuard {
+// A call that fails has no fence to stand for launches of it that read the plan's lists: lists with the host are waited for, for those in the pool it counts as any call without a fence
+struct CallGuard {
     lora_plan_t *p;
     hipStream_t st;
-    ~CopyGuard()
+    bool done = false;
+    ~CallGuard()
     {
-        if (p->copying) (void)hipStreamSynchronize(st);
+        if (done) return;
+        if (p->copying || p->lists == p->pinned_dev) (void)hipStreamSynchronize(st);
         p->copying = false;
+        p->unfenced = true;
     }
 };
 
@@ -2714,10 +2714,11 @@ static int apply_fenced(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc_t
 {
     int32_t f;
     if (const int rc = take_fence(c, p, st, f)) return rc;
-    const CopyGuard guard{p, st};
+    CallGuard guard{p, st};
     const uint8_t one = 1;
     if (const int rc = enqueue_batch(c, p, p, &d, &one, 1, scale, st, sc, f < 0 ? nullptr : c->fences[f].ev, f >= 0)) return rc;
     publish_fence(c, p, st, f, sc.small);
+    guard.done = true;
     return LORA_OK;
 }
 
@@ -2787,7 +2788,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
     a.scale = scale;
     int32_t f;
     if (const int rc_f = take_fence(c, p, st, f)) return rc_f;
-    const CopyGuard guard{p, st};
+    CallGuard guard{p, st};
     const bool copies = p->deferred && f >= 0 && !c->timing && shrink_copies(q, 1, a.h_in);  // (as in enqueue_batch)
     if (const int rc_w = wait_for_inputs(c, p, st, copies)) return rc_w;
     // shrink of the tiles (x is read, v written), then the adapter term of the GEMV tokens: as fp32 into the caller's workspace
@@ -2801,11 +2802,9 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         tb.p[0] = bp;
         tb.group[0] = 1u << 8;
         choose_panels(c, q, pool_scratch(c), tb);
+        if (copies) p->copying = true;
         HIP_TRY(lora::launch_mfma_shrink(tb, copies ? list_copy(p) : lora::ListCopy{}, st, tm));
-        if (copies) {
-            p->deferred = false;
-            p->copying = true;
-        }
+        if (copies) p->deferred = false;
     }
     if (n_gemv_tok > 0) {
         a.y32 = static_cast<float *>(workspace);
@@ -2830,6 +2829,7 @@ int lora_linear_plan(lora_cache_t *c, lora_plan_t *p, int32_t layer, int32_t pro
         ++c->slots[sl].use_count;
     }
     publish_fence(c, p, st, f);
+    guard.done = true;
     return LORA_OK;
 }
 
@@ -2844,7 +2844,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
     }
     int32_t f;
     if (const int rc_f = take_fence(c, p, st, f)) return rc_f;
-    const CopyGuard guard{p, st};
+    CallGuard guard{p, st};
     // Entries that do not depend on each other go as one batch: no output of the batch may overlap an input of it (an
     // earlier entry's: it may not have been read yet; a later one's: it would be read too early) or another output (both
     // would be updated from what was there before).  Within a batch neighbours that read the same x (q, k, v; gate, up)
@@ -2912,6 +2912,7 @@ int lora_apply_plan_multi(lora_cache_t *c, lora_plan_t *p, const lora_apply_desc
         i += m;
     }
     if (n > 0) publish_fence(c, p, st, f);
+    guard.done = true;
     return LORA_OK;
 }
 

@@ -11,11 +11,14 @@ class Busy:
         torch.cuda.synchronize()
         for _ in range(8):
             self.two = torch.cuda.Stream()
-            self.start(20)
+            self.start(10)
+            early = torch.cuda.Event()
+            early.record(self.one)
+            self.start(10)
             with torch.cuda.stream(self.two):
                 word.add_(1)
             self.two.synchronize()
-            free = not self.one.query()
+            free = not early.query()  # (a shared queue: behind all of them)
             torch.cuda.synchronize()
             if free:
                 return

@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from streams import Busy
+
 pytestmark = pytest.mark.gpu
 
 
@@ -63,20 +65,18 @@ def test_refill_waits_for_a_call_with_fixed_scratch_still_to_come():
     pool = LoraPool([(h, h)], 1, [rank], [1], B.LORA_BF16, max_tokens=T, max_segments=T, n_plans=1)
     try:
         pool.fill(0, 1, rank, 1.0, 0, 0, A[0], Bm[0], pin=False)
-        y, busy = torch.zeros(4, T, h, dtype=torch.bfloat16, device="cuda"), torch.randn(4096, 4096, device="cuda")
-        s1, s2, s3 = (torch.cuda.Stream() for _ in range(3))
+        y, busy, s3 = torch.zeros(4, T, h, dtype=torch.bfloat16, device="cuda"), Busy(), torch.cuda.Stream()
+        s1, s2 = busy.one, busy.two
         plan = pool.plan(T, np.arange(T + 1), np.zeros(T, np.int32), np.full(T, rank, np.int32))
         torch.cuda.synchronize()
-        with torch.cuda.stream(s1):
-            for _ in range(60):
-                busy @ busy
+        busy.start()
         B.check(B.lora_apply_plan_static(pool.handle, plan, 0, 0, x.data_ptr(), y[0].data_ptr(), 2.0, s1.cuda_stream))
         pool.apply_plan(plan, 0, 0, x, y[1], 2.0, stream=s2)
         s2.synchronize()
         pool.plan_destroy(plan)
         B.check(B.lora_cache_release_slot(pool.handle, 0))
-        pool.fill(0, 2, rank, 1.0, 0, 0, A[1], Bm[1], stream=s3, pin=False)
         assert not s1.query()
+        pool.fill(0, 2, rank, 1.0, 0, 0, A[1], Bm[1], stream=s3, pin=False)
         torch.cuda.synchronize()
         plan = pool.plan(T, np.arange(T + 1), np.zeros(T, np.int32), np.full(T, rank, np.int32))
         pool.apply_plan(plan, 0, 0, x, y[2], 2.0)

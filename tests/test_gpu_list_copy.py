@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 import torch
 
+from streams import Busy
+
 pytestmark = pytest.mark.gpu
 H, N_L = 512, 6
 
@@ -415,17 +417,15 @@ def test_a_call_with_fixed_scratch_still_to_come(n_plans):
     b = Batch(n_plans=n_plans)
     try:
         slots, other = np.arange(40) % 9, (np.arange(37) * 5 + 1) % 9
-        x, busy = b.x[:40].contiguous(), torch.randn(4096, 4096, device="cuda")
+        x, busy = b.x[:40].contiguous(), Busy()
         base = b.normal(40, H)
         y = [base.clone() for _ in range(4)]
-        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        s1, s2 = busy.one, busy.two
         plan = b.pool.plan(*b.segs(slots), stream=s2)
         torch.cuda.synchronize()
         b.pool.apply_plan(plan, 0, 0, x, y[0], 2.0, stream=s2)
         torch.cuda.synchronize()
-        with torch.cuda.stream(s1):
-            for _ in range(60):
-                busy @ busy
+        busy.start()
         b.B.check(b.B.lora_apply_plan_static(b.pool.handle, plan, 1, 0, x.data_ptr(), y[1].data_ptr(), 2.0, s1.cuda_stream))
         b.pool.apply_plan(plan, 2, 0, x, y[2], 2.0, stream=s2)
         s2.synchronize()
@@ -454,19 +454,17 @@ def test_lists_made_ahead_on_another_stream(why, lens):
         T, n = sum(lens), len(lens)
         slot = (np.arange(n) % 9).astype(np.int32)
         segs = T, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), slot, np.asarray(b.ranks, np.int32)[slot]
-        x, base, busy = b.x[:T].contiguous(), b.normal(T, H), torch.randn(4096, 4096, device="cuda")
+        x, base, busy = b.x[:T].contiguous(), b.normal(T, H), Busy()
         y, y0, done = base.clone(), base.clone(), torch.cuda.Event()
-        s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+        s1, s2 = busy.one, busy.two
         torch.cuda.synchronize()
         if why == "own stream":
             plan = b.pool.plan(*segs, stream=s2)
             b.pool.apply_plan(plan, 0, 0, x, y0, 2.0, stream=s2)
             b.pool.plan_destroy(plan)
             torch.cuda.synchronize()
-        with torch.cuda.stream(s1):
-            for _ in range(60):
-                busy @ busy
-            done.record()
+        busy.start()
+        done.record(s1)
         plan = b.pool.plan(*segs, stream=s1)
         b.pool.apply_plan(plan, 1, 0, x, y, 2.0, stream=s2)
         assert not done.query()
@@ -475,5 +473,40 @@ def test_lists_made_ahead_on_another_stream(why, lens):
         torch.cuda.synchronize()
         b.pool.check_fault()
         b.close_to(y, b.expect(base, np.repeat(slot, lens)))
+    finally:
+        b.pool.close()
+
+
+@pytest.mark.parametrize("lens", [[1] * 50, [200, 56]])
+@pytest.mark.parametrize("one_call", [False, True])
+def test_an_error_of_an_earlier_call(lens, one_call):
+    """An error that another call of the thread has left behind is what the launch that takes the lists along returns, though it is on its way: it is over when the call returns, nothing
+    guards the host's copy of the lists from then on; the plan stays usable."""
+    b = Batch()
+    try:
+        T, n = sum(lens), len(lens)
+        slot = (np.arange(n) % 9).astype(np.int32)
+        segs = T, np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), slot, np.asarray(b.ranks, np.int32)[slot]
+        x, base, busy = b.x[:T].contiguous(), b.normal(T, H), torch.randn(4096, 4096, device="cuda")
+        y, stream = base.clone(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        plan = b.pool.plan(*segs, stream=stream)
+        with torch.cuda.stream(stream):
+            for _ in range(60):
+                busy @ busy
+        assert b.B._lib.hipSetDevice(9999) != 0  # no such device
+        if one_call:
+            rc = b.B.lora_apply(b.pool.handle, 0, 0, x.data_ptr(), y.data_ptr(), T, *segs[1:], 2.0, stream.cuda_stream)
+        else:
+            rc = b.B.lora_apply_plan(b.pool.handle, plan, 0, 0, x.data_ptr(), y.data_ptr(), 2.0, stream.cuda_stream)
+        assert rc == b.B.LORA_E_HIP
+        assert stream.query()
+        for _ in range(2):
+            y.copy_(base)
+            b.pool.apply_plan(plan, 0, 0, x, y, 2.0)
+            b.close_to(y, b.expect(base, np.repeat(slot, lens)))
+            b.pool.plan_destroy(plan)
+            plan = b.pool.plan(*segs)
+        b.pool.check_fault()
     finally:
         b.pool.close()
