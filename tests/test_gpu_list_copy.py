@@ -510,3 +510,54 @@ def test_an_error_of_an_earlier_call(lens, one_call):
         b.pool.check_fault()
     finally:
         b.pool.close()
+
+
+@pytest.mark.parametrize("lens", [[1] * 50, [200, 56]])
+def test_a_copying_launch_still_to_come(lens):
+    """The launch that takes the lists along is still to come: a call on another stream waits for it, and so does the plan that is made in that memory next."""
+    b = Batch()
+    try:
+        T, n = sum(lens), len(lens)
+        x, base, busy = b.x[:T].contiguous(), b.normal(T, H), Busy()
+        y, early = [base.clone() for _ in range(6)], torch.cuda.Event()
+        s1, s2 = busy.one, busy.two
+        slots = [((np.arange(n) * (i + 1) + i) % 9).astype(np.int32) for i in range(5)]
+        off, ranks = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32), np.asarray(b.ranks, np.int32)
+
+        def make(i):
+            return b.pool.plan(T, off, slots[i], ranks[slots[i]], stream=s1)
+
+        torch.cuda.synchronize()
+        plan = make(0)
+        b.pool.apply_plan(plan, 0, 0, x, y[0], 2.0, stream=s1)  # (from here on s1 is a stream with applies)
+        b.pool.plan_destroy(plan)
+        torch.cuda.synchronize()
+
+        busy.start()
+        plan = make(1)
+        b.pool.apply_plan(plan, 1, 0, x, y[1], 2.0, stream=s2)
+        s2.synchronize()
+        assert not s1.query()  # nothing of the plan is behind the work on s1: its lists travelled
+        b.pool.plan_destroy(plan)
+        torch.cuda.synchronize()
+
+        busy.start()
+        early.record(s1)
+        plan = first = make(2)
+        b.pool.apply_plan(plan, 2, 0, x, y[2], 2.0, stream=s1)
+        b.B.check(b.B.lora_apply_plan_static(b.pool.handle, plan, 3, 0, x.data_ptr(), y[3].data_ptr(), 2.0, s2.cuda_stream))
+        b.pool.plan_destroy(plan)
+        plan = make(3)
+        b.pool.apply_plan(plan, 4, 0, x, y[4], 2.0, stream=s1)
+        b.pool.plan_destroy(plan)
+        assert not early.query()
+        plan = make(4)
+        assert early.query()  # waited for the call that read the lists with the host
+        assert plan.value == first.value
+        b.pool.apply_plan(plan, 5, 0, x, y[5], 2.0, stream=s1)
+        torch.cuda.synchronize()
+        b.pool.check_fault()
+        for i, k in enumerate([0, 1, 2, 2, 3, 4]):
+            b.close_to(y[i], b.expect(base, np.repeat(slots[k], lens)))
+    finally:
+        b.pool.close()

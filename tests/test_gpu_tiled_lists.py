@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from plan_checks import check_plan_units
+from streams import Busy
 
 pytestmark = pytest.mark.gpu
 RANKS = [16, 100, 5, 64]
@@ -223,16 +224,18 @@ def test_calls_on_a_second_stream(first):
         go(want, c.stream)
         kinds = c.kernels(lambda: go(c.base.clone(), c.stream))
         assert "mfma_shrink" in kinds
-        y, busy = c.base.clone(), torch.randn(4096, 4096, device="cuda")
+        y, busy, done = c.base.clone(), Busy(), torch.cuda.Event()
         c.pool.plan_destroy(c.plan)
-        other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+        other, mine = busy.one, busy.two  # (no apply has run on `other`: the lists do not wait for their first launch)
         torch.cuda.synchronize()
+        busy.start()
+        done.record(other)
         with torch.cuda.stream(other):
-            for _ in range(40):
-                busy @ busy
             c.plan = c.pool.plan(c.T, c.off, c.slot, c.rank_of[c.slot])
-            assert not other.query()
         go(y, mine.cuda_stream)
+        assert not done.query()
+        mine.synchronize()
+        assert done.query()
         torch.cuda.synchronize()
         c.pool.check_fault()
         assert torch.equal(y, want)
