@@ -80,12 +80,19 @@ constexpr int64_t DIRECT_SHRINK_MAX_BYTES = 225000000;
 // lora_apply's lists, used by one launch, are read where the host writes them (pinned memory, over the link) up to so many wavefronts that read an item: no upload
 // launch.  us a call with the upload and without: 16 fp32 tokens 16.5 and 8.4, 16 requests at 4096 x 4096 16.0 and 8.2, 64 requests (about 2000 wavefronts) 18.5 and 10.5, 200 requests
 // (about 6000) 23.4 and 12.4.  So too while the link is busy: 64 requests beside copies or staged fills 19 and 12.3, beside fills by a kernel that reads host memory 139 and 101.
-// The first launch of a plan does the same and copies the lists for those that follow, in blocks of its own (lora_plan_create, then us a pass: one request on all 224 projections of a 7B
-// model 25.7 and 20.9; a prompt of 77 tokens call by call 271 and 255).  With more wavefronts, wide items or tiles the lists are uploaded ahead of it (64 requests on q of 32 layers, 65000 wavefronts).
+// The first launch of a plan does the same and copies the lists for those that follow, in blocks of its own: one to 200 requests on one projection 1 to 3.7 us a pass less than uploaded ahead,
+// idle and beside copies, on as many projections as stay below the line 1 to 2.5; one request on all 224 projections of a 7B model 25.6 and 20.2.  With more wavefronts or wide
+// items the lists are uploaded ahead of it (64 requests on q of 32 layers, 65000 wavefronts).
 constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
-// So too a tile shrink of up to so many tiles over its projections, all the lists of a plan being copied then: eight prompts on q of eight layers 190.5 -> 187.1 us a pass, the 13B batch
-// 834 -> 828, its base products 1701 -> 1694; lora_apply on a prompt of 1200 tokens of rank 32, four calls 94 -> 73, on eight prompts 193 -> 182.
+// So too a tile shrink of up to so many tiles over its projections, all the lists of a plan being copied then.  us a pass uploaded and copied: eight prompts of 512 tokens 1024 wide on 16 projections (1024 tiles)
+// 133.5 and 130.4, on 32 (2048) 239 and 236; 64 of them on four (2048) 233 and 227; 256 of them 512 wide on one (2048) 337 and 322 to 328; 300 short prompts on seven (2100) 233 and
+// 231.  Beside copies the same.  Beside fills by a kernel that reads host memory 434 and 417, 430 and 408, 430 and 420, 578 and 571.  Of more tiles it is 1 %, and short prompts lose it beside such fills: 300 on 14 (4200) 829 and
+// 838 to 846, on 28 (8400) 1466 and 1497 to 1556.
 constexpr int64_t PINNED_LISTS_MAX_TILES = 2048;
+// And of up to so many blocks where it runs as mfma_shrink_direct_kernel: each begins with a trip over the link, two stay on a compute unit and those behind them make it again.  us a pass uploaded and copied, idle and
+// beside copies: four prompts of 300 tokens 1024 wide, 681 blocks 23.4 and 20.5, 25.0 and 21.6; 908 blocks 24.2 and 23.1, 26.5 and 26.8; 1362 blocks 29.9 and 29.6, 31.8 and 34.4;
+// 3178 blocks 51.1 and 53.7, 52.6 and 59.9.  16 prompts of 60 tokens 2048 wide, 940 blocks 32.2 and 29.5, 34.1 and 31.7; 1128 blocks 33.1 and 32.6, 34.3 and 36.9.
+constexpr int64_t PINNED_LISTS_MAX_DIRECT = 960;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
 // twice that 3507 and 3568, one layer (2.4 GB) 968 and 954; 13B with four prompts of 512 (1.6 GB) 876 and 797, with 5120 prompt tokens (4 GB) 1188 and 1200; 64 requests beside a prompt of
@@ -733,7 +740,7 @@ int32_t direct_shrink(int32_t n_units, int64_t sum_h_in)
 // may a tile shrink of n projections, sum_h_in input columns together, be the launch that lists travel with?
 bool shrink_copies(const PlanLists *q, int n, int64_t sum_h_in)
 {
-    return q->n_tiles > 0 && (int64_t)q->n_tiles * n <= PINNED_LISTS_MAX_TILES && 4 * (int64_t)direct_shrink(q->n_direct, sum_h_in) * n <= PINNED_LISTS_MAX_WAVES;
+    return q->n_tiles > 0 && (int64_t)q->n_tiles * n <= PINNED_LISTS_MAX_TILES && (int64_t)direct_shrink(q->n_direct, sum_h_in) * n <= PINNED_LISTS_MAX_DIRECT;
 }
 // does the GEMV launch of a batch of projections go to the side stream, if there is one?
 bool gemv_beside_tiles(const lora_cache &c, const PlanLists *q, int64_t sum_h_in, int64_t sum_h_out)
