@@ -28,6 +28,7 @@
 //
 // (paper section 3.1: the two adapter products and the aggregation into the base output.)
 #include <algorithm>
+#include <type_traits>
 
 #include "lora_device.h"
 
@@ -331,11 +332,14 @@ __device__ __forceinline__ void gemv_expand_mfma(const GemvUse &a, const ItemU i
 }
 
 // expand, fp32 (the small full-precision configuration): on the vector ALUs, s.v of the item's tokens staged in this
-// wavefront's LDS rows.  What bounds it is trips to memory one behind the other, so the granules of CB x 64 columns (64 registers a
+// wavefront's LDS rows.  What bounds a small launch is trips to memory one behind the other, so the granules of CB x 64 columns (64 registers a
 // lane) and base_out are requested at once, those of the first pass before the intermediate is waited for; a unit is two passes at most.
-// (A column and granule at a time behind the wait: 64 requests on q, k, v 1024 wide, two layers, 34.4 us a pass, 21.9 this way; 40
-// and a prompt of 5 call by call 139 -> 61; 16 tokens at 256 x 256, where the host bounds a call, unchanged.)
-template <int CB, int JB>  // blocks of 64 columns and granules of a pass
+// That takes 153 registers, three wavefronts on a SIMD, and a launch of many (F32_MANY_WAVES) is bound by their number, in the shrink too: its kernels request 16 to 32 registers at once and, from rank
+// 40 up, the next ones while the products of these run: 96 registers, five wavefronts.  us a pass, a column and granule at a time behind the wait (96 registers too), 64 registers, this: four layers' q 1024 wide of rank 128, 64
+// requests (18400 wavefronts) 28.4, 31.4, 27.6, 512 requests (86400) 85.9, 104.9, 84.8; of ranks 8 to 128, 64 requests (7700) 27.8, 17.1, 16.0, 512 (25900) 49.3, 39.6, 36.0; 4096 wide, rank 32, 64
+// requests (6100) 33.2, 27.0, 26.2, rank 8, 512 requests (7200) 46.8, 29.3, 30.4, rank 8, 64 requests (1500) 36.0, 12.7, 14.7; 200 requests of rank 128 on q, k, v 1024 wide call by call (9900) 141, 128, 101.5, 64 of
+// ranks 8 to 128 (1900) 121, 57, 59.
+template <int CB, int JB, int NB = 1>  // blocks of 64 columns and granules of a register set, sets
 __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it, int nt, int c0, int c1,
                                                 float *vs /* [TB][128] */)
 {
@@ -344,14 +348,14 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
     const float s = a.scale * it.alpha;
     const float *Bp = reinterpret_cast<const float *>(a.proj_base + (int64_t)it.row * a.row_bytes) + (size_t)rs * a.h_in;
     float *y = reinterpret_cast<float *>(a.y);
-    float br[CB][JB][8], yv[CB][TB], acc[CB][TB];
+    float br[NB][CB][JB][8], yv[CB][TB], acc[CB][TB];
     // unconditional, from addresses inside the slab: granules past the last and columns past the unit are not used
-    auto load_b = [&](int n0, int j0) {
+    auto load_b = [&](int b, int n0, int j0) {
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int n = (n0 + 64 * cb < c1 ? n0 + 64 * cb : c0) + lane;
 #pragma unroll
-            for (int j = 0; j < JB; ++j) unpack_chunk(load_chunk(Bp + ((size_t)min(j0 + j, rs8 - 1) * a.h_out + n) * 8), br[cb][j]);
+            for (int j = 0; j < JB; ++j) unpack_chunk(load_chunk(Bp + ((size_t)min(j0 + j, rs8 - 1) * a.h_out + n) * 8), br[b][cb][j]);
         }
     };
     auto load_y = [&](int n0) {
@@ -362,7 +366,11 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
             for (int tt = 0; tt < TB; ++tt) yv[cb][tt] = y[(size_t)(tt < nt ? it.tok(tt) : it.tok0) * a.h_out + n];
         }
     };
-    load_b(c0, 0);
+    auto first_b = [&](int n0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) load_b(b, n0, b * JB);
+    };
+    first_b(c0);
     load_y(c0);
     for (int half = 0; half < 2; ++half) {
         const int j = half * 64 + lane;
@@ -381,7 +389,7 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
 #pragma unroll 1
     for (int n0 = c0; n0 < c1; n0 += 64 * CB) {
         if (n0 > c0) {
-            load_b(n0, 0);
+            first_b(n0);
             load_y(n0);
         }
 #pragma unroll
@@ -389,21 +397,25 @@ __device__ __forceinline__ void gemv_expand_f32(const GemvUse &a, const ItemU it
 #pragma unroll
             for (int tt = 0; tt < TB; ++tt) acc[cb][tt] = 0.f;
 #pragma unroll 1
-        for (int j0 = 0; j0 < rs8; j0 += JB) {
-            if (j0 > 0) load_b(n0, j0);
+        for (int j0 = 0; j0 < rs8; j0 += JB * NB) {
+            if (NB == 1 && j0 > 0) load_b(0, n0, j0);
 #pragma unroll
-            for (int j = 0; j < JB; ++j) {
-                if (j0 + j >= rs8) continue;  // uniform
-                __builtin_amdgcn_sched_barrier(0);  // (not the s.v of all granules in registers at once)
+            for (int b = 0; b < NB; ++b) {
 #pragma unroll
-                for (int tt = 0; tt < TB; ++tt) {
-                    const float4 v0 = *reinterpret_cast<const float4 *>(vs + tt * 128 + (j0 + j) * 8), v1 = *reinterpret_cast<const float4 *>(vs + tt * 128 + (j0 + j) * 8 + 4);
-                    const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+                for (int j = b * JB; j < (b + 1) * JB; ++j) {
+                    if (j0 + j >= rs8) continue;  // uniform
+                    __builtin_amdgcn_sched_barrier(0);  // (not the s.v of all granules in registers at once)
 #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb)
+                    for (int tt = 0; tt < TB; ++tt) {
+                        const float4 v0 = *reinterpret_cast<const float4 *>(vs + tt * 128 + (j0 + j) * 8), v1 = *reinterpret_cast<const float4 *>(vs + tt * 128 + (j0 + j) * 8 + 4);
+                        const float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) acc[cb][tt] += v[i] * br[cb][j][i];
+                        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) acc[cb][tt] += v[i] * br[b][cb][j - b * JB][i];
+                    }
                 }
+                if (NB > 1) load_b(b, n0, j0 + (b + NB) * JB);  // (past the last granule: the last again, not used)
             }
         }
 #pragma unroll
@@ -425,7 +437,7 @@ __device__ __forceinline__ void gemv_shrink_work(const GemvUse &a, const ItemU i
     else gemv_shrink_item<E, 4>(a, it, nt, red);
 }
 
-template <typename E>
+template <typename E, bool MANY>
 __device__ __forceinline__ void gemv_expand_work(const GemvUse &a, const ItemU it, uint32_t sc, uint32_t *stage /* this wavefront's */)
 {
     int c0, c1;
@@ -443,10 +455,16 @@ __device__ __forceinline__ void gemv_expand_work(const GemvUse &a, const ItemU i
     } else {
         float *const vs = reinterpret_cast<float *>(stage);
         const int rs8 = rank_storage(it.rank) >> 3;
-        if (rs8 == 1) gemv_expand_f32<8, 1>(a, it, nt, c0, c1, vs);
-        else if (rs8 == 2) gemv_expand_f32<4, 2>(a, it, nt, c0, c1, vs);
-        else if (rs8 <= 4) gemv_expand_f32<2, 4>(a, it, nt, c0, c1, vs);
-        else gemv_expand_f32<1, 8>(a, it, nt, c0, c1, vs);
+        if constexpr (MANY) {
+            if (rs8 <= 2) gemv_expand_f32<2, 1>(a, it, nt, c0, c1, vs);
+            else if (rs8 <= 4) gemv_expand_f32<1, 4>(a, it, nt, c0, c1, vs);
+            else gemv_expand_f32<1, 2, 2>(a, it, nt, c0, c1, vs);
+        } else {
+            if (rs8 == 1) gemv_expand_f32<8, 1>(a, it, nt, c0, c1, vs);
+            else if (rs8 == 2) gemv_expand_f32<4, 2>(a, it, nt, c0, c1, vs);
+            else if (rs8 <= 4) gemv_expand_f32<2, 4>(a, it, nt, c0, c1, vs);
+            else gemv_expand_f32<1, 8>(a, it, nt, c0, c1, vs);
+        }
     }
 }
 
@@ -456,8 +474,8 @@ __device__ __forceinline__ void gemv_expand_work(const GemvUse &a, const ItemU i
 // per wavefront.  Shrink blocks come first in the grid and wait for nothing, so waiting expand
 // wavefronts cannot starve them; waits are bounded all the same.
 // ---------------------------------------------------------------------------------------
-// Copy: nothing, or the ListCopy of lists that blocks behind the others copy (ListCopy)
-template <typename E, typename... Copy>
+// MANY: a launch of many wavefronts, in fp32.  Copy: nothing, or the ListCopy of lists that blocks behind the others copy (ListCopy)
+template <typename E, bool MANY, typename... Copy>
 __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const GemvItem *ge, uint32_t n_gs, uint32_t n_proj_phase, int32_t ue0,
                                                    int32_t ue1, int32_t ue2, int32_t ue3, uint32_t n_super_packed, uint32_t sm0, uint32_t sm1,
                                                    uint32_t sm2, uint32_t sm3, GemvArgs a, Copy... copy)
@@ -484,7 +502,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
         if (unit >= (uint32_t)ue3) return (copy_lists(copy, blockIdx.x, 256), ...);  // (entries past the group repeat its last)
         uint32_t proj, item, sc;
         gemv_expand_unit(unit, m, proj, item, sc);
-        gemv_expand_work<E>(use(proj), load_item(ge + item), sc, stage[w]);
+        gemv_expand_work<E, MANY>(use(proj), load_item(ge + item), sc, stage[w]);
     }
 }
 
@@ -492,7 +510,7 @@ __global__ __launch_bounds__(256) void gemv_kernel(const GemvItem *gs, const Gem
 // its bytes -- the gap to the kernel before it, the ramp, the hand-over at its end, 5 to 6 us -- is paid once per batch.
 __device__ __forceinline__ const GemvItem *items_of(const GemvBatch &b, bool shrink) { return shrink ? b.gs : b.ge; }
 __device__ __forceinline__ const GemvItem *items_of(const GemvLong &b, bool shrink) { return static_cast<const GemvItem *>(shrink ? b.shrink_items : b.expand_items); }
-template <typename E, typename Batch, typename... Copy>
+template <typename E, bool MANY, typename Batch, typename... Copy>
 __global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b, Copy... copy)
 {
     __shared__ float red[4][16];
@@ -518,7 +536,7 @@ __global__ __launch_bounds__(256) void gemv_batch_kernel(Batch b, Copy... copy)
         gemv_batch_unit(unit, b.m, super, item);
         uint32_t first;
         const GemvUse a = use(gemv_batch_super(b, super), first);
-        gemv_expand_work<E>(a, load_item(items_of(b, false) + item), super - first, stage[w]);
+        gemv_expand_work<E, MANY>(a, load_item(items_of(b, false) + item), super - first, stage[w]);
     }
 }
 
@@ -830,26 +848,34 @@ hipError_t launch_gemv_clear(int dtype, unsigned long long *vw, uint64_t vw_set,
     return hipGetLastError();
 }
 
+// Wavefronts of an fp32 launch from which its kernels are those with MANY.  Both ways: 512 requests of rank 8 4096 wide on four layers (7200) 29.3 and 30.4 us, 64 of ranks 8 to 128 1024 wide (7700) 17.1 and 16.0; see gemv_expand_f32
+constexpr int64_t F32_MANY_WAVES = 7424;
+template <typename F> static void with_kernels(int dtype, int64_t waves, F f)
+{
+    if (dtype == LORA_BF16) f(__bf16{}, std::false_type{});
+    else if (waves <= F32_MANY_WAVES) f(float{}, std::false_type{});
+    else f(float{}, std::true_type{});
+}
+
 hipError_t launch_gemv(int dtype, const GemvMap &m, const GemvArgs &a, const ListCopy &copy, hipStream_t st, const KernelTimer *tm, hipEvent_t done)
 {
     const int n_proj = (int)(m.n_proj_phase & 0xffu);
     if (m.n_gs == 0 || a.n_ge <= 0 || n_proj <= 0) return hipSuccess;
     const int n_shrink = n_proj * (int)m.n_gs, n_expand = (m.unit_end[GEMV_MAX_PROJS - 1] + 3) / 4;
+    const int64_t waves = 4 * ((int64_t)n_shrink + n_expand);
     auto go_with = [&](auto kernel, uint32_t phase, int blocks, int kind, hipEvent_t ev, auto... more) {
         launch_k(tm, ev, kind, kernel, dim3(blocks), dim3(256), 0, st, m.gs, m.ge, m.n_gs, (uint32_t)n_proj | (phase << 8), m.unit_end[0], m.unit_end[1], m.unit_end[2], m.unit_end[3],
                  m.n_super_packed, m.super_magic[0], m.super_magic[1], m.super_magic[2], m.super_magic[3], a, more...);
     };
     auto go = [&](uint32_t phase, int blocks, int kind, hipEvent_t ev) {
-        if (dtype == LORA_BF16) go_with(gemv_kernel<__bf16>, phase, blocks, kind, ev);
-        else go_with(gemv_kernel<float>, phase, blocks, kind, ev);
+        with_kernels(dtype, waves, [&](auto e, auto many) { go_with(gemv_kernel<decltype(e), decltype(many)::value>, phase, blocks, kind, ev); });
     };
     if (copy.pieces) {
         if (!a.epoch) return hipErrorInvalidValue;
         ListCopy c = copy;
         c.first_block = (uint32_t)(n_shrink + n_expand);
         const int blocks = n_shrink + n_expand + (int)copy_blocks(c, 256);
-        if (dtype == LORA_BF16) go_with(gemv_kernel<__bf16, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
-        else go_with(gemv_kernel<float, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c);
+        with_kernels(dtype, waves, [&](auto e, auto many) { go_with(gemv_kernel<decltype(e), decltype(many)::value, ListCopy>, 0u, blocks, LORA_K_GEMV_FUSED, done, c); });
     } else if (a.epoch) {
         go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);
     } else {
@@ -864,6 +890,7 @@ template <typename Batch> static hipError_t launch_batch(int dtype, const Batch 
     if (b.m.n_gs == 0 || b.m.n_ge == 0 || b.m.n_proj == 0) return hipSuccess;
     if ((wide && dtype != LORA_BF16) || (copy.pieces && (wide || !b.epoch))) return hipErrorInvalidValue;
     const unsigned n_shrink = b.m.n_proj * b.m.shrink_blocks, n_expand = (b.m.n_units + 3) / 4;
+    const int64_t waves = 4 * ((int64_t)n_shrink + n_expand);
     auto go = [&](uint32_t phase, unsigned blocks, int kind, hipEvent_t ev) {
         Batch q = b;
         q.m.phase = phase;
@@ -871,11 +898,9 @@ template <typename Batch> static hipError_t launch_batch(int dtype, const Batch 
             ListCopy c = copy;
             c.first_block = blocks;
             const dim3 grid(blocks + copy_blocks(c, 256));
-            if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
-            else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch, ListCopy>, grid, dim3(256), 0, st, q, c);
+            with_kernels(dtype, waves, [&](auto e, auto many) { launch_k(tm, ev, kind, gemv_batch_kernel<decltype(e), decltype(many)::value, Batch, ListCopy>, grid, dim3(256), 0, st, q, c); });
         } else if (wide) launch_k(tm, ev, kind, gemv_wide_kernel<Batch>, dim3(blocks), dim3(256), 0, st, q);
-        else if (dtype == LORA_BF16) launch_k(tm, ev, kind, gemv_batch_kernel<__bf16, Batch>, dim3(blocks), dim3(256), 0, st, q);
-        else launch_k(tm, ev, kind, gemv_batch_kernel<float, Batch>, dim3(blocks), dim3(256), 0, st, q);
+        else with_kernels(dtype, waves, [&](auto e, auto many) { launch_k(tm, ev, kind, gemv_batch_kernel<decltype(e), decltype(many)::value, Batch>, dim3(blocks), dim3(256), 0, st, q); });
     };
     if (b.epoch) {
         go(0u, n_shrink + n_expand, LORA_K_GEMV_FUSED, done);

@@ -1,5 +1,5 @@
-"""The fp32 expand at the edges of its passes: one to sixteen granules of 8 ranks, one to three blocks of 64 columns past a pass, an infinity in a weight that no clamped load may bring
-into other columns."""
+"""The fp32 expand at the edges of its passes, in launches of few wavefronts and of many: one to sixteen granules of 8 ranks, one to three blocks of 64 columns past a pass, an infinity in a weight
+that no clamped load may bring into other columns."""
 import numpy as np
 import pytest
 import torch
@@ -8,12 +8,15 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("h_out", [64, 320, 1024, 1088])
-@pytest.mark.parametrize("ranks", [(8, 16, 32), (5, 24, 64), (40, 72, 128), (1, 100, 12)])
-def test_f32_expand(ranks, h_out):
+@pytest.mark.parametrize("ranks", [(8, 16, 32), (5, 24, 64), (40, 72, 128), (1, 100, 12), (48, 56, 96)])
+@pytest.mark.parametrize("many", [False, True])
+def test_f32_expand(ranks, h_out, many):
     from paper_2411_17741_amd import binding as B
     from paper_2411_17741_amd.pool import LoraPool
 
     h_in, lens = 128, [1, 7, 4]
+    if many:  # 60 batches of four tokens, 32 shrink blocks of four wavefronts each
+        lens, ranks = lens + [240], ranks + (128,)
     gen = torch.Generator(device="cuda").manual_seed(h_out + ranks[0])
     normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")
     T, n = sum(lens), len(lens)
@@ -25,6 +28,10 @@ def test_f32_expand(ranks, h_out):
     try:
         for i in range(n):
             pool.fill(i, i + 1, ranks[i], 0.5 + i, 0, 0, A[i].cpu(), Bm[i].cpu())
+        plan = pool.plan(T, off, np.arange(n, dtype=np.int32), np.asarray(ranks, np.int32))
+        rc, info = B.lora_plan_info(plan)
+        assert rc == B.LORA_OK and (4 * info.n_gemv_shrink_items > 7424) == many
+        pool.plan_destroy(plan)
         y = base.clone()
         pool.apply(0, 0, x, y, off, np.arange(n, dtype=np.int32), np.asarray(ranks, np.int32), 2.0)
         pool.check_fault()
