@@ -288,7 +288,8 @@ struct lora_cache {
     // and a join event (default priority, like every stream here)
     hipStream_t side_stream = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    // Uploads that a captured call needs and that must not become part of the graph.  Not the side stream's: one that a captured call has forked to stays in the capture until that ends, joined or not
+    // Uploads that a captured call needs and that must not become part of the graph.  Not the side stream's: one that a captured call has forked to stays in the capture until that ends, joined or not.
+    // Made by the first call that needs it: with a third stream in the process the tile expand of 16 prompts of 512 tokens on eight projections 1024 wide takes 88.5 us instead of 83.7
     hipStream_t upload_stream = nullptr;
     int device = 0;  // the device that was current at lora_cache_create
     int n_cu = 256;  // its compute units
@@ -1072,7 +1073,7 @@ void forget_uses(lora_cache &c, lora_plan &p)
 // pool by the time a call needs them.  And not over lists that calls without a fence, a graph's replays say, may still read: nothing but the order of `st` is known to keep from them.
 bool lists_travel(const lora_cache &c, const lora_plan &p, bool few_waves, hipStream_t st)
 {
-    if (!c.fencing || !c.upload_stream || p.bytes == 0 || p.unfenced) return false;
+    if (!c.fencing || !c.side_stream || p.bytes == 0 || p.unfenced) return false;
     if (!p.internal && (!another_free(c, p) || (!c.stream_fence.empty() && c.stream_fence.count(st) == 0))) return false;
     if (p.n_tiles == 0) return few_waves && c.fused_gemv != 0 && p.n_wgs < GEMV_WIDE_MIN_ITEMS;
     return std::any_of(c.proj.begin(), c.proj.end(), [&](const lora_proj_t &pr) { return shrink_copies(&p, 1, pr.h_in) && !gemv_beside_tiles(c, &p, pr.h_in, pr.h_out); });
@@ -1409,7 +1410,6 @@ int lora_cache_create(const lora_cache_config_t *cfg, void *dev_pool, size_t dev
         fail(hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking));
         fail(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
         fail(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
-        fail(hipStreamCreateWithFlags(&c->upload_stream, hipStreamNonBlocking));
     }
     if (rc != LORA_OK) {
         lora_cache_destroy(c);
@@ -2538,7 +2538,8 @@ static int wait_for_inputs(lora_cache_t *c, lora_plan_t *p, hipStream_t st, bool
         capturing = is_capturing(st);
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         if (capturing && hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return LORA_E_HIP;
-        const hipError_t e = upload_lists(*c, *p, capturing ? c->upload_stream : st);
+        hipError_t e = capturing && !c->upload_stream ? hipStreamCreateWithFlags(&c->upload_stream, hipStreamNonBlocking) : hipSuccess;
+        if (e == hipSuccess) e = upload_lists(*c, *p, capturing ? c->upload_stream : st);
         if (capturing) (void)hipThreadExchangeStreamCaptureMode(&mode);
         HIP_TRY(e);
     }
