@@ -90,9 +90,9 @@ constexpr int64_t PINNED_LISTS_MAX_WAVES = 16384;
 // 838 to 846, on 28 (8400) 1466 and 1497 to 1556.
 constexpr int64_t PINNED_LISTS_MAX_TILES = 2048;
 // And of up to so many blocks where it runs as mfma_shrink_direct_kernel: each begins with a trip over the link, two stay on a compute unit and those behind them make it again.  us a pass uploaded and copied, idle and
-// beside copies: four prompts of 300 tokens 1024 wide, 681 blocks 23.4 and 20.5, 25.0 and 21.6; 908 blocks 24.2 and 23.1, 26.5 and 26.8; 1362 blocks 29.9 and 29.6, 31.8 and 34.4;
-// 3178 blocks 51.1 and 53.7, 52.6 and 59.9.  16 prompts of 60 tokens 2048 wide, 940 blocks 32.2 and 29.5, 34.1 and 31.7; 1128 blocks 33.1 and 32.6, 34.3 and 36.9.
-constexpr int64_t PINNED_LISTS_MAX_DIRECT = 960;
+// beside copies: four prompts of 300 tokens on three projections 1024 wide, 681 blocks, 23.4 and 20.5, 25.0 and 21.6; on six, 1362 blocks, 29.9 and 29.6, 31.8 and 34.4; on 14, 3178 blocks, 51.1 and 53.7, 52.6 and
+// 59.9; of 700 on two, 1052 blocks, 35.9 and 32.3, 35.7 and 32.3; of 1000 on two, 1496 blocks, 34.6 and 31.9, 34.0 and 37.1; on four, 2992 blocks, 48.9 and 54.1, 50.7 and 63.8.
+constexpr int64_t PINNED_LISTS_MAX_DIRECT = 1536;
 // Work of a batch's tile kernels (bytes of activations and outputs of the tile tokens) from which its GEMV launch goes to the side stream: fork and join cost
 // 10 to 25 us, and what there is to gain is the tails of the kernels, a percent of a millisecond.  us forked and on one stream: whole 7B layers of 500 adapters at 4.8 GB 1795 and 1813,
 // twice that 3507 and 3568, one layer (2.4 GB) 968 and 954; 13B with four prompts of 512 (1.6 GB) 876 and 797, with 5120 prompt tokens (4 GB) 1188 and 1200; 64 requests beside a prompt of
@@ -1069,14 +1069,18 @@ void forget_uses(lora_cache &c, lora_plan &p)
 }
 
 // Are a plan's lists left with the host until the first launch that works through them, which copies them (or is preceded by their upload, if it is a launch that cannot)?  Only where a call for
-// one of the cache's projections makes such a launch.  Not on a stream that no apply has run on when others have: whoever makes plans on a stream of their own wants the lists in the
+// one of the cache's projections, or a list of some, makes such a launch.  Not on a stream that no apply has run on when others have: whoever makes plans on a stream of their own wants the lists in the
 // pool by the time a call needs them.  And not over lists that calls without a fence, a graph's replays say, may still read: nothing but the order of `st` is known to keep from them.
 bool lists_travel(const lora_cache &c, const lora_plan &p, bool few_waves, hipStream_t st)
 {
     if (!c.fencing || !c.side_stream || p.bytes == 0 || p.unfenced) return false;
     if (!p.internal && (!another_free(c, p) || (!c.stream_fence.empty() && c.stream_fence.count(st) == 0))) return false;
     if (p.n_tiles == 0) return few_waves && c.fused_gemv != 0 && p.n_wgs < GEMV_WIDE_MIN_ITEMS;
-    return std::any_of(c.proj.begin(), c.proj.end(), [&](const lora_proj_t &pr) { return shrink_copies(&p, 1, pr.h_in) && !gemv_beside_tiles(c, &p, pr.h_in, pr.h_out); });
+    return std::any_of(c.proj.begin(), c.proj.end(), [&](const lora_proj_t &pr) {
+        for (int n = 1; n <= lora::BATCH_MAX_PROJS; n *= 2)  // (a list of several may shrink another way than a call for one)
+            if (shrink_copies(&p, n, n * pr.h_in) && !gemv_beside_tiles(c, &p, n * pr.h_in, n * pr.h_out)) return true;
+        return false;
+    });
 }
 
 // The upload of a plan's lists on `st`, behind what may still read those that lie there.
