@@ -43,10 +43,10 @@ WORKLOAD_TEXT = {
 # are carried here; the line names their source, and they are left out when a flag changes what a launch serves (the
 # number of layers and of activation sets among them: they decide how many projections a batch has).
 TRAFFIC_SOURCE = "profiles/kernel_traffic_all_workloads.txt"
-MEASURED_TRAFFIC = {("decode", "gemv_fused"): 378.9e6, ("decode_qkv", "gemv_fused"): 1115.9e6, ("prefill", "mfma_expand"): 872.9e6,
-                    ("prefill", "mfma_shrink"): 593.1e6, ("mixed", "gemv_fused"): 1402.4e6, ("mixed", "mfma_expand"): 7387.0e6,
-                    ("mixed", "mfma_shrink"): 3732.3e6, ("stress", "gemv_fused"): 2743.6e6, ("stress", "mfma_expand"): 1238.3e6,
-                    ("stress", "mfma_shrink"): 716.8e6}
+MEASURED_TRAFFIC = {("decode", "gemv_fused"): 378.8e6, ("decode_qkv", "gemv_fused"): 1115.9e6, ("prefill", "mfma_expand"): 872.9e6,
+                    ("prefill", "mfma_shrink"): 526.6e6, ("mixed", "gemv_fused"): 1402.4e6, ("mixed", "mfma_expand"): 7387.1e6,
+                    ("mixed", "mfma_shrink"): 2628.5e6, ("stress", "gemv_fused"): 2743.7e6, ("stress", "mfma_expand"): 1238.3e6,
+                    ("stress", "mfma_shrink"): 540.6e6}
 DEFAULT_LAYERS = {"decode": 32, "prefill": 8, "mixed": 2, "stress": 4, "decode_heavy": 8, "decode_paper": 32, "decode_qkv": 16}
 DEFAULT_STEPS = {"decode": 100, "prefill": 60, "mixed": 20, "stress": 20, "decode_heavy": 40, "decode_paper": 100, "decode_qkv": 100}
 

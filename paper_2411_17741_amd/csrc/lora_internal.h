@@ -461,7 +461,8 @@ inline __host__ __device__ constexpr int panel_projs(int runs, int rank_blocks) 
     return (PANEL_SLOT_ROWS - 64 * runs) / (16 * rank_blocks) >= 3 ? 3 : (PANEL_SLOT_ROWS - 64 * runs) / (16 * rank_blocks);
 }
 // Neighbouring panels, mostly of one slot, are dealt out two at a time, to run side by side on one XCD: the second finds part of the first's At in its L2 (eight prompts on q of eight layers fetch
-// 380 MB instead of 403, 192.6 -> 190.6 us a pass with the panel body's reads a step ahead; the 7B mixed batch 1675 -> 1667.5; four at a time 192.5 and 1672: some XCDs get more of the costly ones).
+// 380 MB instead of 403).  By themselves, one at a time -> two: four prompts of 1024 tokens of rank 128 on seven projections of two layers 4096 wide 382 -> 370 us a pass, 2048 wide 211 -> 203, 16 of 512 tokens 725 -> 712; 90
+// batches of prompts 1024 to 4096 wide 0.5 % in the mean, from 1.6 % worse to 5 % better.  (Four at a time: some XCDs get more of the costly ones.)
 constexpr int PANEL_DEAL = 2;
 struct PanelClasses {
     int32_t end[3];  // panels before end[c] take at most c + 1 projections per block

@@ -526,8 +526,8 @@ __device__ __forceinline__ void mfma_panel_body(const PanelArgs &a, const DevIte
     auto row_live = [&](int t) { return RB * STEP == 4 * TT || rb0 + STEP * t < 4 * TT; };  // (uniform)
     auto rank_live = [&](int q) { return NQ * 2 == NBT || HALF_ROWS || q0 + q < NBT; };
     // the operands of a stage's two k steps: those of one are read while the products of the one before run.  (All of a stage's reads first and its products behind them, the wavefronts being in
-    // step, left LDS and the matrix cores waiting for each other: 13B batch 836 -> 834 us, 7B mixed batch 1675 -> 1671.  It is little: a launch without any products takes 75 us where this
-    // one takes 76, see above.)
+    // step, leave LDS and the matrix cores waiting for each other, but what comes in bounds the launch, see above: 0.3 % of a pass over layers of rank 128 (16 prompts of 512 tokens 4096 wide 720 -> 712 us), nothing in the
+    // mean of 90 batches of prompts.)
     bf16x8 xo[2][RB], ao[2][NQ];
     auto read = [&](int slot, auto ks_tag) {
         constexpr int KS = decltype(ks_tag)::value;
